@@ -1165,16 +1165,16 @@ __global__ void k_number_rows(Engine e, uint32_t n_leaf, uint32_t n_cell) {
     if (e.node_of_row) e.node_of_row[i] = e.row_node[f];
   }
 }
-__global__ void k_translate_rows(Engine e, uint32_t n_cell, int has_head, int has_root) {
+__global__ void k_translate_rows(Engine e, const uint32_t* row_of, uint32_t n_cell, int has_head, int has_root) {
   const uint32_t n = n_cell > e.n_inst ? n_cell : e.n_inst;
   for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) {
     if (q < n_cell) {
-      e.q_l[q] = e.row_of[e.q_l[q]];
-      e.q_r[q] = e.row_of[e.q_r[q]];
+      e.q_l[q] = row_of[e.q_l[q]];
+      e.q_r[q] = row_of[e.q_r[q]];
     }
     if (q < e.n_inst) {
-      if (has_head) e.head_row[q] = e.row_of[e.head_row[q]];
-      if (has_root) e.root_ref[q] = e.row_of[e.root_ref[q]];
+      if (has_head) e.head_row[q] = row_of[e.head_row[q]];
+      if (has_root) e.root_ref[q] = row_of[e.root_ref[q]];
     }
   }
 }
@@ -1721,7 +1721,12 @@ void vec_number_rows(const Engine& e, uint32_t n_leaf, uint32_t n_cell, int has_
   const int g1 = (int)std::min<uint32_t>((n_leaf + n_cell + 255) / 256, 2048u);
   hipLaunchKernelGGL(k_number_rows, dim3(std::max(g1, 1)), dim3(256), 0, s, e, n_leaf, n_cell);
   const int g2 = (int)std::min<uint32_t>((std::max(n_cell, e.n_inst) + 255) / 256, 2048u);
-  hipLaunchKernelGGL(k_translate_rows, dim3(std::max(g2, 1)), dim3(256), 0, s, e, n_cell, has_head, has_root);
+  hipLaunchKernelGGL(k_translate_rows, dim3(std::max(g2, 1)), dim3(256), 0, s, e, e.row_of, n_cell, has_head, has_root);
+}
+// (the lanes' sort has numbered the rows already)
+void vec_translate_rows(const Engine& e, const uint32_t* row_of, uint32_t n_cell, int has_head, int has_root, hipStream_t s) {
+  const int g2 = (int)std::min<uint32_t>((std::max(n_cell, e.n_inst) + 255) / 256, 2048u);
+  hipLaunchKernelGGL(k_translate_rows, dim3(std::max(g2, 1)), dim3(256), 0, s, e, row_of, n_cell, has_head, has_root);
 }
 
 void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,

@@ -275,6 +275,41 @@ inline __device__ uint32_t wave_umax(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// ---- the depth-first lanes (lane_device.h) --------------------------------------------------------
+struct alignas(128) LaneCtl {   // zero on entry
+  uint32_t queues_done;         // queues whose instances are done
+  uint32_t status;              // 0, or -(tdf_status)
+  uint32_t log_used;            // log entries reserved by the waves (starts at the chunks dealt to them)
+  uint32_t n_seg;               // stack segments used (starts at the number of lanes, which have one each)
+  uint32_t leaf_next;           // rows given to leaves (after the run)
+};
+struct alignas(128) LaneQueue {
+  uint32_t head, tail;          // tickets of waves without work, calls (and pills) put in; read as one 8-byte word
+  uint32_t next_inst, inst_done;   // of the queue's instances: handed out, done
+  // counts of the queue's waves
+  uint32_t max_depth, max_level, max_iter, pad;
+  uint32_t n_leaf, n_cell, n_rec, n_private;   // n_rec: records used at once, n_private: frames on the lanes' stacks
+  unsigned long long n_tags, n_tokens;
+};
+struct LaneArgs {
+  LaneCtl* ctl;
+  uint4* segs;                  // segments of the lanes' stacks (lane_seg_units each)
+  LaneQueue* queues;            // [n_queues], zero on entry
+  struct LaneMail* mail;        // [n_queues][queue_cap] calls sent to other waves, every flag LANE_EMPTY on entry
+  struct LaneReply* reply;      // per wave 64 places for the values of calls it sent, flags 0 on entry
+  uint4* log;                   // schedule log: leaf {token, -, 0, instance}, cell {left, right, level, instance}; .z = LANE_LOG_HOLE: unused
+  uint32_t* row_of;             // by name (= place in the log): state row
+  uint32_t* row_node;           // by name (= place in the log): tree node whose loss term the row gets
+  const int32_t *left, *right, *token;
+  const long long* args;
+  long long* out_i64;
+  uint32_t *root_ref, *root_lvl, *head_row, *head_label;
+  uint32_t n_segs, n_queues, queue_cap, log_cap, n_inst, n_waves, per_grab;
+  int32_t n_tree_nodes, vocab, n_args;
+  long long idle_ticks;         // longest wait of an idle wave before it leaves (100 MHz ticks)
+  long long run_ticks;          // longest run before the machine gives up
+};
+
 // ---- vector side ----------------------------------------------------------------------
 struct VecArgs {
   int dtype;        // tdf_dtype

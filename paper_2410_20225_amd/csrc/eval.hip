@@ -11,6 +11,7 @@
 
 #include "die_sync.h"
 #include "engine.h"
+#include "lane_device.h"
 #include "tdf_internal.h"
 
 namespace tdf {
@@ -18,6 +19,7 @@ namespace tdf {
 void launch_seed(const DevProgram& P, const Engine& e, hipStream_t s);
 tdf_status launch_round(const DevProgram& P, const Engine& e, int cus, bool local, int small_block, int max_steps,
                         long long spin_ticks, const JitKernels& jit, hipStream_t s);
+tdf_status launch_lanes(const LaneArgs& a, int n_stored, const JitKernels& jit, hipStream_t s);
 int tag_machine_small_block(const DevProgram& P, bool jit);
 void launch_levels(const Engine& e, uint32_t n_cell, uint32_t n_keys, hipStream_t s);
 void launch_class_keys(const DevProgram& P, const Engine& e, uint32_t n_cell, uint32_t deep_level, uint32_t deep_base, hipStream_t s);
@@ -33,6 +35,9 @@ void vec_tail_fwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, 
 void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
                   uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, const uint32_t* root_rows,
                   hipStream_t s);
+void launch_lane_rows(const Engine& e, const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base, hipStream_t s);
+void launch_lane_place(const Engine& e, const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base, hipStream_t s);
+void vec_translate_rows(const Engine& e, const uint32_t* row_of, uint32_t n_cell, int has_head, int has_root, hipStream_t s);
 void vec_number_rows(const Engine& e, uint32_t n_leaf, uint32_t n_cell, int has_head, int has_root, hipStream_t s);
 void vec_head(const VecArgs& v, const Engine& e, const float* dy, int with_grad, int cls, hipStream_t s);
 void vec_node_loss(const VecArgs& v, const Engine& e, uint32_t n_leaf, uint32_t n_cell, const int32_t* node_label,
@@ -71,6 +76,9 @@ struct Plan {
   // embedding-gradient and bias-gradient scratch
   size_t off_tok_count, off_tok_fill, off_seg_off, off_chunk_off, off_sorted, off_de_part, off_db_part;
   uint32_t max_cells;
+  LaneArgs lanes{};          // n_waves 0: the evaluation keeps its frames and runs on the step machine
+  int n_stored = 0;
+  size_t base_total = 0;     // bytes without the lanes' part, which comes last
 };
 
 uint32_t pow2_at_least(uint64_t x) {
@@ -279,6 +287,50 @@ tdf_status make_plan(const Graph& G, const tdf_inputs* in, bool with_grad, char*
       v.dW_part = (float*)at(off_part);
     }
   }
+  P.base_total = L.total;
+  // ---- depth-first lanes: evaluations after which nobody reads the frames
+  P.n_stored = lane_stored(G.prog);
+  if (in->stats_level == 0 && in->step_limit == 0 && P.n_stored <= 8) {
+    LaneArgs& a = P.lanes;
+    // A wave per instance as far as they go, and a wave per 128 tags of the table asked for (a recursion of
+    // few instances fills the GPU once it has that many tags); no more than are resident together (two per SIMD
+    // by registers, and by LDS), which the others would only wait for.  A program in which a frame has one
+    // call at a time shares nothing between lanes: its lanes are filled, once every SIMD has a wave.
+    const uint32_t fits = 256u * std::min<uint32_t>(8u, (160u * 1024u) / (uint32_t)lane_lds_bytes(P.n_stored));
+    const bool branching = lane_branching(G.prog);
+    a.n_waves = branching ? std::max(B, T / 128u) : std::max(std::min(B, 1024u), B / 64u);
+    a.n_waves = std::max(1u, std::min(fits, a.n_waves));
+    if (const char* w = getenv("TDF_LANE_WAVES")) a.n_waves = (uint32_t)std::min(2048, std::max(1, atoi(w)));
+    a.per_grab = std::max(1u, std::min(64u, (B + a.n_waves - 1) / a.n_waves));
+    a.n_queues = 1;
+    while (a.n_queues < 64 && a.n_queues * 32 < a.n_waves) a.n_queues *= 2;
+    a.queue_cap = pow2_at_least(2ull * ((a.n_waves + a.n_queues - 1) / a.n_queues) + 64);
+    // stack segments: one per lane, and room for as many frames as there may be tags
+    a.n_segs = a.n_waves * 64u + T / LANE_SEG + 64u;
+    const size_t off_ctl = L.take(sizeof(LaneCtl) + sizeof(LaneQueue) * (size_t)a.n_queues), off_queues = off_ctl + sizeof(LaneCtl);   // read back together
+    const size_t off_mail = L.take(sizeof(LaneMail) * (size_t)a.queue_cap * a.n_queues);
+    const size_t off_reply = L.take(sizeof(LaneReply) * 64 * (size_t)a.n_waves);
+    const size_t off_segs = L.take((size_t)a.n_segs * lane_seg_units(P.n_stored) * 16);
+    a.ctl = (LaneCtl*)at(off_ctl);
+    a.queues = (LaneQueue*)at(off_queues);
+    a.mail = (LaneMail*)at(off_mail);
+    a.reply = (LaneReply*)at(off_reply);
+    a.segs = (uint4*)at(off_segs);
+    if (P.vec) {   // (a wave goes on to its next chunk when its lanes need more than is left: less than half is)
+      a.log_cap = 2 * T + LANE_CHUNK * (a.n_waves + 1);
+      const size_t off_log = L.take(sizeof(uint4) * (size_t)a.log_cap), off_names = L.take(4 * (size_t)a.log_cap);
+      const size_t off_marks = G.has_node_loss ? L.take(4 * (size_t)a.log_cap) : 0;
+      a.log = (uint4*)at(off_log);
+      a.row_of = (uint32_t*)at(off_names);
+      a.row_node = G.has_node_loss ? (uint32_t*)at(off_marks) : nullptr;
+    }
+    a.left = e.left; a.right = e.right; a.token = e.token;
+    a.args = e.args; a.n_args = e.n_args;
+    a.root_ref = e.root_ref; a.root_lvl = e.root_lvl; a.head_row = e.head_row; a.head_label = e.head_label;
+    a.n_inst = B;
+    a.n_tree_nodes = e.n_tree_nodes;
+    a.vocab = e.vocab;
+  }
   return TDF_OK;
 }
 
@@ -309,7 +361,8 @@ tdf_status status_from_device(uint32_t st) {
 // Layout of tdf_graph::pinned: control blocks, barrier records, firing tables, firing counts, then level offsets.
 constexpr size_t PIN_CTRL = 0, PIN_SYNC = PIN_CTRL + sizeof(Ctrl) * 8, PIN_PROG = PIN_SYNC + sizeof(DieSync) * 16,
                  PIN_FIRE = (PIN_PROG + sizeof(DevProgram) + 255) / 256 * 256,
-                 PIN_LEVELS = PIN_FIRE + sizeof(unsigned long long) * (TDF_STATS_MAX_COUNTS + 2);
+                 PIN_LANES = (PIN_FIRE + sizeof(unsigned long long) * (TDF_STATS_MAX_COUNTS + 2) + 255) / 256 * 256,
+                 PIN_LEVELS = PIN_LANES + sizeof(LaneCtl) + sizeof(LaneQueue) * 64;
 // Makes the graph's pinned buffer at least PIN_LEVELS + level_bytes large (contents are lost when it grows).
 tdf_status pinned_reserve(tdf_graph* gr, size_t level_bytes) {
   const size_t need = PIN_LEVELS + level_bytes;
@@ -347,7 +400,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   Plan P;
   tdf_status st = make_plan(G, in, with_grad, (char*)workspace, P, 8);   // the largest layout
   if (st != TDF_OK) return st;
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < P.L.total) {
+  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < P.base_total) {
     set_error("workspace is NULL, misaligned or smaller than tdf_workspace_size");
     return TDF_ERR_WORKSPACE;
   }
@@ -412,6 +465,13 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     std::string log;
     if (!jit_compile(G.prog, gr->jit, log) && getenv("TDF_JIT_VERBOSE")) fprintf(stderr, "tdf: no generated kernels: %s\n", log.c_str());
   }
+  bool use_lanes = P.lanes.n_waves > 0 && workspace_bytes >= P.L.total && gr->lanes_ok && gr->die_local && !getenv("TDF_NO_LANES");
+  if (use_lanes && !gr->jit.lanes_tried && !no_alloc) {
+    gr->jit.lanes_tried = true;
+    std::string log;
+    if (!jit_compile_lanes(G.prog, gr->jit, log) && getenv("TDF_JIT_VERBOSE")) fprintf(stderr, "tdf: no generated lanes: %s\n", log.c_str());
+  }
+  use_lanes = use_lanes && gr->jit.lanes;
   const bool use_jit = gr->jit.step && gr->jit.small && gr->jit.step_local;
   int small_block = tag_machine_small_block(G.prog, use_jit);
   // A batch of few instances (deep ones, or it would not be worth a GPU) has narrow steps: half the lanes
@@ -446,7 +506,41 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     w_packed = true;
   }
   begin(TDF_PHASE_TAGS);
-  for (;;) {
+  LaneCtl lc{};
+  if (use_lanes) {
+    LaneArgs& a = P.lanes;
+    a.out_i64 = e.out_i64;
+    a.idle_ticks = spin_ticks;
+    a.run_ticks = 2 * spin_ticks;   // (then it is the step machine's)
+    if (P.vec) HIP_TRY(hipMemsetAsync(base + P.L.zero_begin, 0, P.L.zero_end - P.L.zero_begin, s));
+    if (tdf_status ls = launch_lanes(a, P.n_stored, gr->jit, s); ls != TDF_OK) return ls;
+    LaneCtl* pl = (LaneCtl*)((char*)gr->pinned + PIN_LANES);
+    HIP_TRY(hipMemcpyAsync(pl, a.ctl, sizeof(LaneCtl) + sizeof(LaneQueue) * a.n_queues, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    lc = *pl;
+    if (lc.status != 0) {   // left to the step machine, which also says what is wrong if something is
+      if (status_is(lc.status, TDF_ERR_UNSUPPORTED)) gr->lanes_ok = false;
+      use_lanes = false;
+      ++repeats;
+    } else {
+      const LaneQueue* pq = (const LaneQueue*)(pl + 1);
+      unsigned long long frames = 0;
+      for (uint32_t k = 0; k < a.n_queues; ++k) {
+        const LaneQueue& q = pq[k];
+        hc.n_leaf += q.n_leaf; hc.n_cell += q.n_cell;
+        hc.n_tags += q.n_tags; hc.n_tokens += q.n_tokens;
+        frames += (unsigned long long)q.n_rec + q.n_private;
+        hc.step = std::max(hc.step, q.max_iter);
+        hc.max_depth = std::max(hc.max_depth, q.max_depth);
+        hc.max_level = std::max(hc.max_level, q.max_level);
+      }
+      hc.n_alloc = (uint32_t)std::min<unsigned long long>(hc.n_tags, frames);
+      hc.done = 1;
+      // (programs with vector operators: max_tags bounds all tags, and there is a row for each)
+      if (!e.reclaim && hc.n_tags > (unsigned long long)e.max_tags) hc.status = (uint32_t)(-TDF_ERR_TABLE_FULL);
+    }
+  }
+  for (; !use_lanes;) {
     // several machines only where each keeps to its own die; the device-scope kernel runs one
     const uint32_t want_dies = gr->die_local ? gr->max_dies : 1;
     if (dies_for(e.n_inst, want_dies) != e.n_dies) {
@@ -520,7 +614,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (!hc.status) launch_merge_logs(e, leaf_off, cell_off, s);
     break;
   }
-  end(TDF_PHASE_TAGS, 2 + 2ll * rounds);
+  end(TDF_PHASE_TAGS, 2 + 2ll * rounds);   // (the lanes: their initialisation and themselves)
   if (!hc.status && P.vec && with_grad && hc.n_cell > P.max_cells) hc.status = (uint32_t)(-TDF_ERR_TABLE_FULL);
   tdf_status dev = status_from_device(hc.status);
 
@@ -540,10 +634,22 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (no_alloc) locks.data.lock();
     else locks.control.unlock();
     auto enter_data_stage = [&]() { if (!locks.data.owns_lock()) locks.data.lock(); };
+    const uint32_t n_log = std::min(lc.log_used, P.lanes.log_cap);
     e.row0 = hc.n_leaf;   // leaf i has row i, the cell at position q of the sorted log row n_leaf + q
     hipStream_t s2 = (hipStream_t)gr->side_stream, s3 = (hipStream_t)gr->sort_stream;
     auto begin2 = [&](int ph) { if (timed) { (void)hipEventRecord((hipEvent_t)gr->events[2 * ph], s2); phase_used[ph] = true; } };
     auto end2 = [&](int ph, int64_t n) { if (timed) (void)hipEventRecord((hipEvent_t)gr->events[2 * ph + 1], s2); launches[ph] += n; };
+    // Instances never exchange values, so instances whose recursion is deep (long chains: many
+    // levels of a few cells each, bound by latency) can run beside the others (few levels of many
+    // cells each, bound by throughput) instead of after them.  An instance is deep if its root's
+    // level is at least deep_level; its cells get sort keys behind all keys of the shallow ones.
+    uint32_t deep_level = 32;
+    if (const char* w = getenv("TDF_DEEP_LEVEL")) deep_level = (uint32_t)std::max(0, atoi(w));
+    const bool want_deep = with_grad && s2 && gr->die_local && !G.has_node_loss && deep_level > 0 && hc.max_level >= deep_level &&
+                           hc.n_cell > 0;
+    deep_base = want_deep ? deep_level * LEVEL_KEY_DIES : 0;
+    const uint32_t n_keys = hc.n_cell ? deep_base + (hc.max_level + 2) * LEVEL_KEY_DIES : 0;
+    if (use_lanes) launch_lane_rows(e, P.lanes, n_log, n_keys, want_deep ? deep_level : 0, deep_base, s);   // the leaves' rows, and the counts
     begin(TDF_PHASE_LEAVES);
     if (G.cell_kind && !w_packed) vec_pack_w(v, s);   // (a program of EMBEDs alone has no W: the pointers may be NULL)
     if (!with_grad) vec_embed(v, e, hc.n_leaf, s);
@@ -567,22 +673,17 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       HIP_TRY(hipEventRecord((hipEvent_t)gr->join_sort, s3));
       return TDF_OK;
     };
-    // Instances never exchange values, so instances whose recursion is deep (long chains: many
-    // levels of a few cells each, bound by latency) can run beside the others (few levels of many
-    // cells each, bound by throughput) instead of after them.  An instance is deep if its root's
-    // level is at least deep_level; its cells get sort keys behind all keys of the shallow ones.
-    uint32_t deep_level = 32;
-    if (const char* w = getenv("TDF_DEEP_LEVEL")) deep_level = (uint32_t)std::max(0, atoi(w));
-    const bool want_deep = with_grad && s2 && gr->die_local && !G.has_node_loss && deep_level > 0 && hc.max_level >= deep_level &&
-                           hc.n_cell > 0;
     const int deep_wgs = getenv("TDF_DEEP_WGS") ? std::max(1, atoi(getenv("TDF_DEEP_WGS"))) : 16;   // workgroups per die
     if (hc.n_cell) {
       begin(TDF_PHASE_LEVELS);
-      deep_base = want_deep ? deep_level * LEVEL_KEY_DIES : 0;
-      const uint32_t n_keys = deep_base + (hc.max_level + 2) * LEVEL_KEY_DIES;
-      if (want_deep) launch_class_keys(G.prog, e, hc.n_cell, deep_level, deep_base, s);
-      launch_levels(e, hc.n_cell, n_keys, s);
-      vec_number_rows(e, hc.n_leaf, hc.n_cell, G.has_head, G.out_type == T_VEC, s);
+      if (use_lanes) {
+        launch_lane_place(e, P.lanes, n_log, n_keys, want_deep ? deep_level : 0, deep_base, s);
+        vec_translate_rows(e, P.lanes.row_of, hc.n_cell, G.has_head, G.out_type == T_VEC, s);
+      } else {
+        if (want_deep) launch_class_keys(G.prog, e, hc.n_cell, deep_level, deep_base, s);
+        launch_levels(e, hc.n_cell, n_keys, s);
+        vec_number_rows(e, hc.n_leaf, hc.n_cell, G.has_head, G.out_type == T_VEC, s);
+      }
       const size_t level_bytes = (size_t)n_keys * sizeof(uint32_t);
       if (no_alloc && gr->pinned_bytes < PIN_LEVELS + level_bytes) {
         set_error("more dependency levels than the prepared graph's host buffer holds");
@@ -659,7 +760,8 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (!hc.n_cell) {   // leaves only
       if (tdf_status ts_ = token_sort(); ts_ != TDF_OK) return ts_;
       enter_data_stage();
-      vec_number_rows(e, hc.n_leaf, 0, G.has_head, G.out_type == T_VEC, s);
+      if (use_lanes) vec_translate_rows(e, P.lanes.row_of, 0, G.has_head, G.out_type == T_VEC, s);
+      else vec_number_rows(e, hc.n_leaf, 0, G.has_head, G.out_type == T_VEC, s);
       if (with_grad) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)gr->leaves_done, 0));
     }
     begin(TDF_PHASE_HEAD);
@@ -779,14 +881,14 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     }
     stats->n_machines = (int32_t)e.n_dies;
     stats->die_local = gr->die_local ? 1 : 0;
-    stats->generated = use_jit ? 1 : 0;
+    stats->generated = use_jit || use_lanes ? 1 : 0;
     stats->repeats = (int32_t)repeats + inherited_repeats;
     stats->tail_used = use_tail || deep ? 1 : 0;
     stats->deep_split = deep ? (deep_beside ? 2 : 1) : 0;
     stats->max_tag_depth = hc.max_depth;
     stats->table_capacity = e.cap;
     stats->peak_frames = (int64_t)hc.n_alloc;
-    stats->frames_reclaimed = e.reclaim ? 1 : 0;
+    stats->frames_reclaimed = e.reclaim || use_lanes ? 1 : 0;
     stats->max_probe = hc.n_tags > e.n_inst ? 1 : 0;   // the match table is addressed without collisions
     for (int ph = 0; ph < TDF_PHASE_COUNT; ++ph) {
       float ms = 0.f;
@@ -933,6 +1035,11 @@ extern "C" tdf_status tdf_graph_prepare(tdf_graph* g) {
     std::string log;
     (void)jit_compile(g->g.prog, g->jit, log);   // without the run-time compiler the table interpreter runs
   }
+  if (!g->jit.lanes_tried) {
+    g->jit.lanes_tried = true;
+    std::string log;
+    (void)jit_compile_lanes(g->g.prog, g->jit, log);
+  }
   g->prepared = true;
   g->prepared_device = dev;
   return TDF_OK;
@@ -960,8 +1067,8 @@ extern "C" tdf_status tdf_eval_static(tdf_graph* g, const tdf_inputs* in, tdf_ou
   Plan P;
   tdf_status st = make_plan(g->g, in, false, nullptr, P, 8);
   if (st != TDF_OK) return st;
-  if (P.L.total > TDF_STATIC_WORKSPACE_BYTES) {
-    set_error("tdf_eval_static: these inputs need " + std::to_string(P.L.total) + " bytes of workspace, the static one has " +
+  if (P.base_total > TDF_STATIC_WORKSPACE_BYTES) {
+    set_error("tdf_eval_static: these inputs need " + std::to_string(P.base_total) + " bytes of workspace, the static one has " +
               std::to_string((size_t)TDF_STATIC_WORKSPACE_BYTES) + " (lower max_tags, or use tdf_eval with a workspace of your own)");
     return TDF_ERR_WORKSPACE;
   }

@@ -9,6 +9,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <sstream>
@@ -70,6 +71,96 @@ struct Gen {
   static std::string pre(const Instr& I, int k) { return I.src[k] == SRC_IMM ? "true" : "p" + std::to_string(I.src[k]); }
   static std::string ded(const Instr& I, int k) { return I.src[k] == SRC_IMM ? "false" : "d" + std::to_string(I.src[k]); }
 
+  // One entry without tokens, in a block of its own for the lanes (lane: helpers ln_*, else sw_*).
+  void entry(const Instr& I, bool lane) {
+    const std::string D = std::to_string(I.dst), h = lane ? "ln_" : "sw_";
+    if (lane) o << "        {\n";
+    switch (I.op) {
+      case D_IN:
+        o << "          p" << D << " = on && ((x.present >> " << (int)I.aux << ") & 1); v" << D << " = x.sv[" << (int)I.aux
+          << "]; live = p" << D << "; all_in = all_in && p" << D << ";\n";
+        break;
+      case D_RET: {
+        std::string all_p = "true", any_d = "false";
+        bool any_arg = false;
+        for (int k = 0; k < 4; ++k) {
+          if (I.src[k] == SRC_NONE) continue;
+          any_arg = true;
+          all_p += " && p" + std::to_string(I.src[k]);
+          any_d += " || d" + std::to_string(I.src[k]);
+        }
+        o << "          const bool p = on && ((x.present >> " << (int)I.aux << ") & 1);\n";
+        o << "          const bool is_dead = on && !p && " << (any_arg ? "true" : "false") << " && (" << all_p << ") && (" << any_d
+          << ");\n";
+        o << "          v" << D << " = x.sv[" << (int)I.aux << "]; p" << D << " = p || is_dead; d" << D << " = is_dead; live = p;\n";
+        o << "          all_in = all_in && p" << D << ";\n";
+        break;
+      }
+      case D_ADD: case D_SUB: case D_MUL: case D_EQ: case D_LT: {
+        const std::string a = val(I, 0), b = val(I, 1);
+        o << "          const bool p = on && " << pre(I, 0) << " && " << pre(I, 1) << "; const bool d = " << ded(I, 0) << " || "
+          << ded(I, 1) << ";\n";
+        if (I.op == D_ADD) o << "          v" << D << " = (long long)((unsigned long long)" << a << " + (unsigned long long)" << b << ");\n";
+        if (I.op == D_SUB) o << "          v" << D << " = (long long)((unsigned long long)" << a << " - (unsigned long long)" << b << ");\n";
+        if (I.op == D_MUL) o << "          v" << D << " = (long long)((unsigned long long)" << a << " * (unsigned long long)" << b << ");\n";
+        if (I.op == D_EQ) o << "          v" << D << " = " << a << " == " << b << ";\n";
+        if (I.op == D_LT) o << "          v" << D << " = " << a << " < " << b << ";\n";
+        o << "          p" << D << " = p; d" << D << " = p && d; live = p && !d;\n";
+        break;
+      }
+      case D_ID:
+        o << "          v" << D << " = " << val(I, 0) << "; p" << D << " = on && " << pre(I, 0) << "; d" << D << " = p" << D << " && "
+          << ded(I, 0) << "; live = p" << D << " && !d" << D << ";\n";
+        break;
+      case D_ISLEAF: case D_LEFT: case D_RIGHT: case D_TOKEN:
+        o << "          const bool p = on && " << pre(I, 0) << "; bool d = " << ded(I, 0) << "; long long r = 0;\n";
+        o << "          if (p && !d) r = " << h << "tree(x, " << val(I, 0) << ", " << (I.op - D_ISLEAF) << ", d);\n";
+        o << "          v" << D << " = r; p" << D << " = p; d" << D << " = p && d; live = p && !d;\n";
+        break;
+      case D_CE_NODE:
+        o << "          const bool p = on && " << pre(I, 0) << " && " << pre(I, 1) << "; bool d = " << ded(I, 0) << " || " << ded(I, 1)
+          << ";\n";
+        o << "          if (p && !d) " << h << "ce_node(x, " << val(I, 0) << ", " << val(I, 1) << ", d);\n";
+        o << "          v" << D << " = " << val(I, 0) << "; p" << D << " = p; d" << D << " = p && d; live = p && !d;\n";
+        break;
+      case D_SWITCH: {
+        const std::string D1 = std::to_string(I.dst + 1);
+        o << "          const bool p = on && " << pre(I, 0) << " && " << pre(I, 1) << "; const bool d = " << ded(I, 0) << " || "
+          << ded(I, 1) << "; const bool t = " << val(I, 0) << " != 0;\n";
+        o << "          v" << D << " = " << val(I, 1) << "; p" << D << " = p; d" << D << " = p && (d || !t);\n";
+        o << "          v" << D1 << " = " << val(I, 1) << "; p" << D1 << " = p; d" << D1 << " = p && (d || t);\n";
+        o << "          live = p && !d;\n";
+        break;
+      }
+      case D_MERGE: {
+        o << "          bool any_live = false, all_p = true; long long r = 0;\n";
+        for (int k = 0; k < 4; ++k) {
+          if (I.src[k] == SRC_NONE) continue;
+          o << "          if (" << pre(I, k) << " && !" << ded(I, k) << " && !any_live) { any_live = true; r = " << val(I, k) << "; }\n";
+          o << "          all_p = all_p && " << pre(I, k) << ";\n";
+        }
+        o << "          const bool p = on && (any_live || all_p);\n";
+        o << "          v" << D << " = r; p" << D << " = p; d" << D << " = p && !any_live; live = on && any_live;\n";
+        break;
+      }
+      case D_EMBED:
+        o << "          " << h << "embed(x, on, " << (int)I.aux << ", " << (lane ? "" : "x.sv[" + std::to_string(I.aux) + "], ") << pre(I, 0) << ", "
+          << ded(I, 0) << ", " << val(I, 0) << ", v" << D << ", p" << D << ", live);\n";
+        break;
+      case D_CELL:
+        o << "          " << h << "cell(x, on, " << (int)I.aux << ", " << (lane ? "" : "x.sv[" + std::to_string(I.aux) + "], ") << pre(I, 0) << ", "
+          << ded(I, 0) << ", " << val(I, 0) << ", " << pre(I, 1) << ", " << ded(I, 1) << ", " << val(I, 1) << ", v" << D << ", p" << D
+          << ", live);\n";
+        break;
+      case D_HEAD:
+        o << "          " << h << "head(x, on, " << (int)I.aux << ", " << pre(I, 0) << ", " << ded(I, 0) << ", " << val(I, 0) << ", " << pre(I, 1)
+          << ", " << ded(I, 1) << ", " << val(I, 1) << ", v" << D << ", p" << D << ", live);\n";
+        break;
+      default: break;
+    }
+    if (lane) o << "        }\n";
+  }
+
   void function(int f) {
     const DevFn& fn = P.fn[f];
     o << "    {  // function " << f << "\n";
@@ -81,76 +172,8 @@ struct Gen {
     for (int ip = 0; ip < fn.count; ++ip) {
       const Instr& I = P.instr[fn.first + ip];
       const std::string bit = "(1ull << " + std::to_string(ip) + ")";
-      const std::string D = std::to_string(I.dst);
       o << "        {  // entry " << ip << " op " << (int)I.op << "\n";
       switch (I.op) {
-        case D_IN:
-          o << "          p" << D << " = on && ((x.present >> " << (int)I.aux << ") & 1); v" << D << " = x.sv[" << (int)I.aux
-            << "]; live = p" << D << "; all_in = all_in && p" << D << ";\n";
-          break;
-        case D_RET: {
-          std::string all_p = "true", any_d = "false";
-          bool any_arg = false;
-          for (int k = 0; k < 4; ++k) {
-            if (I.src[k] == SRC_NONE) continue;
-            any_arg = true;
-            all_p += " && p" + std::to_string(I.src[k]);
-            any_d += " || d" + std::to_string(I.src[k]);
-          }
-          o << "          const bool p = on && ((x.present >> " << (int)I.aux << ") & 1);\n";
-          o << "          const bool is_dead = on && !p && " << (any_arg ? "true" : "false") << " && (" << all_p << ") && (" << any_d
-            << ");\n";
-          o << "          v" << D << " = x.sv[" << (int)I.aux << "]; p" << D << " = p || is_dead; d" << D << " = is_dead; live = p;\n";
-          o << "          all_in = all_in && p" << D << ";\n";
-          break;
-        }
-        case D_ADD: case D_SUB: case D_MUL: case D_EQ: case D_LT: {
-          const std::string a = val(I, 0), b = val(I, 1);
-          o << "          const bool p = on && " << pre(I, 0) << " && " << pre(I, 1) << "; const bool d = " << ded(I, 0) << " || "
-            << ded(I, 1) << ";\n";
-          if (I.op == D_ADD) o << "          v" << D << " = (long long)((unsigned long long)" << a << " + (unsigned long long)" << b << ");\n";
-          if (I.op == D_SUB) o << "          v" << D << " = (long long)((unsigned long long)" << a << " - (unsigned long long)" << b << ");\n";
-          if (I.op == D_MUL) o << "          v" << D << " = (long long)((unsigned long long)" << a << " * (unsigned long long)" << b << ");\n";
-          if (I.op == D_EQ) o << "          v" << D << " = " << a << " == " << b << ";\n";
-          if (I.op == D_LT) o << "          v" << D << " = " << a << " < " << b << ";\n";
-          o << "          p" << D << " = p; d" << D << " = p && d; live = p && !d;\n";
-          break;
-        }
-        case D_ID:
-          o << "          v" << D << " = " << val(I, 0) << "; p" << D << " = on && " << pre(I, 0) << "; d" << D << " = p" << D << " && "
-            << ded(I, 0) << "; live = p" << D << " && !d" << D << ";\n";
-          break;
-        case D_ISLEAF: case D_LEFT: case D_RIGHT: case D_TOKEN:
-          o << "          const bool p = on && " << pre(I, 0) << "; bool d = " << ded(I, 0) << "; long long r = 0;\n";
-          o << "          if (p && !d) r = sw_tree(x, " << val(I, 0) << ", " << (I.op - D_ISLEAF) << ", d);\n";
-          o << "          v" << D << " = r; p" << D << " = p; d" << D << " = p && d; live = p && !d;\n";
-          break;
-        case D_CE_NODE:
-          o << "          const bool p = on && " << pre(I, 0) << " && " << pre(I, 1) << "; bool d = " << ded(I, 0) << " || " << ded(I, 1)
-            << ";\n";
-          o << "          if (p && !d) sw_ce_node(x, " << val(I, 0) << ", " << val(I, 1) << ", d);\n";
-          o << "          v" << D << " = " << val(I, 0) << "; p" << D << " = p; d" << D << " = p && d; live = p && !d;\n";
-          break;
-        case D_SWITCH: {
-          const std::string D1 = std::to_string(I.dst + 1);
-          o << "          const bool p = on && " << pre(I, 0) << " && " << pre(I, 1) << "; const bool d = " << ded(I, 0) << " || "
-            << ded(I, 1) << "; const bool t = " << val(I, 0) << " != 0;\n";
-          o << "          v" << D << " = " << val(I, 1) << "; p" << D << " = p; d" << D << " = p && (d || !t);\n";
-          o << "          v" << D1 << " = " << val(I, 1) << "; p" << D1 << " = p; d" << D1 << " = p && (d || t);\n";
-          o << "          live = p && !d;\n";
-          break;
-        }
-        case D_MERGE: {
-          o << "          bool any_live = false, all_p = true; long long r = 0;\n";
-          for (int k = 0; k < 4; ++k) {
-            if (I.src[k] == SRC_NONE) continue;
-            o << "          if (" << pre(I, k) << " && !" << ded(I, k) << " && !any_live) { any_live = true; r = " << val(I, k) << "; }\n";
-            o << "          all_p = all_p && " << pre(I, k) << ";\n";
-          }
-          o << "          const bool p = on && (any_live || all_p);\n";
-          o << "          v" << D << " = r; p" << D << " = p; d" << D << " = p && !any_live; live = on && any_live;\n";
-          break;
-        }
         case D_CALL:
           o << "          sw_emit(x, on && " << pre(I, 0) << " && !" << ded(I, 0) << " && !(x.fired & " << bit << "), "
             << (0x80000000u | I.aux | ((uint32_t)I.aux2 << 8)) << "u, " << val(I, 0) << ");\n";
@@ -167,25 +190,649 @@ struct Gen {
           else o << "          sw_emit(x, go, 0u, " << val(I, 0) << ");\n";
           o << "          live = on && " << pre(I, 0) << " && !" << ded(I, 0) << ";\n";
           break;
-        case D_EMBED:
-          o << "          sw_embed(x, on, " << (int)I.aux << ", x.sv[" << (int)I.aux << "], " << pre(I, 0) << ", " << ded(I, 0) << ", "
-            << val(I, 0) << ", v" << D << ", p" << D << ", live);\n";
-          break;
-        case D_CELL:
-          o << "          sw_cell(x, on, " << (int)I.aux << ", x.sv[" << (int)I.aux << "], " << pre(I, 0) << ", " << ded(I, 0) << ", "
-            << val(I, 0) << ", " << pre(I, 1) << ", " << ded(I, 1) << ", " << val(I, 1) << ", v" << D << ", p" << D << ", live);\n";
-          break;
-        case D_HEAD:
-          o << "          sw_head(x, on, " << (int)I.aux << ", " << pre(I, 0) << ", " << ded(I, 0) << ", " << val(I, 0) << ", " << pre(I, 1)
-            << ", " << ded(I, 1) << ", " << val(I, 1) << ", v" << D << ", p" << D << ", live);\n";
-          break;
-        default: break;
+        default: entry(I, false); break;
       }
       o << "          if (live) x.fired |= " << bit << ";\n";
       o << "        }\n";
     }
     o << "        if (on) x.complete = all_in;\n";
     o << "      }\n    }\n";
+  }
+
+  // ---- the same tables for the depth-first lanes (lane_device.h) -------------------------------------
+  // A lane's frame is in a state (function, calls opened, of these still outstanding), and a sweep ends
+  // with the one thing the lane does next: a call all of whose arguments are live, the next iteration, the
+  // return of a complete frame, or waiting.  What is present, and much of what is live, is known from the
+  // state: the arguments of an opened call were live, so the Switches on their way went that side.  Every
+  // reachable state gets code of its own with these facts folded in (fib's first sweep is a comparison,
+  // its last one an addition); a lane whose sweep is a few instructions is what the machine's speed is.
+  // States beyond MAX_STATES (functions with many calls, several of them outstanding) run the generic code
+  // of their function, which keeps the present and opened sets in registers.
+  static constexpr int MAX_STATES = 24;
+  struct State { int f; uint32_t mask, out; };
+  std::vector<State> states;
+  struct B {                      // a truth value: constant 0 / 1, or an expression
+    int k;
+    std::string e;
+  };
+  static B bc(bool v) { return B{v ? 1 : 0, v ? "true" : "false"}; }
+  static B bx(const std::string& e) { return B{2, e}; }
+  static B band(const B& a, const B& b) {
+    if (a.k == 0 || b.k == 0) return bc(false);
+    if (a.k == 1) return b;
+    if (b.k == 1) return a;
+    return bx("(" + a.e + " && " + b.e + ")");
+  }
+  static B bnot(const B& a) { return a.k == 2 ? bx("!" + a.e) : bc(!a.k); }
+  static B bor(const B& a, const B& b) {
+    if (a.k == 1 || b.k == 1) return bc(true);
+    if (a.k == 0) return b;
+    if (b.k == 0) return a;
+    return bx("(" + a.e + " || " + b.e + ")");
+  }
+  // What a state says about the values of its function.
+  struct Facts {
+    std::vector<int> live, truth;   // -1 unknown; live 1: present and not dead; truth of a predicate
+    std::vector<int> def;           // instruction that makes the value
+  };
+  const Instr& at(int f, int ip) const { return P.instr[P.fn[f].first + ip]; }
+  static bool has_value(uint8_t op) { return op != D_CALL && op != D_NEXT && op != D_OUT; }
+  void mark_live(int f, Facts& F, int v) const {
+    if (v >= SRC_NONE || F.live[v] == 1) return;
+    F.live[v] = 1;
+    const Instr& I = at(f, F.def[v]);
+    switch (I.op) {
+      case D_SWITCH:
+        if (I.src[0] < SRC_NONE) F.truth[I.src[0]] = v == I.dst ? 1 : 0;
+        mark_live(f, F, I.src[0]);
+        mark_live(f, F, I.src[1]);
+        break;
+      case D_ADD: case D_SUB: case D_MUL: case D_EQ: case D_LT: case D_CE_NODE: case D_CELL: case D_HEAD:
+        mark_live(f, F, I.src[0]);
+        mark_live(f, F, I.src[1]);
+        break;
+      case D_ID: case D_ISLEAF: case D_LEFT: case D_RIGHT: case D_TOKEN: case D_EMBED:
+        mark_live(f, F, I.src[0]);
+        break;
+      default: break;
+    }
+  }
+  Facts facts(int f, uint32_t mask) const {
+    Facts F;
+    F.live.assign(MAX_VALUES + 2, -1);
+    F.truth.assign(MAX_VALUES + 2, -1);
+    F.def.assign(MAX_VALUES + 2, 0);
+    for (int ip = 0; ip < P.fn[f].count; ++ip) {
+      const Instr& I = at(f, ip);
+      if (!has_value(I.op)) continue;
+      F.def[I.dst] = ip;
+      if (I.op == D_SWITCH) F.def[I.dst + 1] = ip;
+    }
+    for (int ip = 0; ip < P.fn[f].count; ++ip) {
+      const Instr& I = at(f, ip);
+      if (I.op == D_IN) F.live[I.dst] = 1;
+      if (I.op == D_CALL && ((mask >> P.label_site[I.aux]) & 1)) mark_live(f, F, I.src[0]);
+    }
+    // forward: what is made of live values, and the side of a Switch that its known predicate names
+    for (int ip = 0; ip < P.fn[f].count; ++ip) {
+      const Instr& I = at(f, ip);
+      auto lv = [&](int k) { return I.src[k] == SRC_IMM || (I.src[k] != SRC_NONE && F.live[I.src[k]] == 1); };
+      switch (I.op) {
+        case D_ADD: case D_SUB: case D_MUL: case D_EQ: case D_LT: if (lv(0) && lv(1)) F.live[I.dst] = 1; break;
+        case D_ID: case D_ISLEAF: case D_LEFT: case D_RIGHT: case D_TOKEN: if (lv(0)) F.live[I.dst] = 1; break;
+        case D_SWITCH:
+          if (lv(1) && I.src[0] < SRC_NONE && F.truth[I.src[0]] >= 0) F.live[F.truth[I.src[0]] ? I.dst : I.dst + 1] = 1;
+          break;
+        default: break;
+      }
+    }
+    return F;
+  }
+  struct Site { int label; std::vector<const Instr*> args; };   // label -1: the next iteration
+  std::vector<Site> sites(int f) const {
+    std::vector<Site> r;
+    for (int ip = 0; ip < P.fn[f].count; ++ip) {
+      const Instr& I = at(f, ip);
+      if (I.op != D_CALL && I.op != D_NEXT) continue;
+      const int label = I.op == D_CALL ? (int)I.aux : -1;
+      size_t k = 0;
+      while (k < r.size() && r[k].label != label) ++k;
+      if (k == r.size()) r.push_back({label, {}});
+      r[k].args.push_back(&I);
+    }
+    return r;
+  }
+  bool has_state(int f, uint32_t mask, uint32_t out) const {
+    for (const State& t : states)
+      if (t.f == f && t.mask == mask && t.out == out) return true;
+    return false;
+  }
+  // A state's number says what it is (LANE_ST in lane_device.h)
+  static uint32_t state_code_of(int f, uint32_t mask, uint32_t out) { return (uint32_t)f | mask << 3 | out << 11; }
+  // A value of the state's code: name, present, dead.
+  struct Val { std::string v; B p, d; };
+  // (the result of a call that was not opened is there only as a dead value: never live)
+  static B live_of(const Val& a) { return a.p.k == 2 && a.p.e == a.d.e ? bc(false) : band(a.p, bnot(a.d)); }
+
+  // A call that waits while another one runs: an argument that came from the forest is kept where its result
+  // will be, so that it need not be read again.  The slot for value `v` in a state, or -1.
+  int memo_slot(int f, uint32_t mask, int v) const {
+    if (mask == 0) return -1;
+    for (const Site& t : sites(f))
+      if (t.label >= 0 && !((mask >> P.label_site[t.label]) & 1) && t.args.size() == 1 && t.args[0]->src[0] == v) return P.label_ret_slot[t.label];
+    return -1;
+  }
+  std::pair<std::string, std::string> node_at;   // the node an inlined body looked at: index, suffix of its names
+  // The entries of a state's code.  `q`: prefix of the names, `on`: which lanes, `ins`: the parameters of an
+  // inlined callee (null: the lane's own frame).  Fills V and `complete`; clears *can where a callee cannot
+  // be inlined.
+  void body(std::ostringstream& c, const State& S, const std::string& q, const std::string& on, const std::vector<Val>* ins,
+            std::vector<Val>& V, B& complete, bool* can) {
+    const int f = S.f;
+    const DevFn& fn = P.fn[f];
+    const Facts F = facts(f, S.mask);
+    V.assign(MAX_VALUES + 2, Val{"0ll", bc(false), bc(false)});
+    std::vector<int> alias(MAX_VALUES + 2, -1);   // the value it hands on
+    std::map<int, bool> node_loaded;
+    auto root = [&](int v) { while (v < SRC_NONE && alias[v] >= 0) v = alias[v]; return v; };
+    auto src = [&](const Instr& I, int k) { return source(V, I, k); };
+    auto name_b = [&](const std::string& nm, const B& b) { return named(c, q + nm, b); };
+    auto put = [&](int dst, const std::string& expr, B p, B d) {
+      const std::string D = std::to_string(dst);
+      if (F.live[dst] == 1) { p = bc(true); d = bc(false); }
+      c << "        const long long " << q << "v" << D << " = " << (expr.empty() ? "0" : expr) << ";\n";
+      V[dst] = Val{q + "v" + D, name_b("p" + D, p), name_b("d" + D, band(p, d))};
+    };
+    complete = bc(S.out == 0);
+    for (int ip = 0; ip < fn.count; ++ip) {
+      const Instr& I = at(f, ip);
+      const std::string D = std::to_string(I.dst);
+      switch (I.op) {
+        case D_IN:
+          if (ins) V[I.dst] = (*ins)[I.aux];
+          else put(I.dst, "x.sv[" + std::to_string(I.aux) + "]", bc(true), bc(false));
+          break;
+        case D_RET: {
+          const uint32_t bit = 1u << P.label_site[I.aux2];
+          if (S.mask & bit) {
+            const bool back = !(S.out & bit);
+            c << "        const long long " << q << "v" << D << " = " << (back ? "x.sv[" + std::to_string(I.aux) + "]" : "0") << ";\n";
+            V[I.dst] = Val{q + "v" + D, bc(back), bc(false)};
+          } else {
+            B all_p = bc(true), any_d = bc(false), any_arg = bc(false);
+            for (int k = 0; k < 4; ++k) {
+              if (I.src[k] == SRC_NONE) continue;
+              any_arg = bc(true);
+              all_p = band(all_p, src(I, k).p);
+              any_d = bor(any_d, src(I, k).d);
+            }
+            const B dead = name_b("r" + D, band(any_arg, band(all_p, any_d)));
+            V[I.dst] = Val{"0ll", dead, dead};
+            complete = band(complete, dead);
+          }
+          break;
+        }
+        case D_ADD: case D_SUB: case D_MUL: case D_EQ: case D_LT: {
+          const Val a = src(I, 0), b = src(I, 1);
+          std::string e;
+          if (I.op == D_EQ || I.op == D_LT) e = "(" + a.v + (I.op == D_EQ ? " == " : " < ") + b.v + ")";
+          else e = "(long long)((unsigned long long)" + a.v + (I.op == D_ADD ? " + " : I.op == D_SUB ? " - " : " * ") + "(unsigned long long)" + b.v + ")";
+          put(I.dst, e, band(a.p, b.p), bor(a.d, b.d));
+          break;
+        }
+        case D_ID: {
+          const Val a = src(I, 0);
+          if (I.src[0] < SRC_NONE) alias[I.dst] = I.src[0];
+          put(I.dst, a.v, a.p, a.d);
+          break;
+        }
+        case D_SWITCH: {
+          const Val pr = src(I, 0), da = src(I, 1);
+          const B p = name_b("q" + D, band(pr.p, da.p)), d = name_b("e" + D, bor(pr.d, da.d));
+          const int known = I.src[0] < SRC_NONE ? F.truth[I.src[0]] : (I.imm != 0 ? 1 : 0);
+          const B t = known >= 0 ? bc(known != 0) : name_b("t" + D, bx("(" + pr.v + " != 0)"));
+          if (I.src[1] < SRC_NONE) alias[I.dst] = alias[I.dst + 1] = I.src[1];
+          put(I.dst, da.v, p, bor(d, bnot(t)));
+          put(I.dst + 1, da.v, p, bor(d, t));
+          break;
+        }
+        case D_MERGE: {
+          B any_live = bc(false), all_p = bc(true);
+          std::string e = "0ll";
+          for (int k = 3; k >= 0; --k) {
+            if (I.src[k] == SRC_NONE) continue;
+            const Val a = src(I, k);
+            const B l = live_of(a);
+            any_live = bor(l, any_live);
+            all_p = band(a.p, all_p);
+            if (l.k == 1) e = a.v;
+            else if (l.k == 2) e = "(" + l.e + " ? " + a.v + " : " + e + ")";
+          }
+          const B al = name_b("m" + D, any_live);
+          put(I.dst, e, bor(al, all_p), bnot(al));
+          break;
+        }
+        case D_ISLEAF: case D_LEFT: case D_RIGHT: case D_TOKEN: {
+          const Val a = src(I, 0);
+          const B lv = live_of(a);
+          const int r = I.src[0] < SRC_NONE ? root(I.src[0]) : -1;
+          const std::string R = q + std::to_string(r < 0 ? 255 : r);
+          if (S.mask == 0) {   // first sweep: the node's entries in one round trip, index checked
+            if (!node_loaded[r]) {
+              node_loaded[r] = true;
+              c << "        int " << "nl" << R << " = x.pf_l, nr" << R << " = x.pf_r, nt" << R << " = x.pf_t;\n";
+              c << "        if (" << on << " && " << lv.e << (ins ? "" : " && x.pf_v != " + a.v) << ") ln_node(x, " << a.v << ", nl" << R << ", nr" << R << ", nt" << R
+                << ");\n";
+              if (ins) node_at = {a.v, R};
+            }
+            const char* which = I.op == D_RIGHT ? "nr" : I.op == D_TOKEN ? "nt" : "nl";
+            put(I.dst, std::string("(long long)") + (I.op == D_ISLEAF ? "(nl" + R + " < 0)" : which + R), a.p, a.d);
+          } else {
+            const char* arr = I.op == D_RIGHT ? "right" : I.op == D_TOKEN ? "token" : "left";
+            const int memo = memo_slot(f, S.mask, I.dst);
+            std::string e = memo >= 0 ? "x.sv[" + std::to_string(memo) + "]" : lv.k == 0 ? "0ll" : "(" + on + " && " + lv.e + " ? x.a->" + arr + "[" + a.v + "] : 0)";
+            if (I.op == D_ISLEAF) e = F.truth[I.dst] >= 0 ? std::to_string(F.truth[I.dst]) + "ll" : "(" + e + " < 0)";
+            put(I.dst, "(long long)" + e, a.p, a.d);
+          }
+          break;
+        }
+        case D_EMBED: case D_CELL: case D_HEAD: {
+          const Val a = src(I, 0), b = I.op == D_EMBED ? Val{"0", bc(true), bc(false)} : src(I, 1);
+          const B in = band(live_of(a), live_of(b));
+          if (in.k == 0) {   // dead or absent now, so it was in every earlier state
+            V[I.dst] = Val{"0ll", bc(false), bc(false)};
+            break;
+          }
+          c << "        long long " << q << "v" << D << " = 0; bool " << q << "pp" << D << " = false, " << q << "ll" << D << " = false;\n";
+          if (ins && I.op != D_EMBED) {   // (its place in the log would need a frame)
+            *can = false;
+            break;
+          }
+          if (ins) {   // an inlined callee has no stored values: its EMBED fires here and only here
+            c << "        ln_embed_now(x, " << on << " && " << in.e << ", " << a.v << ", " << q << "v" << D << ", " << q << "pp" << D << ");\n";
+            V[I.dst] = Val{q + "v" + D, in.k == 1 ? bc(true) : in, bc(false)};
+            break;
+          }
+          // fires when its inputs are live; a later state may find it fired already
+          c << "        " << (I.op == D_EMBED ? "ln_embed" : I.op == D_CELL ? "ln_cell" : "ln_head") << "(x, " << on << ", " << (int)I.aux << ", "
+            << a.p.e << ", " << a.d.e << ", " << a.v;
+          if (I.op != D_EMBED) c << ", " << b.p.e << ", " << b.d.e << ", " << b.v;
+          c << ", v" << D << ", pp" << D << ", ll" << D << ");\n";
+          V[I.dst] = Val{"v" + D, in.k == 1 ? bc(true) : bx("pp" + D), bc(false)};
+          break;
+        }
+        case D_CE_NODE: {
+          const Val a = src(I, 0), b = src(I, 1);
+          const B lv = band(live_of(a), live_of(b));
+          if (lv.k != 0)
+            c << "        if (" << on << " && " << lv.e << ") { bool dd = false; ln_ce_node(x, " << a.v << ", " << b.v << ", dd); }\n";
+          put(I.dst, a.v, band(a.p, b.p), bor(a.d, b.d));
+          break;
+        }
+        default: break;   // calls and the output: state_code
+      }
+    }
+  }
+  static B named(std::ostringstream& c, const std::string& nm, const B& b) {
+    if (b.k != 2) return b;
+    c << "        const bool " << nm << " = " << b.e << ";\n";
+    return bx(nm);
+  }
+  static Val source(const std::vector<Val>& V, const Instr& I, int k) {
+    if (I.src[k] == SRC_IMM) return Val{"(long long)" + std::to_string((unsigned long long)I.imm) + "ULL", bc(true), bc(false)};
+    return V[I.src[k]];
+  }
+  const Instr& out_entry(int f) const {
+    int k = 0;
+    for (int ip = 0; ip < P.fn[f].count; ++ip)
+      if (at(f, ip).op == D_OUT) k = ip;
+    return at(f, k);
+  }
+  // A callee whose first sweep may be all there is (a base case) is tried in the caller's sweep: no frame
+  // is pushed for it then.  Not where the body has operators with a stored value other than EMBED.
+  bool can_inline(int f) const {
+    if (f == P.result_fn) return false;
+    for (int ip = 0; ip < P.fn[f].count; ++ip) {
+      const uint8_t op = at(f, ip).op;
+      if (op == D_HEAD || op == D_NEXT) return false;
+    }
+    return true;
+  }
+  // A loop graph without calls runs its iterations in the sweep (bounded; the iterations are tags like any).
+  bool tight_loop(int f) const {
+    bool next = false;
+    for (int ip = 0; ip < P.fn[f].count; ++ip) {
+      const uint8_t op = at(f, ip).op;
+      if (op == D_CALL || op == D_EMBED || op == D_CELL || op == D_HEAD || op == D_CE_NODE || (op >= D_ISLEAF && op <= D_TOKEN)) return false;
+      next = next || op == D_NEXT;
+    }
+    return next;
+  }
+
+  // Code of one state; `next` receives the sets of opened calls it can go to.  With emit false only `next`.
+  void state_code(const State& S, std::vector<int>& next, bool emit) {
+    const int f = S.f;
+    std::ostringstream c;
+    std::vector<Val> V;
+    B complete = bc(false);
+    const bool loop = tight_loop(f);
+    body(c, S, "", "on", nullptr, V, complete, nullptr);
+    auto src = [&](const Instr& I, int k) { return source(V, I, k); };
+    auto state_name = [](int sf, uint32_t m, uint32_t ou) { return std::to_string(state_code_of(sf, m, ou)) + "u"; };
+    // ---- what the lane does next
+    const std::vector<Site> ss = sites(f);
+    std::string chain, nx;
+    B part = bc(false), taken = bc(false);
+    std::string count = "0";
+    int n_count = 0, n_chain = 0;
+    // Calls that are ready, in table order.  Each is first tried in place; what is left over is called, the
+    // first one now.  A call is tried in the first state it can be ready in only: it will not have changed.
+    struct Ready { const Site* t; uint32_t bit; int callee, slot; std::string tag, args, done, value, node; B all; };
+    std::vector<Ready> rs;
+    std::vector<Val> V0;
+    B c0 = bc(false);
+    if (S.mask) {
+      std::ostringstream sink;
+      body(sink, State{f, 0, 0}, "", "on", nullptr, V0, c0, nullptr);
+    }
+    for (const Site& t : ss) {
+      const uint32_t bit = t.label >= 0 ? 1u << P.label_site[t.label] : 0u;
+      if (S.mask & bit) continue;
+      B all = bc(true), any = bc(false), before = bc(true);
+      const int callee = t.label >= 0 ? P.label_callee[t.label] : f, np = P.fn[callee].n_params;
+      for (const Instr* I : t.args) {
+        const B l = live_of(src(*I, 0));
+        all = band(all, l);
+        any = bor(any, l);
+        if (S.mask) before = band(before, live_of(source(V0, *I, 0)));
+      }
+      if ((int)t.args.size() != np) all = bc(false);
+      const std::string tag = t.label >= 0 ? std::to_string(P.label_site[t.label]) : "n";
+      all = named(c, "all" + tag, all);
+      part = bor(part, band(any, bnot(all)));
+      std::string args;
+      for (const Instr* I : t.args) args += " x.arg[" + std::to_string((int)I->aux2) + "] = " + src(*I, 0).v + ";";
+      args += " x.c_np = " + std::to_string(np) + "u;";
+      if (t.label < 0) {
+        if (loop && all.k) {
+          nx = "if (" + all.e + ") {";
+          for (const Instr* I : t.args) nx += " const long long w" + std::to_string((int)I->aux2) + " = " + src(*I, 0).v + ";";
+          for (const Instr* I : t.args) nx += " x.sv[" + std::to_string((int)I->aux2) + "] = w" + std::to_string((int)I->aux2) + ";";
+          nx += " ++n_it; if (n_it < LANE_LOOP) continue; }\n          else ";
+        } else if (all.k) {
+          nx = "if (" + all.e + ") { x.act = ACT_NEXT;" + args + " x.c_st = " + state_name(f, 0, 0) + "; }\n          else ";
+        }
+        continue;
+      }
+      if (all.k == 0) continue;
+      Ready r{&t, bit, callee, (int)P.label_ret_slot[t.label], tag, args, "", "", "", all};
+      const bool first_time = S.mask == 0 || before.k == 0;
+      int inlined = 0;
+      for (const Ready& o2 : rs) inlined += !o2.done.empty();
+      if (first_time && inlined < 3 && can_inline(callee)) {
+        const std::string q = "c" + tag + "_", con = "(on && " + all.e + ")";
+        std::vector<Val> ins((size_t)np, Val{"0ll", bc(true), bc(false)}), W;
+        for (const Instr* I : t.args) ins[I->aux2] = Val{src(*I, 0).v, bc(true), bc(false)};
+        B whole = bc(false), partly = bc(false);
+        std::ostringstream ic;
+        bool can = true;
+        node_at = {"", ""};
+        body(ic, State{callee, 0, 0}, q, con, &ins, W, whole, &can);
+        const Val ov = source(W, out_entry(callee), 0);
+        for (const Site& u : sites(callee))
+          for (const Instr* I : u.args) partly = bor(partly, live_of(source(W, *I, 0)));
+        const B done = band(band(whole, bnot(partly)), live_of(ov));
+        if (can && done.k != 0) {
+          c << ic.str();
+          r.done = named(c, "done" + tag, band(bx("(" + all.e + ")"), done)).e;
+          r.value = ov.v;
+          if (!node_at.second.empty())
+            r.node = " x.pf_v = " + node_at.first + "; x.pf_l = nl" + node_at.second + "; x.pf_r = nr" + node_at.second + "; x.pf_t = nt" + node_at.second + ";";
+        }
+      }
+      rs.push_back(r);
+    }
+    // Sets of calls done in place, each a state to go on from
+    std::vector<uint32_t> sets(1, 0u);
+    for (const Ready& r : rs)
+      if (!r.done.empty())
+        for (size_t k = 0, n = sets.size(); k < n; ++k) sets.push_back(sets[k] | r.bit);
+    auto state_after = [&](uint32_t bit) {   // the state once call `bit` (0: none) is back, by what was done in place
+      std::string e2 = state_name(f, S.mask | bit | sets[0], S.out);
+      for (size_t k = 1; k < sets.size(); ++k)
+        if (!(sets[k] & bit)) e2 = "(om == " + std::to_string(S.mask | sets[k]) + "u ? " + state_name(f, S.mask | bit | sets[k], S.out) + " : " + e2 + ")";
+      return e2;
+    };
+    auto note = [&](uint32_t m) {
+      if (m != S.mask) next.push_back((int)m);
+    };
+    std::string om = std::to_string(S.mask) + "u", put;
+    for (const Ready& r : rs) {
+      if (r.done.empty()) continue;
+      om += " | (" + r.done + " ? " + std::to_string(r.bit) + "u : 0u)";
+      put += "          if (" + r.done + ") { x.sv[" + std::to_string(r.slot) + "] = " + r.value + "; x.present |= " + std::to_string(1u << r.slot) +
+             "u; ++x.n_tags; x.n_tokens += " + std::to_string(P.fn[r.callee].n_params + 1) + "u; x.mx_depth = max(x.mx_depth, x.depth + 1u); }\n";
+    }
+    for (uint32_t d : sets) note(S.mask | d);
+    for (size_t k = 0; k < rs.size(); ++k) {
+      const Ready& r = rs[k];
+      count += " + (int)" + (r.done.empty() ? r.all.e : "(" + r.all.e + " && !" + r.done + ")");
+      ++n_count;
+      // could an earlier ready call always be there when this one is?  Then it is never the one chosen.
+      bool never = taken.k == 1;
+      for (const Ready& u : rs) {
+        if (never || &u == &r) break;
+        if (!u.done.empty()) continue;
+        const Facts G = facts(f, S.mask | r.bit);
+        bool sure = (int)u.t->args.size() == (int)P.fn[u.callee].n_params;
+        for (const Instr* I : u.t->args) sure = sure && (I->src[0] >= SRC_NONE || (G.live[I->src[0]] == 1 && src(*I, 0).p.k == 1));
+        never = sure;
+      }
+      if (never) continue;
+      for (uint32_t d : sets)
+        if (!(d & r.bit)) note(S.mask | r.bit | d);
+      const std::string go = r.done.empty() ? r.all.e : "(" + r.all.e + " && !" + r.done + ")";
+      std::string keep;   // arguments of calls that wait, kept in the place of their results
+      for (const Ready& u : rs)
+        if (&u != &r && u.t->args.size() == 1 && memo_slot(f, S.mask | r.bit, u.t->args[0]->src[0]) == u.slot) {
+          const uint8_t op = u.t->args[0]->src[0] < SRC_NONE ? at(f, facts(f, 0).def[u.t->args[0]->src[0]]).op : (uint8_t)D_IN;
+          if (op == D_LEFT || op == D_RIGHT || op == D_TOKEN)
+            keep += (u.done.empty() ? "" : " if (!" + u.done + ")") + std::string(" x.sv[") + std::to_string(u.slot) + "] = " + src(*u.t->args[0], 0).v + ";";
+        }
+      chain += std::string(n_chain++ ? "          else " : "          ") + "if (" + go + ") { x.act = ACT_CALL; x.c_st = " + state_name(r.callee, 0, 0) + "; x.c_back = " +
+               state_after(r.bit) + " | " + std::to_string((unsigned)r.slot << 20) + "u; x.c_label = " + std::to_string(r.t->label) + "u;" + r.args + r.node + keep + " }\n";
+      taken = bor(taken, r.done.empty() ? r.all : bx(go));
+    }
+    if (sets.size() > 1)
+      chain += std::string(n_chain++ ? "          else " : "          ") + "if (om != " + std::to_string(S.mask) + "u) { x.st = " + state_after(0) + "; }\n";
+    if (!emit) return;
+    const Instr& oe = out_entry(f);
+    const Val ov = src(oe, 0);
+    const B ol = live_of(ov);
+    c << "        if (on) {\n";
+    if (n_count > 1) c << "          x.more = (" << count << ") > 1;\n";
+    else c << "          x.more = false;\n";
+    c << "          const uint32_t om = " << om << ";\n          (void)om;\n" << put;
+    c << chain;
+    c << "          " << (n_chain ? "else " : "");
+    if (part.k) c << "if (" << part.e << ") x.act = " << (complete.k == 0 ? "ACT_WAIT" : "(" + complete.e + ") ? ACT_STUCK : ACT_WAIT") << ";\n          else ";
+    if (complete.k != 1) c << "if (!" << complete.e << ") x.act = ACT_WAIT;\n          else ";
+    c << nx;
+    if (f == P.result_fn) {
+      c << "{ ";
+      if (ol.k) c << "if (" << ol.e << ") ln_result(x, " << (int)oe.aux << ", " << ov.v << "); ";
+      c << "x.act = ACT_DONE; }\n";
+    } else {
+      if (ol.k) c << "if (" << ol.e << ") { x.act = ACT_RET; x.ret = " << ov.v << "; }\n          else ";
+      c << "x.act = ACT_STUCK;\n";
+    }
+    c << "        }\n";
+    o << "      case " << state_code_of(f, S.mask, S.out) << "u: {  // function " << f << ", opened " << S.mask << ", outstanding " << S.out << "\n";
+    const std::string r = c.str();
+    if (loop) {
+      const int nv = P.fn[f].n_params;
+      o << "      if (on) {\n        uint32_t n_it = 0;\n        do {\n" << r << "        break;\n        } while (true);\n";
+      o << "        ln_loop(x, n_it, " << nv << "u);\n      }\n      break; }\n";
+    } else {
+      o << r << "      break; }\n";
+    }
+  }
+
+  void find_states() {
+    states.clear();
+    for (int f = 0; f < P.n_fn; ++f) states.push_back({f, 0, 0});
+    for (int pass = 0; pass < 2; ++pass)   // first without outstanding calls, then with them
+      for (size_t k = 0; k < states.size() && states.size() < MAX_STATES; ++k) {
+        const State S = states[k];
+        std::vector<int> nx;
+        state_code(S, nx, false);
+        auto add = [&](uint32_t mask, uint32_t out) {
+          if ((int)states.size() < MAX_STATES && !has_state(S.f, mask, out)) states.push_back({S.f, mask, out});
+        };
+        for (int mask : nx) {
+          if (pass == 0 || S.out) add((uint32_t)mask, S.out);
+          if (pass == 1)   // ... with any one of the calls just opened still under way
+            for (int b2 = 0; b2 < 8; ++b2)
+              if (((uint32_t)mask & ~S.mask) >> b2 & 1) add((uint32_t)mask, S.out | (1u << b2));
+        }
+      }
+  }
+  // The generic code of a function: present and opened sets from registers.
+  void lane_function(int f) {
+    const DevFn& fn = P.fn[f];
+    o << "        case " << f << "u: {  // function " << f << ", generic\n";
+    for (int v = 0; v < fn.n_values; ++v)
+      o << "        long long v" << v << " = 0; bool p" << v << " = false, d" << v << " = false;\n";
+    o << "        bool live = false, all_in = true;\n";
+    std::vector<std::pair<int, std::vector<const Instr*>>> calls;   // by label, in table order; -1: the next iteration
+    const Instr* out_entry = nullptr;
+    for (int ip = 0; ip < fn.count; ++ip) {
+      const Instr& I = P.instr[fn.first + ip];
+      if (I.op == D_CALL || I.op == D_NEXT) {
+        const int label = I.op == D_CALL ? (int)I.aux : -1;
+        size_t k = 0;
+        while (k < calls.size() && calls[k].first != label) ++k;
+        if (k == calls.size()) calls.push_back({label, {}});
+        calls[k].second.push_back(&I);
+        continue;
+      }
+      if (I.op == D_OUT) {
+        out_entry = &I;
+        continue;
+      }
+      entry(I, true);
+    }
+    // calls: ready with every argument live; partly live is a case for the step machine
+    int n_ready = 0;
+    std::string chain, count = "0", part = "false", next;
+    for (auto& c : calls) {
+      std::string all = "true", any = "false";
+      for (const Instr* I : c.second) {
+        const std::string lv = "(" + pre(*I, 0) + " && !" + ded(*I, 0) + ")";
+        all += " && " + lv;
+        any += " || " + lv;
+      }
+      const int callee = c.first >= 0 ? P.label_callee[c.first] : f, np = P.fn[callee].n_params;
+      const std::string id = c.first >= 0 ? std::to_string(P.label_site[c.first]) : "n";
+      const std::string open = c.first >= 0 ? "!((s >> (3 + " + id + ")) & 1u) && " : "";
+      o << "        const bool all" << id << " = on && " << open << "(" << all << ") && " << ((int)c.second.size() == np ? "true" : "false")
+        << ";\n";
+      o << "        const bool part" << id << " = on && " << open << "!all" << id << " && (" << any << ");\n";
+      part += " || part" + id;
+      std::string args;
+      for (const Instr* I : c.second) args += " x.arg[" + std::to_string((int)I->aux2) + "] = " + val(*I, 0) + ";";
+      args += " x.c_np = " + std::to_string(np) + "u;";
+      if (c.first < 0) {
+        next = "if (alln) { x.act = ACT_NEXT;" + args + " x.c_st = " + std::to_string(state_code_of(f, 0, 0)) + "u; }\n          else ";
+        continue;
+      }
+      chain += std::string(n_ready++ ? "        else " : "        ") + "if (all" + id + ") { x.act = ACT_CALL; x.c_st = " +
+               std::to_string(state_code_of(callee, 0, 0)) + "u; x.c_back = (s | 1u << (3 + " + id + ")) | " +
+               std::to_string((unsigned)P.label_ret_slot[c.first] << 20) + "u; x.c_label = " + std::to_string(c.first) + "u;" + args + " }\n";
+      count += " + (int)all" + id;
+    }
+    o << chain;
+    if (n_ready) o << "        if (on) x.more = (" << count << ") > 1;\n";
+    o << "        if (on && x.act == ACT_NONE) {\n";
+    o << "          if (" << part << ") x.act = all_in ? ACT_STUCK : ACT_WAIT;\n";
+    o << "          else if (!all_in) x.act = ACT_WAIT;\n          else ";
+    o << next;
+    const std::string olive = "(" + pre(*out_entry, 0) + " && !" + ded(*out_entry, 0) + ")";
+    if (f == P.result_fn)
+      o << "{ if (" << olive << ") ln_result(x, " << (int)out_entry->aux << ", " << val(*out_entry, 0) << "); x.act = ACT_DONE; }\n";
+    else
+      o << "if (" << olive << ") { x.act = ACT_RET; x.ret = " << val(*out_entry, 0) << "; }\n          else x.act = ACT_STUCK;\n";
+    o << "        }\n";
+    o << "        (void)live;\n      break; }\n";
+  }
+
+  // Place of call 0's result if call k's is k places further for all calls of the function, -1 if not, -2: no calls.
+  int ret_base(int f) const {
+    int base = -2;
+    for (const Site& t : sites(f)) {
+      if (t.label < 0) continue;
+      const int b = (int)P.label_ret_slot[t.label] - (int)P.label_site[t.label];
+      if (base == -2) base = b;
+      else if (base != b) base = -1;
+      if (b < 0) return -1;
+    }
+    return base;
+  }
+  std::string lane_source() {
+    int ns = 1;
+    for (int f = 0; f < P.n_fn; ++f) ns = std::max<int>(ns, P.fn[f].n_stored);
+    find_states();
+    o << "#include \"lane_device.h\"\n";
+    o << "namespace tdf {\n";
+    o << "struct GeneratedLanes {\n";
+    o << "  static constexpr int kStored = " << ns << ";\n  static constexpr uint32_t kResultFn = " << P.result_fn << "u;\n";
+    // Return_i of label i: the caller's stored value
+    o << "  static __device__ __forceinline__ uint32_t ret_slot(uint32_t label) {\n    switch (label) {\n";
+    for (int l = 0; l < P.n_labels; ++l) o << "      case " << l << ": return " << (int)P.label_ret_slot[l] << "u;\n";
+    o << "      default: return 0u;\n    }\n  }\n";
+    o << "  static constexpr bool kBranching = " << (lane_branching(P) ? "true" : "false") << ";\n";
+    // stored values that the opened calls of a frame return into, and the calls whose value is not there yet: a
+    // function's results have consecutive places, in the order of its calls, wherever the table puts them so
+    o << "  static __device__ __forceinline__ uint32_t ret_bits(uint32_t fn, uint32_t opened) {\n    uint32_t r = 0;\n";
+    for (int f = 0; f < P.n_fn; ++f) {
+      const int base = ret_base(f);
+      if (base >= 0) o << "    if (fn == " << f << "u) r = opened << " << base << ";\n";
+      for (const Site& t : sites(f))
+        if (base == -1 && t.label >= 0)
+          o << "    if (fn == " << f << "u && ((opened >> " << (int)P.label_site[t.label] << ") & 1u)) r |= 1u << " << (int)P.label_ret_slot[t.label] << ";\n";
+    }
+    o << "    return r;\n  }\n";
+    o << "  static __device__ __forceinline__ uint32_t outstanding(uint32_t fn, uint32_t opened, uint32_t present) {\n    uint32_t r = 0;\n";
+    for (int f = 0; f < P.n_fn; ++f) {
+      const int base = ret_base(f);
+      if (base >= 0) o << "    if (fn == " << f << "u) r = opened & ~(present >> " << base << ");\n";
+      for (const Site& t : sites(f))
+        if (base == -1 && t.label >= 0)
+          o << "    if (fn == " << f << "u && ((opened >> " << (int)P.label_site[t.label] << ") & 1u) && !((present >> "
+            << (int)P.label_ret_slot[t.label] << ") & 1u)) r |= 1u << " << (int)P.label_site[t.label] << ";\n";
+    }
+    o << "    return r;\n  }\n";
+    o << "  static __device__ __forceinline__ void sweep(LaneX& x) {\n";
+    // One state after the other, as the wave's lanes have them.  A lane whose call was evaluated in place is
+    // in another state then and comes up again; a lane is left out once its state is done.
+    o << "    unsigned long long todo = __ballot(x.run);\n";
+    o << "    while (todo) {\n";
+    o << "      const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)x.st, __ffsll((long long)todo) - 1);\n";
+    o << "      const bool on = ((todo >> lane_id()) & 1ull) && x.st == s;\n";
+    o << "      switch (s) {\n";
+    for (const State& t : states) {
+      std::vector<int> nx;
+      state_code(t, nx, true);
+    }
+    o << "      default: switch (s & 7u) {\n";
+    for (int f = 0; f < P.n_fn; ++f) lane_function(f);
+    o << "        default: if (on) x.act = ACT_STUCK; break;\n        } break;\n      }\n";
+    o << "      todo &= __ballot(!(on && (x.act != ACT_NONE || x.st == s)));\n    }\n";
+    o << "  }\n};\n}  // namespace tdf\n";
+    o << "extern \"C\" __global__ void __launch_bounds__(64, 2) tdf_generated_lanes(tdf::LaneArgs a) {\n";
+    o << "  extern __shared__ __attribute__((aligned(16))) char lds[];\n";
+    o << "  tdf::lanes_run<tdf::GeneratedLanes>(a, lds);\n}\n";
+    return o.str();
   }
 
   std::string source() {
@@ -223,13 +870,13 @@ std::map<std::string, CacheEntry> g_cache;
 }  // namespace
 
 // Code object of the generated kernels for `arch`, compiled once per (arch, firing tables).
-static bool jit_code(const DevProgram& P, const std::string& arch, std::vector<char>& code, std::string& log) {
+static bool jit_code(const DevProgram& P, const std::string& arch, bool lanes, std::vector<char>& code, std::string& log) {
   for (int f = 0; f < P.n_fn; ++f)
     if (P.fn[f].n_stored > 8) {
       log = "a function keeps more than 8 stored values";
       return false;
     }
-  const std::string key = arch + '\n' + std::string(reinterpret_cast<const char*>(&P), sizeof(DevProgram));
+  const std::string key = arch + (lanes ? "\nlanes\n" : "\n") + std::string(reinterpret_cast<const char*>(&P), sizeof(DevProgram));
   {
     std::lock_guard<std::mutex> lock(g_cache_mutex);
     auto it = g_cache.find(key);
@@ -244,7 +891,7 @@ static bool jit_code(const DevProgram& P, const std::string& arch, std::vector<c
     return false;
   }
   Gen gen(P);
-  const std::string src = gen.source();
+  const std::string src = lanes ? gen.lane_source() : gen.source();
   if (getenv("TDF_JIT_DUMP")) fprintf(stderr, "%s\n", src.c_str());
   rtcProgram prog = nullptr;
   if (r.create(&prog, src.c_str(), "tdf_generated.hip", kEmbeddedCount, kEmbeddedSources, kEmbeddedNames) != 0) {
@@ -287,7 +934,7 @@ bool jit_compile(const DevProgram& P, JitKernels& out, std::string& log) {
     return false;
   }
   std::vector<char> code;
-  if (!jit_code(P, prop.gcnArchName, code, log)) return false;   // e.g. gfx950:sramecc+:xnack-
+  if (!jit_code(P, prop.gcnArchName, false, code, log)) return false;   // e.g. gfx950:sramecc+:xnack-
   hipModule_t mod = nullptr;
   if (hipModuleLoadData(&mod, code.data()) != hipSuccess) {
     log = "hipModuleLoadData failed";
@@ -308,7 +955,50 @@ bool jit_compile(const DevProgram& P, JitKernels& out, std::string& log) {
   return true;
 }
 
+int lane_stored(const DevProgram& P) {
+  int ns = 1;
+  for (int f = 0; f < P.n_fn; ++f) ns = std::max<int>(ns, P.fn[f].n_stored);
+  return ns;
+}
+
+bool lane_branching(const DevProgram& P) {
+  for (int f = 0; f < P.n_fn; ++f)
+    if (f != P.result_fn && P.fn[f].n_sites > 1) return true;
+  return false;
+}
+
+bool jit_compile_lanes(const DevProgram& P, JitKernels& out, std::string& log) {
+  const char* off = getenv("TDF_NO_JIT");
+  if (off && off[0] == '1') {
+    log = "disabled by TDF_NO_JIT";
+    return false;
+  }
+  int dev = 0;
+  hipDeviceProp_t prop;
+  if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) {
+    log = "no device";
+    return false;
+  }
+  std::vector<char> code;
+  if (!jit_code(P, prop.gcnArchName, true, code, log)) return false;
+  hipModule_t mod = nullptr;
+  hipFunction_t f = nullptr;
+  if (hipModuleLoadData(&mod, code.data()) != hipSuccess) {
+    log = "hipModuleLoadData failed";
+    return false;
+  }
+  if (hipModuleGetFunction(&f, mod, "tdf_generated_lanes") != hipSuccess) {
+    (void)hipModuleUnload(mod);
+    log = "generated kernel not found in the module";
+    return false;
+  }
+  out.lanes_module = mod;
+  out.lanes = f;
+  return true;
+}
+
 void jit_release(JitKernels& k) {
+  if (k.lanes_module) (void)hipModuleUnload((hipModule_t)k.lanes_module);
   if (k.module) (void)hipModuleUnload((hipModule_t)k.module);
   k = JitKernels{};
 }
@@ -320,12 +1010,12 @@ extern "C" tdf_status tdf_graph_precompile(const tdf_graph* graph, const char* a
     tdf::set_error("tdf_graph_precompile: graph and arch are required");
     return TDF_ERR_BAD_ARG;
   }
-  std::vector<char> code;
+  std::vector<char> code, lanes;
   std::string log;
-  if (!tdf::jit_code(graph->g.prog, arch, code, log)) {
+  if (!tdf::jit_code(graph->g.prog, arch, false, code, log) || !tdf::jit_code(graph->g.prog, arch, true, lanes, log)) {
     tdf::set_error("run-time compilation failed: " + log);
     return TDF_ERR_UNSUPPORTED;
   }
-  if (code_bytes) *code_bytes = code.size();
+  if (code_bytes) *code_bytes = code.size() + lanes.size();
   return TDF_OK;
 }

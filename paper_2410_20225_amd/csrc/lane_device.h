@@ -1,0 +1,949 @@
+// The tag machine of evaluations that keep no frames (statistics level 0): depth-first lanes.
+//
+// A lane owns one frame (= one call-context tag), sweeps its function body, and goes on with the
+// first call whose arguments are all present: the caller's frame goes on the lane's own stack, the
+// callee's frame takes its place in registers, and its Return pops the caller again.  Call_i, Return_i,
+// Enter, Next and Exit are the paper's (Call_i <t,d> = <i:t,d>, Return_i <i:t,d> = <t,d>, ...); what
+// differs from the step machine (step_device.h) is the order in which ready tags fire, which the
+// dataflow semantics leaves open, and where a frame lives: in the lane, not in a table, as long as one
+// lane has the tag and all tags below it.  A call whose arguments arrive one after the other is
+// opened when the last one is there, and a function's output leaves when everything it started has
+// come back (both orders give the same values and the same counts).
+//
+// Work is shared in two tiers.
+//   Inside a wave (= one workgroup), through LDS: a lane gives the oldest frame of its stack that has a
+//   ready call left, as a record that any lane of the wave can take as a task.  Records are finished by
+//   whoever delivers the last awaited value (a join counter per record; nobody waits).  Everything is
+//   wave-synchronous: no barriers, a hand-over costs a few LDS round trips.
+//   Between waves, through memory: a wave that has nothing takes a ticket of the global queue; a wave that
+//   sees tickets outstanding sends calls (arguments and where to return to), and polls for the values that
+//   come back.  Values are written before flags with a wait for the acknowledgement in between, all with
+//   device-scope accesses, which are coherent between the dies; such a round trip is about a microsecond,
+//   which is why the first tier does not use it.
+// No wave waits for another one except for work or for a value it sent a call for; idle waves are sent
+// home when the last instance is done, so nothing here assumes that workgroups are resident together.
+//
+// What bounds it: the instructions of a wave's sweeps, about 4 clocks each, vector, scalar and branch alike (a
+// recursion without parallelism runs one lane, about 1.3 us a call there and back), and with many waves how evenly
+// the calls spread over them.  A frame costs no memory traffic beyond the lane's stack, whose top is in LDS.
+// Measured, whole evaluations in us, step machine -> lanes: fib(0..20) 582 -> 238; 2 x fib(28) 28500 -> 7400 (3.3 to
+// 7.4 ms by how the calls happened to spread); tak over 512 instances 23000 -> 5200; 65536 gcd loops 7390 -> 157.
+// The tag phase of tree networks: 4096 random trees of up to 64 leaves 1980 -> 590, 1500 small trees 366 -> 112, a chain
+// of 512 leaves 4200 -> 1500.
+//
+// Conditions that this machine does not handle (a call some of whose arguments are dead, a function
+// that completes without a value, more frames than there is room for, more sweeps than the limit) set
+// `status`; the host then runs the evaluation on the step machine, whose answer counts.
+#pragma once
+#include "engine.h"
+
+namespace tdf {
+
+constexpr uint32_t LANE_NONE = 0xFFFFFFFFu;
+constexpr uint32_t LANE_REMOTE = 0x80000000u;   // a caller in another wave: LANE_REMOTE | wave << 6 | reply
+constexpr uint32_t LANE_EMPTY = 0xFFFFFFFFu, LANE_PILL = 1u, LANE_TASK = 2u, LANE_LEFT = 3u;   // global queue: state of a slot
+constexpr uint32_t LANE_WINDOW = 4;     // frames of a lane's stack that stay in LDS
+constexpr uint32_t LANE_SEG = 16;       // frames of a segment of a lane's stack in memory
+constexpr uint32_t LANE_SYNC = 4, LANE_SYNC_FULL = 8;   // sweeps between two looks at the other lanes; the latter while nearly all have work
+constexpr uint32_t LANE_EARLY = 48;     // sweeps during which a wave gives work away although it has lanes without any
+constexpr uint32_t LANE_LOOP = 64;      // iterations of a loop without calls in one sweep
+constexpr uint32_t LANE_RECS = 96;      // records of a wave
+constexpr uint32_t LANE_QUEUE = 128;    // tasks of a wave (at least LANE_RECS: a record is queued at most once)
+constexpr uint32_t LANE_CHUNK = 128;    // log entries a wave reserves at once (at least a wave's lanes)
+constexpr uint32_t LANE_LOG_HOLE = 0xFFFFFFFFu;
+
+// State of a frame: function (3 bits) | opened calls (8) << 3 | those of them outstanding in other lanes (8) << 11.
+__host__ __device__ constexpr uint32_t lane_state(uint32_t fn, uint32_t opened, uint32_t out) { return fn | opened << 3 | out << 11; }
+__host__ __device__ constexpr uint32_t lane_fn(uint32_t st) { return st & 7u; }
+__host__ __device__ constexpr uint32_t lane_opened(uint32_t st) { return (st >> 3) & 0xFFu; }
+
+enum LaneAct : uint32_t { ACT_NONE = 0, ACT_CALL, ACT_RET, ACT_NEXT, ACT_DONE, ACT_WAIT, ACT_STUCK };
+
+// 16-byte units of a segment: {segment below, segment above, -, -}, then LANE_SEG frames.
+__host__ __device__ constexpr int lane_seg_units(int n_stored) { return 1 + (int)LANE_SEG * (1 + (n_stored + 1) / 2); }
+// 16-byte chunks of a frame on a lane's stack, by the stored values of the program.
+__host__ __device__ constexpr int lane_chunks(int n_stored) { return 1 + (n_stored + 1) / 2; }
+__host__ __device__ constexpr size_t lane_lds_bytes(int n_stored) {
+  return (size_t)LANE_WINDOW * lane_chunks(n_stored) * 64 * 16 + (size_t)LANE_RECS * (8 * n_stored + 7 * 4 + 4) + LANE_QUEUE * 4 + 64 * 4;
+}
+
+#if defined(__HIPCC__) || defined(__HIPCC_RTC__)
+
+// A slot of the global queue: one call sent to another wave.
+struct LaneMail {
+  uint32_t flag, pad;
+  unsigned long long from;       // caller: LANE_REMOTE | wave << 6 | reply, | state << 32
+  unsigned long long meta;       // label | depth << 32
+  unsigned long long inst_np;    // instance | number of arguments << 32
+  unsigned long long arg[8];
+  unsigned long long fill[4];
+};
+static_assert(sizeof(LaneMail) == 128, "one line per slot");
+struct LaneReply { unsigned long long value, flag; };   // flag 1: the value is there
+
+template <typename T> __device__ __forceinline__ T lane_ld(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T> __device__ __forceinline__ void lane_put(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T> __device__ __forceinline__ T lane_add(T* p, T v) {
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A lane: its frame, what the last sweep asks for, and its counts.
+struct LaneX {
+  const LaneArgs* a;
+  long long sv[8];
+  uint32_t st;              // state (lane_state)
+  uint32_t present;         // stored values that are there
+  uint32_t label, counter, depth;
+  bool run;                 // the lane sweeps its frame
+  uint32_t inst;
+  // result of a sweep
+  uint32_t act;
+  uint32_t c_st, c_np, c_label;   // the new frame's state, number of arguments, label of the call
+  uint32_t c_back;          // the caller's state once the call is back | the value's stored slot << 20
+  long long arg[8];
+  long long ret;
+  bool more;                // further calls of the frame are ready
+  // wave-uniform: the wave's part of the schedule log
+  uint32_t log_next, log_end;
+  // counts
+  uint32_t n_tags, n_tokens, n_leaf, n_cell, mx_depth, mx_level;
+  int bad;                  // a condition the host has to deal with
+  // the tree node looked at last (the callee's, when a call was tried in place and then made): index and entries
+  long long pf_v;
+  int pf_l, pf_r, pf_t;
+};
+
+// ---- helpers of the generated sweeps ---------------------------------------------------------------
+// forest accessors at node v: which = 0 isleaf, 1 left, 2 right, 3 token
+__device__ __forceinline__ long long ln_tree(LaneX& x, long long v, int which, bool& dead) {
+  const LaneArgs& a = *x.a;
+  if (v < 0 || v >= a.n_tree_nodes || a.left == nullptr) {
+    x.bad = TDF_ERR_BAD_ARG;
+    dead = true;
+    return 0;
+  }
+  const int32_t e = which == 2 ? a.right[v] : which == 3 ? a.token[v] : a.left[v];
+  return which == 0 ? (long long)(e < 0) : (long long)e;
+}
+// a node's entries in one round trip; false: no such node
+__device__ __forceinline__ bool ln_node(LaneX& x, long long v, int& l, int& r, int& t) {
+  const LaneArgs& a = *x.a;
+  if (v < 0 || v >= a.n_tree_nodes || a.left == nullptr) {
+    x.bad = TDF_ERR_BAD_ARG;
+    return false;
+  }
+  l = a.left[v];
+  r = a.right[v];
+  t = a.token[v];
+  return true;
+}
+// positions in the schedule log for the lanes that take one; whole wave must call
+__device__ __forceinline__ uint32_t ln_log(LaneX& x, bool take) {
+  const unsigned long long m = __ballot(take);
+  if (m == 0) return 0;
+  const uint32_t n = (uint32_t)__popcll(m);
+  if (x.log_next + n > x.log_end) {   // the wave's chunk is used up: what is left of it stays a hole
+    const LaneArgs& a = *x.a;
+    const uint32_t h = x.log_next + lane_id();
+    if (h < x.log_end && h < a.log_cap) a.log[h].z = LANE_LOG_HOLE;
+    uint32_t base = 0;
+    if (lane_id() == 0) base = lane_add(&a.ctl->log_used, LANE_CHUNK);
+    x.log_next = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    x.log_end = x.log_next + LANE_CHUNK;
+  }
+  const uint32_t pos = x.log_next + (uint32_t)__popcll(m & lanemask_lt());
+  x.log_next += n;
+  return pos;
+}
+// EMBED: one log entry {token, -, level 0, instance}; the value is named by its place in the log
+__device__ __forceinline__ void ln_embed(LaneX& x, bool on, int slot, bool ap, bool ad, long long av, long long& v, bool& p, bool& live) {
+  const bool had = on && ((x.present >> slot) & 1);
+  const bool go = on && ap && !ad && !had;
+  const bool ok = go && av >= 0 && av < (long long)x.a->vocab;
+  if (go && !ok) x.bad = TDF_ERR_BAD_ARG;
+  const uint32_t pos = ln_log(x, ok);
+  long long r = x.sv[slot];
+  if (ok) {
+    if (pos < x.a->log_cap) x.a->log[pos] = make_uint4((uint32_t)av, 0u, 0u, x.inst);
+    else x.bad = TDF_ERR_TABLE_FULL;
+    r = (long long)pos;
+    x.sv[slot] = r;
+    x.present |= 1u << slot;
+    ++x.n_leaf;
+  }
+  v = r;
+  p = had || ok;
+  live = p;
+}
+// the same for a callee that is tried in its caller's sweep
+__device__ __forceinline__ void ln_embed_now(LaneX& x, bool go, long long av, long long& v, bool& p) {
+  const bool ok = go && av >= 0 && av < (long long)x.a->vocab;
+  if (go && !ok) x.bad = TDF_ERR_BAD_ARG;
+  const uint32_t pos = ln_log(x, ok);
+  if (ok) {
+    if (pos < x.a->log_cap) x.a->log[pos] = make_uint4((uint32_t)av, 0u, 0u, x.inst);
+    else x.bad = TDF_ERR_TABLE_FULL;
+    ++x.n_leaf;
+  }
+  v = (long long)pos;
+  p = ok;
+}
+// the iterations a loop graph has run in one sweep
+__device__ __forceinline__ void ln_loop(LaneX& x, uint32_t n, uint32_t n_vars) {
+  x.n_tags += n;
+  x.n_tokens += n * n_vars;
+  x.counter += n;
+  if (x.counter > 0xFFFFFFu) x.bad = TDF_ERR_STEP_LIMIT;
+  if (n) x.mx_depth = x.depth > x.mx_depth ? x.depth : x.mx_depth;
+}
+// RNN / LSTM cell: one log entry {left, right, level, instance}
+__device__ __forceinline__ void ln_cell(LaneX& x, bool on, int slot, bool ap, bool ad, long long av, bool bp, bool bd, long long bv,
+                                        long long& v, bool& p, bool& live) {
+  const bool had = on && ((x.present >> slot) & 1);
+  const bool go = on && ap && bp && !ad && !bd && !had;
+  const uint32_t pos = ln_log(x, go);
+  long long r = x.sv[slot];
+  if (go) {
+    const uint32_t la = (uint32_t)(av >> 32), lb = (uint32_t)(bv >> 32);
+    const uint32_t lvl = 1 + (la > lb ? la : lb);
+    if (pos < x.a->log_cap) x.a->log[pos] = make_uint4((uint32_t)av, (uint32_t)bv, lvl, x.inst);
+    else x.bad = TDF_ERR_TABLE_FULL;
+    r = (long long)pos | ((long long)lvl << 32);
+    x.sv[slot] = r;
+    x.present |= 1u << slot;
+    x.mx_level = lvl > x.mx_level ? lvl : x.mx_level;
+    ++x.n_cell;
+  }
+  v = r;
+  p = had || go;
+  live = p;
+}
+__device__ __forceinline__ void ln_ce_node(LaneX& x, long long row, long long v, bool& dead) {
+  const LaneArgs& a = *x.a;
+  if (v < 0 || v >= a.n_tree_nodes || a.row_node == nullptr) {
+    x.bad = TDF_ERR_BAD_ARG;
+    dead = true;
+    return;
+  }
+  if ((uint32_t)row < a.log_cap) a.row_node[(uint32_t)row] = (uint32_t)v;
+}
+__device__ __forceinline__ void ln_head(LaneX& x, bool on, int slot, bool ap, bool ad, long long av, bool bp, bool bd, long long bv,
+                                        long long& v, bool& p, bool& live) {
+  const bool had = on && ((x.present >> slot) & 1);
+  const bool go = on && ap && bp && !ad && !bd && !had;
+  if (go) {
+    x.a->head_row[x.inst] = (uint32_t)av;
+    x.a->root_lvl[x.inst] = (uint32_t)(av >> 32);
+    x.a->head_label[x.inst] = (uint32_t)bv;
+    x.sv[slot] = x.inst;
+    x.present |= 1u << slot;
+  }
+  v = (long long)x.inst;
+  p = had || go;
+  live = p;
+}
+__device__ __forceinline__ void ln_result(LaneX& x, int type, long long v) {
+  if (type == T_INT) { if (x.a->out_i64) x.a->out_i64[x.inst] = v; }
+  else if (type == T_VEC) {
+    x.a->root_ref[x.inst] = (uint32_t)v;
+    x.a->root_lvl[x.inst] = (uint32_t)(v >> 32);
+  }
+}
+
+// ---- the machine ----------------------------------------------------------------------------------
+// SW (generated): kStored (stored values per frame), kResultFn, kBranching (a function can have two calls
+// under way at once), sweep(x), ret_bits(fn, opened) (stored values that the opened calls return into),
+// outstanding(fn, opened, present) (opened calls whose value is not there), ret_slot(label).
+template <class SW>
+__device__ void lanes_run(const LaneArgs& a, char* lds) {
+  constexpr int NS = SW::kStored, NC = lane_chunks(NS);
+  uint4* const win = reinterpret_cast<uint4*>(lds);                       // [LANE_WINDOW][NC][64]
+  // records: stored values, then one array per field; `po` = present values | opened calls << 24
+  unsigned long long* const r_val = reinterpret_cast<unsigned long long*>(win + LANE_WINDOW * NC * 64);   // [NS][LANE_RECS]
+  uint32_t* const r_parent = reinterpret_cast<uint32_t*>(r_val + NS * LANE_RECS);
+  uint32_t* const r_meta = r_parent + LANE_RECS;      // label | function << 16 | nothing outstanding << 31
+  uint32_t* const r_counter = r_meta + LANE_RECS;
+  uint32_t* const r_depth = r_counter + LANE_RECS;
+  uint32_t* const r_po = r_depth + LANE_RECS;
+  uint32_t* const r_inst = r_po + LANE_RECS;
+  uint32_t* const r_join = r_inst + LANE_RECS;        // calls outstanding, plus one for the lane or task that has the frame
+  uint32_t* const lfree = r_join + LANE_RECS;         // [LANE_RECS] free record ids
+  uint32_t* const lq = lfree + LANE_RECS;             // [LANE_QUEUE] tasks
+  uint32_t* const sent = lq + LANE_QUEUE;             // [64] calls sent to other waves: record | slot << 16
+  const uint32_t lane = threadIdx.x, wave = blockIdx.x;
+  LaneReply* const reply = a.reply + (size_t)wave * 64 + lane;
+  LaneCtl* const ctl = a.ctl;
+
+  LaneX x;
+  x.a = &a;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) x.sv[k] = x.arg[k] = 0;
+  x.st = x.present = x.label = x.counter = x.depth = x.inst = 0;
+  x.c_st = x.c_np = x.c_label = x.c_back = 0;
+  x.act = ACT_NONE;
+  x.run = x.more = false;
+  x.ret = 0;
+  x.log_next = wave * LANE_CHUNK;   // (the first chunks of the log are dealt out)
+  x.log_end = a.log_cap ? x.log_next + LANE_CHUNK : x.log_next;
+  x.n_tags = x.n_tokens = x.n_leaf = x.n_cell = x.mx_depth = x.mx_level = 0;
+  x.bad = 0;
+  x.pf_v = -1;
+  x.pf_l = x.pf_r = x.pf_t = 0;
+  // The lane's stack: frames bs .. sp - 1 (the frame in registers is on top of them), of which those from lo
+  // on lie in the LDS window and the others in a list of segments in memory: frame d in a segment whose
+  // frames start at a multiple of LANE_SEG, `seg` the one of frame lo - 1, `seg_b` the one of frame bs.  `slack`
+  // frames have a ready call left.  (The first frame of an empty stack has number 0: bs is reset then.)
+  bool active = false;
+  uint32_t sp = 0, bs = 0, lo = 0, slack = 0, seg = LANE_NONE, seg_b = LANE_NONE;
+  uint32_t spare = wave * 64u + lane;     // segments the lane has and does not use (a list); it starts with one
+  // The bottom frame (frame bs, or the one in registers if the stack is empty): its record, if it has one, and
+  // its caller: a record, a call from another wave, or none.
+  uint32_t rec = LANE_NONE, parent = LANE_NONE;
+  bool resumed = false;                   // the bottom frame has nothing outstanding in other lanes
+  uint32_t mx_sp = 0;
+  // wave-uniform
+  const long long t_start = wall_clock64();
+  uint32_t qh = 0, qt = 0, nfree = LANE_RECS, iter = 0, syncs = 0, ticket = 0, min_free = LANE_RECS;
+  unsigned long long sent_mask = 0;       // replies awaited, by lane
+  bool more_inst = true, stop = false, have_ticket = false;
+  uint32_t n_own = 0, n_mine = 0, hungry = 0;   // instances of this wave that are not done; those taken since the last report
+  bool starving = false;                  // the queue looked at last had several waves waiting
+  // With every lane busy on work of its own a wave would have none to send a call to a wave without work: where
+  // several waves share a recursion the last two lanes do that and nothing else.
+  const unsigned long long exporter = a.n_waves > 1 && SW::kBranching ? 3ull << 62 : 0ull;
+  for (uint32_t k = lane; k < LANE_RECS; k += 64) lfree[k] = k;
+  a.segs[(size_t)spare * lane_seg_units(NS)].x = LANE_NONE;
+
+  auto seg_at = [&](uint32_t id) { return a.segs + (size_t)id * lane_seg_units(NS); };
+  auto win_put = [&](uint32_t d, const uint4 (&c)[NC]) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) win[((d % LANE_WINDOW) * NC + k) * 64 + lane] = c[k];
+  };
+  auto win_get = [&](uint32_t d, uint4 (&c)[NC]) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) c[k] = win[((d % LANE_WINDOW) * NC + k) * 64 + lane];
+  };
+  auto mem_get = [&](uint32_t id, uint32_t d, uint4 (&c)[NC]) {
+    const uint4* f = seg_at(id) + 1 + (d % LANE_SEG) * NC;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) c[k] = f[k];
+  };
+  // a segment is empty: to the lane's list
+  auto drop_seg = [&](uint32_t id) {
+    seg_at(id)[0].x = spare;
+    spare = id;
+  };
+  // frame on the stack: {state | slot awaited << 20 | ready call left << 25 | label << 26, counter, depth, present} values
+  auto pack = [&](uint4 (&c)[NC], uint32_t back_st, bool more) {
+    c[0] = make_uint4(back_st | (more ? 1u << 25 : 0u) | (x.label << 26), x.counter, x.depth, x.present);
+#pragma unroll
+    for (int k = 1; k < NC; ++k) {
+      const long long u = x.sv[2 * k - 2], v = 2 * k - 1 < NS ? x.sv[(2 * k - 1) & 7] : 0;
+      c[k] = make_uint4((uint32_t)u, (uint32_t)(u >> 32), (uint32_t)v, (uint32_t)(v >> 32));
+    }
+  };
+  auto unpack = [&](const uint4 (&c)[NC]) {
+    x.st = c[0].x & 0xFFFFFu;
+    x.label = c[0].x >> 26;
+    x.counter = c[0].y;
+    x.depth = c[0].z;
+    x.present = c[0].w;
+#pragma unroll
+    for (int k = 1; k < NC; ++k) {
+      x.sv[2 * k - 2] = (long long)((unsigned long long)c[k].x | ((unsigned long long)c[k].y << 32));
+      if (2 * k - 1 < NS) x.sv[(2 * k - 1) & 7] = (long long)((unsigned long long)c[k].z | ((unsigned long long)c[k].w << 32));
+    }
+  };
+  auto set_slot = [&](uint32_t slot, long long v) {
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+      x.sv[k] = (uint32_t)k == slot ? v : x.sv[k];
+    x.present |= 1u << slot;
+  };
+  // the frame of a record becomes the lane's own (bottom) frame
+  auto load_rec = [&](bool on, uint32_t id) {
+    if (on) {
+#pragma unroll
+      for (int k = 0; k < NS; ++k) x.sv[k] = (long long)r_val[k * LANE_RECS + id];
+      parent = r_parent[id];
+      const uint32_t m = r_meta[id], po = r_po[id], fn = (m >> 16) & 7u, opened = po >> 24;
+      x.label = m & 0xFFFFu;
+      x.counter = r_counter[id];
+      x.depth = r_depth[id];
+      x.present = po & 0xFFFFFFu;
+      x.st = lane_state(fn, opened, SW::outstanding(fn, opened, x.present));
+      x.inst = r_inst[id];
+      rec = id;
+      sp = bs = lo = slack = 0;
+      resumed = (m >> 31) != 0;
+      active = x.run = true;
+    }
+  };
+  auto free_recs = [&](bool on, uint32_t id) {   // whole wave
+    const unsigned long long m = __ballot(on);
+    if (m == 0) return;
+    if (on) lfree[nfree + (uint32_t)__popcll(m & lanemask_lt())] = id;
+    nfree += (uint32_t)__popcll(m);
+  };
+  auto push_tasks = [&](bool on, uint32_t id) {  // whole wave
+    const unsigned long long m = __ballot(on);
+    if (m == 0) return;
+    if (on) lq[(qt + (uint32_t)__popcll(m & lanemask_lt())) % LANE_QUEUE] = id;
+    qt += (uint32_t)__popcll(m);
+  };
+  // Everything a frame has opened has come back: it is a task again.
+  auto resume = [&](bool on, uint32_t id) {      // whole wave
+    if (on) {
+      r_join[id] = 1u;
+      r_meta[id] |= 1u << 31;
+    }
+    push_tasks(on, id);
+  };
+  // A value for a record; true for the lane that delivers the last one awaited (it, or a task, goes on with the frame).
+  auto deliver = [&](uint32_t id, uint32_t slot, long long v) -> bool {
+    r_val[slot * LANE_RECS + id] = (unsigned long long)v;
+    atomicOr(&r_po[id], 1u << slot);
+    return atomicSub(&r_join[id], 1u) == 1u;
+  };
+  // Waves are spread over several queues, so that their tickets and polls do not meet on one line: a wave
+  // waits at its own queue (wave % n_queues) and looks for waiting waves at one queue after the other.
+  auto mail_slot = [&](uint32_t q, uint32_t t) { return a.mail + (size_t)q * a.queue_cap + (t & (a.queue_cap - 1)); };
+  const uint32_t my_queue = wave % a.n_queues;
+  uint32_t look = my_queue, send_queue = 0;   // the queue looked at next; the one `hungry` counts at
+  // Pills for every wave: sent once, by the wave that saw the last instance finish or the first error.
+  auto send_home = [&]() {
+    if (lane < a.n_queues) {
+      const uint32_t n = (a.n_waves - lane + a.n_queues - 1) / a.n_queues;   // waves of that queue
+      const uint32_t t0 = lane_add(&a.queues[lane].tail, n);
+      for (uint32_t k = 0; k < n; ++k) lane_put(&mail_slot(lane, t0 + k)->flag, LANE_PILL);
+    }
+  };
+  auto raise_status = [&]() {   // whole wave
+    const unsigned long long m = __ballot(x.bad != 0);
+    if (m == 0) return;
+    const int code = __shfl(x.bad, __ffsll((long long)m) - 1);
+    uint32_t was = 1;
+    if (lane == 0) {
+      uint32_t expect = 0;
+      was = __hip_atomic_compare_exchange_strong(&ctl->status, &expect, (uint32_t)(-code), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT) ? 0u : 1u;
+    }
+    if (__builtin_amdgcn_readfirstlane((int)was) == 0) send_home();
+    stop = true;
+  };
+  // The wave's instances are done (they end in the wave they began in): counted per queue, then over the
+  // queues; the last one sends everybody home.
+  auto instances_done = [&]() {
+    bool all = false;
+    if (lane == 0) {
+      const uint32_t n = (a.n_inst + a.n_queues - 1u - my_queue) / a.n_queues;
+      all = lane_add(&a.queues[my_queue].inst_done, n_mine) + n_mine == n && lane_add(&ctl->queues_done, 1u) + 1u == min(a.n_queues, a.n_inst);
+    }
+    n_mine = 0;
+    if (__ballot(all)) {
+      send_home();
+      stop = true;
+    }
+  };
+  // values of calls that were sent to other waves; whole wave
+  auto poll_replies = [&]() {
+    const bool mine = ((sent_mask >> lane) & 1ull) != 0;
+    const bool got = mine && lane_ld(&reply->flag) == 1ull;
+    const unsigned long long m = __ballot(got);
+    if (m == 0) return;
+    bool last = false;
+    uint32_t id = 0;
+    if (got) {
+      const long long v = (long long)lane_ld(&reply->value);
+      lane_put(&reply->flag, 0ull);
+      id = sent[lane] & 0xFFFFu;
+      last = deliver(id, sent[lane] >> 16, v);
+    }
+    sent_mask &= ~m;
+    resume(last, id);
+  };
+
+  // A call from another wave becomes a record and a task (there is a free record).
+  auto take_mail = [&](LaneMail* slot) {
+    have_ticket = false;
+    uint32_t id = 0;
+    if (lane == 0) {
+      id = lfree[nfree - 1];
+      const unsigned long long w0 = lane_ld(&slot->from), w1 = lane_ld(&slot->meta), w2 = lane_ld(&slot->inst_np);
+      unsigned long long v8[8];
+#pragma unroll
+      for (int k = 0; k < NS; ++k) v8[k] = lane_ld(&slot->arg[k]);
+#pragma unroll
+      for (int k = 0; k < NS; ++k) r_val[k * LANE_RECS + id] = v8[k];
+      r_parent[id] = (uint32_t)w0;
+      r_meta[id] = (uint32_t)w1 | (lane_fn((uint32_t)(w0 >> 32)) << 16);
+      r_counter[id] = 0;
+      r_depth[id] = (uint32_t)(w1 >> 32);
+      r_po[id] = (1u << (uint32_t)(w2 >> 32)) - 1u;
+      r_inst[id] = (uint32_t)w2;
+      r_join[id] = 1u;
+      lane_put(&slot->flag, LANE_EMPTY);
+    }
+    --nfree;
+    min_free = min(min_free, nfree);
+    push_tasks(lane == 0, id);
+  };
+
+  while (!stop) {
+    // ---- idle lanes take a task of the wave, an empty wave takes instances, or a ticket of the global queue
+    if (sent_mask) poll_replies();
+    // (a wave that found work again while it holds a ticket: what is sent to it joins its tasks)
+    if (have_ticket && nfree) {
+      LaneMail* const slot = mail_slot(my_queue, ticket);
+      const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
+      if (v == LANE_PILL) break;
+      if (v == LANE_TASK) take_mail(slot);
+    }
+    {
+      const unsigned long long idle = ~__ballot(active);
+      if (idle) {
+        const uint32_t nq = qt - qh;
+        if (nq) {
+          // (the last lanes work for waves without work only: see the sharing below)
+          const unsigned long long can = hungry || idle == ~0ull ? idle : idle & ~exporter;
+          const uint32_t r = (uint32_t)__popcll(can & lanemask_lt()), n = min(nq, (uint32_t)__popcll(can));
+          const bool on = ((can >> lane) & 1ull) && r < n;
+          const uint32_t id = on ? lq[(qh + r) % LANE_QUEUE] : 0;
+          qh += n;
+          load_rec(on, id);
+        } else if (idle == ~0ull) {
+          if (more_inst) {
+            // instances q, q + n_queues, ... belong to queue q
+            const uint32_t in_queue = (a.n_inst + a.n_queues - 1u - my_queue) / a.n_queues;
+            uint32_t base = in_queue;
+            if (lane == 0 && in_queue) base = lane_add(&a.queues[my_queue].next_inst, a.per_grab);
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+            if (base >= in_queue) {
+              more_inst = false;
+              continue;
+            }
+            const uint32_t got = min(a.per_grab, in_queue - base);
+            n_own += got;
+            n_mine += got;
+            if (lane < got) {
+              const uint32_t b = my_queue + a.n_queues * (base + lane);
+#pragma unroll
+              for (int k = 0; k < NS; ++k)
+                x.sv[k] = k < a.n_args ? a.args[(size_t)b * a.n_args + k] : 0ll;
+              x.present = (1u << a.n_args) - 1u;
+              x.st = lane_state(SW::kResultFn, 0u, 0u);
+              x.label = x.counter = x.depth = 0;
+              x.inst = b;
+              rec = parent = LANE_NONE;
+              sp = bs = lo = slack = 0;
+              resumed = false;
+              active = x.run = true;
+            }
+            continue;
+          }
+          // nothing left in this wave: wait for a task, for a value, or to be sent home
+          if (!have_ticket) {
+            uint32_t t = 0;
+            if (lane == 0) t = lane_add(&a.queues[my_queue].head, 1u);
+            ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+            have_ticket = true;
+          }
+          LaneMail* const slot = mail_slot(my_queue, ticket);
+          const long long t0 = wall_clock64();
+          uint32_t v = LANE_EMPTY;
+          for (;;) {
+            v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
+            if (v != LANE_EMPTY) break;
+            if (sent_mask) {
+              poll_replies();
+              if (qt != qh) break;
+            }
+            __builtin_amdgcn_s_sleep(4);
+            if (wall_clock64() - t0 > a.idle_ticks) {
+              if (sent_mask || nfree != LANE_RECS) {   // others still work on what this wave waits for: look whether they gave up
+                if (lane_ld(&ctl->status) != 0 || wall_clock64() - t_start > a.run_ticks) {
+                  if (lane == 0) x.bad = TDF_ERR_STEP_LIMIT;
+                  raise_status();
+                  v = LANE_PILL;
+                  break;
+                }
+                continue;
+              }
+              uint32_t got = LANE_EMPTY;   // leave; whoever comes to this slot sees that
+              if (lane == 0) {
+                uint32_t expect = LANE_EMPTY;
+                if (!__hip_atomic_compare_exchange_strong(&slot->flag, &expect, LANE_LEFT, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT))
+                  got = expect;
+              }
+              v = (uint32_t)__builtin_amdgcn_readfirstlane((int)got);
+              if (v == LANE_EMPTY) v = LANE_PILL;
+              break;
+            }
+          }
+          if (v == LANE_PILL) break;
+          if (v == LANE_TASK) take_mail(slot);
+          continue;
+        }
+      }
+    }
+
+    // ---- a few sweeps
+    bool any_done = false;
+    const uint32_t n_run = (uint32_t)__popcll(__ballot(x.run));
+    const uint32_t n_sweeps = n_run >= 48 ? LANE_SYNC_FULL : hungry ? 2u : LANE_SYNC;
+#pragma unroll 1
+    for (uint32_t k = 0; k < n_sweeps; ++k) {
+      if (__ballot(x.run) == 0) break;
+      ++iter;
+      if (x.run) x.act = ACT_NONE;
+      SW::sweep(x);
+      if (hungry) {
+        // Waves without work: a call of a frame that has a record goes there, as far as there are reply places.
+        const bool can = x.run && x.act == ACT_CALL && sp == bs && rec != LANE_NONE;
+        const unsigned long long cm = __ballot(can);
+        const uint32_t r = (uint32_t)__popcll(cm & lanemask_lt());
+        const uint32_t n = min(min((uint32_t)__popcll(cm), hungry), 64u - (uint32_t)__popcll(sent_mask));
+        if (n) {
+          unsigned long long places = ~sent_mask;   // the lane's: the r-th free one
+          for (uint32_t k2 = 0; k2 < n; ++k2) places = k2 < r ? places & (places - 1ull) : places;
+          const uint32_t place = (uint32_t)__ffsll((long long)places) - 1u;
+          // tickets without a call, reserved: never more calls than tickets, so that no call waits for a wave
+          uint32_t t0 = 0, n_got = 0;
+          if (lane == 0) {
+            unsigned long long* q = reinterpret_cast<unsigned long long*>(&a.queues[send_queue].head);
+            unsigned long long was = lane_ld(q);
+            for (int tries = 0; tries < 16; ++tries) {
+              const int open = (int)((uint32_t)was - (uint32_t)(was >> 32));
+              if (open <= 0) break;
+              const uint32_t m = min((uint32_t)open, n);
+              if (__hip_atomic_compare_exchange_strong(q, &was, was + ((unsigned long long)m << 32), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT)) {
+                t0 = (uint32_t)(was >> 32);
+                n_got = m;
+                break;
+              }
+            }
+          }
+          t0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)t0);
+          n_got = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_got);
+          bool on = can && r < n_got;
+          if (on) {
+            LaneMail* const slot = mail_slot(send_queue, t0 + r);
+            lane_put(&slot->from, (unsigned long long)(LANE_REMOTE | (wave << 6) | place) | ((unsigned long long)x.c_st << 32));
+            lane_put(&slot->meta, (unsigned long long)x.c_label | ((unsigned long long)(x.depth + 1u) << 32));
+            lane_put(&slot->inst_np, (unsigned long long)x.inst | ((unsigned long long)x.c_np << 32));
+#pragma unroll
+            for (int k2 = 0; k2 < NS; ++k2) lane_put(&slot->arg[k2], (unsigned long long)x.arg[k2]);
+            __builtin_amdgcn_s_waitcnt(0);
+            const long long w0 = wall_clock64();
+            for (;;) {
+              uint32_t expect = LANE_EMPTY;
+              if (__hip_atomic_compare_exchange_strong(&slot->flag, &expect, LANE_TASK, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT))
+                break;
+              if (expect == LANE_LEFT) {   // that wave has left: the slot is free again, the call stays here
+                lane_put(&slot->flag, LANE_EMPTY);
+                on = false;
+                break;
+              }
+              // (the slot's last call is about to be taken: there are far more slots than waves at the queue)
+              if (wall_clock64() - w0 > a.idle_ticks) {
+                x.bad = TDF_ERR_DEVICE;
+                break;
+              }
+            }
+          }
+          if (on) {
+            sent[place] = rec | (((x.c_back >> 20) & 31u) << 16);
+            // the call is opened; its value is outstanding
+            ++x.n_tags;
+            x.n_tokens += x.c_np;
+            x.mx_depth = x.depth + 1u > x.mx_depth ? x.depth + 1u : x.mx_depth;
+            atomicAdd(&r_join[rec], 1u);
+            const uint32_t fn = lane_fn(x.st), opened = lane_opened(x.c_back);
+            x.st = lane_state(fn, opened, SW::outstanding(fn, opened, x.present));
+            x.act = ACT_NONE;
+            resumed = false;
+          }
+          for (unsigned long long m = __ballot(on); m; m &= m - 1ull)
+            sent_mask |= 1ull << (uint32_t)__builtin_amdgcn_readlane((int)place, __ffsll((long long)m) - 1);
+          hungry = n_got < n ? 0u : hungry - n_got;
+        }
+      }
+      {
+        if (x.run && x.act == ACT_CALL) {
+          // the window's oldest frame makes room
+          if (sp - lo == LANE_WINDOW) {
+            if (lo % LANE_SEG == 0 || seg == LANE_NONE) {
+              uint32_t id = spare;
+              if (id != LANE_NONE) spare = seg_at(id)[0].x;
+              else id = lane_add(&ctl->n_seg, 1u);
+              if (id >= a.n_segs) {
+                x.bad = TDF_ERR_TABLE_FULL;
+                id = wave * 64u + lane;   // (its contents do not count any more)
+              }
+              seg_at(id)[0].x = seg;
+              if (seg != LANE_NONE) seg_at(seg)[0].y = id;
+              if (seg_b == LANE_NONE) seg_b = id;
+              seg = id;
+            }
+            uint4 c[NC];
+            win_get(lo, c);
+            uint4* f = seg_at(seg) + 1 + (lo % LANE_SEG) * NC;
+#pragma unroll
+            for (int k2 = 0; k2 < NC; ++k2) f[k2] = c[k2];
+            ++lo;
+          }
+          uint4 c[NC];
+          pack(c, x.c_back, x.more);
+          win_put(sp, c);
+          slack += x.more ? 1u : 0u;
+          ++sp;
+          mx_sp = sp - bs > mx_sp ? sp - bs : mx_sp;
+          x.st = x.c_st;
+          x.label = x.c_label;
+          x.counter = 0;
+          x.depth += 1;
+          x.present = (1u << x.c_np) - 1u;
+#pragma unroll
+          for (int j = 0; j < NS; ++j) x.sv[j] = x.arg[j];
+          ++x.n_tags;
+          x.n_tokens += x.c_np;
+          x.mx_depth = x.depth > x.mx_depth ? x.depth : x.mx_depth;
+        } else if (x.run && x.act == ACT_RET) {
+          if (sp > bs) {
+            ++x.n_tokens;
+            const long long v = x.ret;
+            --sp;
+            uint4 c[NC];
+            if (sp >= lo) {
+              win_get(sp, c);
+            } else {
+              mem_get(seg, sp, c);
+              lo = sp;
+              if (sp % LANE_SEG == 0 || sp == bs) {   // that was the segment's last frame
+                const uint32_t id = seg;
+                seg = sp == bs ? LANE_NONE : seg_at(id)[0].x;
+                if (sp == bs) seg_b = LANE_NONE;
+                drop_seg(id);
+              }
+            }
+            unpack(c);
+            slack -= (c[0].x >> 25) & 1u;
+            set_slot((c[0].x >> 20) & 31u, v);
+          } else {
+            x.run = false;   // to a record or another wave: below
+          }
+        }
+      }
+      if (__ballot(x.run && x.act > ACT_RET)) {
+        bool done = false, next_bottom = false;
+        if (!x.run) {
+        } else if (x.act == ACT_NEXT) {
+          if (x.counter >= 0xFFFFFFu) x.bad = TDF_ERR_STEP_LIMIT;
+          ++x.counter;
+          x.st = x.c_st;
+          x.present = (1u << x.c_np) - 1u;
+#pragma unroll
+          for (int j = 0; j < NS; ++j) x.sv[j] = x.arg[j];
+          ++x.n_tags;
+          x.n_tokens += x.c_np;
+          x.mx_depth = x.depth > x.mx_depth ? x.depth : x.mx_depth;
+          next_bottom = sp == bs && rec != LANE_NONE;
+        } else if (x.act == ACT_DONE) {
+          x.run = active = false;
+          done = true;
+        } else if (x.act == ACT_WAIT && sp == bs && rec != LANE_NONE && !resumed) {
+          x.run = false;     // below
+        } else if (x.act > ACT_RET) {
+          x.bad = x.bad ? x.bad : TDF_ERR_UNSUPPORTED;
+          x.run = false;
+        }
+        n_own -= (uint32_t)__popcll(__ballot(done));
+        any_done = any_done || __ballot(done) != 0;
+        // a finished iteration, or instance, whose frame had a record
+        free_recs((done || next_bottom) && rec != LANE_NONE, rec);
+        if (done || next_bottom) rec = LANE_NONE;
+      }
+    }
+    ++syncs;
+
+    // ---- values for records and for other waves, and frames that wait for others
+    {
+      const bool ret = active && !x.run && x.act == ACT_RET && x.bad == 0;
+      const bool wait = active && !x.run && x.act == ACT_WAIT && x.bad == 0;
+      if (__ballot(ret || wait)) {
+        const bool out = ret;
+        free_recs(out && rec != LANE_NONE, rec);
+        if (out) ++x.n_tokens;
+        const bool remote = out && (parent & LANE_REMOTE) != 0;
+        if (remote) {
+          LaneReply* const rp = a.reply + (parent & ~LANE_REMOTE);
+          lane_put(&rp->value, (unsigned long long)x.ret);
+          __builtin_amdgcn_s_waitcnt(0);
+          lane_put(&rp->flag, 1ull);
+        }
+        bool last = false;
+        uint32_t id = rec;
+        if (out && !remote) {
+          id = parent;
+          last = deliver(id, SW::ret_slot(x.label), x.ret);
+        }
+        if (wait) {   // (values of this lane; those outstanding may be written by others meanwhile)
+#pragma unroll
+          for (int k = 0; k < NS; ++k)
+            if ((x.present >> k) & 1) r_val[k * LANE_RECS + id] = (unsigned long long)x.sv[k];
+          atomicOr(&r_po[id], x.present | (lane_opened(x.st) << 24));
+          last = atomicSub(&r_join[id], 1u) == 1u;
+        }
+        if (out || wait) {
+          active = x.run = false;
+          x.act = ACT_NONE;
+        }
+        resume(last, id);   // (taken at once, most likely by this lane)
+      }
+    }
+    if (any_done && n_own == 0) {
+      instances_done();
+      if (stop) break;
+    }
+    raise_status();
+    if (stop) break;
+    if ((syncs & 15u) == 0) {
+      if (lane_ld(&ctl->status) != 0) break;
+      if (wall_clock64() - t_start > a.run_ticks) {
+        x.bad = TDF_ERR_STEP_LIMIT;
+        raise_status();
+        break;
+      }
+    }
+
+    // ---- sharing
+    {
+      const uint32_t nq = qt - qh;
+      const unsigned long long rich = __ballot(x.run && slack > 0);
+      const uint32_t n_idle = 64u - (uint32_t)__popcll(__ballot(active) | exporter);
+      // Calls go to other waves early on, while many of them have nothing, and later from waves whose own lanes
+      // are busy: a wave that runs out of work itself keeps what it has (it is little by then).
+      const bool early = iter < LANE_EARLY;
+      hungry = n_idle <= 16 || early ? hungry : 0u;
+      if (exporter && (rich || nq) && (early || (n_idle <= 16 && (starving || (syncs & 3u) == 0)))) {
+        const unsigned long long ht = lane_ld(reinterpret_cast<const unsigned long long*>(&a.queues[look].head));
+        send_queue = look;
+        look = look + 1u == a.n_queues ? 0u : look + 1u;
+        const int d = (int)((uint32_t)ht - (uint32_t)(ht >> 32));   // tickets without a task
+        hungry = (uint32_t)__builtin_amdgcn_readfirstlane(d > 0 ? d : 0);
+        starving = hungry >= 4u;
+        if (early && n_idle > 16 && hungry < 8u) hungry = 0;
+      }
+      // Tasks wanted: for the wave's idle lanes, and some for waves without work.  A lane gives the oldest
+      // frame of its stack that has a ready call left (the largest piece of work), and the frames below it.
+      const uint32_t want = n_idle + min(hungry, 16u);
+      bool going = x.run && slack > 0 && want > nq && (uint32_t)__popcll(rich & lanemask_lt()) < want - nq;
+      if (nfree >= 8 && __ballot(going)) {
+        uint32_t below = parent, d = bs;   // the caller of frame d
+        bool moved = false;
+        for (;;) {
+          const unsigned long long gm = __ballot(going);
+          if (gm == 0) break;
+          // a record each (as far as there are any: a lane without one keeps its frames)
+          const bool fresh = going && !(d == bs && rec != LANE_NONE);
+          const unsigned long long rm = __ballot(fresh);
+          const uint32_t rr = (uint32_t)__popcll(rm & lanemask_lt());
+          const bool ok = going && (!fresh || rr < nfree);
+          const uint32_t id = !fresh ? rec : ok ? lfree[nfree - 1 - rr] : 0u;
+          nfree -= min(nfree, (uint32_t)__popcll(rm));
+          min_free = min(min_free, nfree);
+          bool more = false;
+          if (ok) {
+            uint4 c[NC];
+            if (d >= lo) {
+              win_get(d, c);
+            } else {
+              mem_get(seg_b, d, c);
+              if (d % LANE_SEG == LANE_SEG - 1u || d + 1u == lo) {   // that was the segment's last frame
+                const uint32_t sid = seg_b;
+                seg_b = d + 1u == lo ? LANE_NONE : seg_at(sid)[0].y;
+                if (d + 1u == lo) seg = LANE_NONE;
+                drop_seg(sid);
+              }
+            }
+            more = ((c[0].x >> 25) & 1u) != 0;   // it becomes a task
+            const uint32_t fn = lane_fn(c[0].x), opened = lane_opened(c[0].x), present = c[0].w;
+            if (fresh) {
+              r_parent[id] = below;
+              r_meta[id] = (c[0].x >> 26) | (fn << 16);
+              r_counter[id] = c[0].y;
+              r_depth[id] = c[0].z;
+              r_inst[id] = x.inst;
+              r_join[id] = more ? 2u : 1u;
+              r_po[id] = present | (opened << 24);
+            } else {
+              r_meta[id] &= ~(1u << 31);
+              atomicOr(&r_po[id], present | (opened << 24));
+              if (more) atomicAdd(&r_join[id], 1u);   // one more call outstanding; the lane's own part goes to the task
+            }
+            // (all but the values outstanding, which others may have put there already; what is not present may
+            // be the argument of a call that waits)
+            const uint32_t others = SW::ret_bits(fn, opened) & ~present;
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+              const uint4 w = c[1 + k / 2];
+              const unsigned long long v = k & 1 ? ((unsigned long long)w.z | ((unsigned long long)w.w << 32))
+                                                 : ((unsigned long long)w.x | ((unsigned long long)w.y << 32));
+              if (!((others >> k) & 1)) r_val[k * LANE_RECS + id] = v;
+            }
+            slack -= more ? 1u : 0u;
+            below = id;
+            ++d;
+            moved = true;
+          }
+          push_tasks(ok && more, id);
+          going = ok && d < sp && !more;
+        }
+        if (moved) {
+          bs = d;
+          lo = lo > d ? lo : d;
+          parent = below;
+          rec = LANE_NONE;
+          resumed = false;
+        }
+      }
+    }
+  }
+
+  // ---- the wave's part of the log that was not used, and its counts
+  {
+    const uint32_t h0 = x.log_next;
+    for (uint32_t h = h0 + lane; h < x.log_end; h += 64)
+      if (h < a.log_cap) a.log[h].z = LANE_LOG_HOLE;
+    unsigned long long tags = x.n_tags, tokens = x.n_tokens;
+    uint32_t leaf = x.n_leaf, cell = x.n_cell, priv = mx_sp;
+    for (int off = 32; off > 0; off >>= 1) {
+      tags += __shfl_xor(tags, off);
+      tokens += __shfl_xor(tokens, off);
+      leaf += __shfl_xor(leaf, off);
+      cell += __shfl_xor(cell, off);
+      priv += __shfl_xor(priv, off);
+    }
+    const uint32_t md = wave_umax(x.mx_depth), ml = wave_umax(x.mx_level);
+    if (lane == 0 && iter) {   // (per queue, summed by the host)
+      LaneQueue* q = &a.queues[my_queue];
+      (void)lane_add(&q->n_tags, tags);
+      (void)lane_add(&q->n_tokens, tokens);
+      (void)lane_add(reinterpret_cast<unsigned long long*>(&q->n_leaf), (unsigned long long)leaf | ((unsigned long long)cell << 32));
+      (void)lane_add(reinterpret_cast<unsigned long long*>(&q->n_rec), (unsigned long long)(LANE_RECS - min_free) | ((unsigned long long)priv << 32));
+      atomicMax(&q->max_depth, md);
+      if (ml) atomicMax(&q->max_level, ml);
+      atomicMax(&q->max_iter, iter);
+    }
+  }
+}
+
+#endif
+}  // namespace tdf

@@ -3,7 +3,10 @@
 // counts and the bucketing of the cell log by dependency level.
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "bucket.h"
+#include "lane_device.h"
 #include "step_device.h"
 #include "tdf_internal.h"
 
@@ -260,6 +263,131 @@ tdf_status launch_round(const DevProgram& P, const Engine& e, int cus, bool loca
   return TDF_OK;
 }
 
+// ---- depth-first lanes ------------------------------------------------------------------------
+__global__ void k_lane_init(LaneArgs a) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) {
+    *a.ctl = LaneCtl{};
+    a.ctl->log_used = a.log_cap ? a.n_waves * LANE_CHUNK : 0u;
+    a.ctl->n_seg = a.n_waves * 64u;
+  }
+  if (i < a.n_queues) a.queues[i] = LaneQueue{};
+  for (uint32_t k = i; k < a.n_queues * a.queue_cap; k += gridDim.x * blockDim.x) a.mail[k].flag = LANE_EMPTY;
+  for (uint32_t k = i; k < a.n_waves * 64u; k += gridDim.x * blockDim.x) a.reply[k].flag = 0ull;
+  if (a.row_node)
+    for (uint32_t k = i; k < a.log_cap; k += gridDim.x * blockDim.x) a.row_node[k] = 0xFFFFFFFFu;
+}
+tdf_status launch_lanes(const LaneArgs& a, int n_stored, const JitKernels& jit, hipStream_t s) {
+  hipLaunchKernelGGL(k_lane_init, dim3(grid_for(std::max(a.n_waves * 64, a.row_node ? a.log_cap : 0u), 256, 256)), dim3(256), 0, s, a);
+  LaneArgs av = a;
+  void* args[] = {&av};
+  const hipError_t r = hipModuleLaunchKernel((hipFunction_t)jit.lanes, a.n_waves, 1, 1, 64, 1, 1, (unsigned)lane_lds_bytes(n_stored), s,
+                                             args, nullptr);
+  if (r != hipSuccess) {
+    set_error(std::string("launch of the generated lane kernel failed: ") + hipGetErrorString(r));
+    return TDF_ERR_DEVICE;
+  }
+  return TDF_OK;
+}
+
+// ---- rows from the lanes' schedule log -------------------------------------------------------------
+// The log holds leaves and cells as they fired, named by their place in it, with holes where a wave did not
+// use what it had reserved.  First pass: leaves get rows 0 .. n_leaf - 1 (a range per workgroup), cells are
+// counted by sort key; then the scan of the counts; second pass: cells get their places in the sorted
+// schedule.  Both passes write row_of[name], with which k_translate_rows turns the children's names into rows.
+// Memory bound in principle, launch bound at the sizes it runs at: hence two passes over the log instead
+// of separate merge, class, count, number and place kernels.
+struct LaneSort {
+  const uint4* log;
+  uint32_t n_log, n_keys, deep_level, deep_base;   // deep_level 0: one class
+  uint32_t *row_of, *leaf_next;
+  const uint32_t* row_node;
+  int lds_keys;                                     // the counts of a workgroup fit in LDS
+};
+__device__ __forceinline__ uint32_t lane_key(const Engine& e, const LaneSort& t, const uint4& c) {
+  const uint32_t deep = t.deep_level && e.root_lvl[c.w] >= t.deep_level ? t.deep_base : 0u;
+  return deep + c.z * LEVEL_KEY_DIES + c.w % e.n_dies;
+}
+__global__ void __launch_bounds__(BUCKET_THREADS) k_lane_rows(Engine e, LaneSort t) {
+  extern __shared__ uint32_t hist[];
+  __shared__ uint32_t n_leaf, leaf0;
+  const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t.deep_level)
+    for (uint32_t i = gid; i < e.n_inst; i += gridDim.x * blockDim.x) e.inst_class[i] = e.root_lvl[i] >= t.deep_level ? 1u : 0u;
+  const uint32_t per = (t.n_log + gridDim.x - 1) / gridDim.x;
+  const uint32_t lo = min(t.n_log, blockIdx.x * per), hi = min(t.n_log, lo + per);
+  if (t.lds_keys)
+    for (uint32_t k = threadIdx.x; k < t.n_keys; k += blockDim.x) hist[k] = 0;
+  if (threadIdx.x == 0) n_leaf = 0;
+  __syncthreads();
+  for (uint32_t base = lo; base < hi; base += blockDim.x) {   // uniform trip count for the workgroup
+    const uint32_t i = base + threadIdx.x;
+    uint4 c = make_uint4(0u, 0u, LANE_LOG_HOLE, 0u);
+    if (i < hi) c = t.log[i];
+    (void)wave_alloc(c.z == 0u, &n_leaf);
+    const bool cell = c.z != 0u && c.z != LANE_LOG_HOLE;
+    (void)wave_alloc_keyed(cell, cell ? lane_key(e, t, c) : 0u, t.lds_keys ? hist : e.level_count);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    leaf0 = n_leaf ? atomicAdd(t.leaf_next, n_leaf) : 0u;
+    n_leaf = 0;
+  }
+  __syncthreads();
+  for (uint32_t base = lo; base < hi; base += blockDim.x) {
+    const uint32_t i = base + threadIdx.x;
+    uint4 c = make_uint4(0u, 0u, LANE_LOG_HOLE, 0u);
+    if (i < hi) c = t.log[i];
+    const uint32_t row = leaf0 + wave_alloc(c.z == 0u, &n_leaf);
+    if (c.z == 0u) {
+      e.leaf_tok[row] = c.x;
+      t.row_of[i] = row;
+      if (e.node_of_row) e.node_of_row[row] = t.row_node[i];
+    }
+  }
+  if (t.lds_keys)
+    for (uint32_t k = threadIdx.x; k < t.n_keys; k += blockDim.x)
+      if (hist[k]) atomicAdd(&e.level_count[k], hist[k]);
+}
+__global__ void __launch_bounds__(BUCKET_THREADS) k_lane_place(Engine e, LaneSort t) {
+  extern __shared__ uint32_t hist[];
+  const uint32_t per = (t.n_log + gridDim.x - 1) / gridDim.x;
+  const uint32_t lo = min(t.n_log, blockIdx.x * per), hi = min(t.n_log, lo + per);
+  auto cell_at = [&](uint32_t i, uint4& c) {
+    c = make_uint4(0u, 0u, LANE_LOG_HOLE, 0u);
+    if (i < hi) c = t.log[i];
+    return c.z != 0u && c.z != LANE_LOG_HOLE;
+  };
+  if (t.lds_keys) {
+    for (uint32_t k = threadIdx.x; k < t.n_keys; k += blockDim.x) hist[k] = 0;
+    __syncthreads();
+    for (uint32_t base = lo; base < hi; base += blockDim.x) {
+      uint4 c;
+      const bool cell = cell_at(base + threadIdx.x, c);
+      (void)wave_alloc_keyed(cell, cell ? lane_key(e, t, c) : 0u, hist);
+    }
+    __syncthreads();
+    // the workgroup's range of every key it holds; the LDS entry becomes the next free position
+    for (uint32_t k = threadIdx.x; k < t.n_keys; k += blockDim.x)
+      if (hist[k]) hist[k] = e.level_off[k] + atomicAdd(&e.level_fill[k], hist[k]);
+    __syncthreads();
+  }
+  for (uint32_t base = lo; base < hi; base += blockDim.x) {
+    const uint32_t i = base + threadIdx.x;
+    uint4 c;
+    const bool cell = cell_at(i, c);
+    const uint32_t key = cell ? lane_key(e, t, c) : 0u;
+    uint32_t q = wave_alloc_keyed(cell, key, t.lds_keys ? hist : e.level_fill);
+    if (cell) {
+      if (!t.lds_keys) q += e.level_off[key];
+      e.q_l[q] = c.x;
+      e.q_r[q] = c.y;
+      t.row_of[i] = e.row0 + q;
+      if (e.node_of_row) e.node_of_row[e.row0 + q] = t.row_node[i];
+    }
+  }
+}
+
 // Copies the machines' logs into the merged logs; leaf_off / cell_off: n_dies + 1 prefix sums.
 void launch_merge_logs(const Engine& e, const uint32_t* leaf_off, const uint32_t* cell_off, hipStream_t s) {
   if (e.n_dies <= 1) return;   // one machine writes the merged logs directly
@@ -289,6 +417,43 @@ __global__ void k_class_keys(Engine e, DevProgram P, uint32_t n_cell, uint32_t d
 void launch_class_keys(const DevProgram& P, const Engine& e, uint32_t n_cell, uint32_t deep_level, uint32_t deep_base, hipStream_t s) {
   const uint32_t n = n_cell > e.n_inst ? n_cell : e.n_inst;
   hipLaunchKernelGGL(k_class_keys, dim3(grid_for(n, 256, 1 << 20)), dim3(256), 0, s, e, P, n_cell, deep_level, deep_base);
+}
+
+// The two passes over the lanes' log.  n_keys 0: no cells.
+static LaneSort lane_sort(const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base) {
+  LaneSort t{};
+  t.log = a.log;
+  t.n_log = n_log;
+  t.n_keys = n_keys;
+  t.deep_level = deep_level;
+  t.deep_base = deep_base;
+  t.row_of = a.row_of;
+  t.leaf_next = &a.ctl->leaf_next;
+  t.row_node = a.row_node;
+  t.lds_keys = bucket_fits(n_keys);
+  return t;
+}
+static int lane_sort_blocks(uint32_t n_log) { return grid_for(n_log, BUCKET_THREADS, BUCKET_BLOCKS); }
+void launch_lane_rows(const Engine& e, const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base,
+                      hipStream_t s) {
+  if (n_keys) {
+    if (e.level_fill > e.level_count) {   // (the two arrays lie one behind the other in the workspace: one fill)
+      (void)hipMemsetAsync(e.level_count, 0, (size_t)((char*)(e.level_fill + n_keys) - (char*)e.level_count), s);
+    } else {
+      (void)hipMemsetAsync(e.level_count, 0, sizeof(uint32_t) * n_keys, s);
+      (void)hipMemsetAsync(e.level_fill, 0, sizeof(uint32_t) * n_keys, s);
+    }
+  }
+  const LaneSort t = lane_sort(a, n_log, n_keys, deep_level, deep_base);
+  if (t.lds_keys) bucket_lds_opt_in(reinterpret_cast<const void*>(&k_lane_rows), n_keys);
+  hipLaunchKernelGGL(k_lane_rows, dim3(lane_sort_blocks(n_log)), dim3(BUCKET_THREADS), t.lds_keys ? (size_t)n_keys * 4 : 0, s, e, t);
+}
+void launch_lane_place(const Engine& e, const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base,
+                       hipStream_t s) {
+  const LaneSort t = lane_sort(a, n_log, n_keys, deep_level, deep_base);
+  if (t.lds_keys) bucket_lds_opt_in(reinterpret_cast<const void*>(&k_lane_place), n_keys);
+  hipLaunchKernelGGL(k_level_scan, dim3(1), dim3(1024), 0, s, e, n_keys);
+  hipLaunchKernelGGL(k_lane_place, dim3(lane_sort_blocks(n_log)), dim3(BUCKET_THREADS), t.lds_keys ? (size_t)n_keys * 4 : 0, s, e, t);
 }
 
 // Counting sort of the cell log by sort key (n_keys keys); level_off[k] = first cell of key k.

@@ -34,8 +34,14 @@ struct JitKernels {
   void* step_local = nullptr;   // ... and of its variant that keeps to one accelerator die
   void* small = nullptr;    // hipFunction_t of the single-workgroup kernel
   bool tried = false;
+  void* lanes_module = nullptr;   // hipModule_t of the depth-first lanes, compiled when an evaluation without frames first runs
+  void* lanes = nullptr;          // hipFunction_t
+  bool lanes_tried = false;
 };
 bool jit_compile(const DevProgram& P, JitKernels& out, std::string& log);
+bool jit_compile_lanes(const DevProgram& P, JitKernels& out, std::string& log);
+int lane_stored(const DevProgram& P);   // stored values of a frame (the largest function's)
+bool lane_branching(const DevProgram& P);   // a frame (other than of `result`) can have several calls or loops
 void jit_release(JitKernels& k);
 
 }  // namespace tdf
@@ -44,6 +50,7 @@ struct tdf_graph {
   tdf::Graph g;
   tdf::JitKernels jit;
   bool die_local = true;    // tag machines keep to one accelerator die each (cleared if the GPU spreads them)
+  bool lanes_ok = true;     // depth-first lanes (cleared once a run met something they leave to the step machine)
   uint32_t max_dies = 8;    // tag machines a batch is dealt to (set to 1 after a part of the table overflowed)
   void* events[2 * TDF_PHASE_COUNT] = {nullptr};   // hipEvent_t pairs, created on first use
   void* side_stream = nullptr;                     // hipStream_t for work beside the caller's stream
