@@ -1,7 +1,9 @@
 // Counting sort by a small integer key, for inputs in which a few keys are very frequent (the
 // lowest dependency levels hold most cells; token ids follow a Zipf law).  Every workgroup
 // counts its slice of the items in an LDS histogram first and touches each global counter
-// once, so a hot key costs one global atomic per workgroup instead of one per wave.
+// once, so a hot key costs one global atomic per workgroup instead of one per wave.  In LDS every lane counts for
+// itself: lanes with the same key take a clock each there, where finding them first takes some twenty instructions
+// per distinct key of the wave (262144 leaves over 20000 tokens: the two kernels 70 -> 41 us).
 #pragma once
 #include "engine.h"
 
@@ -19,7 +21,7 @@ __device__ inline void bucket_hist_lds(uint32_t* hist, const uint32_t* keys, uin
   for (uint32_t base = lo; base < hi; base += blockDim.x) {   // uniform trip count for the workgroup
     const uint32_t i = base + threadIdx.x;
     const uint32_t k = i < hi ? keys[i] : 0xFFFFFFFFu;
-    (void)wave_alloc_keyed(k < n_keys, k < n_keys ? k : 0, hist);
+    if (k < n_keys) atomicAdd(&hist[k], 1u);
   }
   __syncthreads();
 }
@@ -50,9 +52,7 @@ __global__ void __launch_bounds__(BUCKET_THREADS) k_bucket_place(const uint32_t*
   for (uint32_t base = lo; base < hi; base += blockDim.x) {
     const uint32_t i = base + threadIdx.x;
     const uint32_t k = i < hi ? keys[i] : 0xFFFFFFFFu;
-    const bool on = k < n_keys;
-    const uint32_t pos = wave_alloc_keyed(on, on ? k : 0, hist);
-    if (on) sink(i, pos);
+    if (k < n_keys) sink(i, atomicAdd(&hist[k], 1u));
   }
 }
 

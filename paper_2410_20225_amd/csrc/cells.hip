@@ -12,6 +12,7 @@
 #include "bucket.h"
 #include "die_sync.h"
 #include "engine.h"
+#include "lane_device.h"
 
 namespace tdf {
 
@@ -125,6 +126,7 @@ struct GemmArgs {
   int n_tiles_n;             // column tiles of the launch
   int save_gates;
   int narrow;                // LSTM_FWD: state rows and this level's gate rows end below 4 GiB
+  Stamp stamp;
 };
 
 constexpr int BM_FULL = 128;   // rows of a workgroup tile; half of it for levels that would not fill the GPU
@@ -137,6 +139,7 @@ constexpr int BM_FULL = 128;   // rows of a workgroup tile; half of it for level
 // no exchange between lanes; its workgroups are one such block wide (WNS = 1).
 template <int DT, int MODE, int NW, int BM, int WNS, bool NARROW = false>
 __global__ void __launch_bounds__(NW * 64, WNS == 1 ? 3 : 1) k_gemm(GemmArgs g) {
+  stamp_now(g.stamp);
   constexpr int GEMM_THREADS = NW * 64;
   constexpr int MB = BM * WNS / (32 * NW);       // 32-row blocks per wave (waves as NW/WNS x WNS)
   typedef typename TypeOf<DT>::type T;
@@ -715,6 +718,7 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
 template <int DT, int MODE, int NW>
 __global__ void __launch_bounds__(NW * 64) k_cell_small(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  stamp_now(g.stamp);
   const int n_ct = g.n_tiles_n;                    // column tiles of 32
   cell_small_tile<DT, MODE, NW>(g, blockIdx.x / n_ct, blockIdx.x % n_ct, reinterpret_cast<float*>(smem));
 }
@@ -753,10 +757,20 @@ template <typename T, int MODE> void launch_cell_small(GemmArgs g, int n_col_til
 }
 
 // ---- packing of W: padded, k-contiguous [Np x Kp], and its transpose [Kp x Np] ---------------
+// and what else an evaluation on the lanes clears before it starts (a launch for each would cost as much as
+// this whole kernel at ordinary sizes): the lanes' own records and `n_zero` 16-byte units from `zero` on.
+struct PrepArgs {
+  LaneArgs lanes;   // ctl null: W alone
+  uint4* zero;
+  size_t n_zero;
+};
 template <int DT>
-__global__ void k_pack_w(VecArgs v) {
+__global__ void k_pack_w(VecArgs v, PrepArgs p) {
   typedef typename TypeOf<DT>::type T;
-  const int total = v.Np * v.Kp;
+  const int total = v.cell_kind ? v.Np * v.Kp : 0;   // (a program of EMBEDs alone has no W)
+  stamp_now(v.stamp);
+  if (p.lanes.ctl) lane_init(p.lanes, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+  for (size_t i = blockIdx.x * blockDim.x + threadIdx.x; i < p.n_zero; i += gridDim.x * blockDim.x) p.zero[i] = make_uint4(0u, 0u, 0u, 0u);
   for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += gridDim.x * blockDim.x) {
     const int np = idx / v.Kp, kp = idx % v.Kp;
     const int gate = np / v.Hp, j = np % v.Hp, half = kp / v.Hp, i = kp % v.Hp;
@@ -778,8 +792,10 @@ __global__ void k_pack_w(VecArgs v) {
 // in 16-byte chunks where the rows of E are aligned for that (H a multiple of the chunk), else element by
 // element.
 template <int DT>
-__global__ void k_embed(VecArgs v, Engine e, uint32_t n_leaf, int lpl) {
+__global__ void k_embed(VecArgs v, Engine e, uint32_t n_leaf, const LaneTotals* t, int lpl) {
   typedef typename TypeOf<DT>::type T;
+  stamp_now(v.stamp);
+  if (t) n_leaf = t->bad ? 0u : t->n_leaf;   // (queued before the host knows how many)
   constexpr int EPC = 16 / (int)sizeof(T);
   const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, n_threads = gridDim.x * blockDim.x;
   if (v.cell_kind == 2 && tid < (uint32_t)v.Hp) v.Cs[tid] = 0.f;   // (Hp <= 8192 <= threads of the launch: see vec_embed)
@@ -805,6 +821,7 @@ __global__ void k_embed(VecArgs v, Engine e, uint32_t n_leaf, int lpl) {
 template <int DT>
 __global__ void k_head(VecArgs v, Engine e, const float* dy, int with_grad, int cls) {
   typedef typename TypeOf<DT>::type T;
+  stamp_now(v.stamp);
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63;
   if (wave >= (int)e.n_inst) return;
   if (cls >= 0 && (int)e.inst_class[wave] != cls) return;   // only the instances of one class
@@ -847,6 +864,7 @@ __global__ void __launch_bounds__(256) k_node_ce(VecArgs v, Engine e, uint32_t n
   typedef typename TypeOf<DT>::type T;
   constexpr int CH = 16 / (int)sizeof(T);   // elements of a 16-byte chunk of a state row
   extern __shared__ __attribute__((aligned(16))) float sU[];
+  stamp_now(v.stamp);
   if (u_in_lds) {
     for (int i = threadIdx.x; i < v.n_classes * v.Hp; i += blockDim.x) {
       const int c = i / v.Hp, n = i % v.Hp;
@@ -938,6 +956,7 @@ __global__ void __launch_bounds__(256) k_node_ce(VecArgs v, Engine e, uint32_t n
 
 // vector result: seed dH of each root row with the caller's dy (none: zero); copy the root rows out
 __global__ void k_seed_dy(VecArgs v, Engine e, const float* dy) {
+  stamp_now(v.stamp);
   const int b = blockIdx.x;
   const uint32_t row = e.root_ref[b];
   for (int n = threadIdx.x; n < v.Hp; n += blockDim.x) {
@@ -949,6 +968,7 @@ __global__ void k_seed_dy(VecArgs v, Engine e, const float* dy) {
 template <int DT>
 __global__ void k_out_rows(VecArgs v, Engine e, float* out_h, float* out_c) {
   typedef typename TypeOf<DT>::type T;
+  stamp_now(v.stamp);
   const int b = blockIdx.x;
   const uint32_t row = e.root_ref[b];
   for (int n = threadIdx.x; n < v.H; n += blockDim.x) {
@@ -1012,6 +1032,7 @@ template <> __device__ __forceinline__ void store4<__bf16>(__bf16* p, f32x4 x) {
 template <int DT>
 __global__ void __launch_bounds__(256) k_dz(VecArgs v, Engine e, uint32_t q0, uint32_t count) {
   typedef typename TypeOf<DT>::type T;
+  stamp_now(v.stamp);
   const int group = min(256, v.Hp / 4), per_block = 256 / group;
   const int gi = threadIdx.x / group, gl = threadIdx.x % group;
   const uint32_t k = blockIdx.x * per_block + gi;
@@ -1077,6 +1098,7 @@ __global__ void __launch_bounds__(NW * 64) k_tail_fwd(GemmArgs g, TailArgs t) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ uint32_t sh_ok;
   float* part = reinterpret_cast<float*>(smem);
+  stamp_now(g.stamp);
   const uint32_t die = blockIdx.x % XCDS, rank = blockIdx.x / XCDS, G = gridDim.x / XCDS;
   if (die >= t.n_dies) return;
   // A level here is one link of a dependency chain: these waves are bound by latency, and other
@@ -1119,6 +1141,7 @@ __global__ void __launch_bounds__(NW * 64) k_tail_bwd(GemmArgs g, VecArgs v, Eng
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ uint32_t sh_ok;
   float* part = reinterpret_cast<float*>(smem);
+  stamp_now(g.stamp);
   const uint32_t die = blockIdx.x % XCDS, rank = blockIdx.x / XCDS, G = gridDim.x / XCDS;
   if (die >= t.n_dies) return;
   // A level here is one link of a dependency chain: these waves are bound by latency, and other
@@ -1165,8 +1188,13 @@ __global__ void k_number_rows(Engine e, uint32_t n_leaf, uint32_t n_cell) {
     if (e.node_of_row) e.node_of_row[i] = e.row_node[f];
   }
 }
-__global__ void k_translate_rows(Engine e, const uint32_t* row_of, uint32_t n_cell, int has_head, int has_root) {
-  const uint32_t n = n_cell > e.n_inst ? n_cell : e.n_inst;
+__global__ void k_translate_rows(Engine e, const uint32_t* row_of, uint32_t n_cell, int has_head, int has_root, const LaneTotals* t,
+                                 float* zero, uint32_t n_zero) {
+  if (t) {   // (queued before the host knows how many)
+    if (t->bad) return;
+    n_cell = t->n_cell;
+  }
+  const uint32_t n = max(max(n_cell, e.n_inst), n_zero);
   for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) {
     if (q < n_cell) {
       e.q_l[q] = row_of[e.q_l[q]];
@@ -1176,11 +1204,13 @@ __global__ void k_translate_rows(Engine e, const uint32_t* row_of, uint32_t n_ce
       if (has_head) e.head_row[q] = row_of[e.head_row[q]];
       if (has_root) e.root_ref[q] = row_of[e.root_ref[q]];
     }
+    if (q < n_zero) zero[q] = 0.f;
   }
 }
 // dz of the cells of the tail that have no parent: the roots, whose dh came from the head (or the caller)
 template <int DT>
 __global__ void k_dz_tail_roots(VecArgs v, Engine e, const uint32_t* root_rows, uint32_t q_first) {
+  stamp_now(v.stamp);
   const uint32_t row = root_rows[blockIdx.x];
   if (row >= e.row0 && row - e.row0 >= q_first) dz_row<DT>(v, e, row - e.row0);
 }
@@ -1188,6 +1218,7 @@ __global__ void k_dz_tail_roots(VecArgs v, Engine e, const uint32_t* root_rows, 
 // Gradient-body firings counted on the device: the marks of all leaf and cell rows, summed, and the
 // number of rows whose mark is not exactly one.  out[0] += sum, out[1] += rows fired other than once.
 __global__ void k_count_grad(VecArgs v, Engine e, uint32_t n_leaf, uint32_t n_cell, unsigned long long* out) {
+  stamp_now(v.stamp);
   unsigned long long sum = 0, odd = 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_leaf + n_cell; i += gridDim.x * blockDim.x) {
     const uint32_t m = v.gmark[i];
@@ -1210,6 +1241,7 @@ __global__ void k_count_grad(VecArgs v, Engine e, uint32_t n_leaf, uint32_t n_ce
 template <int DT, bool GATHER>
 __global__ void __launch_bounds__(256) k_transpose(VecArgs v, Engine e, uint32_t n_q, int n_cols, void* out_, float* col_sums) {
   typedef typename TypeOf<DT>::type T;
+  if constexpr (!GATHER) stamp_now(v.stamp);
   constexpr int CH = El<T>::CH;          // elements per 16-byte chunk
   constexpr int TQ = 64, TC = 64;        // tile: 64 tags x 64 columns
   constexpr int CPR = TC / CH;           // chunks per tile row
@@ -1295,11 +1327,13 @@ struct DwArgs {
   int k_per_split, n_splits, n_tiles_n;
   float* dW_part;        // [splits][Np][Kp]
   float* db_part;        // [splits][Np]
+  Stamp stamp;
 };
 
 __global__ void __launch_bounds__(256, 3) k_dw_direct(DwArgs g) {
   __shared__ __attribute__((aligned(16))) __bf16 sA[DWQ * DWLD];
   __shared__ __attribute__((aligned(16))) __bf16 sB[DWQ * DWLD];
+  stamp_now(g.stamp);
   const int n_mt = (g.Np + DWT - 1) / DWT;
   const int xcd = blockIdx.x & 7, u = blockIdx.x >> 3;
   const int tiles = n_mt * g.n_tiles_n;
@@ -1532,6 +1566,7 @@ struct TokenSink {   // leaf rows grouped by token (leaf i has row i)
 // one wave per chunk of at most `chunk` leaves of one token: partial[chunk] = sum of their dH rows
 __global__ void k_de_partial(VecArgs v, const uint32_t* seg_off, const uint32_t* chunk_off,
                              const uint32_t* sorted_row, uint32_t chunk, float* part) {
+  stamp_now(v.stamp);
   const uint32_t n_chunks = chunk_off[v.vocab];
   const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63;
   const uint32_t n_waves = (gridDim.x * blockDim.x) >> 6;
@@ -1602,14 +1637,18 @@ __global__ void __launch_bounds__(256) k_de_final(VecArgs v, const uint32_t* chu
 }  // namespace
 
 // ---- host entry points used by eval.hip ------------------------------------------------------
-template <typename T> static void pack_w_t(const VecArgs& v, hipStream_t s) {
-  hipLaunchKernelGGL(k_pack_w<DtOf<T>::value>, dim3(1024), dim3(256), 0, s, v);
-}
-void vec_pack_w(const VecArgs& v, hipStream_t s) {
-  if (v.dtype == TDF_BF16) pack_w_t<__bf16>(v, s); else pack_w_t<float>(v, s);
+// lanes / zero: see PrepArgs (null: W alone)
+void vec_pack_w(const VecArgs& v, const LaneArgs* lanes, void* zero, size_t zero_bytes, hipStream_t s) {
+  PrepArgs p{};
+  if (lanes) p.lanes = *lanes;
+  p.zero = (uint4*)zero;
+  p.n_zero = zero_bytes / 16;
+  if (v.dtype == TDF_BF16) hipLaunchKernelGGL(k_pack_w<TDF_BF16>, dim3(1024), dim3(256), 0, s, v, p);
+  else hipLaunchKernelGGL(k_pack_w<TDF_F32>, dim3(1024), dim3(256), 0, s, v, p);
 }
 
-void vec_embed(const VecArgs& v, const Engine& e, uint32_t n_leaf, hipStream_t s) {
+// t: the lanes' totals, which hold the number of leaves (n_leaf: at most); null: n_leaf is it
+void vec_embed(const VecArgs& v, const Engine& e, uint32_t n_leaf, const LaneTotals* t, hipStream_t s) {
   if (!n_leaf) return;
   const int epc = v.dtype == TDF_BF16 ? 8 : 4;
   int lpl = 1;   // lanes per leaf: the row's 16-byte chunks rounded up to a power of two, at most 64
@@ -1617,8 +1656,8 @@ void vec_embed(const VecArgs& v, const Engine& e, uint32_t n_leaf, hipStream_t s
   const uint32_t per_block = 256u / (uint32_t)lpl;
   // at least 8192 threads, so that the first Hp of them can clear row 0 of Cs
   const int blocks = (int)std::min<uint32_t>(std::max<uint32_t>((n_leaf + per_block - 1) / per_block, 32u), 8192u);
-  if (v.dtype == TDF_BF16) hipLaunchKernelGGL(k_embed<TDF_BF16>, dim3(blocks), dim3(256), 0, s, v, e, n_leaf, lpl);
-  else hipLaunchKernelGGL(k_embed<TDF_F32>, dim3(blocks), dim3(256), 0, s, v, e, n_leaf, lpl);
+  if (v.dtype == TDF_BF16) hipLaunchKernelGGL(k_embed<TDF_BF16>, dim3(blocks), dim3(256), 0, s, v, e, n_leaf, t, lpl);
+  else hipLaunchKernelGGL(k_embed<TDF_F32>, dim3(blocks), dim3(256), 0, s, v, e, n_leaf, t, lpl);
 }
 
 template <typename T> static void cell_fwd_t(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count,
@@ -1627,6 +1666,7 @@ template <typename T> static void cell_fwd_t(const VecArgs& v, const Engine& e, 
   g.M = (int)count; g.N = v.Np; g.K = v.Kp;
   g.B = v.Wp; g.ldb = v.Kp; g.Bf = v.Wf;
   g.Hs = v.Hs; g.Hp = v.Hp;
+  g.stamp = v.stamp;
   g.out0 = e.row0 + q0; g.l = e.q_l + q0; g.r = e.q_r + q0;
   g.bias = v.bp; g.Hs_out = v.Hs; g.Cs = v.Cs; g.leaf_rows = e.row0;
   g.gates = v.gates ? reinterpret_cast<T*>(v.gates) + (size_t)q0 * v.Np : nullptr;
@@ -1674,6 +1714,7 @@ template <typename T> static void tail_fwd_t(const VecArgs& v, const Engine& e, 
   g.N = v.Np; g.K = v.Kp;
   g.B = v.Wp; g.ldb = v.Kp; g.Bf = v.Wf;
   g.Hs = v.Hs; g.Hp = v.Hp;
+  g.stamp = v.stamp;
   g.out0 = e.row0; g.l = e.q_l; g.r = e.q_r;
   g.bias = v.bp; g.Hs_out = v.Hs; g.Cs = v.Cs; g.leaf_rows = e.row0;
   g.gates = v.gates; g.ldg = v.Np; g.save_gates = save_gates && v.gates;
@@ -1721,12 +1762,14 @@ void vec_number_rows(const Engine& e, uint32_t n_leaf, uint32_t n_cell, int has_
   const int g1 = (int)std::min<uint32_t>((n_leaf + n_cell + 255) / 256, 2048u);
   hipLaunchKernelGGL(k_number_rows, dim3(std::max(g1, 1)), dim3(256), 0, s, e, n_leaf, n_cell);
   const int g2 = (int)std::min<uint32_t>((std::max(n_cell, e.n_inst) + 255) / 256, 2048u);
-  hipLaunchKernelGGL(k_translate_rows, dim3(std::max(g2, 1)), dim3(256), 0, s, e, e.row_of, n_cell, has_head, has_root);
+  hipLaunchKernelGGL(k_translate_rows, dim3(std::max(g2, 1)), dim3(256), 0, s, e, e.row_of, n_cell, has_head, has_root,
+                     (const LaneTotals*)nullptr, (float*)nullptr, 0u);
 }
-// (the lanes' sort has numbered the rows already)
-void vec_translate_rows(const Engine& e, const uint32_t* row_of, uint32_t n_cell, int has_head, int has_root, hipStream_t s) {
-  const int g2 = (int)std::min<uint32_t>((std::max(n_cell, e.n_inst) + 255) / 256, 2048u);
-  hipLaunchKernelGGL(k_translate_rows, dim3(std::max(g2, 1)), dim3(256), 0, s, e, row_of, n_cell, has_head, has_root);
+// The lanes' sort has numbered the rows already: references alone, of at most `most` cells, and `zero` cleared.
+void vec_translate_rows(const Engine& e, const uint32_t* row_of, const LaneTotals* t, uint32_t most, int has_head, int has_root,
+                        float* zero, uint32_t n_zero, hipStream_t s) {
+  const int g2 = (int)std::min<uint32_t>((std::max(std::max(most, e.n_inst), n_zero) + 255) / 256, 2048u);
+  hipLaunchKernelGGL(k_translate_rows, dim3(std::max(g2, 1)), dim3(256), 0, s, e, row_of, 0u, has_head, has_root, t, zero, n_zero);
 }
 
 void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
@@ -1786,6 +1829,7 @@ static void weight_grads_direct(const VecArgs& v, const Engine& e, uint32_t n_q,
                                 hipStream_t s) {
   const int splits = vec_dw_splits(v.q_stride, v.Np, v.Kp);
   DwArgs g{};
+  g.stamp = v.stamp;
   g.Dz = reinterpret_cast<const __bf16*>(v.Dz);
   g.Hs = reinterpret_cast<const __bf16*>(v.Hs);
   g.q_l = e.q_l; g.q_r = e.q_r;

@@ -275,6 +275,19 @@ inline __device__ uint32_t wave_umax(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// ---- phase times -----------------------------------------------------------------------------------
+// A phase begins and ends with the start of a kernel: the kernel writes the 100 MHz clock (the same on every
+// die) to the places in `mask`.  An event between two kernels instead costs a barrier packet, 5 to 6 us.
+struct Stamp {
+  unsigned long long* at;   // [2 * phases]: begin, end
+  uint32_t mask;            // places this launch writes (0: none)
+};
+inline __device__ void stamp_now(const Stamp& s) {
+  if (s.mask == 0 || blockIdx.x != 0 || blockIdx.y != 0 || threadIdx.x != 0) return;
+  const unsigned long long t = (unsigned long long)wall_clock64();
+  for (uint32_t m = s.mask; m; m &= m - 1) s.at[__ffs((int)m) - 1] = t;
+}
+
 // ---- the depth-first lanes (lane_device.h) --------------------------------------------------------
 struct alignas(128) LaneCtl {   // zero on entry
   uint32_t queues_done;         // queues whose instances are done
@@ -282,6 +295,27 @@ struct alignas(128) LaneCtl {   // zero on entry
   uint32_t log_used;            // log entries reserved by the waves (starts at the chunks dealt to them)
   uint32_t n_seg;               // stack segments used (starts at the number of lanes, which have one each)
   uint32_t leaf_next;           // rows given to leaves (after the run)
+  uint32_t rows_done;           // workgroups through with the first pass over the log
+};
+// The run's totals, and how its cells are sorted.
+struct alignas(128) LaneTotals {
+  uint32_t status;              // of the lanes
+  uint32_t bad;                 // nothing may be built on this run: a status, or more tags or cells than there are rows for
+  uint32_t n_log, n_leaf, n_cell;
+  uint32_t max_depth, max_level, max_iter;
+  uint32_t n_keys;              // sort keys; 0: no cells
+  uint32_t deep_level, deep_base;   // instances whose root's level is deep_level or more are sorted apart (0: one class)
+  uint32_t published;           // the level offsets are in the host's copy
+  unsigned long long n_tags, n_tokens, frames;
+};
+struct LaneLimits {
+  uint32_t max_tags, max_cells;   // 0: no limit
+  uint32_t deep_level;            // 0: one class
+};
+// What the host waits for, in pinned memory: `seq` is written last.
+struct alignas(128) LaneReport {
+  LaneTotals t;
+  uint32_t seq;
 };
 struct alignas(128) LaneQueue {
   uint32_t head, tail;          // tickets of waves without work, calls (and pills) put in; read as one 8-byte word
@@ -342,6 +376,7 @@ struct VecArgs {
   uint32_t* gmark;  // [rows] gradient runs: how often the gradient body of a row's tag has fired (cleared per call)
   float* dHn;       // [rows x Hp] gradient of each row's own loss term (CE_NODE, gradient runs; else null):
                     // whoever reads a row of dH adds the row of dHn
+  Stamp stamp;      // of the next launch
   int wide_offsets; // only the build for the tests sets it: kernels with a 32-bit and a 64-bit offset path take the latter
 };
 

@@ -2,7 +2,9 @@
 // the level-by-level execution of the cell firings, and the reversed schedule of the
 // gradient pass.
 #include <algorithm>
+#include <chrono>
 #include <mutex>
+#include <sched.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -19,14 +21,19 @@ namespace tdf {
 void launch_seed(const DevProgram& P, const Engine& e, hipStream_t s);
 tdf_status launch_round(const DevProgram& P, const Engine& e, int cus, bool local, int small_block, int max_steps,
                         long long spin_ticks, const JitKernels& jit, hipStream_t s);
+void launch_lane_init(const LaneArgs& a, const Stamp& st, hipStream_t s);
 tdf_status launch_lanes(const LaneArgs& a, int n_stored, const JitKernels& jit, hipStream_t s);
+void launch_lane_sort(const Engine& e, const LaneArgs& a, const LaneLimits& lim, uint32_t* row_node, LaneTotals* totals,
+                      LaneReport* report, uint32_t* pin_off, uint32_t pin_keys, uint32_t seq, const Stamp& st, hipStream_t s);
+void launch_finish(const LaneArgs& a, const EndArgs& g, const Stamp& st, hipStream_t s);
+void launch_stamp(const Stamp& st, hipStream_t s);
 int tag_machine_small_block(const DevProgram& P, bool jit);
 void launch_levels(const Engine& e, uint32_t n_cell, uint32_t n_keys, hipStream_t s);
 void launch_class_keys(const DevProgram& P, const Engine& e, uint32_t n_cell, uint32_t deep_level, uint32_t deep_base, hipStream_t s);
 void launch_merge_logs(const Engine& e, const uint32_t* leaf_off, const uint32_t* cell_off, hipStream_t s);
 void launch_count_fired(const DevProgram& P, const Engine& e, hipStream_t s);
-void vec_pack_w(const VecArgs& v, hipStream_t s);
-void vec_embed(const VecArgs& v, const Engine& e, uint32_t n_leaf, hipStream_t s);
+void vec_pack_w(const VecArgs& v, const LaneArgs* lanes, void* zero, size_t zero_bytes, hipStream_t s);
+void vec_embed(const VecArgs& v, const Engine& e, uint32_t n_leaf, const LaneTotals* t, hipStream_t s);
 void vec_cell_fwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, int save_gates, hipStream_t s);
 void vec_cell_bwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, hipStream_t s);
 uint32_t vec_small_level();
@@ -35,9 +42,8 @@ void vec_tail_fwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, 
 void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
                   uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, const uint32_t* root_rows,
                   hipStream_t s);
-void launch_lane_rows(const Engine& e, const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base, hipStream_t s);
-void launch_lane_place(const Engine& e, const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base, hipStream_t s);
-void vec_translate_rows(const Engine& e, const uint32_t* row_of, uint32_t n_cell, int has_head, int has_root, hipStream_t s);
+void vec_translate_rows(const Engine& e, const uint32_t* row_of, const LaneTotals* t, uint32_t most, int has_head, int has_root,
+                        float* zero, uint32_t n_zero, hipStream_t s);
 void vec_number_rows(const Engine& e, uint32_t n_leaf, uint32_t n_cell, int has_head, int has_root, hipStream_t s);
 void vec_head(const VecArgs& v, const Engine& e, const float* dy, int with_grad, int cls, hipStream_t s);
 void vec_node_loss(const VecArgs& v, const Engine& e, uint32_t n_leaf, uint32_t n_cell, const int32_t* node_label,
@@ -72,11 +78,12 @@ struct Plan {
   Engine e{};
   VecArgs v{};
   bool vec = false, grad = false;
-  size_t off_ctrl, off_fire, off_frames, off_tail_sync, off_gcount = 0;
+  size_t off_ctrl, off_fire, off_frames, off_tail_sync, off_gcount = 0, off_stamps;
   // embedding-gradient and bias-gradient scratch
   size_t off_tok_count, off_tok_fill, off_seg_off, off_chunk_off, off_sorted, off_de_part, off_db_part;
   uint32_t max_cells;
   LaneArgs lanes{};          // n_waves 0: the evaluation keeps its frames and runs on the step machine
+  LaneTotals* totals = nullptr;
   int n_stored = 0;
   size_t base_total = 0;     // bytes without the lanes' part, which comes last
 };
@@ -150,6 +157,7 @@ tdf_status make_plan(const Graph& G, const tdf_inputs* in, bool with_grad, char*
     off_gmark = L.take(sizeof(uint32_t) * ((size_t)T + 64));
   }
   L.zero_end = L.total;
+  P.off_stamps = L.take(sizeof(unsigned long long) * 2 * TDF_PHASE_COUNT);
   P.off_frames = L.take((size_t)G.prog.frame_stride * ((size_t)e.cap + B));   // headers are written on insertion
   // --- the rest is written before it is read
   size_t off_prog = L.take(sizeof(DevProgram));
@@ -246,14 +254,12 @@ tdf_status make_plan(const Graph& G, const tdf_inputs* in, bool with_grad, char*
     size_t off_Wp = L.take((size_t)v.Np * v.Kp * el);
     size_t off_Wf = L.take((size_t)v.Np * v.Kp * el);
     size_t off_bp = L.take((size_t)v.Np * 4);
-    size_t off_loss = L.take((size_t)B * 4);
     v.Hs = at(off_Hs);
     v.Cs = G.cell_kind == 2 ? (float*)at(off_Cs) : nullptr;
     v.Wp = at(off_Wp);
     v.Wf = at(off_Wf);
     v.WfT = nullptr;
     v.bp = (float*)at(off_bp);
-    v.loss = (float*)at(off_loss);
     if (with_grad) {
       // In a gradient graph every state row has exactly one consumer, so a cell consumes two rows of
       // its own: at most half of the rows are cells.
@@ -307,12 +313,14 @@ tdf_status make_plan(const Graph& G, const tdf_inputs* in, bool with_grad, char*
     a.queue_cap = pow2_at_least(2ull * ((a.n_waves + a.n_queues - 1) / a.n_queues) + 64);
     // stack segments: one per lane, and room for as many frames as there may be tags
     a.n_segs = a.n_waves * 64u + T / LANE_SEG + 64u;
-    const size_t off_ctl = L.take(sizeof(LaneCtl) + sizeof(LaneQueue) * (size_t)a.n_queues), off_queues = off_ctl + sizeof(LaneCtl);   // read back together
+    const size_t off_ctl = L.take(sizeof(LaneCtl)), off_queues = L.take(sizeof(LaneQueue) * (size_t)a.n_queues);
+    const size_t off_totals = L.take(sizeof(LaneTotals));
     const size_t off_mail = L.take(sizeof(LaneMail) * (size_t)a.queue_cap * a.n_queues);
     const size_t off_reply = L.take(sizeof(LaneReply) * 64 * (size_t)a.n_waves);
     const size_t off_segs = L.take((size_t)a.n_segs * lane_seg_units(P.n_stored) * 16);
     a.ctl = (LaneCtl*)at(off_ctl);
     a.queues = (LaneQueue*)at(off_queues);
+    P.totals = (LaneTotals*)at(off_totals);
     a.mail = (LaneMail*)at(off_mail);
     a.reply = (LaneReply*)at(off_reply);
     a.segs = (uint4*)at(off_segs);
@@ -358,11 +366,13 @@ tdf_status status_from_device(uint32_t st) {
   return (tdf_status)code;
 }
 
-// Layout of tdf_graph::pinned: control blocks, barrier records, firing tables, firing counts, then level offsets.
-constexpr size_t PIN_CTRL = 0, PIN_SYNC = PIN_CTRL + sizeof(Ctrl) * 8, PIN_PROG = PIN_SYNC + sizeof(DieSync) * 16,
+// Layout of tdf_graph::pinned: control blocks, firing tables, firing counts, the lanes' report, the end's report, then
+// level offsets.
+constexpr size_t PIN_CTRL = 0, PIN_PROG = PIN_CTRL + sizeof(Ctrl) * 8,
                  PIN_FIRE = (PIN_PROG + sizeof(DevProgram) + 255) / 256 * 256,
-                 PIN_LANES = (PIN_FIRE + sizeof(unsigned long long) * (TDF_STATS_MAX_COUNTS + 2) + 255) / 256 * 256,
-                 PIN_LEVELS = PIN_LANES + sizeof(LaneCtl) + sizeof(LaneQueue) * 64;
+                 PIN_LANES = (PIN_FIRE + sizeof(unsigned long long) * TDF_STATS_MAX_COUNTS + 255) / 256 * 256,
+                 PIN_END = (PIN_LANES + sizeof(LaneReport) + 255) / 256 * 256,
+                 PIN_LEVELS = (PIN_END + sizeof(EndReport) + 255) / 256 * 256;
 // Makes the graph's pinned buffer at least PIN_LEVELS + level_bytes large (contents are lost when it grows).
 tdf_status pinned_reserve(tdf_graph* gr, size_t level_bytes) {
   const size_t need = PIN_LEVELS + level_bytes;
@@ -373,8 +383,30 @@ tdf_status pinned_reserve(tdf_graph* gr, size_t level_bytes) {
   const size_t bytes = std::max<size_t>(need * 2, 64 * 1024);
   HIP_TRY(hipHostMalloc(&gr->pinned, bytes, hipHostMallocDefault));
   gr->pinned_bytes = bytes;
+  memset(gr->pinned, 0, PIN_LEVELS);   // (no report awaited yet: tdf_graph::seq only grows)
   memcpy((char*)gr->pinned + PIN_PROG, &gr->g.prog, sizeof(DevProgram));
   return TDF_OK;
+}
+
+// Waits until a kernel has written `seq` there (a system-scope store to pinned memory, 3 us after the launch
+// it is in ends, where a copy and a stream synchronisation take 8).  The stream is asked now and then, so that an
+// error on it ends the wait.
+tdf_status wait_report(const uint32_t* word, uint32_t seq, hipStream_t s) {
+  using clock = std::chrono::steady_clock;
+  auto next = clock::now() + std::chrono::milliseconds(5);
+  for (uint32_t k = 1;; ++k) {
+    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == seq) return TDF_OK;
+    __builtin_ia32_pause();
+    if (k % 256 != 0) continue;
+    if (clock::now() < next) continue;
+    const hipError_t r = hipStreamQuery(s);
+    if (r != hipErrorNotReady && __atomic_load_n(word, __ATOMIC_ACQUIRE) != seq) {
+      set_error(std::string("the stream ended without a report: ") + hipGetErrorString(r));
+      return TDF_ERR_DEVICE;
+    }
+    next = clock::now() + std::chrono::milliseconds(5);
+    sched_yield();
+  }
 }
 
 // Evaluations of one process take turns, in two stages.  The control plane (the tag machine: persistent
@@ -426,7 +458,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     return TDF_ERR_BAD_ARG;
   }
   hipStream_t s = (hipStream_t)hip_stream;
-  // phase timing: event pairs on the caller's stream, only when statistics are requested
+  // phase times, only when statistics are requested: places that the next launch on a stream writes (Stamp)
   const bool timed = stats != nullptr;
   int64_t launches[TDF_PHASE_COUNT] = {0};
   bool phase_used[TDF_PHASE_COUNT] = {false};
@@ -434,15 +466,27 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     set_error("the graph was not prepared: call tdf_graph_prepare first");
     return TDF_ERR_BAD_ARG;
   }
-  if (timed && !no_alloc)
-    for (int i = 0; i < 2 * TDF_PHASE_COUNT; ++i)
-      if (!gr->events[i]) HIP_TRY(hipEventCreate((hipEvent_t*)&gr->events[i]));
-  auto begin = [&](int ph) { if (timed) { (void)hipEventRecord((hipEvent_t)gr->events[2 * ph], s); phase_used[ph] = true; } };
-  auto end = [&](int ph, int64_t n) { if (timed) (void)hipEventRecord((hipEvent_t)gr->events[2 * ph + 1], s); launches[ph] += n; };
   Engine& e = P.e;
   VecArgs& v = P.v;
   e.out_i64 = (long long*)out->out_i64;
   char* base = (char*)workspace;
+  uint32_t pending[3] = {0u, 0u, 0u};   // by stream: the caller's, the side stream, the sort stream
+  auto pend = [&](hipStream_t st) -> uint32_t& { return pending[st == s ? 0 : st == (hipStream_t)gr->side_stream ? 1 : 2]; };
+  auto take = [&](hipStream_t st) {
+    Stamp r{(unsigned long long*)(base + P.off_stamps), timed ? pend(st) : 0u};
+    pend(st) = 0u;
+    return r;
+  };
+  auto flush = [&](hipStream_t st) {   // where the next launch is a long time off, or writes no stamps
+    const Stamp r = take(st);
+    if (r.mask) launch_stamp(r, st);
+  };
+  auto on = [&](hipStream_t st) -> const VecArgs& { v.stamp = take(st); return v; };
+  auto begin_on = [&](int ph, hipStream_t st) { pend(st) |= 1u << (2 * ph); phase_used[ph] = timed; };
+  auto end_on = [&](int ph, int64_t n, hipStream_t st) { pend(st) |= 2u << (2 * ph); launches[ph] += n; };
+  auto begin = [&](int ph) { begin_on(ph, s); };
+  auto end = [&](int ph, int64_t n) { end_on(ph, n, s); };
+  v.loss = (float*)out->out_f32;
   if (!no_alloc)
     if (tdf_status ps = pinned_reserve(gr, 0); ps != TDF_OK) return ps;
 
@@ -490,56 +534,87 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   uint32_t rounds = 0, repeats = 0;
   const uint32_t poll = 2;          // rounds queued between two looks at the control blocks
   const int max_steps = 4096;       // steps per kernel launch
-  // Gradient runs have two more streams.  The packed copies of W depend on the caller's inputs only: they
-  // are made on one of them, beside the tag machine (again after it, should the plan change meanwhile).
+  // Gradient runs have two more streams.
   if (P.vec && !gr->side_stream && with_grad && !no_alloc) {
     HIP_TRY(hipStreamCreateWithFlags((hipStream_t*)&gr->side_stream, hipStreamNonBlocking));
     HIP_TRY(hipStreamCreateWithFlags((hipStream_t*)&gr->sort_stream, hipStreamNonBlocking));
-    for (void** ev : {&gr->fork_event, &gr->join_event, &gr->fork_deep, &gr->join_deep, &gr->fork_sort, &gr->join_sort, &gr->leaves_done})
+    for (void** ev : {&gr->fork_event, &gr->join_event, &gr->fork_deep, &gr->join_deep, &gr->fork_sort})
       HIP_TRY(hipEventCreateWithFlags((hipEvent_t*)ev, hipEventDisableTiming));
   }
-  bool w_packed = false;
-  if (P.vec && G.cell_kind && with_grad && !no_alloc) {
-    HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_sort, s));
-    HIP_TRY(hipStreamWaitEvent((hipStream_t)gr->sort_stream, (hipEvent_t)gr->fork_sort, 0));
-    vec_pack_w(v, (hipStream_t)gr->sort_stream);
-    w_packed = true;
-  }
+  // Instances never exchange values, so instances whose recursion is deep (long chains: many levels of a few
+  // cells each, bound by latency) can run beside the others (few levels of many cells each, bound by
+  // throughput) instead of after them.  An instance is deep if its root's level is at least deep_level; its
+  // cells get sort keys behind all keys of the shallow ones.
+  uint32_t deep_level = 32;
+  if (const char* w = getenv("TDF_DEEP_LEVEL")) deep_level = (uint32_t)std::max(0, atoi(w));
+  if (!(with_grad && gr->side_stream && gr->die_local && !G.has_node_loss)) deep_level = 0;
   begin(TDF_PHASE_TAGS);
-  LaneCtl lc{};
+  const LaneReport* rep = (const LaneReport*)((char*)gr->pinned + PIN_LANES);
+  const EndReport* fin = (const EndReport*)((char*)gr->pinned + PIN_END);
+  bool ended = false;       // the end's report has been read
+  bool rows_known = false;  // the lanes' report came with the level offsets' totals: rows, order and leaves are queued
+  auto finish = [&](bool lanes_totals, const void* sync, const void* gcount) -> tdf_status {
+    EndArgs g{(EndReport*)fin, (const unsigned long long*)(base + P.off_stamps), (const unsigned long long*)gcount, sync, ++gr->seq,
+              lanes_totals ? 1 : 0};
+    launch_finish(P.lanes, g, take(s), s);
+    return TDF_OK;
+  };
   if (use_lanes) {
     LaneArgs& a = P.lanes;
     a.out_i64 = e.out_i64;
     a.idle_ticks = spin_ticks;
     a.run_ticks = 2 * spin_ticks;   // (then it is the step machine's)
-    if (P.vec) HIP_TRY(hipMemsetAsync(base + P.L.zero_begin, 0, P.L.zero_end - P.L.zero_begin, s));
+    if (P.vec) vec_pack_w(on(s), &a, base + P.L.zero_begin, P.L.zero_end - P.L.zero_begin, s);
+    else launch_lane_init(a, take(s), s);
     if (tdf_status ls = launch_lanes(a, P.n_stored, gr->jit, s); ls != TDF_OK) return ls;
-    LaneCtl* pl = (LaneCtl*)((char*)gr->pinned + PIN_LANES);
-    HIP_TRY(hipMemcpyAsync(pl, a.ctl, sizeof(LaneCtl) + sizeof(LaneQueue) * a.n_queues, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    lc = *pl;
-    if (lc.status != 0) {   // left to the step machine, which also says what is wrong if something is
-      if (status_is(lc.status, TDF_ERR_UNSUPPORTED)) gr->lanes_ok = false;
+    end(TDF_PHASE_TAGS, 2);
+    LaneTotals lt;
+    if (P.vec) {
+      // Everything that does not need the host to know the run's sizes is queued behind the lanes: rows, order
+      // and references of the cells, and the leaves' rows.  The report comes from the middle of that, so the
+      // launches of the levels are made while the rest of it runs.
+      const LaneLimits lim{e.max_tags, with_grad ? P.max_cells : 0u, deep_level};
+      begin(TDF_PHASE_LEVELS);
+      launch_lane_sort(e, a, lim, a.row_node, P.totals, (LaneReport*)rep, (uint32_t*)((char*)gr->pinned + PIN_LEVELS),
+                       (uint32_t)((gr->pinned_bytes - PIN_LEVELS) / sizeof(uint32_t)), ++gr->seq, take(s), s);
+      vec_translate_rows(e, a.row_of, P.totals, e.max_tags, G.has_head, G.out_type == T_VEC, G.has_node_loss ? (float*)out->out_node_loss : nullptr,
+                         G.has_node_loss ? (uint32_t)in->n_tree_nodes : 0u, s);
+      end(TDF_PHASE_LEVELS, 4);
+      begin(TDF_PHASE_LEAVES);
+      vec_embed(on(s), e, e.max_tags, P.totals, s);
+      end(TDF_PHASE_LEAVES, 1);
+      if (with_grad) HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_sort, s));   // (for the token sort)
+      HIP_TRY(hipGetLastError());
+      if (tdf_status ws = wait_report(&rep->seq, gr->seq, s); ws != TDF_OK) return ws;
+      lt = rep->t;
+      rows_known = lt.status == 0;
+    } else {
+      if (tdf_status fs = finish(true, nullptr, nullptr); fs != TDF_OK) return fs;
+      HIP_TRY(hipGetLastError());
+      if (tdf_status ws = wait_report(&fin->seq, gr->seq, s); ws != TDF_OK) return ws;
+      lt = fin->t;
+      ended = lt.status == 0;
+    }
+    if (lt.status != 0) {   // left to the step machine, which also says what is wrong if something is
+      if (status_is(lt.status, TDF_ERR_UNSUPPORTED)) gr->lanes_ok = false;
       use_lanes = false;
       ++repeats;
+      memset(launches, 0, sizeof(launches));
+      begin(TDF_PHASE_TAGS);
     } else {
-      const LaneQueue* pq = (const LaneQueue*)(pl + 1);
-      unsigned long long frames = 0;
-      for (uint32_t k = 0; k < a.n_queues; ++k) {
-        const LaneQueue& q = pq[k];
-        hc.n_leaf += q.n_leaf; hc.n_cell += q.n_cell;
-        hc.n_tags += q.n_tags; hc.n_tokens += q.n_tokens;
-        frames += (unsigned long long)q.n_rec + q.n_private;
-        hc.step = std::max(hc.step, q.max_iter);
-        hc.max_depth = std::max(hc.max_depth, q.max_depth);
-        hc.max_level = std::max(hc.max_level, q.max_level);
-      }
-      hc.n_alloc = (uint32_t)std::min<unsigned long long>(hc.n_tags, frames);
+      hc.n_leaf = lt.n_leaf; hc.n_cell = lt.n_cell;
+      hc.n_tags = lt.n_tags; hc.n_tokens = lt.n_tokens;
+      hc.step = lt.max_iter;
+      hc.max_depth = lt.max_depth;
+      hc.max_level = lt.max_level;
+      hc.n_alloc = (uint32_t)std::min<unsigned long long>(hc.n_tags, lt.frames);
       hc.done = 1;
       // (programs with vector operators: max_tags bounds all tags, and there is a row for each)
       if (!e.reclaim && hc.n_tags > (unsigned long long)e.max_tags) hc.status = (uint32_t)(-TDF_ERR_TABLE_FULL);
     }
   }
+  bool w_packed = use_lanes && P.vec;
+  if (!use_lanes) flush(s);
   for (; !use_lanes;) {
     // several machines only where each keeps to its own die; the device-scope kernel runs one
     const uint32_t want_dies = gr->die_local ? gr->max_dies : 1;
@@ -549,6 +624,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       if (st != TDF_OK) return st;
       w_packed = false;   // (the packed weights lie elsewhere now)
       e.out_i64 = (long long*)out->out_i64;
+      v.loss = (float*)out->out_f32;
     }
     e.small_limit = (uint32_t)small_block;   // one pass of the single workgroup
     if (const char* w = getenv("TDF_SMALL_LIMIT")) e.small_limit = (uint32_t)std::max(1, atoi(w));
@@ -614,7 +690,10 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (!hc.status) launch_merge_logs(e, leaf_off, cell_off, s);
     break;
   }
-  end(TDF_PHASE_TAGS, 2 + 2ll * rounds);   // (the lanes: their initialisation and themselves)
+  if (!use_lanes) {
+    end(TDF_PHASE_TAGS, 2 + 2ll * rounds);
+    flush(s);
+  }
   if (!hc.status && P.vec && with_grad && hc.n_cell > P.max_cells) hc.status = (uint32_t)(-TDF_ERR_TABLE_FULL);
   tdf_status dev = status_from_device(hc.status);
 
@@ -624,7 +703,6 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   bool deep_beside = false;   // ... on the side stream, beside the others
   uint32_t sh_last = 0, deep_base = 0, q_deep0 = 0, n_wide_levels = 0;
   const uint32_t* level_off = nullptr;   // by sort key; in the pinned buffer
-  bool gcount_fetched = false;
   auto lvl_begin = [&](uint32_t lvl) { return level_off[(size_t)lvl * LEVEL_KEY_DIES]; };
   if (dev == TDF_OK && P.vec) {
     // ---- vector operators: leaves at once, cells level by level --------------------------
@@ -634,70 +712,45 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (no_alloc) locks.data.lock();
     else locks.control.unlock();
     auto enter_data_stage = [&]() { if (!locks.data.owns_lock()) locks.data.lock(); };
-    const uint32_t n_log = std::min(lc.log_used, P.lanes.log_cap);
     e.row0 = hc.n_leaf;   // leaf i has row i, the cell at position q of the sorted log row n_leaf + q
     hipStream_t s2 = (hipStream_t)gr->side_stream, s3 = (hipStream_t)gr->sort_stream;
-    auto begin2 = [&](int ph) { if (timed) { (void)hipEventRecord((hipEvent_t)gr->events[2 * ph], s2); phase_used[ph] = true; } };
-    auto end2 = [&](int ph, int64_t n) { if (timed) (void)hipEventRecord((hipEvent_t)gr->events[2 * ph + 1], s2); launches[ph] += n; };
-    // Instances never exchange values, so instances whose recursion is deep (long chains: many
-    // levels of a few cells each, bound by latency) can run beside the others (few levels of many
-    // cells each, bound by throughput) instead of after them.  An instance is deep if its root's
-    // level is at least deep_level; its cells get sort keys behind all keys of the shallow ones.
-    uint32_t deep_level = 32;
-    if (const char* w = getenv("TDF_DEEP_LEVEL")) deep_level = (uint32_t)std::max(0, atoi(w));
-    const bool want_deep = with_grad && s2 && gr->die_local && !G.has_node_loss && deep_level > 0 && hc.max_level >= deep_level &&
-                           hc.n_cell > 0;
+    if (!gr->die_local) deep_level = 0;   // (found out meanwhile)
+    const bool want_deep = deep_level > 0 && hc.max_level >= deep_level && hc.n_cell > 0;
     deep_base = want_deep ? deep_level * LEVEL_KEY_DIES : 0;
     const uint32_t n_keys = hc.n_cell ? deep_base + (hc.max_level + 2) * LEVEL_KEY_DIES : 0;
-    if (use_lanes) launch_lane_rows(e, P.lanes, n_log, n_keys, want_deep ? deep_level : 0, deep_base, s);   // the leaves' rows, and the counts
-    begin(TDF_PHASE_LEAVES);
-    if (G.cell_kind && !w_packed) vec_pack_w(v, s);   // (a program of EMBEDs alone has no W: the pointers may be NULL)
-    if (!with_grad) vec_embed(v, e, hc.n_leaf, s);
-    end(TDF_PHASE_LEAVES, 2);
-    if (with_grad) {
-      // Gradient runs have a third stream.  The leaves' rows do not wait for the level sort, nor it for
-      // them: they are written there, beside the sort on the caller's stream, and so is the embedding
-      // gradient's token sort, which needs the leaf log only and has until the gradient pass's end.
-      HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_sort, s));
-      HIP_TRY(hipStreamWaitEvent(s3, (hipEvent_t)gr->fork_sort, 0));
-      vec_embed(v, e, hc.n_leaf, s3);
-      HIP_TRY(hipEventRecord((hipEvent_t)gr->leaves_done, s3));
+    if (!rows_known) {
+      begin(TDF_PHASE_LEAVES);
+      if (G.cell_kind && !w_packed) vec_pack_w(on(s), nullptr, nullptr, 0, s);   // (a program of EMBEDs alone has no W: the pointers may be NULL)
+      vec_embed(on(s), e, hc.n_leaf, nullptr, s);
+      end(TDF_PHASE_LEAVES, 2);
+      if (with_grad) HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_sort, s));
     }
-    // (the token sort is put on its stream only after the level sort is on the caller's: the host's time
-    // for its launches is not in the way of the first cell launch then)
-    auto token_sort = [&]() -> tdf_status {
-      if (!with_grad) return TDF_OK;
-      vec_embed_sort(v, e, hc.n_leaf, (uint32_t*)(base + P.off_tok_count), (uint32_t*)(base + P.off_seg_off),
-                     (uint32_t*)(base + P.off_chunk_off), (uint32_t*)(base + P.off_tok_fill),
-                     (uint32_t*)(base + P.off_sorted), DE_CHUNK, s3);
-      HIP_TRY(hipEventRecord((hipEvent_t)gr->join_sort, s3));
-      return TDF_OK;
-    };
     const int deep_wgs = getenv("TDF_DEEP_WGS") ? std::max(1, atoi(getenv("TDF_DEEP_WGS"))) : 16;   // workgroups per die
     if (hc.n_cell) {
-      begin(TDF_PHASE_LEVELS);
-      if (use_lanes) {
-        launch_lane_place(e, P.lanes, n_log, n_keys, want_deep ? deep_level : 0, deep_base, s);
-        vec_translate_rows(e, P.lanes.row_of, hc.n_cell, G.has_head, G.out_type == T_VEC, s);
-      } else {
+      const size_t level_bytes = (size_t)n_keys * sizeof(uint32_t);
+      if (!rows_known) {
+        begin(TDF_PHASE_LEVELS);
         if (want_deep) launch_class_keys(G.prog, e, hc.n_cell, deep_level, deep_base, s);
+        flush(s);
         launch_levels(e, hc.n_cell, n_keys, s);
         vec_number_rows(e, hc.n_leaf, hc.n_cell, G.has_head, G.out_type == T_VEC, s);
+        end(TDF_PHASE_LEVELS, 6);
       }
-      const size_t level_bytes = (size_t)n_keys * sizeof(uint32_t);
-      if (no_alloc && gr->pinned_bytes < PIN_LEVELS + level_bytes) {
-        set_error("more dependency levels than the prepared graph's host buffer holds");
-        return TDF_ERR_WORKSPACE;
+      if (!rows_known || !rep->t.published) {   // (published: they came with the report)
+        if (no_alloc && gr->pinned_bytes < PIN_LEVELS + level_bytes) {
+          set_error("more dependency levels than the prepared graph's host buffer holds");
+          return TDF_ERR_WORKSPACE;
+        }
+        if (!no_alloc) {
+          if (tdf_status ps = pinned_reserve(gr, level_bytes); ps != TDF_OK) return ps;
+          rep = (const LaneReport*)((char*)gr->pinned + PIN_LANES);
+          fin = (const EndReport*)((char*)gr->pinned + PIN_END);
+        }
+        HIP_TRY(hipMemcpyAsync((char*)gr->pinned + PIN_LEVELS, e.level_off, level_bytes, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
       }
-      if (!no_alloc)
-        if (tdf_status ps = pinned_reserve(gr, level_bytes); ps != TDF_OK) return ps;
       level_off = (const uint32_t*)((char*)gr->pinned + PIN_LEVELS);
-      HIP_TRY(hipMemcpyAsync((void*)level_off, e.level_off, level_bytes, hipMemcpyDeviceToHost, s));
-      end(TDF_PHASE_LEVELS, 6);
-      if (tdf_status ts_ = token_sort(); ts_ != TDF_OK) return ts_;
-      HIP_TRY(hipStreamSynchronize(s));
       enter_data_stage();
-      if (with_grad) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)gr->leaves_done, 0));   // the cells read the leaves' rows
       sh_last = want_deep ? std::min(hc.max_level, deep_level - 1) : hc.max_level;
       q_deep0 = want_deep ? level_off[deep_base] : hc.n_cell;   // the shallow instances' cells come first
       deep = want_deep && q_deep0 < hc.n_cell;
@@ -714,8 +767,6 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       }
       hipStream_t sd = beside ? s2 : s;   // the deep instances' stream
       const int deep_per_die = beside ? deep_wgs : cus / (int)XCDS;
-      auto begin_d = [&](int ph) { if (beside) begin2(ph); else begin(ph); };
-      auto end_d = [&](int ph, int64_t n) { if (beside) end2(ph, n); else end(ph, n); };
       deep_beside = deep && beside;
       if (deep && beside) {
         // ---- the deep instances: forward, head and gradient pass in one chain on the side stream
@@ -723,19 +774,20 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
         HIP_TRY(hipStreamWaitEvent(s2, (hipEvent_t)gr->fork_deep, 0));
       }
       auto deep_chain = [&]() -> tdf_status {
-        begin_d(TDF_PHASE_TAIL_FWD);
-        vec_tail_fwd(v, e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync, spin_ticks, deep_per_die,
+        begin_on(TDF_PHASE_TAIL_FWD, sd);
+        vec_tail_fwd(on(sd), e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync, spin_ticks, deep_per_die,
                      with_grad, sd);
-        end_d(TDF_PHASE_TAIL_FWD, 1);
-        if (G.has_head) vec_head(v, e, dy->dy, 1, 1, sd);
-        begin_d(TDF_PHASE_TAIL_BWD);
-        vec_tail_bwd(v, e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
+        end_on(TDF_PHASE_TAIL_FWD, 1, sd);
+        if (G.has_head) vec_head(on(sd), e, dy->dy, 1, 1, sd);
+        begin_on(TDF_PHASE_TAIL_BWD, sd);
+        vec_tail_bwd(on(sd), e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
                      spin_ticks, deep_per_die, q_deep0, G.has_head ? e.head_row : e.root_ref, sd);
-        end_d(TDF_PHASE_TAIL_BWD, 2);
+        end_on(TDF_PHASE_TAIL_BWD, 2, sd);
+        if (beside) flush(sd);   // (its next launch waits for the other instances)
         if (beside) HIP_TRY(hipEventRecord((hipEvent_t)gr->join_deep, s2));
         return TDF_OK;
       };
-      if (deep && G.out_type == T_VEC && !G.has_head) vec_seed_dy(v, e, dy->dy, s);   // (root rows of both classes)
+      if (deep && G.out_type == T_VEC && !G.has_head) vec_seed_dy(on(s), e, dy->dy, s);   // (root rows of both classes)
       if (deep)
         if (tdf_status ds = deep_chain(); ds != TDF_OK) return ds;   // beside: on the side stream; else first, on the caller's
       // ---- the (other) instances on the caller's stream: wide levels one launch each; the narrow
@@ -748,72 +800,74 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       n_wide_levels = tail_first - 1;
       begin(TDF_PHASE_CELLS_FWD);
       for (uint32_t lvl = 1; lvl < tail_first; ++lvl)
-        vec_cell_fwd(v, e, lvl_begin(lvl), lvl_begin(lvl + 1) - lvl_begin(lvl), with_grad, s);
+        if (const uint32_t n = lvl_begin(lvl + 1) - lvl_begin(lvl)) vec_cell_fwd(on(s), e, lvl_begin(lvl), n, with_grad, s);
       end(TDF_PHASE_CELLS_FWD, tail_first - 1);
       if (use_tail) {
         begin(TDF_PHASE_TAIL_FWD);
-        vec_tail_fwd(v, e, e.level_off, tail_first, sh_last, e.n_dies, base + P.off_tail_sync, spin_ticks, cus / (int)XCDS,
+        vec_tail_fwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, base + P.off_tail_sync, spin_ticks, cus / (int)XCDS,
                      with_grad, s);
         end(TDF_PHASE_TAIL_FWD, 1);
       }
     }
     if (!hc.n_cell) {   // leaves only
-      if (tdf_status ts_ = token_sort(); ts_ != TDF_OK) return ts_;
       enter_data_stage();
-      if (use_lanes) vec_translate_rows(e, P.lanes.row_of, 0, G.has_head, G.out_type == T_VEC, s);
-      else vec_number_rows(e, hc.n_leaf, 0, G.has_head, G.out_type == T_VEC, s);
-      if (with_grad) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)gr->leaves_done, 0));
+      if (!rows_known) vec_number_rows(e, hc.n_leaf, 0, G.has_head, G.out_type == T_VEC, s);
+    }
+    if (with_grad) {
+      // Gradient runs have a third stream: the embedding gradient's token sort needs the leaf log only, and has
+      // until the gradient pass's end.  (The host's time for its launches is not in the way of the cells' here.)
+      HIP_TRY(hipStreamWaitEvent(s3, (hipEvent_t)gr->fork_sort, 0));
+      vec_embed_sort(v, e, hc.n_leaf, (uint32_t*)(base + P.off_tok_count), (uint32_t*)(base + P.off_seg_off),
+                     (uint32_t*)(base + P.off_chunk_off), (uint32_t*)(base + P.off_tok_fill),
+                     (uint32_t*)(base + P.off_sorted), DE_CHUNK, s3);
     }
     begin(TDF_PHASE_HEAD);
     if (G.has_head) {
-      vec_head(v, e, with_grad ? dy->dy : nullptr, with_grad, deep ? 0 : -1, s);
+      vec_head(on(s), e, with_grad ? dy->dy : nullptr, with_grad, deep ? 0 : -1, s);
     } else if (G.out_type == T_VEC) {
       if (G.has_node_loss) {
         // every state row that has a loss term: the term, and (gradient runs) its gradient with
         // respect to the row, which joins the row's dh where that is read
-        HIP_TRY(hipMemsetAsync(out->out_node_loss, 0, sizeof(float) * (size_t)in->n_tree_nodes, s));
-        vec_node_loss(v, e, hc.n_leaf, hc.n_cell, in->node_label, out->out_node_loss, with_grad ? dy->dnode : nullptr,
+        if (!rows_known) HIP_TRY(hipMemsetAsync(out->out_node_loss, 0, sizeof(float) * (size_t)in->n_tree_nodes, s));
+        vec_node_loss(on(s), e, hc.n_leaf, hc.n_cell, in->node_label, out->out_node_loss, with_grad ? dy->dnode : nullptr,
                       with_grad, s);
       }
-      if (with_grad && !deep) vec_seed_dy(v, e, dy->dy, s);
+      if (with_grad && !deep) vec_seed_dy(on(s), e, dy->dy, s);
     }
     end(TDF_PHASE_HEAD, G.has_node_loss ? 4 : 2);
     if (with_grad) {
       // ---- gradient pass: the level schedule walked backwards -----------------------------
       if (use_tail && hc.n_cell) {
         begin(TDF_PHASE_TAIL_BWD);
-        vec_tail_bwd(v, e, e.level_off, tail_first, sh_last, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
+        vec_tail_bwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
                      spin_ticks, cus / (int)XCDS, lvl_begin(tail_first), G.has_head ? e.head_row : e.root_ref, s);
         end(TDF_PHASE_TAIL_BWD, 2);
       }
       begin(TDF_PHASE_CELLS_BWD);
       for (uint32_t lvl = tail_first - 1; lvl >= 1 && hc.n_cell; --lvl)
-        vec_cell_bwd(v, e, lvl_begin(lvl), lvl_begin(lvl + 1) - lvl_begin(lvl), s);
+        if (const uint32_t n = lvl_begin(lvl + 1) - lvl_begin(lvl)) vec_cell_bwd(on(s), e, lvl_begin(lvl), n, s);
       end(TDF_PHASE_CELLS_BWD, 2ll * (tail_first - 1));
       if (deep_beside) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)gr->join_deep, 0));   // both classes' gradients are complete
     }
     // results of `result`, once every instance's root exists
-    if (G.has_head) HIP_TRY(hipMemcpyAsync(out->out_f32, v.loss, sizeof(float) * e.n_inst, hipMemcpyDeviceToDevice, s));
-    else if (G.out_type == T_VEC) vec_out_rows(v, e, out->out_h, out->out_c, s);
+    if (!G.has_head && G.out_type == T_VEC) vec_out_rows(on(s), e, out->out_h, out->out_c, s);
     if (with_grad) {
       // The embedding gradient and the weight gradients depend on the gradient pass only, not on
-      // each other: the former runs on a second stream beside the latter.
+      // each other: the former runs beside the latter, on the stream that has put the leaves in token order.
       HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_event, s));
-      HIP_TRY(hipStreamWaitEvent(s2, (hipEvent_t)gr->fork_event, 0));
-      HIP_TRY(hipStreamWaitEvent(s2, (hipEvent_t)gr->join_sort, 0));   // the leaves are in token order
-      if (timed) { (void)hipEventRecord((hipEvent_t)gr->events[2 * TDF_PHASE_EMBED_GRAD], s2); phase_used[TDF_PHASE_EMBED_GRAD] = true; }
-      vec_embed_sums(v, hc.n_leaf, (const uint32_t*)(base + P.off_seg_off), (const uint32_t*)(base + P.off_chunk_off),
-                     (const uint32_t*)(base + P.off_sorted), (float*)(base + P.off_de_part), grads->dE, DE_CHUNK, s2);
-      if (timed) (void)hipEventRecord((hipEvent_t)gr->events[2 * TDF_PHASE_EMBED_GRAD + 1], s2);
-      launches[TDF_PHASE_EMBED_GRAD] += 5;
+      HIP_TRY(hipStreamWaitEvent(s3, (hipEvent_t)gr->fork_event, 0));
+      begin_on(TDF_PHASE_EMBED_GRAD, s3);
+      vec_embed_sums(on(s3), hc.n_leaf, (const uint32_t*)(base + P.off_seg_off), (const uint32_t*)(base + P.off_chunk_off),
+                     (const uint32_t*)(base + P.off_sorted), (float*)(base + P.off_de_part), grads->dE, DE_CHUNK, s3);
+      end_on(TDF_PHASE_EMBED_GRAD, 5, s3);
       // how often each tag's gradient body fired, as the kernels marked it (the cells' marks are complete
       // since the gradient pass, the leaves' since the sums just above)
-      vec_count_grad(v, e, hc.n_leaf, hc.n_cell, (unsigned long long*)(base + P.off_gcount), s2);
-      HIP_TRY(hipEventRecord((hipEvent_t)gr->join_event, s2));
+      vec_count_grad(on(s3), e, hc.n_leaf, hc.n_cell, (unsigned long long*)(base + P.off_gcount), s3);
+      HIP_TRY(hipEventRecord((hipEvent_t)gr->join_event, s3));
       begin(TDF_PHASE_WEIGHT_GRAD);
       if (hc.n_cell) {
         v.q_stride = (hc.n_cell + 63) / 64 * 64;   // only the cells that fired
-        vec_weight_grads(v, e, hc.n_cell, grads->dW, grads->db, (float*)(base + P.off_db_part), s);
+        vec_weight_grads(on(s), e, hc.n_cell, grads->dW, grads->db, (float*)(base + P.off_db_part), s);
       } else {
         HIP_TRY(hipMemsetAsync(grads->dW, 0, sizeof(float) * (size_t)v.N * 2 * v.H, s));
         HIP_TRY(hipMemsetAsync(grads->db, 0, sizeof(float) * (size_t)v.N, s));
@@ -822,12 +876,9 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)gr->join_event, 0));
     }
     HIP_TRY(hipGetLastError());
-    const DieSync* ts = (const DieSync*)((char*)gr->pinned + PIN_SYNC);
-    if (use_tail || deep) HIP_TRY(hipMemcpyAsync((void*)ts, base + P.off_tail_sync, sizeof(DieSync) * 16, hipMemcpyDeviceToHost, s));
-    if (stats && with_grad) {   // (with the same synchronisation: how often the gradient bodies fired)
-      HIP_TRY(hipMemcpyAsync((char*)gr->pinned + PIN_FIRE, base + P.off_gcount, sizeof(unsigned long long) * 2, hipMemcpyDeviceToHost, s));
-      gcount_fetched = true;
-    }
+    if (tdf_status fs = finish(false, use_tail || deep ? base + P.off_tail_sync : nullptr, with_grad ? base + P.off_gcount : nullptr);
+        fs != TDF_OK)
+      return fs;
     if (with_grad && !no_alloc && locks.data.owns_lock()) {
       // Once the gradient pass is through (the event that the embedding gradient was forked at), what is
       // left of this evaluation are the weight and embedding sums: ordinary launches, no workgroups that
@@ -835,8 +886,10 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       HIP_TRY(hipEventSynchronize((hipEvent_t)gr->fork_event));
       locks.data.unlock();
     }
-    HIP_TRY(hipStreamSynchronize(s));
+    if (tdf_status ws = wait_report(&fin->seq, gr->seq, s); ws != TDF_OK) return ws;
+    ended = true;
     if (use_tail || deep) {
+      const DieSync* ts = (const DieSync*)fin->sync;
       bool mixed = false, gave_up = false;
       for (int k = 0; k < 16; ++k) {
         const DieSync& d = ts[k];
@@ -856,10 +909,13 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       }
     }
   }
+  if (!ended) {   // (the step machine on a program without vector operators, or a run that failed)
+    if (tdf_status fs = finish(false, nullptr, nullptr); fs != TDF_OK) return fs;
+    if (tdf_status ws = wait_report(&fin->seq, gr->seq, s); ws != TDF_OK) return ws;
+  }
   HIP_TRY(hipGetLastError());
 
   if (stats) {
-    HIP_TRY(hipStreamSynchronize(s));   // the last phase event may still be pending
     memset(stats, 0, sizeof(*stats));
     stats->n_tags = (int64_t)hc.n_tags;
     stats->n_steps = (int64_t)hc.step;
@@ -870,14 +926,9 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     stats->n_wide_waves = hc.n_cell ? n_wide_levels : 0;
     stats->n_wide_cells = hc.n_cell && tail_first ? lvl_begin(tail_first) : 0;
     stats->deep_cells = deep ? (int64_t)(hc.n_cell - q_deep0) : 0;
-    unsigned long long* pin_counts = (unsigned long long*)((char*)gr->pinned + PIN_FIRE);
     if (with_grad && dev == TDF_OK && P.vec) {
-      if (!gcount_fetched) {
-        HIP_TRY(hipMemcpyAsync(pin_counts, base + P.off_gcount, sizeof(unsigned long long) * 2, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-      }
-      stats->n_grad_firings = (int64_t)pin_counts[0];
-      stats->n_grad_not_once = (int64_t)pin_counts[1];
+      stats->n_grad_firings = (int64_t)fin->gcount[0];
+      stats->n_grad_not_once = (int64_t)fin->gcount[1];
     }
     stats->n_machines = (int32_t)e.n_dies;
     stats->die_local = gr->die_local ? 1 : 0;
@@ -890,19 +941,17 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     stats->peak_frames = (int64_t)hc.n_alloc;
     stats->frames_reclaimed = e.reclaim || use_lanes ? 1 : 0;
     stats->max_probe = hc.n_tags > e.n_inst ? 1 : 0;   // the match table is addressed without collisions
+    auto ms_between = [&](int from, int to) {   // 100 MHz clock
+      return fin->stamps[to] > fin->stamps[from] ? (double)(fin->stamps[to] - fin->stamps[from]) * 1e-5 : 0.0;
+    };
     for (int ph = 0; ph < TDF_PHASE_COUNT; ++ph) {
-      float ms = 0.f;
-      if (phase_used[ph] && hipEventElapsedTime(&ms, (hipEvent_t)gr->events[2 * ph], (hipEvent_t)gr->events[2 * ph + 1]) == hipSuccess)
-        stats->phase_ms[ph] = ms;
+      if (phase_used[ph]) stats->phase_ms[ph] = ms_between(2 * ph, 2 * ph + 1);
       stats->phase_launches[ph] = launches[ph];
     }
     if (phase_used[TDF_PHASE_CELLS_FWD]) {   // forward cell kernels on both streams: first launch to last end
-      float a = 0.f, b = 0.f;
-      (void)hipEventElapsedTime(&a, (hipEvent_t)gr->events[2 * TDF_PHASE_CELLS_FWD], (hipEvent_t)gr->events[2 * TDF_PHASE_CELLS_FWD + 1]);
-      if (phase_used[TDF_PHASE_TAIL_FWD] &&
-          hipEventElapsedTime(&b, (hipEvent_t)gr->events[2 * TDF_PHASE_CELLS_FWD], (hipEvent_t)gr->events[2 * TDF_PHASE_TAIL_FWD + 1]) != hipSuccess)
-        b = 0.f;
-      stats->fwd_cells_span_ms = std::max(a, b);
+      stats->fwd_cells_span_ms = ms_between(2 * TDF_PHASE_CELLS_FWD, 2 * TDF_PHASE_CELLS_FWD + 1);
+      if (phase_used[TDF_PHASE_TAIL_FWD])
+        stats->fwd_cells_span_ms = std::max(stats->fwd_cells_span_ms, ms_between(2 * TDF_PHASE_CELLS_FWD, 2 * TDF_PHASE_TAIL_FWD + 1));
     }
     if (e.step_log && !no_alloc && dev == TDF_OK) {
       // the widest steps of the tag machines: frames, frames created, duration
@@ -928,6 +977,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     stats->device_status = -(int32_t)hc.status;
     stats->n_counts = (int32_t)G.snodes.size();
     if (in->stats_level >= 1) {   // (below that level the counts are not taken: fire_count stays zero, no read-back)
+      unsigned long long* pin_counts = (unsigned long long*)((char*)gr->pinned + PIN_FIRE);
       launch_count_fired(G.prog, e, s);
       HIP_TRY(hipMemcpyAsync(pin_counts, e.fire_count, sizeof(unsigned long long) * TDF_STATS_MAX_COUNTS, hipMemcpyDeviceToHost, s));
       HIP_TRY(hipStreamSynchronize(s));
@@ -944,14 +994,12 @@ using namespace tdf;
 
 tdf_graph::~tdf_graph() {
   jit_release(jit);
-  for (void* ev : events)
-    if (ev) (void)hipEventDestroy((hipEvent_t)ev);
   for (void* st : {side_stream, sort_stream})
     if (st) {
       (void)hipStreamSynchronize((hipStream_t)st);
       (void)hipStreamDestroy((hipStream_t)st);
     }
-  for (void* ev : {fork_event, join_event, fork_deep, join_deep, fork_sort, join_sort, leaves_done})
+  for (void* ev : {fork_event, join_event, fork_deep, join_deep, fork_sort})
     if (ev) (void)hipEventDestroy((hipEvent_t)ev);
   if (pinned) (void)hipHostFree(pinned);
 }
@@ -1027,8 +1075,6 @@ extern "C" tdf_status tdf_graph_prepare(tdf_graph* g) {
       g_scratch_ptr[dev] = ptr;
     }
   }
-  for (int i = 0; i < 2 * TDF_PHASE_COUNT; ++i)
-    if (!g->events[i]) HIP_TRY(hipEventCreate((hipEvent_t*)&g->events[i]));
   if (tdf_status ps = pinned_reserve(g, PREPARED_LEVEL_BYTES); ps != TDF_OK) return ps;
   if (!g->jit.tried) {
     g->jit.tried = true;

@@ -80,6 +80,19 @@ struct LaneMail {
 };
 static_assert(sizeof(LaneMail) == 128, "one line per slot");
 struct LaneReply { unsigned long long value, flag; };   // flag 1: the value is there
+// What has to be in place before the lanes start, by thread i of n.
+__device__ inline void lane_init(const LaneArgs& a, uint32_t i, uint32_t n) {
+  if (i == 0) {
+    *a.ctl = LaneCtl{};
+    a.ctl->log_used = a.log_cap ? a.n_waves * LANE_CHUNK : 0u;
+    a.ctl->n_seg = a.n_waves * 64u;
+  }
+  if (i < a.n_queues) a.queues[i] = LaneQueue{};
+  for (uint32_t k = i; k < a.n_queues * a.queue_cap; k += n) a.mail[k].flag = LANE_EMPTY;
+  for (uint32_t k = i; k < a.n_waves * 64u; k += n) a.reply[k].flag = 0ull;
+  if (a.row_node)
+    for (uint32_t k = i; k < a.log_cap; k += n) a.row_node[k] = 0xFFFFFFFFu;
+}
 
 template <typename T> __device__ __forceinline__ T lane_ld(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "bucket.h"
+#include "die_sync.h"
 #include "lane_device.h"
 #include "step_device.h"
 #include "tdf_internal.h"
@@ -264,21 +265,14 @@ tdf_status launch_round(const DevProgram& P, const Engine& e, int cus, bool loca
 }
 
 // ---- depth-first lanes ------------------------------------------------------------------------
-__global__ void k_lane_init(LaneArgs a) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) {
-    *a.ctl = LaneCtl{};
-    a.ctl->log_used = a.log_cap ? a.n_waves * LANE_CHUNK : 0u;
-    a.ctl->n_seg = a.n_waves * 64u;
-  }
-  if (i < a.n_queues) a.queues[i] = LaneQueue{};
-  for (uint32_t k = i; k < a.n_queues * a.queue_cap; k += gridDim.x * blockDim.x) a.mail[k].flag = LANE_EMPTY;
-  for (uint32_t k = i; k < a.n_waves * 64u; k += gridDim.x * blockDim.x) a.reply[k].flag = 0ull;
-  if (a.row_node)
-    for (uint32_t k = i; k < a.log_cap; k += gridDim.x * blockDim.x) a.row_node[k] = 0xFFFFFFFFu;
+__global__ void k_lane_init(LaneArgs a, Stamp st) {
+  stamp_now(st);
+  lane_init(a, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+void launch_lane_init(const LaneArgs& a, const Stamp& st, hipStream_t s) {
+  hipLaunchKernelGGL(k_lane_init, dim3(grid_for(a.n_waves * 64, 256, 256)), dim3(256), 0, s, a, st);
 }
 tdf_status launch_lanes(const LaneArgs& a, int n_stored, const JitKernels& jit, hipStream_t s) {
-  hipLaunchKernelGGL(k_lane_init, dim3(grid_for(std::max(a.n_waves * 64, a.row_node ? a.log_cap : 0u), 256, 256)), dim3(256), 0, s, a);
   LaneArgs av = a;
   void* args[] = {&av};
   const hipError_t r = hipModuleLaunchKernel((hipFunction_t)jit.lanes, a.n_waves, 1, 1, 64, 1, 1, (unsigned)lane_lds_bytes(n_stored), s,
@@ -290,81 +284,207 @@ tdf_status launch_lanes(const LaneArgs& a, int n_stored, const JitKernels& jit, 
   return TDF_OK;
 }
 
+// Totals over the queues, by the first wave of a workgroup (up to 64 queues; the other waves' lanes get nothing).
+__device__ __forceinline__ void lane_totals(const LaneArgs& a, const LaneLimits& lim, LaneTotals& t) {
+  const uint32_t i = threadIdx.x;
+  LaneQueue q{};
+  if (i < a.n_queues) q = a.queues[i];
+  unsigned long long frames = (unsigned long long)q.n_rec + q.n_private;
+  for (int off = 32; off > 0; off >>= 1) {
+    q.n_leaf += __shfl_xor(q.n_leaf, off);
+    q.n_cell += __shfl_xor(q.n_cell, off);
+    q.n_tags += __shfl_xor(q.n_tags, off);
+    q.n_tokens += __shfl_xor(q.n_tokens, off);
+    frames += __shfl_xor(frames, off);
+    q.max_depth = max(q.max_depth, __shfl_xor(q.max_depth, off));
+    q.max_level = max(q.max_level, __shfl_xor(q.max_level, off));
+    q.max_iter = max(q.max_iter, __shfl_xor(q.max_iter, off));
+  }
+  t = LaneTotals{};
+  t.status = a.ctl->status;
+  t.n_log = min(a.ctl->log_used, a.log_cap);
+  t.n_leaf = q.n_leaf;
+  t.n_cell = q.n_cell;
+  t.max_depth = q.max_depth;
+  t.max_level = q.max_level;
+  t.max_iter = q.max_iter;
+  t.n_tags = q.n_tags;
+  t.n_tokens = q.n_tokens;
+  t.frames = frames;
+  t.bad = t.status != 0 || (lim.max_tags && q.n_tags > lim.max_tags) || (lim.max_cells && q.n_cell > lim.max_cells);
+  if (lim.deep_level && t.max_level >= lim.deep_level && t.n_cell) {
+    t.deep_level = lim.deep_level;
+    t.deep_base = lim.deep_level * LEVEL_KEY_DIES;
+  }
+  t.n_keys = t.n_cell ? t.deep_base + (t.max_level + 2) * LEVEL_KEY_DIES : 0u;
+}
+
 // ---- rows from the lanes' schedule log -------------------------------------------------------------
 // The log holds leaves and cells as they fired, named by their place in it, with holes where a wave did not
 // use what it had reserved.  First pass: leaves get rows 0 .. n_leaf - 1 (a range per workgroup), cells are
-// counted by sort key; then the scan of the counts; second pass: cells get their places in the sorted
-// schedule.  Both passes write row_of[name], with which k_translate_rows turns the children's names into rows.
+// counted by sort key, and the last workgroup scans the counts; second pass: cells get their places in the
+// sorted schedule.  Both passes write row_of[name], with which k_translate_rows turns the children's names into rows.
 // Memory bound in principle, launch bound at the sizes it runs at: hence two passes over the log instead
 // of separate merge, class, count, number and place kernels.
 struct LaneSort {
   const uint4* log;
-  uint32_t n_log, n_keys, deep_level, deep_base;   // deep_level 0: one class
-  uint32_t *row_of, *leaf_next;
+  const LaneTotals* t;
+  uint32_t *row_of, *leaf_next, *rows_done;
   const uint32_t* row_node;
-  int lds_keys;                                     // the counts of a workgroup fit in LDS
+  uint32_t lds_keys;                                // counts that a workgroup's LDS takes
+  uint32_t pin_keys;                                // level offsets that the host's copy takes
+  uint32_t* pin_off;
+  LaneReport* report;
+  uint32_t seq;
 };
-__device__ __forceinline__ uint32_t lane_key(const Engine& e, const LaneSort& t, const uint4& c) {
+// Before the first pass: the totals, and the counts of the sort keys cleared (their number is known only now).
+__global__ void __launch_bounds__(256) k_lane_plan(Engine e, LaneArgs a, LaneLimits lim, LaneTotals* out, Stamp st) {
+  __shared__ uint32_t n_keys;
+  stamp_now(st);
+  if (threadIdx.x < 64) {
+    LaneTotals t;
+    lane_totals(a, lim, t);
+    if (threadIdx.x == 0) {
+      n_keys = t.bad ? 0u : t.n_keys;
+      if (blockIdx.x == 0) *out = t;
+    }
+  }
+  __syncthreads();
+  for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n_keys; k += gridDim.x * blockDim.x) e.level_count[k] = e.level_fill[k] = 0;
+}
+__device__ __forceinline__ uint32_t lane_key(const Engine& e, const LaneTotals& t, const uint4& c) {
   const uint32_t deep = t.deep_level && e.root_lvl[c.w] >= t.deep_level ? t.deep_base : 0u;
   return deep + c.z * LEVEL_KEY_DIES + c.w % e.n_dies;
 }
-__global__ void __launch_bounds__(BUCKET_THREADS) k_lane_rows(Engine e, LaneSort t) {
+// The slice of the log of a workgroup: a multiple of its threads, so that a short log keeps few workgroups busy.
+__device__ __forceinline__ uint32_t lane_slice(uint32_t n_log) {
+  const uint32_t per = (n_log + gridDim.x - 1) / gridDim.x;
+  return max((per + blockDim.x - 1) / blockDim.x, 1u) * blockDim.x;
+}
+// The host's copy of what it has to know: the totals and the first cell of every key.  Whole workgroup.
+__device__ inline void lane_publish(const LaneSort& s, const LaneTotals& t, bool with_offsets) {
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    s.report->t = t;
+    s.report->t.published = with_offsets ? 1u : 0u;
+    __threadfence_system();
+    __hip_atomic_store(&s.report->seq, s.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+__global__ void __launch_bounds__(BUCKET_THREADS) k_lane_rows(Engine e, LaneSort s) {
   extern __shared__ uint32_t hist[];
-  __shared__ uint32_t n_leaf, leaf0;
+  __shared__ uint32_t n_leaf, leaf0, last, wsum[BUCKET_THREADS / 64];
+  const LaneTotals t = *s.t;
+  if (t.bad) {
+    if (blockIdx.x == 0) lane_publish(s, t, false);
+    return;
+  }
   const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
   if (t.deep_level)
     for (uint32_t i = gid; i < e.n_inst; i += gridDim.x * blockDim.x) e.inst_class[i] = e.root_lvl[i] >= t.deep_level ? 1u : 0u;
-  const uint32_t per = (t.n_log + gridDim.x - 1) / gridDim.x;
+  const uint32_t per = lane_slice(t.n_log), n_busy = max((t.n_log + per - 1) / per, 1u);
+  if (blockIdx.x >= n_busy) return;
   const uint32_t lo = min(t.n_log, blockIdx.x * per), hi = min(t.n_log, lo + per);
-  if (t.lds_keys)
+  const bool lds = t.n_keys <= s.lds_keys;
+  if (lds)
     for (uint32_t k = threadIdx.x; k < t.n_keys; k += blockDim.x) hist[k] = 0;
   if (threadIdx.x == 0) n_leaf = 0;
   __syncthreads();
   for (uint32_t base = lo; base < hi; base += blockDim.x) {   // uniform trip count for the workgroup
     const uint32_t i = base + threadIdx.x;
     uint4 c = make_uint4(0u, 0u, LANE_LOG_HOLE, 0u);
-    if (i < hi) c = t.log[i];
+    if (i < hi) c = s.log[i];
     (void)wave_alloc(c.z == 0u, &n_leaf);
     const bool cell = c.z != 0u && c.z != LANE_LOG_HOLE;
-    (void)wave_alloc_keyed(cell, cell ? lane_key(e, t, c) : 0u, t.lds_keys ? hist : e.level_count);
+    if (lds) {   // (a clock per lane with the same key)
+      if (cell) atomicAdd(&hist[lane_key(e, t, c)], 1u);
+    } else {
+      (void)wave_alloc_keyed(cell, cell ? lane_key(e, t, c) : 0u, e.level_count);
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    leaf0 = n_leaf ? atomicAdd(t.leaf_next, n_leaf) : 0u;
+    leaf0 = n_leaf ? atomicAdd(s.leaf_next, n_leaf) : 0u;
     n_leaf = 0;
   }
+  if (lds)
+    for (uint32_t k = threadIdx.x; k < t.n_keys; k += blockDim.x)
+      if (hist[k]) atomicAdd(&e.level_count[k], hist[k]);
   __syncthreads();
   for (uint32_t base = lo; base < hi; base += blockDim.x) {
     const uint32_t i = base + threadIdx.x;
     uint4 c = make_uint4(0u, 0u, LANE_LOG_HOLE, 0u);
-    if (i < hi) c = t.log[i];
+    if (i < hi) c = s.log[i];
     const uint32_t row = leaf0 + wave_alloc(c.z == 0u, &n_leaf);
     if (c.z == 0u) {
       e.leaf_tok[row] = c.x;
-      t.row_of[i] = row;
-      if (e.node_of_row) e.node_of_row[row] = t.row_node[i];
+      s.row_of[i] = row;
+      if (e.node_of_row) e.node_of_row[row] = s.row_node[i];
     }
   }
-  if (t.lds_keys)
-    for (uint32_t k = threadIdx.x; k < t.n_keys; k += blockDim.x)
-      if (hist[k]) atomicAdd(&e.level_count[k], hist[k]);
+  // The workgroup that is through last turns the counts into offsets (four keys per thread and round), for the
+  // second pass and for the host, which starts on the launches of the levels while the passes after this one run.
+  // (The counts are device-scope atomics: one that is acknowledged is visible to every die.)
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) last = atomicAdd(s.rows_done, 1u) + 1u == n_busy;
+  __syncthreads();
+  if (!last) return;
+  const bool pin = t.n_keys <= s.pin_keys;
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  uint32_t carry = 0;
+  for (uint32_t base = 0; base < t.n_keys; base += BUCKET_THREADS * 4) {
+    const uint32_t k0 = base + threadIdx.x * 4;
+    uint32_t c[4], sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      c[j] = k0 + j < t.n_keys ? __hip_atomic_load(&e.level_count[k0 + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+      sum += c[j];
+    }
+    uint32_t inc = sum;   // inclusive over the wave
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t o = __shfl_up(inc, off);
+      if ((int)lane >= off) inc += o;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    uint32_t x = carry + inc - sum;
+    for (uint32_t w = 0; w < BUCKET_THREADS / 64; ++w) {
+      if (w < wave) x += wsum[w];
+      carry += wsum[w];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      if (k0 + j < t.n_keys) {
+        e.level_off[k0 + j] = x;
+        if (pin) s.pin_off[k0 + j] = x;
+      }
+      x += c[j];
+    }
+  }
+  lane_publish(s, t, pin);
 }
-__global__ void __launch_bounds__(BUCKET_THREADS) k_lane_place(Engine e, LaneSort t) {
+__global__ void __launch_bounds__(BUCKET_THREADS) k_lane_place(Engine e, LaneSort s) {
   extern __shared__ uint32_t hist[];
-  const uint32_t per = (t.n_log + gridDim.x - 1) / gridDim.x;
+  const LaneTotals t = *s.t;
+  if (t.bad || t.n_keys == 0) return;
+  const uint32_t per = lane_slice(t.n_log);
   const uint32_t lo = min(t.n_log, blockIdx.x * per), hi = min(t.n_log, lo + per);
+  if (lo >= hi) return;
+  const bool lds = t.n_keys <= s.lds_keys;
   auto cell_at = [&](uint32_t i, uint4& c) {
     c = make_uint4(0u, 0u, LANE_LOG_HOLE, 0u);
-    if (i < hi) c = t.log[i];
+    if (i < hi) c = s.log[i];
     return c.z != 0u && c.z != LANE_LOG_HOLE;
   };
-  if (t.lds_keys) {
+  if (lds) {
     for (uint32_t k = threadIdx.x; k < t.n_keys; k += blockDim.x) hist[k] = 0;
     __syncthreads();
     for (uint32_t base = lo; base < hi; base += blockDim.x) {
       uint4 c;
-      const bool cell = cell_at(base + threadIdx.x, c);
-      (void)wave_alloc_keyed(cell, cell ? lane_key(e, t, c) : 0u, hist);
+      if (cell_at(base + threadIdx.x, c)) atomicAdd(&hist[lane_key(e, t, c)], 1u);
     }
     __syncthreads();
     // the workgroup's range of every key it holds; the LDS entry becomes the next free position
@@ -377,16 +497,47 @@ __global__ void __launch_bounds__(BUCKET_THREADS) k_lane_place(Engine e, LaneSor
     uint4 c;
     const bool cell = cell_at(i, c);
     const uint32_t key = cell ? lane_key(e, t, c) : 0u;
-    uint32_t q = wave_alloc_keyed(cell, key, t.lds_keys ? hist : e.level_fill);
+    uint32_t q = 0;
+    if (lds) {
+      if (cell) q = atomicAdd(&hist[key], 1u);
+    } else {
+      q = wave_alloc_keyed(cell, key, e.level_fill);
+      if (cell) q += e.level_off[key];
+    }
     if (cell) {
-      if (!t.lds_keys) q += e.level_off[key];
       e.q_l[q] = c.x;
       e.q_r[q] = c.y;
-      t.row_of[i] = e.row0 + q;
-      if (e.node_of_row) e.node_of_row[e.row0 + q] = t.row_node[i];
+      s.row_of[i] = t.n_leaf + q;
+      if (e.node_of_row) e.node_of_row[t.n_leaf + q] = s.row_node[i];
     }
   }
 }
+
+// The end of an evaluation: what the host reads back, and the word it waits for.
+__global__ void __launch_bounds__(256) k_finish(LaneArgs a, EndArgs g, Stamp st) {
+  stamp_now(st);
+  if (threadIdx.x < 64) {
+    if (g.lanes) {   // (a program without vector operators: the totals have not been read yet)
+      LaneTotals t;
+      lane_totals(a, LaneLimits{}, t);
+      if (threadIdx.x == 0) g.end->t = t;
+    }
+    if (g.gcount && threadIdx.x < 2) g.end->gcount[threadIdx.x] = g.gcount[threadIdx.x];
+    __threadfence();
+    if (threadIdx.x < 2 * TDF_PHASE_COUNT) g.end->stamps[threadIdx.x] = g.stamps[threadIdx.x];
+  }
+  if (g.sync)
+    for (uint32_t i = threadIdx.x; i < 16u * sizeof(DieSync) / 4; i += blockDim.x)
+      reinterpret_cast<uint32_t*>(g.end->sync)[i] = reinterpret_cast<const uint32_t*>(g.sync)[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(&g.end->seq, g.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+void launch_finish(const LaneArgs& a, const EndArgs& g, const Stamp& st, hipStream_t s) {
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(256), 0, s, a, g, st);
+}
+__global__ void k_stamp(Stamp st) { stamp_now(st); }
+void launch_stamp(const Stamp& st, hipStream_t s) { hipLaunchKernelGGL(k_stamp, dim3(1), dim3(1), 0, s, st); }
 
 // Copies the machines' logs into the merged logs; leaf_off / cell_off: n_dies + 1 prefix sums.
 void launch_merge_logs(const Engine& e, const uint32_t* leaf_off, const uint32_t* cell_off, hipStream_t s) {
@@ -419,41 +570,30 @@ void launch_class_keys(const DevProgram& P, const Engine& e, uint32_t n_cell, ui
   hipLaunchKernelGGL(k_class_keys, dim3(grid_for(n, 256, 1 << 20)), dim3(256), 0, s, e, P, n_cell, deep_level, deep_base);
 }
 
-// The two passes over the lanes' log.  n_keys 0: no cells.
-static LaneSort lane_sort(const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base) {
+// Totals and the two passes over the lanes' log, queued behind the lanes: what they work on is known to the GPU
+// only.  The grids and the LDS are for the largest log and the most levels there can be, up to what fills the
+// GPU (then every workgroup has more than one slice of its threads).
+void launch_lane_sort(const Engine& e, const LaneArgs& a, const LaneLimits& lim, uint32_t* row_node, LaneTotals* totals,
+                      LaneReport* report, uint32_t* pin_off, uint32_t pin_keys, uint32_t seq, const Stamp& st, hipStream_t s) {
   LaneSort t{};
   t.log = a.log;
-  t.n_log = n_log;
-  t.n_keys = n_keys;
-  t.deep_level = deep_level;
-  t.deep_base = deep_base;
+  t.t = totals;
   t.row_of = a.row_of;
   t.leaf_next = &a.ctl->leaf_next;
-  t.row_node = a.row_node;
-  t.lds_keys = bucket_fits(n_keys);
-  return t;
-}
-static int lane_sort_blocks(uint32_t n_log) { return grid_for(n_log, BUCKET_THREADS, BUCKET_BLOCKS); }
-void launch_lane_rows(const Engine& e, const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base,
-                      hipStream_t s) {
-  if (n_keys) {
-    if (e.level_fill > e.level_count) {   // (the two arrays lie one behind the other in the workspace: one fill)
-      (void)hipMemsetAsync(e.level_count, 0, (size_t)((char*)(e.level_fill + n_keys) - (char*)e.level_count), s);
-    } else {
-      (void)hipMemsetAsync(e.level_count, 0, sizeof(uint32_t) * n_keys, s);
-      (void)hipMemsetAsync(e.level_fill, 0, sizeof(uint32_t) * n_keys, s);
-    }
-  }
-  const LaneSort t = lane_sort(a, n_log, n_keys, deep_level, deep_base);
-  if (t.lds_keys) bucket_lds_opt_in(reinterpret_cast<const void*>(&k_lane_rows), n_keys);
-  hipLaunchKernelGGL(k_lane_rows, dim3(lane_sort_blocks(n_log)), dim3(BUCKET_THREADS), t.lds_keys ? (size_t)n_keys * 4 : 0, s, e, t);
-}
-void launch_lane_place(const Engine& e, const LaneArgs& a, uint32_t n_log, uint32_t n_keys, uint32_t deep_level, uint32_t deep_base,
-                       hipStream_t s) {
-  const LaneSort t = lane_sort(a, n_log, n_keys, deep_level, deep_base);
-  if (t.lds_keys) bucket_lds_opt_in(reinterpret_cast<const void*>(&k_lane_place), n_keys);
-  hipLaunchKernelGGL(k_level_scan, dim3(1), dim3(1024), 0, s, e, n_keys);
-  hipLaunchKernelGGL(k_lane_place, dim3(lane_sort_blocks(n_log)), dim3(BUCKET_THREADS), t.lds_keys ? (size_t)n_keys * 4 : 0, s, e, t);
+  t.rows_done = &a.ctl->rows_done;
+  t.row_node = row_node;
+  t.pin_keys = pin_keys;
+  t.pin_off = pin_off;
+  t.report = report;
+  t.seq = seq;
+  const uint64_t most_keys = ((uint64_t)e.max_levels + lim.deep_level + 2) * LEVEL_KEY_DIES;
+  t.lds_keys = (uint32_t)std::min<uint64_t>(most_keys, BUCKET_MAX_KEYS);
+  bucket_lds_opt_in(reinterpret_cast<const void*>(&k_lane_rows), t.lds_keys);
+  bucket_lds_opt_in(reinterpret_cast<const void*>(&k_lane_place), t.lds_keys);
+  const int grid = grid_for(a.log_cap, BUCKET_THREADS, BUCKET_BLOCKS);
+  hipLaunchKernelGGL(k_lane_plan, dim3(grid_for(std::min<uint64_t>(most_keys, 1u << 16), 1024, 64)), dim3(256), 0, s, e, a, lim, totals, st);
+  hipLaunchKernelGGL(k_lane_rows, dim3(grid), dim3(BUCKET_THREADS), (size_t)t.lds_keys * 4, s, e, t);
+  hipLaunchKernelGGL(k_lane_place, dim3(grid), dim3(BUCKET_THREADS), (size_t)t.lds_keys * 4, s, e, t);
 }
 
 // Counting sort of the cell log by sort key (n_keys keys); level_off[k] = first cell of key k.

@@ -6,6 +6,7 @@
 #include <string>
 #include <vector>
 
+#include "engine.h"
 #include "tdf.h"
 #include "tdf_tables.h"
 
@@ -24,6 +25,23 @@ struct Graph {
 };
 
 void set_error(const std::string& msg);
+
+// The end of an evaluation: what its last kernel leaves in pinned memory for the host; `seq` is written last.
+struct EndReport {
+  LaneTotals t;
+  uint32_t sync[16][32];          // DieSync records of the chain launches (forward, gradient)
+  unsigned long long gcount[2];
+  unsigned long long stamps[2 * TDF_PHASE_COUNT];
+  uint32_t seq;
+};
+struct EndArgs {
+  EndReport* end;
+  const unsigned long long* stamps;
+  const unsigned long long* gcount;   // null: no gradient pass
+  const void* sync;                   // null: no chain launch
+  uint32_t seq;
+  int lanes;                          // the lanes' totals are wanted
+};
 
 // Run-time generated step kernels for one program (jit.cpp).  Returns false (and leaves the
 // handles null) when the run-time compiler is unavailable, disabled (TDF_NO_JIT=1) or fails;
@@ -52,17 +70,16 @@ struct tdf_graph {
   bool die_local = true;    // tag machines keep to one accelerator die each (cleared if the GPU spreads them)
   bool lanes_ok = true;     // depth-first lanes (cleared once a run met something they leave to the step machine)
   uint32_t max_dies = 8;    // tag machines a batch is dealt to (set to 1 after a part of the table overflowed)
-  void* events[2 * TDF_PHASE_COUNT] = {nullptr};   // hipEvent_t pairs, created on first use
   void* side_stream = nullptr;                     // hipStream_t for work beside the caller's stream
   void* fork_event = nullptr, *join_event = nullptr;   // embedding gradient beside the weight gradients
   void* fork_deep = nullptr, *join_deep = nullptr;     // deep instances beside the others
   void* sort_stream = nullptr;                     // hipStream_t for the embedding gradient's token sort
-  void* fork_sort = nullptr, *join_sort = nullptr;     // ... which starts once the leaves are known
-  void* leaves_done = nullptr;                     // the leaves' rows, written on that stream too
+  void* fork_sort = nullptr;                       // ... which starts once the leaves are known
   // pinned host memory for what an evaluation reads back or sends (control blocks, level offsets,
   // barrier records, the firing tables): copies to and from pageable memory are staged and slower
   void* pinned = nullptr;
   size_t pinned_bytes = 0;
+  uint32_t seq = 0;         // of the last report awaited there
   std::mutex busy;          // one evaluation at a time uses the graph's streams, events and host buffer
   bool prepared = false;    // tdf_graph_prepare has run: kernels compiled, events and host buffers exist
   int prepared_device = -1;
