@@ -496,9 +496,73 @@ struct DzFuse {
   uint32_t q_first;              // first cell of the tail in the sorted log
 };
 
+// What a tile reads that no tile writes: the children's rows, and for the fused dz the forward state of the child
+// cells.  Three loads that follow one another; the tail kernels request the next level's while they wait at the barrier.
+template <int MODE, int NW> struct TileAhead {
+  static constexpr int RPW = 16 / NW;   // accumulator registers (rows of a lane) a wave finishes
+  uint32_t child;                       // operand row of this lane (forward)
+  uint32_t o_l[RPW], o_r[RPW];
+  uint32_t z_q[RPW], z_gl[RPW], z_gr[RPW];   // fused dz: the child cell (none: all ones) and its children's rows
+  float z_gate[RPW][5], z_c[RPW], z_h[RPW], z_own[RPW], z_cl[RPW], z_cr[RPW];
+};
+// row of the tile that this lane finishes with accumulator register r = RPW * wave + rr
+template <int NW> __device__ __forceinline__ int tile_row_of(int rr) {
+  const int r = 16 / NW * (int)(threadIdx.x >> 6) + rr;
+  return (r >> 2) * 8 + (int)((threadIdx.x & 63) >> 5) * 4 + (r & 3);
+}
+template <int DT, int MODE, int NW>
+__device__ __forceinline__ void tile_ahead(const GemmArgs& g, int rt, int ct, const DzFuse* fz, TileAhead<MODE, NW>& p) {
+  typedef typename TypeOf<DT>::type T;
+  constexpr int RPW = TileAhead<MODE, NW>::RPW;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m0 = rt * 32, mA = min(m0 + (lane & 31), g.M - 1);
+  if (MODE != DX_BWD) p.child = wave < NW / 2 ? g.l[mA] : g.r[mA];   // first half of the waves: h_l of [h_l; h_r]
+  if (MODE != RNN_FWD) {
+#pragma unroll
+    for (int rr = 0; rr < RPW; ++rr) {
+      const int m = min(m0 + tile_row_of<NW>(rr), g.M - 1);
+      p.o_l[rr] = g.l[m];
+      p.o_r[rr] = g.r[m];
+    }
+  }
+  if (MODE == DX_BWD && fz != nullptr) {
+    const VecArgs& v = *fz->v;
+    const int unit = ct * 32 + (lane & 31);
+    const bool left = unit < g.Hp;
+    const int n = left ? unit : unit - g.Hp;
+#pragma unroll
+    for (int rr = 0; rr < RPW; ++rr) {
+      const uint32_t row = left ? p.o_l[rr] : p.o_r[rr];
+      const bool ok = row >= fz->row0 && row - fz->row0 >= fz->q_first;   // a cell of the tail (a leaf has none)
+      const uint32_t qc = ok ? row - fz->row0 : 0u;   // (cell 0 exists whenever a level has cells: a safe address)
+      p.z_q[rr] = ok ? qc : 0xFFFFFFFFu;
+      const size_t o = (size_t)row * v.Hp + n;
+      p.z_own[rr] = v.dHn ? v.dHn[o] : 0.f;   // gradient of the child's own loss term
+      if (v.cell_kind == 1) {
+        p.z_h[rr] = to_f(reinterpret_cast<const T*>(v.Hs)[o]);
+      } else {
+        const T* g5 = reinterpret_cast<const T*>(v.gates) + (size_t)qc * v.Np + n;
+        p.z_gl[rr] = fz->q_l[qc];
+        p.z_gr[rr] = fz->q_r[qc];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) p.z_gate[rr][k] = to_f(g5[k * v.Hp]);
+        p.z_c[rr] = ok ? v.Cs[o] : 0.f;
+      }
+    }
+    if (v.cell_kind == 2) {
+#pragma unroll
+      for (int rr = 0; rr < RPW; ++rr) {
+        p.z_cl[rr] = p.z_gl[rr] >= fz->row0 ? v.Cs[(size_t)p.z_gl[rr] * v.Hp + n] : 0.f;   // (a leaf's cell state is zero)
+        p.z_cr[rr] = p.z_gr[rr] >= fz->row0 ? v.Cs[(size_t)p.z_gr[rr] * v.Hp + n] : 0.f;
+      }
+    }
+  }
+}
+
 template <int DT, int MODE, int NW, int RES = 0>
 __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int ct, float* part,
-                                                const ResidentB<MODE, RES>* rb = nullptr, const DzFuse* fz = nullptr) {
+                                                const TileAhead<MODE, NW>& p, const ResidentB<MODE, RES>* rb = nullptr,
+                                                const DzFuse* fz = nullptr) {
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   constexpr int G = MODE == LSTM_FWD ? 5 : 1;      // 32-wide column blocks per tile
@@ -510,25 +574,13 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
   const int mA = min(m0 + (lane & 31), g.M - 1);   // operand row of this lane
   const int kw = g.K / NW;                         // reduction range of this wave: [wave * kw, +kw)
 
-  // rows this lane finishes: accumulator register r = RPW * wave + rr holds row (r / 4) * 8 + (lane / 32) * 4 + r % 4
-  auto row_of = [&](int rr) {
-    const int r = RPW * wave + rr;
-    return (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-  };
-  uint32_t o_out[RPW], o_l[RPW], o_r[RPW];
-#pragma unroll
-  for (int rr = 0; rr < RPW; ++rr) {
-    const int m = min(m0 + row_of(rr), g.M - 1);
-    if (MODE != DX_BWD) o_out[rr] = g.out0 + (uint32_t)m;
-    if (MODE != RNN_FWD) { o_l[rr] = g.l[m]; o_r[rr] = g.r[m]; }
-  }
+  auto row_of = [&](int rr) { return tile_row_of<NW>(rr); };
   // operand bases (elements)
   const T* Ap;
   if (MODE == DX_BWD) {
     Ap = reinterpret_cast<const T*>(g.A) + (size_t)mA * g.lda + wave * kw;
   } else {
-    const uint32_t child = wave < NW / 2 ? g.l[mA] : g.r[mA];   // first half of the waves: h_l of [h_l; h_r]
-    Ap = reinterpret_cast<const T*>(g.Hs) + (size_t)child * g.Hp + (wave % (NW / 2)) * kw;
+    Ap = reinterpret_cast<const T*>(g.Hs) + (size_t)p.child * g.Hp + (wave % (NW / 2)) * kw;
   }
   Ap += (lane >> 5) * EPC;
   const T* Bp[G];
@@ -541,25 +593,15 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
 #pragma unroll
     for (int rr = 0; rr < RPW; ++rr) {
       // (a leaf child has no stored cell state: it reads row 0, a leaf's row that k_embed keeps zero)
-      cl[rr] = g.Cs[(o_l[rr] >= g.leaf_rows ? o_l[rr] : 0u) * (uint32_t)g.Hp + (uint32_t)unit];
-      cr[rr] = g.Cs[(o_r[rr] >= g.leaf_rows ? o_r[rr] : 0u) * (uint32_t)g.Hp + (uint32_t)unit];
+      cl[rr] = g.Cs[(p.o_l[rr] >= g.leaf_rows ? p.o_l[rr] : 0u) * (uint32_t)g.Hp + (uint32_t)unit];
+      cr[rr] = g.Cs[(p.o_r[rr] >= g.leaf_rows ? p.o_r[rr] : 0u) * (uint32_t)g.Hp + (uint32_t)unit];
     }
   }
 
-  // fused dz (DX_BWD in the tail): which child cell, and what its dz needs, requested early
-  uint32_t z_q[RPW], z_row[RPW], z_gl[RPW], z_gr[RPW];
-  float z_gate[RPW][5], z_c[RPW], z_dc[RPW], z_h[RPW], z_own[RPW];
   const bool z_on = MODE == DX_BWD && fz != nullptr;
   const bool z_left = unit < g.Hp;
   const int z_n = z_left ? unit : unit - g.Hp;
-  if (MODE == DX_BWD && z_on) {
-#pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const int m = min(m0 + row_of(rr), g.M - 1);
-      z_row[rr] = z_left ? o_l[rr] : o_r[rr];
-      z_q[rr] = z_row[rr] >= fz->row0 ? z_row[rr] - fz->row0 : 0xFFFFFFFFu;   // a leaf has no cell
-    }
-  }
+  float z_dc[RPW];   // fused dz: dc of the child cells, which their parents' dz (a level ago) has left
 
   f32x16 acc[G];
 #pragma unroll
@@ -567,27 +609,10 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
   const int steps = kw / C::KC;
-  if (MODE == DX_BWD && z_on) {
-    const VecArgs& v = *fz->v;
+  if (MODE == DX_BWD && z_on && fz->v->cell_kind == 2) {
 #pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const bool ok = z_q[rr] != 0xFFFFFFFFu && z_q[rr] >= fz->q_first;
-      if (!ok) z_q[rr] = 0xFFFFFFFFu;
-      const uint32_t qc = ok ? z_q[rr] : 0u;   // (cell 0 exists whenever a level has cells: a safe address)
-      const size_t o = (size_t)z_row[rr] * v.Hp + z_n;
-      z_own[rr] = v.dHn ? v.dHn[o] : 0.f;   // gradient of the child's own loss term
-      if (v.cell_kind == 1) {
-        z_h[rr] = to_f(reinterpret_cast<const T*>(v.Hs)[o]);
-      } else {
-        const T* g5 = reinterpret_cast<const T*>(v.gates) + (size_t)qc * v.Np + z_n;
-#pragma unroll
-        for (int k = 0; k < 5; ++k) z_gate[rr][k] = to_f(g5[k * v.Hp]);
-        z_c[rr] = v.Cs[o];
-        z_dc[rr] = v.dC[o];
-        z_gl[rr] = fz->q_l[qc];
-        z_gr[rr] = fz->q_r[qc];
-      }
-    }
+    for (int rr = 0; rr < RPW; ++rr)
+      z_dc[rr] = p.z_q[rr] != 0xFFFFFFFFu ? fz->v->dC[(size_t)(z_left ? p.o_l[rr] : p.o_r[rr]) * g.Hp + z_n] : 0.f;
   }
   if constexpr (RES > 0) {
     u32x4 fa[RES];
@@ -650,7 +675,7 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
       const float go = Act<T>::sigmoid_b(z[3][rr], bo);
       const float gu = Act<T>::tanh_b(z[4][rr], bu);
       const float c = gi * gu + gfl * cl[rr] + gfr * cr[rr];
-      const size_t o = (size_t)o_out[rr] * g.Hp + unit;
+      const size_t o = (size_t)(g.out0 + (uint32_t)m) * g.Hp + unit;
       g.Cs[o] = c;
       reinterpret_cast<T*>(g.Hs_out)[o] = from_f<T>(go * Act<T>::tanh_b(c, 0.f));
       if (g.save_gates) {
@@ -668,46 +693,40 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
     for (int rr = 0; rr < RPW; ++rr) {
       const int m = m0 + row_of(rr);
       if (m >= g.M) continue;
-      reinterpret_cast<T*>(g.Hs_out)[(size_t)o_out[rr] * g.Hp + unit] = from_f<T>(Act<T>::tanh(z[0][rr] + bias));
+      reinterpret_cast<T*>(g.Hs_out)[(size_t)(g.out0 + (uint32_t)m) * g.Hp + unit] = from_f<T>(Act<T>::tanh(z[0][rr] + bias));
     }
   } else {   // DX_BWD: column `unit` of [dh_l; dh_r]; each child row has exactly one consumer
 #pragma unroll
     for (int rr = 0; rr < RPW; ++rr) {
       const int m = m0 + row_of(rr);
       if (m >= g.M) continue;
-      if (unit < g.Hp) g.C[(size_t)o_l[rr] * g.Hp + unit] = z[0][rr];
-      else g.C[(size_t)o_r[rr] * g.Hp + (unit - g.Hp)] = z[0][rr];
+      if (unit < g.Hp) g.C[(size_t)p.o_l[rr] * g.Hp + unit] = z[0][rr];
+      else g.C[(size_t)p.o_r[rr] * g.Hp + (unit - g.Hp)] = z[0][rr];
     }
     if (z_on) {
       const VecArgs& v = *fz->v;
-      float z_cl[RPW], z_cr[RPW];
-      if (v.cell_kind == 2) {
-#pragma unroll
-        for (int rr = 0; rr < RPW; ++rr) {
-          z_cl[rr] = z_gl[rr] >= fz->row0 ? v.Cs[(size_t)z_gl[rr] * v.Hp + z_n] : 0.f;   // (a leaf's cell state is zero)
-          z_cr[rr] = z_gr[rr] >= fz->row0 ? v.Cs[(size_t)z_gr[rr] * v.Hp + z_n] : 0.f;
-        }
-      }
 #pragma unroll
       for (int rr = 0; rr < RPW; ++rr) {
         const int m = m0 + row_of(rr);
-        if (m >= g.M || z_q[rr] == 0xFFFFFFFFu) continue;
-        const float dh = z[0][rr] + z_own[rr];
-        if (z_n == 0) atomicAdd(&v.gmark[z_row[rr]], 1u);   // one lane per child cell: its gradient body fires here
-        T* dz = reinterpret_cast<T*>(v.Dz) + (size_t)z_q[rr] * v.Np + z_n;
+        if (m >= g.M || p.z_q[rr] == 0xFFFFFFFFu) continue;
+        const float dh = z[0][rr] + p.z_own[rr];
+        // One lane per child cell: its gradient body fires here.  (In the die's L2: the row is this die's.)
+        if (z_n == 0)
+          __hip_atomic_fetch_add(&v.gmark[z_left ? p.o_l[rr] : p.o_r[rr]], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        T* dz = reinterpret_cast<T*>(v.Dz) + (size_t)p.z_q[rr] * v.Np + z_n;
         if (v.cell_kind == 1) {
-          dz[0] = from_f<T>(dh * (1.f - z_h[rr] * z_h[rr]));
+          dz[0] = from_f<T>(dh * (1.f - p.z_h[rr] * p.z_h[rr]));
         } else {
-          const float gi = z_gate[rr][0], gfl = z_gate[rr][1], gfr = z_gate[rr][2], go = z_gate[rr][3], gu = z_gate[rr][4];
-          const float tc = Act<T>::tanh(z_c[rr]);
+          const float gi = p.z_gate[rr][0], gfl = p.z_gate[rr][1], gfr = p.z_gate[rr][2], go = p.z_gate[rr][3], gu = p.z_gate[rr][4];
+          const float tc = Act<T>::tanh(p.z_c[rr]);
           const float dc = z_dc[rr] + dh * go * (1.f - tc * tc);
           dz[0] = from_f<T>(dc * gu * gi * (1.f - gi));
-          dz[v.Hp] = from_f<T>(dc * z_cl[rr] * gfl * (1.f - gfl));
-          dz[2 * v.Hp] = from_f<T>(dc * z_cr[rr] * gfr * (1.f - gfr));
+          dz[v.Hp] = from_f<T>(dc * p.z_cl[rr] * gfl * (1.f - gfl));
+          dz[2 * v.Hp] = from_f<T>(dc * p.z_cr[rr] * gfr * (1.f - gfr));
           dz[3 * v.Hp] = from_f<T>(dh * tc * go * (1.f - go));
           dz[4 * v.Hp] = from_f<T>(dc * gi * (1.f - gu * gu));
-          if (z_gl[rr] >= fz->row0) v.dC[(size_t)z_gl[rr] * v.Hp + z_n] = dc * gfl;   // (a leaf has no use for dc)
-          if (z_gr[rr] >= fz->row0) v.dC[(size_t)z_gr[rr] * v.Hp + z_n] = dc * gfr;
+          if (p.z_gl[rr] >= fz->row0) v.dC[(size_t)p.z_gl[rr] * v.Hp + z_n] = dc * gfl;   // (a leaf has no use for dc)
+          if (p.z_gr[rr] >= fz->row0) v.dC[(size_t)p.z_gr[rr] * v.Hp + z_n] = dc * gfr;
         }
       }
     }
@@ -720,7 +739,10 @@ __global__ void __launch_bounds__(NW * 64) k_cell_small(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   stamp_now(g.stamp);
   const int n_ct = g.n_tiles_n;                    // column tiles of 32
-  cell_small_tile<DT, MODE, NW>(g, blockIdx.x / n_ct, blockIdx.x % n_ct, reinterpret_cast<float*>(smem));
+  const int rt = blockIdx.x / n_ct, ct = blockIdx.x % n_ct;
+  TileAhead<MODE, NW> p;
+  tile_ahead<DT, MODE, NW>(g, rt, ct, nullptr, p);
+  cell_small_tile<DT, MODE, NW>(g, rt, ct, reinterpret_cast<float*>(smem), p);
 }
 
 // Levels of at most this many cells take the small-level kernel (TDF_SMALL_LEVEL overrides).
@@ -1113,23 +1135,40 @@ __global__ void __launch_bounds__(NW * 64) k_tail_fwd(GemmArgs g, TailArgs t) {
   const bool resident = G % (uint32_t)n_ct == 0 && g.K / NW / Chunk<T>::KC <= RES;
   ResidentB<MODE, RES> rb;
   if (resident) load_resident_b<DT, MODE, NW, RES>(g, (int)(rank % n_ct), rb);
-  uint32_t gen = 0;
-  for (uint32_t lvl = t.lvl_first; lvl <= t.lvl_last; ++lvl) {
-    const uint32_t q0 = t.level_off[lvl * LEVEL_KEY_DIES + die];
-    const uint32_t cnt = t.level_off[lvl * LEVEL_KEY_DIES + die + 1] - q0;
+  const uint32_t step = resident ? G / n_ct : G;   // this workgroup's tiles: every step-th row tile of its column, or every step-th tile
+  const uint32_t first = resident ? rank / n_ct : rank;
+  auto cells_of = [&](uint32_t lvl, uint32_t& q0, uint32_t& cnt) {
+    q0 = t.level_off[lvl * LEVEL_KEY_DIES + die];
+    cnt = t.level_off[lvl * LEVEL_KEY_DIES + die + 1] - q0;
+  };
+  auto level_args = [&](uint32_t q0, uint32_t cnt) {
     GemmArgs gl = g;
     gl.M = (int)cnt;
     gl.out0 = g.out0 + q0; gl.l = g.l + q0; gl.r = g.r + q0;
     gl.gates = g.gates ? reinterpret_cast<T*>(g.gates) + (size_t)q0 * g.ldg : nullptr;
-    const uint32_t n_rt = (cnt + 31) / 32;
-    if (resident) {
-      for (uint32_t rt = rank / n_ct; rt < n_rt; rt += G / n_ct)
-        cell_small_tile<DT, MODE, NW, RES>(gl, (int)rt, (int)(rank % n_ct), part, &rb);
-    } else {
-      for (uint32_t tile = rank; tile < n_rt * n_ct; tile += G)
-        cell_small_tile<DT, MODE, NW>(gl, (int)(tile / n_ct), (int)(tile % n_ct), part);
+    return gl;
+  };
+  auto row_tile = [&](uint32_t tile) { return (int)(resident ? tile : tile / n_ct); };
+  auto col_tile = [&](uint32_t tile) { return (int)(resident ? rank % n_ct : tile % n_ct); };
+  auto tiles_of = [&](uint32_t cnt) { return (cnt + 31) / 32 * (resident ? 1u : (uint32_t)n_ct); };
+  uint32_t gen = 0, q0, cnt, q1 = 0, cnt1 = 0;
+  TileAhead<MODE, NW> p;
+  cells_of(t.lvl_first, q0, cnt);
+  if (first < tiles_of(cnt)) tile_ahead<DT, MODE, NW>(level_args(q0, cnt), row_tile(first), col_tile(first), nullptr, p);
+  for (uint32_t lvl = t.lvl_first; lvl <= t.lvl_last; ++lvl) {
+    if (lvl < t.lvl_last) cells_of(lvl + 1, q1, cnt1);
+    const GemmArgs gl = level_args(q0, cnt);
+    for (uint32_t tile = first; tile < tiles_of(cnt); tile += step) {
+      if (tile != first) tile_ahead<DT, MODE, NW>(gl, row_tile(tile), col_tile(tile), nullptr, p);
+      if (resident) cell_small_tile<DT, MODE, NW, RES>(gl, row_tile(tile), col_tile(tile), part, p, &rb);
+      else cell_small_tile<DT, MODE, NW>(gl, row_tile(tile), col_tile(tile), part, p);
     }
-    if (!die_barrier(sy, G, gen++, t.spin_ticks, &sh_ok)) return;
+    die_arrive(sy, gen);
+    if (lvl < t.lvl_last && first < tiles_of(cnt1))
+      tile_ahead<DT, MODE, NW>(level_args(q1, cnt1), row_tile(first), col_tile(first), nullptr, p);
+    if (!die_wait(sy, G, gen++, t.spin_ticks, &sh_ok)) return;
+    q0 = q1;
+    cnt = cnt1;
   }
 }
 
@@ -1154,26 +1193,42 @@ __global__ void __launch_bounds__(NW * 64) k_tail_bwd(GemmArgs g, VecArgs v, Eng
   const bool resident = G % (uint32_t)n_ct == 0 && g.K / NW / Chunk<T>::KC <= RES;
   ResidentB<DX_BWD, RES> rb;
   if (resident) load_resident_b<DT, DX_BWD, NW, RES>(g, (int)(rank % n_ct), rb);
-  uint32_t gen = 0;
-  for (uint32_t lvl = t.lvl_last; lvl >= t.lvl_first; --lvl) {
-    const uint32_t q0 = t.level_off[lvl * LEVEL_KEY_DIES + die];
-    const uint32_t cnt = t.level_off[lvl * LEVEL_KEY_DIES + die + 1] - q0;
-    // (dz of this level's cells: from their parents' tiles, or, for the roots, from k_dz_tail_roots)
+  const uint32_t step = resident ? G / n_ct : G;   // (as in k_tail_fwd)
+  const uint32_t first = resident ? rank / n_ct : rank;
+  auto cells_of = [&](uint32_t lvl, uint32_t& q0, uint32_t& cnt) {
+    q0 = t.level_off[lvl * LEVEL_KEY_DIES + die];
+    cnt = t.level_off[lvl * LEVEL_KEY_DIES + die + 1] - q0;
+  };
+  auto level_args = [&](uint32_t q0, uint32_t cnt) {
     GemmArgs gl = g;
-    DzFuse fz{&v, e.q_l, e.q_r, e.row0, t.q_first};
     gl.M = (int)cnt;
     gl.A = reinterpret_cast<const T*>(g.A) + (size_t)q0 * g.lda;
     gl.l = g.l + q0; gl.r = g.r + q0;
-    const uint32_t n_rt = (cnt + 31) / 32;
-    if (resident) {
-      for (uint32_t rt = rank / n_ct; rt < n_rt; rt += G / n_ct)
-        cell_small_tile<DT, DX_BWD, NW, RES>(gl, (int)rt, (int)(rank % n_ct), part, &rb, &fz);
-    } else {
-      for (uint32_t tile = rank; tile < n_rt * n_ct; tile += G)
-        cell_small_tile<DT, DX_BWD, NW, 0>(gl, (int)(tile / n_ct), (int)(tile % n_ct), part,
-                                           (const ResidentB<DX_BWD, 0>*)nullptr, &fz);
+    return gl;
+  };
+  auto row_tile = [&](uint32_t tile) { return (int)(resident ? tile : tile / n_ct); };
+  auto col_tile = [&](uint32_t tile) { return (int)(resident ? rank % n_ct : tile % n_ct); };
+  auto tiles_of = [&](uint32_t cnt) { return (cnt + 31) / 32 * (resident ? 1u : (uint32_t)n_ct); };
+  const DzFuse fz{&v, e.q_l, e.q_r, e.row0, t.q_first};
+  uint32_t gen = 0, q0, cnt, q1 = 0, cnt1 = 0;
+  TileAhead<DX_BWD, NW> p;
+  cells_of(t.lvl_last, q0, cnt);
+  if (first < tiles_of(cnt)) tile_ahead<DT, DX_BWD, NW>(level_args(q0, cnt), row_tile(first), col_tile(first), &fz, p);
+  for (uint32_t lvl = t.lvl_last; lvl >= t.lvl_first; --lvl) {
+    if (lvl > t.lvl_first) cells_of(lvl - 1, q1, cnt1);
+    // (dz of this level's cells: from their parents' tiles, or, for the roots, from k_dz_tail_roots)
+    const GemmArgs gl = level_args(q0, cnt);
+    for (uint32_t tile = first; tile < tiles_of(cnt); tile += step) {
+      if (tile != first) tile_ahead<DT, DX_BWD, NW>(gl, row_tile(tile), col_tile(tile), &fz, p);
+      if (resident) cell_small_tile<DT, DX_BWD, NW, RES>(gl, row_tile(tile), col_tile(tile), part, p, &rb, &fz);
+      else cell_small_tile<DT, DX_BWD, NW, 0>(gl, row_tile(tile), col_tile(tile), part, p, (const ResidentB<DX_BWD, 0>*)nullptr, &fz);
     }
-    if (!die_barrier(sy, G, gen++, t.spin_ticks, &sh_ok)) return;
+    die_arrive(sy, gen);
+    if (lvl > t.lvl_first && first < tiles_of(cnt1))
+      tile_ahead<DT, DX_BWD, NW>(level_args(q1, cnt1), row_tile(first), col_tile(first), &fz, p);
+    if (!die_wait(sy, G, gen++, t.spin_ticks, &sh_ok)) return;
+    q0 = q1;
+    cnt = cnt1;
   }
 }
 
