@@ -496,12 +496,18 @@ struct DzFuse {
   uint32_t q_first;              // first cell of the tail in the sorted log
 };
 
-// What a tile reads that no tile writes: the children's rows, and for the fused dz the forward state of the child
-// cells.  Three loads that follow one another; the tail kernels request the next level's while they wait at the barrier.
-template <int MODE, int NW> struct TileAhead {
+// What a tile reads that no tile writes, in the two steps that follow one another: the children's rows, and what these
+// lead to: operands that are leaves' rows (RNN_FWD), for the fused dz (CELL: the cell kind, 0: none) the forward state
+// of the child cells.  Most of it comes from HBM.  The tail kernels request the latter a level and the former two levels
+// ahead, behind the loads that the level itself waits for.
+template <int MODE, int NW> struct TileRows {
   static constexpr int RPW = 16 / NW;   // accumulator registers (rows of a lane) a wave finishes
   uint32_t child;                       // operand row of this lane (forward)
   uint32_t o_l[RPW], o_r[RPW];
+};
+template <int MODE, int NW, int RES, int CELL> struct TileAhead {
+  static constexpr int RPW = 16 / NW;
+  u32x4 leaf[RES > 0 && MODE == RNN_FWD ? RES : 1];   // the lane's operands, if its child is a leaf
   uint32_t z_q[RPW], z_gl[RPW], z_gr[RPW];   // fused dz: the child cell (none: all ones) and its children's rows
   float z_gate[RPW][5], z_c[RPW], z_h[RPW], z_own[RPW], z_cl[RPW], z_cr[RPW];
 };
@@ -510,24 +516,43 @@ template <int NW> __device__ __forceinline__ int tile_row_of(int rr) {
   const int r = 16 / NW * (int)(threadIdx.x >> 6) + rr;
   return (r >> 2) * 8 + (int)((threadIdx.x & 63) >> 5) * 4 + (r & 3);
 }
-template <int DT, int MODE, int NW>
-__device__ __forceinline__ void tile_ahead(const GemmArgs& g, int rt, int ct, const DzFuse* fz, TileAhead<MODE, NW>& p) {
-  typedef typename TypeOf<DT>::type T;
-  constexpr int RPW = TileAhead<MODE, NW>::RPW;
+template <int MODE, int NW>
+__device__ __forceinline__ void tile_rows(const GemmArgs& g, int rt, TileRows<MODE, NW>& p) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m0 = rt * 32, mA = min(m0 + (lane & 31), g.M - 1);
   if (MODE != DX_BWD) p.child = wave < NW / 2 ? g.l[mA] : g.r[mA];   // first half of the waves: h_l of [h_l; h_r]
   if (MODE != RNN_FWD) {
 #pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
+    for (int rr = 0; rr < TileRows<MODE, NW>::RPW; ++rr) {
       const int m = min(m0 + tile_row_of<NW>(rr), g.M - 1);
       p.o_l[rr] = g.l[m];
       p.o_r[rr] = g.r[m];
     }
   }
-  if (MODE == DX_BWD && fz != nullptr) {
+}
+// the lane's A operands of a forward tile: chunk step st is st * KC elements further on
+template <int DT, int MODE, int NW>
+__device__ __forceinline__ const typename TypeOf<DT>::type* tile_a_base(const GemmArgs& g, uint32_t child) {
+  typedef typename TypeOf<DT>::type T;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  return reinterpret_cast<const T*>(g.Hs) + (size_t)child * g.Hp + (wave % (NW / 2)) * (g.K / NW) + (lane >> 5) * (16 / (int)sizeof(T));
+}
+template <int DT, int MODE, int NW, int RES, int CELL>
+__device__ __forceinline__ void tile_ahead(const GemmArgs& g, int ct, const DzFuse* fz, const TileRows<MODE, NW>& p,
+                                           TileAhead<MODE, NW, RES, CELL>& q) {
+  typedef typename TypeOf<DT>::type T;
+  constexpr int RPW = 16 / NW;
+  if constexpr (MODE == RNN_FWD && RES > 0) {
+    const int steps = g.K / NW / Chunk<T>::KC;
+    const T* Ap = tile_a_base<DT, MODE, NW>(g, p.child);
+    if (p.child < g.leaf_rows) {
+#pragma unroll
+      for (int st = 0; st < RES; ++st) q.leaf[st] = *reinterpret_cast<const u32x4*>(Ap + min(st, steps - 1) * Chunk<T>::KC);
+    }
+  }
+  if constexpr (CELL != 0) {
     const VecArgs& v = *fz->v;
-    const int unit = ct * 32 + (lane & 31);
+    const int unit = ct * 32 + (int)(threadIdx.x & 31);
     const bool left = unit < g.Hp;
     const int n = left ? unit : unit - g.Hp;
 #pragma unroll
@@ -535,34 +560,35 @@ __device__ __forceinline__ void tile_ahead(const GemmArgs& g, int rt, int ct, co
       const uint32_t row = left ? p.o_l[rr] : p.o_r[rr];
       const bool ok = row >= fz->row0 && row - fz->row0 >= fz->q_first;   // a cell of the tail (a leaf has none)
       const uint32_t qc = ok ? row - fz->row0 : 0u;   // (cell 0 exists whenever a level has cells: a safe address)
-      p.z_q[rr] = ok ? qc : 0xFFFFFFFFu;
-      const size_t o = (size_t)row * v.Hp + n;
-      p.z_own[rr] = v.dHn ? v.dHn[o] : 0.f;   // gradient of the child's own loss term
-      if (v.cell_kind == 1) {
-        p.z_h[rr] = to_f(reinterpret_cast<const T*>(v.Hs)[o]);
+      q.z_q[rr] = ok ? qc : 0xFFFFFFFFu;
+      const size_t o = (size_t)row * g.Hp + n;
+      q.z_own[rr] = v.dHn ? v.dHn[o] : 0.f;   // gradient of the child's own loss term
+      if constexpr (CELL == 1) {
+        q.z_h[rr] = to_f(reinterpret_cast<const T*>(v.Hs)[o]);
       } else {
         const T* g5 = reinterpret_cast<const T*>(v.gates) + (size_t)qc * v.Np + n;
-        p.z_gl[rr] = fz->q_l[qc];
-        p.z_gr[rr] = fz->q_r[qc];
+        q.z_gl[rr] = fz->q_l[qc];
+        q.z_gr[rr] = fz->q_r[qc];
 #pragma unroll
-        for (int k = 0; k < 5; ++k) p.z_gate[rr][k] = to_f(g5[k * v.Hp]);
-        p.z_c[rr] = ok ? v.Cs[o] : 0.f;
+        for (int k = 0; k < 5; ++k) q.z_gate[rr][k] = to_f(g5[k * g.Hp]);
+        q.z_c[rr] = ok ? v.Cs[o] : 0.f;
       }
     }
-    if (v.cell_kind == 2) {
+    if constexpr (CELL == 2) {
 #pragma unroll
       for (int rr = 0; rr < RPW; ++rr) {
-        p.z_cl[rr] = p.z_gl[rr] >= fz->row0 ? v.Cs[(size_t)p.z_gl[rr] * v.Hp + n] : 0.f;   // (a leaf's cell state is zero)
-        p.z_cr[rr] = p.z_gr[rr] >= fz->row0 ? v.Cs[(size_t)p.z_gr[rr] * v.Hp + n] : 0.f;
+        q.z_cl[rr] = q.z_gl[rr] >= fz->row0 ? v.Cs[(size_t)q.z_gl[rr] * g.Hp + n] : 0.f;   // (a leaf's cell state is zero)
+        q.z_cr[rr] = q.z_gr[rr] >= fz->row0 ? v.Cs[(size_t)q.z_gr[rr] * g.Hp + n] : 0.f;
       }
     }
   }
 }
 
-template <int DT, int MODE, int NW, int RES = 0>
-__device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int ct, float* part,
-                                                const TileAhead<MODE, NW>& p, const ResidentB<MODE, RES>* rb = nullptr,
-                                                const DzFuse* fz = nullptr) {
+// `more` is called once the tile's own loads are under way.
+template <int DT, int MODE, int NW, int RES, int CELL, class More>
+__device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int ct, float* part, const TileRows<MODE, NW>& p,
+                                                const TileAhead<MODE, NW, RES, CELL>& q, const ResidentB<MODE, RES>* rb,
+                                                const DzFuse* fz, More more) {
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   constexpr int G = MODE == LSTM_FWD ? 5 : 1;      // 32-wide column blocks per tile
@@ -577,18 +603,18 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
   auto row_of = [&](int rr) { return tile_row_of<NW>(rr); };
   // operand bases (elements)
   const T* Ap;
-  if (MODE == DX_BWD) {
-    Ap = reinterpret_cast<const T*>(g.A) + (size_t)mA * g.lda + wave * kw;
-  } else {
-    Ap = reinterpret_cast<const T*>(g.Hs) + (size_t)p.child * g.Hp + (wave % (NW / 2)) * kw;
-  }
-  Ap += (lane >> 5) * EPC;
+  if constexpr (MODE == DX_BWD) Ap = reinterpret_cast<const T*>(g.A) + (size_t)mA * g.lda + wave * kw + (lane >> 5) * EPC;
+  else Ap = tile_a_base<DT, MODE, NW>(g, p.child);
   const T* Bp[G];
 #pragma unroll
   for (int j = 0; j < G; ++j) Bp[j] = tile_b_base<DT, MODE, NW>(g, ct, j);
-  // children's cell states for the epilogue, requested before the products start
-  float cl[RPW], cr[RPW];
+  // children's cell states and the bias for the epilogue, requested before the products start
+  float cl[RPW], cr[RPW], bias[G];
   const int unit = ct * 32 + (lane & 31);
+  if (MODE != DX_BWD) {
+#pragma unroll
+    for (int j = 0; j < G; ++j) bias[j] = g.bias[j * g.Hp + unit];
+  }
   if (MODE == LSTM_FWD) {
 #pragma unroll
     for (int rr = 0; rr < RPW; ++rr) {
@@ -598,7 +624,6 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
     }
   }
 
-  const bool z_on = MODE == DX_BWD && fz != nullptr;
   const bool z_left = unit < g.Hp;
   const int z_n = z_left ? unit : unit - g.Hp;
   float z_dc[RPW];   // fused dz: dc of the child cells, which their parents' dz (a level ago) has left
@@ -609,15 +634,19 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
   const int steps = kw / C::KC;
-  if (MODE == DX_BWD && z_on && fz->v->cell_kind == 2) {
+  if constexpr (CELL == 2) {
 #pragma unroll
     for (int rr = 0; rr < RPW; ++rr)
-      z_dc[rr] = p.z_q[rr] != 0xFFFFFFFFu ? fz->v->dC[(size_t)(z_left ? p.o_l[rr] : p.o_r[rr]) * g.Hp + z_n] : 0.f;
+      z_dc[rr] = q.z_q[rr] != 0xFFFFFFFFu ? fz->v->dC[(size_t)(z_left ? p.o_l[rr] : p.o_r[rr]) * g.Hp + z_n] : 0.f;
   }
   if constexpr (RES > 0) {
     u32x4 fa[RES];
 #pragma unroll
-    for (int st = 0; st < RES; ++st) fa[st] = *reinterpret_cast<const u32x4*>(Ap + min(st, steps - 1) * C::KC);
+    for (int st = 0; st < RES; ++st) {
+      if (MODE == RNN_FWD && p.child < g.leaf_rows) fa[st] = q.leaf[MODE == RNN_FWD ? st : 0];
+      else fa[st] = *reinterpret_cast<const u32x4*>(Ap + min(st, steps - 1) * C::KC);
+    }
+    more();
 #pragma unroll
     for (int st = 0; st < RES; ++st) {
       if (st < steps) {
@@ -625,7 +654,8 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
         for (int j = 0; j < G; ++j) acc[j] = C::mma(fa[st], rb->f[st][j], acc[j]);
       }
     }
-  } else
+  } else {
+  more();
   for (int s0 = 0; s0 < steps; s0 += BATCH) {
     u32x4 fa[BATCH], fb[BATCH][G];
 #pragma unroll
@@ -642,6 +672,7 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
         for (int j = 0; j < G; ++j) acc[j] = C::mma(fa[b], fb[b][j], acc[j]);
       }
     }
+  }
   }
 
   // partial tiles -> LDS; wave w sums and finishes r = 4w .. 4w+3
@@ -662,9 +693,8 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
     }
 
   if constexpr (MODE == LSTM_FWD) {
-    const float bi = Act<T>::pre_sigmoid(g.bias[unit]), bfl = Act<T>::pre_sigmoid(g.bias[g.Hp + unit]);
-    const float bfr = Act<T>::pre_sigmoid(g.bias[2 * g.Hp + unit]), bo = Act<T>::pre_sigmoid(g.bias[3 * g.Hp + unit]);
-    const float bu = Act<T>::pre_tanh(g.bias[4 * g.Hp + unit]);
+    const float bi = Act<T>::pre_sigmoid(bias[0]), bfl = Act<T>::pre_sigmoid(bias[1]), bfr = Act<T>::pre_sigmoid(bias[2]);
+    const float bo = Act<T>::pre_sigmoid(bias[3]), bu = Act<T>::pre_tanh(bias[4]);
 #pragma unroll
     for (int rr = 0; rr < RPW; ++rr) {
       const int m = m0 + row_of(rr);
@@ -688,45 +718,48 @@ __device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int c
       }
     }
   } else if constexpr (MODE == RNN_FWD) {
-    const float bias = g.bias[unit];
 #pragma unroll
     for (int rr = 0; rr < RPW; ++rr) {
       const int m = m0 + row_of(rr);
       if (m >= g.M) continue;
-      reinterpret_cast<T*>(g.Hs_out)[(size_t)(g.out0 + (uint32_t)m) * g.Hp + unit] = from_f<T>(Act<T>::tanh(z[0][rr] + bias));
+      reinterpret_cast<T*>(g.Hs_out)[(size_t)(g.out0 + (uint32_t)m) * g.Hp + unit] = from_f<T>(Act<T>::tanh(z[0][rr] + bias[0]));
     }
-  } else {   // DX_BWD: column `unit` of [dh_l; dh_r]; each child row has exactly one consumer
+  } else {   // DX_BWD: column `unit` of [dh_l; dh_r]; each child row has exactly one consumer.
+    // (dh of a child whose dz is formed here has no other reader)
 #pragma unroll
     for (int rr = 0; rr < RPW; ++rr) {
       const int m = m0 + row_of(rr);
       if (m >= g.M) continue;
+      if constexpr (CELL != 0) {
+        if (q.z_q[rr] != 0xFFFFFFFFu) continue;
+      }
       if (unit < g.Hp) g.C[(size_t)p.o_l[rr] * g.Hp + unit] = z[0][rr];
       else g.C[(size_t)p.o_r[rr] * g.Hp + (unit - g.Hp)] = z[0][rr];
     }
-    if (z_on) {
+    if constexpr (CELL != 0) {
       const VecArgs& v = *fz->v;
 #pragma unroll
       for (int rr = 0; rr < RPW; ++rr) {
         const int m = m0 + row_of(rr);
-        if (m >= g.M || p.z_q[rr] == 0xFFFFFFFFu) continue;
-        const float dh = z[0][rr] + p.z_own[rr];
+        if (m >= g.M || q.z_q[rr] == 0xFFFFFFFFu) continue;
+        const float dh = z[0][rr] + q.z_own[rr];
         // One lane per child cell: its gradient body fires here.  (In the die's L2: the row is this die's.)
         if (z_n == 0)
           __hip_atomic_fetch_add(&v.gmark[z_left ? p.o_l[rr] : p.o_r[rr]], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        T* dz = reinterpret_cast<T*>(v.Dz) + (size_t)p.z_q[rr] * v.Np + z_n;
-        if (v.cell_kind == 1) {
-          dz[0] = from_f<T>(dh * (1.f - p.z_h[rr] * p.z_h[rr]));
+        T* dz = reinterpret_cast<T*>(v.Dz) + (size_t)q.z_q[rr] * v.Np + z_n;
+        if constexpr (CELL == 1) {
+          dz[0] = from_f<T>(dh * (1.f - q.z_h[rr] * q.z_h[rr]));
         } else {
-          const float gi = p.z_gate[rr][0], gfl = p.z_gate[rr][1], gfr = p.z_gate[rr][2], go = p.z_gate[rr][3], gu = p.z_gate[rr][4];
-          const float tc = Act<T>::tanh(p.z_c[rr]);
+          const float gi = q.z_gate[rr][0], gfl = q.z_gate[rr][1], gfr = q.z_gate[rr][2], go = q.z_gate[rr][3], gu = q.z_gate[rr][4];
+          const float tc = Act<T>::tanh(q.z_c[rr]);
           const float dc = z_dc[rr] + dh * go * (1.f - tc * tc);
           dz[0] = from_f<T>(dc * gu * gi * (1.f - gi));
-          dz[v.Hp] = from_f<T>(dc * p.z_cl[rr] * gfl * (1.f - gfl));
-          dz[2 * v.Hp] = from_f<T>(dc * p.z_cr[rr] * gfr * (1.f - gfr));
+          dz[v.Hp] = from_f<T>(dc * q.z_cl[rr] * gfl * (1.f - gfl));
+          dz[2 * v.Hp] = from_f<T>(dc * q.z_cr[rr] * gfr * (1.f - gfr));
           dz[3 * v.Hp] = from_f<T>(dh * tc * go * (1.f - go));
           dz[4 * v.Hp] = from_f<T>(dc * gi * (1.f - gu * gu));
-          if (p.z_gl[rr] >= fz->row0) v.dC[(size_t)p.z_gl[rr] * v.Hp + z_n] = dc * gfl;   // (a leaf has no use for dc)
-          if (p.z_gr[rr] >= fz->row0) v.dC[(size_t)p.z_gr[rr] * v.Hp + z_n] = dc * gfr;
+          if (q.z_gl[rr] >= fz->row0) v.dC[(size_t)q.z_gl[rr] * v.Hp + z_n] = dc * gfl;   // (a leaf has no use for dc)
+          if (q.z_gr[rr] >= fz->row0) v.dC[(size_t)q.z_gr[rr] * v.Hp + z_n] = dc * gfr;
         }
       }
     }
@@ -740,9 +773,10 @@ __global__ void __launch_bounds__(NW * 64) k_cell_small(GemmArgs g) {
   stamp_now(g.stamp);
   const int n_ct = g.n_tiles_n;                    // column tiles of 32
   const int rt = blockIdx.x / n_ct, ct = blockIdx.x % n_ct;
-  TileAhead<MODE, NW> p;
-  tile_ahead<DT, MODE, NW>(g, rt, ct, nullptr, p);
-  cell_small_tile<DT, MODE, NW>(g, rt, ct, reinterpret_cast<float*>(smem), p);
+  TileRows<MODE, NW> p;
+  TileAhead<MODE, NW, 0, 0> q;
+  tile_rows<MODE, NW>(g, rt, p);
+  cell_small_tile<DT, MODE, NW, 0, 0>(g, rt, ct, reinterpret_cast<float*>(smem), p, q, (const ResidentB<MODE, 0>*)nullptr, nullptr, [] {});
 }
 
 // Levels of at most this many cells take the small-level kernel (TDF_SMALL_LEVEL overrides).
@@ -1114,6 +1148,78 @@ struct TailArgs {
   uint32_t q_first;            // first cell of the tail in the sorted log
 };
 
+// The walk of one workgroup, number `rank` of the G of its die: forward from lvl_first up, DX_BWD from lvl_last down.
+// RES > 0: it keeps to one column tile (the tiles divide evenly among the workgroups) with that tile's weight operands
+// in registers.
+// What bounds it: latency.  A level is the round trip of the barrier (about 1 us), the operands that the level before
+// has written, the products of an eighth or a quarter of the reduction, their sum through LDS, and the store's way to
+// the L2.  The rest is requested ahead (TileRows, TileAhead), by the first tile that a workgroup has in a level; further
+// tiles of the same level request theirs on the spot.
+template <int DT, int MODE, int NW, int RES, int CELL>
+__device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t, uint32_t die, uint32_t rank, uint32_t G, float* part,
+                                            const ResidentB<MODE, RES>* rb, const DzFuse* fz, uint32_t* sh_ok) {
+  typedef typename TypeOf<DT>::type T;
+  DieSync* sy = t.sync + die;
+  const uint32_t n_ct = (uint32_t)g.n_tiles_n;
+  const uint32_t first = RES > 0 ? rank / n_ct : rank, step = RES > 0 ? G / n_ct : G;
+  auto row_tile = [&](uint32_t tile) { return (int)(RES > 0 ? tile : tile / n_ct); };
+  auto col_tile = [&](uint32_t tile) { return (int)(RES > 0 ? rank % n_ct : tile % n_ct); };
+  const uint32_t n_lvl = t.lvl_last + 1 - t.lvl_first;
+  struct Level { uint32_t q0, cnt; };
+  auto level = [&](uint32_t k) {   // the k-th level of the walk; beyond the last one: nothing
+    Level r{0u, 0u};
+    if (k < n_lvl) {
+      const uint32_t* p = t.level_off + (size_t)(MODE == DX_BWD ? t.lvl_last - k : t.lvl_first + k) * LEVEL_KEY_DIES + die;
+      r.q0 = p[0];
+      r.cnt = p[1] - p[0];
+    }
+    return r;
+  };
+  auto args = [&](const Level& l) {
+    GemmArgs gl = g;
+    gl.M = (int)l.cnt;
+    gl.l = g.l + l.q0;
+    gl.r = g.r + l.q0;
+    if constexpr (MODE == DX_BWD) {
+      gl.A = reinterpret_cast<const T*>(g.A) + (size_t)l.q0 * g.lda;
+    } else {
+      gl.out0 = g.out0 + l.q0;
+      gl.gates = g.gates ? reinterpret_cast<T*>(g.gates) + (size_t)l.q0 * g.ldg : nullptr;
+    }
+    return gl;
+  };
+  auto tiles_of = [&](const Level& l) { return (l.cnt + 31) / 32 * (RES > 0 ? 1u : n_ct); };
+  Level l0 = level(0), l1 = level(1), l2 = level(2);
+  TileRows<MODE, NW> p0{}, p1{}, p2{};
+  TileAhead<MODE, NW, RES, CELL> q0{}, q1{};
+  if (first < tiles_of(l0)) {
+    tile_rows<MODE, NW>(args(l0), row_tile(first), p0);
+    tile_ahead<DT, MODE, NW, RES, CELL>(args(l0), col_tile(first), fz, p0, q0);
+  }
+  if (first < tiles_of(l1)) tile_rows<MODE, NW>(args(l1), row_tile(first), p1);
+  for (uint32_t k = 0; k < n_lvl; ++k) {
+    const GemmArgs gl = args(l0);
+    Level l3;
+    auto ahead = [&] {
+      if (first < tiles_of(l1)) tile_ahead<DT, MODE, NW, RES, CELL>(args(l1), col_tile(first), fz, p1, q1);
+      if (first < tiles_of(l2)) tile_rows<MODE, NW>(args(l2), row_tile(first), p2);
+      l3 = level(k + 3);
+    };
+    if (first < tiles_of(l0)) cell_small_tile<DT, MODE, NW, RES, CELL>(gl, row_tile(first), col_tile(first), part, p0, q0, rb, fz, ahead);
+    else ahead();
+    for (uint32_t tile = first + step; tile < tiles_of(l0); tile += step) {
+      tile_rows<MODE, NW>(gl, row_tile(tile), p0);
+      tile_ahead<DT, MODE, NW, RES, CELL>(gl, col_tile(tile), fz, p0, q0);
+      cell_small_tile<DT, MODE, NW, RES, CELL>(gl, row_tile(tile), col_tile(tile), part, p0, q0, rb, fz, [] {});
+    }
+    die_arrive(sy, k);
+    if (!die_wait(sy, G, k, t.spin_ticks, sh_ok)) return;
+    l0 = l1; l1 = l2; l2 = l3;
+    p0 = p1; p1 = p2;
+    q0 = q1;
+  }
+}
+
 template <int DT, int MODE, int NW>
 __global__ void __launch_bounds__(NW * 64) k_tail_fwd(GemmArgs g, TailArgs t) {
   typedef typename TypeOf<DT>::type T;
@@ -1129,52 +1235,19 @@ __global__ void __launch_bounds__(NW * 64) k_tail_fwd(GemmArgs g, TailArgs t) {
   DieSync* sy = t.sync + die;
   if (threadIdx.x == 0) atomicOr(&sy->xcc_mask, 1u << xcc_id());
   const int n_ct = g.n_tiles_n;
-  // A workgroup keeps to one column tile where the tiles divide evenly among the workgroups,
-  // and then holds that tile's weight operands in registers for the whole launch.
   constexpr int RES = 8;
-  const bool resident = G % (uint32_t)n_ct == 0 && g.K / NW / Chunk<T>::KC <= RES;
-  ResidentB<MODE, RES> rb;
-  if (resident) load_resident_b<DT, MODE, NW, RES>(g, (int)(rank % n_ct), rb);
-  const uint32_t step = resident ? G / n_ct : G;   // this workgroup's tiles: every step-th row tile of its column, or every step-th tile
-  const uint32_t first = resident ? rank / n_ct : rank;
-  auto cells_of = [&](uint32_t lvl, uint32_t& q0, uint32_t& cnt) {
-    q0 = t.level_off[lvl * LEVEL_KEY_DIES + die];
-    cnt = t.level_off[lvl * LEVEL_KEY_DIES + die + 1] - q0;
-  };
-  auto level_args = [&](uint32_t q0, uint32_t cnt) {
-    GemmArgs gl = g;
-    gl.M = (int)cnt;
-    gl.out0 = g.out0 + q0; gl.l = g.l + q0; gl.r = g.r + q0;
-    gl.gates = g.gates ? reinterpret_cast<T*>(g.gates) + (size_t)q0 * g.ldg : nullptr;
-    return gl;
-  };
-  auto row_tile = [&](uint32_t tile) { return (int)(resident ? tile : tile / n_ct); };
-  auto col_tile = [&](uint32_t tile) { return (int)(resident ? rank % n_ct : tile % n_ct); };
-  auto tiles_of = [&](uint32_t cnt) { return (cnt + 31) / 32 * (resident ? 1u : (uint32_t)n_ct); };
-  uint32_t gen = 0, q0, cnt, q1 = 0, cnt1 = 0;
-  TileAhead<MODE, NW> p;
-  cells_of(t.lvl_first, q0, cnt);
-  if (first < tiles_of(cnt)) tile_ahead<DT, MODE, NW>(level_args(q0, cnt), row_tile(first), col_tile(first), nullptr, p);
-  for (uint32_t lvl = t.lvl_first; lvl <= t.lvl_last; ++lvl) {
-    if (lvl < t.lvl_last) cells_of(lvl + 1, q1, cnt1);
-    const GemmArgs gl = level_args(q0, cnt);
-    for (uint32_t tile = first; tile < tiles_of(cnt); tile += step) {
-      if (tile != first) tile_ahead<DT, MODE, NW>(gl, row_tile(tile), col_tile(tile), nullptr, p);
-      if (resident) cell_small_tile<DT, MODE, NW, RES>(gl, row_tile(tile), col_tile(tile), part, p, &rb);
-      else cell_small_tile<DT, MODE, NW>(gl, row_tile(tile), col_tile(tile), part, p);
-    }
-    die_arrive(sy, gen);
-    if (lvl < t.lvl_last && first < tiles_of(cnt1))
-      tile_ahead<DT, MODE, NW>(level_args(q1, cnt1), row_tile(first), col_tile(first), nullptr, p);
-    if (!die_wait(sy, G, gen++, t.spin_ticks, &sh_ok)) return;
-    q0 = q1;
-    cnt = cnt1;
+  if (G % (uint32_t)n_ct == 0 && g.K / NW / Chunk<T>::KC <= RES) {
+    ResidentB<MODE, RES> rb;
+    load_resident_b<DT, MODE, NW, RES>(g, (int)(rank % n_ct), rb);
+    walk_levels<DT, MODE, NW, RES, 0>(g, t, die, rank, G, part, &rb, nullptr, &sh_ok);
+  } else {
+    walk_levels<DT, MODE, NW, 0, 0>(g, t, die, rank, G, part, (const ResidentB<MODE, 0>*)nullptr, nullptr, &sh_ok);
   }
 }
 
 // Gradient pass over the same levels, deepest first: dz of the die's cells of a level, barrier,
 // their input gradients, barrier.
-template <int DT, int NW>
+template <int DT, int CELL, int NW>
 __global__ void __launch_bounds__(NW * 64) k_tail_bwd(GemmArgs g, VecArgs v, Engine e, TailArgs t) {
   typedef typename TypeOf<DT>::type T;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1190,45 +1263,14 @@ __global__ void __launch_bounds__(NW * 64) k_tail_bwd(GemmArgs g, VecArgs v, Eng
   if (threadIdx.x == 0) atomicOr(&sy->xcc_mask, 1u << xcc_id());
   const int n_ct = g.n_tiles_n;
   constexpr int RES = 10;
-  const bool resident = G % (uint32_t)n_ct == 0 && g.K / NW / Chunk<T>::KC <= RES;
-  ResidentB<DX_BWD, RES> rb;
-  if (resident) load_resident_b<DT, DX_BWD, NW, RES>(g, (int)(rank % n_ct), rb);
-  const uint32_t step = resident ? G / n_ct : G;   // (as in k_tail_fwd)
-  const uint32_t first = resident ? rank / n_ct : rank;
-  auto cells_of = [&](uint32_t lvl, uint32_t& q0, uint32_t& cnt) {
-    q0 = t.level_off[lvl * LEVEL_KEY_DIES + die];
-    cnt = t.level_off[lvl * LEVEL_KEY_DIES + die + 1] - q0;
-  };
-  auto level_args = [&](uint32_t q0, uint32_t cnt) {
-    GemmArgs gl = g;
-    gl.M = (int)cnt;
-    gl.A = reinterpret_cast<const T*>(g.A) + (size_t)q0 * g.lda;
-    gl.l = g.l + q0; gl.r = g.r + q0;
-    return gl;
-  };
-  auto row_tile = [&](uint32_t tile) { return (int)(resident ? tile : tile / n_ct); };
-  auto col_tile = [&](uint32_t tile) { return (int)(resident ? rank % n_ct : tile % n_ct); };
-  auto tiles_of = [&](uint32_t cnt) { return (cnt + 31) / 32 * (resident ? 1u : (uint32_t)n_ct); };
+  // (dz of a level's cells: from their parents' tiles, or, for the roots, from k_dz_tail_roots)
   const DzFuse fz{&v, e.q_l, e.q_r, e.row0, t.q_first};
-  uint32_t gen = 0, q0, cnt, q1 = 0, cnt1 = 0;
-  TileAhead<DX_BWD, NW> p;
-  cells_of(t.lvl_last, q0, cnt);
-  if (first < tiles_of(cnt)) tile_ahead<DT, DX_BWD, NW>(level_args(q0, cnt), row_tile(first), col_tile(first), &fz, p);
-  for (uint32_t lvl = t.lvl_last; lvl >= t.lvl_first; --lvl) {
-    if (lvl > t.lvl_first) cells_of(lvl - 1, q1, cnt1);
-    // (dz of this level's cells: from their parents' tiles, or, for the roots, from k_dz_tail_roots)
-    const GemmArgs gl = level_args(q0, cnt);
-    for (uint32_t tile = first; tile < tiles_of(cnt); tile += step) {
-      if (tile != first) tile_ahead<DT, DX_BWD, NW>(gl, row_tile(tile), col_tile(tile), &fz, p);
-      if (resident) cell_small_tile<DT, DX_BWD, NW, RES>(gl, row_tile(tile), col_tile(tile), part, p, &rb, &fz);
-      else cell_small_tile<DT, DX_BWD, NW, 0>(gl, row_tile(tile), col_tile(tile), part, p, (const ResidentB<DX_BWD, 0>*)nullptr, &fz);
-    }
-    die_arrive(sy, gen);
-    if (lvl > t.lvl_first && first < tiles_of(cnt1))
-      tile_ahead<DT, DX_BWD, NW>(level_args(q1, cnt1), row_tile(first), col_tile(first), &fz, p);
-    if (!die_wait(sy, G, gen++, t.spin_ticks, &sh_ok)) return;
-    q0 = q1;
-    cnt = cnt1;
+  if (G % (uint32_t)n_ct == 0 && g.K / NW / Chunk<T>::KC <= RES) {
+    ResidentB<DX_BWD, RES> rb;
+    load_resident_b<DT, DX_BWD, NW, RES>(g, (int)(rank % n_ct), rb);
+    walk_levels<DT, DX_BWD, NW, RES, CELL>(g, t, die, rank, G, part, &rb, &fz, &sh_ok);
+  } else {
+    walk_levels<DT, DX_BWD, NW, 0, CELL>(g, t, die, rank, G, part, (const ResidentB<DX_BWD, 0>*)nullptr, &fz, &sh_ok);
   }
 }
 
@@ -1804,12 +1846,15 @@ template <typename T> static void tail_bwd_t(const VecArgs& v, const Engine& e, 
   g.C = v.dH;
   g.n_tiles_n = v.Kp / 32;
   const int grid = std::max(per_die, 1) * (int)XCDS;
+  const bool lstm = v.cell_kind == 2;
   if (small_tile_waves<T, DX_BWD>(g.K) == 8) {
     const size_t lds = (size_t)8 * 16 * 64 * sizeof(float);
-    hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 8>), dim3(grid), dim3(512), lds, s, g, v, e, t);
+    if (lstm) hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 2, 8>), dim3(grid), dim3(512), lds, s, g, v, e, t);
+    else hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 1, 8>), dim3(grid), dim3(512), lds, s, g, v, e, t);
   } else {
     const size_t lds = (size_t)4 * 16 * 64 * sizeof(float);
-    hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 4>), dim3(grid), dim3(256), lds, s, g, v, e, t);
+    if (lstm) hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 2, 4>), dim3(grid), dim3(256), lds, s, g, v, e, t);
+    else hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 1, 4>), dim3(grid), dim3(256), lds, s, g, v, e, t);
   }
 }
 // After the level sort: rows numbered by the sorted schedule, references translated.
