@@ -53,8 +53,8 @@ __device__ inline bool die_wait(DieSync* sy, uint32_t G, uint32_t gen, long long
   if (threadIdx.x == 0) {
     bool ok = true;
     uint32_t nothing = 0;
-    asm volatile("" : "+v"(nothing));   // (an atomic that adds nothing, not a load, which the L1 could answer)
-    const long long t0 = wall_clock64();
+    asm volatile("" : "+s"(nothing));   // (an atomic that adds nothing, not a load, which the L1 could answer)
+    long long t0 = 0;
     for (uint32_t k = 1;; ++k) {
       if (gen == 0) {
         if (__hip_atomic_load(&sy->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= G) {
@@ -70,7 +70,9 @@ __device__ inline bool die_wait(DieSync* sy, uint32_t G, uint32_t gen, long long
         }
       }
       __builtin_amdgcn_s_sleep(1);
-      if (k % 16u == 0 && wall_clock64() - t0 > spin_ticks) {
+      if (k % 64u != 0) continue;   // (the clock is read rarely: that takes as long as a look)
+      if (t0 == 0) t0 = wall_clock64();
+      if (wall_clock64() - t0 > spin_ticks) {
         __hip_atomic_store(&sy->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_fetch_or(&sy->local, DIE_GAVE_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         ok = false;
