@@ -297,17 +297,6 @@ struct alignas(128) LaneCtl {   // zero on entry
   uint32_t leaf_next;           // rows given to leaves (after the run)
   uint32_t rows_done;           // workgroups through with the first pass over the log
 };
-// The run's totals, and how its cells are sorted.
-struct alignas(128) LaneTotals {
-  uint32_t status;              // of the lanes
-  uint32_t bad;                 // nothing may be built on this run: a status, or more tags or cells than there are rows for
-  uint32_t n_log, n_leaf, n_cell;
-  uint32_t max_depth, max_level, max_iter;
-  uint32_t n_keys;              // sort keys; 0: no cells
-  uint32_t deep_level, deep_base;   // instances whose root's level is deep_level or more are sorted apart (0: one class)
-  uint32_t published;           // the level offsets are in the host's copy
-  unsigned long long n_tags, n_tokens, frames;
-};
 struct LaneLimits {
   uint32_t max_tags, max_cells;   // 0: no limit
   uint32_t deep_level;            // 0: one class

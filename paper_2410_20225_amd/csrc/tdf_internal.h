@@ -6,7 +6,6 @@
 #include <string>
 #include <vector>
 
-#include "engine.h"
 #include "tdf.h"
 #include "tdf_tables.h"
 
