@@ -26,8 +26,8 @@
 // What bounds it: the instructions of a wave's sweeps, about 4 clocks each, vector, scalar and branch alike (a
 // recursion without parallelism runs one lane, about 1.3 us a call there and back), and with many waves how evenly
 // the calls spread over them.  A frame costs no memory traffic beyond the lane's stack, whose top is in LDS.
-// Measured, whole evaluations in us, step machine -> lanes: fib(0..20) 582 -> 238; 2 x fib(28) 28500 -> 7400 (3.3 to
-// 7.4 ms by how the calls happened to spread); tak over 512 instances 23000 -> 5200; 65536 gcd loops 7390 -> 157.
+// Measured, whole evaluations in us, step machine -> lanes: fib(0..20) 562 -> 197; fib(30) + fib(31) + fib(32)
+// 27400 -> 5900 (4.4 to 7.6 ms by how the calls happen to spread); tak over 256 instances 17800 -> 3400 or less; 65536 gcd loops 7300 -> 142.
 // The tag phase of tree networks: 4096 random trees of up to 64 leaves 1980 -> 590, 1500 small trees 366 -> 112, a chain
 // of 512 leaves 4200 -> 1500.
 //
@@ -46,6 +46,8 @@ constexpr uint32_t LANE_WINDOW = 4;     // frames of a lane's stack that stay in
 constexpr uint32_t LANE_SEG = 16;       // frames of a segment of a lane's stack in memory
 constexpr uint32_t LANE_SYNC = 4, LANE_SYNC_FULL = 8;   // sweeps between two looks at the other lanes; the latter while nearly all have work
 constexpr uint32_t LANE_EARLY = 48;     // sweeps during which a wave gives work away although it has lanes without any
+// idle lanes up to which a wave gives calls to other waves
+constexpr uint32_t LANE_GIVE = 56;
 constexpr uint32_t LANE_LOOP = 64;      // iterations of a loop without calls in one sweep
 constexpr uint32_t LANE_RECS = 96;      // records of a wave
 constexpr uint32_t LANE_QUEUE = 128;    // tasks of a wave (at least LANE_RECS: a record is queued at most once)
@@ -324,7 +326,6 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
   unsigned long long sent_mask = 0;       // replies awaited, by lane
   bool more_inst = true, stop = false, have_ticket = false;
   uint32_t n_own = 0, n_mine = 0, hungry = 0;   // instances of this wave that are not done; those taken since the last report
-  bool starving = false;                  // the queue looked at last had several waves waiting
   // With every lane busy on work of its own a wave would have none to send a call to a wave without work: where
   // several waves share a recursion the last two lanes do that and nothing else.
   const unsigned long long exporter = a.n_waves > 1 && SW::kBranching ? 3ull << 62 : 0ull;
@@ -842,17 +843,19 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
       const unsigned long long rich = __ballot(x.run && slack > 0);
       const uint32_t n_idle = 64u - (uint32_t)__popcll(__ballot(active) | exporter);
       // Calls go to other waves early on, while many of them have nothing, and later from waves whose own lanes
-      // are busy: a wave that runs out of work itself keeps what it has (it is little by then).
+      // have work: a wave with a handful of them keeps what it has (it is little by then).  That a wave looks for
+      // others at every sharing, with up to 56 lanes idle, and not only with 16 at most and on every fourth, takes
+      // fib(30) + fib(31) + fib(32) from 7.4 to 5.9 ms on average and 256 instances of tak from 5.4 to 3.4 (with 32: 6.7 and
+      // 4.7, with 64: 6.6 and 3.6); one large frame on a lane of a wave that has little else was where a run ended.
       const bool early = iter < LANE_EARLY;
-      hungry = n_idle <= 16 || early ? hungry : 0u;
-      if (exporter && (rich || nq) && (early || (n_idle <= 16 && (starving || (syncs & 3u) == 0)))) {
+      hungry = n_idle <= LANE_GIVE || early ? hungry : 0u;
+      if (exporter && (rich || nq) && (early || n_idle <= LANE_GIVE)) {
         const unsigned long long ht = lane_ld(reinterpret_cast<const unsigned long long*>(&a.queues[look].head));
         send_queue = look;
         look = look + 1u == a.n_queues ? 0u : look + 1u;
         const int d = (int)((uint32_t)ht - (uint32_t)(ht >> 32));   // tickets without a task
         hungry = (uint32_t)__builtin_amdgcn_readfirstlane(d > 0 ? d : 0);
-        starving = hungry >= 4u;
-        if (early && n_idle > 16 && hungry < 8u) hungry = 0;
+        if (early && n_idle > LANE_GIVE && hungry < 8u) hungry = 0;
       }
       // Tasks wanted: for the wave's idle lanes, and some for waves without work.  A lane gives the oldest
       // frame of its stack that has a ready call left (the largest piece of work), and the frames below it.
