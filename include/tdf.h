@@ -241,7 +241,7 @@ typedef struct {
 
 #define TDF_STATS_MAX_COUNTS 256
 
-/* Phases of one evaluation, timed on the caller's stream with HIP events. */
+/* Phases of one evaluation, timed by the clock that the first kernel of each phase reads. */
 enum {
   TDF_PHASE_TAGS = 0,    /* tag machine: clear, seed, all match/fire steps                 */
   TDF_PHASE_LEAVES,      /* weight packing and EMBED rows (gradient runs write the rows on
