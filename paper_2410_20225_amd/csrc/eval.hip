@@ -587,15 +587,15 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       HIP_TRY(hipGetLastError());
       if (tdf_status ws = wait_report(&rep->seq, gr->seq, s); ws != TDF_OK) return ws;
       lt = rep->t;
-      rows_known = lt.status == 0;
+      rows_known = !lt.bad;
     } else {
       if (tdf_status fs = finish(true, nullptr, nullptr); fs != TDF_OK) return fs;
       HIP_TRY(hipGetLastError());
       if (tdf_status ws = wait_report(&fin->seq, gr->seq, s); ws != TDF_OK) return ws;
       lt = fin->t;
-      ended = lt.status == 0;
+      ended = !lt.bad;
     }
-    if (lt.status != 0) {   // left to the step machine, which also says what is wrong if something is
+    if (lt.bad) {   // left to the step machine, which also says what is wrong if something is
       if (status_is(lt.status, TDF_ERR_UNSUPPORTED)) gr->lanes_ok = false;
       use_lanes = false;
       ++repeats;
@@ -609,8 +609,6 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       hc.max_level = lt.max_level;
       hc.n_alloc = (uint32_t)std::min<unsigned long long>(hc.n_tags, lt.frames);
       hc.done = 1;
-      // (programs with vector operators: max_tags bounds all tags, and there is a row for each)
-      if (!e.reclaim && hc.n_tags > (unsigned long long)e.max_tags) hc.status = (uint32_t)(-TDF_ERR_TABLE_FULL);
     }
   }
   bool w_packed = use_lanes && P.vec;

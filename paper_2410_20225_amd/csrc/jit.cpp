@@ -328,9 +328,12 @@ struct Gen {
   // be inlined.
   void body(std::ostringstream& c, const State& S, const std::string& q, const std::string& on, const std::vector<Val>* ins,
             std::vector<Val>& V, B& complete, bool* can) {
+    body(c, S, q, on, ins, facts(S.f, S.mask), V, complete, can);
+  }
+  void body(std::ostringstream& c, const State& S, const std::string& q, const std::string& on, const std::vector<Val>* ins, const Facts& F,
+            std::vector<Val>& V, B& complete, bool* can) {
     const int f = S.f;
     const DevFn& fn = P.fn[f];
-    const Facts F = facts(f, S.mask);
     V.assign(MAX_VALUES + 2, Val{"0ll", bc(false), bc(false)});
     std::vector<int> alias(MAX_VALUES + 2, -1);   // the value it hands on
     std::map<int, bool> node_loaded;
@@ -448,7 +451,7 @@ struct Gen {
             *can = false;
             break;
           }
-          if (ins) {   // an inlined callee has no stored values: its EMBED fires here and only here
+          if (ins) {   // an inlined callee has no stored values: its EMBED fires here and only here (see can_inline)
             c << "        ln_embed_now(x, " << on << " && " << in.e << ", " << a.v << ", " << q << "v" << D << ", " << q << "pp" << D << ");\n";
             V[I.dst] = Val{q + "v" + D, in.k == 1 ? bc(true) : in, bc(false)};
             break;
@@ -488,13 +491,31 @@ struct Gen {
       if (at(f, ip).op == D_OUT) k = ip;
     return at(f, k);
   }
+  // Whether the first sweep of a callee is all there is to it: everything is there, nothing is left to call.
+  B whole_callee(int f, const std::vector<Val>& W, const B& complete) const {
+    B partly = bc(false);
+    for (const Site& u : sites(f))
+      for (const Instr* I : u.args) partly = bor(partly, live_of(source(W, *I, 0)));
+    return band(band(complete, bnot(partly)), live_of(source(W, out_entry(f), 0)));
+  }
   // A callee whose first sweep may be all there is (a base case) is tried in the caller's sweep: no frame
-  // is pushed for it then.  Not where the body has operators with a stored value other than EMBED.
-  bool can_inline(int f) const {
+  // is pushed for it then.  Not where the body has operators with a stored value other than EMBED, and not where an
+  // EMBED can fire although the callee turns out to need a frame, in which it would fire again.
+  bool can_inline(int f) {
     if (f == P.result_fn) return false;
     for (int ip = 0; ip < P.fn[f].count; ++ip) {
-      const uint8_t op = at(f, ip).op;
-      if (op == D_HEAD || op == D_NEXT) return false;
+      const Instr& I = at(f, ip);
+      if (I.op == D_HEAD || I.op == D_NEXT) return false;
+      if (I.op != D_EMBED) continue;
+      Facts F = facts(f, 0);
+      mark_live(f, F, I.dst);
+      const std::vector<Val> ins(P.fn[f].n_params, Val{"0ll", bc(true), bc(false)});
+      std::vector<Val> W;
+      B complete = bc(false);
+      bool can = true;
+      std::ostringstream sink;
+      body(sink, State{f, 0, 0}, "", "on", &ins, F, W, complete, &can);
+      if (whole_callee(f, W, complete).k != 1) return false;
     }
     return true;
   }
@@ -573,15 +594,13 @@ struct Gen {
         const std::string q = "c" + tag + "_", con = "(on && " + all.e + ")";
         std::vector<Val> ins((size_t)np, Val{"0ll", bc(true), bc(false)}), W;
         for (const Instr* I : t.args) ins[I->aux2] = Val{src(*I, 0).v, bc(true), bc(false)};
-        B whole = bc(false), partly = bc(false);
+        B complete0 = bc(false);
         std::ostringstream ic;
         bool can = true;
         node_at = {"", ""};
-        body(ic, State{callee, 0, 0}, q, con, &ins, W, whole, &can);
+        body(ic, State{callee, 0, 0}, q, con, &ins, W, complete0, &can);
         const Val ov = source(W, out_entry(callee), 0);
-        for (const Site& u : sites(callee))
-          for (const Instr* I : u.args) partly = bor(partly, live_of(source(W, *I, 0)));
-        const B done = band(band(whole, bnot(partly)), live_of(ov));
+        const B done = whole_callee(callee, W, complete0);
         if (can && done.k != 0) {
           c << ic.str();
           r.done = named(c, "done" + tag, band(bx("(" + all.e + ")"), done)).e;

@@ -311,7 +311,9 @@ __device__ __forceinline__ void lane_totals(const LaneArgs& a, const LaneLimits&
   t.n_tags = q.n_tags;
   t.n_tokens = q.n_tokens;
   t.frames = frames;
-  t.bad = t.status != 0 || (lim.max_tags && q.n_tags > lim.max_tags) || (lim.max_cells && q.n_cell > lim.max_cells);
+  // (a state row per leaf and per cell, as many as max_tags; the sort writes by these counts)
+  t.bad = t.status != 0 || (lim.max_tags && (q.n_tags > lim.max_tags || (unsigned long long)q.n_leaf + q.n_cell > lim.max_tags)) ||
+          (lim.max_cells && q.n_cell > lim.max_cells);
   if (lim.deep_level && t.max_level >= lim.deep_level && t.n_cell) {
     t.deep_level = lim.deep_level;
     t.deep_base = lim.deep_level * LEVEL_KEY_DIES;

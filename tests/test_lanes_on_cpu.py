@@ -1,0 +1,44 @@
+"""The depth-first lanes run on the CPU (tests/lane_cpu.py) against the oracle and plain Python references: the code that
+is generated for a program, and the machine's hand-overs between lanes and waves in random orders of events."""
+import pytest
+
+import oracle
+from oracle import programs as oprog
+from lane_cpu import Lanes, needs_host_lanes
+from lane_programs import VECTOR
+
+pytestmark = needs_host_lanes
+tdf = pytest.importorskip("paper_2410_20225_amd.tdf")
+from paper_2410_20225_amd import programs  # noqa: E402
+
+INT = {
+    "fib": (programs.fib, oprog.fib_program, [(n,) for n in [16, 3, 0, 11, 14, 1, 9]]),
+    "tak": (programs.tak, oprog.tak_program, [(7, 4, 2), (12, 8, 4), (1, 2, 3), (9, 5, 1)]),
+    "gcd": (programs.gcd_loop, oprog.gcd_loop_program, [(a, b) for a in range(1, 20) for b in range(1, 8)]),
+    "loop_of_calls": (programs.loop_of_calls, oprog.loop_of_calls_program, [(n,) for n in (0, 1, 3, 9, 12)]),
+}
+
+
+@pytest.mark.parametrize("name", list(INT))
+def test_integer_programs_against_the_oracle(name, tmp_path):
+    prog, oracle_prog, args = INT[name]
+    it = oracle.Interpreter(oracle.transform(oracle_prog()))
+    want = it.run({("in", k): [a[k] for a in args] for k in range(len(args[0]))}, len(args))[("out", 0)]
+    lanes = Lanes(prog(), tmp_path)
+    for waves, queues, seed in [(1, 1, 1), (3, 1, 2), (16, 1, 3), (40, 2, 4)]:
+        got = lanes.run(args, waves=waves, queues=queues, seed=seed)
+        assert got["status"] == 0 and got["out"] == want
+        assert got["tags"] == len(it.tags) + len(it.iter_tags) and got["depth"] == it.max_tag_len
+
+
+@pytest.mark.parametrize("name", list(VECTOR))
+def test_vector_results(name, tmp_path):
+    prog, forest, args, ref = VECTOR[name]()
+    lanes = Lanes(prog, tmp_path)
+    for waves in (1, 4):
+        got = lanes.run(args, waves=waves, log_cap=4096, vocab=50, **forest.arrays())
+        log = [got["log"][k:k + 4] for k in range(0, len(got["log"]), 4)]
+        leaves = [e for e in log if e[2] == 0]
+        assert got["status"] == 0 and [log[r][0] for r in got["root"]] == [ref(*a) for a in args]
+        # one leaf under every tag (of f)
+        assert got["leaves"] == len(leaves) == got["tags"]
