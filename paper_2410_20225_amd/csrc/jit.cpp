@@ -322,7 +322,11 @@ struct Gen {
       if (t.label >= 0 && !((mask >> P.label_site[t.label]) & 1) && t.args.size() == 1 && t.args[0]->src[0] == v) return P.label_ret_slot[t.label];
     return -1;
   }
-  std::pair<std::string, std::string> node_at;   // the node an inlined body looked at: index, suffix of its names
+  struct NodeAt {   // the node an inlined body looked at: index, suffix of its names, whether its entries were read
+    std::string index, names;
+    B loaded;
+  };
+  NodeAt node_at;
   // The entries of a state's code.  `q`: prefix of the names, `on`: which lanes, `ins`: the parameters of an
   // inlined callee (null: the lane's own frame).  Fills V and `complete`; clears *can where a callee cannot
   // be inlined.
@@ -336,7 +340,7 @@ struct Gen {
     const DevFn& fn = P.fn[f];
     V.assign(MAX_VALUES + 2, Val{"0ll", bc(false), bc(false)});
     std::vector<int> alias(MAX_VALUES + 2, -1);   // the value it hands on
-    std::map<int, bool> node_loaded;
+    std::map<int, B> node_loaded;   // by node: under which condition its entries have been read
     auto root = [&](int v) { while (v < SRC_NONE && alias[v] >= 0) v = alias[v]; return v; };
     auto src = [&](const Instr& I, int k) { return source(V, I, k); };
     auto name_b = [&](const std::string& nm, const B& b) { return named(c, q + nm, b); };
@@ -421,12 +425,16 @@ struct Gen {
           const int r = I.src[0] < SRC_NONE ? root(I.src[0]) : -1;
           const std::string R = q + std::to_string(r < 0 ? 255 : r);
           if (S.mask == 0) {   // first sweep: the node's entries in one round trip, index checked
-            if (!node_loaded[r]) {
-              node_loaded[r] = true;
-              c << "        int " << "nl" << R << " = x.pf_l, nr" << R << " = x.pf_r, nt" << R << " = x.pf_t;\n";
-              c << "        if (" << on << " && " << lv.e << (ins ? "" : " && x.pf_v != " + a.v) << ") ln_node(x, " << a.v << ", nl" << R << ", nr" << R << ", nt" << R
+            // (once for all accessors of the node, but each under its own condition: the first may be dead)
+            const bool first = !node_loaded.count(r);
+            B& loaded = node_loaded.emplace(r, bc(false)).first->second;
+            if (first) c << "        int " << "nl" << R << " = x.pf_l, nr" << R << " = x.pf_r, nt" << R << " = x.pf_t;\n";
+            const B load = loaded.k == 2 && loaded.e == lv.e ? bc(false) : band(lv, bnot(loaded));
+            if (load.k) {
+              c << "        if (" << on << " && " << load.e << (ins ? "" : " && x.pf_v != " + a.v) << ") ln_node(x, " << a.v << ", nl" << R << ", nr" << R << ", nt" << R
                 << ");\n";
-              if (ins) node_at = {a.v, R};
+              loaded = named(c, q + "n" + D, bor(loaded, lv));
+              if (ins) node_at = NodeAt{a.v, R, loaded};
             }
             const char* which = I.op == D_RIGHT ? "nr" : I.op == D_TOKEN ? "nt" : "nl";
             put(I.dst, std::string("(long long)") + (I.op == D_ISLEAF ? "(nl" + R + " < 0)" : which + R), a.p, a.d);
@@ -597,7 +605,7 @@ struct Gen {
         B complete0 = bc(false);
         std::ostringstream ic;
         bool can = true;
-        node_at = {"", ""};
+        node_at = NodeAt{"", "", bc(false)};
         body(ic, State{callee, 0, 0}, q, con, &ins, W, complete0, &can);
         const Val ov = source(W, out_entry(callee), 0);
         const B done = whole_callee(callee, W, complete0);
@@ -605,8 +613,9 @@ struct Gen {
           c << ic.str();
           r.done = named(c, "done" + tag, band(bx("(" + all.e + ")"), done)).e;
           r.value = ov.v;
-          if (!node_at.second.empty())
-            r.node = " x.pf_v = " + node_at.first + "; x.pf_l = nl" + node_at.second + "; x.pf_r = nr" + node_at.second + "; x.pf_t = nt" + node_at.second + ";";
+          if (node_at.loaded.k)
+            r.node = (node_at.loaded.k == 1 ? "" : " if (" + node_at.loaded.e + ") {") + std::string(" x.pf_v = ") + node_at.index + "; x.pf_l = nl" + node_at.names +
+                     "; x.pf_r = nr" + node_at.names + "; x.pf_t = nt" + node_at.names + ";" + (node_at.loaded.k == 1 ? "" : " }");
         }
       }
       rs.push_back(r);

@@ -44,5 +44,36 @@ def embed_under_every_tag():
     return ([_result(1, 1).desc(), f.desc()], 0), F, [(v,) for v in range(19)], ref
 
 
+def one_of_two_entries():
+    """result(v, c) = if c < 1 then left(v) else right(v)"""
+    r = _Fn("result", 2)
+    v, c = r.add(T.OP_IN, imm=0), r.add(T.OP_IN, imm=1)
+    s = r.add(T.OP_SWITCH, [r.add(T.OP_LT, [c, r.add(T.OP_CONST, imm=1)]), v])
+    r.add(T.OP_OUT, [r.add(T.OP_MERGE, [r.add(T.OP_TREE_LEFT, [(s[0], 0)]), r.add(T.OP_TREE_RIGHT, [(s[0], 1)])])])
+    F = _chain(9)
+    return ([r.desc()], 0), F, [(v, c) for v in range(19) for c in (0, 1)], lambda v, c: F.right[v] if c else F.left[v]
+
+
+def entries_under_an_argument():
+    """f(v, c) = if c < 1 then k(c) + k(c) + k(c) + f(v, c + 1) else token(v), k(c) = c + 1: f(v, 0) is tried in place
+    and does not look at its node, whose entries must not count as read in f(v, 1) (the fourth call is not tried)."""
+    f = _Fn("f", 2)
+    v, c = f.add(T.OP_IN, imm=0), f.add(T.OP_IN, imm=1)
+    p = f.add(T.OP_LT, [c, f.add(T.OP_CONST, imm=1)])
+    sv, sc = f.add(T.OP_SWITCH, [p, v]), f.add(T.OP_SWITCH, [p, c])
+    one = f.add(T.OP_CONST, imm=1)
+    k1, k2, k3 = (f.add(T.OP_CALLFN, [(sc[0], 0)], imm=2) for _ in range(3))
+    y = f.add(T.OP_CALLFN, [(sv[0], 0), f.add(T.OP_ADD, [(sc[0], 0), one])], imm=1)
+    for k in (k1, k2, k3):
+        y = f.add(T.OP_ADD, [y, k])
+    f.add(T.OP_OUT, [f.add(T.OP_MERGE, [y, f.add(T.OP_TREE_TOKEN, [(sv[0], 1)])])])
+    k = _Fn("k", 1)
+    k.add(T.OP_OUT, [k.add(T.OP_ADD, [k.add(T.OP_IN), k.add(T.OP_CONST, imm=1)])])
+    F = _chain(9)
+    return ([_result(2, 1).desc(), f.desc(), k.desc()], 0), F, [(v, c) for v in range(19) for c in range(2)], \
+        lambda v, c: F.token[v] + (0 if c else 3)
+
+
 # name -> program, forest, arguments, reference; the vector results are rows of E
 VECTOR = {"embed_under_every_tag": embed_under_every_tag}
+INTEGER = {p.__name__: p for p in (one_of_two_entries, entries_under_an_argument)}

@@ -5,7 +5,7 @@ import pytest
 import oracle
 from oracle import programs as oprog
 from lane_cpu import Lanes, needs_host_lanes
-from lane_programs import VECTOR
+from lane_programs import INTEGER, VECTOR
 
 pytestmark = needs_host_lanes
 tdf = pytest.importorskip("paper_2410_20225_amd.tdf")
@@ -42,3 +42,12 @@ def test_vector_results(name, tmp_path):
         assert got["status"] == 0 and [log[r][0] for r in got["root"]] == [ref(*a) for a in args]
         # one leaf under every tag (of f)
         assert got["leaves"] == len(leaves) == got["tags"]
+
+
+@pytest.mark.parametrize("name", list(INTEGER))
+def test_integer_results(name, tmp_path):
+    prog, forest, args, ref = INTEGER[name]()
+    lanes = Lanes(prog, tmp_path)
+    for waves in (1, 4):
+        got = lanes.run(args, waves=waves, **forest.arrays())
+        assert got["status"] == 0 and got["out"] == [ref(*a) for a in args]
