@@ -422,8 +422,8 @@ struct Gen {
         case D_ISLEAF: case D_LEFT: case D_RIGHT: case D_TOKEN: {
           const Val a = src(I, 0);
           const B lv = live_of(a);
-          const int r = I.src[0] < SRC_NONE ? root(I.src[0]) : -1;
-          const std::string R = q + std::to_string(r < 0 ? 255 : r);
+          const int r = I.src[0] < SRC_NONE ? root(I.src[0]) : 256 + ip;   // (an immediate: a node of its own)
+          const std::string R = q + std::to_string(r);
           if (S.mask == 0) {   // first sweep: the node's entries in one round trip, index checked
             // (once for all accessors of the node, but each under its own condition: the first may be dead)
             const bool first = !node_loaded.count(r);

@@ -74,6 +74,16 @@ def entries_under_an_argument():
         lambda v, c: F.token[v] + (0 if c else 3)
 
 
+def constant_nodes():
+    """result(n) = token(6) - token(3) + n"""
+    r = _Fn("result", 1)
+    n = r.add(T.OP_IN)
+    b, a = (r.add(T.OP_TREE_TOKEN, [r.add(T.OP_CONST, imm=k)]) for k in (6, 3))
+    r.add(T.OP_OUT, [r.add(T.OP_ADD, [r.add(T.OP_SUB, [b, a]), n])])
+    F = _chain(9)
+    return ([r.desc()], 0), F, [(n,) for n in range(3)], lambda n: F.token[6] - F.token[3] + n
+
+
 # name -> program, forest, arguments, reference; the vector results are rows of E
 VECTOR = {"embed_under_every_tag": embed_under_every_tag}
-INTEGER = {p.__name__: p for p in (one_of_two_entries, entries_under_an_argument)}
+INTEGER = {p.__name__: p for p in (one_of_two_entries, entries_under_an_argument, constant_nodes)}
