@@ -315,11 +315,24 @@ struct Gen {
   static B live_of(const Val& a) { return a.p.k == 2 && a.p.e == a.d.e ? bc(false) : band(a.p, bnot(a.d)); }
 
   // A call that waits while another one runs: an argument that came from the forest is kept where its result
-  // will be, so that it need not be read again.  The slot for value `v` in a state, or -1.
-  int memo_slot(int f, uint32_t mask, int v) const {
+  // will be, so that it need not be read again.  That is sound for arguments that the first sweep decides (there, live or
+  // dead, whatever the calls return): a call with such an argument that is live is ready in the first sweep, which ends
+  // with it or with another call, and whoever calls keeps the arguments of the others.
+  bool kept(int f, int v) {
+    if (v >= SRC_NONE) return false;
+    std::vector<Val> V;
+    B complete = bc(false);
+    std::ostringstream sink;
+    body(sink, State{f, 0, 0}, "", "on", nullptr, V, complete, nullptr);
+    const uint8_t op = at(f, facts(f, 0).def[v]).op;
+    return (op == D_LEFT || op == D_RIGHT || op == D_TOKEN) && V[v].p.k == 1;
+  }
+  // The slot that holds value `v` in a state, or -1.
+  int memo_slot(int f, uint32_t mask, int v) {
     if (mask == 0) return -1;
     for (const Site& t : sites(f))
-      if (t.label >= 0 && !((mask >> P.label_site[t.label]) & 1) && t.args.size() == 1 && t.args[0]->src[0] == v) return P.label_ret_slot[t.label];
+      if (t.label >= 0 && !((mask >> P.label_site[t.label]) & 1) && t.args.size() == 1 && t.args[0]->src[0] == v)
+        return kept(f, v) ? (int)P.label_ret_slot[t.label] : -1;
     return -1;
   }
   struct NodeAt {   // the node an inlined body looked at: index, suffix of its names, whether its entries were read
@@ -662,11 +675,8 @@ struct Gen {
       const std::string go = r.done.empty() ? r.all.e : "(" + r.all.e + " && !" + r.done + ")";
       std::string keep;   // arguments of calls that wait, kept in the place of their results
       for (const Ready& u : rs)
-        if (&u != &r && u.t->args.size() == 1 && memo_slot(f, S.mask | r.bit, u.t->args[0]->src[0]) == u.slot) {
-          const uint8_t op = u.t->args[0]->src[0] < SRC_NONE ? at(f, facts(f, 0).def[u.t->args[0]->src[0]]).op : (uint8_t)D_IN;
-          if (op == D_LEFT || op == D_RIGHT || op == D_TOKEN)
-            keep += (u.done.empty() ? "" : " if (!" + u.done + ")") + std::string(" x.sv[") + std::to_string(u.slot) + "] = " + src(*u.t->args[0], 0).v + ";";
-        }
+        if (&u != &r && u.t->args.size() == 1 && kept(f, u.t->args[0]->src[0]))
+          keep += (u.done.empty() ? "" : " if (!" + u.done + ")") + std::string(" x.sv[") + std::to_string(u.slot) + "] = " + src(*u.t->args[0], 0).v + ";";
       chain += std::string(n_chain++ ? "          else " : "          ") + "if (" + go + ") { x.act = ACT_CALL; x.c_st = " + state_name(r.callee, 0, 0) + "; x.c_back = " +
                state_after(r.bit) + " | " + std::to_string((unsigned)r.slot << 20) + "u; x.c_label = " + std::to_string(r.t->label) + "u;" + r.args + r.node + keep + " }\n";
       taken = bor(taken, r.done.empty() ? r.all : bx(go));

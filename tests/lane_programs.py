@@ -82,8 +82,71 @@ def constant_nodes():
     r.add(T.OP_OUT, [r.add(T.OP_ADD, [r.add(T.OP_SUB, [b, a]), n])])
     F = _chain(9)
     return ([r.desc()], 0), F, [(n,) for n in range(3)], lambda n: F.token[6] - F.token[3] + n
+def _framed(name, index, add):
+    """name(x) = x + add for x below 1000, in a call of its own, so that it is not done in the caller's sweep."""
+    q = _Fn(name, 1)
+    x, k = q.add(T.OP_IN), q.add(T.OP_CONST, imm=1000)
+    s = q.add(T.OP_SWITCH, [q.add(T.OP_LT, [x, k]), x])
+    again = q.add(T.OP_CALLFN, [q.add(T.OP_ADD, [(s[0], 0), q.add(T.OP_CONST, imm=1000 + add)])], imm=index)
+    q.add(T.OP_OUT, [q.add(T.OP_MERGE, [again, q.add(T.OP_SUB, [(s[0], 1), k])])])
+    return q
+
+
+def entry_of_a_calls_result():
+    """f(n) = h(left(g(n))) + token(g(n)): the argument of h is not there when g is called."""
+    f = _Fn("f", 1)
+    g = f.add(T.OP_CALLFN, [f.add(T.OP_IN)], imm=2)
+    h = f.add(T.OP_CALLFN, [f.add(T.OP_TREE_LEFT, [g])], imm=3)
+    f.add(T.OP_OUT, [f.add(T.OP_ADD, [h, f.add(T.OP_TREE_TOKEN, [g])])])
+    F = _chain(9)
+    return ([_result(1, 1).desc(), f.desc(), _framed("g", 2, 1).desc(), _framed("h", 3, 50).desc()], 0), F, \
+        [(n,) for n in range(18)], lambda n: F.left[n + 1] + 50 + F.token[n + 1]
+
+
+def entry_behind_a_switch_on_a_call():
+    """f(n) = let s = g(n) < 5 in (if s then h(right(n)) else h(n)) + k(token(n)): the argument of h waits for g."""
+    f = _Fn("f", 1)
+    n = f.add(T.OP_IN)
+    p = f.add(T.OP_LT, [f.add(T.OP_CALLFN, [n], imm=2), f.add(T.OP_CONST, imm=5)])
+    s = f.add(T.OP_SWITCH, [p, n])
+    a = f.add(T.OP_CALLFN, [f.add(T.OP_TREE_RIGHT, [(s[0], 0)])], imm=3)
+    b = f.add(T.OP_CALLFN, [(s[0], 1)], imm=3)
+    k = f.add(T.OP_CALLFN, [f.add(T.OP_TREE_TOKEN, [n])], imm=2)
+    f.add(T.OP_OUT, [f.add(T.OP_ADD, [f.add(T.OP_MERGE, [a, b]), k])])
+    F = _chain(9)
+    return ([_result(1, 1).desc(), f.desc(), _framed("g", 2, 1).desc(), _framed("h", 3, 50).desc()], 0), F, \
+        [(n,) for n in range(19)], lambda n: (F.right[n] if n + 1 < 5 else n) + 50 + F.token[n] + 1
+
+
+def entry_of_what_may_be_a_call():
+    """f(v, c) = h(left(if c < 1 then v else g(v))): the argument of h is there at once, or waits for g."""
+    f = _Fn("f", 2)
+    v, c = f.add(T.OP_IN, imm=0), f.add(T.OP_IN, imm=1)
+    s = f.add(T.OP_SWITCH, [f.add(T.OP_LT, [c, f.add(T.OP_CONST, imm=1)]), v])
+    w = f.add(T.OP_MERGE, [(s[0], 0), f.add(T.OP_CALLFN, [(s[0], 1)], imm=2)])
+    f.add(T.OP_OUT, [f.add(T.OP_CALLFN, [f.add(T.OP_TREE_LEFT, [w])], imm=3)])
+    F = _chain(9)
+    return ([_result(2, 1).desc(), f.desc(), _framed("g", 2, 1).desc(), _framed("h", 3, 50).desc()], 0), F, \
+        [(v, c) for v in range(18) for c in (0, 1)], lambda v, c: F.left[v + c] + 50
+
+
+def waiting_calls_with_entries_as_arguments():
+    """f(n) = g(n) + g(left(n)) + h(left(n)) + h(isleaf(n)) + h(right(n)): calls that wait, two of them with the same
+    argument, one with an entry that is a truth value; g(x) is done in place for x >= 1000 only."""
+    f = _Fn("f", 1)
+    n = f.add(T.OP_IN)
+    left = f.add(T.OP_TREE_LEFT, [n])
+    y = f.add(T.OP_CALLFN, [n], imm=2)
+    for callee, arg in ((2, left), (3, left), (3, f.add(T.OP_TREE_ISLEAF, [n])), (3, f.add(T.OP_TREE_RIGHT, [n]))):
+        y = f.add(T.OP_ADD, [y, f.add(T.OP_CALLFN, [arg], imm=callee)])
+    f.add(T.OP_OUT, [y])
+    F = _chain(9)
+    return ([_result(1, 1).desc(), f.desc(), _framed("g", 2, 1).desc(), _framed("h", 3, 50).desc()], 0), F, \
+        [(n,) for n in range(19)], lambda n: n + 1 + F.left[n] + 1 + F.left[n] + 50 + (F.left[n] < 0) + 50 + F.right[n] + 50
 
 
 # name -> program, forest, arguments, reference; the vector results are rows of E
 VECTOR = {"embed_under_every_tag": embed_under_every_tag}
-INTEGER = {p.__name__: p for p in (one_of_two_entries, entries_under_an_argument, constant_nodes)}
+INTEGER = {p.__name__: p for p in (one_of_two_entries, entries_under_an_argument, constant_nodes, entry_of_a_calls_result,
+                                   entry_behind_a_switch_on_a_call, entry_of_what_may_be_a_call,
+                                   waiting_calls_with_entries_as_arguments)}
