@@ -822,12 +822,12 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
         resume(last, id);   // (taken at once, most likely by this lane)
       }
     }
+    raise_status();   // (before the instances that it concerns count as done)
+    if (stop) break;
     if (any_done && n_own == 0) {
       instances_done();
       if (stop) break;
     }
-    raise_status();
-    if (stop) break;
     if ((syncs & 15u) == 0) {
       if (lane_ld(&ctl->status) != 0) break;
       if (wall_clock64() - t_start > a.run_ticks) {

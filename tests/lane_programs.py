@@ -145,8 +145,17 @@ def waiting_calls_with_entries_as_arguments():
         [(n,) for n in range(19)], lambda n: n + 1 + F.left[n] + 1 + F.left[n] + 50 + (F.left[n] < 0) + 50 + F.right[n] + 50
 
 
+def bad_index_in_result():
+    """result(n) = token(n): the instance that names no node is also the last to end."""
+    r = _Fn("result", 1)
+    r.add(T.OP_OUT, [r.add(T.OP_TREE_TOKEN, [r.add(T.OP_IN)])])
+    return ([r.desc()], 0), _chain(9), [-1000, -2, 19, 500]
+
+
 # name -> program, forest, arguments, reference; the vector results are rows of E
 VECTOR = {"embed_under_every_tag": embed_under_every_tag}
 INTEGER = {p.__name__: p for p in (one_of_two_entries, entries_under_an_argument, constant_nodes, entry_of_a_calls_result,
                                    entry_behind_a_switch_on_a_call, entry_of_what_may_be_a_call,
                                    waiting_calls_with_entries_as_arguments)}
+# name -> program, forest, arguments that name a node that does not exist
+BAD_INDEX = {p.__name__: p for p in (bad_index_in_result,)}

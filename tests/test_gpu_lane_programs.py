@@ -6,7 +6,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2410_20225_amd import tdf  # noqa: E402
-from lane_programs import INTEGER, VECTOR  # noqa: E402
+from lane_programs import BAD_INDEX, INTEGER, VECTOR  # noqa: E402
 from gpu_util import DEV  # noqa: E402
 
 
@@ -59,3 +59,15 @@ def test_integer_results(name, monkeypatch):
     def check():
         assert out.cpu().tolist() == want
     _both_ways(prog, inp, dict(out_i64=out), monkeypatch, check)
+
+
+@pytest.mark.parametrize("name", list(BAD_INDEX))
+def test_nodes_that_do_not_exist_are_refused(name):
+    # (every accessor checks its index before it reads: tests/test_lanes_on_cpu.py)
+    prog, forest, bad = BAD_INDEX[name]()
+    g = tdf.graph_build(*prog)
+    for v in bad:
+        keep, inp = _inputs(forest, [(v,)])
+        ws = torch.empty(tdf.workspace_size(g, inp), dtype=torch.uint8, device=DEV)
+        st, _ = tdf.eval(g, inp, ws, out_i64=torch.zeros(1, dtype=torch.int64, device=DEV), check=False)
+        assert st == tdf.ERR_BAD_ARG, v

@@ -5,7 +5,7 @@ import pytest
 import oracle
 from oracle import programs as oprog
 from lane_cpu import Lanes, needs_host_lanes
-from lane_programs import INTEGER, VECTOR
+from lane_programs import BAD_INDEX, INTEGER, VECTOR
 
 pytestmark = needs_host_lanes
 tdf = pytest.importorskip("paper_2410_20225_amd.tdf")
@@ -51,3 +51,12 @@ def test_integer_results(name, tmp_path):
     for waves in (1, 4):
         got = lanes.run(args, waves=waves, **forest.arrays())
         assert got["status"] == 0 and got["out"] == [ref(*a) for a in args]
+
+
+@pytest.mark.parametrize("name", list(BAD_INDEX))
+def test_nodes_that_do_not_exist_are_refused(name, tmp_path):
+    # (the forest's arrays lie between inaccessible pages, so a read out of range would end the driver)
+    prog, forest, bad = BAD_INDEX[name]()
+    lanes = Lanes(prog, tmp_path)
+    for v in bad:
+        assert lanes.run([(v,)], **forest.arrays())["status"] == -tdf.ERR_BAD_ARG, v
