@@ -320,12 +320,16 @@ struct Gen {
   // with it or with another call, and whoever calls keeps the arguments of the others.
   bool kept(int f, int v) {
     if (v >= SRC_NONE) return false;
+    const uint8_t op = at(f, facts(f, 0).def[v]).op;
+    return (op == D_LEFT || op == D_RIGHT || op == D_TOKEN) && decided(f, v);
+  }
+  // Whether the first sweep decides a value: it is there then, live or dead.
+  bool decided(int f, int v) {
     std::vector<Val> V;
     B complete = bc(false);
     std::ostringstream sink;
     body(sink, State{f, 0, 0}, "", "on", nullptr, V, complete, nullptr);
-    const uint8_t op = at(f, facts(f, 0).def[v]).op;
-    return (op == D_LEFT || op == D_RIGHT || op == D_TOKEN) && V[v].p.k == 1;
+    return V[v].p.k == 1;
   }
   // The slot that holds value `v` in a state, or -1.
   int memo_slot(int f, uint32_t mask, int v) {
@@ -452,9 +456,13 @@ struct Gen {
             const char* which = I.op == D_RIGHT ? "nr" : I.op == D_TOKEN ? "nt" : "nl";
             put(I.dst, std::string("(long long)") + (I.op == D_ISLEAF ? "(nl" + R + " < 0)" : which + R), a.p, a.d);
           } else {
-            const char* arr = I.op == D_RIGHT ? "right" : I.op == D_TOKEN ? "token" : "left";
+            // The node may be a value that a call has just returned, which nobody has looked at yet.  Where the first
+            // sweep has, a bad index is known and this sweep's values do not count; only the read itself is checked,
+            // so that the compiler can leave it out where nobody needs it.
             const int memo = memo_slot(f, S.mask, I.dst);
-            std::string e = memo >= 0 ? "x.sv[" + std::to_string(memo) + "]" : lv.k == 0 ? "0ll" : "(" + on + " && " + lv.e + " ? x.a->" + arr + "[" + a.v + "] : 0)";
+            std::string e = memo >= 0 ? "x.sv[" + std::to_string(memo) + "]" : lv.k == 0 ? "0ll" :
+                            "(" + on + " && " + lv.e + " ? " + (decided(f, I.dst) ? "ln_entry_again" : "ln_entry") + "(x, " + a.v + ", " +
+                            std::to_string(std::max<int>(I.op, D_LEFT) - D_ISLEAF) + ") : 0ll)";
             if (I.op == D_ISLEAF) e = F.truth[I.dst] >= 0 ? std::to_string(F.truth[I.dst]) + "ll" : "(" + e + " < 0)";
             put(I.dst, "(long long)" + e, a.p, a.d);
           }

@@ -144,6 +144,17 @@ __device__ __forceinline__ long long ln_tree(LaneX& x, long long v, int which, b
   const int32_t e = which == 2 ? a.right[v] : which == 3 ? a.token[v] : a.left[v];
   return which == 0 ? (long long)(e < 0) : (long long)e;
 }
+// the entry itself; 0 if there is no such node
+__device__ __forceinline__ long long ln_entry(LaneX& x, long long v, int which) {
+  bool dead = false;
+  return ln_tree(x, v, which, dead);
+}
+// the same for a node that an earlier sweep has found bad if it is
+__device__ __forceinline__ long long ln_entry_again(const LaneX& x, long long v, int which) {
+  const LaneArgs& a = *x.a;
+  if (v < 0 || v >= a.n_tree_nodes || a.left == nullptr) return 0;
+  return which == 2 ? a.right[v] : which == 3 ? a.token[v] : a.left[v];
+}
 // a node's entries in one round trip; false: no such node
 __device__ __forceinline__ bool ln_node(LaneX& x, long long v, int& l, int& r, int& t) {
   const LaneArgs& a = *x.a;

@@ -152,10 +152,22 @@ def bad_index_in_result():
     return ([r.desc()], 0), _chain(9), [-1000, -2, 19, 500]
 
 
+def bad_index_from_a_call():
+    """entry_of_a_calls_result with nodes that do not exist, which the sweep after the call of g meets first."""
+    prog, F, _, _ = entry_of_a_calls_result()
+    return prog, F, [18, 19, 500, 998]
+
+
+def bad_index_through_calls():
+    """waiting_calls_with_entries_as_arguments with nodes that do not exist: every sweep reads their entries."""
+    prog, F, _, _ = waiting_calls_with_entries_as_arguments()
+    return prog, F, [-1000, -2, 19, 500]
+
+
 # name -> program, forest, arguments, reference; the vector results are rows of E
 VECTOR = {"embed_under_every_tag": embed_under_every_tag}
 INTEGER = {p.__name__: p for p in (one_of_two_entries, entries_under_an_argument, constant_nodes, entry_of_a_calls_result,
                                    entry_behind_a_switch_on_a_call, entry_of_what_may_be_a_call,
                                    waiting_calls_with_entries_as_arguments)}
 # name -> program, forest, arguments that name a node that does not exist
-BAD_INDEX = {p.__name__: p for p in (bad_index_in_result,)}
+BAD_INDEX = {p.__name__: p for p in (bad_index_in_result, bad_index_from_a_call, bad_index_through_calls)}
