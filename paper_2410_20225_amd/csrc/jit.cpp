@@ -448,7 +448,7 @@ struct Gen {
             if (first) c << "        int " << "nl" << R << " = x.pf_l, nr" << R << " = x.pf_r, nt" << R << " = x.pf_t;\n";
             const B load = loaded.k == 2 && loaded.e == lv.e ? bc(false) : band(lv, bnot(loaded));
             if (load.k) {
-              c << "        if (" << on << " && " << load.e << (ins ? "" : " && x.pf_v != " + a.v) << ") ln_node(x, " << a.v << ", nl" << R << ", nr" << R << ", nt" << R
+              c << "        if (" << on << " && " << load.e << (ins ? "" : " && (x.pf_v != " + a.v + " || " + a.v + " < 0)") << ") ln_node(x, " << a.v << ", nl" << R << ", nr" << R << ", nt" << R
                 << ");\n";
               loaded = named(c, q + "n" + D, bor(loaded, lv));
               if (ins) node_at = NodeAt{a.v, R, loaded};

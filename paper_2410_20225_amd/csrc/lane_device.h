@@ -127,7 +127,8 @@ struct LaneX {
   // counts
   uint32_t n_tags, n_tokens, n_leaf, n_cell, mx_depth, mx_level;
   int bad;                  // a condition the host has to deal with
-  // the tree node looked at last (the callee's, when a call was tried in place and then made): index and entries
+  // the tree node looked at last (the callee's, when a call was tried in place and then made): index and entries;
+  // negative: none (no node has such an index: it is never taken for one)
   long long pf_v;
   int pf_l, pf_r, pf_t;
 };

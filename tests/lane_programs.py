@@ -149,7 +149,7 @@ def bad_index_in_result():
     """result(n) = token(n): the instance that names no node is also the last to end."""
     r = _Fn("result", 1)
     r.add(T.OP_OUT, [r.add(T.OP_TREE_TOKEN, [r.add(T.OP_IN)])])
-    return ([r.desc()], 0), _chain(9), [-1000, -2, 19, 500]
+    return ([r.desc()], 0), _chain(9), [-1, -1000, -2, 19, 500]
 
 
 def bad_index_from_a_call():
