@@ -493,7 +493,10 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     resume(last, id);
   };
 
-  // A call from another wave becomes a record and a task (there is a free record).
+  // A call from another wave becomes a record and a task.  There is a free record: a wave takes a ticket only if it has
+  // one, and keeps one back while it holds the ticket.  (Otherwise all records could wait for values from other waves, which
+  // wait for the call that lies in this wave's slot.)
+  auto spare_recs = [&]() { return nfree - (have_ticket ? 1u : 0u); };
   auto take_mail = [&](LaneMail* slot) {
     have_ticket = false;
     uint32_t id = 0;
@@ -523,7 +526,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     // ---- idle lanes take a task of the wave, an empty wave takes instances, or a ticket of the global queue
     if (sent_mask) poll_replies();
     // (a wave that found work again while it holds a ticket: what is sent to it joins its tasks)
-    if (have_ticket && nfree) {
+    if (have_ticket) {
       LaneMail* const slot = mail_slot(my_queue, ticket);
       const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
       if (v == LANE_PILL) break;
@@ -572,7 +575,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
             continue;
           }
           // nothing left in this wave: wait for a task, for a value, or to be sent home
-          if (!have_ticket) {
+          if (!have_ticket && nfree) {
             uint32_t t = 0;
             if (lane == 0) t = lane_add(&a.queues[my_queue].head, 1u);
             ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
@@ -582,7 +585,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           const long long t0 = wall_clock64();
           uint32_t v = LANE_EMPTY;
           for (;;) {
-            v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
+            if (have_ticket) v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
             if (v != LANE_EMPTY) break;
             if (sent_mask) {
               poll_replies();
@@ -873,7 +876,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
       // frame of its stack that has a ready call left (the largest piece of work), and the frames below it.
       const uint32_t want = n_idle + min(hungry, 16u);
       bool going = x.run && slack > 0 && want > nq && (uint32_t)__popcll(rich & lanemask_lt()) < want - nq;
-      if (nfree >= 8 && __ballot(going)) {
+      if (spare_recs() >= 8 && __ballot(going)) {
         uint32_t below = parent, d = bs;   // the caller of frame d
         bool moved = false;
         for (;;) {
@@ -883,9 +886,10 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           const bool fresh = going && !(d == bs && rec != LANE_NONE);
           const unsigned long long rm = __ballot(fresh);
           const uint32_t rr = (uint32_t)__popcll(rm & lanemask_lt());
-          const bool ok = going && (!fresh || rr < nfree);
+          const uint32_t n_spare = spare_recs();
+          const bool ok = going && (!fresh || rr < n_spare);
           const uint32_t id = !fresh ? rec : ok ? lfree[nfree - 1 - rr] : 0u;
-          nfree -= min(nfree, (uint32_t)__popcll(rm));
+          nfree -= min(n_spare, (uint32_t)__popcll(rm));
           min_free = min(min_free, nfree);
           bool more = false;
           if (ok) {

@@ -1,6 +1,6 @@
 """Programs over a forest whose generated lanes are easy to get wrong, each with a small forest, arguments and a plain
 Python function that says what an instance gives: the value, or for vector results the token whose row it is."""
-from paper_2410_20225_amd import tdf as T
+from paper_2410_20225_amd import programs, tdf as T
 from paper_2410_20225_amd.programs import _Fn
 
 
@@ -162,6 +162,27 @@ def bad_index_through_calls():
     """waiting_calls_with_entries_as_arguments with nodes that do not exist: every sweep reads their entries."""
     prog, F, _, _ = waiting_calls_with_entries_as_arguments()
     return prog, F, [-1000, -2, 19, 500]
+
+
+def fib_below_a_chain():
+    """f(n, m) = if n < 1 then fib(m - 6) + fib(m) else 1 + f(n - 1, m): a program and its reference."""
+    f = _Fn("f", 2)
+    n, m, one = f.add(T.OP_IN, imm=0), f.add(T.OP_IN, imm=1), f.add(T.OP_CONST, imm=1)
+    p = f.add(T.OP_LT, [n, one])
+    sn, sm = f.add(T.OP_SWITCH, [p, n]), f.add(T.OP_SWITCH, [p, m])
+    a = f.add(T.OP_CALLFN, [f.add(T.OP_SUB, [(sm[0], 0), f.add(T.OP_CONST, imm=6)])], imm=2)
+    b = f.add(T.OP_CALLFN, [(sm[0], 0)], imm=2)
+    c = f.add(T.OP_ADD, [one, f.add(T.OP_CALLFN, [f.add(T.OP_SUB, [(sn[0], 1), one]), (sm[0], 1)], imm=1)])
+    f.add(T.OP_OUT, [f.add(T.OP_MERGE, [f.add(T.OP_ADD, [a, b]), c])])
+    (_, (name, n_params, nodes)), _ = programs.fib()
+    fib = (name, n_params, [(op, ins, 2 if op == T.OP_CALLFN else imm) for op, ins, imm in nodes])
+
+    def ref(n, m):
+        F = [0, 1]
+        while len(F) <= m:
+            F.append(F[-1] + F[-2])
+        return n + (m - 6 if m < 6 else F[m - 6]) + F[m]
+    return ([_result(2, 1).desc(), f.desc(), fib], 0), ref
 
 
 # name -> program, forest, arguments, reference; the vector results are rows of E

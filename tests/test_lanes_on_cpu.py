@@ -5,7 +5,7 @@ import pytest
 import oracle
 from oracle import programs as oprog
 from lane_cpu import Lanes, needs_host_lanes
-from lane_programs import BAD_INDEX, INTEGER, VECTOR
+from lane_programs import BAD_INDEX, INTEGER, VECTOR, fib_below_a_chain
 
 pytestmark = needs_host_lanes
 tdf = pytest.importorskip("paper_2410_20225_amd.tdf")
@@ -60,3 +60,20 @@ def test_nodes_that_do_not_exist_are_refused(name, tmp_path):
     lanes = Lanes(prog, tmp_path)
     for v in bad:
         assert lanes.run([(v,)], **forest.arrays())["status"] == -tdf.ERR_BAD_ARG, v
+
+
+@pytest.fixture(scope="module")
+def fib_under_chain(tmp_path_factory):
+    prog, ref = fib_below_a_chain()
+    return Lanes(prog, tmp_path_factory.mktemp("lanes")), ref
+
+
+def test_a_wave_whose_records_all_wait_takes_no_call(fib_under_chain):
+    # six chains of 16 frames take the 96 records of a wave; the calls at their ends are in other waves when a call for
+    # this wave comes
+    lanes, ref = fib_under_chain
+    args = [(14, 14)] * 6 + [(0, 1)] * 42
+    for seed in range(1, 25):
+        got = lanes.run(args, waves=8, seed=seed)
+        assert got["status"] == 0 and got["out"] == [ref(*a) for a in args], seed
+        assert got["records"] <= 8 * 96
