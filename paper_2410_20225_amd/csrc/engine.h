@@ -318,7 +318,7 @@ struct LaneArgs {
   LaneCtl* ctl;
   uint4* segs;                  // segments of the lanes' stacks (lane_seg_units each)
   LaneQueue* queues;            // [n_queues], zero on entry
-  struct LaneMail* mail;        // [n_queues][queue_cap] calls sent to other waves, every flag LANE_EMPTY on entry
+  struct LaneMail* mail;        // [n_queues][queue_cap] calls sent to other waves, every flag empty in round 0 on entry (queue_cap: a power of two, 4 or more)
   struct LaneReply* reply;      // per wave 64 places for the values of calls it sent, flags 0 on entry
   uint4* log;                   // schedule log: leaf {token, -, 0, instance}, cell {left, right, level, instance}; .z = LANE_LOG_HOLE: unused
   uint32_t* row_of;             // by name (= place in the log): state row

@@ -41,7 +41,12 @@ namespace tdf {
 
 constexpr uint32_t LANE_NONE = 0xFFFFFFFFu;
 constexpr uint32_t LANE_REMOTE = 0x80000000u;   // a caller in another wave: LANE_REMOTE | wave << 6 | reply
-constexpr uint32_t LANE_EMPTY = 0xFFFFFFFFu, LANE_PILL = 1u, LANE_TASK = 2u, LANE_LEFT = 3u;   // global queue: state of a slot
+// Global queue: state of a slot, and the round of tickets that it is in (a ticket's number without its place in the
+// queue).  A slot is written only in the round of the ticket that it is written for, so a call that nobody has taken
+// yet stays as it is, however many tickets have been dealt out since.
+constexpr uint32_t LANE_EMPTY = 0u, LANE_PILL = 1u, LANE_TASK = 2u, LANE_LEFT = 3u;
+__host__ __device__ constexpr uint32_t lane_slot(uint32_t ticket, uint32_t cap, uint32_t state) { return (ticket & ~(cap - 1u)) | state; }
+__host__ __device__ constexpr bool lane_is_pill(uint32_t flag) { return (flag & 3u) == LANE_PILL; }
 constexpr uint32_t LANE_WINDOW = 4;     // frames of a lane's stack that stay in LDS
 constexpr uint32_t LANE_SEG = 16;       // frames of a segment of a lane's stack in memory
 constexpr uint32_t LANE_SYNC = 4, LANE_SYNC_FULL = 8;   // sweeps between two looks at the other lanes; the latter while nearly all have work
@@ -73,7 +78,7 @@ __host__ __device__ constexpr size_t lane_lds_bytes(int n_stored) {
 
 // A slot of the global queue: one call sent to another wave.
 struct LaneMail {
-  uint32_t flag, pad;
+  uint32_t flag, pad;            // lane_slot
   unsigned long long from;       // caller: LANE_REMOTE | wave << 6 | reply, | state << 32
   unsigned long long meta;       // label | depth << 32
   unsigned long long inst_np;    // instance | number of arguments << 32
@@ -90,7 +95,7 @@ __device__ inline void lane_init(const LaneArgs& a, uint32_t i, uint32_t n) {
     a.ctl->n_seg = a.n_waves * 64u;
   }
   if (i < a.n_queues) a.queues[i] = LaneQueue{};
-  for (uint32_t k = i; k < a.n_queues * a.queue_cap; k += n) a.mail[k].flag = LANE_EMPTY;
+  for (uint32_t k = i; k < a.n_queues * a.queue_cap; k += n) a.mail[k].flag = lane_slot(0u, a.queue_cap, LANE_EMPTY);
   for (uint32_t k = i; k < a.n_waves * 64u; k += n) a.reply[k].flag = 0ull;
   if (a.row_node)
     for (uint32_t k = i; k < a.log_cap; k += n) a.row_node[k] = 0xFFFFFFFFu;
@@ -445,7 +450,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     if (lane < a.n_queues) {
       const uint32_t n = (a.n_waves - lane + a.n_queues - 1) / a.n_queues;   // waves of that queue
       const uint32_t t0 = lane_add(&a.queues[lane].tail, n);
-      for (uint32_t k = 0; k < n; ++k) lane_put(&mail_slot(lane, t0 + k)->flag, LANE_PILL);
+      for (uint32_t k = 0; k < n; ++k) lane_put(&mail_slot(lane, t0 + k)->flag, lane_slot(t0 + k, a.queue_cap, LANE_PILL));
     }
   };
   auto raise_status = [&]() {   // whole wave
@@ -515,7 +520,8 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
       r_po[id] = (1u << (uint32_t)(w2 >> 32)) - 1u;
       r_inst[id] = (uint32_t)w2;
       r_join[id] = 1u;
-      lane_put(&slot->flag, LANE_EMPTY);
+      __builtin_amdgcn_s_waitcnt(0);
+      lane_put(&slot->flag, lane_slot(ticket + a.queue_cap, a.queue_cap, LANE_EMPTY));   // (the next round's)
     }
     --nfree;
     min_free = min(min_free, nfree);
@@ -529,8 +535,8 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     if (have_ticket) {
       LaneMail* const slot = mail_slot(my_queue, ticket);
       const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
-      if (v == LANE_PILL) break;
-      if (v == LANE_TASK) take_mail(slot);
+      if (lane_is_pill(v)) break;
+      if (v == lane_slot(ticket, a.queue_cap, LANE_TASK)) take_mail(slot);
     }
     {
       const unsigned long long idle = ~__ballot(active);
@@ -584,9 +590,14 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           LaneMail* const slot = mail_slot(my_queue, ticket);
           const long long t0 = wall_clock64();
           uint32_t v = LANE_EMPTY;
+          bool task = false, home = false;
           for (;;) {
-            if (have_ticket) v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
-            if (v != LANE_EMPTY) break;
+            if (have_ticket) {
+              v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
+              task = v == lane_slot(ticket, a.queue_cap, LANE_TASK);
+              home = lane_is_pill(v);
+              if (task || home) break;
+            }
             if (sent_mask) {
               poll_replies();
               if (qt != qh) break;
@@ -597,25 +608,23 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
                 if (lane_ld(&ctl->status) != 0 || wall_clock64() - t_start > a.run_ticks) {
                   if (lane == 0) x.bad = TDF_ERR_STEP_LIMIT;
                   raise_status();
-                  v = LANE_PILL;
+                  home = true;
                   break;
                 }
                 continue;
               }
-              uint32_t got = LANE_EMPTY;   // leave; whoever comes to this slot sees that
+              uint32_t left = 0;   // leave; whoever comes to this slot sees that
               if (lane == 0) {
-                uint32_t expect = LANE_EMPTY;
-                if (!__hip_atomic_compare_exchange_strong(&slot->flag, &expect, LANE_LEFT, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT))
-                  got = expect;
+                uint32_t expect = lane_slot(ticket, a.queue_cap, LANE_EMPTY);
+                left = __hip_atomic_compare_exchange_strong(&slot->flag, &expect, lane_slot(ticket, a.queue_cap, LANE_LEFT), __ATOMIC_RELAXED,
+                                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
               }
-              v = (uint32_t)__builtin_amdgcn_readfirstlane((int)got);
-              if (v == LANE_EMPTY) v = LANE_PILL;
-              break;
+              home = __builtin_amdgcn_readfirstlane((int)left) != 0;
+              if (home) break;
             }
           }
-          if (v == LANE_PILL) break;
-          if (v == LANE_TASK) take_mail(slot);
+          if (home) break;
+          if (task) take_mail(slot);
           continue;
         }
       }
@@ -642,10 +651,13 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           for (uint32_t k2 = 0; k2 < n; ++k2) places = k2 < r ? places & (places - 1ull) : places;
           const uint32_t place = (uint32_t)__ffsll((long long)places) - 1u;
           // tickets without a call, reserved: never more calls than tickets, so that no call waits for a wave
+          // (the flags of the slots are requested meanwhile: one that is found empty for its ticket stays so)
           uint32_t t0 = 0, n_got = 0;
+          unsigned long long* const q = reinterpret_cast<unsigned long long*>(&a.queues[send_queue].head);
+          unsigned long long was = lane_ld(q);
+          const uint32_t guess = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(was >> 32));
+          uint32_t f = can && r < n ? lane_ld(&mail_slot(send_queue, guess + r)->flag) : 0u;
           if (lane == 0) {
-            unsigned long long* q = reinterpret_cast<unsigned long long*>(&a.queues[send_queue].head);
-            unsigned long long was = lane_ld(q);
             for (int tries = 0; tries < 16; ++tries) {
               const int open = (int)((uint32_t)was - (uint32_t)(was >> 32));
               if (open <= 0) break;
@@ -661,30 +673,42 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           t0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)t0);
           n_got = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_got);
           bool on = can && r < n_got;
-          if (on) {
-            LaneMail* const slot = mail_slot(send_queue, t0 + r);
-            lane_put(&slot->from, (unsigned long long)(LANE_REMOTE | (wave << 6) | place) | ((unsigned long long)x.c_st << 32));
-            lane_put(&slot->meta, (unsigned long long)x.c_label | ((unsigned long long)(x.depth + 1u) << 32));
-            lane_put(&slot->inst_np, (unsigned long long)x.inst | ((unsigned long long)x.c_np << 32));
+          // The slot of ticket t belongs to the call with that ticket from the moment on that the one a round before has
+          // been taken out (there are far more slots than waves at the queue: practically always).  While a lane waits for
+          // that, its wave goes on taking what is sent to itself: so no waves wait for one another in a circle.
+          bool to_send = on, known = t0 == guess;
+          long long w0 = 0;
+          while (__ballot(to_send)) {
+            if (to_send) {
+              const uint32_t t = t0 + r;
+              LaneMail* const slot = mail_slot(send_queue, t);
+              if (!known) f = lane_ld(&slot->flag);
+              if (f == lane_slot(t, a.queue_cap, LANE_EMPTY)) {
+                lane_put(&slot->from, (unsigned long long)(LANE_REMOTE | (wave << 6) | place) | ((unsigned long long)x.c_st << 32));
+                lane_put(&slot->meta, (unsigned long long)x.c_label | ((unsigned long long)(x.depth + 1u) << 32));
+                lane_put(&slot->inst_np, (unsigned long long)x.inst | ((unsigned long long)x.c_np << 32));
 #pragma unroll
-            for (int k2 = 0; k2 < NS; ++k2) lane_put(&slot->arg[k2], (unsigned long long)x.arg[k2]);
-            __builtin_amdgcn_s_waitcnt(0);
-            const long long w0 = wall_clock64();
-            for (;;) {
-              uint32_t expect = LANE_EMPTY;
-              if (__hip_atomic_compare_exchange_strong(&slot->flag, &expect, LANE_TASK, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT))
-                break;
-              if (expect == LANE_LEFT) {   // that wave has left: the slot is free again, the call stays here
-                lane_put(&slot->flag, LANE_EMPTY);
-                on = false;
-                break;
-              }
-              // (the slot's last call is about to be taken: there are far more slots than waves at the queue)
-              if (wall_clock64() - w0 > a.idle_ticks) {
+                for (int k2 = 0; k2 < NS; ++k2) lane_put(&slot->arg[k2], (unsigned long long)x.arg[k2]);
+                __builtin_amdgcn_s_waitcnt(0);
+                uint32_t expect = f;
+                to_send = !__hip_atomic_compare_exchange_strong(&slot->flag, &expect, lane_slot(t, a.queue_cap, LANE_TASK), __ATOMIC_RELAXED,
+                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              } else if (f == lane_slot(t, a.queue_cap, LANE_LEFT)) {   // that wave has left: the slot is free again, the call stays here
+                lane_put(&slot->flag, lane_slot(t + a.queue_cap, a.queue_cap, LANE_EMPTY));
+                on = to_send = false;
+              } else if (lane_is_pill(f)) {   // (another wave has met an error)
+                on = to_send = false;
+              } else if (w0 == 0) {
+                w0 = wall_clock64();
+              } else if (wall_clock64() - w0 > a.idle_ticks) {
                 x.bad = TDF_ERR_DEVICE;
-                break;
+                on = to_send = false;
               }
+            }
+            known = false;
+            if (have_ticket && __ballot(to_send)) {
+              LaneMail* const slot = mail_slot(my_queue, ticket);
+              if ((uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag)) == lane_slot(ticket, a.queue_cap, LANE_TASK)) take_mail(slot);
             }
           }
           if (on) {
@@ -699,7 +723,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
             x.act = ACT_NONE;
             resumed = false;
           }
-          for (unsigned long long m = __ballot(on); m; m &= m - 1ull)
+          for (unsigned long long m = __ballot(on); m; m &= m - 1ull)   // (the places of the calls that went)
             sent_mask |= 1ull << (uint32_t)__builtin_amdgcn_readlane((int)place, __ffsll((long long)m) - 1);
           hungry = n_got < n ? 0u : hungry - n_got;
         }

@@ -77,3 +77,17 @@ def test_a_wave_whose_records_all_wait_takes_no_call(fib_under_chain):
         got = lanes.run(args, waves=8, seed=seed)
         assert got["status"] == 0 and got["out"] == [ref(*a) for a in args], seed
         assert got["records"] <= 8 * 96
+
+
+@pytest.fixture(scope="module")
+def fib(tmp_path_factory):
+    return Lanes(programs.fib(), tmp_path_factory.mktemp("lanes"))
+
+
+@pytest.mark.parametrize("slow", [0, 100, 1000])
+def test_a_call_that_nobody_has_taken_yet_is_not_overwritten(fib, slow):
+    # queues of few slots, which the tickets go round while a slow wave (one of `slow` turns) has not looked at its own
+    for cap, waves, queues in [(8, 7, 1), (4, 3, 1), (4, 4, 2)]:
+        for seed in range(1, 7):
+            got = fib.run([(19,), (3,)], waves=waves, queues=queues, queue_cap=cap, slow=slow, seed=seed, max_turns=2000000)
+            assert got["status"] == 0 and got["out"] == [4181, 2], (cap, waves, seed)
