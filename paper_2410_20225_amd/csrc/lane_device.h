@@ -13,7 +13,9 @@
 // Work is shared in two tiers.
 //   Inside a wave (= one workgroup), through LDS: a lane gives the oldest frame of its stack that has a
 //   ready call left, as a record that any lane of the wave can take as a task.  Records are finished by
-//   whoever delivers the last awaited value (a join counter per record; nobody waits).  Everything is
+//   whoever delivers the last awaited value (a join counter per record; nobody waits).  The frames below
+//   the one given have nothing to share and wait for one value each: they stay a stack, in memory, and take one
+//   record together, however many they are; who returns to it has that stack from then on.  Everything is
 //   wave-synchronous: no barriers, a hand-over costs a few LDS round trips.
 //   Between waves, through memory: a wave that has nothing takes a ticket of the global queue; a wave that
 //   sees tickets outstanding sends calls (arguments and where to return to), and polls for the values that
@@ -41,6 +43,7 @@ namespace tdf {
 
 constexpr uint32_t LANE_NONE = 0xFFFFFFFFu;
 constexpr uint32_t LANE_REMOTE = 0x80000000u;   // a caller in another wave: LANE_REMOTE | wave << 6 | reply
+constexpr uint32_t LANE_STACK = 0x40000000u;    // a caller on a stack that nobody runs: LANE_STACK | record of the stack
 // Global queue: state of a slot, and the round of tickets that it is in (a ticket's number without its place in the
 // queue).  A slot is written only in the round of the ticket that it is written for, so a call that nobody has taken
 // yet stays as it is, however many tickets have been dealt out since.
@@ -55,6 +58,7 @@ constexpr uint32_t LANE_EARLY = 48;     // sweeps during which a wave gives work
 constexpr uint32_t LANE_GIVE = 56;
 constexpr uint32_t LANE_LOOP = 64;      // iterations of a loop without calls in one sweep
 constexpr uint32_t LANE_RECS = 96;      // records of a wave
+constexpr uint32_t LANE_SCARCE = 8, LANE_FEW = 16;   // free records below which all frames below a given one take one; else the first so many take one each
 constexpr uint32_t LANE_QUEUE = 128;    // tasks of a wave (at least LANE_RECS: a record is queued at most once)
 constexpr uint32_t LANE_CHUNK = 128;    // log entries a wave reserves at once (at least a wave's lanes)
 constexpr uint32_t LANE_LOG_HOLE = 0xFFFFFFFFu;
@@ -368,6 +372,32 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     seg_at(id)[0].x = spare;
     spare = id;
   };
+  auto new_seg = [&]() -> uint32_t {
+    uint32_t id = spare;
+    if (id != LANE_NONE) spare = seg_at(id)[0].x;
+    else id = lane_add(&ctl->n_seg, 1u);
+    if (id >= a.n_segs) {
+      x.bad = TDF_ERR_TABLE_FULL;
+      id = wave * 64u + lane;   // (its contents do not count any more)
+    }
+    return id;
+  };
+  // the window's oldest frame goes to memory
+  auto evict = [&]() {
+    if (lo % LANE_SEG == 0 || seg == LANE_NONE) {
+      const uint32_t id = new_seg();
+      seg_at(id)[0].x = seg;
+      if (seg != LANE_NONE) seg_at(seg)[0].y = id;
+      if (seg_b == LANE_NONE) seg_b = id;
+      seg = id;
+    }
+    uint4 c[NC];
+    win_get(lo, c);
+    uint4* f = seg_at(seg) + 1 + (lo % LANE_SEG) * NC;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) f[k] = c[k];
+    ++lo;
+  };
   // frame on the stack: {state | slot awaited << 20 | ready call left << 25 | label << 26, counter, depth, present} values
   auto pack = [&](uint4 (&c)[NC], uint32_t back_st, bool more) {
     c[0] = make_uint4(back_st | (more ? 1u << 25 : 0u) | (x.label << 26), x.counter, x.depth, x.present);
@@ -394,6 +424,26 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     for (int k = 0; k < NS; ++k)
       x.sv[k] = (uint32_t)k == slot ? v : x.sv[k];
     x.present |= 1u << slot;
+  };
+  // the stack's top frame becomes the lane's own, with the value that it waited for
+  auto pop = [&](long long v) {
+    --sp;
+    uint4 c[NC];
+    if (sp >= lo) {
+      win_get(sp, c);
+    } else {
+      mem_get(seg, sp, c);
+      lo = sp;
+      if (sp % LANE_SEG == 0 || sp == bs) {   // that was the segment's last frame
+        const uint32_t id = seg;
+        seg = sp == bs ? LANE_NONE : seg_at(id)[0].x;
+        if (sp == bs) seg_b = LANE_NONE;
+        drop_seg(id);
+      }
+    }
+    unpack(c);
+    slack -= (c[0].x >> 25) & 1u;
+    set_slot((c[0].x >> 20) & 31u, v);
   };
   // the frame of a record becomes the lane's own (bottom) frame
   auto load_rec = [&](bool on, uint32_t id) {
@@ -676,39 +726,42 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           // The slot of ticket t belongs to the call with that ticket from the moment on that the one a round before has
           // been taken out (there are far more slots than waves at the queue: practically always).  While a lane waits for
           // that, its wave goes on taking what is sent to itself: so no waves wait for one another in a circle.
-          bool to_send = on, known = t0 == guess;
+          auto not_there = [&]() {   // that wave has left: the slot is free again, the call stays here
+            lane_put(&mail_slot(send_queue, t0 + r)->flag, lane_slot(t0 + r + a.queue_cap, a.queue_cap, LANE_EMPTY));
+            on = false;
+          };
+          const uint32_t mine = lane_slot(t0 + r, a.queue_cap, LANE_EMPTY);
+          LaneMail* const slot = mail_slot(send_queue, t0 + r);
+          if (t0 != guess) f = ~mine;   // (another ticket's)
           long long w0 = 0;
-          while (__ballot(to_send)) {
-            if (to_send) {
-              const uint32_t t = t0 + r;
-              LaneMail* const slot = mail_slot(send_queue, t);
-              if (!known) f = lane_ld(&slot->flag);
-              if (f == lane_slot(t, a.queue_cap, LANE_EMPTY)) {
-                lane_put(&slot->from, (unsigned long long)(LANE_REMOTE | (wave << 6) | place) | ((unsigned long long)x.c_st << 32));
-                lane_put(&slot->meta, (unsigned long long)x.c_label | ((unsigned long long)(x.depth + 1u) << 32));
-                lane_put(&slot->inst_np, (unsigned long long)x.inst | ((unsigned long long)x.c_np << 32));
-#pragma unroll
-                for (int k2 = 0; k2 < NS; ++k2) lane_put(&slot->arg[k2], (unsigned long long)x.arg[k2]);
-                __builtin_amdgcn_s_waitcnt(0);
-                uint32_t expect = f;
-                to_send = !__hip_atomic_compare_exchange_strong(&slot->flag, &expect, lane_slot(t, a.queue_cap, LANE_TASK), __ATOMIC_RELAXED,
-                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              } else if (f == lane_slot(t, a.queue_cap, LANE_LEFT)) {   // that wave has left: the slot is free again, the call stays here
-                lane_put(&slot->flag, lane_slot(t + a.queue_cap, a.queue_cap, LANE_EMPTY));
-                on = to_send = false;
-              } else if (lane_is_pill(f)) {   // (another wave has met an error)
-                on = to_send = false;
-              } else if (w0 == 0) {
-                w0 = wall_clock64();
-              } else if (wall_clock64() - w0 > a.idle_ticks) {
+          while (__ballot(on && f != mine)) {
+            if (on && f != mine) {
+              f = lane_ld(&slot->flag);
+              if (f == lane_slot(t0 + r, a.queue_cap, LANE_LEFT)) not_there();
+              else if (lane_is_pill(f)) on = false;   // (another wave has met an error)
+              else if (w0 == 0) w0 = wall_clock64();
+              else if (wall_clock64() - w0 > a.idle_ticks) {
                 x.bad = TDF_ERR_DEVICE;
-                on = to_send = false;
+                on = false;
               }
             }
-            known = false;
-            if (have_ticket && __ballot(to_send)) {
-              LaneMail* const slot = mail_slot(my_queue, ticket);
-              if ((uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag)) == lane_slot(ticket, a.queue_cap, LANE_TASK)) take_mail(slot);
+            if (have_ticket) {
+              LaneMail* const own = mail_slot(my_queue, ticket);
+              if ((uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&own->flag)) == lane_slot(ticket, a.queue_cap, LANE_TASK)) take_mail(own);
+            }
+          }
+          if (on) {
+            lane_put(&slot->from, (unsigned long long)(LANE_REMOTE | (wave << 6) | place) | ((unsigned long long)x.c_st << 32));
+            lane_put(&slot->meta, (unsigned long long)x.c_label | ((unsigned long long)(x.depth + 1u) << 32));
+            lane_put(&slot->inst_np, (unsigned long long)x.inst | ((unsigned long long)x.c_np << 32));
+#pragma unroll
+            for (int k2 = 0; k2 < NS; ++k2) lane_put(&slot->arg[k2], (unsigned long long)x.arg[k2]);
+            __builtin_amdgcn_s_waitcnt(0);
+            uint32_t expect = mine;
+            if (!__hip_atomic_compare_exchange_strong(&slot->flag, &expect, lane_slot(t0 + r, a.queue_cap, LANE_TASK), __ATOMIC_RELAXED,
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+              if (lane_is_pill(expect)) on = false;
+              else not_there();
             }
           }
           if (on) {
@@ -730,28 +783,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
       }
       {
         if (x.run && x.act == ACT_CALL) {
-          // the window's oldest frame makes room
-          if (sp - lo == LANE_WINDOW) {
-            if (lo % LANE_SEG == 0 || seg == LANE_NONE) {
-              uint32_t id = spare;
-              if (id != LANE_NONE) spare = seg_at(id)[0].x;
-              else id = lane_add(&ctl->n_seg, 1u);
-              if (id >= a.n_segs) {
-                x.bad = TDF_ERR_TABLE_FULL;
-                id = wave * 64u + lane;   // (its contents do not count any more)
-              }
-              seg_at(id)[0].x = seg;
-              if (seg != LANE_NONE) seg_at(seg)[0].y = id;
-              if (seg_b == LANE_NONE) seg_b = id;
-              seg = id;
-            }
-            uint4 c[NC];
-            win_get(lo, c);
-            uint4* f = seg_at(seg) + 1 + (lo % LANE_SEG) * NC;
-#pragma unroll
-            for (int k2 = 0; k2 < NC; ++k2) f[k2] = c[k2];
-            ++lo;
-          }
+          if (sp - lo == LANE_WINDOW) evict();   // (the window's oldest frame makes room)
           uint4 c[NC];
           pack(c, x.c_back, x.more);
           win_put(sp, c);
@@ -771,24 +803,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
         } else if (x.run && x.act == ACT_RET) {
           if (sp > bs) {
             ++x.n_tokens;
-            const long long v = x.ret;
-            --sp;
-            uint4 c[NC];
-            if (sp >= lo) {
-              win_get(sp, c);
-            } else {
-              mem_get(seg, sp, c);
-              lo = sp;
-              if (sp % LANE_SEG == 0 || sp == bs) {   // that was the segment's last frame
-                const uint32_t id = seg;
-                seg = sp == bs ? LANE_NONE : seg_at(id)[0].x;
-                if (sp == bs) seg_b = LANE_NONE;
-                drop_seg(id);
-              }
-            }
-            unpack(c);
-            slack -= (c[0].x >> 25) & 1u;
-            set_slot((c[0].x >> 20) & 31u, v);
+            pop(x.ret);
           } else {
             x.run = false;   // to a record or another wave: below
           }
@@ -841,9 +856,27 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           __builtin_amdgcn_s_waitcnt(0);
           lane_put(&rp->flag, 1ull);
         }
+        // to a stack that nobody runs: it is this lane's from now on
+        const bool stack = out && !remote && (parent & LANE_STACK) != 0;
+        const uint32_t stack_rec = parent & ~LANE_STACK;
+        if (stack) {
+          const uint32_t m = r_meta[stack_rec];
+          bs = r_counter[stack_rec];
+          sp = lo = r_depth[stack_rec];
+          seg = r_po[stack_rec];
+          seg_b = r_join[stack_rec];
+          parent = r_parent[stack_rec];
+          rec = (m & 0xFFFFu) == 0xFFFFu ? LANE_NONE : m & 0xFFFFu;
+          resumed = (m >> 31) != 0;
+          slack = 0;
+          pop(x.ret);
+          x.run = true;
+          x.act = ACT_NONE;
+        }
+        free_recs(stack, stack_rec);
         bool last = false;
         uint32_t id = rec;
-        if (out && !remote) {
+        if (out && !remote && !stack) {
           id = parent;
           last = deliver(id, SW::ret_slot(x.label), x.ret);
         }
@@ -854,7 +887,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           atomicOr(&r_po[id], x.present | (lane_opened(x.st) << 24));
           last = atomicSub(&r_join[id], 1u) == 1u;
         }
-        if (out || wait) {
+        if ((out && !stack) || wait) {
           active = x.run = false;
           x.act = ACT_NONE;
         }
@@ -897,20 +930,47 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
         if (early && n_idle > LANE_GIVE && hungry < 8u) hungry = 0;
       }
       // Tasks wanted: for the wave's idle lanes, and some for waves without work.  A lane gives the oldest
-      // frame of its stack that has a ready call left (the largest piece of work), and the frames below it.
+      // frame of its stack that has a ready call left (the largest piece of work).
       const uint32_t want = n_idle + min(hungry, 16u);
       bool going = x.run && slack > 0 && want > nq && (uint32_t)__popcll(rich & lanemask_lt()) < want - nq;
-      if (spare_recs() >= 8 && __ballot(going)) {
+      // the values of a frame for its record: all but those outstanding, which others may have put there already; what
+      // is not present may be the argument of a call that waits
+      auto put_frame = [&](const uint4 (&c)[NC], uint32_t id, uint32_t below, bool fresh, bool more) {
+        const uint32_t fn = lane_fn(c[0].x), opened = lane_opened(c[0].x), present = c[0].w;
+        if (fresh) {
+          r_parent[id] = below;
+          r_meta[id] = (c[0].x >> 26) | (fn << 16);
+          r_counter[id] = c[0].y;
+          r_depth[id] = c[0].z;
+          r_inst[id] = x.inst;
+          r_join[id] = more ? 2u : 1u;   // the call that the frame waits for, and the task
+          r_po[id] = present | (opened << 24);
+        } else {
+          r_meta[id] &= ~(1u << 31);
+          atomicOr(&r_po[id], present | (opened << 24));
+          if (more) atomicAdd(&r_join[id], 1u);   // one more call outstanding; the lane's own part goes to the task
+        }
+        const uint32_t others = SW::ret_bits(fn, opened) & ~present;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          const uint4 w = c[1 + k / 2];
+          const unsigned long long v = k & 1 ? ((unsigned long long)w.z | ((unsigned long long)w.w << 32))
+                                             : ((unsigned long long)w.x | ((unsigned long long)w.y << 32));
+          if (!((others >> k) & 1)) r_val[k * LANE_RECS + id] = v;
+        }
+      };
+      // Frames below it become records of their own as far as they are few and records plenty: a value for a record
+      // costs a few LDS accesses, one for a stack a round trip to memory (with stacks alone fib(30) + fib(31) + fib(32)
+      // takes 7.2 ms instead of 5.2, 256 instances of tak 3.4 instead of 2.7).
+      if (spare_recs() >= LANE_SCARCE && __ballot(going)) {
         uint32_t below = parent, d = bs;   // the caller of frame d
         bool moved = false;
-        for (;;) {
-          const unsigned long long gm = __ballot(going);
-          if (gm == 0) break;
+        for (uint32_t few = 0; few < LANE_FEW; ++few) {
+          if (__ballot(going) == 0) break;
           // a record each (as far as there are any: a lane without one keeps its frames)
           const bool fresh = going && !(d == bs && rec != LANE_NONE);
           const unsigned long long rm = __ballot(fresh);
-          const uint32_t rr = (uint32_t)__popcll(rm & lanemask_lt());
-          const uint32_t n_spare = spare_recs();
+          const uint32_t rr = (uint32_t)__popcll(rm & lanemask_lt()), n_spare = spare_recs();
           const bool ok = going && (!fresh || rr < n_spare);
           const uint32_t id = !fresh ? rec : ok ? lfree[nfree - 1 - rr] : 0u;
           nfree -= min(n_spare, (uint32_t)__popcll(rm));
@@ -930,30 +990,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
               }
             }
             more = ((c[0].x >> 25) & 1u) != 0;   // it becomes a task
-            const uint32_t fn = lane_fn(c[0].x), opened = lane_opened(c[0].x), present = c[0].w;
-            if (fresh) {
-              r_parent[id] = below;
-              r_meta[id] = (c[0].x >> 26) | (fn << 16);
-              r_counter[id] = c[0].y;
-              r_depth[id] = c[0].z;
-              r_inst[id] = x.inst;
-              r_join[id] = more ? 2u : 1u;
-              r_po[id] = present | (opened << 24);
-            } else {
-              r_meta[id] &= ~(1u << 31);
-              atomicOr(&r_po[id], present | (opened << 24));
-              if (more) atomicAdd(&r_join[id], 1u);   // one more call outstanding; the lane's own part goes to the task
-            }
-            // (all but the values outstanding, which others may have put there already; what is not present may
-            // be the argument of a call that waits)
-            const uint32_t others = SW::ret_bits(fn, opened) & ~present;
-#pragma unroll
-            for (int k = 0; k < NS; ++k) {
-              const uint4 w = c[1 + k / 2];
-              const unsigned long long v = k & 1 ? ((unsigned long long)w.z | ((unsigned long long)w.w << 32))
-                                                 : ((unsigned long long)w.x | ((unsigned long long)w.y << 32));
-              if (!((others >> k) & 1)) r_val[k * LANE_RECS + id] = v;
-            }
+            put_frame(c, id, below, fresh, more);
             slack -= more ? 1u : 0u;
             below = id;
             ++d;
@@ -969,6 +1006,87 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           rec = LANE_NONE;
           resumed = false;
         }
+      }
+      // Else all of them stay a stack, with one record.
+      if (spare_recs() >= 2 && __ballot(going)) {
+        uint32_t d = bs, in = seg_b;   // the frame, and the segment it is in if it is in memory
+        if (going) {
+          while (!(((d >= lo ? win[((d % LANE_WINDOW) * NC) * 64 + lane].x : seg_at(in)[1 + (d % LANE_SEG) * NC].x) >> 25) & 1u)) {
+            ++d;
+            if (d < lo && d % LANE_SEG == 0) in = seg_at(in)[0].y;
+          }
+        }
+        // a record for the frame, unless it has one, and one for the stack, unless there is none (a lane for which there
+        // are not enough keeps its frames)
+        const bool fresh = going && !(d == bs && rec != LANE_NONE), stack = going && d > bs;
+        const unsigned long long fm = __ballot(fresh), sm = __ballot(stack);
+        const uint32_t before = (uint32_t)__popcll(fm & lanemask_lt()) + (uint32_t)__popcll(sm & lanemask_lt());
+        const uint32_t need = (fresh ? 1u : 0u) + (stack ? 1u : 0u);
+        const bool ok = going && (need == 0 || before + need <= spare_recs());
+        uint32_t id = rec, below = parent;
+        if (ok && fresh) id = lfree[nfree - 1 - before];
+        if (ok && stack) {
+          const uint32_t s_id = lfree[nfree - 2 - before];   // (a frame above others is fresh)
+          uint32_t top = seg, bottom = seg_b;   // the stack's segments
+          if (d >= lo) {   // in the window, like all frames above it
+            while (lo < d) evict();
+            top = seg;
+            bottom = seg_b;
+          } else if (d % LANE_SEG == 0) {
+            top = seg_at(in)[0].x;
+          } else {
+            top = in;
+            if (d + 1 < lo && d % LANE_SEG != LANE_SEG - 1u) {   // the lane has frames above it in the same segment: a copy for the stack
+              const bool all = d / LANE_SEG == bs / LANE_SEG;
+              const uint32_t under = all ? LANE_NONE : seg_at(in)[0].x;
+              top = new_seg();
+              seg_at(top)[0].x = under;
+              if (all) bottom = top;
+              else seg_at(under)[0].y = top;
+              for (uint32_t k = all ? bs % LANE_SEG : 0u; k < d % LANE_SEG; ++k) {
+#pragma unroll
+                for (int j = 0; j < NC; ++j) seg_at(top)[1 + k * NC + j] = seg_at(in)[1 + k * NC + j];
+              }
+            }
+          }
+          r_parent[s_id] = parent;
+          r_counter[s_id] = bs;
+          r_depth[s_id] = d;
+          r_po[s_id] = top;
+          r_join[s_id] = bottom;
+          r_meta[s_id] = (rec & 0xFFFFu) | (resumed ? 1u << 31 : 0u);
+          below = LANE_STACK | s_id;
+        }
+        if (sm) __builtin_amdgcn_s_waitcnt(0);   // (a stack's frames are in memory before anybody can see its record)
+        if (ok) {
+          uint4 c[NC];
+          if (d >= lo) {
+            win_get(d, c);
+            seg = seg_b = LANE_NONE;   // (all that was in memory, if anything, is the stack's)
+          } else {
+            mem_get(in, d, c);
+            if (d + 1u == lo) {
+              seg = seg_b = LANE_NONE;
+              if (d == bs || d % LANE_SEG == 0) drop_seg(in);   // (no frame of the stack is in it)
+            } else if (d % LANE_SEG == LANE_SEG - 1u) {
+              seg_b = seg_at(in)[0].y;
+              if (d == bs) drop_seg(in);
+            } else {
+              seg_b = in;
+            }
+          }
+          put_frame(c, id, below, fresh, true);
+          --slack;
+          bs = d + 1u;
+          lo = max(lo, bs);
+          parent = id;
+          rec = LANE_NONE;
+          resumed = false;
+        }
+        const unsigned long long om = __ballot(ok);
+        nfree -= (uint32_t)__popcll(fm & om) + (uint32_t)__popcll(sm & om);
+        min_free = min(min_free, nfree);
+        push_tasks(ok, id);
       }
     }
   }

@@ -164,6 +164,19 @@ def bad_index_through_calls():
     return prog, F, [-1000, -2, 19, 500]
 
 
+def fib_value(n):
+    a, b = 0, 1
+    for _ in range(n):
+        a, b = b, a + b
+    return a
+
+
+def _fib_as(index):
+    """fib as the function of that number."""
+    (_, (name, n_params, nodes)), _ = programs.fib()
+    return (name, n_params, [(op, ins, index if op == T.OP_CALLFN else imm) for op, ins, imm in nodes])
+
+
 def fib_below_a_chain():
     """f(n, m) = if n < 1 then fib(m - 6) + fib(m) else 1 + f(n - 1, m): a program and its reference."""
     f = _Fn("f", 2)
@@ -174,15 +187,29 @@ def fib_below_a_chain():
     b = f.add(T.OP_CALLFN, [(sm[0], 0)], imm=2)
     c = f.add(T.OP_ADD, [one, f.add(T.OP_CALLFN, [f.add(T.OP_SUB, [(sn[0], 1), one]), (sm[0], 1)], imm=1)])
     f.add(T.OP_OUT, [f.add(T.OP_MERGE, [f.add(T.OP_ADD, [a, b]), c])])
-    (_, (name, n_params, nodes)), _ = programs.fib()
-    fib = (name, n_params, [(op, ins, 2 if op == T.OP_CALLFN else imm) for op, ins, imm in nodes])
+    return ([_result(2, 1).desc(), f.desc(), _fib_as(2)], 0), lambda n, m: n + (m - 6 if m < 6 else fib_value(m - 6)) + fib_value(m)
 
-    def ref(n, m):
-        F = [0, 1]
-        while len(F) <= m:
-            F.append(F[-1] + F[-2])
-        return n + (m - 6 if m < 6 else F[m - 6]) + F[m]
-    return ([_result(2, 1).desc(), f.desc(), fib], 0), ref
+
+def fibs_along_a_chain():
+    """f(n, c, m) = if n < 1 then fib(m) else if c < 1 then f(n - 1, 2, m) + fib(m) else 1 + f(n - 1, c - 1, m): every third
+    frame of a chain has a second call; a program and its reference."""
+    f = _Fn("f", 3)
+    n, c, m = (f.add(T.OP_IN, imm=k) for k in range(3))
+    one, two = f.add(T.OP_CONST, imm=1), f.add(T.OP_CONST, imm=2)
+    sn, sc, sm = (f.add(T.OP_SWITCH, [f.add(T.OP_LT, [n, one]), v]) for v in (n, c, m))
+    base = f.add(T.OP_CALLFN, [(sm[0], 0)], imm=2)
+    tn, tc, tm = (f.add(T.OP_SWITCH, [f.add(T.OP_LT, [(sc[0], 1), one]), (s[0], 1)]) for s in (sn, sc, sm))
+    a = f.add(T.OP_CALLFN, [f.add(T.OP_SUB, [(tn[0], 0), one]), f.add(T.OP_ADD, [(tc[0], 0), two]), (tm[0], 0)], imm=1)
+    b = f.add(T.OP_CALLFN, [(tm[0], 0)], imm=2)
+    d = f.add(T.OP_CALLFN, [f.add(T.OP_SUB, [(tn[0], 1), one]), f.add(T.OP_SUB, [(tc[0], 1), one]), (tm[0], 1)], imm=1)
+    f.add(T.OP_OUT, [f.add(T.OP_MERGE, [base, f.add(T.OP_ADD, [a, b]), f.add(T.OP_ADD, [one, d])])])
+
+    def ref(n, c, m):
+        total = fib_value(m)
+        for _ in range(n):
+            total, c = (total + fib_value(m), 2) if c < 1 else (total + 1, c - 1)
+        return total
+    return ([_result(3, 1).desc(), f.desc(), _fib_as(2)], 0), ref
 
 
 # name -> program, forest, arguments, reference; the vector results are rows of E

@@ -5,7 +5,7 @@ import pytest
 import oracle
 from oracle import programs as oprog
 from lane_cpu import Lanes, needs_host_lanes
-from lane_programs import BAD_INDEX, INTEGER, VECTOR, fib_below_a_chain
+from lane_programs import BAD_INDEX, INTEGER, VECTOR, fib_below_a_chain, fibs_along_a_chain
 
 pytestmark = needs_host_lanes
 tdf = pytest.importorskip("paper_2410_20225_amd.tdf")
@@ -91,3 +91,26 @@ def test_a_call_that_nobody_has_taken_yet_is_not_overwritten(fib, slow):
         for seed in range(1, 7):
             got = fib.run([(19,), (3,)], waves=waves, queues=queues, queue_cap=cap, slow=slow, seed=seed, max_turns=2000000)
             assert got["status"] == 0 and got["out"] == [4181, 2], (cap, waves, seed)
+
+
+def test_frames_with_nothing_to_share_do_not_keep_a_wave_from_sharing(fib_under_chain):
+    # a chain of calls above fib(18): every frame of it is pushed and popped, beyond that it costs nothing
+    lanes, ref = fib_under_chain
+    sweeps = {}
+    for n in (0, 1, 4, 5, 16, 17, 20, 100, 200, 1000):
+        got = [lanes.run([(n, 18)], waves=8, seed=seed) for seed in (1, 2, 3)]
+        assert all(g["status"] == 0 and g["out"] == [ref(n, 18)] for g in got), n
+        sweeps[n] = min(g["sweeps"] for g in got)
+    for n in (100, 200, 1000):
+        assert sweeps[n] - 2 * (n - 20) < 1.5 * sweeps[20], sweeps
+
+
+@pytest.mark.parametrize("waves", [1, 2, 5, 16])
+def test_stacks_between_frames_that_are_shared(waves, tmp_path):
+    prog, ref = fibs_along_a_chain()
+    lanes = Lanes(prog, tmp_path)
+    args = [(70, 2, 9), (40, 0, 12), (3, 1, 5), (200, 2, 6), (0, 0, 10), (17, 1, 11)]
+    for seed in range(1, 7):
+        got = lanes.run(args, waves=waves, seed=seed)
+        assert got["status"] == 0 and got["out"] == [ref(*a) for a in args], seed
+        assert got["records"] <= 96 * waves
