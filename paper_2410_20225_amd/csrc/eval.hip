@@ -553,9 +553,9 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   const EndReport* fin = (const EndReport*)((char*)gr->pinned + PIN_END);
   bool ended = false;       // the end's report has been read
   bool rows_known = false;  // the lanes' report came with the level offsets' totals: rows, order and leaves are queued
-  auto finish = [&](bool lanes_totals, const void* sync, const void* gcount) -> tdf_status {
+  auto finish = [&](uint32_t lanes_max_tags, const void* sync, const void* gcount) -> tdf_status {
     EndArgs g{(EndReport*)fin, (const unsigned long long*)(base + P.off_stamps), (const unsigned long long*)gcount, sync, ++gr->seq,
-              lanes_totals ? 1 : 0};
+              lanes_max_tags};
     launch_finish(P.lanes, g, take(s), s);
     return TDF_OK;
   };
@@ -564,6 +564,9 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     a.out_i64 = e.out_i64;
     a.idle_ticks = spin_ticks;
     a.run_ticks = 2 * spin_ticks;   // (then it is the step machine's)
+    a.max_tags = e.max_tags;
+    // (two reports of a wave, about, in a run of max_tags tags)
+    a.tags_at_once = std::max(64u, e.max_tags / (2u * a.n_waves));
     if (P.vec) vec_pack_w(on(s), &a, base + P.L.zero_begin, P.L.zero_end - P.L.zero_begin, s);
     else launch_lane_init(a, take(s), s);
     if (tdf_status ls = launch_lanes(a, P.n_stored, gr->jit, s); ls != TDF_OK) return ls;
@@ -589,7 +592,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       lt = rep->t;
       rows_known = !lt.bad;
     } else {
-      if (tdf_status fs = finish(true, nullptr, nullptr); fs != TDF_OK) return fs;
+      if (tdf_status fs = finish(e.max_tags, nullptr, nullptr); fs != TDF_OK) return fs;
       HIP_TRY(hipGetLastError());
       if (tdf_status ws = wait_report(&fin->seq, gr->seq, s); ws != TDF_OK) return ws;
       lt = fin->t;
@@ -874,7 +877,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)gr->join_event, 0));
     }
     HIP_TRY(hipGetLastError());
-    if (tdf_status fs = finish(false, use_tail || deep ? base + P.off_tail_sync : nullptr, with_grad ? base + P.off_gcount : nullptr);
+    if (tdf_status fs = finish(0u, use_tail || deep ? base + P.off_tail_sync : nullptr, with_grad ? base + P.off_gcount : nullptr);
         fs != TDF_OK)
       return fs;
     if (with_grad && !no_alloc && locks.data.owns_lock()) {
@@ -908,7 +911,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     }
   }
   if (!ended) {   // (the step machine on a program without vector operators, or a run that failed)
-    if (tdf_status fs = finish(false, nullptr, nullptr); fs != TDF_OK) return fs;
+    if (tdf_status fs = finish(0u, nullptr, nullptr); fs != TDF_OK) return fs;
     if (tdf_status ws = wait_report(&fin->seq, gr->seq, s); ws != TDF_OK) return ws;
   }
   HIP_TRY(hipGetLastError());

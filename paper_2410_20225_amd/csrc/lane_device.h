@@ -34,8 +34,10 @@
 // of 512 leaves 4200 -> 1500.
 //
 // Conditions that this machine does not handle (a call some of whose arguments are dead, a function
-// that completes without a value, more frames than there is room for, more sweeps than the limit) set
-// `status`; the host then runs the evaluation on the step machine, whose answer counts.
+// that completes without a value, more frames than there is room for, more tags than max_tags) set
+// `status`; the host then runs the evaluation on the step machine, whose answer counts.  Up to max_tags the step machine
+// would have had a record for every tag; whether the tags alive at once fit where there are more is its to say.  (The
+// same limit ends a recursion without a base case.)
 #pragma once
 #include "engine.h"
 
@@ -113,6 +115,12 @@ template <typename T> __device__ __forceinline__ void lane_put(T* p, T v) {
 }
 template <typename T> __device__ __forceinline__ T lane_add(T* p, T v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum over the lanes of a wave; every lane must call.
+__device__ __forceinline__ uint32_t wave_usum(uint32_t v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
 // A lane: its frame, what the last sweep asks for, and its counts.
@@ -343,6 +351,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
   uint32_t mx_sp = 0;
   // wave-uniform
   const long long t_start = wall_clock64();
+  uint32_t n_told = 0;                    // tags reported
   uint32_t qh = 0, qt = 0, nfree = LANE_RECS, iter = 0, syncs = 0, ticket = 0, min_free = LANE_RECS;
   unsigned long long sent_mask = 0;       // replies awaited, by lane
   bool more_inst = true, stop = false, have_ticket = false;
@@ -503,6 +512,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
       for (uint32_t k = 0; k < n; ++k) lane_put(&mail_slot(lane, t0 + k)->flag, lane_slot(t0 + k, a.queue_cap, LANE_PILL));
     }
   };
+  auto given_up = [&]() { return (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&ctl->status)); };
   auto raise_status = [&]() {   // whole wave
     const unsigned long long m = __ballot(x.bad != 0);
     if (m == 0) return;
@@ -655,7 +665,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
             __builtin_amdgcn_s_sleep(4);
             if (wall_clock64() - t0 > a.idle_ticks) {
               if (sent_mask || nfree != LANE_RECS) {   // others still work on what this wave waits for: look whether they gave up
-                if (lane_ld(&ctl->status) != 0 || wall_clock64() - t_start > a.run_ticks) {
+                if (given_up() != 0 || wall_clock64() - t_start > a.run_ticks) {
                   if (lane == 0) x.bad = TDF_ERR_STEP_LIMIT;
                   raise_status();
                   home = true;
@@ -901,9 +911,22 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
       if (stop) break;
     }
     if ((syncs & 15u) == 0) {
-      if (lane_ld(&ctl->status) != 0) break;
+      if (given_up() != 0) break;
       if (wall_clock64() - t_start > a.run_ticks) {
         x.bad = TDF_ERR_STEP_LIMIT;
+        raise_status();
+        break;
+      }
+    }
+    if ((syncs & 63u) == 0) {   // (rarely: a run that is refused may as well be a little longer)
+      const unsigned long long told = lane_ld(&ctl->n_tags);
+      const uint32_t n = wave_usum(x.n_tags);   // (modulo 2^32, like the difference)
+      if (n - n_told >= a.tags_at_once) {
+        if (lane == 0) (void)lane_add(&ctl->n_tags, (unsigned long long)(n - n_told));
+        n_told = n;
+      }
+      if (__ballot(told > a.max_tags)) {
+        x.bad = TDF_ERR_TABLE_FULL;
         raise_status();
         break;
       }

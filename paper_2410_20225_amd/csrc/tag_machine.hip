@@ -519,9 +519,9 @@ __global__ void __launch_bounds__(BUCKET_THREADS) k_lane_place(Engine e, LaneSor
 __global__ void __launch_bounds__(256) k_finish(LaneArgs a, EndArgs g, Stamp st) {
   stamp_now(st);
   if (threadIdx.x < 64) {
-    if (g.lanes) {   // (a program without vector operators: the totals have not been read yet)
+    if (g.lanes_max_tags) {   // (a program without vector operators: the totals have not been read yet)
       LaneTotals t;
-      lane_totals(a, LaneLimits{}, t);
+      lane_totals(a, LaneLimits{g.lanes_max_tags, 0u, 0u}, t);
       if (threadIdx.x == 0) g.end->t = t;
     }
     if (g.gcount && threadIdx.x < 2) g.end->gcount[threadIdx.x] = g.gcount[threadIdx.x];

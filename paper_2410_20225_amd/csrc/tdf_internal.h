@@ -39,7 +39,7 @@ struct EndArgs {
   const unsigned long long* gcount;   // null: no gradient pass
   const void* sync;                   // null: no chain launch
   uint32_t seq;
-  int lanes;                          // the lanes' totals are wanted
+  uint32_t lanes_max_tags;            // 0, or: the lanes' totals are wanted, and this is the limit on tags
 };
 
 // Run-time generated step kernels for one program (jit.cpp).  Returns false (and leaves the

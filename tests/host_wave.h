@@ -61,6 +61,7 @@ struct Wave {
   Lane lane[64];
   uint64_t post[2][64];    // what the lanes brought to the last two cross-lane operations
   uint32_t id = 0, next = 0;
+  long long clock = 0;     // the same for all lanes until they meet again
   bool done = false;
   char* lds = nullptr;
 };
@@ -152,6 +153,7 @@ inline bool run(uint32_t n, size_t lds_bytes, uint64_t seed, uint64_t max_turns,
       if (met == 0) { w.done = true; --left; }
       else if (met != 64) { fprintf(stderr, "a cross-lane operation without all lanes\n"); abort(); }
       w.next = 0;
+      w.clock = (long long)g.turns;
       --quantum;
     }
   }
@@ -192,7 +194,7 @@ inline int hw_dpp(int old, int v, int ctrl, int row_mask) {
 #define __builtin_amdgcn_s_sleep(n) hw::yield()
 #define __builtin_amdgcn_s_waitcnt(n) ((void)0)
 #define __builtin_amdgcn_s_getreg(n) 0
-inline long long wall_clock64() { hw::yield(); return (long long)hw::world().turns; }
+inline long long wall_clock64() { hw::yield(); return hw::world().w->clock; }
 inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
 inline int __ffsll(long long v) { return __builtin_ffsll(v); }
 inline int __ffs(int v) { return __builtin_ffs(v); }

@@ -46,6 +46,8 @@ int main() {
   a.log_cap = (uint32_t)num("log_cap", 0);
   a.vocab = (int32_t)num("vocab", 0);
   a.idle_ticks = a.run_ticks = num("ticks", 1ll << 40);
+  a.max_tags = (uint32_t)num("max_tags", 1ll << 30);
+  a.tags_at_once = max(64u, a.max_tags / (2u * a.n_waves));
   LaneCtl ctl{};
   std::vector<LaneQueue> queues(a.n_queues);
   std::vector<LaneMail> mail((size_t)a.n_queues * a.queue_cap);

@@ -139,3 +139,25 @@ def test_tree_programs(name, waves, monkeypatch):
     st, stats = run.run(None, dnode=dnode)
     got = run.out_node_loss.cpu().numpy()
     assert stats.repeats == 0 and np.array_equal(got == 0.0, want == 0.0) and rel_fro(got, want) < 2e-2
+
+
+def test_max_tags_is_the_step_machines_limit(monkeypatch):
+    # Without kept frames max_tags bounds the tags alive at once, as the step machine counts them; the lanes answer where
+    # there are no more tags than that at all, and leave every other call to it.
+    ns = [(n,) for n in [20] * 8]
+    tags = 8 * (2 * 10946 - 1)
+    fns, r = programs.fib()
+    g = tdf.graph_build(fns, r)
+    out, counts, repeats = _eval_int(g, ns, 1, tags)
+    assert out == [6765] * 8 and counts[0] == tags and repeats == 0
+    out, counts, repeats = _eval_int(g, ns, 1, tags - 1)
+    assert out == [6765] * 8 and counts[0] == tags and repeats >= 1
+
+    def status(max_tags):
+        t_args = torch.tensor(ns, dtype=torch.int64, device=DEV).reshape(-1)
+        inp = tdf.make_inputs(8, args=t_args, n_args=1, max_tags=max_tags, stats_level=0)
+        ws = torch.empty(tdf.workspace_size(g, inp), dtype=torch.uint8, device=DEV)
+        return tdf.eval(g, inp, ws, out_i64=torch.zeros(8, dtype=torch.int64, device=DEV), check=False)[0]
+    got = [status(m) for m in (8, 64, 4096)]
+    monkeypatch.setenv("TDF_NO_LANES", "1")
+    assert got == [status(m) for m in (8, 64, 4096)] and got[0] == got[1] == tdf.ERR_TABLE_FULL

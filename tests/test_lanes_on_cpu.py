@@ -114,3 +114,16 @@ def test_stacks_between_frames_that_are_shared(waves, tmp_path):
         got = lanes.run(args, waves=waves, seed=seed)
         assert got["status"] == 0 and got["out"] == [ref(*a) for a in args], seed
         assert got["records"] <= 96 * waves
+
+
+def test_a_run_beyond_max_tags_is_given_up(fib, tmp_path):
+    # f(n) = 1 + f(n + 1) never ends: reports of the waves' tags end it soon after max_tags
+    T = tdf
+    f = [(T.OP_IN, [], 0), (T.OP_CONST, [], 1), (T.OP_ADD, [(0, 0), (1, 0)], 0), (T.OP_CALLFN, [(2, 0)], 1),
+         (T.OP_ADD, [(3, 0), (1, 0)], 0), (T.OP_OUT, [(4, 0)], 0)]
+    res = [(T.OP_IN, [], 0), (T.OP_CALLFN, [(0, 0)], 1), (T.OP_OUT, [(1, 0)], 0)]
+    lanes = Lanes(([("result", 1, res), ("f", 1, f)], 0), tmp_path)
+    got = lanes.run([(n,) for n in range(6)], waves=4, max_tags=5000)
+    assert got["status"] == -tdf.ERR_TABLE_FULL and 2500 < got["tags"] < 15000
+    # (as many tags as there may be are no reason)
+    assert fib.run([(n,) for n in range(21)], waves=40, max_tags=57291)["status"] == 0
