@@ -296,6 +296,7 @@ struct alignas(128) LaneCtl {   // zero on entry
   uint32_t n_seg;               // stack segments used (starts at the number of lanes, which have one each)
   uint32_t leaf_next;           // rows given to leaves (after the run)
   uint32_t rows_done;           // workgroups through with the first pass over the log
+  uint32_t beat;                // counted on by every wave that works, 32 times in LaneArgs::dead_ticks
   unsigned long long n_tags;    // tags that the waves have reported so far
 };
 struct LaneLimits {
@@ -331,7 +332,7 @@ struct LaneArgs {
   uint32_t n_segs, n_queues, queue_cap, log_cap, n_inst, n_waves, per_grab;
   int32_t n_tree_nodes, vocab, n_args;
   long long idle_ticks;         // longest wait of an idle wave before it leaves (100 MHz ticks)
-  long long run_ticks;          // longest run before the machine gives up
+  long long dead_ticks;         // longest time in which nobody works before waves that wait give up
   uint32_t max_tags;            // a run with more tags is the step machine's
   uint32_t tags_at_once;        // tags that a wave reports at once
 };

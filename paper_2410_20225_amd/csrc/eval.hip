@@ -563,7 +563,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     LaneArgs& a = P.lanes;
     a.out_i64 = e.out_i64;
     a.idle_ticks = spin_ticks;
-    a.run_ticks = 2 * spin_ticks;   // (then it is the step machine's)
+    a.dead_ticks = 2 * spin_ticks;
     a.max_tags = e.max_tags;
     // (two reports of a wave, about, in a run of max_tags tags)
     a.tags_at_once = std::max(64u, e.max_tags / (2u * a.n_waves));

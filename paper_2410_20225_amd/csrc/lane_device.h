@@ -37,7 +37,7 @@
 // that completes without a value, more frames than there is room for, more tags than max_tags) set
 // `status`; the host then runs the evaluation on the step machine, whose answer counts.  Up to max_tags the step machine
 // would have had a record for every tag; whether the tags alive at once fit where there are more is its to say.  (The
-// same limit ends a recursion without a base case.)
+// same limit ends a recursion without a base case; there is none on time while any wave works.)
 #pragma once
 #include "engine.h"
 
@@ -350,8 +350,8 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
   bool resumed = false;                   // the bottom frame has nothing outstanding in other lanes
   uint32_t mx_sp = 0;
   // wave-uniform
-  const long long t_start = wall_clock64();
-  uint32_t n_told = 0;                    // tags reported
+  uint32_t n_told = 0, beat_seen = 0;     // tags reported; the beat when this wave looked last
+  long long t_beat = wall_clock64();      // when this wave counted it on, or saw that another one had, last
   uint32_t qh = 0, qt = 0, nfree = LANE_RECS, iter = 0, syncs = 0, ticket = 0, min_free = LANE_RECS;
   unsigned long long sent_mask = 0;       // replies awaited, by lane
   bool more_inst = true, stop = false, have_ticket = false;
@@ -662,10 +662,17 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
               poll_replies();
               if (qt != qh) break;
             }
+            home = !have_ticket && given_up() != 0;   // (with a ticket it is sent home)
+            if (home) break;
             __builtin_amdgcn_s_sleep(4);
             if (wall_clock64() - t0 > a.idle_ticks) {
               if (sent_mask || nfree != LANE_RECS) {   // others still work on what this wave waits for: look whether they gave up
-                if (given_up() != 0 || wall_clock64() - t_start > a.run_ticks) {
+                const uint32_t beat = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&ctl->beat));
+                if (beat != beat_seen) {
+                  beat_seen = beat;
+                  t_beat = wall_clock64();
+                }
+                if (given_up() != 0 || wall_clock64() - t_beat > a.dead_ticks) {
                   if (lane == 0) x.bad = TDF_ERR_STEP_LIMIT;
                   raise_status();
                   home = true;
@@ -912,10 +919,10 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     }
     if ((syncs & 15u) == 0) {
       if (given_up() != 0) break;
-      if (wall_clock64() - t_start > a.run_ticks) {
-        x.bad = TDF_ERR_STEP_LIMIT;
-        raise_status();
-        break;
+      const long long now = wall_clock64();
+      if (now - t_beat > a.dead_ticks / 32) {
+        if (lane == 0) (void)lane_add(&ctl->beat, 1u);
+        t_beat = now;
       }
     }
     if ((syncs & 63u) == 0) {   // (rarely: a run that is refused may as well be a little longer)

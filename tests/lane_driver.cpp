@@ -45,7 +45,8 @@ int main() {
   a.n_segs = a.n_waves * 64u + (uint32_t)num("segs", 4096);
   a.log_cap = (uint32_t)num("log_cap", 0);
   a.vocab = (int32_t)num("vocab", 0);
-  a.idle_ticks = a.run_ticks = num("ticks", 1ll << 40);
+  a.idle_ticks = num("idle_ticks", 1ll << 40);
+  a.dead_ticks = num("dead_ticks", 1ll << 40);
   a.max_tags = (uint32_t)num("max_tags", 1ll << 30);
   a.tags_at_once = max(64u, a.max_tags / (2u * a.n_waves));
   LaneCtl ctl{};

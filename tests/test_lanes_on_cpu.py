@@ -127,3 +127,10 @@ def test_a_run_beyond_max_tags_is_given_up(fib, tmp_path):
     assert got["status"] == -tdf.ERR_TABLE_FULL and 2500 < got["tags"] < 15000
     # (as many tags as there may be are no reason)
     assert fib.run([(n,) for n in range(21)], waves=40, max_tags=57291)["status"] == 0
+
+
+def test_a_long_run_is_not_given_up_while_waves_work(fib):
+    # longer than the time in which nobody may work; waves that wait look at that all the time
+    for seed in (1, 2, 3):
+        got = fib.run([(24,)], waves=6, seed=seed, idle_ticks=50, dead_ticks=30000)
+        assert got["status"] == 0 and got["out"] == [46368] and got["turns"] > 40000, seed
