@@ -417,7 +417,9 @@ tdf_status wait_report(const uint32_t* word, uint32_t seq, hipStream_t s) {
 // most compute units have nothing else to do.  The data stage ends with the gradient pass: the sums that
 // follow it (weight and embedding gradients) are ordinary launches and run beside the next data plane.
 // A caller gets that overlap by evaluating from two threads, each with its own graph, workspace and
-// stream.  Lock order: control, then data.
+// stream.  Lock order: control, then data.  A tag phase can be long and hold much of every compute unit (the lanes'
+// stacks and records in LDS); a chain launch whose workgroups could not all start beside it gives up after its
+// bounded wait, and its evaluation is repeated in a turn of its own, which keeps both stages.
 std::mutex g_control_mutex, g_data_mutex;
 struct EvalLocks {
   std::unique_lock<std::mutex> control{g_control_mutex, std::defer_lock}, data{g_data_mutex, std::defer_lock};
@@ -425,7 +427,7 @@ struct EvalLocks {
 
 tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outputs* out, tdf_grads* grads,
                void* workspace, size_t workspace_bytes, void* hip_stream, tdf_stats* stats, bool with_grad,
-               EvalLocks& locks, int inherited_repeats = 0, bool no_alloc = false) {
+               EvalLocks& locks, int inherited_repeats = 0, bool no_alloc = false, bool alone = false) {
   if (!locks.control.owns_lock()) locks.control.lock();
   if (!gr || !out) { set_error("NULL graph or outputs"); return TDF_ERR_BAD_ARG; }
   const Graph& G = gr->g;
@@ -527,8 +529,9 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   // Only the build for the tests has this: 1 = the host treats the machines' kernels as having left
   // their dies (once per graph), 2 = the level tail's launches.  The reaction is the product's own.
   const int test_mixed_dies = getenv("TDF_TEST_MIXED_DIES") ? atoi(getenv("TDF_TEST_MIXED_DIES")) : 0;
+  const int test_gave_up = getenv("TDF_TEST_GAVE_UP") ? atoi(getenv("TDF_TEST_GAVE_UP")) : 0;   // 1: the first chain launches, 2: all
 #else
-  constexpr int test_mixed_dies = 0;
+  constexpr int test_mixed_dies = 0, test_gave_up = 0;
 #endif
   Ctrl hc{};
   uint32_t rounds = 0, repeats = 0;
@@ -710,8 +713,11 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     // From here on the next evaluation's tag machine may run (not beside an evaluation in the static
     // workspace, which has one user at a time).  The leaves' rows and the sorts of the schedule are
     // ordinary launches: they do not wait for the data stage, which begins with the first cell launch.
-    if (no_alloc) locks.data.lock();
-    else locks.control.unlock();
+    if (no_alloc || alone) {
+      if (!locks.data.owns_lock()) locks.data.lock();
+    } else {
+      locks.control.unlock();
+    }
     auto enter_data_stage = [&]() { if (!locks.data.owns_lock()) locks.data.lock(); };
     e.row0 = hc.n_leaf;   // leaf i has row i, the cell at position q of the sorted log row n_leaf + q
     hipStream_t s2 = (hipStream_t)gr->side_stream, s3 = (hipStream_t)gr->sort_stream;
@@ -898,6 +904,13 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
         gave_up = gave_up || d.abort != 0;
       }
       mixed = mixed || test_mixed_dies == 2;
+      gave_up = gave_up || test_gave_up == 2 || (test_gave_up == 1 && !alone);
+      if (gave_up && !mixed && !alone) {   // (the other evaluation's tag phase may have been in the way)
+        if (locks.data.owns_lock()) locks.data.unlock();
+        if (locks.control.owns_lock()) locks.control.unlock();
+        return run(gr, in, dy, out, grads, workspace, workspace_bytes, hip_stream, stats, with_grad, locks,
+                   inherited_repeats + (int)repeats + 1, no_alloc, true);
+      }
       if (gave_up && !mixed) {
         set_error("device: a workgroup waited too long at a die barrier of the level tail");
         return TDF_ERR_DEVICE;
@@ -906,7 +919,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
         gr->die_local = false;
         if (locks.data.owns_lock()) locks.data.unlock();   // (control before data: start over in order)
         return run(gr, in, dy, out, grads, workspace, workspace_bytes, hip_stream, stats, with_grad, locks,
-                   inherited_repeats + (int)repeats + 1, no_alloc);
+                   inherited_repeats + (int)repeats + 1, no_alloc, alone);
       }
     }
   }

@@ -130,3 +130,103 @@ def test_one_graph_from_two_threads_takes_turns():
     assert torch.equal(run.out_f32, want["out_f32"])
     for k in ("dW", "db", "dE"):
         assert rel_fro(getattr(run, k).cpu().numpy(), want[k].cpu().numpy()) < 1e-5, k
+
+
+def _deep_trees():
+    """Half of the trees are chains: levels in the chain launches, forward and gradient."""
+    from tdf_workloads.trees import left_chain_tree, random_split_tree, build_forest
+    from tdf_workloads import SplitMix64
+    shapes = [left_chain_tree(90 + b) for b in range(12)] + [random_split_tree(20 + b, SplitMix64(b)) for b in range(12)]
+    c = make_config(4, n_trees=len(shapes), max_leaves=4, hidden=64, vocab=300)
+    rng = SplitMix64(5)
+    c["forest"] = build_forest(shapes, lambda n: rng.randint(0, c["V"] - 1, n))
+    c["labels"] = rng.randint(0, 4, len(shapes))
+    return c
+
+
+def test_two_tree_evaluations_in_flight_on_the_lanes():
+    # statistics level 0: one evaluation's depth-first lanes beside the other's level and chain launches
+    c = _deep_trees()
+    B = c["forest"].n_trees
+    dy = np.full(B, 1.0 / B)
+    ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
+    runs = [TreeRun(c, head=True, grad=True, stats_level=0) for _ in range(2)]
+    got = [[] for _ in runs]
+
+    def loop(i):
+        for _ in range(8):
+            st, stats = runs[i].run(dy)
+            got[i].append((stats.n_tags, stats.n_grad_firings, stats.n_grad_not_once, stats.repeats, stats.tail_used, runs[i].out_f32.clone()))
+
+    _in_threads([lambda i=i: loop(i) for i in range(2)])
+    for i in range(2):
+        for n_tags, n_gf, n_bad, repeats, tail, loss in got[i]:
+            assert n_tags == n_gf == len(ref["it"].tags) and n_bad == 0 and repeats == 0 and tail == 1
+            assert torch.equal(loss, got[0][0][5])
+        assert rel_fro(runs[i].out_f32.cpu().numpy(), np.array(ref["out"])) < 2e-2
+        for k in ("dW", "db", "dE"):
+            assert rel_fro(getattr(runs[i], k).cpu().numpy(), ref["grads"][k]) < 2e-2, k
+
+
+def test_chain_launches_beside_a_recursion_that_fills_the_gpu(monkeypatch):
+    # The lanes of the other thread's recursion hold most of every compute unit's LDS for longer than the chain's
+    # barriers wait (the limit is set low; all waits end): an evaluation whose chain could not start in time takes a turn
+    # of its own, so all of them give what they give alone.  (How many had to is printed: it depends on the order of events.)
+    monkeypatch.setenv("TDF_GRID_WAIT_MS", "2")
+    c = _deep_trees()
+    B = c["forest"].n_trees
+    dy = np.full(B, 1.0 / B)
+    tree = TreeRun(c, head=True, grad=True, stats_level=0)
+    tree.run(dy)
+    want = tree.out_f32.clone()
+    fns, r = programs.fib()
+    g = tdf.graph_build(fns, r)
+    args = torch.full((1,), 36, dtype=torch.int64, device=DEV)
+    inp = tdf.make_inputs(1, args=args, n_args=1, max_tags=2 * 24157817 - 1, stats_level=0)
+    ws = torch.empty(tdf.workspace_size(g, inp), dtype=torch.uint8, device=DEV)
+    out = torch.full((1,), -1, dtype=torch.int64, device=DEV)
+    repeats = []
+
+    def ints():
+        for _ in range(8):
+            tdf.eval(g, inp, ws, out_i64=out)
+            assert out.cpu().tolist() == [14930352]
+
+    def trees():
+        for _ in range(12):
+            st, stats = tree.run(dy)
+            repeats.append(stats.repeats)
+            assert stats.n_grad_not_once == 0 and torch.equal(tree.out_f32, want)
+
+    _in_threads([ints, trees])
+    print("repeats of the tree evaluations:", repeats)
+
+
+@pytest.mark.parametrize("threads", [1, 2])
+def test_an_evaluation_whose_chain_gave_up_takes_a_turn_of_its_own(threads, monkeypatch):
+    # the host is told that the chain launches gave up: the first ones of an evaluation, or those of its own turn too
+    import os
+    hooks = tdf.load_library(os.path.join(os.path.dirname(tdf.__file__), "libtdf_hooks.so"))
+    c = _deep_trees()
+    B = c["forest"].n_trees
+    dy = np.full(B, 1.0 / B)
+    ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
+    monkeypatch.setenv("TDF_TEST_GAVE_UP", "1")
+    with tdf.use_library(hooks):
+        runs = [TreeRun(c, head=True, grad=True, stats_level=0) for _ in range(threads)]
+    repeats = []
+
+    def loop(i):
+        for _ in range(4):
+            repeats.append(runs[i].run(dy)[1].repeats)
+
+    _in_threads([lambda i=i: loop(i) for i in range(threads)])
+    assert repeats == [1] * 4 * threads
+    for run in runs:
+        assert rel_fro(run.out_f32.cpu().numpy(), np.array(ref["out"])) < 2e-2
+        for k in ("dW", "db", "dE"):
+            assert rel_fro(getattr(run, k).cpu().numpy(), ref["grads"][k]) < 2e-2, k
+    monkeypatch.setenv("TDF_TEST_GAVE_UP", "2")
+    with pytest.raises(tdf.TdfError) as e:
+        runs[0].run(dy)
+    assert e.value.status == tdf.ERR_DEVICE
