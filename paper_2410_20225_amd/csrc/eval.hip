@@ -511,7 +511,11 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     std::string log;
     if (!jit_compile(G.prog, gr->jit, log) && getenv("TDF_JIT_VERBOSE")) fprintf(stderr, "tdf: no generated kernels: %s\n", log.c_str());
   }
-  bool use_lanes = P.lanes.n_waves > 0 && workspace_bytes >= P.L.total && gr->lanes_ok && gr->die_local && !getenv("TDF_NO_LANES");
+  bool use_lanes = P.lanes.n_waves > 0 && workspace_bytes >= P.L.total && gr->die_local && !getenv("TDF_NO_LANES");
+  if (use_lanes && gr->lanes_skip > 0) {
+    --gr->lanes_skip;
+    use_lanes = false;
+  }
   if (use_lanes && !gr->jit.lanes_tried && !no_alloc) {
     gr->jit.lanes_tried = true;
     std::string log;
@@ -555,6 +559,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   const LaneReport* rep = (const LaneReport*)((char*)gr->pinned + PIN_LANES);
   const EndReport* fin = (const EndReport*)((char*)gr->pinned + PIN_END);
   bool ended = false;       // the end's report has been read
+  bool left_over = false;   // the lanes have left the evaluation to the step machine
   bool rows_known = false;  // the lanes' report came with the level offsets' totals: rows, order and leaves are queued
   auto finish = [&](uint32_t lanes_max_tags, const void* sync, const void* gcount) -> tdf_status {
     EndArgs g{(EndReport*)fin, (const unsigned long long*)(base + P.off_stamps), (const unsigned long long*)gcount, sync, ++gr->seq,
@@ -602,12 +607,13 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       ended = !lt.bad;
     }
     if (lt.bad) {   // left to the step machine, which also says what is wrong if something is
-      if (status_is(lt.status, TDF_ERR_UNSUPPORTED)) gr->lanes_ok = false;
       use_lanes = false;
+      left_over = true;
       ++repeats;
       memset(launches, 0, sizeof(launches));
       begin(TDF_PHASE_TAGS);
     } else {
+      gr->lanes_skip_next = tdf_graph::LANES_SKIP;
       hc.n_leaf = lt.n_leaf; hc.n_cell = lt.n_cell;
       hc.n_tags = lt.n_tags; hc.n_tokens = lt.n_tokens;
       hc.step = lt.max_iter;
@@ -693,6 +699,10 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (!e.reclaim && hc.n_tags > (unsigned long long)e.max_tags && !hc.status) hc.status = (uint32_t)(-TDF_ERR_TABLE_FULL);
     if (!hc.status) launch_merge_logs(e, leaf_off, cell_off, s);
     break;
+  }
+  if (left_over && !hc.status) {   // ... which had no complaint
+    gr->lanes_skip = gr->lanes_skip_next;
+    gr->lanes_skip_next = std::min(2u * gr->lanes_skip_next, (uint32_t)tdf_graph::LANES_SKIP_MOST);
   }
   if (!use_lanes) {
     end(TDF_PHASE_TAGS, 2 + 2ll * rounds);

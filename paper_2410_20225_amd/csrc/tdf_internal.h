@@ -67,7 +67,10 @@ struct tdf_graph {
   tdf::Graph g;
   tdf::JitKernels jit;
   bool die_local = true;    // tag machines keep to one accelerator die each (cleared if the GPU spreads them)
-  bool lanes_ok = true;     // depth-first lanes (cleared once a run met something they leave to the step machine)
+  // A run that the depth-first lanes leave to the step machine costs their time too: where that then answers it, the next
+  // lanes_skip evaluations do not try them, and twice as many after the next such run (other inputs may be theirs again).
+  uint32_t lanes_skip = 0, lanes_skip_next = LANES_SKIP;
+  static constexpr uint32_t LANES_SKIP = 8, LANES_SKIP_MOST = 1024;
   uint32_t max_dies = 8;    // tag machines a batch is dealt to (set to 1 after a part of the table overflowed)
   void* side_stream = nullptr;                     // hipStream_t for work beside the caller's stream
   void* fork_event = nullptr, *join_event = nullptr;   // embedding gradient beside the weight gradients

@@ -161,3 +161,33 @@ def test_max_tags_is_the_step_machines_limit(monkeypatch):
     got = [status(m) for m in (8, 64, 4096)]
     monkeypatch.setenv("TDF_NO_LANES", "1")
     assert got == [status(m) for m in (8, 64, 4096)] and got[0] == got[1] == tdf.ERR_TABLE_FULL
+
+
+def test_the_lanes_are_tried_again_after_a_call_they_left_to_the_step_machine():
+    # f(n) = if n < -5 then n else h(n, -5), h(a, b) = a + b: one argument of the call is dead below -5.  The lanes leave such
+    # a call to the step machine, and the next eight evaluations with it; then they have their turn again
+    T = tdf
+    h = [(T.OP_IN, [], 0), (T.OP_IN, [], 1), (T.OP_ADD, [(0, 0), (1, 0)], 0), (T.OP_OUT, [(2, 0)], 0)]
+    f = [(T.OP_IN, [], 0), (T.OP_CONST, [], -5), (T.OP_LT, [(0, 0), (1, 0)], 0), (T.OP_SWITCH, [(2, 0), (0, 0)], 0),
+         (T.OP_CALLFN, [(3, 1), (1, 0)], 2), (T.OP_ID, [(3, 0)], 0), (T.OP_MERGE, [(5, 0), (4, 0)], 0), (T.OP_OUT, [(6, 0)], 0)]
+    res = [(T.OP_IN, [], 0), (T.OP_CALLFN, [(0, 0)], 1), (T.OP_OUT, [(1, 0)], 0)]
+    g = tdf.graph_build([("result", 1, res), ("f", 1, f), ("h", 2, h)], 0)
+    good, bad = [(n,) for n in (3, 0, 9)], [(n,) for n in (3, -9, 9)]
+    want = lambda ns: [n if n < -5 else n - 5 for n, in ns]  # noqa: E731
+    for skipped in (8, 16):
+        out, _, repeats = _eval_int(g, bad, 1, 200)
+        assert out == want(bad) and repeats == 1
+        for _ in range(skipped):
+            out, _, repeats = _eval_int(g, bad, 1, 200)
+            assert out == want(bad) and repeats == 0        # (the step machine from the start)
+    out, _, repeats = _eval_int(g, bad, 1, 200)
+    assert out == want(bad) and repeats == 1
+    for _ in range(32):
+        _eval_int(g, good, 1, 200)
+    out, _, repeats = _eval_int(g, good, 1, 200)            # on the lanes, which makes eight of it again
+    assert out == want(good) and repeats == 0
+    out, _, repeats = _eval_int(g, bad, 1, 200)
+    assert repeats == 1
+    for _ in range(8):
+        assert _eval_int(g, bad, 1, 200)[2] == 0
+    assert _eval_int(g, bad, 1, 200)[2] == 1
