@@ -293,7 +293,7 @@ struct alignas(128) LaneCtl {   // zero on entry
   uint32_t queues_done;         // queues whose instances are done
   uint32_t status;              // 0, or -(tdf_status)
   uint32_t log_used;            // log entries reserved by the waves (starts at the chunks dealt to them)
-  uint32_t n_seg;               // stack segments used (starts at the number of lanes, which have one each)
+  uint32_t n_seg;               // stack segments handed out
   uint32_t leaf_next;           // rows given to leaves (after the run)
   uint32_t rows_done;           // workgroups through with the first pass over the log
   uint32_t beat;                // counted on by every wave that works, 32 times in LaneArgs::dead_ticks

@@ -78,7 +78,7 @@ struct Plan {
   Engine e{};
   VecArgs v{};
   bool vec = false, grad = false;
-  size_t off_ctrl, off_fire, off_frames, off_tail_sync, off_gcount = 0, off_stamps;
+  size_t off_ctrl, off_fire, off_frames, end_frames, off_tail_sync, off_gcount = 0, off_stamps;
   // embedding-gradient and bias-gradient scratch
   size_t off_tok_count, off_tok_fill, off_seg_off, off_chunk_off, off_sorted, off_de_part, off_db_part;
   uint32_t max_cells;
@@ -159,6 +159,7 @@ tdf_status make_plan(const Graph& G, const tdf_inputs* in, bool with_grad, char*
   L.zero_end = L.total;
   P.off_stamps = L.take(sizeof(unsigned long long) * 2 * TDF_PHASE_COUNT);
   P.off_frames = L.take((size_t)G.prog.frame_stride * ((size_t)e.cap + B));   // headers are written on insertion
+  P.end_frames = L.total;
   // --- the rest is written before it is read
   size_t off_prog = L.take(sizeof(DevProgram));
   size_t off_touched = L.take(sizeof(uint32_t) * 2 * (size_t)e.touched_cap * e.n_dies);
@@ -311,13 +312,22 @@ tdf_status make_plan(const Graph& G, const tdf_inputs* in, bool with_grad, char*
     a.n_queues = 1;
     while (a.n_queues < 64 && a.n_queues * 32 < a.n_waves) a.n_queues *= 2;
     a.queue_cap = pow2_at_least(2ull * ((a.n_waves + a.n_queues - 1) / a.n_queues) + 64);
-    // stack segments: one per lane, and room for as many frames as there may be tags
-    a.n_segs = a.n_waves * 64u + T / LANE_SEG + 64u;
-    const size_t off_ctl = L.take(sizeof(LaneCtl)), off_queues = L.take(sizeof(LaneQueue) * (size_t)a.n_queues);
-    const size_t off_totals = L.take(sizeof(LaneTotals));
-    const size_t off_mail = L.take(sizeof(LaneMail) * (size_t)a.queue_cap * a.n_queues);
-    const size_t off_reply = L.take(sizeof(LaneReply) * 64 * (size_t)a.n_waves);
-    const size_t off_segs = L.take((size_t)a.n_segs * lane_seg_units(P.n_stored) * 16);
+    // Stack segments: room for as many frames as there may be tags, and for one partly filled segment of every lane whose
+    // stack leaves the window of four frames (one for 16 tags: recursions of nine calls use one for 70, deeper ones less).
+    a.n_segs = std::min(a.n_waves * 64u, T / 16u) + T / LANE_SEG + 64u;
+    // The lanes keep no frames: what they need lies where the step machine's would, as far as that goes.
+    size_t inside = P.off_frames;
+    auto take_l = [&](size_t bytes) {
+      const size_t at_ = inside, next = inside + (bytes + 255) / 256 * 256;
+      if (next > P.end_frames) return L.take(bytes);
+      inside = next;
+      return at_;
+    };
+    const size_t off_ctl = take_l(sizeof(LaneCtl)), off_queues = take_l(sizeof(LaneQueue) * (size_t)a.n_queues);
+    const size_t off_totals = take_l(sizeof(LaneTotals));
+    const size_t off_mail = take_l(sizeof(LaneMail) * (size_t)a.queue_cap * a.n_queues);
+    const size_t off_reply = take_l(sizeof(LaneReply) * 64 * (size_t)a.n_waves);
+    const size_t off_segs = take_l((size_t)a.n_segs * lane_seg_units(P.n_stored) * 16);
     a.ctl = (LaneCtl*)at(off_ctl);
     a.queues = (LaneQueue*)at(off_queues);
     P.totals = (LaneTotals*)at(off_totals);
@@ -326,8 +336,8 @@ tdf_status make_plan(const Graph& G, const tdf_inputs* in, bool with_grad, char*
     a.segs = (uint4*)at(off_segs);
     if (P.vec) {   // (a wave goes on to its next chunk when its lanes need more than is left: less than half is)
       a.log_cap = 2 * T + LANE_CHUNK * (a.n_waves + 1);
-      const size_t off_log = L.take(sizeof(uint4) * (size_t)a.log_cap), off_names = L.take(4 * (size_t)a.log_cap);
-      const size_t off_marks = G.has_node_loss ? L.take(4 * (size_t)a.log_cap) : 0;
+      const size_t off_log = take_l(sizeof(uint4) * (size_t)a.log_cap), off_names = take_l(4 * (size_t)a.log_cap);
+      const size_t off_marks = G.has_node_loss ? take_l(4 * (size_t)a.log_cap) : 0;
       a.log = (uint4*)at(off_log);
       a.row_of = (uint32_t*)at(off_names);
       a.row_node = G.has_node_loss ? (uint32_t*)at(off_marks) : nullptr;

@@ -98,7 +98,6 @@ __device__ inline void lane_init(const LaneArgs& a, uint32_t i, uint32_t n) {
   if (i == 0) {
     *a.ctl = LaneCtl{};
     a.ctl->log_used = a.log_cap ? a.n_waves * LANE_CHUNK : 0u;
-    a.ctl->n_seg = a.n_waves * 64u;
   }
   if (i < a.n_queues) a.queues[i] = LaneQueue{};
   for (uint32_t k = i; k < a.n_queues * a.queue_cap; k += n) a.mail[k].flag = lane_slot(0u, a.queue_cap, LANE_EMPTY);
@@ -343,7 +342,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
   // frames have a ready call left.  (The first frame of an empty stack has number 0: bs is reset then.)
   bool active = false;
   uint32_t sp = 0, bs = 0, lo = 0, slack = 0, seg = LANE_NONE, seg_b = LANE_NONE;
-  uint32_t spare = wave * 64u + lane;     // segments the lane has and does not use (a list); it starts with one
+  uint32_t spare = LANE_NONE;             // segments the lane has and does not use (a list)
   // The bottom frame (frame bs, or the one in registers if the stack is empty): its record, if it has one, and
   // its caller: a record, a call from another wave, or none.
   uint32_t rec = LANE_NONE, parent = LANE_NONE;
@@ -360,7 +359,6 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
   // several waves share a recursion the last two lanes do that and nothing else.
   const unsigned long long exporter = a.n_waves > 1 && SW::kBranching ? 3ull << 62 : 0ull;
   for (uint32_t k = lane; k < LANE_RECS; k += 64) lfree[k] = k;
-  a.segs[(size_t)spare * lane_seg_units(NS)].x = LANE_NONE;
 
   auto seg_at = [&](uint32_t id) { return a.segs + (size_t)id * lane_seg_units(NS); };
   auto win_put = [&](uint32_t d, const uint4 (&c)[NC]) {
@@ -387,7 +385,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     else id = lane_add(&ctl->n_seg, 1u);
     if (id >= a.n_segs) {
       x.bad = TDF_ERR_TABLE_FULL;
-      id = wave * 64u + lane;   // (its contents do not count any more)
+      id = 0;   // (its contents do not count any more)
     }
     return id;
   };

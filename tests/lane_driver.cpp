@@ -42,7 +42,7 @@ int main() {
   a.per_grab = (uint32_t)num("per_grab", max(1u, min(64u, (a.n_inst + a.n_waves - 1) / a.n_waves)));
   a.n_queues = (uint32_t)num("queues", 1);
   a.queue_cap = (uint32_t)num("queue_cap", 128);
-  a.n_segs = a.n_waves * 64u + (uint32_t)num("segs", 4096);
+  a.n_segs = (uint32_t)num("segs", 1 << 16);
   a.log_cap = (uint32_t)num("log_cap", 0);
   a.vocab = (int32_t)num("vocab", 0);
   a.idle_ticks = num("idle_ticks", 1ll << 40);

@@ -252,3 +252,17 @@ def test_malformed_loops_are_rejected():
     build(head + [(T.OP_LOOP, [n, zero], 1), (T.OP_OUT, [(2, 0)], 0)], two_next)           # two NEXT nodes
     short_next = [(op, ins[:1], imm) if op == T.OP_NEXT else (op, ins, imm) for op, ins, imm in good_loop]
     build(head + [(T.OP_LOOP, [n, zero], 1), (T.OP_OUT, [(2, 0)], 0)], short_next)         # NEXT without a value for a variable
+
+
+@pytest.mark.parametrize("case", ["small_recursions", "large_recursion", "loops", "trees", "node_losses"])
+def test_the_lanes_need_no_memory_beside_the_step_machines(case):
+    # (statistics level 0 adds the ring of frames given back, 4 bytes a frame record of 64 bytes or more)
+    tree = dict(n_instances=400, n_args=2, max_tags=52000, hidden=128, vocab=2000, n_classes=5, dtype=tdf.BF16)
+    prog, grad, k = {"small_recursions": (programs.fib(), False, dict(n_instances=4096, n_args=1, max_tags=67000)),
+                     "large_recursion": (programs.fib(), False, dict(n_instances=3, n_args=1, max_tags=14000000)),
+                     "loops": (programs.gcd_loop(), False, dict(n_instances=65536, n_args=2, max_tags=2200000)),
+                     "trees": (programs.tree("lstm", True), True, tree),
+                     "node_losses": (programs.tree("rnn", node_loss=True), True, dict(tree, n_args=1))}[case]
+    g = tdf.graph_build(*prog, want_grad=grad)
+    with_lanes, without = (tdf.workspace_size(g, tdf.make_inputs(stats_level=level, **k), grad) for level in (0, 1))
+    assert with_lanes <= 1.07 * without, (with_lanes, without)
