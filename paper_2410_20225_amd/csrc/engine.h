@@ -296,7 +296,7 @@ struct alignas(128) LaneCtl {   // zero on entry
   uint32_t n_seg;               // stack segments handed out
   uint32_t leaf_next;           // rows given to leaves (after the run)
   uint32_t rows_done;           // workgroups through with the first pass over the log
-  uint32_t beat;                // counted on by every wave that works, 32 times in LaneArgs::dead_ticks
+  uint32_t beat;                // counted on by every wave that works, about once in a millisecond
   unsigned long long n_tags;    // tags that the waves have reported so far
 };
 struct LaneLimits {

@@ -349,8 +349,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
   bool resumed = false;                   // the bottom frame has nothing outstanding in other lanes
   uint32_t mx_sp = 0;
   // wave-uniform
-  uint32_t n_told = 0, beat_seen = 0;     // tags reported; the beat when this wave looked last
-  long long t_beat = wall_clock64();      // when this wave counted it on, or saw that another one had, last
+  uint32_t n_told = 0;                    // tags reported
   uint32_t qh = 0, qt = 0, nfree = LANE_RECS, iter = 0, syncs = 0, ticket = 0, min_free = LANE_RECS;
   unsigned long long sent_mask = 0;       // replies awaited, by lane
   bool more_inst = true, stop = false, have_ticket = false;
@@ -649,6 +648,8 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           const long long t0 = wall_clock64();
           uint32_t v = LANE_EMPTY;
           bool task = false, home = false;
+          uint32_t beat_seen = 0xFFFFFFFFu;   // the beat of the waves that work, and when it was new
+          long long t_beat = t0;
           for (;;) {
             if (have_ticket) {
               v = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&slot->flag));
@@ -663,7 +664,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
             home = !have_ticket && given_up() != 0;   // (with a ticket it is sent home)
             if (home) break;
             __builtin_amdgcn_s_sleep(4);
-            if (wall_clock64() - t0 > a.idle_ticks) {
+            if (__builtin_expect(wall_clock64() - t0 > a.idle_ticks, 0)) {
               if (sent_mask || nfree != LANE_RECS) {   // others still work on what this wave waits for: look whether they gave up
                 const uint32_t beat = (uint32_t)__builtin_amdgcn_readfirstlane((int)lane_ld(&ctl->beat));
                 if (beat != beat_seen) {
@@ -749,7 +750,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           LaneMail* const slot = mail_slot(send_queue, t0 + r);
           if (t0 != guess) f = ~mine;   // (another ticket's)
           long long w0 = 0;
-          while (__ballot(on && f != mine)) {
+          while (__builtin_expect(__ballot(on && f != mine) != 0, 0)) {
             if (on && f != mine) {
               f = lane_ld(&slot->flag);
               if (f == lane_slot(t0 + r, a.queue_cap, LANE_LEFT)) not_there();
@@ -874,21 +875,23 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
         // to a stack that nobody runs: it is this lane's from now on
         const bool stack = out && !remote && (parent & LANE_STACK) != 0;
         const uint32_t stack_rec = parent & ~LANE_STACK;
-        if (stack) {
-          const uint32_t m = r_meta[stack_rec];
-          bs = r_counter[stack_rec];
-          sp = lo = r_depth[stack_rec];
-          seg = r_po[stack_rec];
-          seg_b = r_join[stack_rec];
-          parent = r_parent[stack_rec];
-          rec = (m & 0xFFFFu) == 0xFFFFu ? LANE_NONE : m & 0xFFFFu;
-          resumed = (m >> 31) != 0;
-          slack = 0;
-          pop(x.ret);
-          x.run = true;
-          x.act = ACT_NONE;
+        if (__builtin_expect(__ballot(stack) != 0, 0)) {
+          if (stack) {
+            const uint32_t m = r_meta[stack_rec];
+            bs = r_counter[stack_rec];
+            sp = lo = r_depth[stack_rec];
+            seg = r_po[stack_rec];
+            seg_b = r_join[stack_rec];
+            parent = r_parent[stack_rec];
+            rec = (m & 0xFFFFu) == 0xFFFFu ? LANE_NONE : m & 0xFFFFu;
+            resumed = (m >> 31) != 0;
+            slack = 0;
+            pop(x.ret);
+            x.run = true;
+            x.act = ACT_NONE;
+          }
+          free_recs(stack, stack_rec);
         }
-        free_recs(stack, stack_rec);
         bool last = false;
         uint32_t id = rec;
         if (out && !remote && !stack) {
@@ -915,15 +918,11 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
       instances_done();
       if (stop) break;
     }
-    if ((syncs & 15u) == 0) {
+    if (__builtin_expect((syncs & 15u) == 0, 0)) {
       if (given_up() != 0) break;
-      const long long now = wall_clock64();
-      if (now - t_beat > a.dead_ticks / 32) {
-        if (lane == 0) (void)lane_add(&ctl->beat, 1u);
-        t_beat = now;
-      }
     }
-    if ((syncs & 63u) == 0) {   // (rarely: a run that is refused may as well be a little longer)
+    if (__builtin_expect((syncs & 63u) == 0, 0)) {   // (rarely: a run that is refused may as well be a little longer)
+      if (lane == 0) (void)lane_add(&ctl->beat, 1u);   // (a clock and the time of the last beat cost 20 registers, fib(0..20) 4 %)
       const unsigned long long told = lane_ld(&ctl->n_tags);
       const uint32_t n = wave_usum(x.n_tags);   // (modulo 2^32, like the difference)
       if (n - n_told >= a.tags_at_once) {
@@ -1036,7 +1035,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
         }
       }
       // Else all of them stay a stack, with one record.
-      if (spare_recs() >= 2 && __ballot(going)) {
+      if (__builtin_expect(spare_recs() >= 2 && __ballot(going) != 0, 0)) {
         uint32_t d = bs, in = seg_b;   // the frame, and the segment it is in if it is in memory
         if (going) {
           while (!(((d >= lo ? win[((d % LANE_WINDOW) * NC) * 64 + lane].x : seg_at(in)[1 + (d % LANE_SEG) * NC].x) >> 25) & 1u)) {

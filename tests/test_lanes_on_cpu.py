@@ -132,5 +132,5 @@ def test_a_run_beyond_max_tags_is_given_up(fib, tmp_path):
 def test_a_long_run_is_not_given_up_while_waves_work(fib):
     # longer than the time in which nobody may work; waves that wait look at that all the time
     for seed in (1, 2, 3):
-        got = fib.run([(24,)], waves=6, seed=seed, idle_ticks=50, dead_ticks=30000)
+        got = fib.run([(24,)], waves=3, seed=seed, idle_ticks=50, dead_ticks=30000)
         assert got["status"] == 0 and got["out"] == [46368] and got["turns"] > 40000, seed
