@@ -1,5 +1,7 @@
 """The depth-first lanes on the CPU: the library prints the code that it generates for a program (no GPU is needed for
 that), tests/lane_driver.cpp is compiled with it, and the waves run as fibers that take turns at random places."""
+import concurrent.futures
+import json
 import os
 import platform
 import shutil
@@ -23,13 +25,26 @@ tdf.graph_precompile(tdf.graph_build(fns, r, want_grad=grad))
 """
 
 
-def lane_source(prog, want_grad=False):
-    """The generated lanes of a program, as the library compiles them."""
-    import json
-    env = dict(os.environ, TDF_JIT_DUMP="1")
-    res = subprocess.run([sys.executable, "-c", _DUMP % ROOT], input=json.dumps([*prog, want_grad]), capture_output=True, text=True, env=env)
+def _lane_source(job):
+    res = subprocess.run([sys.executable, "-c", _DUMP % ROOT], input=job, capture_output=True, text=True, env=dict(os.environ, TDF_JIT_DUMP="1"))
     assert res.returncode == 0, res.stderr[-2000:]
     return res.stderr[res.stderr.index('#include "lane_device.h"'):]
+
+
+_pool = concurrent.futures.ThreadPoolExecutor(6)
+_sources = {}   # by program: the library compiles what it prints, which takes some seconds a program
+
+
+def prefetch(prog, want_grad=False):
+    job = json.dumps([*prog, want_grad])
+    if job not in _sources:
+        _sources[job] = _pool.submit(_lane_source, job)
+    return _sources[job]
+
+
+def lane_source(prog, want_grad=False):
+    """The generated lanes of a program, as the library compiles them."""
+    return prefetch(prog, want_grad).result()
 
 
 class Lanes:
@@ -58,11 +73,3 @@ class Lanes:
                 out[k] = out[k][0]
         assert "hung" not in out, "the lanes do not come to an end"
         return out
-
-
-def lanes_fixture(prog):
-    """A module-scoped fixture: the lanes of prog(), compiled once."""
-    @pytest.fixture(scope="module")
-    def lanes(tmp_path_factory):
-        return Lanes(prog(), tmp_path_factory.mktemp("lanes"))
-    return lanes

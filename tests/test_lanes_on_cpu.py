@@ -4,7 +4,7 @@ import pytest
 
 import oracle
 from oracle import programs as oprog
-from lane_cpu import Lanes, needs_host_lanes
+from lane_cpu import Lanes, needs_host_lanes, prefetch
 from lane_programs import BAD_INDEX, INTEGER, VECTOR, fib_below_a_chain, fibs_along_a_chain
 
 pytestmark = needs_host_lanes
@@ -17,6 +17,12 @@ INT = {
     "gcd": (programs.gcd_loop, oprog.gcd_loop_program, [(a, b) for a in range(1, 20) for b in range(1, 8)]),
     "loop_of_calls": (programs.loop_of_calls, oprog.loop_of_calls_program, [(n,) for n in (0, 1, 3, 9, 12)]),
 }
+
+
+@pytest.fixture(scope="module", autouse=True)
+def all_sources():
+    for p in [v[0]() for v in INT.values()] + [v()[0] for t in (VECTOR, INTEGER, BAD_INDEX) for v in t.values()]:
+        prefetch(p)
 
 
 @pytest.mark.parametrize("name", list(INT))
@@ -134,3 +140,43 @@ def test_a_long_run_is_not_given_up_while_waves_work(fib):
     for seed in (1, 2, 3):
         got = fib.run([(24,)], waves=3, seed=seed, idle_ticks=50, dead_ticks=30000)
         assert got["status"] == 0 and got["out"] == [46368] and got["turns"] > 40000, seed
+
+
+@pytest.mark.parametrize("node_loss", [False, True], ids=["roots", "node_losses"])
+def test_the_schedule_of_tree_networks(node_loss, tmp_path):
+    # chains of leaf-sided nodes above random trees: every cell of the log names the rows of its node's children, its level
+    # is one above theirs, and with a loss term at every node every row is marked with its node
+    import random
+    rng = random.Random(3)
+    left, right, token, roots = [], [], [], []
+
+    def node(n, chain):
+        v = len(left)
+        left.append(-1), right.append(-1), token.append(rng.randrange(50))
+        if n > 1:
+            k = 1 if chain else rng.randrange(1, n)
+            first = node(n - k, chain - 1 if chain else 0)
+            second = node(k, 0)
+            left[v], right[v] = (first, second) if chain % 2 else (second, first)
+        return v
+
+    for n, chain in [(1, 0), (2, 0), (140, 90), (40, 0), (130, 125), (60, 0), (17, 16), (64, 3)] * 2:
+        roots.append(node(n, chain))
+    lanes = Lanes(programs.tree("rnn", node_loss=node_loss), tmp_path)
+    for waves, seed in [(1, 1), (6, 2), (20, 3)]:
+        got = lanes.run([(v,) for v in roots], waves=waves, seed=seed, log_cap=16384, vocab=50, left=left, right=right, token=token,
+                        node_loss=int(node_loss))
+        n_leaf = sum(x < 0 for x in left)
+        assert got["status"] == 0 and got["tags"] == len(left) and got["leaves"] == n_leaf and got["cells"] == len(left) - n_leaf
+        log = [got["log"][k:k + 4] for k in range(0, len(got["log"]), 4)]
+
+        def check(name, v, b):
+            x, y, level, inst = log[name]
+            assert inst == b and (not node_loss or got["marks"][name] == v)
+            if left[v] < 0:
+                assert (x, level) == (token[v], 0)
+                return 0
+            assert level == 1 + max(check(x, left[v], b), check(y, right[v], b))
+            return level
+        for b, v in enumerate(roots):
+            check(got["root"][b], v, b)
