@@ -269,9 +269,13 @@ def main():
                      "how": "one host thread, graph, workspace and stream per evaluation in flight; the library runs an "
                             "evaluation's tag machine (which depends on the trees only) beside the previous evaluation's "
                             "data plane; every evaluation is complete"}
+    # which tag phase it was: the depth-first lanes are two launches, the step machine two and more per round
+    on_lanes = int(st.phase_launches[0]) == 2
     # one more evaluation, outside the timed region, with the tag machines' step records switched on
     widest = []
-    if cfg in (1, 6):
+    if on_lanes:
+        pass
+    elif cfg in (1, 6):
         inp.stats_level = 2
         ws = torch.empty(tdf.workspace_size(g, inp), dtype=torch.uint8, device=dev)
         st2 = step()
@@ -279,7 +283,7 @@ def main():
         run.inputs.stats_level = 2
         run.ws = torch.empty(tdf.workspace_size(run.graph, run.inputs, run.grad), dtype=torch.uint8, device=dev)
         st2 = step()
-    for k in range(8):
+    for k in range(0 if on_lanes else 8):
         if st2.wide_step_frames[k] > 0 and st2.wide_step_us[k] > 0:
             fr, cr, us = int(st2.wide_step_frames[k]), int(st2.wide_step_created[k]), float(st2.wide_step_us[k])
             widest.append({"frames": fr, "tags_created": cr, "us": round(us, 2),
@@ -288,18 +292,24 @@ def main():
     value = firings * a.steps / dt
     phase_ms = {n: round(float(p) / a.steps, 4) for n, p in zip(tdf.PHASES, phase)}
 
-    # tag machine: algorithmic bytes per tag of matching + compaction (table entry and frame record
-    # written, frame read on return, operand slot, arrival word, ready id, schedule-log entry): 72 B
-    tag_bytes = 72.0 * n_tags
     tag_ms = phase[0] / a.steps
-    roof_tags = {"bound": "hbm", "kernel": "tag machine step kernels (all steps)",
-                 "achieved": tag_bytes / (tag_ms * 1e-3) / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s",
-                 "launches_per_step": launches[0] / a.steps, "traffic": measured_traffic(cfg, "steps")}
+    if on_lanes:
+        # What the phase cannot do without: arguments and results; for trees the forest (12 B a node) and the schedule
+        # (16 B a leaf or cell).  What bounds it is the chain of dependent calls, not these bytes.
+        tag_bytes = (8.0 * (len(ns) * 2 if cfg == 1 else n_inst * 3) if cfg in (1, 6) else
+                     12.0 * c["forest"].n_nodes + 16.0 * int(st.n_leaf_rows + st.n_cell_rows) + 8.0 * 2 * B)
+        roof_tags = {"bound": "latency", "kernel": "depth-first lanes (one launch)", "tags_per_us": n_tags / (tag_ms * 1e3)}
+    else:
+        # step machine: algorithmic bytes per tag of matching + compaction (table entry and frame record
+        # written, frame read on return, operand slot, arrival word, ready id, schedule-log entry): 72 B
+        tag_bytes = 72.0 * n_tags
+        roof_tags = {"bound": "hbm", "kernel": "tag machine step kernels (all steps)", "traffic": measured_traffic(cfg, "steps")}
+        # the widest steps of a single tag machine (one of up to eight running side by side): frames that
+        # received a token, tags the step created, duration; useful bytes = 72 B per tag created
+        roof_tags["widest_steps_of_one_machine"] = widest
+    roof_tags.update(achieved=tag_bytes / (tag_ms * 1e-3) / 1e9, peak=PEAK_HBM / 1e9, unit="GB/s", launches_per_step=launches[0] / a.steps)
     roof_tags["frac"] = roof_tags["achieved"] / roof_tags["peak"]
     roof_tags["copy_kernel_GBps"] = copy_gbps   # measured read + write rate of a plain 1 GiB device copy
-    # the widest steps of a single tag machine (one of up to eight running side by side): frames that
-    # received a token, tags the step created, duration; useful bytes = 72 B per tag created
-    roof_tags["widest_steps_of_one_machine"] = widest
     if cfg in (1, 6):
         roof = roof_tags
     else:
