@@ -209,10 +209,14 @@ typedef struct {
   int64_t max_tags;   /* capacity in call-context tags (= invocations and loop iterations).
                          tdf_eval of a program without vector operators with stats_level 0
                          gives a frame back when its tag has finished (Section 5.1: Return_i
-                         deallocates), and max_tags bounds the tags alive at once; in every
+                         deallocates), and max_tags bounds the tags alive at once, in the
+                         order in which the step machine fires them; in every
                          other case all frames are kept and it bounds all tags of the call */
-  int32_t step_limit; /* 0 = default (1<<20)                                            */
-  int32_t stats_level; /* 0: counters and phase times; 1: also tdf_stats.fire_count (one
+  int32_t step_limit; /* steps of the step machine; 0 = default (1<<20).  With another value
+                         the evaluation runs on it                                       */
+  int32_t stats_level; /* 0: counters and phase times; an evaluation with no more tags than
+                          max_tags may run on the depth-first lanes, which keep no frames, any
+                          other one runs on the step machine; 1: also tdf_stats.fire_count (one
                           extra pass over the frame table after the evaluation); 2: also the
                           size and duration of the tag machines' widest steps              */
 } tdf_inputs;
@@ -243,9 +247,9 @@ typedef struct {
 
 /* Phases of one evaluation, timed by the clock that the first kernel of each phase reads. */
 enum {
-  TDF_PHASE_TAGS = 0,    /* tag machine: clear, seed, all match/fire steps                 */
-  TDF_PHASE_LEAVES,      /* weight packing and EMBED rows (gradient runs write the rows on
-                            a stream of their own, beside the level sort: outside this bracket) */
+  TDF_PHASE_TAGS = 0,    /* the step machine (clear, seed, all match/fire steps) or the lanes
+                            (clear and weight packing, the lanes: two launches)            */
+  TDF_PHASE_LEAVES,      /* EMBED rows (after the step machine: and weight packing)        */
   TDF_PHASE_LEVELS,      /* bucketing of the cell firings by dependency level              */
   TDF_PHASE_CELLS_FWD,   /* cell GEMMs of the wide levels, one launch per level            */
   TDF_PHASE_HEAD,        /* head / result rows / gradient seeds                            */
@@ -260,7 +264,8 @@ enum {
 
 typedef struct {
   int64_t n_tags;         /* tags created = function invocations + loop iterations      */
-  int64_t n_steps;        /* match/fire steps of the tag machine                        */
+  int64_t n_steps;        /* match/fire steps of the tag machine; on the lanes the most sweeps
+                             of one of their waves                                      */
   int64_t n_tokens;       /* Call and Return tokens delivered                           */
   int64_t n_leaf_rows;    /* EMBED firings                                              */
   int64_t n_cell_rows;    /* RNN_CELL / LSTM_CELL firings                               */
@@ -275,8 +280,11 @@ typedef struct {
   int64_t table_capacity; /* frame records the machines could hand out (all parts)      */
   int64_t max_probe;      /* accesses to find a tag's frame: 1 (the match table has no collisions) */
   int64_t peak_frames;    /* frame records ever handed out: with frames given back, the largest
-                             number of tags alive at once (summed over the machines)    */
-  int64_t frames_reclaimed; /* 1: frames were given back as their tags finished        */
+                             number of tags alive at once (summed over the machines); on the lanes
+                             the records in use at once and the frames on a lane's stack, the
+                             largest number of every wave and lane summed, n_tags at most */
+  int64_t frames_reclaimed; /* 1: frames were given back as their tags finished (always so on
+                             the lanes)                                                */
   double phase_ms[TDF_PHASE_COUNT];        /* device time of each phase                */
   int64_t phase_launches[TDF_PHASE_COUNT]; /* kernel launches of each phase            */
   double fwd_cells_span_ms; /* first launch to last end of the forward cell kernels, over both
@@ -292,10 +300,13 @@ typedef struct {
   int32_t n_machines;     /* independent tag machines the batch was dealt to (1, 2, 4, 8) */
   int32_t die_local;      /* 1: every machine kept to one accelerator die, atomics in its L2;
                              0: device-scope kernels                                    */
-  int32_t generated;      /* 1: step kernels generated for this program at run time; 0: the
-                             table interpreter                                          */
-  int32_t repeats;        /* runs that were discarded and repeated inside this call (a part of
-                             the tag table overflowed, or die-private kernels left their die) */
+  int32_t generated;      /* 1: step kernels (or lanes) generated for this program at run time;
+                             0: the table interpreter                                   */
+  int32_t repeats;        /* runs that were discarded and repeated inside this call: a part of
+                             the tag table overflowed, die-private kernels left their die, the
+                             lanes left the evaluation to the step machine (more tags than
+                             max_tags, a call with some arguments dead), or the workgroups of a
+                             chain launch could not all start in time                    */
   int32_t tail_used;      /* 1: narrow levels ran in one launch per pass                */
   int32_t deep_split;     /* 1: the deep instances (root level >= 32) ran apart from the others,
                              all their levels in one launch per pass; 2: ... on a second

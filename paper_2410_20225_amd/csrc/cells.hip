@@ -1146,7 +1146,7 @@ __global__ void __launch_bounds__(256) k_dz(VecArgs v, Engine e, uint32_t q0, ui
 // cell depends only on cells of its own instance.  So each die can walk the levels on its own:
 // workgroups i, i + 8, ... of the launch take the tiles of machine i % 8's cells, level after
 // level, with a barrier among themselves (die_sync.h) where a launch boundary would be.  Used
-// for the deep levels, where a level is a few tiles per die and costs one barrier (~2 us)
+// for the deep levels, where a level is a few tiles per die and costs one barrier (about 1 us)
 // instead of one launch (~10 us).
 struct TailArgs {
   const uint32_t* level_off;   // first cell of (level, machine) in the sorted log, by sort key
