@@ -1,12 +1,12 @@
-"""The depth-first lanes on the CPU: the library prints the code that it generates for a program (no GPU is needed for
-that), tests/lane_driver.cpp is compiled with it, and the waves run as fibers that take turns at random places."""
-import concurrent.futures
-import json
+"""The depth-first lanes on the CPU: tests/lane_source.cpp prints the code that the library generates for a program,
+tests/lane_driver.cpp is compiled with it, and the waves run as fibers that take turns at random places."""
+import atexit
+import functools
 import os
 import platform
 import shutil
 import subprocess
-import sys
+import tempfile
 
 import pytest
 
@@ -15,45 +15,36 @@ CSRC = os.path.join(ROOT, "paper_2410_20225_amd", "csrc")
 
 needs_host_lanes = pytest.mark.skipif(not shutil.which("g++") or platform.machine() != "x86_64", reason="needs g++ on x86-64")
 
-_DUMP = """
-import json, sys
-sys.path.insert(0, %r)
-from paper_2410_20225_amd import tdf
-fns, r, grad = json.load(sys.stdin)
-fns = [(n, p, [(op, [tuple(i) for i in ins], imm) for op, ins, imm in nodes]) for n, p, nodes in fns]
-tdf.graph_precompile(tdf.graph_build(fns, r, want_grad=grad))
-"""
+@functools.lru_cache(maxsize=None)
+def _generator():
+    """tests/lane_source.cpp, built once."""
+    folder = tempfile.mkdtemp(prefix="lane_source")
+    atexit.register(shutil.rmtree, folder, ignore_errors=True)
+    exe = os.path.join(folder, "lane_source")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "lane_source.cpp"), os.path.join(CSRC, "graph_build.cpp"),
+                    "-L/opt/rocm/lib", "-lamdhip64", "-ldl", "-Wl,-rpath,/opt/rocm/lib", "-o", exe], check=True)
+    return exe
 
 
-def _lane_source(job):
-    res = subprocess.run([sys.executable, "-c", _DUMP % ROOT], input=job, capture_output=True, text=True, env=dict(os.environ, TDF_JIT_DUMP="1"))
-    assert res.returncode == 0, res.stderr[-2000:]
-    return res.stderr[res.stderr.index('#include "lane_device.h"'):]
-
-
-_pool = concurrent.futures.ThreadPoolExecutor(6)
-_sources = {}   # by program: the library compiles what it prints, which takes some seconds a program
-
-
-def prefetch(prog, want_grad=False):
-    job = json.dumps([*prog, want_grad])
-    if job not in _sources:
-        _sources[job] = _pool.submit(_lane_source, job)
-    return _sources[job]
-
-
-def lane_source(prog, want_grad=False):
-    """The generated lanes of a program, as the library compiles them."""
-    return prefetch(prog, want_grad).result()
+def lane_source(prog):
+    """The generated lanes of a program, as the library compiles them; None if it is no program or none of the lanes'."""
+    fns, result = prog
+    text = "%d %d\n" % (len(fns), result)
+    for _, n_params, nodes in fns:
+        text += "%d %d\n" % (n_params, len(nodes))
+        text += "".join("%d %d %d %s\n" % (op, imm, len(ins), " ".join("%d %d" % tuple(r) for r in ins)) for op, ins, imm in nodes)
+    res = subprocess.run([_generator()], input=text, capture_output=True, text=True)
+    assert res.returncode in (0, 2, 3), res.stderr[-500:]
+    return res.stdout if res.returncode == 0 else None
 
 
 class Lanes:
-    def __init__(self, prog, folder, defines=()):
-        self.source = lane_source(prog)
+    def __init__(self, prog, folder, optimise="-O1", source=None):
         with open(os.path.join(folder, "generated.inc"), "w") as f:
-            f.write(self.source)
+            f.write(source or lane_source(prog))
         self.exe = os.path.join(folder, "lanes")
-        subprocess.run(["g++", "-std=c++17", "-O1", "-w", *("-D" + d for d in defines), "-I", str(folder), "-I", CSRC,
+        subprocess.run(["g++", "-std=c++17", optimise, "-w", "-I", str(folder), "-I", CSRC,
                         "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "tests"),
                         os.path.join(ROOT, "tests", "lane_driver.cpp"), "-o", self.exe], check=True)
 

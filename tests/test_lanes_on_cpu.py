@@ -4,7 +4,8 @@ import pytest
 
 import oracle
 from oracle import programs as oprog
-from lane_cpu import Lanes, needs_host_lanes, prefetch
+import lane_random
+from lane_cpu import Lanes, lane_source, needs_host_lanes
 from lane_programs import BAD_INDEX, INTEGER, VECTOR, fib_below_a_chain, fibs_along_a_chain
 
 pytestmark = needs_host_lanes
@@ -17,12 +18,6 @@ INT = {
     "gcd": (programs.gcd_loop, oprog.gcd_loop_program, [(a, b) for a in range(1, 20) for b in range(1, 8)]),
     "loop_of_calls": (programs.loop_of_calls, oprog.loop_of_calls_program, [(n,) for n in (0, 1, 3, 9, 12)]),
 }
-
-
-@pytest.fixture(scope="module", autouse=True)
-def all_sources():
-    for p in [v[0]() for v in INT.values()] + [v()[0] for t in (VECTOR, INTEGER, BAD_INDEX) for v in t.values()]:
-        prefetch(p)
 
 
 @pytest.mark.parametrize("name", list(INT))
@@ -180,3 +175,45 @@ def test_the_schedule_of_tree_networks(node_loss, tmp_path):
             return level
         for b, v in enumerate(roots):
             check(got["root"][b], v, b)
+
+
+def _random_case(seed):
+    """What went wrong with the program of a seed, or None; whether it was one of the lanes' at all."""
+    import random
+    import tempfile
+    rng = random.Random(seed)
+    vector = seed % 2 == 1
+    F, prog = lane_random.forest(rng), lane_random.program(rng, vector)
+    source = lane_source(prog)
+    cases = []
+    for _ in range(40):
+        args = (rng.randrange(12), rng.randint(-1, 9), rng.randint(-4, 9))
+        try:
+            cases.append((args, lane_random.evaluate(prog, F, args)))
+        except lane_random.Skip:
+            pass
+    if source is None or not cases:
+        return None, False
+    with tempfile.TemporaryDirectory() as folder:
+        lanes = Lanes(prog, folder, "-O0", source)
+        for waves in (1, 3):
+            got = lanes.run([a for a, _ in cases], waves=waves, log_cap=200000, vocab=9, **F)
+            if got["status"] != 0 or [got[k] for k in ("tags", "leaves", "cells")] != [sum(r[i] for _, r in cases) for i in (1, 2, 3)]:
+                return (seed, waves, "status or counts", {k: got[k] for k in ("status", "tags", "leaves", "cells")}), True
+
+            def same(name, v):
+                x, y, level, _ = got["log"][4 * name:4 * name + 4]
+                return level == 0 and x == v[1] if v[0] == "E" else level > 0 and same(x, v[1]) and same(y, v[2])
+            for k, (a, r) in enumerate(cases):
+                if not (same(got["root"][k], r[0]) if vector else got["out"][k] == r[0]):
+                    return (seed, waves, a), True
+    return None, True
+
+
+def test_random_programs():
+    from concurrent.futures import ThreadPoolExecutor
+    lane_source(programs.fib())   # (builds the generator before the threads use it)
+    with ThreadPoolExecutor(6) as pool:
+        results = list(pool.map(_random_case, range(48)))
+    assert [r for r, _ in results if r] == []
+    assert sum(ran for _, ran in results) >= 24   # (the others are too large, or none of the lanes')
