@@ -31,10 +31,9 @@ COPY_BYTES = 1 << 30    # calibration copy: 1 GiB read + 1 GiB written
 
 # HBM bytes per evaluation from the FETCH_SIZE / WRITE_SIZE counter passes (see
 # profiles/bench_workload4_hbm_traffic.md), with the hash of the kernel source they were taken on:
-# reported as `traffic` only while that source is unchanged.  (The passes over the tag phase were taken on the
-# step machine; the timed evaluations run on the depth-first lanes, which have none.)
+# reported as `traffic` only while that source is unchanged.
 MEASURED_TRAFFIC = {
-    4: {"cells": ("paper_2410_20225_amd/csrc/cells.hip", "dda69c6299073a74", 1925062852.9)},
+    4: {"cells": ("paper_2410_20225_amd/csrc/cells.hip", "dd47d3509a6464be", 1917841557.3)},
 }
 
 
