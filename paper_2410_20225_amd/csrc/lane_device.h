@@ -378,13 +378,14 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     seg_at(id)[0].x = spare;
     spare = id;
   };
+  // LANE_NONE if there is none left: the caller then leaves everything as it is, and the run ends before anybody goes on
   auto new_seg = [&]() -> uint32_t {
     uint32_t id = spare;
     if (id != LANE_NONE) spare = seg_at(id)[0].x;
     else id = lane_add(&ctl->n_seg, 1u);
     if (id >= a.n_segs) {
       x.bad = TDF_ERR_TABLE_FULL;
-      id = 0;   // (its contents do not count any more)
+      id = LANE_NONE;
     }
     return id;
   };
@@ -392,6 +393,10 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
   auto evict = [&]() {
     if (lo % LANE_SEG == 0 || seg == LANE_NONE) {
       const uint32_t id = new_seg();
+      if (id == LANE_NONE) {
+        x.run = false;   // (the lane's stack is not whole any more)
+        return;
+      }
       seg_at(id)[0].x = seg;
       if (seg != LANE_NONE) seg_at(seg)[0].y = id;
       if (seg_b == LANE_NONE) seg_b = id;
@@ -1056,7 +1061,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
           const uint32_t s_id = lfree[nfree - 2 - before];   // (a frame above others is fresh)
           uint32_t top = seg, bottom = seg_b;   // the stack's segments
           if (d >= lo) {   // in the window, like all frames above it
-            while (lo < d) evict();
+            while (lo < d && x.bad == 0) evict();
             top = seg;
             bottom = seg_b;
           } else if (d % LANE_SEG == 0) {
@@ -1067,10 +1072,12 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
               const bool all = d / LANE_SEG == bs / LANE_SEG;
               const uint32_t under = all ? LANE_NONE : seg_at(in)[0].x;
               top = new_seg();
-              seg_at(top)[0].x = under;
-              if (all) bottom = top;
-              else seg_at(under)[0].y = top;
-              for (uint32_t k = all ? bs % LANE_SEG : 0u; k < d % LANE_SEG; ++k) {
+              if (top != LANE_NONE) {
+                seg_at(top)[0].x = under;
+                if (all) bottom = top;
+                else seg_at(under)[0].y = top;
+              }
+              for (uint32_t k = all ? bs % LANE_SEG : 0u; top != LANE_NONE && k < d % LANE_SEG; ++k) {
 #pragma unroll
                 for (int j = 0; j < NC; ++j) seg_at(top)[1 + k * NC + j] = seg_at(in)[1 + k * NC + j];
               }
@@ -1114,6 +1121,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
         nfree -= (uint32_t)__popcll(fm & om) + (uint32_t)__popcll(sm & om);
         min_free = min(min_free, nfree);
         push_tasks(ok, id);
+        raise_status();   // (no segment for a stack: nobody may go on with it)
       }
     }
   }

@@ -130,6 +130,16 @@ def test_a_run_beyond_max_tags_is_given_up(fib, tmp_path):
     assert fib.run([(n,) for n in range(21)], waves=40, max_tags=57291)["status"] == 0
 
 
+def test_a_run_without_stack_segments_is_given_up(fib_under_chain):
+    # (an index that no segment has would end the driver)
+    lanes, ref = fib_under_chain
+    for segs in (1, 2, 5, 20):
+        for args in ([(300, 14)] * 3 + [(20, 3)] * 9, [(150, 16)], [(40, 12)] * 60):
+            for waves in (1, 3):
+                got = lanes.run(args, waves=waves, segs=segs, seed=1)
+                assert got["status"] == -tdf.ERR_TABLE_FULL, (segs, waves)
+
+
 def test_a_long_run_is_not_given_up_while_waves_work(fib):
     # longer than the time in which nobody may work; waves that wait look at that all the time
     for seed in (1, 2, 3):
