@@ -219,3 +219,17 @@ INTEGER = {p.__name__: p for p in (one_of_two_entries, entries_under_an_argument
                                    waiting_calls_with_entries_as_arguments)}
 # name -> program, forest, arguments that name a node that does not exist
 BAD_INDEX = {p.__name__: p for p in (bad_index_in_result, bad_index_from_a_call, bad_index_through_calls)}
+
+
+def fib_at_every_frame_of_a_chain(fib_first):
+    """f(n, m) = fib(m) + f(n - 1, m) down to f(0, m) = fib(m), either call first: a program and its reference."""
+    f = _Fn("f", 2)
+    n, m, one = f.add(T.OP_IN, imm=0), f.add(T.OP_IN, imm=1), f.add(T.OP_CONST, imm=1)
+    sn, sm = (f.add(T.OP_SWITCH, [f.add(T.OP_LT, [n, one]), v]) for v in (n, m))
+    base = f.add(T.OP_CALLFN, [(sm[0], 0)], imm=2)
+    two = {}
+    for first in (fib_first, not fib_first):
+        two[first] = f.add(T.OP_CALLFN, [(sm[0], 1)], imm=2) if first else \
+            f.add(T.OP_CALLFN, [f.add(T.OP_SUB, [(sn[0], 1), one]), (sm[0], 1)], imm=1)
+    f.add(T.OP_OUT, [f.add(T.OP_MERGE, [base, f.add(T.OP_ADD, [two[True], two[False]])])])
+    return ([_result(2, 1).desc(), f.desc(), _fib_as(2)], 0), lambda n, m: (n + 1) * fib_value(m)

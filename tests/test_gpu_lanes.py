@@ -191,3 +191,20 @@ def test_the_lanes_are_tried_again_after_a_call_they_left_to_the_step_machine():
     for _ in range(8):
         assert _eval_int(g, bad, 1, 200)[2] == 0
     assert _eval_int(g, bad, 1, 200)[2] == 1
+
+
+@pytest.mark.parametrize("waves", ["1", None], ids=["one_wave", "waves_default"])
+@pytest.mark.parametrize("name", ["fib_first", "chain_first", "every_third", "below"])
+def test_chains_longer_than_a_wave_has_records(name, waves, monkeypatch):
+    # chains with nothing to hand over, and chains whose frames are handed over and wait for one value each
+    import lane_programs
+    prog, ref = {"fib_first": lambda: lane_programs.fib_at_every_frame_of_a_chain(True),
+                 "chain_first": lambda: lane_programs.fib_at_every_frame_of_a_chain(False),
+                 "every_third": lane_programs.fibs_along_a_chain, "below": lane_programs.fib_below_a_chain}[name]()
+    args = {"every_third": [(400, 2, 9), (90, 0, 12), (3, 1, 5)], "below": [(300, 18), (120, 14)]}.get(name, [(300, 12), (1000, 6), (5, 3)])
+    if waves:
+        monkeypatch.setenv("TDF_LANE_WAVES", waves)
+    g = tdf.graph_build(*prog)
+    for _ in range(3):
+        out, counts, repeats = _eval_int(g, args, len(args[0]), 400000)
+        assert out == [ref(*a) for a in args] and repeats == 0

@@ -6,7 +6,7 @@ import oracle
 from oracle import programs as oprog
 import lane_random
 from lane_cpu import Lanes, lane_source, needs_host_lanes
-from lane_programs import BAD_INDEX, INTEGER, VECTOR, fib_below_a_chain, fibs_along_a_chain
+from lane_programs import BAD_INDEX, INTEGER, VECTOR, fib_at_every_frame_of_a_chain, fib_below_a_chain, fibs_along_a_chain
 
 pytestmark = needs_host_lanes
 tdf = pytest.importorskip("paper_2410_20225_amd.tdf")
@@ -185,6 +185,18 @@ def test_the_schedule_of_tree_networks(node_loss, tmp_path):
             return level
         for b, v in enumerate(roots):
             check(got["root"][b], v, b)
+
+
+@pytest.mark.parametrize("fib_first", [True, False], ids=["fib_first", "chain_first"])
+def test_chains_in_which_every_frame_is_shared(fib_first, tmp_path):
+    prog, ref = fib_at_every_frame_of_a_chain(fib_first)
+    lanes = Lanes(prog, tmp_path)
+    args = [(150, 8), (3, 12), (300, 5), (90, 10), (0, 5)]
+    for waves in (1, 2, 5):
+        for seed in range(1, 7):
+            got = lanes.run(args, waves=waves, seed=seed)
+            assert got["status"] == 0 and got["out"] == [ref(*a) for a in args], (waves, seed)
+            assert got["records"] <= 96 * waves
 
 
 def _random_case(seed):
