@@ -26,7 +26,6 @@ using std::max;
 using std::min;
 struct alignas(16) uint4 { uint32_t x, y, z, w; };
 inline uint4 make_uint4(uint32_t x, uint32_t y, uint32_t z, uint32_t w) { return uint4{x, y, z, w}; }
-struct Dim { uint32_t x = 0, y = 0, z = 0; };
 
 extern "C" void hw_switch(void** save, void* load);
 asm(R"(
