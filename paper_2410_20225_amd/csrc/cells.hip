@@ -117,6 +117,10 @@ struct GemmArgs {
   void* Hs_out;              // state rows written by the forward cells
   float* Cs;                 // LSTM cell state rows
   uint32_t leaf_rows;        // rows below this one are leaves: their cell state is zero and is not stored
+  uint32_t fresh_row;        // tail launches: rows from this one on are written by the launch itself
+  int fresh_narrow;          // ... which end below 4 GiB from there
+  void* dz_fill;             // tail launch of a gradient run: Dz and dC, where what the gradient tail will write is marked
+  float* dc_fill;            // as not written
   void* gates;               // LSTM activations, row m of this level
   size_t ldg;
   float* C;                  // fp32 output (DX_BWD: dH; DW_SPLIT: partial tiles)
@@ -410,83 +414,162 @@ template <typename T, int MODE> void launch_gemm(GemmArgs g, int n_tiles_n, int 
 }
 
 // ---- small levels ----------------------------------------------------------------------
-// Deep in the recursion a dependency level holds few cells, and a level costs the latency of
-// one kernel.  This variant keeps that chain short: a workgroup owns 32 cells x 32 hidden units
-// (x gates), its four waves split the reduction four ways and load their MFMA operands
-// straight from global memory (the weights come from L2, no LDS staging, few dependent round
-// trips), and the partial tiles meet in LDS; wave w then finishes rows 8w..8w+7 of the tile.
-// Operands are fetched as 16-byte chunks: for bf16 one chunk is one 32x32x16 operand; for fp32
-// a chunk of four k-values feeds four 32x32x2 products, component j of both operands in
-// product j (a fixed permutation of the reduction index).
-// Operand order of a k-contiguous matrix [rows x K] for 32-row MFMA operands: the 16-byte chunks
-// that the 64 lanes of a wave feed into one product step are stored one after the other (lane l
-// holds row 32 rt + l % 32, reduction indices s * KC + (l / 32) * EPC ...), so a wave fetches an
-// operand with one fully coalesced 1 KB load instead of touching 32 rows.
-template <typename T> __host__ __device__ inline size_t frag_offset(int row, int k, int K) {
-  constexpr int EPC = 16 / (int)sizeof(T), KC = 2 * EPC;
-  const int rt = row >> 5, r = row & 31, st = k / KC, kk = k % KC, half = kk / EPC, el = kk % EPC;
-  return (((size_t)rt * (K / KC) + st) * 64 + half * 32 + r) * EPC + el;
-}
-
+// Deep in the recursion a dependency level holds few cells, and a level costs its latency.  A tile is kept small
+// for that: 16 cells x 16 hidden units x 5 gates (TreeLSTM, four waves), or 16 cells x 32 columns (TreeRNN and
+// input gradients, eight waves).  The waves split the reduction and load their MFMA operands straight from global
+// memory (no staging through LDS), the partial tiles meet in LDS, and every lane then finishes one element.
+// Against the 32 x 32 tile that this one replaced, a wave multiplies a quarter as long (20 products of 16 clocks
+// instead of 40 of 32 for a TreeLSTM of 256 units), a quarter as much goes through LDS, and a lane has one
+// element's gates to compute instead of four in a row.
+// Operands are fetched as 16-byte chunks: for bf16 one chunk is one 16x16x32 operand; for fp32 a chunk of four
+// k-values feeds four 16x16x4 products, component j of both operands in product j (a fixed permutation of the
+// reduction index).
 template <typename T> struct Chunk;
 template <> struct Chunk<__bf16> {
-  static constexpr int KC = 16;   // reduction indices covered by one chunk step of a wave
-  static __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  static constexpr int KC = 32;   // reduction indices covered by one chunk step of a wave
+  static constexpr int EPC = 8;   // elements per chunk
+  static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  }
+  // Bit patterns of an element that has not been written yet (below: announce), and whether a chunk holds one.
+  static constexpr unsigned short NONE = 0xFFFF;
+  static __device__ __forceinline__ bool waiting(u32x4 c) {
+    typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+    const u16x2 m = __builtin_elementwise_max(__builtin_elementwise_max(__builtin_bit_cast(u16x2, c.x), __builtin_bit_cast(u16x2, c.y)),
+                                              __builtin_elementwise_max(__builtin_bit_cast(u16x2, c.z), __builtin_bit_cast(u16x2, c.w)));
+    return m.x == NONE || m.y == NONE;
   }
 };
 template <> struct Chunk<float> {
-  static constexpr int KC = 8;
-  static __device__ __forceinline__ f32x16 mma(u32x4 a, u32x4 b, f32x16 c) {
-    typedef __attribute__((ext_vector_type(4))) float f32x4;
+  static constexpr int KC = 16;
+  static constexpr int EPC = 4;
+  static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
     const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, y.x, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, y.y, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, y.z, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, y.w, c, 0, 0, 0);
     return c;
   }
+  static constexpr uint32_t NONE = 0xFFFFFFFFu;
+  static __device__ __forceinline__ bool waiting(u32x4 c) { return c.x == NONE || c.y == NONE || c.z == NONE || c.w == NONE; }
 };
 
-// One tile: rows 32 rt .. 32 rt + 31 of the level, hidden units (output columns) 32 ct .. 32 ct + 31.
-// Called by all NW * 64 threads of a workgroup (NW = 4 or 8 waves split the reduction); `part` is
-// its LDS scratch [wave][G][16][64].
-// Weight operands of a wave for one column tile, kept in registers across tiles by the tail
-// kernels (a workgroup there always works on the same column tile): RES chunk steps.
-template <int MODE, int RES> struct ResidentB {
-  static constexpr int G = MODE == LSTM_FWD ? 5 : 1;
-  u32x4 f[RES > 0 ? RES : 1][G];
-};
-
-template <int DT, int MODE, int NW>
-__device__ __forceinline__ const typename TypeOf<DT>::type* tile_b_base(const GemmArgs& g, int ct, int j) {
-  typedef typename TypeOf<DT>::type T;
-  constexpr int EPC = 16 / (int)sizeof(T);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int brt = (MODE == LSTM_FWD ? j * (g.Hp / 32) : 0) + ct;
-  // operand order: chunk step st of this wave is 64 * EPC elements further on
-  return reinterpret_cast<const T*>(g.Bf) + (((size_t)brt * (g.K / Chunk<T>::KC) + wave * (g.K / NW / Chunk<T>::KC)) * 64 + lane) * EPC;
+// Operand order of a k-contiguous matrix [rows x K] for 16-row MFMA operands: the 16-byte chunks
+// that the 64 lanes of a wave feed into one product step are stored one after the other (lane l
+// holds row 16 rt + l % 16, reduction indices s * KC + (l / 16) * EPC ...), so a wave fetches an
+// operand with one fully coalesced 1 KB load instead of touching 16 rows.
+template <typename T> __host__ __device__ inline size_t frag_offset(int row, int k, int K) {
+  constexpr int EPC = Chunk<T>::EPC, KC = Chunk<T>::KC;
+  const int rt = row >> 4, r = row & 15, st = k / KC, kk = k % KC, part = kk / EPC, el = kk % EPC;
+  return (((size_t)rt * (K / KC) + st) * 64 + part * 16 + r) * EPC + el;
 }
 
-template <int DT, int MODE, int NW, int RES>
-__device__ __forceinline__ void load_resident_b(const GemmArgs& g, int ct, ResidentB<MODE, RES>& rb) {
+// Rows that announce themselves.  In the tail launches (below) a tile reads rows that other workgroups of its die have
+// just written.  An element that is still to be written holds the pattern NONE, which is a NaN; a NaN that is a
+// result is stored with another pattern.  So a reader that finds no NONE in what it has loaded has the row, whatever
+// order the stores arrive in, and neither side waits for an acknowledgement or a counter.
+__device__ __forceinline__ float announce(float x) {
+  return __builtin_bit_cast(uint32_t, x) == 0xFFFFFFFFu ? __builtin_bit_cast(float, 0x7FFFFFFFu) : x;
+}
+__device__ __forceinline__ __bf16 announce(__bf16 x) {
+  return __builtin_bit_cast(unsigned short, x) == 0xFFFFu ? __builtin_bit_cast(__bf16, (unsigned short)0x7FFFu) : x;
+}
+template <typename T> __device__ __forceinline__ T not_written();
+template <> __device__ __forceinline__ float not_written<float>() { return __builtin_bit_cast(float, 0xFFFFFFFFu); }
+template <> __device__ __forceinline__ __bf16 not_written<__bf16>() { return __builtin_bit_cast(__bf16, (unsigned short)0xFFFFu); }
+// Loads of such rows go past the L1, which could hold an older copy of the line.  A chunk is one request where its offset
+// from the first such row fits 32 bits; two halves cost twice the requests, and the L1 passes one of 64 bytes per clock
+// on (16 rows of 2 KB: 500 clocks).
+struct FreshRows {
+  const char* base;
+  __amdgpu_buffer_rsrc_t rsrc;
+};
+__device__ __forceinline__ FreshRows fresh_rows(const void* base) {
+  return FreshRows{reinterpret_cast<const char*>(base), __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, -1, 0x00027000)};
+}
+__device__ __forceinline__ u32x4 load_fresh16(const FreshRows& f, uint64_t offset, bool narrow) {
+  if (narrow) {
+    asm volatile("" ::: "memory");   // (looked at again and again)
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(f.rsrc, (int)offset, 0, 16));   // sc1: device scope
+  }
+  const unsigned long long* q = reinterpret_cast<const unsigned long long*>(f.base + offset);
+  const unsigned long long a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
+}
+__device__ __forceinline__ uint32_t load_fresh(const float* p) {
+  return __hip_atomic_load(reinterpret_cast<const uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+constexpr uint32_t F_NONE = 0xFFFFFFFFu;
+
+template <int MODE> struct Tile {
+  static constexpr int NW = MODE == LSTM_FWD ? 4 : 8;   // waves, which split the reduction
+  static constexpr int CB = MODE == LSTM_FWD ? 1 : 2;   // blocks of 16 units (output columns)
+  static constexpr int G = MODE == LSTM_FWD ? 5 : 1;    // gates
+  static constexpr int NB = G * CB;                     // column blocks of a wave
+  static constexpr int UNITS = 16 * CB;
+  static constexpr int ROWS = 16;
+  static constexpr int PART = NW * NB * 4 * 64;         // floats of the partial tiles [wave][block][4][64]
+  // the chunk steps of a wave: [first, first + n) of the K / KC of the whole reduction.  Forward: the first half
+  // of the waves has h_l of [h_l; h_r].
+  static __host__ __device__ int first_step(int steps, int wave) {
+    if (MODE == DX_BWD) return steps * wave / NW;
+    const int half = steps / 2, nh = NW / 2;
+    return (wave / nh) * half + half * (wave % nh) / nh;
+  }
+  static __host__ __device__ int steps_most(int steps) {
+    const int per = MODE == DX_BWD ? NW : NW / 2, n = MODE == DX_BWD ? steps : steps / 2;
+    return (n + per - 1) / per;
+  }
+};
+__device__ __forceinline__ int wave_of() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }   // (a scalar)
+// What is the same for all tiles of a workgroup.
+struct TileLane {
+  int wave, s0, n;      // the wave's chunk steps
+  uint32_t a;           // element of an operand row with which the lane's operands begin; chunk step st is st * KC further on
+  int row, col;         // the lane's element of a tile: row, and place among its columns
+};
+template <int DT, int MODE> __device__ __forceinline__ TileLane tile_lane(const GemmArgs& g) {
+  typedef Chunk<typename TypeOf<DT>::type> C;
+  typedef Tile<MODE> TL;
+  const int lane = threadIdx.x & 63, steps = g.K / C::KC;
+  TileLane c;
+  c.wave = wave_of();
+  c.s0 = TL::first_step(steps, c.wave);
+  c.n = TL::first_step(steps, c.wave + 1) - c.s0;
+  c.a = (uint32_t)((c.s0 - (MODE == DX_BWD || c.wave < TL::NW / 2 ? 0 : steps / 2)) * C::KC + (lane >> 4) * C::EPC);
+  c.row = 4 * (lane >> 4) + (c.wave & 3);
+  c.col = (TL::CB == 2 ? (c.wave >> 2) * 16 : 0) + (lane & 15);
+  return c;
+}
+
+// Weight operands of a wave for one column tile: RES chunk steps.  The tail kernels keep them in registers across
+// tiles (a workgroup there always works on the same column tile).
+template <int MODE, int RES> struct TileB {
+  u32x4 f[RES][Tile<MODE>::NB];
+};
+template <int DT, int MODE, int RES>
+__device__ __forceinline__ void load_b(const GemmArgs& g, int ct, int s0, int n, TileB<MODE, RES>& b) {
   typedef typename TypeOf<DT>::type T;
-  constexpr int EPC = 16 / (int)sizeof(T);
-  const int steps = g.K / NW / Chunk<T>::KC;
+  typedef Chunk<T> C;
+  const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int j = 0; j < ResidentB<MODE, RES>::G; ++j) {
-    const T* bp = tile_b_base<DT, MODE, NW>(g, ct, j);
+  for (int j = 0; j < Tile<MODE>::NB; ++j) {
+    const int brt = MODE == LSTM_FWD ? j * (g.Hp / 16) + ct : ct * Tile<MODE>::CB + j;
+    const T* bp = reinterpret_cast<const T*>(g.Bf) + (((size_t)brt * (g.K / C::KC) + s0) * 64 + lane) * C::EPC;
 #pragma unroll
-    for (int st = 0; st < RES; ++st) rb.f[st][j] = *reinterpret_cast<const u32x4*>(bp + (size_t)min(st, steps - 1) * 64 * EPC);
+    for (int st = 0; st < RES; ++st) {
+      b.f[st][j] = u32x4{0u, 0u, 0u, 0u};   // (the products of steps that a wave has not are made too: a branch around them costs more)
+      if (st < n) b.f[st][j] = *reinterpret_cast<const u32x4*>(bp + (size_t)st * 64 * C::EPC);
+    }
   }
 }
 
-// RES > 0: the weight operands come from `rb` (which holds all chunk steps of this wave: the
-// caller checked steps <= RES); RES == 0: they are fetched here.
 // DX_BWD tiles of the tail launches also form the pre-activation gradients of the children they
 // have just given their dh: a child has one parent, so once the parent's tile has produced dh of
 // (child, unit) everything that dz of (child, unit) needs is final (dc came from the parent's own
-// dz, the rest is forward state).  The separate dz pass over a level, and the barrier after it,
+// dz, the rest is forward state).  The separate dz pass over a level, and the wait after it,
 // are not needed then.  Only children inside the tail are handled (cq >= q_first): the cells of
 // the wide levels get their dz from k_dz as before.
 struct DzFuse {
@@ -496,296 +579,357 @@ struct DzFuse {
   uint32_t q_first;              // first cell of the tail in the sorted log
 };
 
-// What a tile reads that no tile writes, in the two steps that follow one another: the children's rows, and what these
-// lead to: operands that are leaves' rows (RNN_FWD), for the fused dz (CELL: the cell kind, 0: none) the forward state
-// of the child cells.  Most of it comes from HBM.  The tail kernels request the latter a level and the former two levels
-// ahead, behind the loads that the level itself waits for.
-template <int MODE, int NW> struct TileRows {
-  static constexpr int RPW = 16 / NW;   // accumulator registers (rows of a lane) a wave finishes
-  uint32_t child;                       // operand row of this lane (forward)
-  uint32_t o_l[RPW], o_r[RPW];
+// One tile's cells: q0 .. q0 + M - 1 of the sorted log (M <= 16; 0: no tile), column tile ct.
+struct TileAt {
+  uint32_t q0;
+  int M, ct;
 };
-template <int MODE, int NW, int RES, int CELL> struct TileAhead {
-  static constexpr int RPW = 16 / NW;
-  u32x4 leaf[RES > 0 && MODE == RNN_FWD ? RES : 1];   // the lane's operands, if its child is a leaf
-  float bias[MODE == LSTM_FWD ? 5 : 1];
-  uint32_t z_q[RPW], z_gl[RPW], z_gr[RPW];   // fused dz: the child cell (none: all ones) and its children's rows
-  float z_gate[RPW][5], z_c[RPW], z_h[RPW], z_own[RPW], z_cl[RPW], z_cr[RPW];
+// What a tile reads that no tile writes, in the steps that follow one another: rows of the children (TileRows, to which
+// the fused dz adds the rows of the children's children), and what these lead to (TileAhead): operands of children that
+// are complete before the launch, and for the fused dz (CELL: the cell kind, 0: none) the forward state of the child
+// cells.  Most of it comes from HBM.  The tail kernels request it one to three tiles ahead.
+template <int MODE> struct TileRows {
+  uint32_t child;                   // operand row of this lane (forward)
+  uint32_t o_l, o_r;                // children of the lane's element
+  uint32_t z_q, z_gl, z_gr;         // fused dz: the child cell (none: all ones) and its children's rows
 };
-// row of the tile that this lane finishes with accumulator register r = RPW * wave + rr
-template <int NW> __device__ __forceinline__ int tile_row_of(int rr) {
-  const int r = 16 / NW * (int)(threadIdx.x >> 6) + rr;
-  return (r >> 2) * 8 + (int)((threadIdx.x & 63) >> 5) * 4 + (r & 3);
+template <int MODE, int RES, int CELL> struct TileAhead {
+  u32x4 a[RES > 0 && MODE != DX_BWD ? RES : 1];   // the lane's operands, if its child is complete
+  float bias[Tile<MODE>::G];   // (RES == 0)
+  float c_l, c_r;                             // cell states of complete children (TreeLSTM)
+  float z_gate[5], z_c, z_h, z_own, z_cl, z_cr;
+};
+// (element offsets of state rows are 32 bits wide: the host checks)
+template <int MODE>
+__device__ __forceinline__ void tile_rows(const GemmArgs& g, const TileLane& c, const TileAt& t, TileRows<MODE>& p) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t* const l = g.l + t.q0;
+  const uint32_t* const r = g.r + t.q0;
+  if constexpr (MODE != DX_BWD) {
+    p.child = 0;
+    if ((lane & 15) < t.M) p.child = (c.wave < Tile<MODE>::NW / 2 ? l : r)[lane & 15];
+  }
+  p.o_l = p.o_r = 0;
+  if (c.row < t.M) {
+    p.o_l = l[c.row];
+    p.o_r = r[c.row];
+  }
 }
-template <int MODE, int NW>
-__device__ __forceinline__ void tile_rows(const GemmArgs& g, int rt, TileRows<MODE, NW>& p) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m0 = rt * 32, mA = min(m0 + (lane & 31), g.M - 1);
-  if (MODE != DX_BWD) p.child = wave < NW / 2 ? g.l[mA] : g.r[mA];   // first half of the waves: h_l of [h_l; h_r]
-  if (MODE != RNN_FWD) {
-#pragma unroll
-    for (int rr = 0; rr < TileRows<MODE, NW>::RPW; ++rr) {
-      const int m = min(m0 + tile_row_of<NW>(rr), g.M - 1);
-      p.o_l[rr] = g.l[m];
-      p.o_r[rr] = g.r[m];
+template <int DT, int MODE, int CELL>
+__device__ __forceinline__ void tile_rows2(const GemmArgs& g, const TileLane& c, const TileAt& t, const DzFuse* fz, TileRows<MODE>& p) {
+  if constexpr (CELL != 0) {
+    const bool left = t.ct * Tile<MODE>::UNITS + c.col < g.Hp;   // column of [dh_l; dh_r]: which child
+    const uint32_t row = left ? p.o_l : p.o_r;
+    const bool ok = c.row < t.M && row >= fz->row0 && row - fz->row0 >= fz->q_first;   // a cell of the tail (a leaf has no dz)
+    p.z_q = ok ? row - fz->row0 : 0xFFFFFFFFu;
+    if constexpr (CELL == 2) {
+      p.z_gl = p.z_gr = 0;
+      if (ok) {
+        p.z_gl = fz->q_l[p.z_q];
+        p.z_gr = fz->q_r[p.z_q];
+      }
     }
   }
 }
-// the lane's A operands of a forward tile: chunk step st is st * KC elements further on
-template <int DT, int MODE, int NW>
-__device__ __forceinline__ const typename TypeOf<DT>::type* tile_a_base(const GemmArgs& g, uint32_t child) {
+template <int DT, int MODE, int RES, int CELL>
+__device__ __forceinline__ void tile_ahead(const GemmArgs& g, const TileLane& c, const TileAt& t, const DzFuse* fz, const TileRows<MODE>& p,
+                                           TileAhead<MODE, RES, CELL>& q) {
   typedef typename TypeOf<DT>::type T;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  return reinterpret_cast<const T*>(g.Hs) + (size_t)child * g.Hp + (wave % (NW / 2)) * (g.K / NW) + (lane >> 5) * (16 / (int)sizeof(T));
-}
-template <int DT, int MODE, int NW, int RES, int CELL>
-__device__ __forceinline__ void tile_ahead(const GemmArgs& g, int ct, const DzFuse* fz, const TileRows<MODE, NW>& p,
-                                           TileAhead<MODE, NW, RES, CELL>& q) {
-  typedef typename TypeOf<DT>::type T;
-  constexpr int RPW = 16 / NW;
+  typedef Chunk<T> C;
+  const int lane = threadIdx.x & 63;
+  const int unit = t.ct * Tile<MODE>::UNITS + c.col;
   if constexpr (MODE != DX_BWD) {
+    if constexpr (RES == 0) {   // (else the workgroup's column tile is always the same)
 #pragma unroll
-    for (int j = 0; j < (MODE == LSTM_FWD ? 5 : 1); ++j) q.bias[j] = g.bias[j * g.Hp + ct * 32 + (int)(threadIdx.x & 31)];
-  }
-  if constexpr (MODE == RNN_FWD && RES > 0) {
-    const int steps = g.K / NW / Chunk<T>::KC;
-    const T* Ap = tile_a_base<DT, MODE, NW>(g, p.child);
-    if (p.child < g.leaf_rows) {
+      for (int j = 0; j < Tile<MODE>::G; ++j) q.bias[j] = g.bias[j * g.Hp + unit];
+    } else {
+      const bool ready = (lane & 15) < t.M && p.child < g.fresh_row;
+      const T* ap = reinterpret_cast<const T*>(g.Hs) + (p.child * (uint32_t)g.Hp + c.a);
 #pragma unroll
-      for (int st = 0; st < RES; ++st) q.leaf[st] = *reinterpret_cast<const u32x4*>(Ap + min(st, steps - 1) * Chunk<T>::KC);
+      for (int st = 0; st < RES; ++st) {
+        q.a[st] = u32x4{0u, 0u, 0u, 0u};
+        if (ready && st < c.n) q.a[st] = *reinterpret_cast<const u32x4*>(ap + st * C::KC);
+      }
+    }
+    if constexpr (MODE == LSTM_FWD) {   // (a leaf has no stored cell state: zero)
+      q.c_l = q.c_r = 0.f;
+      if (c.row < t.M) {
+        if (p.o_l >= g.leaf_rows && p.o_l < g.fresh_row) q.c_l = g.Cs[p.o_l * (uint32_t)g.Hp + (uint32_t)unit];
+        if (p.o_r >= g.leaf_rows && p.o_r < g.fresh_row) q.c_r = g.Cs[p.o_r * (uint32_t)g.Hp + (uint32_t)unit];
+      }
     }
   }
   if constexpr (CELL != 0) {
-    const VecArgs& v = *fz->v;
-    const int unit = ct * 32 + (int)(threadIdx.x & 31);
-    const bool left = unit < g.Hp;
-    const int n = left ? unit : unit - g.Hp;
-#pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const uint32_t row = left ? p.o_l[rr] : p.o_r[rr];
-      const bool ok = row >= fz->row0 && row - fz->row0 >= fz->q_first;   // a cell of the tail (a leaf has none)
-      const uint32_t qc = ok ? row - fz->row0 : 0u;   // (cell 0 exists whenever a level has cells: a safe address)
-      q.z_q[rr] = ok ? qc : 0xFFFFFFFFu;
-      const size_t o = (size_t)row * g.Hp + n;
-      q.z_own[rr] = v.dHn ? v.dHn[o] : 0.f;   // gradient of the child's own loss term
+    if (p.z_q != 0xFFFFFFFFu) {
+      const VecArgs& v = *fz->v;
+      const uint32_t n = (uint32_t)(unit < g.Hp ? unit : unit - g.Hp);
+      const uint32_t o = (fz->row0 + p.z_q) * (uint32_t)g.Hp + n;
+      q.z_own = v.dHn ? v.dHn[o] : 0.f;   // gradient of the child's own loss term
       if constexpr (CELL == 1) {
-        q.z_h[rr] = to_f(reinterpret_cast<const T*>(v.Hs)[o]);
+        q.z_h = to_f(reinterpret_cast<const T*>(v.Hs)[o]);
       } else {
-        const T* g5 = reinterpret_cast<const T*>(v.gates) + (size_t)qc * v.Np + n;
-        q.z_gl[rr] = fz->q_l[qc];
-        q.z_gr[rr] = fz->q_r[qc];
+        const T* g5 = reinterpret_cast<const T*>(v.gates) + ((uint64_t)p.z_q * (uint32_t)v.Np + n);
 #pragma unroll
-        for (int k = 0; k < 5; ++k) q.z_gate[rr][k] = to_f(g5[k * g.Hp]);
-        q.z_c[rr] = ok ? v.Cs[o] : 0.f;
-      }
-    }
-    if constexpr (CELL == 2) {
-#pragma unroll
-      for (int rr = 0; rr < RPW; ++rr) {
-        q.z_cl[rr] = q.z_gl[rr] >= fz->row0 ? v.Cs[(size_t)q.z_gl[rr] * g.Hp + n] : 0.f;   // (a leaf's cell state is zero)
-        q.z_cr[rr] = q.z_gr[rr] >= fz->row0 ? v.Cs[(size_t)q.z_gr[rr] * g.Hp + n] : 0.f;
+        for (int k = 0; k < 5; ++k) q.z_gate[k] = to_f(g5[k * g.Hp]);
+        q.z_c = v.Cs[o];
+        q.z_cl = p.z_gl >= fz->row0 ? v.Cs[p.z_gl * (uint32_t)g.Hp + n] : 0.f;   // (a leaf's cell state is zero)
+        q.z_cr = p.z_gr >= fz->row0 ? v.Cs[p.z_gr * (uint32_t)g.Hp + n] : 0.f;
       }
     }
   }
 }
 
-// `more` requests what later tiles need, behind the tile's own loads: in RNN_FWD, where it has most of a level's time to
-// come, once these are through and the products on their way (4095 levels: 12.1 -> 11.3 ms), else right away (LSTM
-// forward and gradient tails 4 to 7 % faster than the other way).
-template <int DT, int MODE, int NW, int RES, int CELL, class More>
-__device__ __forceinline__ void cell_small_tile(const GemmArgs& g, int rt, int ct, float* part, const TileRows<MODE, NW>& p,
-                                                const TileAhead<MODE, NW, RES, CELL>& q, const ResidentB<MODE, RES>* rb,
-                                                const DzFuse* fz, More more) {
+// Waiting for rows of other workgroups: `attempt` looks again (true: this lane has what it needs) until all lanes of the
+// wave have.  False: no workgroup of the die has got anywhere for spin_ticks, or another one has given up.
+struct TailWait {
+  DieSync* sync;
+  long long spin_ticks;
+};
+template <class F> __device__ __forceinline__ bool wait_rows(const TailWait& w, F attempt) {
+  if (__all(attempt())) return true;
+  long long t0 = 0;
+  uint32_t beat = 0;
+  for (uint32_t k = 1;; ++k) {
+    if (__all(attempt())) return true;
+    if (__builtin_expect(k % 64u != 0, 1)) continue;   // (64 looks: some 20 us)
+    const uint32_t b = __hip_atomic_load(&w.sync->beat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const long long now = wall_clock64();
+    if (t0 == 0 || b != beat) {
+      t0 = now;
+      beat = b;
+    } else if (now - t0 > w.spin_ticks) {
+      break;
+    }
+    if (__hip_atomic_load(&w.sync->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
+  }
+  __hip_atomic_store(&w.sync->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return false;
+}
+
+// One tile, by all NW * 64 threads of a workgroup.  `part` is its LDS scratch of Tile<MODE>::PART floats; consecutive
+// tiles of a workgroup use two of them in turn, and then one workgroup barrier a tile is enough: who writes a buffer
+// again has passed the barrier of the tile between, which all waves reach after they have read it.
+// RES > 0: the weight operands are in `b` (all chunk steps of this wave); 0: they are fetched here.
+// WAIT: rows from g.fresh_row on (forward: children, gradient: the tile's own dz and the children's dc) are written by
+// this launch and waited for.  `advance` finds the workgroup's next tile and `request` asks for what later tiles need: the
+// former in the products' shadow, when all that was asked for before has come, the latter behind the tile's stores.
+// failed: a flag in LDS, two of them in turn like `part`; false is returned if it is set.
+template <int DT, int MODE, int RES, int CELL, bool WAIT, class Advance, class Request>
+__device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLane& c, const TileAt& t, float* part, const TileRows<MODE>& p,
+                                                const TileAhead<MODE, RES, CELL>& q, const float (&bias)[Tile<MODE>::G],
+                                                const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, const TailWait& w, uint32_t* failed,
+                                                Advance advance, Request request) {
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
-  constexpr int G = MODE == LSTM_FWD ? 5 : 1;      // 32-wide column blocks per tile
-  constexpr int BATCH = 8;                          // chunk steps in flight
-  constexpr int EPC = 16 / (int)sizeof(T);         // elements per chunk
-  constexpr int RPW = 16 / NW;                     // accumulator registers (rows of a lane) a wave finishes
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = rt * 32;
-  const int mA = min(m0 + (lane & 31), g.M - 1);   // operand row of this lane
-  const int kw = g.K / NW;                         // reduction range of this wave: [wave * kw, +kw)
-
-  auto row_of = [&](int rr) { return tile_row_of<NW>(rr); };
-  // operand bases (elements)
+  typedef Tile<MODE> TL;
+  constexpr int BATCH = RES > 0 ? RES : 4;   // chunk steps in flight
+  const int lane = threadIdx.x & 63, n = c.n, s0 = c.s0, wave = c.wave;
+  const bool valid = (lane & 15) < t.M;
   const T* Ap;
-  if constexpr (MODE == DX_BWD) Ap = reinterpret_cast<const T*>(g.A) + (size_t)mA * g.lda + wave * kw + (lane >> 5) * EPC;
-  else Ap = tile_a_base<DT, MODE, NW>(g, p.child);
-  const T* Bp[G];
-#pragma unroll
-  for (int j = 0; j < G; ++j) Bp[j] = tile_b_base<DT, MODE, NW>(g, ct, j);
-  // children's cell states for the epilogue, requested before the products start
-  float cl[RPW], cr[RPW];
-  const int unit = ct * 32 + (lane & 31);
-  if (MODE == LSTM_FWD) {
-#pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      // (a leaf child has no stored cell state: it reads row 0, a leaf's row that k_embed keeps zero)
-      cl[rr] = g.Cs[(p.o_l[rr] >= g.leaf_rows ? p.o_l[rr] : 0u) * (uint32_t)g.Hp + (uint32_t)unit];
-      cr[rr] = g.Cs[(p.o_r[rr] >= g.leaf_rows ? p.o_r[rr] : 0u) * (uint32_t)g.Hp + (uint32_t)unit];
-    }
+  if constexpr (MODE == DX_BWD) Ap = reinterpret_cast<const T*>(g.A) + ((uint64_t)(t.q0 + (uint32_t)(lane & 15)) * (uint32_t)g.lda + c.a);
+  else Ap = reinterpret_cast<const T*>(g.Hs) + (p.child * (uint32_t)g.Hp + c.a);
+  FreshRows rows{};
+  uint64_t off = 0;   // of the lane's operands, bytes
+  if constexpr (WAIT && MODE == DX_BWD) {
+    rows = fresh_rows(reinterpret_cast<const T*>(g.A) + (uint64_t)t.q0 * (uint32_t)g.lda);
+    off = ((uint32_t)(lane & 15) * (uint32_t)g.lda + c.a) * (uint32_t)sizeof(T);
+  } else if constexpr (WAIT) {
+    rows = fresh_rows(reinterpret_cast<const T*>(g.Hs) + g.fresh_row * (uint32_t)g.Hp);
+    off = ((uint64_t)(p.child - g.fresh_row) * (uint32_t)g.Hp + c.a) * sizeof(T);
+  }
+  const bool narrow = MODE == DX_BWD || g.fresh_narrow;
+  const bool fresh = WAIT && valid && (MODE == DX_BWD || p.child >= g.fresh_row);   // (a tile of the gradient tail: all its rows)
+
+  const int unit = t.ct * TL::UNITS + c.col;
+  const bool el = c.row < t.M;   // the lane's element exists
+  const bool z_left = unit < g.Hp;
+  const uint32_t z_n = (uint32_t)(z_left ? unit : unit - g.Hp);
+  // values of single elements that are waited for: the children's cell states (forward), dc of the child cell (gradient)
+  const float *w0 = nullptr, *w1 = nullptr;
+  uint32_t u0 = 0, u1 = 0;
+  bool f0 = false, f1 = false;
+  if constexpr (WAIT && MODE == LSTM_FWD) {
+    f0 = el && p.o_l >= g.fresh_row;
+    f1 = el && p.o_r >= g.fresh_row;
+    w0 = g.Cs + (p.o_l * (uint32_t)g.Hp + (uint32_t)unit);
+    w1 = g.Cs + (p.o_r * (uint32_t)g.Hp + (uint32_t)unit);
+  }
+  if constexpr (CELL == 2) {
+    f0 = p.z_q != 0xFFFFFFFFu;
+    w0 = fz->v->dC + ((fz->row0 + p.z_q) * (uint32_t)g.Hp + z_n);
   }
 
-  const bool z_left = unit < g.Hp;
-  const int z_n = z_left ? unit : unit - g.Hp;
-  float z_dc[RPW];   // fused dz: dc of the child cells, which their parents' dz (a level ago) has left
-
-  f32x16 acc[G];
+  f32x4 acc[TL::NB];
 #pragma unroll
-  for (int j = 0; j < G; ++j)
+  for (int j = 0; j < TL::NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 fa[BATCH];
+  auto load_a = [&](int st0, int cnt) {   // steps st0 .. of this wave
+    if constexpr (!WAIT) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-  const int steps = kw / C::KC;
-  if constexpr (CELL == 2) {
+      for (int st = 0; st < BATCH; ++st) {
+        fa[st] = u32x4{0u, 0u, 0u, 0u};
+        if (valid && st < cnt) fa[st] = *reinterpret_cast<const u32x4*>(Ap + (st0 + st) * C::KC);
+      }
+    } else {
+      bool open[BATCH];
 #pragma unroll
-    for (int rr = 0; rr < RPW; ++rr)
-      z_dc[rr] = q.z_q[rr] != 0xFFFFFFFFu ? fz->v->dC[(size_t)(z_left ? p.o_l[rr] : p.o_r[rr]) * g.Hp + z_n] : 0.f;
+      for (int st = 0; st < BATCH; ++st) {
+        open[st] = fresh && st < cnt;
+        fa[st] = u32x4{0u, 0u, 0u, 0u};
+        if (MODE != DX_BWD && RES == 0)
+          if (valid && !fresh && st < cnt) fa[st] = *reinterpret_cast<const u32x4*>(Ap + (st0 + st) * C::KC);
+      }
+      bool o0 = f0 && st0 == 0, o1 = f1 && st0 == 0;
+      const bool ok = wait_rows(w, [&] {
+#pragma unroll
+        for (int st = 0; st < BATCH; ++st)
+          if (open[st]) fa[st] = load_fresh16(rows, off + (uint32_t)((st0 + st) * C::KC * (int)sizeof(T)), narrow);
+        if (MODE == LSTM_FWD || CELL == 2) {   // (written right behind the rows)
+          if (o0) u0 = load_fresh(w0);
+          if (MODE == LSTM_FWD && o1) u1 = load_fresh(w1);
+        }
+        bool any = false;
+#pragma unroll
+        for (int st = 0; st < BATCH; ++st) {
+          open[st] = open[st] && C::waiting(fa[st]);
+          any = any || open[st];
+        }
+        o0 = o0 && u0 == F_NONE;
+        o1 = o1 && u1 == F_NONE;
+        return !(any || o0 || o1);
+      });
+      if (!ok) *failed = 1u;
+      // (Whatever was requested is here by now.  Said in so many words, or the compiler, which does not know that on the way
+      // past the loads above, waits for the tile's stores before the next tile's first look.)
+      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+      if constexpr (RES > 0 && MODE != DX_BWD) {
+#pragma unroll
+        for (int st = 0; st < BATCH; ++st) fa[st] = fresh ? fa[st] : q.a[st];
+      }
+    }
+  };
+  if constexpr (RES > 0) {
+    load_a(0, n);
   }
   if constexpr (RES > 0) {
-    u32x4 fa[RES];
 #pragma unroll
-    for (int st = 0; st < RES; ++st) {
-      if (MODE == RNN_FWD && p.child < g.leaf_rows) fa[st] = q.leaf[MODE == RNN_FWD ? st : 0];
-      else fa[st] = *reinterpret_cast<const u32x4*>(Ap + min(st, steps - 1) * C::KC);
-    }
-    if constexpr (MODE != RNN_FWD) more();
+    for (int st = 0; st < RES; ++st)
 #pragma unroll
-    for (int st = 0; st < RES; ++st) {
-      if (st < steps) {
-#pragma unroll
-        for (int j = 0; j < G; ++j) acc[j] = C::mma(fa[st], rb->f[st][j], acc[j]);
-      }
-    }
+      for (int j = 0; j < TL::NB; ++j) acc[j] = C::mma(fa[st], b->f[st][j], acc[j]);
   } else {
-  if constexpr (MODE != RNN_FWD) more();
-  for (int s0 = 0; s0 < steps; s0 += BATCH) {
-    u32x4 fa[BATCH], fb[BATCH][G];
+    for (int st0 = 0; st0 < n; st0 += BATCH) {
+      TileB<MODE, BATCH> fb;
+      const int cnt = min(BATCH, n - st0);
+      load_b<DT, MODE, BATCH>(g, t.ct, s0 + st0, cnt, fb);
+      load_a(st0, cnt);
 #pragma unroll
-    for (int b = 0; b < BATCH; ++b) {
-      const int st = min(s0 + b, steps - 1);       // a short last batch repeats its final chunk ...
+      for (int st = 0; st < BATCH; ++st)
 #pragma unroll
-      for (int j = 0; j < G; ++j) fb[b][j] = *reinterpret_cast<const u32x4*>(Bp[j] + (size_t)st * 64 * EPC);
-      fa[b] = *reinterpret_cast<const u32x4*>(Ap + st * C::KC);
-    }
-#pragma unroll
-    for (int b = 0; b < BATCH; ++b) {
-      if (s0 + b < steps) {                        // ... and leaves it out of the sum
-#pragma unroll
-        for (int j = 0; j < G; ++j) acc[j] = C::mma(fa[b], fb[b][j], acc[j]);
-      }
+        for (int j = 0; j < TL::NB; ++j) acc[j] = C::mma(fa[st], fb.f[st][j], acc[j]);
     }
   }
-  }
-
-  if constexpr (MODE == RNN_FWD) {
-    // (all that was requested above is here by now; said once, so that nothing below waits for what `more` requests)
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    more();
-  }
-  // partial tiles -> LDS; wave w sums and finishes r = 4w .. 4w+3
+  advance();
+  // partial tiles -> LDS; every lane sums and finishes its element
 #pragma unroll
-  for (int j = 0; j < G; ++j)
+  for (int j = 0; j < TL::NB; ++j)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) part[((wave * G + j) * 16 + r) * 64 + lane] = acc[j][r];
+    for (int r = 0; r < 4; ++r) part[((wave * TL::NB + j) * 4 + r) * 64 + lane] = acc[j][r];
   __syncthreads();
-  float z[G][RPW];
+  uint32_t stop = 0;
+  if constexpr (WAIT) stop = *failed;
+  float z[TL::G];
 #pragma unroll
-  for (int j = 0; j < G; ++j)
+  for (int j = 0; j < TL::G; ++j) {
+    float s = 0.f;
 #pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      float t = 0.f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) t += part[((w * G + j) * 16 + RPW * wave + rr) * 64 + lane];
-      z[j][rr] = t;
-    }
-
-  if constexpr (MODE == LSTM_FWD) {
-    const float bi = Act<T>::pre_sigmoid(q.bias[0]), bfl = Act<T>::pre_sigmoid(q.bias[1]), bfr = Act<T>::pre_sigmoid(q.bias[2]);
-    const float bo = Act<T>::pre_sigmoid(q.bias[3]), bu = Act<T>::pre_tanh(q.bias[4]);
-#pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const int m = m0 + row_of(rr);
-      if (m >= g.M) continue;
-      const float gi = Act<T>::sigmoid_b(z[0][rr], bi);
-      const float gfl = Act<T>::sigmoid_b(z[1][rr], bfl);
-      const float gfr = Act<T>::sigmoid_b(z[2][rr], bfr);
-      const float go = Act<T>::sigmoid_b(z[3][rr], bo);
-      const float gu = Act<T>::tanh_b(z[4][rr], bu);
-      const float c = gi * gu + gfl * cl[rr] + gfr * cr[rr];
-      const size_t o = (size_t)(g.out0 + (uint32_t)m) * g.Hp + unit;
-      g.Cs[o] = c;
-      reinterpret_cast<T*>(g.Hs_out)[o] = from_f<T>(go * Act<T>::tanh_b(c, 0.f));
+    for (int wv = 0; wv < TL::NW; ++wv) s += part[((wv * TL::NB + (TL::CB == 2 ? wave >> 2 : j)) * 4 + (wave & 3)) * 64 + lane];
+    z[j] = s;
+  }
+  if constexpr (WAIT) {
+    if (__builtin_expect(stop != 0, 0)) return false;
+  }
+  if (!el) {
+  } else if constexpr (MODE != DX_BWD) {
+    const uint32_t o = (g.out0 + t.q0 + (uint32_t)c.row) * (uint32_t)g.Hp + (uint32_t)unit;
+    T* const dz = g.dz_fill ? reinterpret_cast<T*>(g.dz_fill) : nullptr;
+    if constexpr (MODE == LSTM_FWD) {
+      const float cl = f0 ? __builtin_bit_cast(float, u0) : q.c_l, cr = f1 ? __builtin_bit_cast(float, u1) : q.c_r;
+      const float gi = Act<T>::sigmoid_b(z[0], Act<T>::pre_sigmoid(bias[0]));
+      const float gfl = Act<T>::sigmoid_b(z[1], Act<T>::pre_sigmoid(bias[1]));
+      const float gfr = Act<T>::sigmoid_b(z[2], Act<T>::pre_sigmoid(bias[2]));
+      const float go = Act<T>::sigmoid_b(z[3], Act<T>::pre_sigmoid(bias[3]));
+      const float gu = Act<T>::tanh_b(z[4], Act<T>::pre_tanh(bias[4]));
+      const float cs = gi * gu + gfl * cl + gfr * cr;
+      reinterpret_cast<T*>(g.Hs_out)[o] = announce(from_f<T>(go * Act<T>::tanh_b(cs, 0.f)));
+      g.Cs[o] = announce(cs);
       if (g.save_gates) {
-        T* gr = reinterpret_cast<T*>(g.gates) + (size_t)m * g.ldg;
+        T* gr = reinterpret_cast<T*>(g.gates) + (uint64_t)(t.q0 + (uint32_t)c.row) * (uint32_t)g.ldg;
         gr[unit] = from_f<T>(gi);
         gr[g.Hp + unit] = from_f<T>(gfl);
         gr[2 * g.Hp + unit] = from_f<T>(gfr);
         gr[3 * g.Hp + unit] = from_f<T>(go);
         gr[4 * g.Hp + unit] = from_f<T>(gu);
       }
+    } else {
+      reinterpret_cast<T*>(g.Hs_out)[o] = announce(from_f<T>(Act<T>::tanh(z[0] + bias[0])));
     }
-  } else if constexpr (MODE == RNN_FWD) {
+    if constexpr (WAIT) {
+      // A gradient run: dz (and dc) of the children that the gradient tail will write are still to be written.
+      if (dz) {
 #pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const int m = m0 + row_of(rr);
-      if (m >= g.M) continue;
-      reinterpret_cast<T*>(g.Hs_out)[(size_t)(g.out0 + (uint32_t)m) * g.Hp + unit] = from_f<T>(Act<T>::tanh(z[0][rr] + q.bias[0]));
-    }
-  } else {   // DX_BWD: column `unit` of [dh_l; dh_r]; each child row has exactly one consumer.
-    // (dh of a child whose dz is formed here has no other reader)
+        for (int side = 0; side < 2; ++side) {
+          const uint32_t child = side ? p.o_r : p.o_l;
+          if (child >= g.fresh_row) {
 #pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const int m = m0 + row_of(rr);
-      if (m >= g.M) continue;
-      if constexpr (CELL != 0) {
-        if (q.z_q[rr] != 0xFFFFFFFFu) continue;
-      }
-      if (unit < g.Hp) g.C[(size_t)p.o_l[rr] * g.Hp + unit] = z[0][rr];
-      else g.C[(size_t)p.o_r[rr] * g.Hp + (unit - g.Hp)] = z[0][rr];
-    }
-    if constexpr (CELL != 0) {
-      const VecArgs& v = *fz->v;
-#pragma unroll
-      for (int rr = 0; rr < RPW; ++rr) {
-        const int m = m0 + row_of(rr);
-        if (m >= g.M || q.z_q[rr] == 0xFFFFFFFFu) continue;
-        const float dh = z[0][rr] + q.z_own[rr];
-        // One lane per child cell: its gradient body fires here.  (In the die's L2: the row is this die's.)
-        if (z_n == 0)
-          __hip_atomic_fetch_add(&v.gmark[z_left ? p.o_l[rr] : p.o_r[rr]], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        T* dz = reinterpret_cast<T*>(v.Dz) + (size_t)q.z_q[rr] * v.Np + z_n;
-        if constexpr (CELL == 1) {
-          dz[0] = from_f<T>(dh * (1.f - q.z_h[rr] * q.z_h[rr]));
-        } else {
-          const float gi = q.z_gate[rr][0], gfl = q.z_gate[rr][1], gfr = q.z_gate[rr][2], go = q.z_gate[rr][3], gu = q.z_gate[rr][4];
-          const float tc = Act<T>::tanh(q.z_c[rr]);
-          const float dc = z_dc[rr] + dh * go * (1.f - tc * tc);
-          dz[0] = from_f<T>(dc * gu * gi * (1.f - gi));
-          dz[v.Hp] = from_f<T>(dc * q.z_cl[rr] * gfl * (1.f - gfl));
-          dz[2 * v.Hp] = from_f<T>(dc * q.z_cr[rr] * gfr * (1.f - gfr));
-          dz[3 * v.Hp] = from_f<T>(dh * tc * go * (1.f - go));
-          dz[4 * v.Hp] = from_f<T>(dc * gi * (1.f - gu * gu));
-          if (q.z_gl[rr] >= fz->row0) v.dC[(size_t)q.z_gl[rr] * v.Hp + z_n] = dc * gfl;   // (a leaf has no use for dc)
-          if (q.z_gr[rr] >= fz->row0) v.dC[(size_t)q.z_gr[rr] * v.Hp + z_n] = dc * gfr;
+            for (int k = 0; k < TL::G; ++k) dz[(uint64_t)(child - g.out0) * (uint32_t)g.ldg + (uint32_t)(k * g.Hp + unit)] = not_written<T>();
+            if (MODE == LSTM_FWD) g.dc_fill[child * (uint32_t)g.Hp + (uint32_t)unit] = not_written<float>();
+          }
         }
       }
     }
+  } else {   // DX_BWD: column `unit` of [dh_l; dh_r]; each child row has exactly one consumer.
+    const uint32_t child = z_left ? p.o_l : p.o_r;
+    // (dh of a child whose dz is formed here has no other reader)
+    if (CELL == 0 || p.z_q == 0xFFFFFFFFu) {
+      g.C[child * (uint32_t)g.Hp + z_n] = z[0];
+    } else if constexpr (CELL != 0) {
+      const VecArgs& v = *fz->v;
+      const float dh = z[0] + q.z_own;
+      T* dz = reinterpret_cast<T*>(v.Dz) + ((uint64_t)p.z_q * (uint32_t)v.Np + z_n);
+      if constexpr (CELL == 1) {
+        dz[0] = announce(from_f<T>(dh * (1.f - q.z_h * q.z_h)));
+      } else {
+        const float gi = q.z_gate[0], gfl = q.z_gate[1], gfr = q.z_gate[2], go = q.z_gate[3], gu = q.z_gate[4];
+        const float tc = Act<T>::tanh(q.z_c);
+        const float dc = __builtin_bit_cast(float, u0) + dh * go * (1.f - tc * tc);
+        dz[0] = announce(from_f<T>(dc * gu * gi * (1.f - gi)));
+        dz[v.Hp] = announce(from_f<T>(dc * q.z_cl * gfl * (1.f - gfl)));
+        dz[2 * v.Hp] = announce(from_f<T>(dc * q.z_cr * gfr * (1.f - gfr)));
+        dz[3 * v.Hp] = announce(from_f<T>(dh * tc * go * (1.f - go)));
+        dz[4 * v.Hp] = announce(from_f<T>(dc * gi * (1.f - gu * gu)));
+        if (p.z_gl >= fz->row0) v.dC[p.z_gl * (uint32_t)v.Hp + z_n] = announce(dc * gfl);   // (a leaf has no use for dc)
+        if (p.z_gr >= fz->row0) v.dC[p.z_gr * (uint32_t)v.Hp + z_n] = announce(dc * gfr);
+      }
+      // One lane per child cell: its gradient body fires here.  (In the die's L2: the row is this die's.)
+      if (z_n == 0) __hip_atomic_fetch_add(&v.gmark[child], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
   }
-  __syncthreads();   // `part` is free for the workgroup's next tile
+  request();
+  return true;
 }
 
-template <int DT, int MODE, int NW>
-__global__ void __launch_bounds__(NW * 64) k_cell_small(GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+template <int DT, int MODE>
+__global__ void __launch_bounds__(Tile<MODE>::NW * 64) k_cell_small(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) float part[Tile<MODE>::PART];
   stamp_now(g.stamp);
-  const int n_ct = g.n_tiles_n;                    // column tiles of 32
-  const int rt = blockIdx.x / n_ct, ct = blockIdx.x % n_ct;
-  TileRows<MODE, NW> p;
-  TileAhead<MODE, NW, 0, 0> q;
-  tile_rows<MODE, NW>(g, rt, p);
-  tile_ahead<DT, MODE, NW, 0, 0>(g, ct, nullptr, p, q);
-  cell_small_tile<DT, MODE, NW, 0, 0>(g, rt, ct, reinterpret_cast<float*>(smem), p, q, (const ResidentB<MODE, 0>*)nullptr, nullptr, [] {});
+  const int rt = blockIdx.x / g.n_tiles_n, ct = blockIdx.x % g.n_tiles_n;   // (column tiles of one row tile side by side)
+  const TileAt t{(uint32_t)rt * Tile<MODE>::ROWS, min(Tile<MODE>::ROWS, g.M - rt * Tile<MODE>::ROWS), ct};
+  TileRows<MODE> p;
+  TileAhead<MODE, 0, 0> q;
+  const TileLane c = tile_lane<DT, MODE>(g);
+  tile_rows<MODE>(g, c, t, p);
+  tile_ahead<DT, MODE, 0, 0>(g, c, t, nullptr, p, q);
+  cell_small_tile<DT, MODE, 0, 0, false>(g, c, t, part, p, q, q.bias, (const TileB<MODE, 1>*)nullptr, nullptr, TailWait{}, nullptr, [] {}, [] {});
 }
 
 // Levels of at most this many cells take the small-level kernel (TDF_SMALL_LEVEL overrides).
@@ -794,31 +938,12 @@ static uint32_t small_level() {
   return e ? (uint32_t)atoll(e) : 1024u;
 }
 
-// Waves that split the reduction of a small-level tile: eight where the tile has one column
-// block (RNN forward, input gradient) and the reduction divides evenly, else four.
-template <typename T, int MODE> int small_tile_waves(int K) {
-  return MODE != LSTM_FWD && (K / 8) % Chunk<T>::KC == 0 && K / 8 >= Chunk<T>::KC ? 8 : 4;
-}
-
-template <typename T, int MODE, int NW> void launch_cell_small_nw(GemmArgs g, int n_col_tiles, hipStream_t s) {
-  constexpr int G = MODE == LSTM_FWD ? 5 : 1;
-  const size_t lds = (size_t)NW * G * 16 * 64 * sizeof(float);
-  static bool lds_opt_in = false;
-  if (!lds_opt_in && lds > 48 * 1024) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cell_small<DtOf<T>::value, MODE, NW>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    lds_opt_in = true;
-  }
-  g.n_tiles_n = n_col_tiles;
-  const int n_rt = (g.M + 31) / 32;
-  hipLaunchKernelGGL((k_cell_small<DtOf<T>::value, MODE, NW>), dim3(n_rt * n_col_tiles), dim3(NW * 64), lds, s, g);
-}
-template <typename T, int MODE> void launch_cell_small(GemmArgs g, int n_col_tiles, hipStream_t s) {
+template <typename T, int MODE> void launch_cell_small(GemmArgs g, hipStream_t s) {
   if (g.M <= 0) return;
-  if constexpr (MODE != LSTM_FWD) {
-    if (small_tile_waves<T, MODE>(g.K) == 8) return launch_cell_small_nw<T, MODE, 8>(g, n_col_tiles, s);
-  }
-  launch_cell_small_nw<T, MODE, 4>(g, n_col_tiles, s);
+  g.n_tiles_n = (MODE == DX_BWD ? g.N : g.Hp) / Tile<MODE>::UNITS;
+  g.fresh_row = 0xFFFFFFFFu;   // (all operands are complete)
+  const int n_rt = (g.M + Tile<MODE>::ROWS - 1) / Tile<MODE>::ROWS;
+  hipLaunchKernelGGL((k_cell_small<DtOf<T>::value, MODE>), dim3(n_rt * g.n_tiles_n), dim3(Tile<MODE>::NW * 64), 0, s, g);
 }
 
 // ---- packing of W: padded, k-contiguous [Np x Kp], and its transpose [Kp x Np] ---------------
@@ -1054,7 +1179,7 @@ __device__ __forceinline__ void dz_row(const VecArgs& v, const Engine& e, uint32
   if (v.cell_kind == 1) {
     for (int n = threadIdx.x; n < v.Hp; n += blockDim.x) {
       const float h = to_f(reinterpret_cast<const T*>(v.Hs)[o + n]);
-      dz[n] = from_f<T>((v.dH[o + n] + (v.dHn ? v.dHn[o + n] : 0.f)) * (1.f - h * h));
+      dz[n] = announce(from_f<T>((v.dH[o + n] + (v.dHn ? v.dHn[o + n] : 0.f)) * (1.f - h * h)));
     }
   } else {
     const bool cell_l = e.q_l[q] >= e.row0, cell_r = e.q_r[q] >= e.row0;   // a leaf child: c = 0, no use for dc
@@ -1067,13 +1192,13 @@ __device__ __forceinline__ void dz_row(const VecArgs& v, const Engine& e, uint32
       const float dh = v.dH[o + n] + (v.dHn ? v.dHn[o + n] : 0.f);
       const float dc = v.dC[o + n] + dh * go * (1.f - tc * tc);
       const float cl = cell_l ? v.Cs[ol + n] : 0.f, cr = cell_r ? v.Cs[orr + n] : 0.f;
-      dz[n] = from_f<T>(dc * gu * gi * (1.f - gi));
-      dz[v.Hp + n] = from_f<T>(dc * cl * gfl * (1.f - gfl));
-      dz[2 * v.Hp + n] = from_f<T>(dc * cr * gfr * (1.f - gfr));
-      dz[3 * v.Hp + n] = from_f<T>(dh * tc * go * (1.f - go));
-      dz[4 * v.Hp + n] = from_f<T>(dc * gi * (1.f - gu * gu));
-      if (cell_l) v.dC[ol + n] = dc * gfl;
-      if (cell_r) v.dC[orr + n] = dc * gfr;
+      dz[n] = announce(from_f<T>(dc * gu * gi * (1.f - gi)));
+      dz[v.Hp + n] = announce(from_f<T>(dc * cl * gfl * (1.f - gfl)));
+      dz[2 * v.Hp + n] = announce(from_f<T>(dc * cr * gfr * (1.f - gfr)));
+      dz[3 * v.Hp + n] = announce(from_f<T>(dh * tc * go * (1.f - go)));
+      dz[4 * v.Hp + n] = announce(from_f<T>(dc * gi * (1.f - gu * gu)));
+      if (cell_l) v.dC[ol + n] = announce(dc * gfl);
+      if (cell_r) v.dC[orr + n] = announce(dc * gfr);
     }
   }
 }
@@ -1145,8 +1270,8 @@ __global__ void __launch_bounds__(256) k_dz(VecArgs v, Engine e, uint32_t q0, ui
 // The cells of a level are sorted by the tag machine (= die) their instance was dealt to, and a
 // cell depends only on cells of its own instance.  So each die can walk the levels on its own:
 // workgroups i, i + 8, ... of the launch take the tiles of machine i % 8's cells, level after
-// level, with a barrier among themselves (die_sync.h) where a launch boundary would be.  Used
-// for the deep levels, where a level is a few tiles per die and costs one barrier (about 1 us)
+// level, and wait for the rows that a tile reads where a launch boundary would be.  Used
+// for the deep levels, where a level is a few tiles per die and costs about a microsecond
 // instead of one launch (~10 us).
 struct TailArgs {
   const uint32_t* level_off;   // first cell of (level, machine) in the sorted log, by sort key
@@ -1158,128 +1283,240 @@ struct TailArgs {
 };
 
 // The walk of one workgroup, number `rank` of the G of its die: forward from lvl_first up, DX_BWD from lvl_last down.
-// RES > 0: it keeps to one column tile (the tiles divide evenly among the workgroups) with that tile's weight operands
-// in registers.
-// What bounds it: latency.  A level is the round trip of the barrier (about 1 us), the operands that the level before
-// has written, the products of an eighth or a quarter of the reduction, their sum through LDS, and the store's way to
-// the L2.  The rest is requested ahead (TileRows, TileAhead), by the first tile that a workgroup has in a level; further
-// tiles of the same level request theirs on the spot.
-template <int DT, int MODE, int NW, int RES, int CELL>
-__device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t, uint32_t die, uint32_t rank, uint32_t G, float* part,
-                                            const ResidentB<MODE, RES>* rb, const DzFuse* fz, uint32_t* sh_ok) {
-  typedef typename TypeOf<DT>::type T;
-  DieSync* sy = t.sync + die;
+// RES > 0: it keeps to one column tile (G is a multiple of the column tiles) with that tile's weight operands in registers.
+// What bounds it: latency.  A level is the way of the rows that the level before has written to the L2 and back (about 1000
+// clocks until a look that finds them has returned), the products of a fraction of the reduction (100), their sum through
+// LDS (400), the gates and stores (600 to 800) and the requests for what comes (500 to 1000): 1.6 to 2.4 us.  Everything
+// else is requested ahead, in the order of the workgroup's tiles, whatever levels these are in.
+// With a barrier of the die's workgroups between the levels and tiles of 32 x 32: 4,095 levels of a TreeRNN of 512 units
+// 11.4 ms forward and 15.0 gradient, now 7.2 and 6.4; 112 levels of a TreeLSTM of 256 units 576 us, now 361.
+template <int DT, int MODE, int RES, int CELL>
+__device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& ta, uint32_t die, uint32_t rank, uint32_t G, float* part,
+                                            const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, uint32_t* failed) {
+  typedef Tile<MODE> TL;
+  DieSync* const sy = ta.sync + die;
+  const TailWait w{sy, ta.spin_ticks};
   const uint32_t n_ct = (uint32_t)g.n_tiles_n;
   const uint32_t first = RES > 0 ? rank / n_ct : rank, step = RES > 0 ? G / n_ct : G;
-  auto row_tile = [&](uint32_t tile) { return (int)(RES > 0 ? tile : tile / n_ct); };
-  auto col_tile = [&](uint32_t tile) { return (int)(RES > 0 ? rank % n_ct : tile % n_ct); };
+  const uint32_t n_lvl = ta.lvl_last + 1 - ta.lvl_first;
+  // the workgroup's tiles in order: tile `t` of the k-th level of the walk, whose cells of this die are q0 .. end - 1
+  // (the offsets of the level after it have been requested)
+  uint32_t k = 0, t = first, q0, end, next_q0, next_end;
+  auto offsets = [&](uint32_t kk, uint32_t& from, uint32_t& to) {
+    kk = min(kk, n_lvl - 1);
+    const uint32_t* o = ta.level_off + (size_t)(MODE == DX_BWD ? ta.lvl_last - kk : ta.lvl_first + kk) * LEVEL_KEY_DIES + die;
+    from = o[0];
+    to = o[1];
+  };
+  auto take = [&](uint32_t from, uint32_t to) {
+    q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)from);
+    end = (uint32_t)__builtin_amdgcn_readfirstlane((int)to);
+  };
+  auto tile_of = [&](TileAt& r) {
+    const uint32_t rows = (end - q0 + TL::ROWS - 1) / TL::ROWS, row = RES > 0 ? t : t / n_ct;
+    if (row >= rows) return false;
+    const uint32_t at = q0 + row * TL::ROWS;
+    r = TileAt{at, (int)min((uint32_t)TL::ROWS, end - at), (int)(RES > 0 ? rank % n_ct : t % n_ct)};
+    t += step;
+    return true;
+  };
+  auto next = [&]() -> TileAt {
+    TileAt r{0, 0, 0};
+    if (tile_of(r) || k + 1 >= n_lvl) return r;
+    take(next_q0, next_end);
+    for (++k, t = first; !tile_of(r) && k + 1 < n_lvl; t = first) {   // (levels without a tile for this workgroup)
+      uint32_t from, to;
+      offsets(++k, from, to);
+      take(from, to);
+    }
+    return r;
+  };
+  {
+    uint32_t from, to;
+    offsets(0, from, to);
+    take(from, to);
+  }
+  const TileLane c = tile_lane<DT, MODE>(g);
+  float bias[TL::G] = {};
+  if constexpr (MODE != DX_BWD && RES > 0) {
+#pragma unroll
+    for (int j = 0; j < TL::G; ++j) bias[j] = g.bias[j * g.Hp + (int)(rank % n_ct) * TL::UNITS + c.col];
+  }
+  offsets(1, next_q0, next_end);
+  TileAt t0 = next();
+  offsets(k + 1, next_q0, next_end);
+  TileAt t1 = next();
+  offsets(k + 1, next_q0, next_end);
+  TileAt t2 = next(), t3;
+  offsets(k + 1, next_q0, next_end);
+  TileRows<MODE> p0{}, p1{}, p2{}, p3{};
+  TileAhead<MODE, RES, CELL> a0{}, a1{};
+  tile_rows<MODE>(g, c, t0, p0);
+  tile_rows<MODE>(g, c, t1, p1);
+  tile_rows<MODE>(g, c, t2, p2);
+  tile_rows2<DT, MODE, CELL>(g, c, t0, fz, p0);
+  tile_rows2<DT, MODE, CELL>(g, c, t1, fz, p1);
+  if (t0.M) tile_ahead<DT, MODE, RES, CELL>(g, c, t0, fz, p0, a0);
+  // A tile, and behind its own loads the requests for the next one, the rows of the children's children for the one after
+  // that and the rows of a third.  The registers that these go to take turns by name: a copy from tile to tile would wait
+  // for them in the middle of the tile that has just asked.
+  auto tile = [&](uint32_t side, const TileAt& t, const TileRows<MODE>& p, const TileAhead<MODE, RES, CELL>& a, const TileAt& ta1,
+                  const TileRows<MODE>& pa1, TileAhead<MODE, RES, CELL>& a1, const TileAt& ta2, TileRows<MODE>& pa2, TileAt& ta3,
+                  TileRows<MODE>& pa3) __attribute__((always_inline)) {
+    return t.M && cell_small_tile<DT, MODE, RES, CELL, true>(g, c, t, part + side * TL::PART, p, a, RES > 0 ? bias : a.bias, b, fz, w, failed + side, [&] { ta3 = next(); }, [&] {
+      tile_rows<MODE>(g, c, ta3, pa3);
+      tile_rows2<DT, MODE, CELL>(g, c, ta2, fz, pa2);
+      if (ta1.M) tile_ahead<DT, MODE, RES, CELL>(g, c, ta1, fz, pa1, a1);
+      offsets(k + 1, next_q0, next_end);
+      if (rank == 0 && threadIdx.x == 0) __hip_atomic_store(&sy->at, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    });
+  };
+  for (uint32_t n = 0;; ++n) {
+    if (!tile(0, t0, p0, a0, t1, p1, a1, t2, p2, t3, p3)) return;
+    if (!tile(1, t1, p1, a1, t2, p2, a0, t3, p3, t0, p0)) return;
+    if (!tile(0, t2, p2, a0, t3, p3, a1, t0, p0, t1, p1)) return;
+    if (!tile(1, t3, p3, a1, t0, p0, a0, t1, p1, t2, p2)) return;
+    if ((n & 7u) == 7u && threadIdx.x == 0) __hip_atomic_fetch_add(&sy->beat, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+}
+
+// The last workgroup of a die goes ahead of the others and touches what their requests will lead to (which is in HBM,
+// or in other dies' L2s until the launch before has ended): a wave's loads return in order, so a tile that had to wait for
+// a request of the tile before on its way from HBM would wait 2000 clocks at the rows it needs, which the L2 has.
+// Each of its waves takes every NW-th level, at most TAIL_AHEAD levels and about a megabyte ahead of the tiles.  Nobody waits for it,
+// and it waits for the tiles only so long.
+constexpr uint32_t TAIL_AHEAD = 12;
+template <int DT, int MODE, int CELL>
+__device__ __forceinline__ void scout_levels(const GemmArgs& g, const TailArgs& ta, uint32_t die, const DzFuse* fz) {
+  typedef typename TypeOf<DT>::type T;
+  constexpr uint32_t NW = Tile<MODE>::NW;
+  const uint32_t n_lvl = ta.lvl_last + 1 - ta.lvl_first, lane = threadIdx.x & 63;
+  const int row_b = g.Hp * (int)sizeof(T);
+  uint32_t seen = 0;
+  // the lines of the rows of `n` lanes' (those with `has`): a lane takes a line, four loads in flight
+  auto touch = [&](bool has, const void* base, uint64_t offset, int bytes, uint32_t n) {
+    const uint32_t lines = (uint32_t)(bytes + 127) / 128u;
+    const uint32_t lo = (uint32_t)offset, hi = (uint32_t)(offset >> 32);
+    const unsigned long long who = __ballot(has);
+    for (uint32_t i0 = 0; i0 < n * lines; i0 += 256u) {
+      uint32_t x[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t i = i0 + 64u * j + lane, r = min(i / lines, 63u);
+        const uint64_t off = (uint64_t)__shfl(lo, (int)r) | ((uint64_t)__shfl(hi, (int)r) << 32);
+        if (i < n * lines && ((who >> r) & 1ull))
+          x[j] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(base) + off + (i % lines) * 128u);
+      }
+      seen |= x[0] | x[1] | x[2] | x[3];
+    }
+  };
+  for (uint32_t k = (uint32_t)wave_of(); k < n_lvl; k += NW) {
+    const uint32_t* o = ta.level_off + (size_t)(MODE == DX_BWD ? ta.lvl_last - k : ta.lvl_first + k) * LEVEL_KEY_DIES + die;
+    const uint32_t q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)o[0]), end = (uint32_t)__builtin_amdgcn_readfirstlane((int)o[1]);
+    const uint32_t ahead = end - q0 > 64u ? 2u : TAIL_AHEAD;   // (a wide level's rows are some hundred KB)
+    for (int looks = 0; looks < 1000; ++looks) {
+      const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&ta.sync[die].at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      if (at + ahead >= k) break;
+      __builtin_amdgcn_s_sleep(8);
+    }
+    for (uint32_t q = q0; q < end; q += 64u) {
+      const uint32_t n = min(64u, end - q);
+      const bool on = lane < n;
+      const uint32_t l = on ? g.l[q + lane] : 0u, r = on ? g.r[q + lane] : 0u;
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        const uint32_t row = side ? r : l;
+        if constexpr (MODE != DX_BWD) {
+          const bool ready = on && row < g.fresh_row;
+          touch(ready, g.Hs, (uint64_t)row * (uint32_t)row_b, row_b, n);
+          if (MODE == LSTM_FWD) touch(ready && row >= g.leaf_rows, g.Cs, (uint64_t)row * (uint32_t)(g.Hp * 4), g.Hp * 4, n);
+        } else {
+          const bool cell = on && row >= fz->row0 && row - fz->row0 >= fz->q_first;
+          const VecArgs& v = *fz->v;
+          touch(cell, v.gmark, (uint64_t)row * 4u, 4, n);
+          if (v.dHn) touch(cell, v.dHn, (uint64_t)row * (uint32_t)(g.Hp * 4), g.Hp * 4, n);
+          if constexpr (CELL == 1) {
+            touch(cell, v.Hs, (uint64_t)row * (uint32_t)row_b, row_b, n);
+          } else {
+            const uint32_t z = cell ? row - fz->row0 : 0u, zl = cell ? fz->q_l[z] : 0u, zr = cell ? fz->q_r[z] : 0u;
+            touch(cell, v.gates, (uint64_t)z * (uint32_t)(v.Np * (int)sizeof(T)), v.Np * (int)sizeof(T), n);
+            touch(cell, v.Cs, (uint64_t)row * (uint32_t)(g.Hp * 4), g.Hp * 4, n);
+            touch(cell && zl >= fz->row0, v.Cs, (uint64_t)zl * (uint32_t)(g.Hp * 4), g.Hp * 4, n);
+            touch(cell && zr >= fz->row0, v.Cs, (uint64_t)zr * (uint32_t)(g.Hp * 4), g.Hp * 4, n);
+          }
+        }
+      }
+    }
+  }
+  asm volatile("" ::"v"(seen));
+}
+
+__device__ __forceinline__ void tail_begin(DieSync* sy, uint32_t* failed) {
+  if (threadIdx.x < 2) failed[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) atomicOr(&sy->xcc_mask, 1u << xcc_id());   // (looked at behind die_meet's barrier)
+}
+
+template <int DT, int MODE, int RES>
+__global__ void __launch_bounds__(Tile<MODE>::NW * 64, RES == 8 ? 1 : Tile<MODE>::NW / 2) k_tail_fwd(GemmArgs g, TailArgs t) {
+  typedef typename TypeOf<DT>::type T;
+  typedef Tile<MODE> TL;
+  __shared__ __attribute__((aligned(16))) float part[2 * TL::PART];
+  __shared__ uint32_t sh_ok, failed[2];
+  stamp_now(g.stamp);
+  const uint32_t die = blockIdx.x % XCDS, rank = blockIdx.x / XCDS, G = gridDim.x / XCDS - 1u;
+  if (die >= t.n_dies) return;
+  if (rank == G) return scout_levels<DT, MODE, 0>(g, t, die, nullptr);
+  // A level here is one link of a dependency chain: these waves are bound by latency, and other
+  // kernels (the wide levels of other instances) may share the compute unit: issue before them.
+  __builtin_amdgcn_s_setprio(3);
+  DieSync* sy = t.sync + die;
+  tail_begin(sy, failed);
+  const int wave = wave_of(), lane = threadIdx.x & 63;
+  TileB<MODE, (RES > 0 ? RES : 1)> b;
+  if constexpr (RES > 0) {
+    const int steps = g.K / Chunk<T>::KC, s0 = TL::first_step(steps, wave);
+    load_b<DT, MODE, RES>(g, (int)(rank % (uint32_t)g.n_tiles_n), s0, TL::first_step(steps, wave + 1) - s0, b);
+  }
+  // The rows that this die's workgroups will write: not written yet.  A level's rows are shared out to eight waves.
   const uint32_t n_lvl = t.lvl_last + 1 - t.lvl_first;
-  struct Level { uint32_t q0, end; };   // the die's cells of a level
-  auto level = [&](uint32_t k) {   // the k-th level of the walk (the last one for those beyond it)
-    k = min(k, n_lvl - 1);
-    const uint32_t* p = t.level_off + (size_t)(MODE == DX_BWD ? t.lvl_last - k : t.lvl_first + k) * LEVEL_KEY_DIES + die;
-    return Level{p[0], p[1]};
-  };
-  auto uniform = [](const Level& l) {
-    return Level{(uint32_t)__builtin_amdgcn_readfirstlane((int)l.q0), (uint32_t)__builtin_amdgcn_readfirstlane((int)l.end)};
-  };
-  auto args = [&](const Level& l) {
-    GemmArgs gl = g;
-    gl.M = (int)(l.end - l.q0);
-    gl.l = g.l + l.q0;
-    gl.r = g.r + l.q0;
-    if constexpr (MODE == DX_BWD) {
-      gl.A = reinterpret_cast<const T*>(g.A) + (size_t)l.q0 * g.lda;
-    } else {
-      gl.out0 = g.out0 + l.q0;
-      gl.gates = g.gates ? reinterpret_cast<T*>(g.gates) + (size_t)l.q0 * g.ldg : nullptr;
+  const u32x4 none = {F_NONE, F_NONE, F_NONE, F_NONE};
+  for (uint32_t i = rank * TL::NW + wave; i < n_lvl * 8u; i += G * TL::NW) {
+    const uint32_t* o = t.level_off + (size_t)(t.lvl_first + i / 8u) * LEVEL_KEY_DIES + die;
+    const uint32_t end = o[1];
+    for (uint32_t q = o[0] + i % 8u; q < end; q += 8u) {
+      T* h = reinterpret_cast<T*>(g.Hs_out) + (size_t)(g.out0 + q) * g.Hp;
+      for (int c = lane * Chunk<T>::EPC; c < g.Hp; c += 64 * Chunk<T>::EPC) *reinterpret_cast<u32x4*>(h + c) = none;
+      if constexpr (MODE == LSTM_FWD)
+        for (int c = lane * 4; c < g.Hp; c += 256) *reinterpret_cast<u32x4*>(g.Cs + (size_t)(g.out0 + q) * g.Hp + c) = none;
     }
-    return gl;
-  };
-  auto tiles_of = [&](const Level& l) { return (l.end - l.q0 + 31) / 32 * (RES > 0 ? 1u : n_ct); };
-  Level l0 = uniform(level(0)), l1 = uniform(level(1)), l2 = uniform(level(2));
-  TileRows<MODE, NW> p0{}, p1{}, p2{};
-  TileAhead<MODE, NW, RES, CELL> q0{}, q1{};
-  if (first < tiles_of(l0)) {
-    tile_rows<MODE, NW>(args(l0), row_tile(first), p0);
-    tile_ahead<DT, MODE, NW, RES, CELL>(args(l0), col_tile(first), fz, p0, q0);
   }
-  if (first < tiles_of(l1)) tile_rows<MODE, NW>(args(l1), row_tile(first), p1);
-  for (uint32_t k = 0; k < n_lvl; ++k) {
-    const GemmArgs gl = args(l0);
-    Level l3;
-    auto ahead = [&] {
-      l3 = level(k + 3);
-      if (first < tiles_of(l2)) tile_rows<MODE, NW>(args(l2), row_tile(first), p2);
-      if (first < tiles_of(l1)) tile_ahead<DT, MODE, NW, RES, CELL>(args(l1), col_tile(first), fz, p1, q1);
-    };
-    if (first < tiles_of(l0)) cell_small_tile<DT, MODE, NW, RES, CELL>(gl, row_tile(first), col_tile(first), part, p0, q0, rb, fz, ahead);
-    else ahead();
-    for (uint32_t tile = first + step; tile < tiles_of(l0); tile += step) {
-      tile_rows<MODE, NW>(gl, row_tile(tile), p0);
-      tile_ahead<DT, MODE, NW, RES, CELL>(gl, col_tile(tile), fz, p0, q0);
-      cell_small_tile<DT, MODE, NW, RES, CELL>(gl, row_tile(tile), col_tile(tile), part, p0, q0, rb, fz, [] {});
-    }
-    die_arrive(sy, k);
-    if (!die_wait(sy, G, k, t.spin_ticks, sh_ok)) return;
-    l0 = l1; l1 = l2; l2 = uniform(l3);
-    p0 = p1; p1 = p2;
-    q0 = q1;
-  }
+  if (!die_meet(sy, G, t.spin_ticks, &sh_ok)) return;
+  walk_levels<DT, MODE, RES, 0>(g, t, die, rank, G, part, &b, nullptr, failed);
 }
 
-template <int DT, int MODE, int NW>
-__global__ void __launch_bounds__(NW * 64) k_tail_fwd(GemmArgs g, TailArgs t) {
+// Gradient pass over the same levels, deepest first.  (dz of a level's cells: from their parents' tiles, or, for the
+// roots, from k_dz_tail_roots.  Those that come from tiles were marked as not written by k_tail_fwd.)
+template <int DT, int CELL, int RES>
+__global__ void __launch_bounds__(Tile<DX_BWD>::NW * 64, CELL == 1 && RES <= 5 ? 4 : 2) k_tail_bwd(GemmArgs g, VecArgs v, Engine e, TailArgs t) {
   typedef typename TypeOf<DT>::type T;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ uint32_t sh_ok;
-  float* part = reinterpret_cast<float*>(smem);
+  typedef Tile<DX_BWD> TL;
+  __shared__ __attribute__((aligned(16))) float part[2 * TL::PART];
+  __shared__ uint32_t sh_ok, failed[2];
   stamp_now(g.stamp);
-  const uint32_t die = blockIdx.x % XCDS, rank = blockIdx.x / XCDS, G = gridDim.x / XCDS;
+  const uint32_t die = blockIdx.x % XCDS, rank = blockIdx.x / XCDS, G = gridDim.x / XCDS - 1u;
   if (die >= t.n_dies) return;
-  // A level here is one link of a dependency chain: these waves are bound by latency, and other
-  // kernels (the wide levels of other instances) may share the compute unit: issue before them.
-  __builtin_amdgcn_s_setprio(3);
-  DieSync* sy = t.sync + die;
-  if (threadIdx.x == 0) atomicOr(&sy->xcc_mask, 1u << xcc_id());
-  const int n_ct = g.n_tiles_n;
-  constexpr int RES = 8;
-  if (G % (uint32_t)n_ct == 0 && g.K / NW / Chunk<T>::KC <= RES) {
-    ResidentB<MODE, RES> rb;
-    load_resident_b<DT, MODE, NW, RES>(g, (int)(rank % n_ct), rb);
-    walk_levels<DT, MODE, NW, RES, 0>(g, t, die, rank, G, part, &rb, nullptr, &sh_ok);
-  } else {
-    walk_levels<DT, MODE, NW, 0, 0>(g, t, die, rank, G, part, (const ResidentB<MODE, 0>*)nullptr, nullptr, &sh_ok);
-  }
-}
-
-// Gradient pass over the same levels, deepest first: dz of the die's cells of a level, barrier,
-// their input gradients, barrier.
-template <int DT, int CELL, int NW>
-__global__ void __launch_bounds__(NW * 64) k_tail_bwd(GemmArgs g, VecArgs v, Engine e, TailArgs t) {
-  typedef typename TypeOf<DT>::type T;
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ uint32_t sh_ok;
-  float* part = reinterpret_cast<float*>(smem);
-  stamp_now(g.stamp);
-  const uint32_t die = blockIdx.x % XCDS, rank = blockIdx.x / XCDS, G = gridDim.x / XCDS;
-  if (die >= t.n_dies) return;
-  // A level here is one link of a dependency chain: these waves are bound by latency, and other
-  // kernels (the wide levels of other instances) may share the compute unit: issue before them.
-  __builtin_amdgcn_s_setprio(3);
-  DieSync* sy = t.sync + die;
-  if (threadIdx.x == 0) atomicOr(&sy->xcc_mask, 1u << xcc_id());
-  const int n_ct = g.n_tiles_n;
-  constexpr int RES = 10;
-  // (dz of a level's cells: from their parents' tiles, or, for the roots, from k_dz_tail_roots)
   const DzFuse fz{&v, e.q_l, e.q_r, e.row0, t.q_first};
-  if (G % (uint32_t)n_ct == 0 && g.K / NW / Chunk<T>::KC <= RES) {
-    ResidentB<DX_BWD, RES> rb;
-    load_resident_b<DT, DX_BWD, NW, RES>(g, (int)(rank % n_ct), rb);
-    walk_levels<DT, DX_BWD, NW, RES, CELL>(g, t, die, rank, G, part, &rb, &fz, &sh_ok);
-  } else {
-    walk_levels<DT, DX_BWD, NW, 0, CELL>(g, t, die, rank, G, part, (const ResidentB<DX_BWD, 0>*)nullptr, &fz, &sh_ok);
+  if (rank == G) return scout_levels<DT, DX_BWD, CELL>(g, t, die, &fz);
+  __builtin_amdgcn_s_setprio(3);   // (see k_tail_fwd)
+  DieSync* sy = t.sync + die;
+  tail_begin(sy, failed);
+  TileB<DX_BWD, (RES > 0 ? RES : 1)> b;
+  if constexpr (RES > 0) {
+    const int steps = g.K / Chunk<T>::KC, wave = wave_of(), s0 = TL::first_step(steps, wave);
+    load_b<DT, DX_BWD, RES>(g, (int)(rank % (uint32_t)g.n_tiles_n), s0, TL::first_step(steps, wave + 1) - s0, b);
   }
+  if (!die_meet(sy, G, t.spin_ticks, &sh_ok)) return;
+  walk_levels<DT, DX_BWD, RES, CELL>(g, t, die, rank, G, part, &b, &fz, failed);
 }
 
 // ---- numbering of the state rows by the sorted schedule ------------------------------------------
@@ -1779,8 +2016,8 @@ template <typename T> static void cell_fwd_t(const VecArgs& v, const Engine& e, 
   g.narrow = !v.wide_offsets && (uint64_t)(e.row0 + q0 + count) * (uint64_t)v.Hp * 4u < (1ull << 32) &&
              (uint64_t)count * (uint64_t)v.Np * sizeof(T) < (1ull << 32);
   if (count <= small_level()) {
-    if (v.cell_kind == 2) launch_cell_small<T, LSTM_FWD>(g, v.Hp / 32, s);
-    else launch_cell_small<T, RNN_FWD>(g, v.Hp / 32, s);
+    if (v.cell_kind == 2) launch_cell_small<T, LSTM_FWD>(g, s);
+    else launch_cell_small<T, RNN_FWD>(g, s);
   } else if (v.cell_kind == 2) {
     launch_gemm<T, LSTM_FWD>(g, (v.Hp / 32 + 1) / 2, 1, s);
   } else {
@@ -1802,7 +2039,7 @@ template <typename T> static void cell_bwd_t(const VecArgs& v, const Engine& e, 
   g.B = v.WpT; g.ldb = v.Np; g.Bf = v.WfT;
   g.Hp = v.Hp; g.l = e.q_l + q0; g.r = e.q_r + q0;
   g.C = v.dH;
-  if (count <= small_level()) launch_cell_small<T, DX_BWD>(g, v.Kp / 32, s);
+  if (count <= small_level()) launch_cell_small<T, DX_BWD>(g, s);
   else launch_gemm<T, DX_BWD>(g, (v.Kp + 127) / 128, 1, s);
 }
 void vec_cell_bwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, hipStream_t s) {
@@ -1813,57 +2050,80 @@ uint32_t vec_small_level() { return small_level(); }
 
 // The levels lvl_first .. lvl_last in one launch, every die walking its own cells (k_tail_fwd).
 // level_off: device array of first cells by sort key; sync: eight zeroed DieSync records.
-template <typename T> static void tail_fwd_t(const VecArgs& v, const Engine& e, const TailArgs& t, int per_die, int save_gates,
-                                             hipStream_t s) {
+// Workgroups per die: groups of n_ct, one per column tile; as many groups as the widest level has row tiles and as fit
+// `slots` with one left for the workgroup that goes ahead (alone on a compute unit it does not slow the tiles there down:
+// 1,200 cells a level of a TreeLSTM, three groups of 16 on 32 compute units 383 us, four 406).  0: not even one group fits, or a
+// wave's weight operands do not fit its registers (chunk steps > RES): any workgroup then takes any tile.
+static int tail_wgs(int slots, int n_ct, uint32_t row_tiles) {
+  return (int)std::min<uint32_t>((uint32_t)std::max(slots - 1, n_ct) / n_ct, std::max(row_tiles, 1u)) * (slots >= n_ct ? n_ct : 0);
+}
+template <typename T, int MODE, int RES> static void launch_tail_fwd(const GemmArgs& g, const TailArgs& t, int wgs, hipStream_t s) {
+  hipLaunchKernelGGL((k_tail_fwd<DtOf<T>::value, MODE, RES>), dim3((wgs + 1) * (int)XCDS), dim3(Tile<MODE>::NW * 64), 0, s, g, t);
+}
+template <typename T, int MODE> static void tail_fwd_mode(GemmArgs g, const TailArgs& t, int cus_per_die, uint32_t row_tiles, hipStream_t s) {
+  g.n_tiles_n = g.Hp / Tile<MODE>::UNITS;
+  const int n = Tile<MODE>::steps_most(g.K / Chunk<T>::KC);
+  const int slots = cus_per_die * (n <= 4 ? 2 : 1);   // (two workgroups share a compute unit, but for the variants with most weights in registers)
+  const int wgs = tail_wgs(slots, g.n_tiles_n, row_tiles);
+  if (wgs && n <= 2) launch_tail_fwd<T, MODE, 2>(g, t, wgs, s);
+  else if (wgs && n <= 4) launch_tail_fwd<T, MODE, 4>(g, t, wgs, s);
+  else if (wgs && n <= 8) launch_tail_fwd<T, MODE, 8>(g, t, wgs, s);
+  else launch_tail_fwd<T, MODE, 0>(g, t, cus_per_die, s);
+}
+template <typename T> static void tail_fwd_t(const VecArgs& v, const Engine& e, const TailArgs& t, uint32_t n_cells, int per_die,
+                                             uint32_t row_tiles, int save_gates, hipStream_t s) {
   GemmArgs g{};
   g.N = v.Np; g.K = v.Kp;
-  g.B = v.Wp; g.ldb = v.Kp; g.Bf = v.Wf;
+  g.Bf = v.Wf;
   g.Hs = v.Hs; g.Hp = v.Hp;
   g.stamp = v.stamp;
   g.out0 = e.row0; g.l = e.q_l; g.r = e.q_r;
   g.bias = v.bp; g.Hs_out = v.Hs; g.Cs = v.Cs; g.leaf_rows = e.row0;
+  g.fresh_row = e.row0 + t.q_first;
+  g.fresh_narrow = !v.wide_offsets && (uint64_t)n_cells * (uint64_t)v.Hp * sizeof(T) < (1ull << 32);
   g.gates = v.gates; g.ldg = v.Np; g.save_gates = save_gates && v.gates;
-  g.n_tiles_n = v.Hp / 32;
-  const int grid = std::max(per_die, 1) * (int)XCDS;
-  if (v.cell_kind == 2) {
-    const size_t lds = (size_t)4 * 5 * 16 * 64 * sizeof(float);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tail_fwd<DtOf<T>::value, LSTM_FWD, 4>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((k_tail_fwd<DtOf<T>::value, LSTM_FWD, 4>), dim3(grid), dim3(256), lds, s, g, t);
-  } else if (small_tile_waves<T, RNN_FWD>(g.K) == 8) {
-    const size_t lds = (size_t)8 * 16 * 64 * sizeof(float);
-    hipLaunchKernelGGL((k_tail_fwd<DtOf<T>::value, RNN_FWD, 8>), dim3(grid), dim3(512), lds, s, g, t);
-  } else {
-    const size_t lds = (size_t)4 * 16 * 64 * sizeof(float);
-    hipLaunchKernelGGL((k_tail_fwd<DtOf<T>::value, RNN_FWD, 4>), dim3(grid), dim3(256), lds, s, g, t);
+  if (save_gates) {
+    g.dz_fill = v.Dz;
+    g.dc_fill = v.dC;
   }
+  if (v.cell_kind == 2) tail_fwd_mode<T, LSTM_FWD>(g, t, per_die, row_tiles, s);
+  else tail_fwd_mode<T, RNN_FWD>(g, t, per_die, row_tiles, s);
 }
-// per_die: workgroups per accelerator die (all of one launch must be resident together)
+// The tail's cells are the n_cells from q_first on.  per_die: compute units per accelerator die for this launch (all of its
+// workgroups must be resident together); most_rows: cells of a level on a die, at most
 void vec_tail_fwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
-                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, int save_gates, hipStream_t s) {
-  TailArgs t{level_off, lvl_first, lvl_last, n_dies, (DieSync*)sync, spin_ticks};
-  if (v.dtype == TDF_BF16) tail_fwd_t<__bf16>(v, e, t, per_die, save_gates, s); else tail_fwd_t<float>(v, e, t, per_die, save_gates, s);
+                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t n_cells, uint32_t most_rows,
+                  int save_gates, hipStream_t s) {
+  TailArgs t{level_off, lvl_first, lvl_last, n_dies, (DieSync*)sync, spin_ticks, q_first};
+  const uint32_t tiles = (most_rows + 15u) / 16u;
+  if (v.dtype == TDF_BF16) tail_fwd_t<__bf16>(v, e, t, n_cells, per_die, tiles, save_gates, s);
+  else tail_fwd_t<float>(v, e, t, n_cells, per_die, tiles, save_gates, s);
 }
 
-template <typename T> static void tail_bwd_t(const VecArgs& v, const Engine& e, const TailArgs& t, int per_die, hipStream_t s) {
+template <typename T, int CELL, int RES>
+static void launch_tail_bwd(const GemmArgs& g, const VecArgs& v, const Engine& e, const TailArgs& t, int wgs, hipStream_t s) {
+  hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, CELL, RES>), dim3((wgs + 1) * (int)XCDS), dim3(Tile<DX_BWD>::NW * 64), 0, s, g, v, e, t);
+}
+template <typename T, int CELL>
+static void tail_bwd_cell(const GemmArgs& g, const VecArgs& v, const Engine& e, const TailArgs& t, int cus_per_die, uint32_t row_tiles,
+                          hipStream_t s) {
+  const int n = Tile<DX_BWD>::steps_most(g.K / Chunk<T>::KC);
+  const int wgs = tail_wgs(cus_per_die * (n <= 5 && CELL == 1 ? 2 : 1), g.n_tiles_n, row_tiles);
+  if (wgs && n <= 5) launch_tail_bwd<T, CELL, 5>(g, v, e, t, wgs, s);
+  else if (wgs && n <= 10) launch_tail_bwd<T, CELL, 10>(g, v, e, t, wgs, s);
+  else launch_tail_bwd<T, CELL, 0>(g, v, e, t, cus_per_die, s);
+}
+template <typename T> static void tail_bwd_t(const VecArgs& v, const Engine& e, const TailArgs& t, int per_die, uint32_t row_tiles,
+                                             hipStream_t s) {
   GemmArgs g{};
   g.N = v.Kp; g.K = v.Np;
   g.A = v.Dz; g.lda = v.Np;
-  g.B = v.WpT; g.ldb = v.Np; g.Bf = v.WfT;
+  g.Bf = v.WfT;
   g.Hp = v.Hp; g.l = e.q_l; g.r = e.q_r;
   g.C = v.dH;
-  g.n_tiles_n = v.Kp / 32;
-  const int grid = std::max(per_die, 1) * (int)XCDS;
-  const bool lstm = v.cell_kind == 2;
-  if (small_tile_waves<T, DX_BWD>(g.K) == 8) {
-    const size_t lds = (size_t)8 * 16 * 64 * sizeof(float);
-    if (lstm) hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 2, 8>), dim3(grid), dim3(512), lds, s, g, v, e, t);
-    else hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 1, 8>), dim3(grid), dim3(512), lds, s, g, v, e, t);
-  } else {
-    const size_t lds = (size_t)4 * 16 * 64 * sizeof(float);
-    if (lstm) hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 2, 4>), dim3(grid), dim3(256), lds, s, g, v, e, t);
-    else hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, 1, 4>), dim3(grid), dim3(256), lds, s, g, v, e, t);
-  }
+  g.n_tiles_n = v.Kp / Tile<DX_BWD>::UNITS;
+  if (v.cell_kind == 2) tail_bwd_cell<T, 2>(g, v, e, t, per_die, row_tiles, s);
+  else tail_bwd_cell<T, 1>(g, v, e, t, per_die, row_tiles, s);
 }
 // After the level sort: rows numbered by the sorted schedule, references translated.
 void vec_number_rows(const Engine& e, uint32_t n_leaf, uint32_t n_cell, int has_head, int has_root, hipStream_t s) {
@@ -1881,12 +2141,13 @@ void vec_translate_rows(const Engine& e, const uint32_t* row_of, const LaneTotal
 }
 
 void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
-                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, const uint32_t* root_rows,
-                  hipStream_t s) {
+                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t most_rows,
+                  const uint32_t* root_rows, hipStream_t s) {
   TailArgs t{level_off, lvl_first, lvl_last, n_dies, (DieSync*)sync, spin_ticks, q_first};
   if (v.dtype == TDF_BF16) hipLaunchKernelGGL(k_dz_tail_roots<TDF_BF16>, dim3(e.n_inst), dim3(256), 0, s, v, e, root_rows, q_first);
   else hipLaunchKernelGGL(k_dz_tail_roots<TDF_F32>, dim3(e.n_inst), dim3(256), 0, s, v, e, root_rows, q_first);
-  if (v.dtype == TDF_BF16) tail_bwd_t<__bf16>(v, e, t, per_die, s); else tail_bwd_t<float>(v, e, t, per_die, s);
+  if (v.dtype == TDF_BF16) tail_bwd_t<__bf16>(v, e, t, per_die, (most_rows + 15u) / 16u, s);
+  else tail_bwd_t<float>(v, e, t, per_die, (most_rows + 15u) / 16u, s);
 }
 
 // cls < 0: every instance; else only the instances of that class (Engine::inst_class)

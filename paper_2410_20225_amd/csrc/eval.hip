@@ -38,10 +38,11 @@ void vec_cell_fwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count
 void vec_cell_bwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, hipStream_t s);
 uint32_t vec_small_level();
 void vec_tail_fwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
-                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, int save_gates, hipStream_t s);
+                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t n_cells, uint32_t most_rows,
+                  int save_gates, hipStream_t s);
 void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
-                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, const uint32_t* root_rows,
-                  hipStream_t s);
+                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t most_rows,
+                  const uint32_t* root_rows, hipStream_t s);
 void vec_translate_rows(const Engine& e, const uint32_t* row_of, const LaneTotals* t, uint32_t most, int has_head, int has_root,
                         float* zero, uint32_t n_zero, hipStream_t s);
 void vec_number_rows(const Engine& e, uint32_t n_leaf, uint32_t n_cell, int has_head, int has_root, hipStream_t s);
@@ -728,6 +729,10 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   uint32_t sh_last = 0, deep_base = 0, q_deep0 = 0, n_wide_levels = 0;
   const uint32_t* level_off = nullptr;   // by sort key; in the pinned buffer
   auto lvl_begin = [&](uint32_t lvl) { return level_off[(size_t)lvl * LEVEL_KEY_DIES]; };
+  uint32_t tail_rows = 0;    // cells of one level and die among the tail's levels, at most
+  auto most_rows = [&](uint32_t key, uint32_t end_key) {
+    for (tail_rows = 0; key < end_key; ++key) tail_rows = std::max(tail_rows, level_off[key + 1] - level_off[key]);
+  };
   if (dev == TDF_OK && P.vec) {
     // ---- vector operators: leaves at once, cells level by level --------------------------
     // From here on the next evaluation's tag machine may run (not beside an evaluation in the static
@@ -752,7 +757,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       end(TDF_PHASE_LEAVES, 2);
       if (with_grad) HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_sort, s));
     }
-    const int deep_wgs = getenv("TDF_DEEP_WGS") ? std::max(1, atoi(getenv("TDF_DEEP_WGS"))) : 16;   // workgroups per die
+    const int deep_wgs = getenv("TDF_DEEP_WGS") ? std::max(1, atoi(getenv("TDF_DEEP_WGS"))) : 20;   // workgroups per die
     if (hc.n_cell) {
       const size_t level_bytes = (size_t)n_keys * sizeof(uint32_t);
       if (!rows_known) {
@@ -803,18 +808,19 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       auto deep_chain = [&]() -> tdf_status {
         begin_on(TDF_PHASE_TAIL_FWD, sd);
         vec_tail_fwd(on(sd), e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync, spin_ticks, deep_per_die,
-                     with_grad, sd);
+                     q_deep0, hc.n_cell - q_deep0, tail_rows, with_grad, sd);
         end_on(TDF_PHASE_TAIL_FWD, 1, sd);
         if (G.has_head) vec_head(on(sd), e, dy->dy, 1, 1, sd);
         begin_on(TDF_PHASE_TAIL_BWD, sd);
         vec_tail_bwd(on(sd), e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
-                     spin_ticks, deep_per_die, q_deep0, G.has_head ? e.head_row : e.root_ref, sd);
+                     spin_ticks, deep_per_die, q_deep0, tail_rows, G.has_head ? e.head_row : e.root_ref, sd);
         end_on(TDF_PHASE_TAIL_BWD, 2, sd);
         if (beside) flush(sd);   // (its next launch waits for the other instances)
         if (beside) HIP_TRY(hipEventRecord((hipEvent_t)gr->join_deep, s2));
         return TDF_OK;
       };
       if (deep && G.out_type == T_VEC && !G.has_head) vec_seed_dy(on(s), e, dy->dy, s);   // (root rows of both classes)
+      if (deep) most_rows(deep_base + LEVEL_KEY_DIES, deep_base + (hc.max_level + 1) * LEVEL_KEY_DIES);
       if (deep)
         if (tdf_status ds = deep_chain(); ds != TDF_OK) return ds;   // beside: on the side stream; else first, on the caller's
       // ---- the (other) instances on the caller's stream: wide levels one launch each; the narrow
@@ -830,9 +836,10 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
         if (const uint32_t n = lvl_begin(lvl + 1) - lvl_begin(lvl)) vec_cell_fwd(on(s), e, lvl_begin(lvl), n, with_grad, s);
       end(TDF_PHASE_CELLS_FWD, tail_first - 1);
       if (use_tail) {
+        most_rows(tail_first * LEVEL_KEY_DIES, (sh_last + 1) * LEVEL_KEY_DIES);
         begin(TDF_PHASE_TAIL_FWD);
         vec_tail_fwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, base + P.off_tail_sync, spin_ticks, cus / (int)XCDS,
-                     with_grad, s);
+                     lvl_begin(tail_first), hc.n_cell - lvl_begin(tail_first), tail_rows, with_grad, s);
         end(TDF_PHASE_TAIL_FWD, 1);
       }
     }
@@ -867,7 +874,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       if (use_tail && hc.n_cell) {
         begin(TDF_PHASE_TAIL_BWD);
         vec_tail_bwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
-                     spin_ticks, cus / (int)XCDS, lvl_begin(tail_first), G.has_head ? e.head_row : e.root_ref, s);
+                     spin_ticks, cus / (int)XCDS, lvl_begin(tail_first), tail_rows, G.has_head ? e.head_row : e.root_ref, s);
         end(TDF_PHASE_TAIL_BWD, 2);
       }
       begin(TDF_PHASE_CELLS_BWD);

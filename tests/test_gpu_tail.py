@@ -1,0 +1,83 @@
+"""The launches in which every die walks the narrow levels on its own (k_tail_fwd, k_tail_bwd): widths at which a
+wave's share of the reduction, or where its weights are kept, changes; levels of one cell and of several row tiles;
+NaNs, whose bit patterns these launches use for rows that are still to be written."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2410_20225_amd import tdf  # noqa: E402
+from tdf_workloads import make_config  # noqa: E402
+from gpu_util import TreeRun, run_oracle_tree, rel_fro  # noqa: E402
+
+# (workload recipe, hidden, trees, most leaves): 2 TreeRNN fp32, 3 TreeRNN bf16, 4 TreeLSTM bf16.  The padded width is a
+# multiple of 64; weights stay in registers up to 512 units (TreeRNN forward: 1024), and are fetched per tile beyond.
+FORWARD = [(2, 33, 1, 9), (2, 256, 60, 12), (2, 520, 20, 10), (2, 1040, 6, 8), (3, 64, 300, 14), (3, 192, 40, 12), (3, 512, 9, 40),
+           (3, 1056, 6, 8), (4, 60, 1, 30), (4, 150, 50, 12), (4, 320, 40, 10), (4, 512, 20, 9), (4, 580, 8, 8)]
+
+
+@pytest.mark.parametrize("cfg,hidden,trees,leaves", FORWARD)
+def test_forward_and_gradients_at_the_widths_where_the_tiles_change(cfg, hidden, trees, leaves):
+    c = make_config(cfg, n_trees=trees, max_leaves=leaves, hidden=hidden, vocab=200)
+    B = c["forest"].n_trees
+    dy = np.full(B, 1.0 / B)
+    ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
+    run = TreeRun(c, head=True, grad=True, stats_level=0)
+    # fp32: sums over at most 2 x 1088 terms through at most 40 contracting levels; bf16: the suite's bar for rounded states
+    tol = 1e-5 if cfg == 2 else 2e-2
+    for _ in range(2):
+        st, stats = run.run(dy)
+        assert stats.n_waves < 4 or stats.tail_used == 1
+        assert stats.n_grad_not_once == 0 and stats.n_grad_firings == c["forest"].n_nodes
+        assert rel_fro(run.out_f32.cpu().numpy(), np.array(ref["out"])) < tol
+        for name, t in (("dW", run.dW), ("db", run.db), ("dE", run.dE)):
+            assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < tol, name
+
+
+@pytest.mark.parametrize("cfg", [3, 4])
+def test_offsets_beyond_32_bits(cfg, monkeypatch):
+    import os
+    hooks = tdf.load_library(os.path.join(os.path.dirname(tdf.__file__), "libtdf_hooks.so"))
+    monkeypatch.setenv("TDF_TEST_WIDE_OFFSETS", "1")
+    c = make_config(cfg, n_trees=30, max_leaves=30, hidden=96, vocab=200)
+    B = c["forest"].n_trees
+    dy = np.full(B, 1.0 / B)
+    ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
+    with tdf.use_library(hooks):
+        run = TreeRun(c, head=True, grad=True, stats_level=0)
+        st, stats = run.run(dy)
+    assert stats.tail_used == 1
+    assert rel_fro(run.out_f32.cpu().numpy(), np.array(ref["out"])) < 2e-2
+    for name, t in (("dW", run.dW), ("db", run.db), ("dE", run.dE)):
+        assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < 2e-2, name
+
+
+@pytest.mark.parametrize("pattern", [-1, 0x7FC0])
+@pytest.mark.parametrize("cfg", [3, 4])
+def test_nans_pass_through(cfg, pattern):
+    # an embedding row of NaNs (all bits set: the pattern that stands for a row that is still to be written, and another
+    # one): nothing waits, and no other tree's loss is a NaN.  (The 16-bit path's tanh of a TreeRNN cell clamps its
+    # argument, which makes a number of a NaN; the gates of a TreeLSTM cell keep it.)
+    c = make_config(cfg, n_trees=40, max_leaves=16, hidden=64, vocab=60)
+    F = c["forest"]
+    B = F.n_trees
+    run = TreeRun(c, head=True, grad=True, stats_level=0)
+    run.t_E.view(torch.int16)[7].fill_(pattern)
+    st, stats = run.run(np.full(B, 1.0 / B))
+    assert stats.tail_used == 1 and stats.n_grad_not_once == 0
+    roots = np.asarray(F.roots)
+    tree_of = np.full(F.n_nodes, -1)
+    for b in range(B):
+        todo = [int(roots[b])]
+        while todo:
+            v = todo.pop()
+            tree_of[v] = b
+            if F.left[v] >= 0:
+                todo += [int(F.left[v]), int(F.right[v])]
+    has = np.zeros(B, bool)
+    has[tree_of[np.asarray(F.token) == 7]] = True
+    assert has.any() and not has.all()
+    nan = np.isnan(run.out_f32.cpu().numpy())
+    assert not nan[~has].any()
+    assert cfg == 3 or nan[has].all()
