@@ -9,7 +9,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtdf.so")
 LIB_HOOKS = os.path.join(HERE, "libtdf_hooks.so")
-SOURCES = ["graph_build.cpp", "tag_machine.hip", "cells.hip", "eval.hip", "jit.cpp"]
+SOURCES = ["graph_build.cpp", "tag_machine.hip", "forest_walk.hip", "cells.hip", "eval.hip", "jit.cpp"]
 # headers the run-time compiler needs, embedded into the library as string literals
 EMBEDDED = [("tdf.h", os.path.join(ROOT, "include", "tdf.h")), ("tdf_tables.h", os.path.join(CSRC, "tdf_tables.h")),
             ("engine.h", os.path.join(CSRC, "engine.h")), ("die_sync.h", os.path.join(CSRC, "die_sync.h")), ("step_device.h", os.path.join(CSRC, "step_device.h")),

@@ -335,6 +335,7 @@ struct LaneArgs {
   long long dead_ticks;         // longest time in which nobody works before waves that wait give up
   uint32_t max_tags;            // a run with more tags is the step machine's
   uint32_t tags_at_once;        // tags that a wave reports at once
+  uint32_t walk_nodes;          // 0, or: the forest of so many nodes is walked (forest_walk.hip), and the log is indexed by node
 };
 
 // ---- vector side ----------------------------------------------------------------------

@@ -23,6 +23,7 @@ tdf_status launch_round(const DevProgram& P, const Engine& e, int cus, bool loca
                         long long spin_ticks, const JitKernels& jit, hipStream_t s);
 void launch_lane_init(const LaneArgs& a, const Stamp& st, hipStream_t s);
 tdf_status launch_lanes(const LaneArgs& a, int n_stored, const JitKernels& jit, hipStream_t s);
+void launch_forest_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s);
 void launch_lane_sort(const Engine& e, const LaneArgs& a, const LaneLimits& lim, uint32_t* row_node, LaneTotals* totals,
                       LaneReport* report, uint32_t* pin_off, uint32_t pin_keys, uint32_t seq, const Stamp& st, hipStream_t s);
 void launch_finish(const LaneArgs& a, const EndArgs& g, const Stamp& st, hipStream_t s);
@@ -61,6 +62,7 @@ void vec_embed_sums(const VecArgs& v, uint32_t n_leaf, const uint32_t* seg_off, 
 
 namespace {
 
+constexpr uint32_t WALK_NODES = 32768;   // nodes an instance, on average, up to which a wave walks its tree (forest_walk.hip)
 constexpr uint32_t DE_CHUNK = 128;
 constexpr uint32_t DB_CHUNK = 64;
 
@@ -527,12 +529,26 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     --gr->lanes_skip;
     use_lanes = false;
   }
-  if (use_lanes && !gr->jit.lanes_tried && !no_alloc) {
-    gr->jit.lanes_tried = true;
-    std::string log;
-    if (!jit_compile_lanes(G.prog, gr->jit, log) && getenv("TDF_JIT_VERBOSE")) fprintf(stderr, "tdf: no generated lanes: %s\n", log.c_str());
+  // A program that is a recursion over the children of tree nodes: its schedule follows from the forest.
+  if (!gr->walk_known) {
+    gr->walk = walk_form(G.prog);
+    gr->walk_known = true;
   }
-  use_lanes = use_lanes && gr->jit.lanes;
+  bool use_walk = use_lanes && gr->walk.ok && in->n_tree_nodes <= (int64_t)std::min(P.lanes.log_cap, (1u << 28) - 1u) &&
+                  (uint64_t)in->n_tree_nodes / (uint64_t)in->n_instances <= WALK_NODES && !getenv("TDF_NO_WALK");
+  if (use_walk && gr->walk_skip > 0) {
+    --gr->walk_skip;
+    use_walk = false;
+  }
+  auto compile_lanes = [&]() {
+    if (use_lanes && !gr->jit.lanes_tried && !no_alloc) {
+      gr->jit.lanes_tried = true;
+      std::string log;
+      if (!jit_compile_lanes(G.prog, gr->jit, log) && getenv("TDF_JIT_VERBOSE")) fprintf(stderr, "tdf: no generated lanes: %s\n", log.c_str());
+    }
+    use_lanes = use_lanes && (gr->jit.lanes || use_walk);
+  };
+  if (!use_walk) compile_lanes();
   const bool use_jit = gr->jit.step && gr->jit.small && gr->jit.step_local;
   int small_block = tag_machine_small_block(G.prog, use_jit);
   // A batch of few instances (deep ones, or it would not be worth a GPU) has narrow steps: half the lanes
@@ -578,8 +594,9 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     launch_finish(P.lanes, g, take(s), s);
     return TDF_OK;
   };
-  if (use_lanes) {
+  while (use_lanes) {
     LaneArgs& a = P.lanes;
+    a.walk_nodes = use_walk ? (uint32_t)in->n_tree_nodes : 0u;
     a.out_i64 = e.out_i64;
     a.idle_ticks = spin_ticks;
     a.dead_ticks = 2 * spin_ticks;
@@ -588,7 +605,8 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     a.tags_at_once = std::max(64u, e.max_tags / (2u * a.n_waves));
     if (P.vec) vec_pack_w(on(s), &a, base + P.L.zero_begin, P.L.zero_end - P.L.zero_begin, s);
     else launch_lane_init(a, take(s), s);
-    if (tdf_status ls = launch_lanes(a, P.n_stored, gr->jit, s); ls != TDF_OK) return ls;
+    if (use_walk) launch_forest_walk(a, gr->walk, take(s), s);
+    else if (tdf_status ls = launch_lanes(a, P.n_stored, gr->jit, s); ls != TDF_OK) return ls;
     end(TDF_PHASE_TAGS, 2);
     LaneTotals lt;
     if (P.vec) {
@@ -617,6 +635,16 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       lt = fin->t;
       ended = !lt.bad;
     }
+    if (lt.bad && use_walk) {   // left to the lanes, which start over
+      use_walk = false;
+      gr->walk_skip = gr->walk_skip_next;
+      gr->walk_skip_next = std::min(2u * gr->walk_skip_next, (uint32_t)tdf_graph::LANES_SKIP_MOST);
+      memset(launches, 0, sizeof(launches));
+      begin(TDF_PHASE_TAGS);
+      compile_lanes();
+      continue;
+    }
+    if (use_walk) gr->walk_skip_next = tdf_graph::LANES_SKIP;
     if (lt.bad) {   // left to the step machine, which also says what is wrong if something is
       use_lanes = false;
       left_over = true;
@@ -633,6 +661,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       hc.n_alloc = (uint32_t)std::min<unsigned long long>(hc.n_tags, lt.frames);
       hc.done = 1;
     }
+    break;
   }
   bool w_packed = use_lanes && P.vec;
   if (!use_lanes) flush(s);

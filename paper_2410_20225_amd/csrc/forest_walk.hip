@@ -1,0 +1,313 @@
+// Structural recursion over the forest: the tag phase of programs whose calls follow the children of a tree node.
+//
+// A function f(v) = cell(f(left v), f(right v)) at inner nodes, embed(token v) at leaves, has one tag per visit of a node:
+// Call_i of its two calls are the edges to the children, Return_i the edges back.  Where every node is visited at most
+// once, tags and nodes are the same thing, and what the tag machine would log (lane_device.h) follows from the forest
+// alone: a leaf fires its EMBED, an inner node its cell when both children have, one level above the higher of them.
+// One wave walks the tree of one instance.  A lane goes down to the left child and leaves the right one on a stack in LDS,
+// which lanes without a node take from; a leaf turns the lane round, and the second of two children that arrive at their
+// parent goes on up.  The schedule log is indexed by node, so a value's name is its node.
+//
+// The rule: programs of that form (walk_form, below), forests of at most as many nodes as the log has entries, and at most
+// WALK_NODES nodes an instance on average, since one wave works on an instance: beyond, the lanes share a tree
+// between waves.  A forest whose nodes are shared (between parents or instances), or have bad entries, and a tree that is
+// much wider than the average, leave a status, and the lanes run the evaluation; what they make of it counts.
+//
+// What bounds it: the latency of one request per level down (the node's entries) and one up (the parent's word, in the die's
+// L2), and some 150 instructions a step: 1.4 us a level there and back, where the lanes' sweeps take 3.3.
+// The tag phase, lanes -> walk: one tree of 35 leaves 94 -> 22 us, 50 trees of up to 50 leaves 128 -> 28, 1,024 trees 205 ->
+// 37, 4,096 trees of up to 128 leaves, a fifth of them chains, 620 -> 240, 64 chains of 4,096 leaves 13.5 -> 5.8 ms.
+#include "engine.h"
+#include "lane_device.h"
+#include "tdf_internal.h"
+
+namespace tdf {
+
+// ---- which programs ---------------------------------------------------------------------------------
+// The instruction that makes value v of function f, looking through identities; null: none.
+static const Instr* maker(const DevProgram& P, int f, int v) {
+  for (int hops = 0; v < SRC_NONE && hops < MAX_VALUES; ++hops) {
+    const Instr* found = nullptr;
+    for (int i = 0; i < P.fn[f].count; ++i) {
+      const Instr& I = P.instr[P.fn[f].first + i];
+      if (I.op == D_CALL || I.op == D_OUT || I.op == D_NEXT) continue;   // (no value)
+      if (I.dst == v || (I.op == D_SWITCH && I.dst + 1 == v)) found = &I;
+    }
+    if (!found || found->op != D_ID) return found;
+    v = found->src[0];
+  }
+  return nullptr;
+}
+static int count_of(const DevProgram& P, int f, DevOp op) {
+  int n = 0;
+  for (int i = 0; i < P.fn[f].count; ++i) n += P.instr[P.fn[f].first + i].op == op;
+  return n;
+}
+static const Instr* only(const DevProgram& P, int f, DevOp op) {
+  for (int i = 0; i < P.fn[f].count; ++i)
+    if (P.instr[P.fn[f].first + i].op == op) return &P.instr[P.fn[f].first + i];
+  return nullptr;
+}
+// the argument of the one-parameter call with this label; its callee must be g
+static const Instr* call_of(const DevProgram& P, int f, int label, int g) {
+  const Instr* c = nullptr;
+  for (int i = 0; i < P.fn[f].count; ++i) {
+    const Instr& I = P.instr[P.fn[f].first + i];
+    if (I.op != D_CALL || I.aux != label) continue;
+    if (c) return nullptr;
+    c = &I;
+  }
+  return c && P.label_callee[label] == g ? c : nullptr;
+}
+WalkForm walk_form(const DevProgram& P) {
+  WalkForm w;
+  if (P.n_fn != 2) return w;
+  const int r = P.result_fn, f = 1 - r;
+  if (P.fn[f].n_params != 1) return w;
+  // result: IN.., one call of f with a parameter, OUT of its value or of HEAD(value, parameter)
+  const Instr* out = only(P, r, D_OUT);
+  if (!out || count_of(P, r, D_CALL) != 1 || count_of(P, r, D_RET) != 1 || count_of(P, r, D_HEAD) > 1) return w;
+  const Instr *head = only(P, r, D_HEAD), *ret = only(P, r, D_RET);
+  int others = P.fn[r].count - count_of(P, r, D_IN) - count_of(P, r, D_ID) - 3 - (head ? 1 : 0);
+  if (others != 0 || maker(P, r, out->src[0]) != (head ? head : ret)) return w;
+  const Instr* call = call_of(P, r, ret->aux2, f);
+  const Instr* arg = call ? maker(P, r, call->src[0]) : nullptr;
+  if (!arg || arg->op != D_IN) return w;
+  w.root_arg = arg->aux;
+  if (head) {
+    const Instr *row = maker(P, r, head->src[0]), *label = maker(P, r, head->src[1]);
+    if (row != ret || !label || label->op != D_IN) return w;
+    w.label_arg = label->aux;
+  }
+  // f: IN v, ISLEAF v, SWITCH(isleaf, v), TOKEN(leaf side) -> EMBED, LEFT and RIGHT(inner side) -> two calls of f -> CELL,
+  // MERGE of the two rows, CE_NODE(row, v) if any, OUT
+  for (DevOp op : {D_IN, D_ISLEAF, D_SWITCH, D_TOKEN, D_EMBED, D_LEFT, D_RIGHT, D_CELL, D_MERGE, D_OUT})
+    if (count_of(P, f, op) != 1) return w;
+  const Instr *v = only(P, f, D_IN), *sw = only(P, f, D_SWITCH), *cell = only(P, f, D_CELL), *merge = only(P, f, D_MERGE);
+  const Instr *ce = only(P, f, D_CE_NODE), *embed = only(P, f, D_EMBED), *token = only(P, f, D_TOKEN);
+  if (count_of(P, f, D_CALL) != 2 || count_of(P, f, D_RET) != 2 || count_of(P, f, D_CE_NODE) > 1) return w;
+  others = P.fn[f].count - count_of(P, f, D_ID) - 10 - 4 - (ce ? 1 : 0);
+  if (others != 0) return w;
+  auto side = [&](int value, int which) {   // value is that side of the switch (identities in between)
+    for (int hops = 0; value < SRC_NONE && hops < MAX_VALUES; ++hops) {
+      if (value == sw->dst + which) return true;
+      const Instr* id = nullptr;
+      for (int i = 0; i < P.fn[f].count; ++i) {
+        const Instr& I = P.instr[P.fn[f].first + i];
+        if (I.op == D_ID && I.dst == value) id = &I;
+      }
+      if (!id) return false;
+      value = id->src[0];
+    }
+    return false;
+  };
+  const Instr* isleaf = maker(P, f, sw->src[0]);
+  if (!isleaf || isleaf->op != D_ISLEAF || maker(P, f, isleaf->src[0]) != v || maker(P, f, sw->src[1]) != v) return w;
+  if (!side(token->src[0], 0) || maker(P, f, embed->src[0]) != token) return w;
+  const Instr* kids[2] = {maker(P, f, cell->src[0]), maker(P, f, cell->src[1])};
+  const Instr* ends[2] = {nullptr, nullptr};
+  for (int k = 0; k < 2; ++k) {
+    if (!kids[k] || kids[k]->op != D_RET) return w;
+    const Instr* c = call_of(P, f, kids[k]->aux2, f);
+    ends[k] = c ? maker(P, f, c->src[0]) : nullptr;
+    if (!ends[k] || (ends[k]->op != D_LEFT && ends[k]->op != D_RIGHT) || !side(ends[k]->src[0], 1)) return w;
+  }
+  if (ends[0]->op == ends[1]->op) return w;
+  int rows = 0, from = 0;   // the merge's inputs: the two rows, nothing else
+  for (int k = 0; k < 4; ++k) {
+    if (merge->src[k] == SRC_NONE) continue;
+    const Instr* m = maker(P, f, merge->src[k]);
+    ++rows;
+    from |= m == embed ? 1 : m == cell ? 2 : 4;
+  }
+  if (rows != 2 || from != 3) return w;
+  const Instr* end = maker(P, f, only(P, f, D_OUT)->src[0]);
+  if (ce ? end != ce || maker(P, f, ce->src[0]) != merge || maker(P, f, ce->src[1]) != v : end != merge) return w;
+  w.swapped = ends[0]->op == D_RIGHT;
+  w.ok = true;
+  return w;
+}
+
+// ---- the walk ----------------------------------------------------------------------------------------
+constexpr uint32_t WALK_STACK = 512;            // nodes on a wave's stack in LDS
+constexpr uint32_t WALK_ROOT = 0xFFFFFFFEu;     // parent of an instance's root
+constexpr uint32_t WALK_NONE = 0xFFFFFFFFu;     // no node
+constexpr uint32_t WALK_WIDE = 65536u;          // visits from which on a tree of 16 nodes a step or more is left to the lanes
+
+// On entry log[v].z is LANE_LOG_HOLE for all nodes.  row_of[v] becomes v's parent (until the rows are numbered), log[v] the
+// entry of v's EMBED or cell; before that log[v].z is the level of the first child that is through.  All that concerns a
+// tree is written and read by its wave, in one die's L2: past the L1 where it is read.
+// A node that is visited twice is not noticed here: its leaves count twice then, and the pass over the log, which meets
+// every node once, finds fewer.  What has to hold is that nothing leaves the arrays and that the walk ends, on any forest and
+// whatever waves with the same nodes write: indices are checked, and no wave makes more visits or cells than there are nodes.
+template <typename T> __device__ __forceinline__ T* at32(T* base, uint32_t i) {   // (a uniform base and 32 bits of offset)
+  return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+template <typename T> __device__ __forceinline__ const T* at32(const T* base, uint32_t i) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+__global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w, Stamp st) {
+  __shared__ uint32_t s_node[WALK_STACK], s_parent[WALK_STACK], s_depth[WALK_STACK];
+  stamp_now(st);
+  const uint32_t lane = threadIdx.x, b = blockIdx.x, n_nodes = (uint32_t)a.n_tree_nodes;
+  uint32_t n_stack = 0, most = 0, iter = 0;   // (uniform)
+  bool down = false, up = false;
+  uint32_t v = 0, p = WALK_ROOT, depth = 1, lvl = 0;   // down: node, its parent and depth; up: level of a node that is through, its parent
+  uint32_t own = WALK_NONE;                   // nodes for which the stack had no room: a list through the log entries of these
+  uint32_t n_leaf = 0, n_inner = 0, n_cell = 0, mx_depth = 0, mx_level = 0;
+  int bad = 0;
+  const long long root = a.args[(size_t)b * a.n_args + w.root_arg];
+  if (root < 0 || root >= (long long)n_nodes) bad = TDF_ERR_BAD_ARG;
+  else if (lane == 0) {
+    v = (uint32_t)root;
+    down = true;
+  }
+  auto finish = [&](uint32_t name, uint32_t level) {
+    a.root_lvl[b] = level;
+    if (w.label_arg >= 0) {
+      a.head_row[b] = name;
+      a.head_label[b] = (uint32_t)a.args[(size_t)b * a.n_args + w.label_arg];
+    } else {
+      a.root_ref[b] = name;
+    }
+  };
+  bool lists = false;   // (uniform) a lane has had a list of its own
+  for (;;) {
+    if (__builtin_expect(__ballot(bad != 0) != 0, 0)) break;
+    // ---- lanes without a node take one of the stack, or of their own list
+    unsigned long long idle = ~__ballot(down || up);
+    if (idle != 0 && n_stack != 0) {
+      const uint32_t n_take = min(n_stack, (uint32_t)__popcll(idle)), rank = (uint32_t)__popcll(idle & lanemask_lt());
+      if (!down && !up && rank < n_take) {
+        const uint32_t i = n_stack - 1u - rank;
+        v = s_node[i];
+        p = s_parent[i];
+        depth = s_depth[i];
+        down = true;
+      }
+      n_stack -= n_take;
+      idle = ~__ballot(down || up);
+    }
+    if (__builtin_expect(lists, 0)) {
+      if (!down && !up && own != WALK_NONE) {
+        v = own;
+        const uint4* e = at32(a.log, v);
+        own = lane_ld(&e->x);
+        p = lane_ld(&e->y);
+        depth = lane_ld(&e->w);
+        down = p < n_nodes && (own < n_nodes || own == WALK_NONE);   // (else another instance has been here)
+        if (!down) bad = TDF_ERR_UNSUPPORTED;
+      }
+      idle = ~__ballot(down || up || bad != 0);
+    }
+    if (idle == ~0ull) break;
+    ++iter;
+    // ---- one request of every lane
+    int l = 0, r = 0, t = 0;
+    uint32_t was = 0, pp = 0;
+    if (down) {
+      l = *at32(a.left, v);
+      r = *at32(a.right, v);
+      t = *at32(a.token, v);
+    }
+    if (up) {
+      pp = lane_ld(at32(a.row_of, p));
+      was = __hip_atomic_exchange(&at32(a.log, p)->z, lvl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    // (Waited for here, together: the compiler would do so on each way, and on the second behind the first one's stores.)
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    // ---- up: the first child to arrive leaves its level, the second goes on
+    bool push = false;
+    if (up) {
+      up = was != LANE_LOG_HOLE;
+      if (up) {
+        lvl = 1u + max(lvl, was);
+        at32(a.log, p)->z = lvl;
+        ++n_cell;
+        if (pp >= n_nodes) {
+          up = false;
+          mx_level = lvl;
+          if (pp == WALK_ROOT) finish(p, lvl);
+          else bad = TDF_ERR_UNSUPPORTED;   // (another instance has been here)
+        }
+        p = pp;
+      }
+    } else if (down) {
+      // ---- down: the node's entries
+      *at32(a.row_of, v) = p;
+      if (a.row_node) *at32(a.row_node, v) = v;
+      if (l < 0) {
+        if (t < 0 || t >= a.vocab) bad = TDF_ERR_BAD_ARG;
+        *at32(a.log, v) = make_uint4((uint32_t)t, 0u, 0u, b);
+        ++n_leaf;
+        mx_depth = max(mx_depth, depth);
+        lvl = 0;
+        down = false;
+        up = p != WALK_ROOT;
+        if (!up) finish(v, 0u);
+      } else if ((uint32_t)l >= n_nodes || (uint32_t)r >= n_nodes) {
+        bad = TDF_ERR_BAD_ARG;
+      } else {
+        uint4* e = at32(a.log, v);
+        *reinterpret_cast<uint2*>(e) = w.swapped ? make_uint2((uint32_t)r, (uint32_t)l) : make_uint2((uint32_t)l, (uint32_t)r);
+        e->w = b;
+        ++n_inner;
+        ++depth;
+        push = true;
+        p = v;
+        v = (uint32_t)l;
+      }
+    }
+    // ---- right children for lanes without a node
+    const unsigned long long pm = __ballot(push);
+    if (pm) {
+      const uint32_t room = WALK_STACK - n_stack, k = (uint32_t)__popcll(pm & lanemask_lt()), n = (uint32_t)__popcll(pm);
+      if (push && k < room) {
+        s_node[n_stack + k] = (uint32_t)r;
+        s_parent[n_stack + k] = p;
+        s_depth[n_stack + k] = depth;
+      }
+      if (__builtin_expect(n > room, 0)) {
+        lists = true;
+        if (push && k >= room) {
+          uint4* e = at32(a.log, (uint32_t)r);   // (nobody has visited it; z stays as it is)
+          lane_put(&e->x, own);
+          lane_put(&e->y, p);
+          lane_put(&e->w, depth);
+          own = (uint32_t)r;
+        }
+      }
+      n_stack += min(room, n);
+      most = max(most, n_stack);
+    }
+    if (__builtin_expect((iter & 63u) == 0, 0)) {
+      // (A step of the wave is a visit, or a cell, or the first child's arrival, of which there is one a visit or cell: on
+      // any forest one of the two counts passes the number of nodes if the walk does not end before.)
+      const uint32_t seen = wave_usum(n_leaf + n_inner);
+      if (seen > n_nodes || wave_usum(n_cell) > n_nodes || (seen > WALK_WIDE && seen > 16u * iter)) bad = TDF_ERR_UNSUPPORTED;
+      if (lane_ld(&a.ctl->status) != 0) break;   // another wave has left
+    }
+  }
+  const unsigned long long leaves = wave_usum(n_leaf), inner = wave_usum(n_inner), cells = wave_usum(n_cell);
+  if (bad == 0 && inner != cells) bad = TDF_ERR_UNSUPPORTED;
+  const unsigned long long bm = __ballot(bad != 0);
+  const uint32_t md = wave_umax(mx_depth), ml = wave_umax(mx_level);
+  if (bm) {
+    const int code = __shfl(bad, __ffsll((long long)bm) - 1);
+    if (lane == 0) lane_put(&a.ctl->status, (uint32_t)(-code));
+  } else if (lane == 0) {
+    LaneQueue* q = &a.queues[b % a.n_queues];
+    (void)lane_add(&q->n_tags, leaves + cells);
+    (void)lane_add(&q->n_tokens, 2ull * (leaves + cells));   // an argument and a value each
+    (void)lane_add(reinterpret_cast<unsigned long long*>(&q->n_leaf), leaves | (cells << 32));
+    (void)lane_add(reinterpret_cast<unsigned long long*>(&q->n_rec), (unsigned long long)(most + 64u));
+    atomicMax(&q->max_depth, md);
+    if (ml) atomicMax(&q->max_level, ml);
+    atomicMax(&q->max_iter, iter);
+  }
+}
+void launch_forest_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s) {
+  hipLaunchKernelGGL(k_forest_walk, dim3(a.n_inst), dim3(64), 0, s, a, w, st);
+}
+
+}  // namespace tdf

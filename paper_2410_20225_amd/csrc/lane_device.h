@@ -97,9 +97,13 @@ struct LaneReply { unsigned long long value, flag; };   // flag 1: the value is 
 __device__ inline void lane_init(const LaneArgs& a, uint32_t i, uint32_t n) {
   if (i == 0) {
     *a.ctl = LaneCtl{};
-    a.ctl->log_used = a.log_cap ? a.n_waves * LANE_CHUNK : 0u;
+    a.ctl->log_used = a.walk_nodes ? a.walk_nodes : a.log_cap ? a.n_waves * LANE_CHUNK : 0u;
   }
   if (i < a.n_queues) a.queues[i] = LaneQueue{};
+  if (a.walk_nodes) {   // nobody has visited a node
+    for (uint32_t k = i; k < a.walk_nodes; k += n) a.log[k].z = LANE_LOG_HOLE;
+    return;
+  }
   for (uint32_t k = i; k < a.n_queues * a.queue_cap; k += n) a.mail[k].flag = lane_slot(0u, a.queue_cap, LANE_EMPTY);
   for (uint32_t k = i; k < a.n_waves * 64u; k += n) a.reply[k].flag = 0ull;
   if (a.row_node)

@@ -330,9 +330,10 @@ __device__ __forceinline__ void lane_totals(const LaneArgs& a, const LaneLimits&
 // of separate merge, class, count, number and place kernels.
 struct LaneSort {
   const uint4* log;
-  const LaneTotals* t;
+  LaneTotals* t;
   uint32_t *row_of, *leaf_next, *rows_done;
   const uint32_t* row_node;
+  uint32_t exact;                                   // entries of a log that is indexed by node are counted: a node that two instances share has one
   uint32_t lds_keys;                                // counts that a workgroup's LDS takes
   uint32_t pin_keys;                                // level offsets that the host's copy takes
   uint32_t* pin_off;
@@ -377,7 +378,7 @@ __device__ inline void lane_publish(const LaneSort& s, const LaneTotals& t, bool
 __global__ void __launch_bounds__(BUCKET_THREADS) k_lane_rows(Engine e, LaneSort s) {
   extern __shared__ uint32_t hist[];
   __shared__ uint32_t n_leaf, leaf0, last, wsum[BUCKET_THREADS / 64];
-  const LaneTotals t = *s.t;
+  LaneTotals t = *s.t;
   if (t.bad) {
     if (blockIdx.x == 0) lane_publish(s, t, false);
     return;
@@ -465,6 +466,10 @@ __global__ void __launch_bounds__(BUCKET_THREADS) k_lane_rows(Engine e, LaneSort
       }
       x += c[j];
     }
+  }
+  if (s.exact && (carry != t.n_cell || __hip_atomic_load(s.leaf_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != t.n_leaf)) {
+    t.bad = 1u;
+    if (threadIdx.x == 0) s.t->bad = 1u;   // (for the passes behind this one)
   }
   lane_publish(s, t, pin);
 }
@@ -583,6 +588,7 @@ void launch_lane_sort(const Engine& e, const LaneArgs& a, const LaneLimits& lim,
   t.row_of = a.row_of;
   t.leaf_next = &a.ctl->leaf_next;
   t.rows_done = &a.ctl->rows_done;
+  t.exact = a.walk_nodes != 0;
   t.row_node = row_node;
   t.pin_keys = pin_keys;
   t.pin_off = pin_off;

@@ -57,6 +57,13 @@ struct JitKernels {
 };
 bool jit_compile(const DevProgram& P, JitKernels& out, std::string& log);
 bool jit_compile_lanes(const DevProgram& P, JitKernels& out, std::string& log);
+// Programs that are a recursion over the children of tree nodes (forest_walk.hip).
+struct WalkForm {
+  int ok = 0;
+  int root_arg = 0, label_arg = -1;   // arguments of `result`: the instance's root, its label (-1: no head)
+  int swapped = 0;                    // the cell's first operand is the right child
+};
+WalkForm walk_form(const DevProgram& P);
 int lane_stored(const DevProgram& P);   // stored values of a frame (the largest function's)
 bool lane_branching(const DevProgram& P);   // a frame (other than of `result`) can have several calls or loops
 void jit_release(JitKernels& k);
@@ -71,6 +78,10 @@ struct tdf_graph {
   // lanes_skip evaluations do not try them, and twice as many after the next such run (other inputs may be theirs again).
   uint32_t lanes_skip = 0, lanes_skip_next = LANES_SKIP;
   static constexpr uint32_t LANES_SKIP = 8, LANES_SKIP_MOST = 1024;
+  // The same for a walk over the forest that was left to the lanes.
+  tdf::WalkForm walk;
+  bool walk_known = false;
+  uint32_t walk_skip = 0, walk_skip_next = LANES_SKIP;
   uint32_t max_dies = 8;    // tag machines a batch is dealt to (set to 1 after a part of the table overflowed)
   void* side_stream = nullptr;                     // hipStream_t for work beside the caller's stream
   void* fork_event = nullptr, *join_event = nullptr;   // embedding gradient beside the weight gradients

@@ -1,0 +1,196 @@
+"""The walk over the forest (forest_walk.hip) against the lanes, which run every program: same results, same counts, same
+refusals, on forests of every shape: shuffled, with nodes nobody asks for, shared nodes, bad entries, and trees that
+leave the walk's stack."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2410_20225_amd import tdf, programs  # noqa: E402
+from paper_2410_20225_amd.programs import _Fn  # noqa: E402
+
+DEV, H, V, C = "cuda:0", 64, 50, 5
+KEYS = ("n_tags", "n_tokens", "n_leaf_rows", "n_cell_rows", "n_waves", "max_tag_depth")
+
+
+def _trees(shapes, rng, shuffle=True):
+    """shapes: nested pairs, None a leaf -> left, right, token, roots; nodes numbered at random."""
+    left, right, roots = [], [], []
+
+    def add(s):
+        todo, top = [(s, None, 0)], len(left)
+        while todo:
+            s, parent, side = todo.pop()
+            v = len(left)
+            left.append(-1)
+            right.append(-1)
+            if parent is not None:
+                (left, right)[side][parent] = v
+            if s is not None:
+                todo += [(s[1], v, 1), (s[0], v, 0)]
+        return top
+
+    roots = [add(s) for s in shapes]
+    left, right, roots = np.array(left), np.array(right), np.array(roots)
+    if shuffle:
+        name = rng.permutation(left.size)
+        new = lambda a: np.where(a >= 0, name[np.maximum(a, 0)], -1)  # noqa: E731
+        l2, r2 = np.empty_like(left), np.empty_like(right)
+        l2[name], r2[name] = new(left), new(right)
+        left, right, roots = l2, r2, name[roots]
+    return left, right, rng.integers(0, V, left.size), roots
+
+
+def _chain(n, right=None):
+    s = None
+    for _ in range(n):
+        s = (s, right)
+    return s
+
+
+def _random(n, rng):
+    if n == 1:
+        return None
+    k = int(rng.integers(1, n))
+    return (_random(k, rng), _random(n - k, rng))
+
+
+def _swapped():   # cell(f(right), f(left)), with identities in between
+    T = tdf
+    r = _Fn("result", 2)
+    y = r.add(T.OP_CALLFN, [r.add(T.OP_IN, imm=1)], imm=1)
+    r.add(T.OP_OUT, [r.add(T.OP_CE_HEAD, [y, r.add(T.OP_IN, imm=0)])])
+    f = _Fn("f", 1)
+    v = f.add(T.OP_ID, [f.add(T.OP_IN, imm=0)])
+    sw = f.add(T.OP_SWITCH, [f.add(T.OP_TREE_ISLEAF, [v]), v])
+    leaf, inner = (sw[0], 0), (sw[0], 1)
+    e = f.add(T.OP_EMBED, [f.add(T.OP_TREE_TOKEN, [leaf])])
+    hl = f.add(T.OP_CALLFN, [f.add(T.OP_TREE_LEFT, [f.add(T.OP_ID, [inner])])], imm=1)
+    hr = f.add(T.OP_CALLFN, [f.add(T.OP_TREE_RIGHT, [inner])], imm=1)
+    f.add(T.OP_OUT, [f.add(T.OP_ID, [f.add(T.OP_MERGE, [f.add(T.OP_LSTM_CELL, [hr, hl]), e])])])
+    return [r.desc(), f.desc()], 0
+
+
+def _leaf_label():   # not the walk's form: the head's label is a node's token
+    T = tdf
+    r = _Fn("result", 2)
+    v = r.add(T.OP_IN, imm=0)
+    y = r.add(T.OP_CALLFN, [v], imm=1)
+    r.add(T.OP_OUT, [r.add(T.OP_CE_HEAD, [y, r.add(T.OP_SUB, [r.add(T.OP_IN, imm=1), r.add(T.OP_CONST, imm=0)])])])
+    fns, _ = programs.tree("lstm", True)
+    return [r.desc(), fns[1]], 0
+
+
+def _run(prog, forest, walk, max_tags=None, label_first=False, nodes=False, vocab=V):
+    left, right, token, roots = forest
+    os.environ.pop("TDF_NO_WALK", None)
+    if not walk:
+        os.environ["TDF_NO_WALK"] = "1"
+    try:
+        g = tdf.graph_build(*prog)
+        B, n = len(roots), len(left)
+        lab = np.arange(B) % C
+        args = roots[:, None] if nodes else np.stack([lab, roots] if label_first else [roots, lab], 1)
+        t = lambda a, d: torch.tensor(np.ascontiguousarray(a), dtype=d, device=DEV)  # noqa: E731
+        gen = torch.Generator(device=DEV).manual_seed(3)
+        rn = lambda *s: torch.randn(*s, generator=gen, device=DEV) * 0.3  # noqa: E731
+        keep = dict(args=t(args, torch.int64), left=t(left, torch.int32), right=t(right, torch.int32), token=t(token, torch.int32),
+                    E=rn(vocab, H).bfloat16(), W=rn(5 * H, 2 * H).bfloat16(), b=rn(5 * H), U=rn(C, H), u0=rn(C))
+        if nodes:
+            keep["node_label"] = t(np.arange(n) % (C + 1) - 1, torch.int32)
+        inp = tdf.make_inputs(B, n_args=args.shape[1], dtype=tdf.BF16, hidden=H, vocab=vocab, n_classes=C,
+                              max_tags=max(n, B) if max_tags is None else max_tags, stats_level=0, **keep)
+        ws = torch.full((tdf.workspace_size(g, inp),), 0x5A, dtype=torch.uint8, device=DEV)
+        out = dict(out_h=torch.zeros(B, H, device=DEV), out_c=torch.zeros(B, H, device=DEV), out_node_loss=torch.zeros(n, device=DEV)) if nodes \
+            else dict(out_f32=torch.zeros(B, device=DEV))
+        res = []
+        for _ in range(2):
+            st, stats = tdf.eval(g, inp, ws, check=False, **out)
+            res.append((st, [getattr(stats, k) for k in KEYS] if st == tdf.OK else None,
+                        [o.cpu().numpy().copy() for o in out.values()] if st == tdf.OK else None))
+        return res
+    finally:
+        os.environ.pop("TDF_NO_WALK", None)
+
+
+def _same(prog, forest, **kw):
+    a, b = _run(prog, forest, True, **kw), _run(prog, forest, False, **kw)
+    for x, y in zip(a, b):
+        assert x[0] == y[0] and x[1] == y[1], (x[:2], y[:2])
+        if x[0] == tdf.OK:   # (a row's arithmetic does not depend on where the row lies)
+            for o, p in zip(x[2], y[2]):
+                assert np.array_equal(o, p)
+    return a[0][0]
+
+
+def _forests():
+    rng = np.random.default_rng(5)
+    some = [_random(int(n), rng) for n in rng.integers(1, 40, 30)]
+    yield "one_leaf", _trees([None], rng)
+    yield "one_pair", _trees([(None, None)], rng)
+    yield "random", _trees(some, rng)
+    yield "in_order", _trees(some, rng, shuffle=False)
+    yield "chains", _trees([_chain(70), _chain(3), None], rng)
+    yield "right_chain", _trees([tuple_chain(90)], rng)
+    # 60 spines of 50 under a spine: more right children than the stack holds
+    yield "combs", _trees([_chain(80, _chain(60)), _chain(5)], rng)
+    l, r, t, roots = _trees(some, rng)
+    yield "nodes_nobody_asks_for", (l, r, t, roots[::3])
+    yield "the_same_root_twice", (l, r, t, np.concatenate([roots[:5], roots[3:9]]))
+    inner = roots[np.nonzero(l[roots] >= 0)[0][:6]]
+    yield "a_root_inside_another_tree", (l, r, t, np.concatenate([inner, l[inner]]))
+    l2, r2 = l.copy(), r.copy()
+    r2[inner[0]] = l2[inner[0]]
+    yield "both_children_the_same", (l2, r2, t, roots)
+    l3, r3 = l.copy(), r.copy()
+    r3[inner[0]] = l3[inner[1]]
+    yield "a_child_of_two_trees", (l3, r3, t, roots)
+    for k, bad in (("right_missing", -1), ("right_out_of_range", l.size), ("left_out_of_range", l.size + 7)):
+        a, b = l.copy(), r.copy()
+        (a if k[0] == "l" else b)[inner[2]] = bad
+        yield k, (a, b, t, roots)
+    t2 = t.copy()
+    t2[np.nonzero(l < 0)[0][3]] = V
+    yield "token_out_of_range", (l, r, t2, roots)
+    yield "root_out_of_range", (l, r, t, np.concatenate([roots, [l.size]]))
+    a, b = l.copy(), r.copy()
+    leaf = l[inner[3]]
+    while a[leaf] >= 0:
+        leaf = a[leaf]
+    a[leaf], b[leaf] = inner[3], inner[3]
+    yield "a_cycle", (a, b, t, roots)
+
+
+def tuple_chain(n):
+    s = None
+    for _ in range(n):
+        s = (None, s)
+    return s
+
+
+FORESTS = list(_forests())
+
+
+@pytest.mark.parametrize("name,forest", FORESTS, ids=[n for n, _ in FORESTS])
+def test_forests(name, forest):
+    wrong = {"right_missing", "right_out_of_range", "left_out_of_range", "token_out_of_range", "root_out_of_range", "a_cycle"}
+    st = _same(programs.tree("lstm", True), forest, max_tags=4 * max(len(forest[0]), len(forest[3])))
+    assert (st != tdf.OK) == (name in wrong)
+
+
+@pytest.mark.parametrize("max_tags", [1, 2])
+def test_fewer_tags_than_nodes(max_tags):
+    forest = dict(FORESTS)["random"]
+    n = len(forest[0])
+    assert _same(programs.tree("lstm", True), forest, max_tags=max(n // max_tags, 30)) == (tdf.OK if max_tags == 1 else tdf.ERR_TABLE_FULL)
+
+
+def test_other_programs():
+    for name in ("random", "combs", "nodes_nobody_asks_for"):
+        forest = dict(FORESTS)[name]
+        assert _same(_swapped(), forest, label_first=True) == tdf.OK
+        assert _same(_leaf_label(), forest) == tdf.OK
+        assert _same(programs.tree("lstm", False, True), forest, nodes=True) == tdf.OK
