@@ -932,7 +932,7 @@ __global__ void __launch_bounds__(Tile<MODE>::NW * 64) k_cell_small(GemmArgs g) 
   cell_small_tile<DT, MODE, 0, 0, false>(g, c, t, part, p, q, q.bias, (const TileB<MODE, 1>*)nullptr, nullptr, TailWait{}, nullptr, [] {}, [] {});
 }
 
-// Levels of at most this many cells take the small-level kernel (TDF_SMALL_LEVEL overrides).
+// Levels of at most this many cells take the small-level kernel where they are launched one by one (TDF_SMALL_LEVEL overrides).
 static uint32_t small_level() {
   const char* e = getenv("TDF_SMALL_LEVEL");
   return e ? (uint32_t)atoll(e) : 1024u;
@@ -1551,10 +1551,10 @@ __global__ void k_translate_rows(Engine e, const uint32_t* row_of, uint32_t n_ce
 }
 // dz of the cells of the tail that have no parent: the roots, whose dh came from the head (or the caller)
 template <int DT>
-__global__ void k_dz_tail_roots(VecArgs v, Engine e, const uint32_t* root_rows, uint32_t q_first) {
+__global__ void k_dz_tail_roots(VecArgs v, Engine e, const uint32_t* root_rows, uint32_t q_first, uint32_t q_end) {
   stamp_now(v.stamp);
   const uint32_t row = root_rows[blockIdx.x];
-  if (row >= e.row0 && row - e.row0 >= q_first) dz_row<DT>(v, e, row - e.row0);
+  if (row >= e.row0 && row - e.row0 >= q_first && row - e.row0 < q_end) dz_row<DT>(v, e, row - e.row0);
 }
 
 // Gradient-body firings counted on the device: the marks of all leaf and cell rows, summed, and the
@@ -2046,7 +2046,6 @@ void vec_cell_bwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count
   if (v.dtype == TDF_BF16) cell_bwd_t<__bf16>(v, e, q0, count, s); else cell_bwd_t<float>(v, e, q0, count, s);
 }
 
-uint32_t vec_small_level() { return small_level(); }
 
 // The levels lvl_first .. lvl_last in one launch, every die walking its own cells (k_tail_fwd).
 // level_off: device array of first cells by sort key; sync: eight zeroed DieSync records.
@@ -2088,6 +2087,18 @@ template <typename T> static void tail_fwd_t(const VecArgs& v, const Engine& e, 
   }
   if (v.cell_kind == 2) tail_fwd_mode<T, LSTM_FWD>(g, t, per_die, row_tiles, s);
   else tail_fwd_mode<T, RNN_FWD>(g, t, per_die, row_tiles, s);
+}
+// Levels of at most this many cells go to a tail on so many compute units per die: a level there takes some 1.2 us (TreeRNN)
+// or 1.9 us (TreeLSTM) for every row of tiles that its workgroups make side by side, a launch of its own 15 us and more
+// (1,024 trees of a TreeRNN of 300 units, training: 487 us with levels of 1,024 cells, 441 with 2,048, 430 with 3,072 to 6,000;
+// 4,096 trees of a TreeLSTM of 256 units forward: 1,282, 1,266, 1,280).
+uint32_t vec_tail_level(const VecArgs& v, int cus_per_die) {
+  if (getenv("TDF_SMALL_LEVEL")) return small_level();
+  const bool lstm = v.cell_kind == 2;
+  const int n_ct = v.Hp / (lstm ? Tile<LSTM_FWD>::UNITS : Tile<RNN_FWD>::UNITS), kc = v.dtype == TDF_BF16 ? Chunk<__bf16>::KC : Chunk<float>::KC;
+  const int n = lstm ? Tile<LSTM_FWD>::steps_most(v.Kp / kc) : Tile<RNN_FWD>::steps_most(v.Kp / kc);
+  const int wgs = n > 8 ? 0 : tail_wgs(cus_per_die * (n <= 4 ? 2 : 1), n_ct, 1u << 20);
+  return std::min<uint32_t>(8192u, std::max<uint32_t>(1024u, (uint32_t)(wgs / n_ct) * (lstm ? 640u : 1024u)));
 }
 // The tail's cells are the n_cells from q_first on.  per_die: compute units per accelerator die for this launch (all of its
 // workgroups must be resident together); most_rows: cells of a level on a die, at most
@@ -2141,11 +2152,11 @@ void vec_translate_rows(const Engine& e, const uint32_t* row_of, const LaneTotal
 }
 
 void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
-                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t most_rows,
+                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t n_cells, uint32_t most_rows,
                   const uint32_t* root_rows, hipStream_t s) {
   TailArgs t{level_off, lvl_first, lvl_last, n_dies, (DieSync*)sync, spin_ticks, q_first};
-  if (v.dtype == TDF_BF16) hipLaunchKernelGGL(k_dz_tail_roots<TDF_BF16>, dim3(e.n_inst), dim3(256), 0, s, v, e, root_rows, q_first);
-  else hipLaunchKernelGGL(k_dz_tail_roots<TDF_F32>, dim3(e.n_inst), dim3(256), 0, s, v, e, root_rows, q_first);
+  if (v.dtype == TDF_BF16) hipLaunchKernelGGL(k_dz_tail_roots<TDF_BF16>, dim3(e.n_inst), dim3(256), 0, s, v, e, root_rows, q_first, q_first + n_cells);
+  else hipLaunchKernelGGL(k_dz_tail_roots<TDF_F32>, dim3(e.n_inst), dim3(256), 0, s, v, e, root_rows, q_first, q_first + n_cells);
   if (v.dtype == TDF_BF16) tail_bwd_t<__bf16>(v, e, t, per_die, (most_rows + 15u) / 16u, s);
   else tail_bwd_t<float>(v, e, t, per_die, (most_rows + 15u) / 16u, s);
 }

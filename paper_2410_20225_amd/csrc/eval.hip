@@ -37,12 +37,12 @@ void vec_pack_w(const VecArgs& v, const LaneArgs* lanes, void* zero, size_t zero
 void vec_embed(const VecArgs& v, const Engine& e, uint32_t n_leaf, const LaneTotals* t, hipStream_t s);
 void vec_cell_fwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, int save_gates, hipStream_t s);
 void vec_cell_bwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, hipStream_t s);
-uint32_t vec_small_level();
+uint32_t vec_tail_level(const VecArgs& v, int cus_per_die);
 void vec_tail_fwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
                   uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t n_cells, uint32_t most_rows,
                   int save_gates, hipStream_t s);
 void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
-                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t most_rows,
+                  uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t n_cells, uint32_t most_rows,
                   const uint32_t* root_rows, hipStream_t s);
 void vec_translate_rows(const Engine& e, const uint32_t* row_of, const LaneTotals* t, uint32_t most, int has_head, int has_root,
                         float* zero, uint32_t n_zero, hipStream_t s);
@@ -153,7 +153,7 @@ tdf_status make_plan(const Graph& G, const tdf_inputs* in, bool with_grad, char*
     P.off_tok_count = L.take(sizeof(uint32_t) * ((size_t)in->vocab + 1));
     P.off_tok_fill = L.take(sizeof(uint32_t) * ((size_t)in->vocab + 1));
   }
-  P.off_tail_sync = L.take(sizeof(DieSync) * 16);   // forward and gradient tail launches
+  P.off_tail_sync = L.take(sizeof(DieSync) * 32);   // forward and gradient tail launches, of the deep instances and of the others
   size_t off_gmark = 0;
   if (P.vec && with_grad) {
     P.off_gcount = L.take(sizeof(unsigned long long) * 2);
@@ -758,10 +758,14 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   uint32_t sh_last = 0, deep_base = 0, q_deep0 = 0, n_wide_levels = 0;
   const uint32_t* level_off = nullptr;   // by sort key; in the pinned buffer
   auto lvl_begin = [&](uint32_t lvl) { return level_off[(size_t)lvl * LEVEL_KEY_DIES]; };
-  uint32_t tail_rows = 0;    // cells of one level and die among the tail's levels, at most
-  auto most_rows = [&](uint32_t key, uint32_t end_key) {
-    for (tail_rows = 0; key < end_key; ++key) tail_rows = std::max(tail_rows, level_off[key + 1] - level_off[key]);
+  auto most_rows = [&](uint32_t key, uint32_t end_key) {   // cells of one level and die, at most
+    uint32_t m = 0;
+    for (; key < end_key; ++key) m = std::max(m, level_off[key + 1] - level_off[key]);
+    return m;
   };
+  uint32_t tail_rows = 0, tail_cells = 0;   // of the tail on the caller's stream
+  int tail_per_die = cus / (int)XCDS;       // its compute units per die
+  char* tail_sync = base + P.off_tail_sync + 16 * sizeof(DieSync);
   if (dev == TDF_OK && P.vec) {
     // ---- vector operators: leaves at once, cells level by level --------------------------
     // From here on the next evaluation's tag machine may run (not beside an evaluation in the static
@@ -834,30 +838,31 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
         HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_deep, s));
         HIP_TRY(hipStreamWaitEvent(s2, (hipEvent_t)gr->fork_deep, 0));
       }
+      const uint32_t deep_rows = deep ? most_rows(deep_base + LEVEL_KEY_DIES, deep_base + (hc.max_level + 1) * LEVEL_KEY_DIES) : 0u;
       auto deep_chain = [&]() -> tdf_status {
         begin_on(TDF_PHASE_TAIL_FWD, sd);
         vec_tail_fwd(on(sd), e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync, spin_ticks, deep_per_die,
-                     q_deep0, hc.n_cell - q_deep0, tail_rows, with_grad, sd);
+                     q_deep0, hc.n_cell - q_deep0, deep_rows, with_grad, sd);
         end_on(TDF_PHASE_TAIL_FWD, 1, sd);
         if (G.has_head) vec_head(on(sd), e, dy->dy, 1, 1, sd);
         begin_on(TDF_PHASE_TAIL_BWD, sd);
         vec_tail_bwd(on(sd), e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
-                     spin_ticks, deep_per_die, q_deep0, tail_rows, G.has_head ? e.head_row : e.root_ref, sd);
+                     spin_ticks, deep_per_die, q_deep0, hc.n_cell - q_deep0, deep_rows, G.has_head ? e.head_row : e.root_ref, sd);
         end_on(TDF_PHASE_TAIL_BWD, 2, sd);
         if (beside) flush(sd);   // (its next launch waits for the other instances)
         if (beside) HIP_TRY(hipEventRecord((hipEvent_t)gr->join_deep, s2));
         return TDF_OK;
       };
       if (deep && G.out_type == T_VEC && !G.has_head) vec_seed_dy(on(s), e, dy->dy, s);   // (root rows of both classes)
-      if (deep) most_rows(deep_base + LEVEL_KEY_DIES, deep_base + (hc.max_level + 1) * LEVEL_KEY_DIES);
       if (deep)
         if (tdf_status ds = deep_chain(); ds != TDF_OK) return ds;   // beside: on the side stream; else first, on the caller's
       // ---- the (other) instances on the caller's stream: wide levels one launch each; the narrow
-      // levels behind them in one launch in which every die walks its own cells (unless the side
-      // stream already runs such a launch)
+      // levels behind them in one launch in which every die walks its own cells
+      if (deep_beside) tail_per_die = std::max(1, tail_per_die - deep_wgs);
+      const uint32_t tail_level = vec_tail_level(v, tail_per_die);
       tail_first = sh_last + 1;
-      while (tail_first > 1 && lvl_begin(tail_first) - lvl_begin(tail_first - 1) <= vec_small_level()) --tail_first;
-      use_tail = !deep && gr->die_local && sh_last + 1 - tail_first >= 4;
+      while (tail_first > 1 && lvl_begin(tail_first) - lvl_begin(tail_first - 1) <= tail_level) --tail_first;
+      use_tail = gr->die_local && sh_last + 1 - tail_first >= 4;
       if (!use_tail) tail_first = sh_last + 1;
       n_wide_levels = tail_first - 1;
       begin(TDF_PHASE_CELLS_FWD);
@@ -865,11 +870,12 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
         if (const uint32_t n = lvl_begin(lvl + 1) - lvl_begin(lvl)) vec_cell_fwd(on(s), e, lvl_begin(lvl), n, with_grad, s);
       end(TDF_PHASE_CELLS_FWD, tail_first - 1);
       if (use_tail) {
-        most_rows(tail_first * LEVEL_KEY_DIES, (sh_last + 1) * LEVEL_KEY_DIES);
-        begin(TDF_PHASE_TAIL_FWD);
-        vec_tail_fwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, base + P.off_tail_sync, spin_ticks, cus / (int)XCDS,
-                     lvl_begin(tail_first), hc.n_cell - lvl_begin(tail_first), tail_rows, with_grad, s);
-        end(TDF_PHASE_TAIL_FWD, 1);
+        tail_rows = most_rows(tail_first * LEVEL_KEY_DIES, (sh_last + 1) * LEVEL_KEY_DIES);
+        tail_cells = q_deep0 - lvl_begin(tail_first);
+        if (!deep) begin(TDF_PHASE_TAIL_FWD);   // (with deep instances these levels count among the level launches)
+        vec_tail_fwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, tail_sync, spin_ticks, tail_per_die,
+                     lvl_begin(tail_first), tail_cells, tail_rows, with_grad, s);
+        if (!deep) end(TDF_PHASE_TAIL_FWD, 1);
       }
     }
     if (!hc.n_cell) {   // leaves only
@@ -901,10 +907,10 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (with_grad) {
       // ---- gradient pass: the level schedule walked backwards -----------------------------
       if (use_tail && hc.n_cell) {
-        begin(TDF_PHASE_TAIL_BWD);
-        vec_tail_bwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
-                     spin_ticks, cus / (int)XCDS, lvl_begin(tail_first), tail_rows, G.has_head ? e.head_row : e.root_ref, s);
-        end(TDF_PHASE_TAIL_BWD, 2);
+        if (!deep) begin(TDF_PHASE_TAIL_BWD);
+        vec_tail_bwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, tail_sync + 8 * sizeof(DieSync), spin_ticks, tail_per_die,
+                     lvl_begin(tail_first), tail_cells, tail_rows, G.has_head ? e.head_row : e.root_ref, s);
+        if (!deep) end(TDF_PHASE_TAIL_BWD, 2);
       }
       begin(TDF_PHASE_CELLS_BWD);
       for (uint32_t lvl = tail_first - 1; lvl >= 1 && hc.n_cell; --lvl)
@@ -954,7 +960,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (use_tail || deep) {
       const DieSync* ts = (const DieSync*)fin->sync;
       bool mixed = false, gave_up = false;
-      for (int k = 0; k < 16; ++k) {
+      for (int k = 0; k < 32; ++k) {
         const DieSync& d = ts[k];
         mixed = mixed || (d.xcc_mask & (d.xcc_mask - 1)) != 0;
         gave_up = gave_up || d.abort != 0;

@@ -534,7 +534,7 @@ __global__ void __launch_bounds__(256) k_finish(LaneArgs a, EndArgs g, Stamp st)
     if (threadIdx.x < 2 * TDF_PHASE_COUNT) g.end->stamps[threadIdx.x] = g.stamps[threadIdx.x];
   }
   if (g.sync)
-    for (uint32_t i = threadIdx.x; i < 16u * sizeof(DieSync) / 4; i += blockDim.x)
+    for (uint32_t i = threadIdx.x; i < 32u * sizeof(DieSync) / 4; i += blockDim.x)
       reinterpret_cast<uint32_t*>(g.end->sync)[i] = reinterpret_cast<const uint32_t*>(g.sync)[i];
   __threadfence_system();
   __syncthreads();

@@ -28,7 +28,7 @@ void set_error(const std::string& msg);
 // The end of an evaluation: what its last kernel leaves in pinned memory for the host; `seq` is written last.
 struct EndReport {
   LaneTotals t;
-  uint32_t sync[16][32];          // DieSync records of the chain launches (forward, gradient)
+  uint32_t sync[32][32];          // DieSync records of the chain launches (forward, gradient; deep instances and others)
   unsigned long long gcount[2];
   unsigned long long stamps[2 * TDF_PHASE_COUNT];
   uint32_t seq;
