@@ -1802,8 +1802,17 @@ __global__ void k_reduce_dw(VecArgs v, float* dW, int splits) {
   for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < R * K2; idx += gridDim.x * blockDim.x) {
     const int n = idx / K2, k = idx % K2;
     const int np = (n / v.H) * v.Hp + n % v.H, kp = (k / v.H) * v.Hp + k % v.H;
+    const float* const part = v.dW_part + (size_t)np * v.Kp + kp;
+    const size_t step = (size_t)v.Np * v.Kp;
     float s = 0.f;
-    for (int z = 0; z < splits; ++z) s += v.dW_part[((size_t)z * v.Np + np) * v.Kp + kp];
+    for (int z0 = 0; z0 < splits; z0 += 8) {   // eight partial tiles in flight, added in order (one: 68 us for 16 of 1280 x 512)
+      float x[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = part[(size_t)min(z0 + j, splits - 1) * step];
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (z0 + j < splits) s += x[j];
+    }
     dW[idx] = s;
   }
 }
@@ -1961,9 +1970,15 @@ __global__ void __launch_bounds__(256) k_de_final(VecArgs v, const uint32_t* chu
   if ((v.H & 3) == 0) {
     for (int n = lane * 4; n < v.H; n += 256) {
       float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (uint32_t c = c_lo; c < c_hi; ++c) {
-        const float4 x = *reinterpret_cast<const float4*>(part + (size_t)c * v.Hp + n);
-        s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+      for (uint32_t c0 = c_lo; c0 < c_hi; c0 += 8) {   // eight rows in flight, added in chunk order
+        float4 x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = *reinterpret_cast<const float4*>(part + (size_t)min(c0 + j, c_hi - 1) * v.Hp + n);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (c0 + j < c_hi) {
+            s.x += x[j].x; s.y += x[j].y; s.z += x[j].z; s.w += x[j].w;
+          }
       }
       *reinterpret_cast<float4*>(dE + (size_t)tok * v.H + n) = s;
     }
@@ -2222,7 +2237,7 @@ static void weight_grads_direct(const VecArgs& v, const Engine& e, uint32_t n_q,
   g.db_part = db_part;
   const int n_mt = (v.Np + DWT - 1) / DWT;
   hipLaunchKernelGGL(k_dw_direct, dim3(8 * n_mt * g.n_tiles_n * ((splits + 7) / 8)), dim3(256), 0, s, g);
-  hipLaunchKernelGGL(k_reduce_dw, dim3(512), dim3(256), 0, s, v, dW, splits);
+  hipLaunchKernelGGL(k_reduce_dw, dim3(1024), dim3(256), 0, s, v, dW, splits);
   hipLaunchKernelGGL(k_db_final, dim3((v.Np + 15) / 16), dim3(256), 0, s, v, db_part, splits, 1, db);
 }
 
@@ -2243,7 +2258,7 @@ template <typename T> static void weight_grads_t(const VecArgs& v, const Engine&
   g.C = v.dW_part; g.ldc = v.Kp;
   g.k_per_split = kps;
   launch_gemm<T, DW_SPLIT>(g, (v.Kp + 127) / 128, splits, s);
-  hipLaunchKernelGGL(k_reduce_dw, dim3(512), dim3(256), 0, s, v, dW, splits);
+  hipLaunchKernelGGL(k_reduce_dw, dim3(1024), dim3(256), 0, s, v, dW, splits);
   const int parts = (int)(v.q_stride / 64);   // written by the transpose of Dz above
   hipLaunchKernelGGL(k_db_runs, dim3((v.Np + 63) / 64, (parts + DB_RUN - 1) / DB_RUN), dim3(256), 0, s, v, db_part, parts);
   hipLaunchKernelGGL(k_db_final, dim3((v.Np + 15) / 16), dim3(256), 0, s, v, db_part, (parts + DB_RUN - 1) / DB_RUN, DB_RUN, db);

@@ -63,7 +63,7 @@ void vec_embed_sums(const VecArgs& v, uint32_t n_leaf, const uint32_t* seg_off, 
 namespace {
 
 constexpr uint32_t WALK_NODES = 32768;   // nodes an instance, on average, up to which a wave walks its tree (forest_walk.hip)
-constexpr uint32_t DE_CHUNK = 128;
+constexpr uint32_t DE_CHUNK = 128;   // leaves of a token that a wave sums, at most (the workspace holds the sums of chunks of so many)
 constexpr uint32_t DB_CHUNK = 64;
 
 struct Layout {
@@ -763,6 +763,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     for (; key < end_key; ++key) m = std::max(m, level_off[key + 1] - level_off[key]);
     return m;
   };
+  uint32_t de_chunk = DE_CHUNK;
   uint32_t tail_rows = 0, tail_cells = 0;   // of the tail on the caller's stream
   int tail_per_die = cus / (int)XCDS;       // its compute units per die
   char* tail_sync = base + P.off_tail_sync + 16 * sizeof(DieSync);
@@ -886,9 +887,13 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       // Gradient runs have a third stream: the embedding gradient's token sort needs the leaf log only, and has
       // until the gradient pass's end.  (The host's time for its launches is not in the way of the cells' here.)
       HIP_TRY(hipStreamWaitEvent(s3, (hipEvent_t)gr->fork_sort, 0));
+      // A frequent token's chunk is a serial sum, and the wait of a small batch (1,300 leaves, the commonest token a tenth of
+      // them: 44 us with chunks of 128): as short as the room for the sums allows.
+      const uint64_t room = (uint64_t)e.log_cap / DE_CHUNK + (uint64_t)v.vocab + 1u;
+      for (de_chunk = 16; de_chunk < DE_CHUNK && hc.n_leaf / de_chunk + std::min<uint64_t>(v.vocab, hc.n_leaf) + 1u > room;) de_chunk *= 2;
       vec_embed_sort(v, e, hc.n_leaf, (uint32_t*)(base + P.off_tok_count), (uint32_t*)(base + P.off_seg_off),
                      (uint32_t*)(base + P.off_chunk_off), (uint32_t*)(base + P.off_tok_fill),
-                     (uint32_t*)(base + P.off_sorted), DE_CHUNK, s3);
+                     (uint32_t*)(base + P.off_sorted), de_chunk, s3);
     }
     begin(TDF_PHASE_HEAD);
     if (G.has_head) {
@@ -927,7 +932,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       HIP_TRY(hipStreamWaitEvent(s3, (hipEvent_t)gr->fork_event, 0));
       begin_on(TDF_PHASE_EMBED_GRAD, s3);
       vec_embed_sums(on(s3), hc.n_leaf, (const uint32_t*)(base + P.off_seg_off), (const uint32_t*)(base + P.off_chunk_off),
-                     (const uint32_t*)(base + P.off_sorted), (float*)(base + P.off_de_part), grads->dE, DE_CHUNK, s3);
+                     (const uint32_t*)(base + P.off_sorted), (float*)(base + P.off_de_part), grads->dE, de_chunk, s3);
       end_on(TDF_PHASE_EMBED_GRAD, 5, s3);
       // how often each tag's gradient body fired, as the kernels marked it (the cells' marks are complete
       // since the gradient pass, the leaves' since the sums just above)

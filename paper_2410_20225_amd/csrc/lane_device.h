@@ -708,7 +708,11 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     // ---- a few sweeps
     bool any_done = false;
     const uint32_t n_run = (uint32_t)__popcll(__ballot(x.run));
-    const uint32_t n_sweeps = n_run >= 48 ? LANE_SYNC_FULL : hungry ? 2u : LANE_SYNC;
+    // Early on, while a few lanes have all the work, or a run that fills the GPU spreads over its waves, the lanes look at
+    // one another after every sweep (8 recursions of 3 to 10 levels: 106 us with four sweeps between, 90 now; fib(0..20) 214
+    // and 202; fib(30..32) 4,650 and 3,980.  With as many lanes busy in a run of 447 waves fib(0..20) takes 240).
+    const bool spread = iter < LANE_EARLY && (n_run < 32 || a.n_waves >= 1024u);
+    const uint32_t n_sweeps = spread ? 1u : n_run >= 48 ? LANE_SYNC_FULL : hungry ? 2u : LANE_SYNC;
 #pragma unroll 1
     for (uint32_t k = 0; k < n_sweeps; ++k) {
       if (__ballot(x.run) == 0) break;
