@@ -583,6 +583,7 @@ struct DzFuse {
 struct TileAt {
   uint32_t q0;
   int M, ct;
+  uint32_t lvl;   // of the walk
 };
 // What a tile reads that no tile writes, in the steps that follow one another: rows of the children (TileRows, to which
 // the fused dz adds the rows of the children's children), and what these lead to (TileAhead): operands of children that
@@ -593,7 +594,14 @@ template <int MODE> struct TileRows {
   uint32_t o_l, o_r;                // children of the lane's element
   uint32_t z_q, z_gl, z_gr;         // fused dz: the child cell (none: all ones) and its children's rows
 };
+// LOOK: a tile that is not its workgroup's first of a level reads rows that are likely there already: the tile before looks
+// for them while it sums and finishes.  Gradient tails of a TreeLSTM (127 levels of up to 80 cells a die beside the level
+// launches 1,635 -> 1,306 us); the forward ones, whose workgroups share a compute unit, gain nothing (827 us either way).
 template <int MODE, int RES, int CELL> struct TileAhead {
+  static constexpr bool LOOK = CELL == 2 && RES == 5;
+  u32x4 look[LOOK ? RES : 1];
+  uint32_t u0, u1;
+  bool looked;   // (uniform)
   u32x4 a[RES > 0 && MODE != DX_BWD ? RES : 1];   // the lane's operands, if its child is complete
   float bias[Tile<MODE>::G];   // (RES == 0)
   float c_l, c_r;                             // cell states of complete children (TreeLSTM)
@@ -679,6 +687,61 @@ __device__ __forceinline__ void tile_ahead(const GemmArgs& g, const TileLane& c,
   }
 }
 
+// The rows that a tile waits for: where, and whether this lane has any.
+template <typename T, int MODE> struct TileWaits {
+  FreshRows rows;
+  uint64_t off;                 // of the lane's operands, bytes
+  bool fresh;
+  const float *w0, *w1;         // values of single elements: the children's cell states (forward), dc of the child cell (gradient)
+  bool f0, f1;
+};
+template <int DT, int MODE, int CELL>
+__device__ __forceinline__ TileWaits<typename TypeOf<DT>::type, MODE> tile_waits(const GemmArgs& g, const TileLane& c, const TileAt& t,
+                                                                                 const TileRows<MODE>& p, const DzFuse* fz) {
+  typedef typename TypeOf<DT>::type T;
+  const int lane = threadIdx.x & 63;
+  const bool valid = (lane & 15) < t.M, el = c.row < t.M;
+  const int unit = t.ct * Tile<MODE>::UNITS + c.col;
+  TileWaits<T, MODE> r{};
+  if constexpr (MODE == DX_BWD) {   // (a tile of the gradient tail: all its rows)
+    r.rows = fresh_rows(reinterpret_cast<const T*>(g.A) + (uint64_t)t.q0 * (uint32_t)g.lda);
+    r.off = ((uint32_t)(lane & 15) * (uint32_t)g.lda + c.a) * (uint32_t)sizeof(T);
+    r.fresh = valid;
+  } else {
+    r.rows = fresh_rows(reinterpret_cast<const T*>(g.Hs) + g.fresh_row * (uint32_t)g.Hp);
+    r.off = ((uint64_t)(p.child - g.fresh_row) * (uint32_t)g.Hp + c.a) * sizeof(T);
+    r.fresh = valid && p.child >= g.fresh_row;
+  }
+  if constexpr (MODE == LSTM_FWD) {
+    r.f0 = el && p.o_l >= g.fresh_row;
+    r.f1 = el && p.o_r >= g.fresh_row;
+    r.w0 = g.Cs + (p.o_l * (uint32_t)g.Hp + (uint32_t)unit);
+    r.w1 = g.Cs + (p.o_r * (uint32_t)g.Hp + (uint32_t)unit);
+  }
+  if constexpr (CELL == 2) {
+    r.f0 = p.z_q != 0xFFFFFFFFu;
+    r.w0 = fz->v->dC + ((fz->row0 + p.z_q) * (uint32_t)g.Hp + (uint32_t)(unit < g.Hp ? unit : unit - g.Hp));
+  }
+  return r;
+}
+template <int DT, int MODE, int RES, int CELL>
+__device__ __forceinline__ void tile_look(const GemmArgs& g, const TileLane& c, const TileAt& t, const TileRows<MODE>& p, const DzFuse* fz,
+                                          TileAhead<MODE, RES, CELL>& q) {
+  typedef typename TypeOf<DT>::type T;
+  typedef Chunk<T> C;
+  if constexpr (TileAhead<MODE, RES, CELL>::LOOK) {
+    const auto w = tile_waits<DT, MODE, CELL>(g, c, t, p, fz);
+#pragma unroll
+    for (int st = 0; st < RES; ++st) {
+      q.look[st] = u32x4{0u, 0u, 0u, 0u};
+      if (w.fresh && st < c.n) q.look[st] = load_fresh16(w.rows, w.off + (uint32_t)(st * C::KC * (int)sizeof(T)), MODE == DX_BWD || g.fresh_narrow);
+    }
+    q.u0 = q.u1 = 0;
+    if (w.f0) q.u0 = load_fresh(w.w0);
+    if (MODE == LSTM_FWD && w.f1) q.u1 = load_fresh(w.w1);
+  }
+}
+
 // Waiting for rows of other workgroups: `attempt` looks again (true: this lane has what it needs) until all lanes of the
 // wave have.  False: no workgroup of the die has got anywhere for spin_ticks, or another one has given up.
 struct TailWait {
@@ -728,36 +791,15 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
   const T* Ap;
   if constexpr (MODE == DX_BWD) Ap = reinterpret_cast<const T*>(g.A) + ((uint64_t)(t.q0 + (uint32_t)(lane & 15)) * (uint32_t)g.lda + c.a);
   else Ap = reinterpret_cast<const T*>(g.Hs) + (p.child * (uint32_t)g.Hp + c.a);
-  FreshRows rows{};
-  uint64_t off = 0;   // of the lane's operands, bytes
-  if constexpr (WAIT && MODE == DX_BWD) {
-    rows = fresh_rows(reinterpret_cast<const T*>(g.A) + (uint64_t)t.q0 * (uint32_t)g.lda);
-    off = ((uint32_t)(lane & 15) * (uint32_t)g.lda + c.a) * (uint32_t)sizeof(T);
-  } else if constexpr (WAIT) {
-    rows = fresh_rows(reinterpret_cast<const T*>(g.Hs) + g.fresh_row * (uint32_t)g.Hp);
-    off = ((uint64_t)(p.child - g.fresh_row) * (uint32_t)g.Hp + c.a) * sizeof(T);
-  }
-  const bool narrow = MODE == DX_BWD || g.fresh_narrow;
-  const bool fresh = WAIT && valid && (MODE == DX_BWD || p.child >= g.fresh_row);   // (a tile of the gradient tail: all its rows)
-
+  TileWaits<T, MODE> tw{};
+  if constexpr (WAIT) tw = tile_waits<DT, MODE, CELL>(g, c, t, p, fz);
+  const bool narrow = MODE == DX_BWD || g.fresh_narrow, fresh = tw.fresh;
   const int unit = t.ct * TL::UNITS + c.col;
   const bool el = c.row < t.M;   // the lane's element exists
   const bool z_left = unit < g.Hp;
   const uint32_t z_n = (uint32_t)(z_left ? unit : unit - g.Hp);
-  // values of single elements that are waited for: the children's cell states (forward), dc of the child cell (gradient)
-  const float *w0 = nullptr, *w1 = nullptr;
   uint32_t u0 = 0, u1 = 0;
-  bool f0 = false, f1 = false;
-  if constexpr (WAIT && MODE == LSTM_FWD) {
-    f0 = el && p.o_l >= g.fresh_row;
-    f1 = el && p.o_r >= g.fresh_row;
-    w0 = g.Cs + (p.o_l * (uint32_t)g.Hp + (uint32_t)unit);
-    w1 = g.Cs + (p.o_r * (uint32_t)g.Hp + (uint32_t)unit);
-  }
-  if constexpr (CELL == 2) {
-    f0 = p.z_q != 0xFFFFFFFFu;
-    w0 = fz->v->dC + ((fz->row0 + p.z_q) * (uint32_t)g.Hp + z_n);
-  }
+  const bool f0 = tw.f0, f1 = tw.f1;
 
   f32x4 acc[TL::NB];
 #pragma unroll
@@ -780,14 +822,7 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
           if (valid && !fresh && st < cnt) fa[st] = *reinterpret_cast<const u32x4*>(Ap + (st0 + st) * C::KC);
       }
       bool o0 = f0 && st0 == 0, o1 = f1 && st0 == 0;
-      const bool ok = wait_rows(w, [&] {
-#pragma unroll
-        for (int st = 0; st < BATCH; ++st)
-          if (open[st]) fa[st] = load_fresh16(rows, off + (uint32_t)((st0 + st) * C::KC * (int)sizeof(T)), narrow);
-        if (MODE == LSTM_FWD || CELL == 2) {   // (written right behind the rows)
-          if (o0) u0 = load_fresh(w0);
-          if (MODE == LSTM_FWD && o1) u1 = load_fresh(w1);
-        }
+      auto still_open = [&] {
         bool any = false;
 #pragma unroll
         for (int st = 0; st < BATCH; ++st) {
@@ -796,7 +831,27 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
         }
         o0 = o0 && u0 == F_NONE;
         o1 = o1 && u1 == F_NONE;
-        return !(any || o0 || o1);
+        return any || o0 || o1;
+      };
+      bool there = false;
+      if constexpr (TileAhead<MODE, RES, CELL>::LOOK) {
+        if (q.looked) {
+#pragma unroll
+          for (int st = 0; st < BATCH; ++st) fa[st] = q.look[st];
+          u0 = q.u0;
+          u1 = q.u1;
+          there = !__any(still_open());
+        }
+      }
+      const bool ok = there || wait_rows(w, [&] {
+#pragma unroll
+        for (int st = 0; st < BATCH; ++st)
+          if (open[st]) fa[st] = load_fresh16(tw.rows, tw.off + (uint32_t)((st0 + st) * C::KC * (int)sizeof(T)), narrow);
+        if (MODE == LSTM_FWD || CELL == 2) {   // (written right behind the rows)
+          if (o0) u0 = load_fresh(tw.w0);
+          if (MODE == LSTM_FWD && o1) u1 = load_fresh(tw.w1);
+        }
+        return !still_open();
       });
       if (!ok) *failed = 1u;
       // (Whatever was requested is here by now.  Said in so many words, or the compiler, which does not know that on the way
@@ -923,7 +978,7 @@ __global__ void __launch_bounds__(Tile<MODE>::NW * 64) k_cell_small(GemmArgs g) 
   __shared__ __attribute__((aligned(16))) float part[Tile<MODE>::PART];
   stamp_now(g.stamp);
   const int rt = blockIdx.x / g.n_tiles_n, ct = blockIdx.x % g.n_tiles_n;   // (column tiles of one row tile side by side)
-  const TileAt t{(uint32_t)rt * Tile<MODE>::ROWS, min(Tile<MODE>::ROWS, g.M - rt * Tile<MODE>::ROWS), ct};
+  const TileAt t{(uint32_t)rt * Tile<MODE>::ROWS, min(Tile<MODE>::ROWS, g.M - rt * Tile<MODE>::ROWS), ct, 0};
   TileRows<MODE> p;
   TileAhead<MODE, 0, 0> q;
   const TileLane c = tile_lane<DT, MODE>(g);
@@ -1316,12 +1371,12 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
     const uint32_t rows = (end - q0 + TL::ROWS - 1) / TL::ROWS, row = RES > 0 ? t : t / n_ct;
     if (row >= rows) return false;
     const uint32_t at = q0 + row * TL::ROWS;
-    r = TileAt{at, (int)min((uint32_t)TL::ROWS, end - at), (int)(RES > 0 ? rank % n_ct : t % n_ct)};
+    r = TileAt{at, (int)min((uint32_t)TL::ROWS, end - at), (int)(RES > 0 ? rank % n_ct : t % n_ct), k};
     t += step;
     return true;
   };
   auto next = [&]() -> TileAt {
-    TileAt r{0, 0, 0};
+    TileAt r{0, 0, 0, 0};
     if (tile_of(r) || k + 1 >= n_lvl) return r;
     take(next_q0, next_end);
     for (++k, t = first; !tile_of(r) && k + 1 < n_lvl; t = first) {   // (levels without a tile for this workgroup)
@@ -1363,7 +1418,13 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
   auto tile = [&](uint32_t side, const TileAt& t, const TileRows<MODE>& p, const TileAhead<MODE, RES, CELL>& a, const TileAt& ta1,
                   const TileRows<MODE>& pa1, TileAhead<MODE, RES, CELL>& a1, const TileAt& ta2, TileRows<MODE>& pa2, TileAt& ta3,
                   TileRows<MODE>& pa3) __attribute__((always_inline)) {
-    return t.M && cell_small_tile<DT, MODE, RES, CELL, true>(g, c, t, part + side * TL::PART, p, a, RES > 0 ? bias : a.bias, b, fz, w, failed + side, [&] { ta3 = next(); }, [&] {
+    return t.M && cell_small_tile<DT, MODE, RES, CELL, true>(g, c, t, part + side * TL::PART, p, a, RES > 0 ? bias : a.bias, b, fz, w, failed + side, [&] {
+      ta3 = next();
+      if constexpr (TileAhead<MODE, RES, CELL>::LOOK) {
+        a1.looked = ta1.M && ta1.lvl == t.lvl;
+        if (a1.looked) tile_look<DT, MODE, RES, CELL>(g, c, ta1, pa1, fz, a1);
+      }
+    }, [&] {
       tile_rows<MODE>(g, c, ta3, pa3);
       tile_rows2<DT, MODE, CELL>(g, c, ta2, fz, pa2);
       if (ta1.M) tile_ahead<DT, MODE, RES, CELL>(g, c, ta1, fz, pa1, a1);
