@@ -215,8 +215,8 @@ typedef struct {
   int32_t step_limit; /* steps of the step machine; 0 = default (1<<20).  With another value
                          the evaluation runs on it                                       */
   int32_t stats_level; /* 0: counters and phase times; an evaluation with no more tags than
-                          max_tags may run on the depth-first lanes, which keep no frames, any
-                          other one runs on the step machine; 1: also tdf_stats.fire_count (one
+                          max_tags may run without frames, as a walk over the forest or on the
+                          depth-first lanes, any other one runs on the step machine; 1: also tdf_stats.fire_count (one
                           extra pass over the frame table after the evaluation); 2: also the
                           size and duration of the tag machines' widest steps              */
 } tdf_inputs;
@@ -247,8 +247,9 @@ typedef struct {
 
 /* Phases of one evaluation, timed by the clock that the first kernel of each phase reads. */
 enum {
-  TDF_PHASE_TAGS = 0,    /* the step machine (clear, seed, all match/fire steps) or the lanes
-                            (clear and weight packing, the lanes: two launches)            */
+  TDF_PHASE_TAGS = 0,    /* the step machine (clear, seed, all match/fire steps) or the walk
+                            over the forest or the lanes (clear and weight packing, then
+                            one launch)                                                    */
   TDF_PHASE_LEAVES,      /* EMBED rows (after the step machine: and weight packing)        */
   TDF_PHASE_LEVELS,      /* bucketing of the cell firings by dependency level              */
   TDF_PHASE_CELLS_FWD,   /* cell GEMMs of the wide levels, one launch per level            */
@@ -265,7 +266,7 @@ enum {
 typedef struct {
   int64_t n_tags;         /* tags created = function invocations + loop iterations      */
   int64_t n_steps;        /* match/fire steps of the tag machine; on the lanes the most sweeps
-                             of one of their waves                                      */
+                             of one of their waves, on the walk those of its longest wave */
   int64_t n_tokens;       /* Call and Return tokens delivered                           */
   int64_t n_leaf_rows;    /* EMBED firings                                              */
   int64_t n_cell_rows;    /* RNN_CELL / LSTM_CELL firings                               */

@@ -424,7 +424,7 @@ tdf_status wait_report(const uint32_t* word, uint32_t seq, hipStream_t s) {
 
 // Evaluations of one process take turns, in two stages.  The control plane (the tag machine: persistent
 // step kernels whose workgroups must all be resident, one machine per die) of one evaluation at a time;
-// the data plane (level launches, the chain launches with their die barriers, the gradient sums) of one
+// the data plane (level launches, the chain launches whose workgroups wait for each other's rows, the gradient sums) of one
 // evaluation at a time; but the control plane of one evaluation may run beside the data plane of the
 // one before it, which depends on other inputs' trees only: while a tag machine walks its narrow steps
 // most compute units have nothing else to do.  The data stage ends with the gradient pass: the sums that
@@ -791,7 +791,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       end(TDF_PHASE_LEAVES, 2);
       if (with_grad) HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_sort, s));
     }
-    const int deep_wgs = getenv("TDF_DEEP_WGS") ? std::max(1, atoi(getenv("TDF_DEEP_WGS"))) : 20;   // workgroups per die
+    const int deep_wgs = getenv("TDF_DEEP_WGS") ? std::max(1, atoi(getenv("TDF_DEEP_WGS"))) : 20;   // compute units per die
     if (hc.n_cell) {
       const size_t level_bytes = (size_t)n_keys * sizeof(uint32_t);
       if (!rows_known) {
@@ -979,7 +979,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
                    inherited_repeats + (int)repeats + 1, no_alloc, true);
       }
       if (gave_up && !mixed) {
-        set_error("device: a workgroup waited too long at a die barrier of the level tail");
+        set_error("device: a workgroup of the level tail waited too long");
         return TDF_ERR_DEVICE;
       }
       if (mixed) {   // the die-private launches did not keep to their dies: the results are void
@@ -1098,8 +1098,8 @@ extern "C" tdf_status tdf_workspace_size(const tdf_graph* g, const tdf_inputs* i
   return TDF_OK;
 }
 
-// The step kernels and the chain launches are persistent: their workgroups wait for each other at
-// barriers, so all of them must be on the GPU together.  Two tag machines, or two data planes, in
+// The step kernels and the chain launches are persistent: their workgroups wait for each other,
+// so all of them must be on the GPU together.  Two tag machines, or two data planes, in
 // flight on different streams could each hold a part of the compute units and wait for the rest (the
 // bounded waits would end that with TDF_ERR_DEVICE, not a hang): evaluations of one process take
 // turns, stage by stage (EvalLocks).

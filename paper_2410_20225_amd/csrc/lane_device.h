@@ -708,10 +708,12 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     // ---- a few sweeps
     bool any_done = false;
     const uint32_t n_run = (uint32_t)__popcll(__ballot(x.run));
-    // Early on, while a few lanes have all the work, or a run that fills the GPU spreads over its waves, the lanes look at
-    // one another after every sweep (8 recursions of 3 to 10 levels: 106 us with four sweeps between, 90 now; fib(0..20) 214
-    // and 202; fib(30..32) 4,650 and 3,980.  With as many lanes busy in a run of 447 waves fib(0..20) takes 240).
-    const bool spread = iter < LANE_EARLY && (n_run < 32 || a.n_waves >= 1024u);
+    // Early on, while a few lanes have all the work, or at first in a run that fills the GPU, the lanes look at one another
+    // after every sweep (8 recursions of 3 to 10 levels: 104 us with four sweeps between, 89 now; 1,000 of 3 to 12: 147 and
+    // 115; fib(0..20) 214 and 199; 256 of tak 2,940 and 2,720; fib(30..32) 5,050 and 4,660.  With as many lanes busy in a
+    // run of 447 waves fib(0..20) takes 240; for 48 sweeps instead of 16 in a run that fills the GPU 300 of fib(5..18) 330
+    // instead of 252).  Where no function has two calls there is nothing to give.
+    const bool spread = SW::kBranching && iter < LANE_EARLY && (n_run < 32 || (a.n_waves >= 1024u && iter < LANE_EARLY / 3));
     const uint32_t n_sweeps = spread ? 1u : n_run >= 48 ? LANE_SYNC_FULL : hungry ? 2u : LANE_SYNC;
 #pragma unroll 1
     for (uint32_t k = 0; k < n_sweeps; ++k) {
