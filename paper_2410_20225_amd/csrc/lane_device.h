@@ -708,12 +708,16 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     // ---- a few sweeps
     bool any_done = false;
     const uint32_t n_run = (uint32_t)__popcll(__ballot(x.run));
-    // Early on, while a few lanes have all the work, or at first in a run that fills the GPU, the lanes look at one another
-    // after every sweep (8 recursions of 3 to 10 levels: 104 us with four sweeps between, 89 now; 1,000 of 3 to 12: 147 and
-    // 115; fib(0..20) 214 and 199; 256 of tak 2,940 and 2,720; fib(30..32) 5,050 and 4,660.  With as many lanes busy in a
-    // run of 447 waves fib(0..20) takes 240; for 48 sweeps instead of 16 in a run that fills the GPU 300 of fib(5..18) 330
-    // instead of 252).  Where no function has two calls there is nothing to give.
-    const bool spread = SW::kBranching && iter < LANE_EARLY && (n_run < 32 || (a.n_waves >= 1024u && iter < LANE_EARLY / 3));
+    // Early on the lanes look at one another after every sweep instead of every fourth in two cases.  While a few lanes
+    // of the wave have all the work (8 recursions of 3 to 10 levels: 104 us, now 89; 1,000 of 3 to 12: 147 and 115;
+    // fib(0..20) 214 and 199; 64 of tak 830 and 760; with as many lanes busy fib(0..20) takes 240), but not in a run that
+    // fills the GPU from a few roots, which pieces that small only chop up (fib(28) alone 720 us, 800 with it).  And
+    // at first, however many lanes are busy, in such a run with 1,024 tags and more for a wave (fib(30..32) 4,810 and
+    // 4,100; with fewer tags fib(28) again, and for 48 sweeps instead of 16 300 of fib(5..18) 330 instead of 250).
+    // Where no function has two calls there is nothing to give.
+    const bool fills = a.n_waves >= 1024u, few = n_run < 32 && (!fills || a.n_inst >= 16u);
+    const bool spread = SW::kBranching && iter < LANE_EARLY &&
+                        (few || (fills && iter < LANE_EARLY / 3 && a.tags_at_once >= 512u));
     const uint32_t n_sweeps = spread ? 1u : n_run >= 48 ? LANE_SYNC_FULL : hungry ? 2u : LANE_SYNC;
 #pragma unroll 1
     for (uint32_t k = 0; k < n_sweeps; ++k) {
