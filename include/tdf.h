@@ -252,13 +252,15 @@ enum {
                             one launch)                                                    */
   TDF_PHASE_LEAVES,      /* EMBED rows (after the step machine: and weight packing)        */
   TDF_PHASE_LEVELS,      /* bucketing of the cell firings by dependency level              */
-  TDF_PHASE_CELLS_FWD,   /* cell GEMMs of the wide levels, one launch per level            */
+  TDF_PHASE_CELLS_FWD,   /* cell GEMMs of the wide levels, one launch per level; where deep
+                            instances run apart, also the other instances' narrow levels   */
   TDF_PHASE_HEAD,        /* head / result rows / gradient seeds                            */
   TDF_PHASE_CELLS_BWD,   /* gradient bodies of the cells of the wide levels, in reverse    */
   TDF_PHASE_WEIGHT_GRAD, /* dW, db                                                         */
   TDF_PHASE_EMBED_GRAD,  /* dE: the per-token sums (beside the weight gradients; the token
                             sort ran earlier, beside the cells)                            */
-  TDF_PHASE_TAIL_FWD,    /* cells of the deep, narrow levels: one launch for all of them   */
+  TDF_PHASE_TAIL_FWD,    /* cells of the deep, narrow levels: one launch for all of them;
+                            where deep instances run apart, these instances' levels alone  */
   TDF_PHASE_TAIL_BWD,    /* ... and their gradient bodies                                  */
   TDF_PHASE_COUNT
 };

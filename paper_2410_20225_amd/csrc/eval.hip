@@ -869,15 +869,18 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       begin(TDF_PHASE_CELLS_FWD);
       for (uint32_t lvl = 1; lvl < tail_first; ++lvl)
         if (const uint32_t n = lvl_begin(lvl + 1) - lvl_begin(lvl)) vec_cell_fwd(on(s), e, lvl_begin(lvl), n, with_grad, s);
-      end(TDF_PHASE_CELLS_FWD, tail_first - 1);
+      // (with deep instances the others' tail counts among the level launches: the tail phases are the deep chain's)
+      const bool tail_among_levels = deep && use_tail;
+      if (!tail_among_levels) end(TDF_PHASE_CELLS_FWD, tail_first - 1);
       if (use_tail) {
         tail_rows = most_rows(tail_first * LEVEL_KEY_DIES, (sh_last + 1) * LEVEL_KEY_DIES);
         tail_cells = q_deep0 - lvl_begin(tail_first);
-        if (!deep) begin(TDF_PHASE_TAIL_FWD);   // (with deep instances these levels count among the level launches)
+        if (!deep) begin(TDF_PHASE_TAIL_FWD);
         vec_tail_fwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, tail_sync, spin_ticks, tail_per_die,
                      lvl_begin(tail_first), tail_cells, tail_rows, with_grad, s);
         if (!deep) end(TDF_PHASE_TAIL_FWD, 1);
       }
+      if (tail_among_levels) end(TDF_PHASE_CELLS_FWD, tail_first);
     }
     if (!hc.n_cell) {   // leaves only
       enter_data_stage();
@@ -911,16 +914,17 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     end(TDF_PHASE_HEAD, G.has_node_loss ? 4 : 2);
     if (with_grad) {
       // ---- gradient pass: the level schedule walked backwards -----------------------------
+      if (deep) begin(TDF_PHASE_CELLS_BWD);
       if (use_tail && hc.n_cell) {
         if (!deep) begin(TDF_PHASE_TAIL_BWD);
         vec_tail_bwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, tail_sync + 8 * sizeof(DieSync), spin_ticks, tail_per_die,
                      lvl_begin(tail_first), tail_cells, tail_rows, G.has_head ? e.head_row : e.root_ref, s);
         if (!deep) end(TDF_PHASE_TAIL_BWD, 2);
       }
-      begin(TDF_PHASE_CELLS_BWD);
+      if (!deep) begin(TDF_PHASE_CELLS_BWD);
       for (uint32_t lvl = tail_first - 1; lvl >= 1 && hc.n_cell; --lvl)
         if (const uint32_t n = lvl_begin(lvl + 1) - lvl_begin(lvl)) vec_cell_bwd(on(s), e, lvl_begin(lvl), n, s);
-      end(TDF_PHASE_CELLS_BWD, 2ll * (tail_first - 1));
+      end(TDF_PHASE_CELLS_BWD, 2ll * (tail_first - 1) + (deep && use_tail ? 2 : 0));
       if (deep_beside) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)gr->join_deep, 0));   // both classes' gradients are complete
     }
     // results of `result`, once every instance's root exists

@@ -1,0 +1,50 @@
+"""How the levels of a batch are dealt to launches (level launches, tails, the chain of deep instances), as tdf_stats
+reports it, on batches whose levels lie unevenly: parity with the oracle at the bars of the other bf16 tests."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2410_20225_amd import tdf  # noqa: E402
+from tdf_workloads import make_config, SplitMix64  # noqa: E402
+from tdf_workloads.trees import left_chain_tree, random_split_tree, build_forest  # noqa: E402
+from gpu_util import TreeRun, run_oracle_tree, rel_fro  # noqa: E402
+
+FWD, BWD, TAIL_FWD, TAIL_BWD = (tdf.PHASES.index(n) for n in ("cells_fwd", "cells_bwd", "tail_fwd", "tail_bwd"))
+
+
+def _case(cfg, shapes, hidden=64):
+    c = make_config(cfg, n_trees=len(shapes), max_leaves=4, hidden=hidden, vocab=300)
+    rng = SplitMix64(5)
+    c["forest"] = build_forest(shapes, lambda n: rng.randint(0, c["V"] - 1, n))
+    c["labels"] = rng.randint(0, 4, len(shapes))
+    return c
+
+
+def _train(c, times=1):
+    """The statistics of the evaluations, whose results are the oracle's."""
+    F = c["forest"]
+    dy = np.full(F.n_trees, 1.0 / F.n_trees)
+    ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
+    run = TreeRun(c, head=True, grad=True, stats_level=0)
+    all_stats = []
+    for _ in range(times):
+        all_stats.append(run.run(dy)[1])
+        assert rel_fro(run.out_f32.cpu().numpy(), np.array(ref["out"])) < 2e-2
+        for name, t in (("dW", run.dW), ("db", run.db), ("dE", run.dE)):
+            assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < 2e-2, name
+        assert all_stats[-1].n_grad_firings == F.n_nodes and all_stats[-1].n_grad_not_once == 0
+    return all_stats
+
+
+SHALLOW = [random_split_tree(12 + b % 13, SplitMix64(b)) for b in range(40)]
+
+
+@pytest.mark.parametrize("cfg", [3, 4])
+def test_both_tails_of_a_batch_with_deep_instances_are_in_the_phases(cfg):
+    st, = _train(_case(cfg, SHALLOW + [left_chain_tree(60 + b) for b in range(4)]))
+    assert st.deep_split and st.tail_used
+    # the chain's launches, and the other instances' levels (here all of them a tail) beside or behind it
+    assert st.phase_launches[TAIL_FWD] == 1 and st.phase_launches[TAIL_BWD] == 2
+    assert st.phase_launches[FWD] == st.n_wide_waves + 1 and st.phase_launches[BWD] == 2 * st.n_wide_waves + 2
+    assert st.phase_ms[FWD] > 0.005 and st.phase_ms[BWD] > 0.005   # (some ten levels of a microsecond and more)
