@@ -817,8 +817,11 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       }
       level_off = (const uint32_t*)((char*)gr->pinned + PIN_LEVELS);
       enter_data_stage();
-      sh_last = want_deep ? std::min(hc.max_level, deep_level - 1) : hc.max_level;
       q_deep0 = want_deep ? level_off[deep_base] : hc.n_cell;   // the shallow instances' cells come first
+      // Their last level with a cell (none: 0): empty levels behind it, up to all of deep_level where every instance is
+      // deep, would make a tail that has nothing to do and whose workgroups wait for one another all the same.
+      sh_last = want_deep ? std::min(hc.max_level, deep_level - 1) : hc.max_level;
+      while (sh_last > 0 && lvl_begin(sh_last) == q_deep0) --sh_last;
       deep = want_deep && q_deep0 < hc.n_cell;
       // Side by side only where the shallow instances' levels are worth about as much time as the deep
       // ones' chain (a level of the chain costs some microseconds whatever it holds, a wide level

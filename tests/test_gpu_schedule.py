@@ -48,3 +48,15 @@ def test_both_tails_of_a_batch_with_deep_instances_are_in_the_phases(cfg):
     assert st.phase_launches[TAIL_FWD] == 1 and st.phase_launches[TAIL_BWD] == 2
     assert st.phase_launches[FWD] == st.n_wide_waves + 1 and st.phase_launches[BWD] == 2 * st.n_wide_waves + 2
     assert st.phase_ms[FWD] > 0.005 and st.phase_ms[BWD] > 0.005   # (some ten levels of a microsecond and more)
+
+
+@pytest.mark.parametrize("cfg", [3, 4])
+@pytest.mark.parametrize("shallow,levels", [([], 0), ([left_chain_tree(1)], 0), ([left_chain_tree(2)] * 3, 1),
+                                            ([left_chain_tree(5)], 4), ([left_chain_tree(9)], 8)])
+def test_shallow_instances_that_end_early_beside_deep_ones(cfg, shallow, levels):
+    # nothing is launched for levels that only deep instances have: level launches up to three levels, else a tail of its own
+    st, = _train(_case(cfg, shallow + [left_chain_tree(50 + b) for b in range(9)]))
+    assert st.deep_split and st.tail_used and st.n_waves == 57
+    assert st.n_wide_waves == (levels if levels < 4 else 0)
+    assert st.phase_launches[FWD] == (levels if levels < 4 else 1)
+    assert st.phase_launches[BWD] == 2 * st.phase_launches[FWD]
