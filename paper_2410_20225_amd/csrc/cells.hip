@@ -1432,6 +1432,8 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
       if (rank == 0 && threadIdx.x == 0) __hip_atomic_store(&sy->at, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     });
   };
+  // (On a die without a cell in these levels that is the last one, and nobody waits for tiles there.)
+  if (rank == 0 && threadIdx.x == 0) __hip_atomic_store(&sy->at, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   for (uint32_t n = 0;; ++n) {
     if (!tile(0, t0, p0, a0, t1, p1, a1, t2, p2, t3, p3)) return;
     if (!tile(1, t1, p1, a1, t2, p2, a0, t3, p3, t0, p0)) return;
@@ -1479,7 +1481,7 @@ __device__ __forceinline__ void scout_levels(const GemmArgs& g, const TailArgs& 
     for (int looks = 0;; ++looks) {
       const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&ta.sync[die].at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
       if (at + ahead >= k) break;
-      if (looks == 1000) return;   // (half a millisecond: the tiles have not begun, or have given up, or a level is huge)
+      if (looks == 1000) return;   // (0.3 ms: the tiles have not begun, or have given up, or a level is huge)
       __builtin_amdgcn_s_sleep(8);
     }
     for (uint32_t q = q0; q < end; q += 64u) {

@@ -60,3 +60,16 @@ def test_shallow_instances_that_end_early_beside_deep_ones(cfg, shallow, levels)
     assert st.n_wide_waves == (levels if levels < 4 else 0)
     assert st.phase_launches[FWD] == (levels if levels < 4 else 1)
     assert st.phase_launches[BWD] == 2 * st.phase_launches[FWD]
+
+
+@pytest.mark.parametrize("cfg", [3, 4])
+def test_dies_without_a_cell_hold_nobody_up(cfg):
+    # chains on one die of eight, and the same chains on all of them: the launches over all levels last as long
+    times = []
+    for deep in ([7], range(8)):
+        shapes = [left_chain_tree(100) if b in deep else left_chain_tree(3) for b in range(8)]
+        all_stats = _train(_case(cfg, shapes), times=5)
+        assert all(st.n_machines == 8 and st.deep_split for st in all_stats)
+        times.append([min(st.phase_ms[ph] for st in all_stats) for ph in (TAIL_FWD, TAIL_BWD)])
+    for one, all_ in zip(*times):
+        assert one < 1.5 * all_, times
