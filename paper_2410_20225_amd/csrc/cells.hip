@@ -2168,17 +2168,22 @@ template <typename T> static void tail_fwd_t(const VecArgs& v, const Engine& e, 
   if (v.cell_kind == 2) tail_fwd_mode<T, LSTM_FWD>(g, t, per_die, row_tiles, s);
   else tail_fwd_mode<T, RNN_FWD>(g, t, per_die, row_tiles, s);
 }
-// Levels of at most this many cells go to a tail on so many compute units per die: a level there takes some 1.2 us (TreeRNN)
-// or 1.9 us (TreeLSTM) for every row of tiles that its workgroups make side by side, a launch of its own 15 us and more
-// (1,024 trees of a TreeRNN of 300 units, training: 487 us with levels of 1,024 cells, 441 with 2,048, 430 with 3,072 to 6,000;
-// 4,096 trees of a TreeLSTM of 256 units forward: 1,282, 1,266, 1,280).
-uint32_t vec_tail_level(const VecArgs& v, int cus_per_die) {
-  if (getenv("TDF_SMALL_LEVEL")) return small_level();
+// Whether a tail on so many compute units per die takes a level of `cells` cells, `most_rows` of them on the die with most:
+// the die that has most is the last one through, and with one instance it has them all.
+// A row of tiles that a die's workgroups make side by side (16 cells for every group of them) takes 1.2 to 2.6 us (TreeRNN) or
+// 2.1 to 2.7 (TreeLSTM), a launch of its own 11 to 18: eight or five rows go to the tail, and 128 cells at any rate (as many
+// as 1,024 make where the dies share them evenly).
+// us, all dies' cells counted -> the fullest die's: one complete tree of 4,096 leaves, its levels of up to 2,048 cells on one
+// die, TreeRNN of 512 units (three groups) 448 -> 283 forward and 904 -> 442 training, TreeLSTM of 256 351 -> 278 and 738 ->
+// 470; two such trees 357 -> 296 and 644 -> 471.  Where the dies share a level evenly nothing changes: 1,024 trees of a TreeRNN
+// of 300 units, training, 487 with levels of 1,024 cells, 441 with 2,048, 430 with 3,072 to 6,000.
+bool vec_tail_takes(const VecArgs& v, int cus_per_die, uint32_t cells, uint32_t most_rows) {
+  if (getenv("TDF_SMALL_LEVEL")) return cells <= small_level();
   const bool lstm = v.cell_kind == 2;
   const int n_ct = v.Hp / (lstm ? Tile<LSTM_FWD>::UNITS : Tile<RNN_FWD>::UNITS), kc = v.dtype == TDF_BF16 ? Chunk<__bf16>::KC : Chunk<float>::KC;
   const int n = lstm ? Tile<LSTM_FWD>::steps_most(v.Kp / kc) : Tile<RNN_FWD>::steps_most(v.Kp / kc);
   const int wgs = n > 8 ? 0 : tail_wgs(cus_per_die * (n <= 4 ? 2 : 1), n_ct, 1u << 20);
-  return std::min<uint32_t>(8192u, std::max<uint32_t>(1024u, (uint32_t)(wgs / n_ct) * (lstm ? 640u : 1024u)));
+  return most_rows <= std::min(1024u, std::max(128u, (uint32_t)(wgs / n_ct) * (lstm ? 80u : 128u)));
 }
 // The tail's cells are the n_cells from q_first on.  per_die: compute units per accelerator die for this launch (all of its
 // workgroups must be resident together); most_rows: cells of a level on a die, at most

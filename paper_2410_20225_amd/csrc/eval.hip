@@ -37,7 +37,7 @@ void vec_pack_w(const VecArgs& v, const LaneArgs* lanes, void* zero, size_t zero
 void vec_embed(const VecArgs& v, const Engine& e, uint32_t n_leaf, const LaneTotals* t, hipStream_t s);
 void vec_cell_fwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, int save_gates, hipStream_t s);
 void vec_cell_bwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, hipStream_t s);
-uint32_t vec_tail_level(const VecArgs& v, int cus_per_die);
+bool vec_tail_takes(const VecArgs& v, int cus_per_die, uint32_t cells, uint32_t most_rows);
 void vec_tail_fwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
                   uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t n_cells, uint32_t most_rows,
                   int save_gates, hipStream_t s);
@@ -863,9 +863,11 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       // ---- the (other) instances on the caller's stream: wide levels one launch each; the narrow
       // levels behind them in one launch in which every die walks its own cells
       if (deep_beside) tail_per_die = std::max(1, tail_per_die - deep_wgs);
-      const uint32_t tail_level = vec_tail_level(v, tail_per_die);
+      auto takes = [&](uint32_t lvl) {
+        return vec_tail_takes(v, tail_per_die, lvl_begin(lvl + 1) - lvl_begin(lvl), most_rows(lvl * LEVEL_KEY_DIES, (lvl + 1) * LEVEL_KEY_DIES));
+      };
       tail_first = sh_last + 1;
-      while (tail_first > 1 && lvl_begin(tail_first) - lvl_begin(tail_first - 1) <= tail_level) --tail_first;
+      while (tail_first > 1 && takes(tail_first - 1)) --tail_first;
       use_tail = gr->die_local && sh_last + 1 - tail_first >= 4;
       if (!use_tail) tail_first = sh_last + 1;
       n_wide_levels = tail_first - 1;

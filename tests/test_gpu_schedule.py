@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 from paper_2410_20225_amd import tdf  # noqa: E402
 from tdf_workloads import make_config, SplitMix64  # noqa: E402
-from tdf_workloads.trees import left_chain_tree, random_split_tree, build_forest  # noqa: E402
+from tdf_workloads.trees import complete_tree, left_chain_tree, random_split_tree, build_forest  # noqa: E402
 from gpu_util import TreeRun, run_oracle_tree, rel_fro  # noqa: E402
 
 FWD, BWD, TAIL_FWD, TAIL_BWD = (tdf.PHASES.index(n) for n in ("cells_fwd", "cells_bwd", "tail_fwd", "tail_bwd"))
@@ -73,3 +73,13 @@ def test_dies_without_a_cell_hold_nobody_up(cfg):
         times.append([min(st.phase_ms[ph] for st in all_stats) for ph in (TAIL_FWD, TAIL_BWD)])
     for one, all_ in zip(*times):
         assert one < 1.5 * all_, times
+
+
+@pytest.mark.parametrize("cfg,hidden,trees,wide", [
+    (3, 512, 1, 2), (3, 512, 2, 1), (3, 512, 8, 0),   # 1,024 cells of the first level on a die, 512, 256: its three groups take 384
+    (4, 256, 1, 3), (3, 64, 1, 0)])   # TreeLSTM, three groups that take 240; TreeRNN of 64 units: a die takes 1,024
+def test_levels_that_lie_on_few_dies_are_launched_over_all_of_them(cfg, hidden, trees, wide):
+    c = _case(cfg, [complete_tree(2048 if trees == 1 else 1024 if trees == 2 else 512)] * trees, hidden=hidden)
+    run = TreeRun(c, head=True, grad=False, stats_level=0)
+    st, stats = run.run()
+    assert stats.n_machines == trees and stats.tail_used and stats.n_wide_waves == wide
