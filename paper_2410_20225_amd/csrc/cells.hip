@@ -2136,14 +2136,17 @@ void vec_cell_bwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count
 static int tail_wgs(int slots, int n_ct, uint32_t row_tiles) {
   return (int)std::min<uint32_t>((uint32_t)std::max(slots - 1, n_ct) / n_ct, std::max(row_tiles, 1u)) * (slots >= n_ct ? n_ct : 0);
 }
+// Workgroups of a pass that are on a die's compute units together, where a wave keeps the operands of n chunk steps: two share
+// a compute unit, but for the variants with most weights in registers.
+static int tail_slots_fwd(int cus_per_die, int n) { return cus_per_die * (n <= 4 ? 2 : 1); }
+static int tail_slots_bwd(int cus_per_die, int n, int cell_kind) { return cus_per_die * (n <= 5 && cell_kind == 1 ? 2 : 1); }
 template <typename T, int MODE, int RES> static void launch_tail_fwd(const GemmArgs& g, const TailArgs& t, int wgs, hipStream_t s) {
   hipLaunchKernelGGL((k_tail_fwd<DtOf<T>::value, MODE, RES>), dim3((wgs + 1) * (int)XCDS), dim3(Tile<MODE>::NW * 64), 0, s, g, t);
 }
 template <typename T, int MODE> static void tail_fwd_mode(GemmArgs g, const TailArgs& t, int cus_per_die, uint32_t row_tiles, hipStream_t s) {
   g.n_tiles_n = g.Hp / Tile<MODE>::UNITS;
   const int n = Tile<MODE>::steps_most(g.K / Chunk<T>::KC);
-  const int slots = cus_per_die * (n <= 4 ? 2 : 1);   // (two workgroups share a compute unit, but for the variants with most weights in registers)
-  const int wgs = tail_wgs(slots, g.n_tiles_n, row_tiles);
+  const int wgs = tail_wgs(tail_slots_fwd(cus_per_die, n), g.n_tiles_n, row_tiles);
   if (wgs && n <= 2) launch_tail_fwd<T, MODE, 2>(g, t, wgs, s);
   else if (wgs && n <= 4) launch_tail_fwd<T, MODE, 4>(g, t, wgs, s);
   else if (wgs && n <= 8) launch_tail_fwd<T, MODE, 8>(g, t, wgs, s);
@@ -2168,22 +2171,32 @@ template <typename T> static void tail_fwd_t(const VecArgs& v, const Engine& e, 
   if (v.cell_kind == 2) tail_fwd_mode<T, LSTM_FWD>(g, t, per_die, row_tiles, s);
   else tail_fwd_mode<T, RNN_FWD>(g, t, per_die, row_tiles, s);
 }
-// Whether a tail on so many compute units per die takes a level of `cells` cells, `most_rows` of them on the die with most:
-// the die that has most is the last one through, and with one instance it has them all.
+// The levels that a tail of a pass takes, on so many compute units per die: those with at most this many cells on the die that
+// has most of them.  That die is the last one through, and with one instance it has them all.
 // A row of tiles that a die's workgroups make side by side (16 cells for every group of them) takes 1.2 to 2.6 us (TreeRNN) or
-// 2.1 to 2.7 (TreeLSTM), a launch of its own 11 to 18: eight or five rows go to the tail, and 128 cells at any rate (as many
-// as 1,024 make where the dies share them evenly).
-// us, all dies' cells counted -> the fullest die's: one complete tree of 4,096 leaves, its levels of up to 2,048 cells on one
-// die, TreeRNN of 512 units (three groups) 448 -> 283 forward and 904 -> 442 training, TreeLSTM of 256 351 -> 278 and 738 ->
-// 470; two such trees 357 -> 296 and 644 -> 471.  Where the dies share a level evenly nothing changes: 1,024 trees of a TreeRNN
-// of 300 units, training, 487 with levels of 1,024 cells, 441 with 2,048, 430 with 3,072 to 6,000.
-bool vec_tail_takes(const VecArgs& v, int cus_per_die, uint32_t cells, uint32_t most_rows) {
-  if (getenv("TDF_SMALL_LEVEL")) return cells <= small_level();
+// 2.1 to 2.7 (TreeLSTM) forward, a launch of its own 11 to 18; in the gradient pass, which has a third as many groups, 1.5 to
+// 2.3 us and two launches of together 14 to 26.  So eight rows go to the tail (TreeLSTM forward: five), and 128 cells at any
+// rate (as many as 1,024 make where the dies share them evenly).
+// us, all dies' cells counted -> the fullest die's -> each pass by its own groups: one complete tree of 4,096 leaves, its
+// levels of up to 2,048 cells on one die, TreeRNN of 512 units (three groups and one) 448 -> 283 forward and 904 -> @A@
+// training, TreeLSTM of 256 351 -> 278 and 738 -> @B@; two such trees 357 -> 296 and 644 -> @C@.  Where the dies
+// share a level evenly the forward pass takes what it did: 1,024 trees of a TreeRNN of 300 units, training, 487 with levels of
+// 1,024 cells, 441 with 2,048, 430 with 3,072 to 6,000.
+TailLimit vec_tail_limit(const VecArgs& v, int cus_per_die, bool backward) {
+  if (getenv("TDF_SMALL_LEVEL")) return TailLimit{small_level(), 0xFFFFFFFFu};
   const bool lstm = v.cell_kind == 2;
-  const int n_ct = v.Hp / (lstm ? Tile<LSTM_FWD>::UNITS : Tile<RNN_FWD>::UNITS), kc = v.dtype == TDF_BF16 ? Chunk<__bf16>::KC : Chunk<float>::KC;
-  const int n = lstm ? Tile<LSTM_FWD>::steps_most(v.Kp / kc) : Tile<RNN_FWD>::steps_most(v.Kp / kc);
-  const int wgs = n > 8 ? 0 : tail_wgs(cus_per_die * (n <= 4 ? 2 : 1), n_ct, 1u << 20);
-  return most_rows <= std::min(1024u, std::max(128u, (uint32_t)(wgs / n_ct) * (lstm ? 80u : 128u)));
+  const int kc = v.dtype == TDF_BF16 ? Chunk<__bf16>::KC : Chunk<float>::KC;
+  int n_ct, wgs;
+  if (backward) {
+    const int n = Tile<DX_BWD>::steps_most(v.Np / kc);
+    n_ct = v.Kp / Tile<DX_BWD>::UNITS;
+    wgs = n > 10 ? 0 : tail_wgs(tail_slots_bwd(cus_per_die, n, v.cell_kind), n_ct, 1u << 20);
+  } else {
+    const int n = lstm ? Tile<LSTM_FWD>::steps_most(v.Kp / kc) : Tile<RNN_FWD>::steps_most(v.Kp / kc);
+    n_ct = v.Hp / (lstm ? Tile<LSTM_FWD>::UNITS : Tile<RNN_FWD>::UNITS);
+    wgs = n > 8 ? 0 : tail_wgs(tail_slots_fwd(cus_per_die, n), n_ct, 1u << 20);
+  }
+  return TailLimit{0xFFFFFFFFu, std::min(1024u, std::max(128u, (uint32_t)(wgs / n_ct) * (lstm && !backward ? 80u : 128u)))};
 }
 // The tail's cells are the n_cells from q_first on.  per_die: compute units per accelerator die for this launch (all of its
 // workgroups must be resident together); most_rows: cells of a level on a die, at most
@@ -2204,7 +2217,7 @@ template <typename T, int CELL>
 static void tail_bwd_cell(const GemmArgs& g, const VecArgs& v, const Engine& e, const TailArgs& t, int cus_per_die, uint32_t row_tiles,
                           hipStream_t s) {
   const int n = Tile<DX_BWD>::steps_most(g.K / Chunk<T>::KC);
-  const int wgs = tail_wgs(cus_per_die * (n <= 5 && CELL == 1 ? 2 : 1), g.n_tiles_n, row_tiles);
+  const int wgs = tail_wgs(tail_slots_bwd(cus_per_die, n, CELL), g.n_tiles_n, row_tiles);
   if (wgs && n <= 5) launch_tail_bwd<T, CELL, 5>(g, v, e, t, wgs, s);
   else if (wgs && n <= 10) launch_tail_bwd<T, CELL, 10>(g, v, e, t, wgs, s);
   else launch_tail_bwd<T, CELL, 0>(g, v, e, t, cus_per_die, s);

@@ -374,4 +374,7 @@ struct VecArgs {
   int wide_offsets; // only the build for the tests sets it: kernels with a 32-bit and a 64-bit offset path take the latter
 };
 
+// The levels that a tail takes: those of at most `cells` cells, at most `most_rows` of them on one die.
+struct TailLimit { uint32_t cells, most_rows; };
+
 }  // namespace tdf

@@ -37,7 +37,7 @@ void vec_pack_w(const VecArgs& v, const LaneArgs* lanes, void* zero, size_t zero
 void vec_embed(const VecArgs& v, const Engine& e, uint32_t n_leaf, const LaneTotals* t, hipStream_t s);
 void vec_cell_fwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, int save_gates, hipStream_t s);
 void vec_cell_bwd(const VecArgs& v, const Engine& e, uint32_t q0, uint32_t count, hipStream_t s);
-bool vec_tail_takes(const VecArgs& v, int cus_per_die, uint32_t cells, uint32_t most_rows);
+TailLimit vec_tail_limit(const VecArgs& v, int cus_per_die, bool backward);
 void vec_tail_fwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, uint32_t lvl_first, uint32_t lvl_last,
                   uint32_t n_dies, void* sync, long long spin_ticks, int per_die, uint32_t q_first, uint32_t n_cells, uint32_t most_rows,
                   int save_gates, hipStream_t s);
@@ -751,7 +751,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   if (!hc.status && P.vec && with_grad && hc.n_cell > P.max_cells) hc.status = (uint32_t)(-TDF_ERR_TABLE_FULL);
   tdf_status dev = status_from_device(hc.status);
 
-  uint32_t tail_first = 0;
+  uint32_t tail_first = 0, tail_first_bwd = 0;   // of the forward and of the gradient pass
   bool use_tail = false;   // the narrow levels run in one launch per pass on the caller's stream
   bool deep = false;       // deep instances run apart from the others, all their levels in one launch per pass
   bool deep_beside = false;   // ... on the side stream, beside the others
@@ -763,8 +763,15 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     for (; key < end_key; ++key) m = std::max(m, level_off[key + 1] - level_off[key]);
     return m;
   };
+  // The first level of a tail over the (shallow) instances' last levels, from `lowest` on; a tail of fewer than four is none.
+  auto first_of_tail = [&](const TailLimit& lim, uint32_t lowest) {
+    uint32_t first = sh_last + 1;
+    while (first > lowest && lvl_begin(first) - lvl_begin(first - 1) <= lim.cells &&
+           most_rows((first - 1) * LEVEL_KEY_DIES, first * LEVEL_KEY_DIES) <= lim.most_rows)
+      --first;
+    return sh_last + 1 - first >= 4 ? first : sh_last + 1;
+  };
   uint32_t de_chunk = DE_CHUNK;
-  uint32_t tail_rows = 0, tail_cells = 0;   // of the tail on the caller's stream
   int tail_per_die = cus / (int)XCDS;       // its compute units per die
   char* tail_sync = base + P.off_tail_sync + 16 * sizeof(DieSync);
   if (dev == TDF_OK && P.vec) {
@@ -863,13 +870,11 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       // ---- the (other) instances on the caller's stream: wide levels one launch each; the narrow
       // levels behind them in one launch in which every die walks its own cells
       if (deep_beside) tail_per_die = std::max(1, tail_per_die - deep_wgs);
-      auto takes = [&](uint32_t lvl) {
-        return vec_tail_takes(v, tail_per_die, lvl_begin(lvl + 1) - lvl_begin(lvl), most_rows(lvl * LEVEL_KEY_DIES, (lvl + 1) * LEVEL_KEY_DIES));
-      };
-      tail_first = sh_last + 1;
-      while (tail_first > 1 && takes(tail_first - 1)) --tail_first;
-      use_tail = gr->die_local && sh_last + 1 - tail_first >= 4;
-      if (!use_tail) tail_first = sh_last + 1;
+      tail_first = first_of_tail(vec_tail_limit(v, tail_per_die, false), 1);
+      if (!gr->die_local) tail_first = sh_last + 1;
+      use_tail = tail_first <= sh_last;
+      // (no lower than the forward one, which marks the rows that the gradient tail waits for)
+      if (with_grad) tail_first_bwd = first_of_tail(vec_tail_limit(v, tail_per_die, true), tail_first);
       n_wide_levels = tail_first - 1;
       begin(TDF_PHASE_CELLS_FWD);
       for (uint32_t lvl = 1; lvl < tail_first; ++lvl)
@@ -878,11 +883,10 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       const bool tail_among_levels = deep && use_tail;
       if (!tail_among_levels) end(TDF_PHASE_CELLS_FWD, tail_first - 1);
       if (use_tail) {
-        tail_rows = most_rows(tail_first * LEVEL_KEY_DIES, (sh_last + 1) * LEVEL_KEY_DIES);
-        tail_cells = q_deep0 - lvl_begin(tail_first);
         if (!deep) begin(TDF_PHASE_TAIL_FWD);
         vec_tail_fwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, tail_sync, spin_ticks, tail_per_die,
-                     lvl_begin(tail_first), tail_cells, tail_rows, with_grad, s);
+                     lvl_begin(tail_first), q_deep0 - lvl_begin(tail_first),
+                     most_rows(tail_first * LEVEL_KEY_DIES, (sh_last + 1) * LEVEL_KEY_DIES), with_grad, s);
         if (!deep) end(TDF_PHASE_TAIL_FWD, 1);
       }
       if (tail_among_levels) end(TDF_PHASE_CELLS_FWD, tail_first);
@@ -919,17 +923,20 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     end(TDF_PHASE_HEAD, G.has_node_loss ? 4 : 2);
     if (with_grad) {
       // ---- gradient pass: the level schedule walked backwards -----------------------------
+      const bool tail = use_tail && hc.n_cell && tail_first_bwd <= sh_last;
       if (deep) begin(TDF_PHASE_CELLS_BWD);
-      if (use_tail && hc.n_cell) {
+      if (tail) {
         if (!deep) begin(TDF_PHASE_TAIL_BWD);
-        vec_tail_bwd(on(s), e, e.level_off, tail_first, sh_last, e.n_dies, tail_sync + 8 * sizeof(DieSync), spin_ticks, tail_per_die,
-                     lvl_begin(tail_first), tail_cells, tail_rows, G.has_head ? e.head_row : e.root_ref, s);
+        vec_tail_bwd(on(s), e, e.level_off, tail_first_bwd, sh_last, e.n_dies, tail_sync + 8 * sizeof(DieSync), spin_ticks, tail_per_die,
+                     lvl_begin(tail_first_bwd), q_deep0 - lvl_begin(tail_first_bwd),
+                     most_rows(tail_first_bwd * LEVEL_KEY_DIES, (sh_last + 1) * LEVEL_KEY_DIES), G.has_head ? e.head_row : e.root_ref, s);
         if (!deep) end(TDF_PHASE_TAIL_BWD, 2);
       }
       if (!deep) begin(TDF_PHASE_CELLS_BWD);
-      for (uint32_t lvl = tail_first - 1; lvl >= 1 && hc.n_cell; --lvl)
+      const uint32_t n_levels = hc.n_cell ? tail_first_bwd - 1 : 0;   // launched one by one
+      for (uint32_t lvl = n_levels; lvl >= 1; --lvl)
         if (const uint32_t n = lvl_begin(lvl + 1) - lvl_begin(lvl)) vec_cell_bwd(on(s), e, lvl_begin(lvl), n, s);
-      end(TDF_PHASE_CELLS_BWD, 2ll * (tail_first - 1) + (deep && use_tail ? 2 : 0));
+      end(TDF_PHASE_CELLS_BWD, 2ll * n_levels + (deep && tail ? 2 : 0));
       if (deep_beside) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)gr->join_deep, 0));   // both classes' gradients are complete
     }
     // results of `result`, once every instance's root exists

@@ -83,3 +83,13 @@ def test_levels_that_lie_on_few_dies_are_launched_over_all_of_them(cfg, hidden, 
     run = TreeRun(c, head=True, grad=False, stats_level=0)
     st, stats = run.run()
     assert stats.n_machines == trees and stats.tail_used and stats.n_wide_waves == wide
+
+
+@pytest.mark.parametrize("cfg,others", [(3, 0), (4, 0), (3, 7), (4, 7)])
+def test_the_gradient_tail_may_begin_above_the_forward_one(cfg, others):
+    # a complete tree's levels of 1,024 cells and fewer: all of them a tail forward, the first one (TreeRNN: none) launched
+    # in the gradient pass, which has fewer workgroups for it; roots in that level too
+    st, = _train(_case(cfg, [complete_tree(2048)] + [left_chain_tree(2)] * others))
+    assert st.n_waves == 11 and st.tail_used and st.n_wide_waves == 0
+    assert st.phase_launches[TAIL_FWD] == 1 and st.phase_launches[TAIL_BWD] == 2
+    assert st.phase_launches[BWD] == (0 if cfg == 3 else 2)
