@@ -260,7 +260,7 @@ enum {
   TDF_PHASE_EMBED_GRAD,  /* dE: the per-token sums (beside the weight gradients; the token
                             sort ran earlier, beside the cells)                            */
   TDF_PHASE_TAIL_FWD,    /* cells of the deep, narrow levels: one launch for all of them;
-                            where deep instances run apart, these instances' levels alone  */
+                            where deep instances run apart, all levels of these alone      */
   TDF_PHASE_TAIL_BWD,    /* ... and their gradient bodies                                  */
   TDF_PHASE_COUNT
 };
@@ -312,7 +312,7 @@ typedef struct {
                              chain launch could not all start in time                    */
   int32_t tail_used;      /* 1: narrow levels ran in one launch per pass                */
   int32_t deep_split;     /* 1: the deep instances (root level >= 32) ran apart from the others,
-                             all their levels in one launch per pass; 2: ... on a second
+                             their narrow levels in one launch per pass; 2: ... on a second
                              stream, beside the others                                   */
   /* live firings per static-graph node, indexed like tdf_graph_info_t.nodes            */
   int64_t fire_count[TDF_STATS_MAX_COUNTS];

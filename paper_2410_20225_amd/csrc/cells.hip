@@ -2178,10 +2178,11 @@ template <typename T> static void tail_fwd_t(const VecArgs& v, const Engine& e, 
 // 2.3 us and two launches of together 14 to 26.  So eight rows go to the tail (TreeLSTM forward: five), and 128 cells at any
 // rate (as many as 1,024 make where the dies share them evenly).
 // us, all dies' cells counted -> the fullest die's -> each pass by its own groups: one complete tree of 4,096 leaves, its
-// levels of up to 2,048 cells on one die, TreeRNN of 512 units (three groups and one) 448 -> 283 forward and 904 -> @A@
-// training, TreeLSTM of 256 351 -> 278 and 738 -> @B@; two such trees 357 -> 296 and 644 -> @C@.  Where the dies
+// levels of up to 2,048 cells on one die, TreeRNN of 512 units (three groups and one) 448 -> 283 forward and 904 -> 455
+// training, TreeLSTM of 256 351 -> 278 and 738 -> 474; two such trees 357 -> 296 and 644 -> 486.  Where the dies
 // share a level evenly the forward pass takes what it did: 1,024 trees of a TreeRNN of 300 units, training, 487 with levels of
-// 1,024 cells, 441 with 2,048, 430 with 3,072 to 6,000.
+// 1,024 cells, 441 with 2,048, 430 with 3,072 to 6,000.  The chain of deep instances takes levels by the same rule: one tree of
+// 16,384 leaves and 33 levels, training, all levels in the chain 3,564 us (512 units) and 4,268 (TreeLSTM), now 1,617 and 1,680.
 TailLimit vec_tail_limit(const VecArgs& v, int cus_per_die, bool backward) {
   if (getenv("TDF_SMALL_LEVEL")) return TailLimit{small_level(), 0xFFFFFFFFu};
   const bool lstm = v.cell_kind == 2;

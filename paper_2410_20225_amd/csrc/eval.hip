@@ -753,7 +753,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
 
   uint32_t tail_first = 0, tail_first_bwd = 0;   // of the forward and of the gradient pass
   bool use_tail = false;   // the narrow levels run in one launch per pass on the caller's stream
-  bool deep = false;       // deep instances run apart from the others, all their levels in one launch per pass
+  bool deep = false;       // deep instances run apart from the others, their narrow levels in one launch per pass
   bool deep_beside = false;   // ... on the side stream, beside the others
   uint32_t sh_last = 0, deep_base = 0, q_deep0 = 0, n_wide_levels = 0;
   const uint32_t* level_off = nullptr;   // by sort key; in the pinned buffer
@@ -763,13 +763,16 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     for (; key < end_key; ++key) m = std::max(m, level_off[key + 1] - level_off[key]);
     return m;
   };
-  // The first level of a tail over the (shallow) instances' last levels, from `lowest` on; a tail of fewer than four is none.
-  auto first_of_tail = [&](const TailLimit& lim, uint32_t lowest) {
-    uint32_t first = sh_last + 1;
-    while (first > lowest && lvl_begin(first) - lvl_begin(first - 1) <= lim.cells &&
-           most_rows((first - 1) * LEVEL_KEY_DIES, first * LEVEL_KEY_DIES) <= lim.most_rows)
-      --first;
-    return sh_last + 1 - first >= 4 ? first : sh_last + 1;
+  // The first level of a tail over the last levels of a class of instances, whose keys begin at key0: from level `lowest` on,
+  // up to `last`.  A tail of fewer than four levels is none.
+  auto first_of_tail = [&](uint32_t key0, uint32_t last, const TailLimit& lim, uint32_t lowest) {
+    auto takes = [&](uint32_t lvl) {
+      const uint32_t key = key0 + lvl * LEVEL_KEY_DIES, end_key = key + LEVEL_KEY_DIES;
+      return level_off[end_key] - level_off[key] <= lim.cells && most_rows(key, end_key) <= lim.most_rows;
+    };
+    uint32_t first = last + 1;
+    while (first > lowest && takes(first - 1)) --first;
+    return last + 1 - first >= 4 ? first : last + 1;
   };
   uint32_t de_chunk = DE_CHUNK;
   int tail_per_die = cus / (int)XCDS;       // its compute units per die
@@ -849,17 +852,26 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
         HIP_TRY(hipEventRecord((hipEvent_t)gr->fork_deep, s));
         HIP_TRY(hipStreamWaitEvent(s2, (hipEvent_t)gr->fork_deep, 0));
       }
-      const uint32_t deep_rows = deep ? most_rows(deep_base + LEVEL_KEY_DIES, deep_base + (hc.max_level + 1) * LEVEL_KEY_DIES) : 0u;
+      // (their wide levels one launch each, the narrow ones in one launch per pass, as for the others below)
       auto deep_chain = [&]() -> tdf_status {
+        const uint32_t last = hc.max_level, first = first_of_tail(deep_base, last, vec_tail_limit(v, deep_per_die, false), 1),
+                       first_bwd = first_of_tail(deep_base, last, vec_tail_limit(v, deep_per_die, true), first);
+        auto at = [&](uint32_t lvl) { return level_off[deep_base + (size_t)lvl * LEVEL_KEY_DIES]; };
+        auto rows_from = [&](uint32_t lvl) { return most_rows(deep_base + lvl * LEVEL_KEY_DIES, deep_base + (last + 1) * LEVEL_KEY_DIES); };
         begin_on(TDF_PHASE_TAIL_FWD, sd);
-        vec_tail_fwd(on(sd), e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync, spin_ticks, deep_per_die,
-                     q_deep0, hc.n_cell - q_deep0, deep_rows, with_grad, sd);
-        end_on(TDF_PHASE_TAIL_FWD, 1, sd);
+        for (uint32_t lvl = 1; lvl < first; ++lvl) vec_cell_fwd(on(sd), e, at(lvl), at(lvl + 1) - at(lvl), with_grad, sd);
+        if (first <= last)
+          vec_tail_fwd(on(sd), e, e.level_off + deep_base, first, last, e.n_dies, base + P.off_tail_sync, spin_ticks, deep_per_die,
+                       at(first), hc.n_cell - at(first), rows_from(first), with_grad, sd);
+        end_on(TDF_PHASE_TAIL_FWD, first - 1 + (first <= last ? 1 : 0), sd);
         if (G.has_head) vec_head(on(sd), e, dy->dy, 1, 1, sd);
         begin_on(TDF_PHASE_TAIL_BWD, sd);
-        vec_tail_bwd(on(sd), e, e.level_off + deep_base, 1, hc.max_level, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
-                     spin_ticks, deep_per_die, q_deep0, hc.n_cell - q_deep0, deep_rows, G.has_head ? e.head_row : e.root_ref, sd);
-        end_on(TDF_PHASE_TAIL_BWD, 2, sd);
+        if (first_bwd <= last)
+          vec_tail_bwd(on(sd), e, e.level_off + deep_base, first_bwd, last, e.n_dies, base + P.off_tail_sync + 8 * sizeof(DieSync),
+                       spin_ticks, deep_per_die, at(first_bwd), hc.n_cell - at(first_bwd), rows_from(first_bwd),
+                       G.has_head ? e.head_row : e.root_ref, sd);
+        for (uint32_t lvl = first_bwd - 1; lvl >= 1; --lvl) vec_cell_bwd(on(sd), e, at(lvl), at(lvl + 1) - at(lvl), sd);
+        end_on(TDF_PHASE_TAIL_BWD, 2ll * (first_bwd - 1) + (first_bwd <= last ? 2 : 0), sd);
         if (beside) flush(sd);   // (its next launch waits for the other instances)
         if (beside) HIP_TRY(hipEventRecord((hipEvent_t)gr->join_deep, s2));
         return TDF_OK;
@@ -870,11 +882,11 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
       // ---- the (other) instances on the caller's stream: wide levels one launch each; the narrow
       // levels behind them in one launch in which every die walks its own cells
       if (deep_beside) tail_per_die = std::max(1, tail_per_die - deep_wgs);
-      tail_first = first_of_tail(vec_tail_limit(v, tail_per_die, false), 1);
+      tail_first = first_of_tail(0, sh_last, vec_tail_limit(v, tail_per_die, false), 1);
       if (!gr->die_local) tail_first = sh_last + 1;
       use_tail = tail_first <= sh_last;
       // (no lower than the forward one, which marks the rows that the gradient tail waits for)
-      if (with_grad) tail_first_bwd = first_of_tail(vec_tail_limit(v, tail_per_die, true), tail_first);
+      if (with_grad) tail_first_bwd = first_of_tail(0, sh_last, vec_tail_limit(v, tail_per_die, true), tail_first);
       n_wide_levels = tail_first - 1;
       begin(TDF_PHASE_CELLS_FWD);
       for (uint32_t lvl = 1; lvl < tail_first; ++lvl)

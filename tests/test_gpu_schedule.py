@@ -93,3 +93,24 @@ def test_the_gradient_tail_may_begin_above_the_forward_one(cfg, others):
     assert st.n_waves == 11 and st.tail_used and st.n_wide_waves == 0
     assert st.phase_launches[TAIL_FWD] == 1 and st.phase_launches[TAIL_BWD] == 2
     assert st.phase_launches[BWD] == (0 if cfg == 3 else 2)
+
+
+def _on_top(shape, n):
+    """The tree `shape` under a spine of n cells, each with a leaf on the right."""
+    left, right = shape
+    m = left.size
+    up = np.arange(n)
+    l = np.concatenate([np.append(up[1:], 2 * n), np.full(n, -1), np.where(left >= 0, left + 2 * n, -1)])
+    r = np.concatenate([up + n, np.full(n, -1), np.where(right >= 0, right + 2 * n, -1)])
+    assert l.size == m + 2 * n
+    return l, r
+
+
+@pytest.mark.parametrize("cfg,hidden,beside,fwd,bwd", [(3, 256, "0", 1, 2), (4, 128, "0", 1, 2), (3, 256, "1", 1, 2), (4, 128, "1", 2, 2)])
+def test_wide_levels_of_deep_instances_are_launched_over_all_dies(cfg, hidden, beside, fwd, bwd, monkeypatch):
+    # levels of 1,024 and 512 cells on one die: on 32 compute units a die a chain takes 896 and 384 (TreeRNN), 560 and 384; on the
+    # 20 it has beside other instances 512 and 256, 320 and 256
+    monkeypatch.setenv("TDF_DEEP_BESIDE", beside)
+    st, = _train(_case(cfg, [_on_top(complete_tree(2048), 30)] + SHALLOW[:9], hidden=hidden))
+    assert st.deep_split == 1 + int(beside) and st.n_waves == 41
+    assert st.phase_launches[TAIL_FWD] == fwd + 1 and st.phase_launches[TAIL_BWD] == 2 * bwd + 2
