@@ -55,6 +55,7 @@ __host__ __device__ constexpr bool lane_is_pill(uint32_t flag) { return (flag & 
 constexpr uint32_t LANE_WINDOW = 4;     // frames of a lane's stack that stay in LDS
 constexpr uint32_t LANE_SEG = 16;       // frames of a segment of a lane's stack in memory
 constexpr uint32_t LANE_SYNC = 4, LANE_SYNC_FULL = 8;   // sweeps between two looks at the other lanes; the latter while nearly all have work
+constexpr uint32_t LANE_YOUNG = 12000;  // ticks (100 MHz) for which a run is young
 constexpr uint32_t LANE_EARLY = 48;     // sweeps during which a wave gives work away although it has lanes without any
 // idle lanes up to which a wave gives calls to other waves
 constexpr uint32_t LANE_GIVE = 56;
@@ -301,6 +302,24 @@ __device__ __forceinline__ void ln_result(LaneX& x, int type, long long v) {
   }
 }
 
+// Early on the lanes look at one another after every sweep instead of every fourth in two cases.  While a few lanes
+// of the wave have all the work (8 recursions of 3 to 10 levels: 104 us, now 89; 1,000 of 3 to 12: 147 and 115;
+// fib(0..20) 214 and 199; with as many lanes busy fib(0..20) takes 240), but not in a run that fills the GPU from a
+// few roots, which pieces that small only chop up.  And in such a run at a wave's first sweeps, however many lanes are
+// busy, while the run is young: fib(30..32) 4,090 us and 3,500, fib(30) 1,480 and 1,260, three of fib(28) 1,510 and 1,300.
+// How much there is to do is not known then.  max_tags is only the room there is: with less than 1,024 tags for a wave
+// the run is too small for this (fib(28), a million tags: 705 us, 775 in pieces), with more it may be all the same.
+// What costs such a run most are the pieces that waves which join late make of pieces, so there is an end to it after
+// 120 us: fib(28) with room for 16 times its tags 730 us.  (An end after 90 us takes back most of what the large runs gain:
+// fib(30..32) 4,000.)  With many roots it gains nothing: 300 of fib(5..18) 220 us and 236 with room for a few million tags, 256 of
+// tak the same either way.  Where no function has two calls there is nothing to give.
+template <class Age>   // age(): ticks since the run began
+__device__ __forceinline__ bool lane_spreads(uint32_t n_waves, uint32_t n_inst, uint32_t tags_at_once, uint32_t n_run, uint32_t iter, Age age) {
+  const bool fills = n_waves >= 1024u, many = n_inst >= 16u;
+  if (n_run < 32u && (!fills || many)) return iter < LANE_EARLY;
+  return fills && !many && tags_at_once >= 512u && iter < LANE_EARLY / 3 && age() < LANE_YOUNG;
+}
+
 // ---- the machine ----------------------------------------------------------------------------------
 // SW (generated): kStored (stored values per frame), kResultFn, kBranching (a function can have two calls
 // under way at once), sweep(x), ret_bits(fn, opened) (stored values that the opened calls return into),
@@ -353,6 +372,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
   bool resumed = false;                   // the bottom frame has nothing outstanding in other lanes
   uint32_t mx_sp = 0;
   // wave-uniform
+  const uint32_t t_begin = SW::kBranching ? (uint32_t)wall_clock64() : 0u;   // (all waves of a run are resident: they begin together)
   uint32_t n_told = 0;                    // tags reported
   uint32_t qh = 0, qt = 0, nfree = LANE_RECS, iter = 0, syncs = 0, ticket = 0, min_free = LANE_RECS;
   unsigned long long sent_mask = 0;       // replies awaited, by lane
@@ -708,16 +728,8 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     // ---- a few sweeps
     bool any_done = false;
     const uint32_t n_run = (uint32_t)__popcll(__ballot(x.run));
-    // Early on the lanes look at one another after every sweep instead of every fourth in two cases.  While a few lanes
-    // of the wave have all the work (8 recursions of 3 to 10 levels: 104 us, now 89; 1,000 of 3 to 12: 147 and 115;
-    // fib(0..20) 214 and 199; 64 of tak 830 and 760; with as many lanes busy fib(0..20) takes 240), but not in a run that
-    // fills the GPU from a few roots, which pieces that small only chop up (fib(28) alone 720 us, 800 with it).  And
-    // at first, however many lanes are busy, in such a run with 1,024 tags and more for a wave (fib(30..32) 4,810 and
-    // 4,100; with fewer tags fib(28) again, and for 48 sweeps instead of 16 300 of fib(5..18) 330 instead of 250).
-    // Where no function has two calls there is nothing to give.
-    const bool fills = a.n_waves >= 1024u, few = n_run < 32 && (!fills || a.n_inst >= 16u);
-    const bool spread = SW::kBranching && iter < LANE_EARLY &&
-                        (few || (fills && iter < LANE_EARLY / 3 && a.tags_at_once >= 512u));
+    const bool spread = SW::kBranching && lane_spreads(a.n_waves, a.n_inst, a.tags_at_once, n_run, iter,
+                                                       [&] { return (uint32_t)wall_clock64() - t_begin; });
     const uint32_t n_sweeps = spread ? 1u : n_run >= 48 ? LANE_SYNC_FULL : hungry ? 2u : LANE_SYNC;
 #pragma unroll 1
     for (uint32_t k = 0; k < n_sweeps; ++k) {

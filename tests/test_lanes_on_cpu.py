@@ -1,11 +1,14 @@
 """The depth-first lanes run on the CPU (tests/lane_cpu.py) against the oracle and plain Python references: the code that
 is generated for a program, and the machine's hand-overs between lanes and waves in random orders of events."""
+import os
+import subprocess
+
 import pytest
 
 import oracle
 from oracle import programs as oprog
 import lane_random
-from lane_cpu import Lanes, lane_source, needs_host_lanes
+from lane_cpu import CSRC, ROOT, Lanes, lane_source, needs_host_lanes
 from lane_programs import BAD_INDEX, INTEGER, VECTOR, fib_at_every_frame_of_a_chain, fib_below_a_chain, fibs_along_a_chain
 
 pytestmark = needs_host_lanes
@@ -239,3 +242,28 @@ def test_random_programs():
         results = list(pool.map(_random_case, range(48)))
     assert [r for r, _ in results if r] == []
     assert sum(ran for _, ran in results) >= 24   # (the others are too large, or none of the lanes')
+
+
+def test_when_waves_look_after_every_sweep(tmp_path):
+    # (waves, instances, tags a wave reports at once, busy lanes, sweeps of the wave, age of the run): max_tags says what there
+    # is room for (tags_at_once is max_tags over twice the waves), so ample room alone must not break a run up for good
+    cases = {(2048, 1, 4096, 60, 3, 5000): 1, (2048, 1, 4096, 60, 3, 50000): 0,   # while the run is young
+             (2048, 1, 256, 60, 3, 5000): 0, (2048, 300, 4096, 60, 3, 5000): 0,   # too small for it at any rate; many roots
+             (2048, 1, 4096, 60, 16, 5000): 0, (2048, 1, 4096, 10, 3, 50000): 0,
+             (2048, 300, 64, 10, 47, 50000): 1, (2048, 300, 64, 10, 48, 50000): 0,   # few lanes with all the work
+             (8, 8, 64, 10, 47, 50000): 1, (8, 8, 64, 32, 3, 0): 0}
+    src = tmp_path / "spreads.cpp"
+    src.write_text("""#include "host_wave.h"
+#include "lane_device.h"
+int main() {
+  unsigned w, n, t, r, i, age;
+  while (scanf("%u %u %u %u %u %u", &w, &n, &t, &r, &i, &age) == 6)
+    printf("%d\\n", (int)tdf::lane_spreads(w, n, t, r, i, [&] { return age; }));
+}
+""")
+    exe = tmp_path / "spreads"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-I", CSRC, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "tests"),
+                    str(src), "-o", str(exe)], check=True)
+    text = "".join("%d %d %d %d %d %d\n" % c for c in cases)
+    got = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.split()
+    assert dict(zip(cases, map(int, got))) == cases
