@@ -268,8 +268,9 @@ def main():
                      "how": "one host thread, graph, workspace and stream per evaluation in flight; the library runs an "
                             "evaluation's tag machine (which depends on the trees only) beside the previous evaluation's "
                             "data plane; every evaluation is complete"}
-    # which tag phase it was: the depth-first lanes are two launches, the step machine two and more per round
-    on_lanes = int(st.phase_launches[0]) == 2
+    # which tag phase it was (the walk and the depth-first lanes are one launch behind the one that clears)
+    tag_phase = {tdf.TAGS_STEP_MACHINE: "step machine", tdf.TAGS_LANES: "depth-first lanes", tdf.TAGS_WALK: "walk over the forest"}[int(st.tag_phase)]
+    on_lanes = int(st.tag_phase) != tdf.TAGS_STEP_MACHINE
     # one more evaluation, outside the timed region, with the tag machines' step records switched on
     widest = []
     if on_lanes:
@@ -294,10 +295,10 @@ def main():
     tag_ms = phase[0] / a.steps
     if on_lanes:
         # What the phase cannot do without: arguments and results; for trees the forest (12 B a node) and the schedule
-        # (16 B a leaf or cell).  What bounds it is the chain of dependent calls, not these bytes.
+        # (16 B a leaf or cell).  What bounds it is the chain of dependent calls or nodes, not these bytes.
         tag_bytes = (8.0 * (len(ns) * 2 if cfg == 1 else n_inst * 3) if cfg in (1, 6) else
                      12.0 * c["forest"].n_nodes + 16.0 * int(st.n_leaf_rows + st.n_cell_rows) + 8.0 * 2 * B)
-        roof_tags = {"bound": "latency", "kernel": "depth-first lanes (one launch)", "tags_per_us": n_tags / (tag_ms * 1e3)}
+        roof_tags = {"bound": "latency", "kernel": tag_phase + " (one launch)", "tags_per_us": n_tags / (tag_ms * 1e3)}
     else:
         # step machine: algorithmic bytes per tag of matching + compaction (table entry and frame record
         # written, frame read on return, operand slot, arrival word, ready id, schedule-log entry): 72 B
@@ -359,7 +360,7 @@ def main():
                       "n_levels": int(st.n_waves), "max_tag_depth": int(st.max_tag_depth), "scale": a.scale,
                       "latency_ms": round(latency_ms, 4),   # mean time of one evaluation from call to return
                       # which way the evaluation took
-                      "n_machines": int(st.n_machines), "die_local": int(st.die_local), "generated_step_kernels": int(st.generated),
+                      "tag_phase": tag_phase, "n_machines": int(st.n_machines), "die_local": int(st.die_local), "generated_step_kernels": int(st.generated),
                       "repeats": int(st.repeats), "tail_used": int(st.tail_used), "deep_split": int(st.deep_split),
                       "deep_cells": int(st.deep_cells), "frames_reclaimed": int(st.frames_reclaimed),
                       "peak_frames": int(st.peak_frames)},

@@ -265,6 +265,13 @@ enum {
   TDF_PHASE_COUNT
 };
 
+/* What made the tags of an evaluation (tdf_stats.tag_phase). */
+enum {
+  TDF_TAGS_STEP_MACHINE = 0, /* match/fire steps over a frame table                        */
+  TDF_TAGS_LANES,            /* the depth-first lanes                                      */
+  TDF_TAGS_WALK              /* a walk over the forest                                     */
+};
+
 typedef struct {
   int64_t n_tags;         /* tags created = function invocations + loop iterations      */
   int64_t n_steps;        /* match/fire steps of the tag machine; on the lanes the most sweeps
@@ -285,9 +292,11 @@ typedef struct {
   int64_t peak_frames;    /* frame records ever handed out: with frames given back, the largest
                              number of tags alive at once (summed over the machines); on the lanes
                              the records in use at once and the frames on a lane's stack, the
-                             largest number of every wave and lane summed, n_tags at most */
+                             largest number of every wave and lane summed, n_tags at most; on
+                             the walk, which has no frames, the nodes that wait on a wave's stack
+                             (512 at most) and its 64 lanes, summed likewise            */
   int64_t frames_reclaimed; /* 1: frames were given back as their tags finished (always so on
-                             the lanes)                                                */
+                             the lanes and the walk)                                   */
   double phase_ms[TDF_PHASE_COUNT];        /* device time of each phase                */
   int64_t phase_launches[TDF_PHASE_COUNT]; /* kernel launches of each phase            */
   double fwd_cells_span_ms; /* first launch to last end of the forward cell kernels, over both
@@ -304,18 +313,22 @@ typedef struct {
   int32_t die_local;      /* 1: every machine kept to one accelerator die, atomics in its L2;
                              0: device-scope kernels                                    */
   int32_t generated;      /* 1: step kernels (or lanes) generated for this program at run time;
-                             0: the table interpreter                                   */
+                             0: there are none (the table interpreter, or a walk without them) */
   int32_t repeats;        /* runs that were discarded and repeated inside this call: a part of
                              the tag table overflowed, die-private kernels left their die, the
                              lanes left the evaluation to the step machine (more tags than
-                             max_tags, a call with some arguments dead), or the workgroups of a
-                             chain launch could not all start in time                    */
+                             max_tags, a call with some arguments dead), the walk left it to
+                             the lanes (nodes that several visit, trees that are too wide for
+                             it), or the workgroups of a chain launch could not all start in
+                             time                                                        */
   int32_t tail_used;      /* 1: narrow levels ran in one launch per pass                */
   int32_t deep_split;     /* 1: the deep instances (root level >= 32) ran apart from the others,
                              their narrow levels in one launch per pass; 2: ... on a second
                              stream, beside the others                                   */
   /* live firings per static-graph node, indexed like tdf_graph_info_t.nodes            */
   int64_t fire_count[TDF_STATS_MAX_COUNTS];
+  int32_t tag_phase;      /* TDF_TAGS_*                                                  */
+  int32_t reserved;       /* 0                                                           */
 } tdf_stats;
 
 /* Bytes of workspace needed by tdf_eval (with_grad = 0) or tdf_eval_grad (1) for these

@@ -637,6 +637,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     }
     if (lt.bad && use_walk) {   // left to the lanes, which start over
       use_walk = false;
+      ++repeats;
       gr->walk_skip = gr->walk_skip_next;
       gr->walk_skip_next = std::min(2u * gr->walk_skip_next, (uint32_t)tdf_graph::LANES_SKIP_MOST);
       memset(launches, 0, sizeof(launches));
@@ -1041,7 +1042,8 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     }
     stats->n_machines = (int32_t)e.n_dies;
     stats->die_local = gr->die_local ? 1 : 0;
-    stats->generated = use_jit || use_lanes ? 1 : 0;
+    stats->generated = use_jit || (use_lanes && !use_walk) ? 1 : 0;
+    stats->tag_phase = !use_lanes ? TDF_TAGS_STEP_MACHINE : use_walk ? TDF_TAGS_WALK : TDF_TAGS_LANES;
     stats->repeats = (int32_t)repeats + inherited_repeats;
     stats->tail_used = use_tail || deep ? 1 : 0;
     stats->deep_split = deep ? (deep_beside ? 2 : 1) : 0;

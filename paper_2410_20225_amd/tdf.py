@@ -26,6 +26,7 @@ F32, BF16 = 0, 1
 SNODE_MERGE_ENTRY, SNODE_CALL, SNODE_RETURN, SNODE_ENTER, SNODE_NEXT, SNODE_EXIT = 100, 101, 102, 103, 104, 105
 MAX_INPUTS = 4
 STATS_MAX_COUNTS = 256
+TAGS_STEP_MACHINE, TAGS_LANES, TAGS_WALK = range(3)   # Stats.tag_phase
 PHASES = ("tags", "leaves", "levels", "cells_fwd", "head", "cells_bwd", "weight_grad", "embed_grad", "tail_fwd", "tail_bwd")
 
 
@@ -96,7 +97,7 @@ class Stats(C.Structure):
                 ("device_status", C.c_int32), ("n_counts", C.c_int32),
                 ("n_machines", C.c_int32), ("die_local", C.c_int32), ("generated", C.c_int32),
                 ("repeats", C.c_int32), ("tail_used", C.c_int32), ("deep_split", C.c_int32),
-                ("fire_count", C.c_int64 * STATS_MAX_COUNTS)]
+                ("fire_count", C.c_int64 * STATS_MAX_COUNTS), ("tag_phase", C.c_int32), ("reserved", C.c_int32)]
 
 
 def _declare(l):

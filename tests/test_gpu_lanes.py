@@ -108,19 +108,25 @@ TREES = {
 }
 
 
-@pytest.mark.parametrize("waves", ["1", None], ids=["one_wave", "waves_default"])
+@pytest.mark.parametrize("waves", ["1", None, "walk"], ids=["one_wave", "waves_default", "walk"])
 @pytest.mark.parametrize("name", list(TREES))
 def test_tree_programs(name, waves, monkeypatch):
+    # (recursions over the children of tree nodes are walked, unless that is switched off)
     c = TREES[name]()
     F = c["forest"]
     B = F.n_trees
-    if waves:
-        monkeypatch.setenv("TDF_LANE_WAVES", waves)
+    tag_phase = tdf.TAGS_WALK
+    if waves != "walk":
+        monkeypatch.setenv("TDF_NO_WALK", "1")
+        tag_phase = tdf.TAGS_LANES
+        if waves:
+            monkeypatch.setenv("TDF_LANE_WAVES", waves)
     dy = np.full(B, 1.0 / B)
     ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
     run = TreeRun(c, head=True, grad=True, stats_level=0)
     for _ in range(2):
         st, stats = run.run(dy)
+        assert stats.tag_phase == tag_phase
         assert stats.repeats == 0 and stats.n_tags == F.n_nodes == len(ref["it"].tags) and stats.max_tag_depth == ref["it"].max_tag_len
         assert stats.n_leaf_rows == int(F.n_leaves.sum()) and stats.n_cell_rows == int(F.n_leaves.sum()) - B
         assert stats.n_grad_firings == F.n_nodes and stats.n_grad_not_once == 0
@@ -138,6 +144,7 @@ def test_tree_programs(name, waves, monkeypatch):
     run = TreeRun(c, head=False, grad=True, node_labels=lab, stats_level=0)
     st, stats = run.run(None, dnode=dnode)
     got = run.out_node_loss.cpu().numpy()
+    assert stats.tag_phase == tag_phase
     assert stats.repeats == 0 and np.array_equal(got == 0.0, want == 0.0) and rel_fro(got, want) < 2e-2
 
 

@@ -144,8 +144,11 @@ def _deep_trees():
     return c
 
 
-def test_two_tree_evaluations_in_flight_on_the_lanes():
-    # statistics level 0: one evaluation's depth-first lanes beside the other's level and chain launches
+@pytest.mark.parametrize("walk", [False, True], ids=["lanes", "walk"])
+def test_two_tree_evaluations_in_flight_on_the_lanes(walk, monkeypatch):
+    # statistics level 0: one evaluation's depth-first lanes, or its walk, beside the other's level and chain launches
+    if not walk:
+        monkeypatch.setenv("TDF_NO_WALK", "1")
     c = _deep_trees()
     B = c["forest"].n_trees
     dy = np.full(B, 1.0 / B)
@@ -156,6 +159,7 @@ def test_two_tree_evaluations_in_flight_on_the_lanes():
     def loop(i):
         for _ in range(8):
             st, stats = runs[i].run(dy)
+            assert stats.tag_phase == (tdf.TAGS_WALK if walk else tdf.TAGS_LANES)
             got[i].append((stats.n_tags, stats.n_grad_firings, stats.n_grad_not_once, stats.repeats, stats.tail_used, runs[i].out_f32.clone()))
 
     _in_threads([lambda i=i: loop(i) for i in range(2)])

@@ -1,6 +1,8 @@
 """The walk over the forest (forest_walk.hip) against the lanes, which run every program: same results, same counts, same
 refusals, on forests of every shape: shuffled, with nodes nobody asks for, shared nodes, bad entries, and trees that
-leave the walk's stack."""
+leave the walk's stack; and which of the two ran (tdf_stats.tag_phase).  Gradients on both, and where a walk was left to the
+lanes, against the oracle."""
+import dataclasses
 import os
 
 import numpy as np
@@ -11,6 +13,8 @@ pytestmark = pytest.mark.gpu
 
 from paper_2410_20225_amd import tdf, programs  # noqa: E402
 from paper_2410_20225_amd.programs import _Fn  # noqa: E402
+from tdf_workloads import make_config  # noqa: E402
+from gpu_util import TreeRun, run_oracle_tree, rel_fro  # noqa: E402
 
 DEV, H, V, C = "cuda:0", 64, 50, 5
 KEYS = ("n_tags", "n_tokens", "n_leaf_rows", "n_cell_rows", "n_waves", "max_tag_depth")
@@ -110,20 +114,23 @@ def _run(prog, forest, walk, max_tags=None, label_first=False, nodes=False, voca
         for _ in range(2):
             st, stats = tdf.eval(g, inp, ws, check=False, **out)
             res.append((st, [getattr(stats, k) for k in KEYS] if st == tdf.OK else None,
-                        [o.cpu().numpy().copy() for o in out.values()] if st == tdf.OK else None))
+                        [o.cpu().numpy().copy() for o in out.values()] if st == tdf.OK else None, stats))
         return res
     finally:
         os.environ.pop("TDF_NO_WALK", None)
 
 
-def _same(prog, forest, **kw):
+def _same(prog, forest, left=False, form=True, **kw):
+    """left: the forest is one that the walk leaves to the lanes; form: the program is one that is walked."""
     a, b = _run(prog, forest, True, **kw), _run(prog, forest, False, **kw)
-    for x, y in zip(a, b):
+    for k, (x, y) in enumerate(zip(a, b)):
         assert x[0] == y[0] and x[1] == y[1], (x[:2], y[:2])
         if x[0] == tdf.OK:   # (a row's arithmetic does not depend on where the row lies)
             for o, p in zip(x[2], y[2]):
                 assert np.array_equal(o, p)
-    return a[0][0]
+            assert x[3].tag_phase == (tdf.TAGS_WALK if form and not left else tdf.TAGS_LANES) and y[3].tag_phase == tdf.TAGS_LANES
+            assert x[3].repeats == (1 if form and left and k == 0 else 0) and y[3].repeats == 0   # (a graph remembers it for a while)
+    return a[0]
 
 
 def _forests():
@@ -135,8 +142,8 @@ def _forests():
     yield "in_order", _trees(some, rng, shuffle=False)
     yield "chains", _trees([_chain(70), _chain(3), None], rng)
     yield "right_chain", _trees([tuple_chain(90)], rng)
-    # 60 spines of 50 under a spine: more right children than the stack holds
-    yield "combs", _trees([_chain(80, _chain(60)), _chain(5)], rng)
+    # spines of spines of spines: more right children at once than the stack holds (leaves would be taken as they come)
+    yield "combs", _trees([_chain(100, _chain(20, _chain(4))), _chain(5)], rng)
     l, r, t, roots = _trees(some, rng)
     yield "nodes_nobody_asks_for", (l, r, t, roots[::3])
     yield "the_same_root_twice", (l, r, t, np.concatenate([roots[:5], roots[3:9]]))
@@ -174,23 +181,58 @@ def tuple_chain(n):
 FORESTS = list(_forests())
 
 
+SHARED = {"the_same_root_twice", "a_root_inside_another_tree", "both_children_the_same", "a_child_of_two_trees"}
+
+
 @pytest.mark.parametrize("name,forest", FORESTS, ids=[n for n, _ in FORESTS])
 def test_forests(name, forest):
     wrong = {"right_missing", "right_out_of_range", "left_out_of_range", "token_out_of_range", "root_out_of_range", "a_cycle"}
-    st = _same(programs.tree("lstm", True), forest, max_tags=4 * max(len(forest[0]), len(forest[3])))
+    st, _, _, stats = _same(programs.tree("lstm", True), forest, left=name in SHARED, max_tags=4 * max(len(forest[0]), len(forest[3])))
     assert (st != tdf.OK) == (name in wrong)
+    if name == "combs":   # a wave's stack was full (512 nodes, and 64 lanes), so its lanes kept lists
+        assert stats.peak_frames >= 512 + 64 + 64
 
 
 @pytest.mark.parametrize("max_tags", [1, 2])
 def test_fewer_tags_than_nodes(max_tags):
     forest = dict(FORESTS)["random"]
     n = len(forest[0])
-    assert _same(programs.tree("lstm", True), forest, max_tags=max(n // max_tags, 30)) == (tdf.OK if max_tags == 1 else tdf.ERR_TABLE_FULL)
+    assert _same(programs.tree("lstm", True), forest, max_tags=max(n // max_tags, 30))[0] == (tdf.OK if max_tags == 1 else tdf.ERR_TABLE_FULL)
 
 
 def test_other_programs():
     for name in ("random", "combs", "nodes_nobody_asks_for"):
         forest = dict(FORESTS)[name]
-        assert _same(_swapped(), forest, label_first=True) == tdf.OK
-        assert _same(_leaf_label(), forest) == tdf.OK
-        assert _same(programs.tree("lstm", False, True), forest, nodes=True) == tdf.OK
+        assert _same(_swapped(), forest, label_first=True)[0] == tdf.OK
+        assert _same(_leaf_label(), forest, form=False)[0] == tdf.OK
+        assert _same(programs.tree("lstm", False, True), forest, nodes=True)[0] == tdf.OK
+
+
+@pytest.mark.parametrize("walk", [True, False], ids=["walk", "lanes"])
+@pytest.mark.parametrize("shared", [False, True], ids=["trees", "roots_twice"])
+@pytest.mark.parametrize("cfg,bf16", [(2, False), (4, True)])
+def test_gradients(cfg, bf16, shared, walk, monkeypatch):
+    # shared: some instances ask for the same trees, so the first evaluation's walk is left to the lanes half way
+    if not walk:
+        monkeypatch.setenv("TDF_NO_WALK", "1")
+    c = make_config(cfg, n_trees=30, max_leaves=20, hidden=48, vocab=100)
+    F = c["forest"]
+    n_tags = F.n_nodes
+    if shared:
+        again = np.arange(0, 30, 4)
+        c["forest"] = dataclasses.replace(F, roots=np.concatenate([F.roots, F.roots[again]]), n_leaves=np.concatenate([F.n_leaves, F.n_leaves[again]]))
+        c["labels"] = np.concatenate([c["labels"], c["labels"][again]])
+        n_tags += int((2 * F.n_leaves[again] - 1).sum())
+    B = c["forest"].n_trees
+    dy = np.linspace(0.5, 1.5, B) / B
+    ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
+    run = TreeRun(c, head=True, grad=True, stats_level=0, max_tags=n_tags)
+    tol = 2e-2 if bf16 else 2e-5   # (the bars of the other gradient tests)
+    for k in range(2):
+        st, stats = run.run(dy)
+        assert stats.tag_phase == (tdf.TAGS_WALK if walk and not shared else tdf.TAGS_LANES)
+        assert stats.repeats == (1 if walk and shared and k == 0 else 0)
+        assert stats.n_tags == stats.n_grad_firings == n_tags and stats.n_grad_not_once == 0
+        assert rel_fro(run.out_f32.cpu().numpy(), np.array(ref["out"])) < tol
+        for name, t in (("dW", run.dW), ("db", run.db), ("dE", run.dE)):
+            assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < tol, name
