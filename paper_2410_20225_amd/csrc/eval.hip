@@ -586,6 +586,7 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
   const LaneReport* rep = (const LaneReport*)((char*)gr->pinned + PIN_LANES);
   const EndReport* fin = (const EndReport*)((char*)gr->pinned + PIN_END);
   bool ended = false;       // the end's report has been read
+  bool walk_left = false;   // the walk has left the evaluation to the lanes
   bool left_over = false;   // the lanes have left the evaluation to the step machine
   bool rows_known = false;  // the lanes' report came with the level offsets' totals: rows, order and leaves are queued
   auto finish = [&](uint32_t lanes_max_tags, const void* sync, const void* gcount) -> tdf_status {
@@ -637,9 +638,8 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     }
     if (lt.bad && use_walk) {   // left to the lanes, which start over
       use_walk = false;
+      walk_left = true;
       ++repeats;
-      gr->walk_skip = gr->walk_skip_next;
-      gr->walk_skip_next = std::min(2u * gr->walk_skip_next, (uint32_t)tdf_graph::LANES_SKIP_MOST);
       memset(launches, 0, sizeof(launches));
       begin(TDF_PHASE_TAGS);
       compile_lanes();
@@ -741,7 +741,13 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     if (!hc.status) launch_merge_logs(e, leaf_off, cell_off, s);
     break;
   }
-  if (left_over && !hc.status) {   // ... which had no complaint
+  // What had no complaint was left for what the inputs are, and the next ones may be like them; inputs that are refused say
+  // nothing about others.
+  if (walk_left && !hc.status) {
+    gr->walk_skip = gr->walk_skip_next;
+    gr->walk_skip_next = std::min(2u * gr->walk_skip_next, (uint32_t)tdf_graph::LANES_SKIP_MOST);
+  }
+  if (left_over && !hc.status) {
     gr->lanes_skip = gr->lanes_skip_next;
     gr->lanes_skip_next = std::min(2u * gr->lanes_skip_next, (uint32_t)tdf_graph::LANES_SKIP_MOST);
   }

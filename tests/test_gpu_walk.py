@@ -236,3 +236,25 @@ def test_gradients(cfg, bf16, shared, walk, monkeypatch):
         assert rel_fro(run.out_f32.cpu().numpy(), np.array(ref["out"])) < tol
         for name, t in (("dW", run.dW), ("db", run.db), ("dE", run.dE)):
             assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < tol, name
+
+
+def test_a_refused_evaluation_does_not_keep_the_next_one_from_the_walk():
+    # a token out of range; then the same graph on a forest that is in order, and on one with shared nodes
+    c = make_config(4, n_trees=12, max_leaves=9, hidden=32, vocab=40)
+    run = TreeRun(c, head=True, grad=False, stats_level=0, max_tags=2 * c["forest"].n_nodes)
+    run.run()
+    want = run.out_f32.clone()
+    leaf = int(np.nonzero(c["forest"].left < 0)[0][4])
+    good = int(run.t_token[leaf])
+    for _ in range(3):
+        run.t_token[leaf] = 40
+        assert run.run(check=False)[0] == tdf.ERR_BAD_ARG
+        run.t_token[leaf] = good
+        st, stats = run.run()
+        assert stats.tag_phase == tdf.TAGS_WALK and stats.repeats == 0 and torch.equal(run.out_f32, want)
+    args = run.t_args.clone()
+    run.t_args[1] = run.t_args[0]
+    got = [run.run()[1] for _ in range(10)]   # left once, eight at once on the lanes, and the walk has its turn again
+    assert [st.repeats for st in got] == [1] + [0] * 8 + [1] and all(st.tag_phase == tdf.TAGS_LANES for st in got)
+    run.t_args.copy_(args)
+    assert run.run()[1].tag_phase == tdf.TAGS_LANES and torch.equal(run.out_f32, want)
