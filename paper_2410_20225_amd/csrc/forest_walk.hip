@@ -8,10 +8,18 @@
 // which lanes without a node take from; a leaf turns the lane round, and the second of two children that arrive at their
 // parent goes on up.  The schedule log is indexed by node, so a value's name is its node.
 //
-// The rule: programs of that form (walk_form, below), forests of at most as many nodes as the log has entries, and at most
-// WALK_NODES nodes an instance on average, since one wave works on an instance: beyond, the lanes share a tree
-// between waves.  A forest whose nodes are shared (between parents or instances), or have bad entries, and a tree that is
-// much wider than the average, leave a status, and the lanes run the evaluation; what they make of it counts.
+// The rule: programs of that form (walk_form, below) and forests of at most as many nodes as the log has entries.  One wave
+// works on an instance, at 32 nodes a step where the tree is wide, 0.02 to 0.03 us a node; the lanes share a tree
+// between waves, at some 3 us a level and, with all of them busy, 0.003 us a node of all instances.  So a wave leaves a wide tree to
+// them (16 nodes a step and more) once it is, or the trees are on average, of more than 6,000 nodes, 150 for every level down and a
+// twelfth of the forest.  us of an evaluation, all nodes walked -> left to the lanes (and the call whose walk is left): one complete
+// tree of 16,384 leaves 850 -> 287 (397), a random one of 16,384 1,197 -> 611 (763), of 8,192 665 -> 522, a complete one of 30,000
+// with 63 of 20 beside it 1,539 -> 366 (803), eight complete ones of 16,384 777 -> 465 (575), eight random ones 1,205 -> 1,340.
+// Walked all the same (lanes): a complete tree of 4,096 leaves 248 us (226), a random one of 4,096 377 (450), 64 complete ones of
+// 16,384 1,035 (849), 64 random ones 1,463 (2,372); chains of any length, 16,384 leaves 40.1 ms (66.8).  More than WALK_NODES
+// nodes an instance on average, more than those, were not measured and go to the lanes.
+// A forest whose nodes are shared (between parents or instances), or have bad entries, leaves a status, and the lanes run the
+// evaluation; what they make of it counts.
 //
 // What bounds it: the latency of one request per level down (the node's entries) and one up (the parent's word, in the die's
 // L2), and some 150 instructions a step: 1.4 us a level there and back, where the lanes' sweeps take 3.3.
@@ -132,7 +140,6 @@ WalkForm walk_form(const DevProgram& P) {
 constexpr uint32_t WALK_STACK = 512;            // nodes on a wave's stack in LDS
 constexpr uint32_t WALK_ROOT = 0xFFFFFFFEu;     // parent of an instance's root
 constexpr uint32_t WALK_NONE = 0xFFFFFFFFu;     // no node
-constexpr uint32_t WALK_WIDE = 65536u;          // visits from which on a tree of 16 nodes a step or more is left to the lanes
 
 // On entry log[v].z is LANE_LOG_HOLE for all nodes.  row_of[v] becomes v's parent (until the rows are numbered), log[v] the
 // entry of v's EMBED or cell; before that log[v].z is the level of the first child that is through.  All that concerns a
@@ -172,6 +179,7 @@ __global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w, Stam
     }
   };
   bool lists = false;   // (uniform) a lane has had a list of its own
+  const uint32_t average = n_nodes / a.n_inst;
   for (;;) {
     if (__builtin_expect(__ballot(bad != 0) != 0, 0)) break;
     // ---- lanes without a node take one of the stack, or of their own list
@@ -284,7 +292,8 @@ __global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w, Stam
       // (A step of the wave is a visit, or a cell, or the first child's arrival, of which there is one a visit or cell: on
       // any forest one of the two counts passes the number of nodes if the walk does not end before.)
       const uint32_t seen = wave_usum(n_leaf + n_inner);
-      if (seen > n_nodes || wave_usum(n_cell) > n_nodes || (seen > WALK_WIDE && seen > 16u * iter)) bad = TDF_ERR_UNSUPPORTED;
+      const bool wide = seen > 16u * iter && max(seen, average) > 6000u + 150u * wave_umax(depth) + n_nodes / 12u;   // (see above)
+      if (seen > n_nodes || wave_usum(n_cell) > n_nodes || wide) bad = TDF_ERR_UNSUPPORTED;
       if (lane_ld(&a.ctl->status) != 0) break;   // another wave has left
     }
   }

@@ -238,6 +238,20 @@ def test_gradients(cfg, bf16, shared, walk, monkeypatch):
             assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < tol, name
 
 
+def _complete(levels):
+    s = None
+    for _ in range(levels):
+        s = (s, s)
+    return s
+
+
+@pytest.mark.parametrize("shapes,left", [([_complete(11)], False), ([_complete(14)], True), ([_complete(14)] + [_chain(9)] * 20, True),
+                                         ([_complete(12)] * 16, False), ([_chain(9000)], False), ([_chain(3000), _complete(11)], False)],
+                         ids=["complete_2k", "complete_16k", "complete_16k_and_small_ones", "16_of_4k", "chain_9k", "chain_and_complete"])
+def test_wide_trees_are_left_to_the_lanes(shapes, left):
+    assert _same(programs.tree("lstm", True), _trees(shapes, np.random.default_rng(3)), left=left)[0] == tdf.OK
+
+
 def test_a_refused_evaluation_does_not_keep_the_next_one_from_the_walk():
     # a token out of range; then the same graph on a forest that is in order, and on one with shared nodes
     c = make_config(4, n_trees=12, max_leaves=9, hidden=32, vocab=40)
