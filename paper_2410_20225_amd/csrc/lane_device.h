@@ -311,13 +311,17 @@ __device__ __forceinline__ void ln_result(LaneX& x, int type, long long v) {
 // the run is too small for this (fib(28), a million tags: 705 us, 775 in pieces), with more it may be all the same.
 // What costs such a run most are the pieces that waves which join late make of pieces, so there is an end to it after
 // 120 us: fib(28) with room for 16 times its tags 730 us.  (An end after 90 us takes back most of what the large runs gain:
-// fib(30..32) 4,000.)  With many roots it gains nothing: 300 of fib(5..18) 220 us and 236 with room for a few million tags, 256 of
-// tak the same either way.  Where no function has two calls there is nothing to give.
+// fib(30..32) 4,000.)  With many roots, where nobody joins late, that end is none: 256 of tak 2,030 us without it, 2,075 with
+// none of this.  Where no function has two calls there is nothing to give.  And only for integer programs: a sweep of
+// a tree program is several times as long, and pieces that small cost more than they bring (tag phase of 8 complete trees of
+// 4,096 leaves 257 us, 188 without; of a random tree of 8,000 leaves with 63 small ones 531 and 390).
 template <class Age>   // age(): ticks since the run began
-__device__ __forceinline__ bool lane_spreads(uint32_t n_waves, uint32_t n_inst, uint32_t tags_at_once, uint32_t n_run, uint32_t iter, Age age) {
+__device__ __forceinline__ bool lane_spreads(uint32_t n_waves, uint32_t n_inst, uint32_t tags_at_once, uint32_t log_cap, uint32_t n_run,
+                                             uint32_t iter, Age age) {
+  if (log_cap) return false;
   const bool fills = n_waves >= 1024u, many = n_inst >= 16u;
   if (n_run < 32u && (!fills || many)) return iter < LANE_EARLY;
-  return fills && !many && tags_at_once >= 512u && iter < LANE_EARLY / 3 && age() < LANE_YOUNG;
+  return fills && tags_at_once >= 512u && iter < LANE_EARLY / 3 && (many || age() < LANE_YOUNG);
 }
 
 // ---- the machine ----------------------------------------------------------------------------------
@@ -728,7 +732,7 @@ __device__ void lanes_run(const LaneArgs& a, char* lds) {
     // ---- a few sweeps
     bool any_done = false;
     const uint32_t n_run = (uint32_t)__popcll(__ballot(x.run));
-    const bool spread = SW::kBranching && lane_spreads(a.n_waves, a.n_inst, a.tags_at_once, n_run, iter,
+    const bool spread = SW::kBranching && lane_spreads(a.n_waves, a.n_inst, a.tags_at_once, a.log_cap, n_run, iter,
                                                        [&] { return (uint32_t)wall_clock64() - t_begin; });
     const uint32_t n_sweeps = spread ? 1u : n_run >= 48 ? LANE_SYNC_FULL : hungry ? 2u : LANE_SYNC;
 #pragma unroll 1

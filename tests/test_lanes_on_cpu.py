@@ -245,25 +245,27 @@ def test_random_programs():
 
 
 def test_when_waves_look_after_every_sweep(tmp_path):
-    # (waves, instances, tags a wave reports at once, busy lanes, sweeps of the wave, age of the run): max_tags says what there
-    # is room for (tags_at_once is max_tags over twice the waves), so ample room alone must not break a run up for good
-    cases = {(2048, 1, 4096, 60, 3, 5000): 1, (2048, 1, 4096, 60, 3, 50000): 0,   # while the run is young
-             (2048, 1, 256, 60, 3, 5000): 0, (2048, 300, 4096, 60, 3, 5000): 0,   # too small for it at any rate; many roots
-             (2048, 1, 4096, 60, 16, 5000): 0, (2048, 1, 4096, 10, 3, 50000): 0,
-             (2048, 300, 64, 10, 47, 50000): 1, (2048, 300, 64, 10, 48, 50000): 0,   # few lanes with all the work
-             (8, 8, 64, 10, 47, 50000): 1, (8, 8, 64, 32, 3, 0): 0}
+    # (waves, instances, tags a wave reports at once, entries of the log, busy lanes, sweeps of the wave, age of the run): max_tags
+    # says what there is room for (tags_at_once is max_tags over twice the waves), so ample room alone must not break a run up
+    # for good; and tree programs, which keep a log, are not broken up at all
+    cases = {(2048, 1, 4096, 0, 60, 3, 5000): 1, (2048, 1, 4096, 0, 60, 3, 50000): 0,   # while the run is young
+             (2048, 1, 256, 0, 60, 3, 5000): 0, (2048, 300, 4096, 0, 60, 3, 50000): 1,   # too small for it at any rate; many roots
+             (2048, 1, 4096, 0, 60, 16, 5000): 0, (2048, 1, 4096, 0, 10, 3, 50000): 0,
+             (2048, 300, 64, 0, 10, 47, 50000): 1, (2048, 300, 64, 0, 10, 48, 50000): 0,   # few lanes with all the work
+             (8, 8, 64, 0, 10, 47, 50000): 1, (8, 8, 64, 0, 32, 3, 0): 0,
+             (2048, 1, 4096, 1 << 20, 60, 3, 5000): 0, (8, 8, 64, 4096, 10, 3, 0): 0}
     src = tmp_path / "spreads.cpp"
     src.write_text("""#include "host_wave.h"
 #include "lane_device.h"
 int main() {
-  unsigned w, n, t, r, i, age;
-  while (scanf("%u %u %u %u %u %u", &w, &n, &t, &r, &i, &age) == 6)
-    printf("%d\\n", (int)tdf::lane_spreads(w, n, t, r, i, [&] { return age; }));
+  unsigned w, n, t, l, r, i, age;
+  while (scanf("%u %u %u %u %u %u %u", &w, &n, &t, &l, &r, &i, &age) == 7)
+    printf("%d\\n", (int)tdf::lane_spreads(w, n, t, l, r, i, [&] { return age; }));
 }
 """)
     exe = tmp_path / "spreads"
     subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-I", CSRC, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "tests"),
                     str(src), "-o", str(exe)], check=True)
-    text = "".join("%d %d %d %d %d %d\n" % c for c in cases)
+    text = "".join("%d %d %d %d %d %d %d\n" % c for c in cases)
     got = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.split()
     assert dict(zip(cases, map(int, got))) == cases
