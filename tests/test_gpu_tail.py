@@ -81,3 +81,44 @@ def test_nans_pass_through(cfg, pattern):
     nan = np.isnan(run.out_f32.cpu().numpy())
     assert not nan[~has].any()
     assert cfg == 3 or nan[has].all()
+
+
+@pytest.mark.parametrize("where", ["embedding", "dy"])
+@pytest.mark.parametrize("cfg,bf16", [(2, False), (3, True), (4, False), (4, True)])
+def test_nans_pass_through_both_passes(cfg, bf16, where):
+    # A NaN with all bits set enters a tree, as a row of E or as the gradient of its loss, and flows through the states, dz and
+    # dc that the tails wait for: nothing waits for good, and what no such tree has part in is a number.
+    c = make_config(cfg, n_trees=40, max_leaves=16, hidden=64, vocab=400)
+    c["bf16"] = bf16
+    F = c["forest"]
+    B, rnd = F.n_trees, np.random.default_rng(1)
+    tree_of = np.full(F.n_nodes, -1)
+    for b in range(B):   # (a tree's nodes are contiguous from its root)
+        tree_of[F.roots[b]:F.roots[b] + 2 * F.n_leaves[b] - 1] = b
+    leaf = F.token >= 0
+    bad = np.zeros(B, bool)
+    bad[np.flatnonzero(F.n_leaves >= 4)[:5]] = True
+    # the bad trees' tokens are theirs alone
+    F.token[leaf] = np.where(bad[tree_of[leaf]], rnd.integers(300, 400, leaf.sum()), rnd.integers(0, 300, leaf.sum()))
+    run = TreeRun(c, head=True, grad=True, stats_level=0)
+    dy = torch.full((B,), 1.0 / B, dtype=torch.float32, device="cuda:0")
+    if where == "embedding":
+        deepest = [int(F.token[(tree_of == b) & leaf][0]) for b in np.flatnonzero(bad)]
+        run.t_E.view(torch.int16 if bf16 else torch.int32)[deepest] = -1
+    else:
+        dy.view(torch.int32)[torch.tensor(bad, device="cuda:0")] = -1
+    for _ in range(2):   # (the second evaluation finds the first one's rows in the workspace)
+        st, stats = tdf.eval_grad(run.graph, run.inputs, dy, run.ws, run.dW, run.db, run.dE, out_f32=run.out_f32)
+        assert st == tdf.OK and stats.tail_used == 1 and stats.repeats == 0
+        assert stats.n_grad_not_once == 0 and stats.n_grad_firings == F.n_nodes
+        loss, dE = run.out_f32.cpu().numpy(), run.dE.cpu().numpy()
+        assert not np.isnan(loss[~bad]).any() and not np.isnan(dE[:300]).any()
+        # (the 16-bit tanh of a TreeRNN cell clamps its argument, which makes a number of a NaN)
+        clamped = cfg == 3 and bf16
+        if where == "embedding":
+            assert clamped or np.isnan(loss[bad]).all()
+        else:
+            assert not np.isnan(loss).any()
+        if where == "dy" or not clamped:   # every leaf of a bad tree gets its gradient through NaNs
+            assert np.isnan(dE[np.unique(F.token[leaf & bad[tree_of]])]).all()
+            assert np.isnan(run.dW.cpu().numpy()).any() and np.isnan(run.db.cpu().numpy()).any()
