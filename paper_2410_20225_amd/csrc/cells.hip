@@ -2175,7 +2175,7 @@ template <typename T> static void tail_fwd_t(const VecArgs& v, const Engine& e, 
 // has most of them.  That die is the last one through, and with one instance it has them all.
 // A row of tiles that a die's workgroups make side by side (16 cells for every group of them) takes 1.2 to 2.6 us (TreeRNN) or
 // 2.1 to 2.7 (TreeLSTM) forward, a launch of its own 11 to 18; in the gradient pass, which has a third as many groups, 1.5 to
-// 2.3 us and two launches of together 14 to 26.  So eight rows go to the tail (TreeLSTM forward: five), and 128 cells at any
+// 2.3 us and two launches of together 14 to 26.  So eight rows go to the tail (TreeLSTM forward five, TreeRNN backward ten), and 128 cells at any
 // rate (as many as 1,024 make where the dies share them evenly).
 // us, all dies' cells counted -> the fullest die's -> each pass by its own groups: one complete tree of 4,096 leaves, its
 // levels of up to 2,048 cells on one die, TreeRNN of 512 units (three groups and one) 448 -> 283 forward and 904 -> 455
@@ -2197,7 +2197,7 @@ TailLimit vec_tail_limit(const VecArgs& v, int cus_per_die, bool backward) {
     n_ct = v.Hp / (lstm ? Tile<LSTM_FWD>::UNITS : Tile<RNN_FWD>::UNITS);
     wgs = n > 8 ? 0 : tail_wgs(tail_slots_fwd(cus_per_die, n), n_ct, 1u << 20);
   }
-  return TailLimit{0xFFFFFFFFu, std::min(1024u, std::max(128u, (uint32_t)(wgs / n_ct) * (lstm && !backward ? 80u : 128u)))};
+  return TailLimit{0xFFFFFFFFu, std::min(1024u, std::max(128u, (uint32_t)(wgs / n_ct) * (backward ? (lstm ? 128u : 160u) : (lstm ? 80u : 128u))))};
 }
 // The tail's cells are the n_cells from q_first on.  per_die: compute units per accelerator die for this launch (all of its
 // workgroups must be resident together); most_rows: cells of a level on a die, at most

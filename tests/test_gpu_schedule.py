@@ -108,8 +108,8 @@ def _on_top(shape, n):
 
 @pytest.mark.parametrize("cfg,hidden,beside,fwd,bwd", [(3, 256, "0", 1, 2), (4, 128, "0", 1, 2), (3, 256, "1", 1, 2), (4, 128, "1", 2, 2)])
 def test_wide_levels_of_deep_instances_are_launched_over_all_dies(cfg, hidden, beside, fwd, bwd, monkeypatch):
-    # levels of 1,024 and 512 cells on one die: on 32 compute units a die a chain takes 896 and 384 (TreeRNN), 560 and 384; on the
-    # 20 it has beside other instances 512 and 256, 320 and 256
+    # levels of 1,024 and 512 cells on one die: on 32 compute units a die a chain takes 896 and 480 (TreeRNN), 560 and 384; on the
+    # 20 it has beside other instances 512 and 320, 320 and 256
     monkeypatch.setenv("TDF_DEEP_BESIDE", beside)
     st, = _train(_case(cfg, [_on_top(complete_tree(2048), 30)] + SHALLOW[:9], hidden=hidden))
     assert st.deep_split == 1 + int(beside) and st.n_waves == 41
