@@ -4,7 +4,7 @@
 // Call_i of its two calls are the edges to the children, Return_i the edges back.  Where every node is visited at most
 // once, tags and nodes are the same thing, and what the tag machine would log (lane_device.h) follows from the forest
 // alone: a leaf fires its EMBED, an inner node its cell when both children have, one level above the higher of them.
-// One wave walks the tree of one instance.  A lane goes down to the left child and leaves the right one on a stack in LDS,
+// A tree that lies in one piece is numbered where it lies (tree_in_piece).  Any other one wave walks, an instance each: a lane goes down to the left child and leaves the right one on a stack in LDS,
 // which lanes without a node take from; a leaf turns the lane round, and the second of two children that arrive at their
 // parent goes on up.  The schedule log is indexed by node, so a value's name is its node.
 //
@@ -153,31 +153,201 @@ template <typename T> __device__ __forceinline__ T* at32(T* base, uint32_t i) { 
 template <typename T> __device__ __forceinline__ const T* at32(const T* base, uint32_t i) {
   return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)(i * (uint32_t)sizeof(T)));
 }
-__global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w, Stamp st) {
-  __shared__ uint32_t s_node[WALK_STACK], s_parent[WALK_STACK], s_depth[WALK_STACK];
+__device__ __forceinline__ void walk_root(const LaneArgs& a, const WalkForm& w, uint32_t b, uint32_t name, uint32_t level) {
+  a.root_lvl[b] = level;
+  if (w.label_arg >= 0) {
+    a.head_row[b] = name;
+    a.head_label[b] = (uint32_t)a.args[(size_t)b * a.n_args + w.label_arg];
+  } else {
+    a.root_ref[b] = name;
+  }
+}
+// An instance's part of the totals, by one lane.
+__device__ __forceinline__ void walk_count(const LaneArgs& a, uint32_t b, uint32_t leaves, uint32_t cells, uint32_t frames, uint32_t depth,
+                                           uint32_t level, uint32_t steps) {
+  LaneQueue* q = &a.queues[b % a.n_queues];
+  const unsigned long long tags = (unsigned long long)leaves + cells;
+  (void)lane_add(&q->n_tags, tags);
+  (void)lane_add(&q->n_tokens, 2ull * tags);   // an argument and a value each
+  (void)lane_add(reinterpret_cast<unsigned long long*>(&q->n_leaf), leaves | ((unsigned long long)cells << 32));
+  (void)lane_add(reinterpret_cast<unsigned long long*>(&q->n_rec), (unsigned long long)frames);
+  atomicMax(&q->max_depth, depth);
+  if (level) atomicMax(&q->max_level, level);
+  atomicMax(&q->max_iter, steps);
+}
+
+// ---- trees that lie in one piece -----------------------------------------------------------------------
+// A tree whose nodes are neighbours in memory, the root at one end and every parent on the root's side of its children
+// (depth first or level by level, from the first node on or from the last), needs no walk: its workgroup holds it in LDS, where
+// it ends follows from counting (the nodes still open: one more with every inner node, one less with every leaf), and the
+// heights come from doubling: every node knows an ancestor 2^k edges up and tells it the height of what is below itself, then
+// takes that ancestor's ancestor.  ceil(log2 depth) rounds of LDS instead of two requests to the L2 a level.
+// What the nodes are taken for is checked: n - 1 links that all lead to different nodes of the piece, and from all of which the root
+// is reached, are a tree.  Whatever fails (another order, nodes in between, shared nodes, bad entries, more than WINDOW nodes)
+// is walked, which says what is wrong.
+// What bounds it: a dozen LDS accesses a node and round, and the barriers of the rounds where a workgroup has more than one wave.
+// The tag phase in us, walked -> this: one tree of 35 leaves 24 -> 14.5 (two launches), 256 trees of up to 50 leaves 26 -> 14, 1,024 of
+// up to 60 33 -> 15, 4,096 of up to 128, a fifth of them chains, 240 -> 23, 64 chains of 4,096 leaves and 64 complete trees of as many
+// 5,894 -> 68.
+constexpr uint32_t WALK_ANC = 0xFFFFu;   // low half of a node's word: the ancestor it has got to; high half: how far that is
+template <int THREADS, int WINDOW>
+__device__ __forceinline__ bool tree_in_piece(const LaneArgs& a, const WalkForm& w, uint32_t b, uint32_t root, uint32_t* s_up, uint32_t* s_high,
+                                              uint32_t* s_tot, uint32_t* s_end) {
+  constexpr int K = WINDOW / THREADS, NW = THREADS / 64;
+  const uint32_t tid = threadIdx.x, wave = tid >> 6, n_nodes = (uint32_t)a.n_tree_nodes;
+  const int first = a.left[root];
+  const bool ahead = first < 0 || (uint32_t)first > root;   // the children lie behind their parent, or all the other way round
+  const uint32_t room = min((uint32_t)WINDOW, ahead ? n_nodes - root : root + 1u);
+  auto node = [&](uint32_t i) { return ahead ? root + i : root - i; };
+  auto place = [&](int v) { return ahead ? (uint32_t)v - root : root - (uint32_t)v; };   // (a huge one if it is not there)
+  int el[K], er[K];   // left and right child of the thread's nodes; a leaf: negative, token
+  auto entries = [&](int c) {
+    const uint32_t i = (uint32_t)c * THREADS + tid;
+    el[c] = -1;
+    er[c] = 0;
+    if (i < room) {
+      const uint32_t v = node(i);
+      const int l = *at32(a.left, v), r = *at32(a.right, v), t = *at32(a.token, v);
+      el[c] = l;
+      er[c] = l < 0 ? t : r;
+    }
+  };
+  // ---- the nodes' links, up to the one that leaves nothing open
+  if (tid == 0) *s_end = WALK_NONE;
+  uint32_t n = WALK_NONE;   // (uniform, as are the trip counts)
+  int open = 1;
+  entries(0);
+#pragma unroll
+  for (int c = 0; c < K; ++c) {
+    if (n != WALK_NONE || (uint32_t)c * THREADS >= room) break;
+    if (c + 1 < K) entries(c + 1);   // (on their way meanwhile)
+    const uint32_t i = (uint32_t)c * THREADS + tid;
+    const unsigned long long inner = __ballot(i < room && el[c] >= 0);
+    int at = open, after = open;   // open before the wave's first node, and behind the last of all
+    if constexpr (NW > 1) {
+      if ((tid & 63u) == 0) s_tot[wave] = (uint32_t)__popcll(inner);
+      __syncthreads();
+#pragma unroll
+      for (uint32_t k = 0; k < NW; ++k) {
+        const int d = 2 * (int)s_tot[k] - 64;
+        if (k < wave) at += d;
+        after += d;
+      }
+    } else {
+      after += 2 * (int)__popcll(inner) - 64;
+    }
+    const unsigned long long upto = lanemask_lt() | (1ull << (tid & 63u));
+    const unsigned long long closed = __ballot(i < room && at + 2 * (int)__popcll(inner & upto) - (int)(tid & 63u) - 1 == 0);
+    if constexpr (NW > 1) {
+      if (closed && (tid & 63u) == 0) atomicMin(s_end, (uint32_t)c * THREADS + wave * 64u + (uint32_t)__ffsll((long long)closed));
+      __syncthreads();
+      n = (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_end);
+    } else if (closed) {
+      n = (uint32_t)c * THREADS + (uint32_t)__ffsll((long long)closed);
+    }
+    open = after;
+    if (i < min(n, room)) {
+      s_high[i] = 0;
+      if (el[c] >= 0) {
+        const uint32_t l = place(el[c]), r = place(er[c]);
+        if (l < (uint32_t)WINDOW) s_up[l] = i | 0x10000u;
+        if (r < (uint32_t)WINDOW) s_up[r] = i | 0x10000u;
+      }
+    }
+  }
+  if (n == WALK_NONE) return false;
+  __syncthreads();
+  bool good = true;
+  uint32_t up[K];
+#pragma unroll
+  for (int c = 0; c < K; ++c) {
+    const uint32_t i = (uint32_t)c * THREADS + tid;
+    up[c] = 0;
+    if ((uint32_t)c * THREADS < n && i < n) {
+      if (i) up[c] = s_up[i];
+      if (el[c] >= 0) {
+        const uint32_t l = place(el[c]), r = place(er[c]), me = i | 0x10000u;
+        good = good && l - 1u < n - 1u && r - 1u < n - 1u && l != r && s_up[min(l, n - 1u)] == me && s_up[min(r, n - 1u)] == me;
+      }
+    }
+  }
+  if (!__syncthreads_and(good)) return false;
+  // ---- every node tells an ancestor twice as far away as in the round before
+  uint32_t rounds = 0;
+  for (;; ++rounds) {
+    if (rounds > 31u - (uint32_t)__builtin_clz((uint32_t)WINDOW)) return false;   // (a cycle: the piece has no more edges in a row)
+    bool on = false;
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+      const uint32_t p = up[c] & WALK_ANC;
+      if ((uint32_t)c * THREADS < n && p) {   // (the root's own height is the greatest distance from it)
+        const uint32_t q = s_up[p];
+        atomicMax(&s_high[p], s_high[(uint32_t)c * THREADS + tid] + (up[c] >> 16));
+        up[c] = (q & WALK_ANC) | ((up[c] & ~WALK_ANC) + (q & ~WALK_ANC));
+        on = on || (q & WALK_ANC) != 0;
+      }
+    }
+    if (!__syncthreads_or(on)) break;
+#pragma unroll
+    for (int c = 0; c < K; ++c)
+      if ((uint32_t)c * THREADS < n && (uint32_t)c * THREADS + tid < n) s_up[(uint32_t)c * THREADS + tid] = up[c];
+    __syncthreads();
+  }
+  uint32_t far = 0;
+#pragma unroll
+  for (int c = 0; c < K; ++c) far = max(far, up[c] >> 16);
+  far = wave_umax(far);
+  if ((tid & 63u) == 0) atomicMax(&s_high[0], far);
+  __syncthreads();
+  const uint32_t high = s_high[0];   // of the root
+  // ---- the schedule
+  bool bad = false;
+#pragma unroll
+  for (int c = 0; c < K; ++c) {
+    const uint32_t i = (uint32_t)c * THREADS + tid;
+    if ((uint32_t)c * THREADS < n && i < n) {
+      const uint32_t v = node(i);
+      const bool leaf = el[c] < 0;
+      bad = bad || (leaf && (er[c] < 0 || er[c] >= a.vocab));
+      const uint32_t x = (uint32_t)(leaf || w.swapped ? er[c] : el[c]), y = leaf ? 0u : (uint32_t)(w.swapped ? el[c] : er[c]);
+      *at32(a.log, v) = make_uint4(x, y, s_high[i], b);
+      if (a.row_node) *at32(a.row_node, v) = v;
+    }
+  }
+  if (bad) lane_put(&a.ctl->status, (uint32_t)(-TDF_ERR_BAD_ARG));
+  if (tid == 0) {
+    walk_root(a, w, b, root, high);
+    walk_count(a, b, (n + 1u) / 2u, n / 2u, n, high + 1u, high, rounds);
+  }
+  return true;
+}
+
+template <int THREADS, int WINDOW>
+__global__ void __launch_bounds__(THREADS) k_forest_walk(LaneArgs a, WalkForm w, Stamp st) {
+  extern __shared__ uint32_t lds[];   // a piece's words and heights, or the walk's stack
+  __shared__ uint32_t s_tot[THREADS / 64], s_end;
   stamp_now(st);
   const uint32_t lane = threadIdx.x, b = blockIdx.x, n_nodes = (uint32_t)a.n_tree_nodes;
+  const long long root = a.args[(size_t)b * a.n_args + w.root_arg];
+  if (root >= 0 && root < (long long)n_nodes &&
+      tree_in_piece<THREADS, WINDOW>(a, w, b, (uint32_t)root, lds, lds + WINDOW, s_tot, &s_end))
+    return;
+  __syncthreads();   // (the others are through with the piece's words)
+  if (THREADS > 64 && lane >= 64u) return;
+  uint32_t* const s_node = lds;
+  uint32_t* const s_parent = lds + WALK_STACK;
+  uint32_t* const s_depth = lds + 2 * WALK_STACK;
   uint32_t n_stack = 0, most = 0, iter = 0;   // (uniform)
   bool down = false, up = false;
   uint32_t v = 0, p = WALK_ROOT, depth = 1, lvl = 0;   // down: node, its parent and depth; up: level of a node that is through, its parent
   uint32_t own = WALK_NONE;                   // nodes for which the stack had no room: a list through the log entries of these
   uint32_t n_leaf = 0, n_inner = 0, n_cell = 0, mx_depth = 0, mx_level = 0;
   int bad = 0;
-  const long long root = a.args[(size_t)b * a.n_args + w.root_arg];
   if (root < 0 || root >= (long long)n_nodes) bad = TDF_ERR_BAD_ARG;
   else if (lane == 0) {
     v = (uint32_t)root;
     down = true;
   }
-  auto finish = [&](uint32_t name, uint32_t level) {
-    a.root_lvl[b] = level;
-    if (w.label_arg >= 0) {
-      a.head_row[b] = name;
-      a.head_label[b] = (uint32_t)a.args[(size_t)b * a.n_args + w.label_arg];
-    } else {
-      a.root_ref[b] = name;
-    }
-  };
   bool lists = false;   // (uniform) a lane has had a list of its own
   const uint32_t average = n_nodes / a.n_inst;
   for (;;) {
@@ -235,7 +405,7 @@ __global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w, Stam
         if (pp >= n_nodes) {
           up = false;
           mx_level = lvl;
-          if (pp == WALK_ROOT) finish(p, lvl);
+          if (pp == WALK_ROOT) walk_root(a, w, b, p, lvl);
           else bad = TDF_ERR_UNSUPPORTED;   // (another instance has been here)
         }
         p = pp;
@@ -252,7 +422,7 @@ __global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w, Stam
         lvl = 0;
         down = false;
         up = p != WALK_ROOT;
-        if (!up) finish(v, 0u);
+        if (!up) walk_root(a, w, b, v, 0u);
       } else if ((uint32_t)l >= n_nodes || (uint32_t)r >= n_nodes) {
         bad = TDF_ERR_BAD_ARG;
       } else {
@@ -297,7 +467,7 @@ __global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w, Stam
       if (lane_ld(&a.ctl->status) != 0) break;   // another wave has left
     }
   }
-  const unsigned long long leaves = wave_usum(n_leaf), inner = wave_usum(n_inner), cells = wave_usum(n_cell);
+  const uint32_t leaves = wave_usum(n_leaf), inner = wave_usum(n_inner), cells = wave_usum(n_cell);
   if (bad == 0 && inner != cells) bad = TDF_ERR_UNSUPPORTED;
   const unsigned long long bm = __ballot(bad != 0);
   const uint32_t md = wave_umax(mx_depth), ml = wave_umax(mx_level);
@@ -305,18 +475,22 @@ __global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w, Stam
     const int code = __shfl(bad, __ffsll((long long)bm) - 1);
     if (lane == 0) lane_put(&a.ctl->status, (uint32_t)(-code));
   } else if (lane == 0) {
-    LaneQueue* q = &a.queues[b % a.n_queues];
-    (void)lane_add(&q->n_tags, leaves + cells);
-    (void)lane_add(&q->n_tokens, 2ull * (leaves + cells));   // an argument and a value each
-    (void)lane_add(reinterpret_cast<unsigned long long*>(&q->n_leaf), leaves | (cells << 32));
-    (void)lane_add(reinterpret_cast<unsigned long long*>(&q->n_rec), (unsigned long long)(most + 64u));
-    atomicMax(&q->max_depth, md);
-    if (ml) atomicMax(&q->max_level, ml);
-    atomicMax(&q->max_iter, iter);
+    walk_count(a, b, leaves, cells, most + 64u, md, ml, iter);
   }
 }
+template <int THREADS, int WINDOW> static void launch_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s) {
+  constexpr size_t lds = sizeof(uint32_t) * (2 * WINDOW > 3 * (int)WALK_STACK ? 2 * WINDOW : 3 * (int)WALK_STACK);
+  if (lds > 48 * 1024)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_forest_walk<THREADS, WINDOW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_forest_walk<THREADS, WINDOW>), dim3(a.n_inst), dim3(THREADS), lds, s, a, w, st);
+}
+// The workgroup and its window by the nodes of an instance on average: room for a few times as many, where that leaves a compute unit enough
+// instances to work on.
 void launch_forest_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s) {
-  hipLaunchKernelGGL(k_forest_walk, dim3(a.n_inst), dim3(64), 0, s, a, w, st);
+  const uint32_t average = (uint32_t)a.n_tree_nodes / a.n_inst;
+  if (average > 1024u) launch_walk<1024, 16384>(a, w, st, s);
+  else if (average > 192u || a.n_inst <= 256u) launch_walk<256, 4096>(a, w, st, s);
+  else launch_walk<64, 512>(a, w, st, s);
 }
 
 }  // namespace tdf

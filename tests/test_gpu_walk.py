@@ -272,3 +272,93 @@ def test_a_refused_evaluation_does_not_keep_the_next_one_from_the_walk():
     assert [st.repeats for st in got] == [1] + [0] * 8 + [1] and all(st.tag_phase == tdf.TAGS_LANES for st in got)
     run.t_args.copy_(args)
     assert run.run()[1].tag_phase == tdf.TAGS_LANES and torch.equal(run.out_f32, want)
+
+
+# ---- trees in one piece of memory, which are not walked: the schedule's steps are rounds of doubling (14 at most)
+
+def _in_pieces(shapes, order, rng):
+    """Tree after tree, depth first or level by level, the roots in front or (back) behind their trees."""
+    left, right, token, roots = _trees(shapes, rng, shuffle=False)
+    name = np.arange(left.size)
+    if "level" in order:
+        for top, end in zip(roots, np.append(roots[1:], left.size)):
+            todo = [top]
+            for v in todo:
+                if left[v] >= 0:
+                    todo += [left[v], right[v]]
+            name[todo] = np.arange(top, end)
+    if "back" in order:
+        name = left.size - 1 - name
+    new = lambda a: np.where(a >= 0, name[np.maximum(a, 0)], -1)  # noqa: E731
+    l2, r2 = np.empty_like(left), np.empty_like(right)
+    l2[name], r2[name] = new(left), new(right)
+    return l2, r2, token, name[roots]
+
+
+# (one wave and 512 nodes, four and 4,096, sixteen and 16,384: a workgroup's window by the trees' number and average size)
+PIECES = {
+    "waves1": lambda rng: [_random(int(n), rng) for n in rng.integers(1, 70, 270)] + [_chain(255), _complete(8), _random(256, rng)],
+    "waves4": lambda rng: [_chain(2047), _complete(11), _random(900, rng), None, (None, None)] + [_random(9, rng)] * 20,
+    "waves16": lambda rng: [_chain(8191), _random(3000, rng), _complete(13)],
+}
+
+
+@pytest.mark.parametrize("order", ["depth", "depth back", "level", "level back"])
+@pytest.mark.parametrize("size", PIECES)
+def test_trees_in_one_piece(size, order):
+    rng = np.random.default_rng(8)
+    stats = _same(programs.tree("lstm", True), _in_pieces(PIECES[size](rng), order, rng))[3]
+    assert 0 < stats.n_steps <= 14
+
+
+@pytest.mark.parametrize("leaves,small", [(257, 300), (2049, 4), (8193, 0)], ids=["waves1", "waves4", "waves16"])
+def test_a_tree_too_large_for_the_window_is_walked(leaves, small):
+    rng = np.random.default_rng(9)
+    stats = _same(programs.tree("lstm", True), _in_pieces([_chain(leaves - 1)] + [_random(20, rng)] * small, "depth", rng))[3]
+    assert stats.n_steps > leaves
+
+
+@pytest.mark.parametrize("order", ["depth", "level back"])
+@pytest.mark.parametrize("what", ["a_stranger_inside", "a_child_before_its_parent", "right_is_left", "a_child_of_two_trees", "a_cycle",
+                                  "right_missing", "right_out_of_range", "token_out_of_range", "roots_in_another_order", "every_other_tree"])
+def test_pieces_that_are_none(what, order):
+    rng = np.random.default_rng(10)
+    l, r, t, roots = _in_pieces([_chain(40), _random(30, rng), _complete(4), _random(25, rng)], order, rng)
+    inner = [next(v for v in (l[x], r[x]) if l[v] >= 0) for x in roots]   # an inner node below each root
+    left, st = False, tdf.OK
+    if what in ("a_stranger_inside", "a_child_before_its_parent"):   # (another numbering of the same trees)
+        n = l.size
+        if what == "a_stranger_inside":   # a leaf that belongs to nobody, between two nodes of the first tree
+            a = min(roots[0], inner[0]) + 1
+            name = np.arange(n) + (np.arange(n) >= a)
+            size = n + 1
+        else:   # an inner node and the last of its subtree change places
+            name, size = np.arange(n), n
+            v = inner[1]
+            low = r[v] if l[r[v]] < 0 else l[v]
+            name[[v, low]] = name[[low, v]]
+        new = lambda x: np.where(x >= 0, name[np.maximum(x, 0)], -1)  # noqa: E731
+        l2, r2, t2 = np.full(size, -1), np.full(size, -1), np.zeros(size, np.int64)
+        l2[name], r2[name], t2[name] = new(l), new(r), t
+        l, r, t, roots = l2, r2, t2, name[roots]
+    elif what == "right_is_left":
+        r[inner[1]], left = l[inner[1]], True
+    elif what == "a_child_of_two_trees":
+        r[inner[1]], left = l[inner[3]], True
+    elif what == "a_cycle":
+        leaf = inner[0]
+        while l[leaf] >= 0:
+            leaf = r[leaf]
+        l[leaf], r[leaf], st = inner[0], inner[0], None
+    elif what == "right_missing":
+        r[inner[2]], st = -1, tdf.ERR_BAD_ARG
+    elif what == "right_out_of_range":
+        r[inner[2]], st = l.size, tdf.ERR_BAD_ARG
+    elif what == "token_out_of_range":
+        t[np.nonzero(l < 0)[0][7]], st = V, tdf.ERR_BAD_ARG
+    elif what == "roots_in_another_order":
+        roots = roots[[2, 0, 3, 1]]
+    else:
+        roots = roots[1::2]
+    got = _same(programs.tree("lstm", True), (l, r, t, roots), left=left, max_tags=4 * l.size)[0]
+    assert got == st if st is not None else got != tdf.OK
