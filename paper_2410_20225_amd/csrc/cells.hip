@@ -431,13 +431,19 @@ template <> struct Chunk<__bf16> {
   static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   }
-  // Bit patterns of an element that has not been written yet (below: announce), and whether a chunk holds one.
-  static constexpr unsigned short NONE = 0xFFFF;
-  static __device__ __forceinline__ bool waiting(u32x4 c) {
+  // Elements that have not been written yet hold the pattern 0xFFFF (below: announce): whether chunks hold one follows from the
+  // greatest elements of their words' halves.  (One instruction a word; the compiler, if it sees the comparison behind the
+  // maxima, compares every half.)
+  static __device__ __forceinline__ uint32_t greatest(uint32_t m, u32x4 c) {
     typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
-    const u16x2 m = __builtin_elementwise_max(__builtin_elementwise_max(__builtin_bit_cast(u16x2, c.x), __builtin_bit_cast(u16x2, c.y)),
-                                              __builtin_elementwise_max(__builtin_bit_cast(u16x2, c.z), __builtin_bit_cast(u16x2, c.w)));
-    return m.x == NONE || m.y == NONE;
+    const uint32_t x = c.x, y = c.y, z = c.z, w = c.w;   // (a bit cast of a vector's component itself is the first one's, whichever it names)
+    const u16x2 a = __builtin_elementwise_max(__builtin_bit_cast(u16x2, x), __builtin_bit_cast(u16x2, y));
+    const u16x2 b = __builtin_elementwise_max(__builtin_bit_cast(u16x2, z), __builtin_bit_cast(u16x2, w));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m), __builtin_elementwise_max(a, b)));
+  }
+  static __device__ __forceinline__ bool waiting(uint32_t m) {
+    asm("" : "+v"(m));
+    return ((0xFFFEFFFEu - m) & m & 0x80008000u) != 0;   // (a half of ~m is zero)
   }
 };
 template <> struct Chunk<float> {
@@ -451,8 +457,11 @@ template <> struct Chunk<float> {
     c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, y.w, c, 0, 0, 0);
     return c;
   }
-  static constexpr uint32_t NONE = 0xFFFFFFFFu;
-  static __device__ __forceinline__ bool waiting(u32x4 c) { return c.x == NONE || c.y == NONE || c.z == NONE || c.w == NONE; }
+  static __device__ __forceinline__ uint32_t greatest(uint32_t m, u32x4 c) { return max(max(max(m, c.x), c.y), max(c.z, c.w)); }
+  static __device__ __forceinline__ bool waiting(uint32_t m) {
+    asm("" : "+v"(m));
+    return m == 0xFFFFFFFFu;
+  }
 };
 
 // Operand order of a k-contiguous matrix [rows x K] for 16-row MFMA operands: the 16-byte chunks
@@ -488,11 +497,11 @@ struct FreshRows {
 __device__ __forceinline__ FreshRows fresh_rows(const void* base) {
   return FreshRows{reinterpret_cast<const char*>(base), __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, -1, 0x00027000)};
 }
-__device__ __forceinline__ u32x4 load_fresh16(const FreshRows& f, uint64_t offset, bool narrow) {
-  if (narrow) {
-    asm volatile("" ::: "memory");   // (looked at again and again)
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(f.rsrc, (int)offset, 0, 16));   // sc1: device scope
-  }
+__device__ __forceinline__ u32x4 load_fresh16(const FreshRows& f, uint32_t offset) {
+  asm volatile("" ::: "memory");   // (looked at again and again)
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(f.rsrc, (int)offset, 0, 16));   // sc1: device scope
+}
+__device__ __forceinline__ u32x4 load_fresh16_wide(const FreshRows& f, uint64_t offset) {
   const unsigned long long* q = reinterpret_cast<const unsigned long long*>(f.base + offset);
   const unsigned long long a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const unsigned long long b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -527,7 +536,7 @@ __device__ __forceinline__ int wave_of() { return __builtin_amdgcn_readfirstlane
 // What is the same for all tiles of a workgroup.
 struct TileLane {
   int wave, s0, n;      // the wave's chunk steps
-  uint32_t a;           // element of an operand row with which the lane's operands begin; chunk step st is st * KC further on
+  uint32_t a;           // element of an operand row with which the lane's loads begin; chunk step st is st * KC further on
   int row, col;         // the lane's element of a tile: row, and place among its columns
 };
 template <int DT, int MODE> __device__ __forceinline__ TileLane tile_lane(const GemmArgs& g) {
@@ -538,12 +547,28 @@ template <int DT, int MODE> __device__ __forceinline__ TileLane tile_lane(const 
   c.wave = wave_of();
   c.s0 = TL::first_step(steps, c.wave);
   c.n = TL::first_step(steps, c.wave + 1) - c.s0;
-  c.a = (uint32_t)((c.s0 - (MODE == DX_BWD || c.wave < TL::NW / 2 ? 0 : steps / 2)) * C::KC + (lane >> 4) * C::EPC);
+  c.a = (uint32_t)((c.s0 - (MODE == DX_BWD || c.wave < TL::NW / 2 ? 0 : steps / 2)) * C::KC + (lane & 3) * C::EPC);
   c.row = 4 * (lane >> 4) + (c.wave & 3);
   c.col = (TL::CB == 2 ? (c.wave >> 2) * 16 : 0) + (lane & 15);
   return c;
 }
 
+// Chunk steps that every wave has where the wave that has most takes the variant with RES of them (they differ by one).
+__host__ __device__ constexpr int least_steps(int res) { return res == 4 ? 2 : res == 8 ? 4 : res == 10 ? 5 : 0; }
+// Rows of operands are loaded with four lanes side by side on the 64 bytes of a row that belong to a chunk step (lane l: row
+// l / 4, chunk l % 4), and turned into operand order (row l % 16, chunk l / 16) through a wave's own kilobyte of LDS.  In
+// operand order each lane's 16 bytes are a request of their own, which the L1 passes on at one a clock: 64 a load
+// instead of 16, and a tile of 16 rows of 2 KB is 2,048 clocks of them.  (LDS operations of a wave keep their order: the next
+// step's chunks are written behind this one's reads without a wait.  Eight lanes that are served together fall into different banks.)
+constexpr int TURN = 64;   // 16-byte units a wave
+__device__ __forceinline__ u32x4 turn(u32x4* w, u32x4 x) {
+  const int lane = threadIdx.x & 63;
+  w[(lane & 3) * 16 + ((lane >> 2) ^ ((lane & 3) * 2))] = x;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const u32x4 y = w[(lane >> 4) * 16 + ((lane & 15) ^ ((lane >> 4) * 2))];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return y;
+}
 // Weight operands of a wave for one column tile: RES chunk steps.  The tail kernels keep them in registers across
 // tiles (a workgroup there always works on the same column tile).
 template <int MODE, int RES> struct TileB {
@@ -583,29 +608,22 @@ struct DzFuse {
 struct TileAt {
   uint32_t q0;
   int M, ct;
-  uint32_t lvl;   // of the walk
 };
 // What a tile reads that no tile writes, in the steps that follow one another: rows of the children (TileRows, to which
 // the fused dz adds the rows of the children's children), and what these lead to (TileAhead): operands of children that
 // are complete before the launch, and for the fused dz (CELL: the cell kind, 0: none) the forward state of the child
 // cells.  Most of it comes from HBM.  The tail kernels request it one to three tiles ahead.
 template <int MODE> struct TileRows {
-  uint32_t child;                   // operand row of this lane (forward)
+  uint32_t child;                   // operand row of which this lane loads a part (forward)
   uint32_t o_l, o_r;                // children of the lane's element
   uint32_t z_q, z_gl, z_gr;         // fused dz: the child cell (none: all ones) and its children's rows
 };
-// LOOK: a tile that is not its workgroup's first of a level reads rows that are likely there already: the tile before looks
-// for them while it sums and finishes.  Gradient tails of a TreeLSTM (127 levels of up to 80 cells a die beside the level
-// launches 1,635 -> 1,306 us); the forward ones, whose workgroups share a compute unit, gain nothing (827 us either way).
-template <int MODE, int RES, int CELL> struct TileAhead {
-  static constexpr bool LOOK = CELL == 2 && RES == 5;
-  u32x4 look[LOOK ? RES : 1];
-  uint32_t u0, u1;
-  bool looked;   // (uniform)
+template <typename T, int MODE, int RES, int CELL> struct TileAhead {
   u32x4 a[RES > 0 && MODE != DX_BWD ? RES : 1];   // the lane's operands, if its child is complete
   float bias[Tile<MODE>::G];   // (RES == 0)
   float c_l, c_r;                             // cell states of complete children (TreeLSTM)
-  float z_gate[5], z_c, z_h, z_own, z_cl, z_cr;
+  T z_gate[5], z_h;   // (as they are loaded: a conversion here would wait for them)
+  float z_c, z_own, z_cl, z_cr;
 };
 // (element offsets of state rows are 32 bits wide: the host checks)
 template <int MODE>
@@ -613,14 +631,11 @@ __device__ __forceinline__ void tile_rows(const GemmArgs& g, const TileLane& c, 
   const int lane = threadIdx.x & 63;
   const uint32_t* const l = g.l + t.q0;
   const uint32_t* const r = g.r + t.q0;
-  if constexpr (MODE != DX_BWD) {
-    p.child = 0;
-    if ((lane & 15) < t.M) p.child = (c.wave < Tile<MODE>::NW / 2 ? l : r)[lane & 15];
-  }
-  p.o_l = p.o_r = 0;
-  if (c.row < t.M) {
-    p.o_l = l[c.row];
-    p.o_r = r[c.row];
+  const int last = max(t.M - 1, 0), row = min(c.row, last);   // (no branches: rows that the tile has not read its last one; no tile: cell 0)
+  if constexpr (MODE != DX_BWD) p.child = (c.wave < Tile<MODE>::NW / 2 ? l : r)[min(lane >> 2, last)];
+  if constexpr (MODE != RNN_FWD) {
+    p.o_l = l[row];
+    p.o_r = r[row];
   }
 }
 template <int DT, int MODE, int CELL>
@@ -631,17 +646,15 @@ __device__ __forceinline__ void tile_rows2(const GemmArgs& g, const TileLane& c,
     const bool ok = c.row < t.M && row >= fz->row0 && row - fz->row0 >= fz->q_first;   // a cell of the tail (a leaf has no dz)
     p.z_q = ok ? row - fz->row0 : 0xFFFFFFFFu;
     if constexpr (CELL == 2) {
-      p.z_gl = p.z_gr = 0;
-      if (ok) {
-        p.z_gl = fz->q_l[p.z_q];
-        p.z_gr = fz->q_r[p.z_q];
-      }
+      const uint32_t z = ok ? p.z_q : 0u;
+      p.z_gl = fz->q_l[z];
+      p.z_gr = fz->q_r[z];
     }
   }
 }
 template <int DT, int MODE, int RES, int CELL>
 __device__ __forceinline__ void tile_ahead(const GemmArgs& g, const TileLane& c, const TileAt& t, const DzFuse* fz, const TileRows<MODE>& p,
-                                           TileAhead<MODE, RES, CELL>& q) {
+                                           TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& q) {
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   const int lane = threadIdx.x & 63;
@@ -651,20 +664,18 @@ __device__ __forceinline__ void tile_ahead(const GemmArgs& g, const TileLane& c,
 #pragma unroll
       for (int j = 0; j < Tile<MODE>::G; ++j) q.bias[j] = g.bias[j * g.Hp + unit];
     } else {
-      const bool ready = (lane & 15) < t.M && p.child < g.fresh_row;
-      const T* ap = reinterpret_cast<const T*>(g.Hs) + (p.child * (uint32_t)g.Hp + c.a);
+      if (p.child < g.fresh_row) {   // (a row that the tile has not is read for nothing: it is no other row's operand)
+        const T* ap = reinterpret_cast<const T*>(g.Hs) + (p.child * (uint32_t)g.Hp + c.a);
 #pragma unroll
-      for (int st = 0; st < RES; ++st) {
-        q.a[st] = u32x4{0u, 0u, 0u, 0u};
-        if (ready && st < c.n) q.a[st] = *reinterpret_cast<const u32x4*>(ap + st * C::KC);
+        for (int st = 0; st < RES; ++st)
+          if (st < least_steps(RES) || st < c.n) q.a[st] = *reinterpret_cast<const u32x4*>(ap + st * C::KC);
       }
     }
-    if constexpr (MODE == LSTM_FWD) {   // (a leaf has no stored cell state: zero)
-      q.c_l = q.c_r = 0.f;
-      if (c.row < t.M) {
-        if (p.o_l >= g.leaf_rows && p.o_l < g.fresh_row) q.c_l = g.Cs[p.o_l * (uint32_t)g.Hp + (uint32_t)unit];
-        if (p.o_r >= g.leaf_rows && p.o_r < g.fresh_row) q.c_r = g.Cs[p.o_r * (uint32_t)g.Hp + (uint32_t)unit];
-      }
+    if constexpr (MODE == LSTM_FWD) {   // (a leaf has no stored cell state: row 0, a leaf's, is kept zero)
+      const uint32_t r_l = p.o_l >= g.leaf_rows && p.o_l < g.fresh_row ? p.o_l : 0u;
+      const uint32_t r_r = p.o_r >= g.leaf_rows && p.o_r < g.fresh_row ? p.o_r : 0u;
+      q.c_l = g.Cs[r_l * (uint32_t)g.Hp + (uint32_t)unit];
+      q.c_r = g.Cs[r_r * (uint32_t)g.Hp + (uint32_t)unit];
     }
   }
   if constexpr (CELL != 0) {
@@ -674,14 +685,14 @@ __device__ __forceinline__ void tile_ahead(const GemmArgs& g, const TileLane& c,
       const uint32_t o = (fz->row0 + p.z_q) * (uint32_t)g.Hp + n;
       q.z_own = v.dHn ? v.dHn[o] : 0.f;   // gradient of the child's own loss term
       if constexpr (CELL == 1) {
-        q.z_h = to_f(reinterpret_cast<const T*>(v.Hs)[o]);
+        q.z_h = reinterpret_cast<const T*>(v.Hs)[o];
       } else {
         const T* g5 = reinterpret_cast<const T*>(v.gates) + ((uint64_t)p.z_q * (uint32_t)v.Np + n);
 #pragma unroll
-        for (int k = 0; k < 5; ++k) q.z_gate[k] = to_f(g5[k * g.Hp]);
+        for (int k = 0; k < 5; ++k) q.z_gate[k] = g5[k * g.Hp];
         q.z_c = v.Cs[o];
-        q.z_cl = p.z_gl >= fz->row0 ? v.Cs[p.z_gl * (uint32_t)g.Hp + n] : 0.f;   // (a leaf's cell state is zero)
-        q.z_cr = p.z_gr >= fz->row0 ? v.Cs[p.z_gr * (uint32_t)g.Hp + n] : 0.f;
+        q.z_cl = v.Cs[(p.z_gl >= fz->row0 ? p.z_gl : 0u) * (uint32_t)g.Hp + n];   // (a leaf's cell state is zero, like row 0)
+        q.z_cr = v.Cs[(p.z_gr >= fz->row0 ? p.z_gr : 0u) * (uint32_t)g.Hp + n];
       }
     }
   }
@@ -700,12 +711,12 @@ __device__ __forceinline__ TileWaits<typename TypeOf<DT>::type, MODE> tile_waits
                                                                                  const TileRows<MODE>& p, const DzFuse* fz) {
   typedef typename TypeOf<DT>::type T;
   const int lane = threadIdx.x & 63;
-  const bool valid = (lane & 15) < t.M, el = c.row < t.M;
+  const bool valid = (lane >> 2) < t.M, el = c.row < t.M;
   const int unit = t.ct * Tile<MODE>::UNITS + c.col;
   TileWaits<T, MODE> r{};
   if constexpr (MODE == DX_BWD) {   // (a tile of the gradient tail: all its rows)
     r.rows = fresh_rows(reinterpret_cast<const T*>(g.A) + (uint64_t)t.q0 * (uint32_t)g.lda);
-    r.off = ((uint32_t)(lane & 15) * (uint32_t)g.lda + c.a) * (uint32_t)sizeof(T);
+    r.off = ((uint32_t)(lane >> 2) * (uint32_t)g.lda + c.a) * (uint32_t)sizeof(T);
     r.fresh = valid;
   } else {
     r.rows = fresh_rows(reinterpret_cast<const T*>(g.Hs) + g.fresh_row * (uint32_t)g.Hp);
@@ -724,24 +735,32 @@ __device__ __forceinline__ TileWaits<typename TypeOf<DT>::type, MODE> tile_waits
   }
   return r;
 }
-template <int DT, int MODE, int RES, int CELL>
-__device__ __forceinline__ void tile_look(const GemmArgs& g, const TileLane& c, const TileAt& t, const TileRows<MODE>& p, const DzFuse* fz,
-                                          TileAhead<MODE, RES, CELL>& q) {
-  typedef typename TypeOf<DT>::type T;
-  typedef Chunk<T> C;
-  if constexpr (TileAhead<MODE, RES, CELL>::LOOK) {
-    const auto w = tile_waits<DT, MODE, CELL>(g, c, t, p, fz);
+// One look at a tile's rows, by the lanes with `fresh` (f0, f1): n chunk steps from st0 on.
+template <typename T, int MODE, int N>
+__device__ __forceinline__ void look_rows(const TileWaits<T, MODE>& w, bool narrow, int st0, int n, bool fresh, bool f0, bool f1, u32x4 (&a)[N], uint32_t& u0,
+                                          uint32_t& u1) {
+  constexpr uint32_t step = Chunk<T>::KC * sizeof(T);
+  if (fresh) {
+    if (narrow) {
 #pragma unroll
-    for (int st = 0; st < RES; ++st) {
-      q.look[st] = u32x4{0u, 0u, 0u, 0u};
-      if (w.fresh && st < c.n) q.look[st] = load_fresh16(w.rows, w.off + (uint32_t)(st * C::KC * (int)sizeof(T)), MODE == DX_BWD || g.fresh_narrow);
+      for (int st = 0; st < N; ++st)
+        if (st < least_steps(N) || st < n) a[st] = load_fresh16(w.rows, (uint32_t)w.off + (uint32_t)(st0 + st) * step);
+    } else {
+#pragma unroll
+      for (int st = 0; st < N; ++st)
+        if (st < least_steps(N) || st < n) a[st] = load_fresh16_wide(w.rows, w.off + (uint32_t)(st0 + st) * step);
     }
-    q.u0 = q.u1 = 0;
-    if (w.f0) q.u0 = load_fresh(w.w0);
-    if (MODE == LSTM_FWD && w.f1) q.u1 = load_fresh(w.w1);
   }
+  if (f0) u0 = load_fresh(w.w0);   // (written right behind the rows)
+  if (MODE == LSTM_FWD && f1) u1 = load_fresh(w.w1);
 }
-
+template <typename T, int N> __device__ __forceinline__ bool rows_waiting(const u32x4 (&a)[N], int n) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int st = 0; st < N; ++st)
+    if (st < least_steps(N) || st < n) m = Chunk<T>::greatest(m, a[st]);
+  return Chunk<T>::waiting(m);
+}
 // Waiting for rows of other workgroups: `attempt` looks again (true: this lane has what it needs) until all lanes of the
 // wave have.  False: no workgroup of the die has got anywhere for spin_ticks, or another one has given up.
 struct TailWait {
@@ -774,26 +793,29 @@ template <class F> __device__ __forceinline__ bool wait_rows(const TailWait& w, 
 // again has passed the barrier of the tile between, which all waves reach after they have read it.
 // RES > 0: the weight operands are in `b` (all chunk steps of this wave); 0: they are fetched here.
 // WAIT: rows from g.fresh_row on (forward: children, gradient: the tile's own dz and the children's dc) are written by
-// this launch and waited for.  `advance` finds the workgroup's next tile and `request` asks for what later tiles need: the
-// former in the products' shadow, when all that was asked for before has come, the latter behind the tile's stores.
-// failed: a flag in LDS, two of them in turn like `part`; false is returned if it is set.
-template <int DT, int MODE, int RES, int CELL, bool WAIT, class Advance, class Request>
-__device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLane& c, const TileAt& t, float* part, const TileRows<MODE>& p,
-                                                const TileAhead<MODE, RES, CELL>& q, const float (&bias)[Tile<MODE>::G],
+// this launch and waited for.  `request` finds a later tile and asks for what later tiles need, behind the tile's stores, which are on
+// their way to the other workgroups meanwhile.
+// failed: a flag in LDS, two of them in turn like `part`; false is returned if it is set (the launch's results are void then).
+// From the tile's stores to the next tile's first look there is no wait for anything: row numbers are two looks old, and
+// each look is waited for with all that was asked for before it.  (The compiler has to see that: branches are uniform or around
+// loads alone.)
+template <int DT, int MODE, int RES, int CELL, bool WAIT, bool NARROW, class Request>
+__device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLane& c, const TileAt& t, float* part, u32x4* turns, const TileRows<MODE>& p,
+                                                TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& q, const float (&bias)[Tile<MODE>::G],
                                                 const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, const TailWait& w, uint32_t* failed,
-                                                Advance advance, Request request) {
+                                                Request request) {
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   typedef Tile<MODE> TL;
-  constexpr int BATCH = RES > 0 ? RES : 4;   // chunk steps in flight
+  constexpr int BATCH = RES > 0 ? RES : 3;   // chunk steps in flight (not 4: least_steps)
   const int lane = threadIdx.x & 63, n = c.n, s0 = c.s0, wave = c.wave;
-  const bool valid = (lane & 15) < t.M;
+  const bool valid = (lane >> 2) < t.M;
   const T* Ap;
-  if constexpr (MODE == DX_BWD) Ap = reinterpret_cast<const T*>(g.A) + ((uint64_t)(t.q0 + (uint32_t)(lane & 15)) * (uint32_t)g.lda + c.a);
+  if constexpr (MODE == DX_BWD) Ap = reinterpret_cast<const T*>(g.A) + ((uint64_t)(t.q0 + (uint32_t)(lane >> 2)) * (uint32_t)g.lda + c.a);
   else Ap = reinterpret_cast<const T*>(g.Hs) + (p.child * (uint32_t)g.Hp + c.a);
   TileWaits<T, MODE> tw{};
   if constexpr (WAIT) tw = tile_waits<DT, MODE, CELL>(g, c, t, p, fz);
-  const bool narrow = MODE == DX_BWD || g.fresh_narrow, fresh = tw.fresh;
+  const bool narrow = MODE == DX_BWD || NARROW || g.fresh_narrow, fresh = tw.fresh;
   const int unit = t.ct * TL::UNITS + c.col;
   const bool el = c.row < t.M;   // the lane's element exists
   const bool z_left = unit < g.Hp;
@@ -804,86 +826,69 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
   f32x4 acc[TL::NB];
 #pragma unroll
   for (int j = 0; j < TL::NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  u32x4 fa[BATCH];
-  auto load_a = [&](int st0, int cnt) {   // steps st0 .. of this wave
-    if constexpr (!WAIT) {
-#pragma unroll
-      for (int st = 0; st < BATCH; ++st) {
-        fa[st] = u32x4{0u, 0u, 0u, 0u};
-        if (valid && st < cnt) fa[st] = *reinterpret_cast<const u32x4*>(Ap + (st0 + st) * C::KC);
-      }
-    } else {
-      bool open[BATCH];
-#pragma unroll
-      for (int st = 0; st < BATCH; ++st) {
-        open[st] = fresh && st < cnt;
-        fa[st] = u32x4{0u, 0u, 0u, 0u};
-        if (MODE != DX_BWD && RES == 0)
-          if (valid && !fresh && st < cnt) fa[st] = *reinterpret_cast<const u32x4*>(Ap + (st0 + st) * C::KC);
-      }
-      bool o0 = f0 && st0 == 0, o1 = f1 && st0 == 0;
+  auto await = [&](u32x4 (&fa)[BATCH], int st0, int cnt) {   // steps st0 .. of this wave
+    if constexpr (WAIT) {
+      bool open = fresh, o0 = f0 && st0 == 0, o1 = f1 && st0 == 0;
       auto still_open = [&] {
-        bool any = false;
-#pragma unroll
-        for (int st = 0; st < BATCH; ++st) {
-          open[st] = open[st] && C::waiting(fa[st]);
-          any = any || open[st];
-        }
+        open = open && rows_waiting<T>(fa, cnt);
         o0 = o0 && u0 == F_NONE;
         o1 = o1 && u1 == F_NONE;
-        return any || o0 || o1;
+        return open || o0 || o1;
       };
-      bool there = false;
-      if constexpr (TileAhead<MODE, RES, CELL>::LOOK) {
-        if (q.looked) {
-#pragma unroll
-          for (int st = 0; st < BATCH; ++st) fa[st] = q.look[st];
-          u0 = q.u0;
-          u1 = q.u1;
-          there = !__any(still_open());
-        }
-      }
-      const bool ok = there || wait_rows(w, [&] {
-#pragma unroll
-        for (int st = 0; st < BATCH; ++st)
-          if (open[st]) fa[st] = load_fresh16(tw.rows, tw.off + (uint32_t)((st0 + st) * C::KC * (int)sizeof(T)), narrow);
-        if (MODE == LSTM_FWD || CELL == 2) {   // (written right behind the rows)
-          if (o0) u0 = load_fresh(tw.w0);
-          if (MODE == LSTM_FWD && o1) u1 = load_fresh(tw.w1);
-        }
+      auto attempt = [&] {
+        look_rows(tw, narrow, st0, cnt, open, o0, o1, fa, u0, u1);
         return !still_open();
-      });
-      if (!ok) *failed = 1u;
+      };
+      if (__builtin_expect(!__all(attempt()), 0))
+        if (!wait_rows(w, attempt)) *failed = 1u;
       // (Whatever was requested is here by now.  Said in so many words, or the compiler, which does not know that on the way
       // past the loads above, waits for the tile's stores before the next tile's first look.)
       __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-      if constexpr (RES > 0 && MODE != DX_BWD) {
-#pragma unroll
-        for (int st = 0; st < BATCH; ++st) fa[st] = fresh ? fa[st] : q.a[st];
-      }
     }
   };
   if constexpr (RES > 0) {
-    load_a(0, n);
-  }
-  if constexpr (RES > 0) {
+    // (Forward, NARROW: the look's lanes join those whose rows were there before, in the same registers.)
+    u32x4 fw[RES];
+    constexpr bool JOIN = MODE != DX_BWD && NARROW;
+    u32x4 (&fa)[RES] = [&]() -> u32x4 (&)[RES] { if constexpr (JOIN) return q.a; else return fw; }();
+    await(fa, 0, n);
 #pragma unroll
     for (int st = 0; st < RES; ++st)
+      if (st < least_steps(RES) || st < n) {
+        if constexpr (MODE != DX_BWD && !JOIN) fa[st] = fresh ? fa[st] : q.a[st];
+        fa[st] = turn(turns + wave * TURN, fa[st]);
+      }
 #pragma unroll
-      for (int j = 0; j < TL::NB; ++j) acc[j] = C::mma(fa[st], b->f[st][j], acc[j]);
+    for (int st = 0; st < RES; ++st)
+      if (st < least_steps(RES) || st < n) {
+#pragma unroll
+        for (int j = 0; j < TL::NB; ++j) acc[j] = C::mma(fa[st], b->f[st][j], acc[j]);
+      }
   } else {
     for (int st0 = 0; st0 < n; st0 += BATCH) {
       TileB<MODE, BATCH> fb;
+      u32x4 fa[BATCH];
       const int cnt = min(BATCH, n - st0);
       load_b<DT, MODE, BATCH>(g, t.ct, s0 + st0, cnt, fb);
-      load_a(st0, cnt);
+      if (MODE != DX_BWD || !WAIT) {
+#pragma unroll
+        for (int st = 0; st < BATCH; ++st) {
+          fa[st] = u32x4{0u, 0u, 0u, 0u};
+          if (valid && !fresh && st < cnt) fa[st] = *reinterpret_cast<const u32x4*>(Ap + (st0 + st) * C::KC);
+        }
+      }
+      await(fa, st0, cnt);
 #pragma unroll
       for (int st = 0; st < BATCH; ++st)
+        if (st < cnt) fa[st] = turn(turns + wave * TURN, fa[st]);
 #pragma unroll
-        for (int j = 0; j < TL::NB; ++j) acc[j] = C::mma(fa[st], fb.f[st][j], acc[j]);
+      for (int st = 0; st < BATCH; ++st)
+        if (st < cnt) {
+#pragma unroll
+          for (int j = 0; j < TL::NB; ++j) acc[j] = C::mma(fa[st], fb.f[st][j], acc[j]);
+        }
     }
   }
-  advance();
   // partial tiles -> LDS; every lane sums and finishes its element
 #pragma unroll
   for (int j = 0; j < TL::NB; ++j)
@@ -900,13 +905,9 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
     for (int wv = 0; wv < TL::NW; ++wv) s += part[((wv * TL::NB + (TL::CB == 2 ? wave >> 2 : j)) * 4 + (wave & 3)) * 64 + lane];
     z[j] = s;
   }
-  if constexpr (WAIT) {
-    if (__builtin_expect(stop != 0, 0)) return false;
-  }
   if (!el) {
   } else if constexpr (MODE != DX_BWD) {
     const uint32_t o = (g.out0 + t.q0 + (uint32_t)c.row) * (uint32_t)g.Hp + (uint32_t)unit;
-    T* const dz = g.dz_fill ? reinterpret_cast<T*>(g.dz_fill) : nullptr;
     if constexpr (MODE == LSTM_FWD) {
       const float cl = f0 ? __builtin_bit_cast(float, u0) : q.c_l, cr = f1 ? __builtin_bit_cast(float, u1) : q.c_r;
       const float gi = Act<T>::sigmoid_b(z[0], Act<T>::pre_sigmoid(bias[0]));
@@ -928,20 +929,6 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
     } else {
       reinterpret_cast<T*>(g.Hs_out)[o] = announce(from_f<T>(Act<T>::tanh(z[0] + bias[0])));
     }
-    if constexpr (WAIT) {
-      // A gradient run: dz (and dc) of the children that the gradient tail will write are still to be written.
-      if (dz) {
-#pragma unroll
-        for (int side = 0; side < 2; ++side) {
-          const uint32_t child = side ? p.o_r : p.o_l;
-          if (child >= g.fresh_row) {
-#pragma unroll
-            for (int k = 0; k < TL::G; ++k) dz[(uint64_t)(child - g.out0) * (uint32_t)g.ldg + (uint32_t)(k * g.Hp + unit)] = not_written<T>();
-            if (MODE == LSTM_FWD) g.dc_fill[child * (uint32_t)g.Hp + (uint32_t)unit] = not_written<float>();
-          }
-        }
-      }
-    }
   } else {   // DX_BWD: column `unit` of [dh_l; dh_r]; each child row has exactly one consumer.
     const uint32_t child = z_left ? p.o_l : p.o_r;
     // (dh of a child whose dz is formed here has no other reader)
@@ -952,9 +939,10 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
       const float dh = z[0] + q.z_own;
       T* dz = reinterpret_cast<T*>(v.Dz) + ((uint64_t)p.z_q * (uint32_t)v.Np + z_n);
       if constexpr (CELL == 1) {
-        dz[0] = announce(from_f<T>(dh * (1.f - q.z_h * q.z_h)));
+        const float h = to_f(q.z_h);
+        dz[0] = announce(from_f<T>(dh * (1.f - h * h)));
       } else {
-        const float gi = q.z_gate[0], gfl = q.z_gate[1], gfr = q.z_gate[2], go = q.z_gate[3], gu = q.z_gate[4];
+        const float gi = to_f(q.z_gate[0]), gfl = to_f(q.z_gate[1]), gfr = to_f(q.z_gate[2]), go = to_f(q.z_gate[3]), gu = to_f(q.z_gate[4]);
         const float tc = Act<T>::tanh(q.z_c);
         const float dc = __builtin_bit_cast(float, u0) + dh * go * (1.f - tc * tc);
         dz[0] = announce(from_f<T>(dc * gu * gi * (1.f - gi)));
@@ -969,22 +957,36 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
       if (z_n == 0) __hip_atomic_fetch_add(&v.gmark[child], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   }
+  if constexpr (WAIT && MODE != DX_BWD) {
+    // A gradient run: dz (and dc) of the children that the gradient tail will write are still to be written.  The first wave with
+    // left children and the first with right ones mark the tile's columns of them, 16 bytes a lane.
+    if (g.dz_fill && (wave == 0 || wave == TL::NW / 2) && fresh) {
+      const u32x4 none = {F_NONE, F_NONE, F_NONE, F_NONE};
+      constexpr int CH = 16 / (int)sizeof(T);
+      T* const dz = reinterpret_cast<T*>(g.dz_fill) + ((uint64_t)(p.child - g.out0) * (uint32_t)g.ldg + (uint32_t)(t.ct * TL::UNITS));
+#pragma unroll
+      for (int k = 0; k < TL::G; ++k)
+        for (int c = (lane & 3) * CH; c < TL::UNITS; c += 4 * CH) *reinterpret_cast<u32x4*>(dz + k * g.Hp + c) = none;
+      if (MODE == LSTM_FWD) *reinterpret_cast<u32x4*>(g.dc_fill + (p.child * (uint32_t)g.Hp + (uint32_t)(t.ct * TL::UNITS + (lane & 3) * 4))) = none;
+    }
+  }
   request();
-  return true;
+  return __builtin_amdgcn_readfirstlane((int)stop) == 0;
 }
 
 template <int DT, int MODE>
 __global__ void __launch_bounds__(Tile<MODE>::NW * 64) k_cell_small(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) float part[Tile<MODE>::PART];
+  __shared__ u32x4 turns[Tile<MODE>::NW * TURN];
   stamp_now(g.stamp);
   const int rt = blockIdx.x / g.n_tiles_n, ct = blockIdx.x % g.n_tiles_n;   // (column tiles of one row tile side by side)
-  const TileAt t{(uint32_t)rt * Tile<MODE>::ROWS, min(Tile<MODE>::ROWS, g.M - rt * Tile<MODE>::ROWS), ct, 0};
+  const TileAt t{(uint32_t)rt * Tile<MODE>::ROWS, min(Tile<MODE>::ROWS, g.M - rt * Tile<MODE>::ROWS), ct};
   TileRows<MODE> p;
-  TileAhead<MODE, 0, 0> q;
+  TileAhead<typename TypeOf<DT>::type, MODE, 0, 0> q;
   const TileLane c = tile_lane<DT, MODE>(g);
   tile_rows<MODE>(g, c, t, p);
   tile_ahead<DT, MODE, 0, 0>(g, c, t, nullptr, p, q);
-  cell_small_tile<DT, MODE, 0, 0, false>(g, c, t, part, p, q, q.bias, (const TileB<MODE, 1>*)nullptr, nullptr, TailWait{}, nullptr, [] {}, [] {});
+  cell_small_tile<DT, MODE, 0, 0, false, false>(g, c, t, part, turns, p, q, q.bias, (const TileB<MODE, 1>*)nullptr, nullptr, TailWait{}, nullptr, [] {});
 }
 
 // Levels of at most this many cells take the small-level kernel where they are launched one by one (TDF_SMALL_LEVEL overrides).
@@ -1339,14 +1341,18 @@ struct TailArgs {
 
 // The walk of one workgroup, number `rank` of the G of its die: forward from lvl_first up, DX_BWD from lvl_last down.
 // RES > 0: it keeps to one column tile (G is a multiple of the column tiles) with that tile's weight operands in registers.
-// What bounds it: latency.  A level is the way of the rows that the level before has written to the L2 and back (about 1000
-// clocks until a look that finds them has returned), the products of a fraction of the reduction (100), their sum through
-// LDS (400), the gates and stores (600 to 800) and the requests for what comes (500 to 1000): 1.6 to 2.4 us.  Everything
-// else is requested ahead, in the order of the workgroup's tiles, whatever levels these are in.
-// With a barrier of the die's workgroups between the levels and tiles of 32 x 32: 4,095 levels of a TreeRNN of 512 units
-// 11.4 ms forward and 15.0 gradient, now 7.2 and 6.4; 112 levels of a TreeLSTM of 256 units 576 us, now 361.
-template <int DT, int MODE, int RES, int CELL>
-__device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& ta, uint32_t die, uint32_t rank, uint32_t G, float* part,
+// What bounds it: latency.  Clocks of a level of a TreeRNN of 512 units, eight chains a die: 800 until a look that finds the rows has
+// returned (the way of a row through the L2 is 600, half of it the store's), 600 for turning the operands and the products, 250 for
+// their sum through LDS, 550 for gates and stores, 550 for the next requests, 400 for the rows to look at.  Everything else is requested
+// ahead, in the order of the workgroup's tiles, whatever levels these are in.  No memory beyond the registers (scratch): these
+// workgroups have to be resident together, which a launch that waits for its scratch may not be.
+// 4,095 levels of a TreeRNN of 512 units, ms forward and gradient: with a barrier of the die's workgroups between the levels and tiles
+// of 32 x 32 11.4 and 15.0; rows that announce themselves 7.4 and 6.5; the rows to be written brought to the L2 by the workgroup
+// that goes ahead 6.5 and 6.4; no wait between a tile's stores and the next look 6.2 and 6.4; rows loaded 64 bytes at a time 5.4
+// and 6.0; no conversions of what was just requested 5.4 and 5.3; the marks of dz in 16-byte stores 5.2 and 5.0.  127 levels of a TreeLSTM of
+// 256 units beside the level launches: 0.94 and 1.40, now 0.75 and 1.25.
+template <int DT, int MODE, int RES, int CELL, bool NARROW>
+__device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& ta, uint32_t die, uint32_t rank, uint32_t G, float* part, u32x4* turns,
                                             const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, uint32_t* failed) {
   typedef Tile<MODE> TL;
   DieSync* const sy = ta.sync + die;
@@ -1371,12 +1377,12 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
     const uint32_t rows = (end - q0 + TL::ROWS - 1) / TL::ROWS, row = RES > 0 ? t : t / n_ct;
     if (row >= rows) return false;
     const uint32_t at = q0 + row * TL::ROWS;
-    r = TileAt{at, (int)min((uint32_t)TL::ROWS, end - at), (int)(RES > 0 ? rank % n_ct : t % n_ct), k};
+    r = TileAt{at, (int)min((uint32_t)TL::ROWS, end - at), (int)(RES > 0 ? rank % n_ct : t % n_ct)};
     t += step;
     return true;
   };
   auto next = [&]() -> TileAt {
-    TileAt r{0, 0, 0, 0};
+    TileAt r{0, 0, 0};
     if (tile_of(r) || k + 1 >= n_lvl) return r;
     take(next_q0, next_end);
     for (++k, t = first; !tile_of(r) && k + 1 < n_lvl; t = first) {   // (levels without a tile for this workgroup)
@@ -1405,40 +1411,39 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
   TileAt t2 = next(), t3;
   offsets(k + 1, next_q0, next_end);
   TileRows<MODE> p0{}, p1{}, p2{}, p3{};
-  TileAhead<MODE, RES, CELL> a0{}, a1{};
+  TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL> a0{}, a1{};
   tile_rows<MODE>(g, c, t0, p0);
   tile_rows<MODE>(g, c, t1, p1);
   tile_rows<MODE>(g, c, t2, p2);
   tile_rows2<DT, MODE, CELL>(g, c, t0, fz, p0);
   tile_rows2<DT, MODE, CELL>(g, c, t1, fz, p1);
-  if (t0.M) tile_ahead<DT, MODE, RES, CELL>(g, c, t0, fz, p0, a0);
+  tile_ahead<DT, MODE, RES, CELL>(g, c, t0, fz, p0, a0);
   // A tile, and behind its own loads the requests for the next one, the rows of the children's children for the one after
   // that and the rows of a third.  The registers that these go to take turns by name: a copy from tile to tile would wait
   // for them in the middle of the tile that has just asked.
-  auto tile = [&](uint32_t side, const TileAt& t, const TileRows<MODE>& p, const TileAhead<MODE, RES, CELL>& a, const TileAt& ta1,
-                  const TileRows<MODE>& pa1, TileAhead<MODE, RES, CELL>& a1, const TileAt& ta2, TileRows<MODE>& pa2, TileAt& ta3,
+  auto tile = [&](uint32_t side, const TileAt& t, const TileRows<MODE>& p, TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& a, const TileAt& ta1,
+                  const TileRows<MODE>& pa1, TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& a1, const TileAt& ta2, TileRows<MODE>& pa2, TileAt& ta3,
                   TileRows<MODE>& pa3) __attribute__((always_inline)) {
-    return t.M && cell_small_tile<DT, MODE, RES, CELL, true>(g, c, t, part + side * TL::PART, p, a, RES > 0 ? bias : a.bias, b, fz, w, failed + side, [&] {
+    // (The end of the program, not a way out of the loop: the compiler joins such ways, with copies and waits where they meet.)
+    if (!t.M) __builtin_amdgcn_endpgm();
+    const bool ok = cell_small_tile<DT, MODE, RES, CELL, true, NARROW>(g, c, t, part + side * TL::PART, turns, p, a, RES > 0 ? bias : a.bias, b, fz, w, failed + side, [&] {
       ta3 = next();
-      if constexpr (TileAhead<MODE, RES, CELL>::LOOK) {
-        a1.looked = ta1.M && ta1.lvl == t.lvl;
-        if (a1.looked) tile_look<DT, MODE, RES, CELL>(g, c, ta1, pa1, fz, a1);
-      }
-    }, [&] {
       tile_rows<MODE>(g, c, ta3, pa3);
       tile_rows2<DT, MODE, CELL>(g, c, ta2, fz, pa2);
-      if (ta1.M) tile_ahead<DT, MODE, RES, CELL>(g, c, ta1, fz, pa1, a1);
+      tile_ahead<DT, MODE, RES, CELL>(g, c, ta1, fz, pa1, a1);   // (no tile: the rows of cell 0)
       offsets(k + 1, next_q0, next_end);
       if (rank == 0 && threadIdx.x == 0) __hip_atomic_store(&sy->at, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     });
+    if (!ok) __builtin_amdgcn_endpgm();
   };
   // (On a die without a cell in these levels that is the last one, and nobody waits for tiles there.)
   if (rank == 0 && threadIdx.x == 0) __hip_atomic_store(&sy->at, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // (vmcnt(0): so that no tile has to wait for what is asked for here)
   for (uint32_t n = 0;; ++n) {
-    if (!tile(0, t0, p0, a0, t1, p1, a1, t2, p2, t3, p3)) return;
-    if (!tile(1, t1, p1, a1, t2, p2, a0, t3, p3, t0, p0)) return;
-    if (!tile(0, t2, p2, a0, t3, p3, a1, t0, p0, t1, p1)) return;
-    if (!tile(1, t3, p3, a1, t0, p0, a0, t1, p1, t2, p2)) return;
+    tile(0, t0, p0, a0, t1, p1, a1, t2, p2, t3, p3);
+    tile(1, t1, p1, a1, t2, p2, a0, t3, p3, t0, p0);
+    tile(0, t2, p2, a0, t3, p3, a1, t0, p0, t1, p1);
+    tile(1, t3, p3, a1, t0, p0, a0, t1, p1, t2, p2);
     if ((n & 7u) == 7u && threadIdx.x == 0) __hip_atomic_fetch_add(&sy->beat, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
@@ -1446,9 +1451,11 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
 // The last workgroup of a die goes ahead of the others and touches what their requests will lead to (which is in HBM,
 // or in other dies' L2s until the launch before has ended): a wave's loads return in order, so a tile that had to wait for
 // a request of the tile before on its way from HBM would wait 2000 clocks at the rows it needs, which the L2 has.
+// The same goes for the rows that the tiles of a level will write and others look at: what was filled when the launch began, or by
+// the launch before, is no longer in the die's L2 (not where a level has more than a tile of 16 cells: it would be late for what
+// comes next, 127 levels of up to 80 cells a die 940 -> 1,050 us).
 // Each of its waves takes every NW-th level, at most TAIL_AHEAD levels and about a megabyte ahead of the tiles.  Nobody waits for
-// it, and it waits for the tiles only so long.  (4,095 levels of a TreeRNN of 512 units, forward and gradient: 9.3 and 8.3 ms
-// with a slow one, 8.9 and 7.4 with this; a chunk of a row as one request instead of two, next: 7.2 and 6.4.)
+// it, and it waits for the tiles only so long.
 constexpr uint32_t TAIL_AHEAD = 12;
 template <int DT, int MODE, int CELL>
 __device__ __forceinline__ void scout_levels(const GemmArgs& g, const TailArgs& ta, uint32_t die, const DzFuse* fz) {
@@ -1488,6 +1495,15 @@ __device__ __forceinline__ void scout_levels(const GemmArgs& g, const TailArgs& 
       const uint32_t n = min(64u, end - q);
       const bool on = lane < n;
       const uint32_t l = on ? g.l[q + lane] : 0u, r = on ? g.r[q + lane] : 0u;
+      // what this level's tiles, or their parents', write and others look at
+      if (end - q0 > 16u) {
+      } else if constexpr (MODE != DX_BWD) {
+        touch(on, g.Hs, (uint64_t)(g.out0 + q + lane) * (uint32_t)row_b, row_b, n);
+        if (MODE == LSTM_FWD) touch(on, g.Cs, (uint64_t)(g.out0 + q + lane) * (uint32_t)(g.Hp * 4), g.Hp * 4, n);
+      } else {
+        touch(on, g.A, (uint64_t)(q + lane) * (uint32_t)((int)g.lda * (int)sizeof(T)), (int)g.lda * (int)sizeof(T), n);
+        if (CELL == 2) touch(on, fz->v->dC, (uint64_t)(fz->row0 + q + lane) * (uint32_t)(g.Hp * 4), g.Hp * 4, n);
+      }
 #pragma unroll
       for (int side = 0; side < 2; ++side) {
         const uint32_t row = side ? r : l;
@@ -1521,11 +1537,18 @@ __device__ __forceinline__ void tail_begin(DieSync* sy, uint32_t* failed) {
   if (threadIdx.x == 0) atomicOr(&sy->xcc_mask, 1u << xcc_id());   // (looked at behind die_meet's barrier)
 }
 
-template <int DT, int MODE, int RES>
-__global__ void __launch_bounds__(Tile<MODE>::NW * 64, RES == 8 ? 1 : Tile<MODE>::NW / 2) k_tail_fwd(GemmArgs g, TailArgs t) {
+// Workgroups of eight waves that share a compute unit with another of their kind have two waves each on a SIMD.  Four times 128
+// registers would fill it, and a wave of a small kernel on another stream (the token sort: 16 registers) that happens to be there
+// when they are placed leaves a hole that the fourth never fits into: the compute unit holds one workgroup for good, and the
+// others wait for it until the launch gives up.  So these should take at most 112 (TreeRNN forward 102 and 105, gradient 107); the
+// forward variant for rows beyond 4 GiB, which takes more, has a compute unit to itself.
+template <int DT, int MODE, int RES, bool NARROW>
+__global__ void __launch_bounds__(Tile<MODE>::NW * 64, RES == 8 || (MODE == RNN_FWD && RES > 0 && !NARROW) ? (MODE == RNN_FWD ? 2 : 1) : Tile<MODE>::NW / 2)
+k_tail_fwd(GemmArgs g, TailArgs t) {
   typedef typename TypeOf<DT>::type T;
   typedef Tile<MODE> TL;
   __shared__ __attribute__((aligned(16))) float part[2 * TL::PART];
+  __shared__ u32x4 turns[TL::NW * TURN];
   __shared__ uint32_t sh_ok, failed[2];
   stamp_now(g.stamp);
   const uint32_t die = blockIdx.x % XCDS, rank = blockIdx.x / XCDS, G = gridDim.x / XCDS - 1u;
@@ -1556,16 +1579,17 @@ __global__ void __launch_bounds__(Tile<MODE>::NW * 64, RES == 8 ? 1 : Tile<MODE>
     }
   }
   if (!die_meet(sy, G, t.spin_ticks, &sh_ok)) return;
-  walk_levels<DT, MODE, RES, 0>(g, t, die, rank, G, part, &b, nullptr, failed);
+  walk_levels<DT, MODE, RES, 0, NARROW>(g, t, die, rank, G, part, turns, &b, nullptr, failed);
 }
 
 // Gradient pass over the same levels, deepest first.  (dz of a level's cells: from their parents' tiles, or, for the
 // roots, from k_dz_tail_roots.  Those that come from tiles were marked as not written by k_tail_fwd.)
 template <int DT, int CELL, int RES>
-__global__ void __launch_bounds__(Tile<DX_BWD>::NW * 64, CELL == 1 && RES <= 5 ? 4 : 2) k_tail_bwd(GemmArgs g, VecArgs v, Engine e, TailArgs t) {
+__global__ void __launch_bounds__(Tile<DX_BWD>::NW * 64, CELL == 1 && RES == 5 ? 4 : 2) k_tail_bwd(GemmArgs g, VecArgs v, Engine e, TailArgs t) {
   typedef typename TypeOf<DT>::type T;
   typedef Tile<DX_BWD> TL;
   __shared__ __attribute__((aligned(16))) float part[2 * TL::PART];
+  __shared__ u32x4 turns[TL::NW * TURN];
   __shared__ uint32_t sh_ok, failed[2];
   stamp_now(g.stamp);
   const uint32_t die = blockIdx.x % XCDS, rank = blockIdx.x / XCDS, G = gridDim.x / XCDS - 1u;
@@ -1581,7 +1605,7 @@ __global__ void __launch_bounds__(Tile<DX_BWD>::NW * 64, CELL == 1 && RES <= 5 ?
     load_b<DT, DX_BWD, RES>(g, (int)(rank % (uint32_t)g.n_tiles_n), s0, TL::first_step(steps, wave + 1) - s0, b);
   }
   if (!die_meet(sy, G, t.spin_ticks, &sh_ok)) return;
-  walk_levels<DT, DX_BWD, RES, CELL>(g, t, die, rank, G, part, &b, &fz, failed);
+  walk_levels<DT, DX_BWD, RES, CELL, true>(g, t, die, rank, G, part, turns, &b, &fz, failed);
 }
 
 // ---- numbering of the state rows by the sorted schedule ------------------------------------------
@@ -2138,15 +2162,17 @@ static int tail_wgs(int slots, int n_ct, uint32_t row_tiles) {
 }
 // Workgroups of a pass that are on a die's compute units together, where a wave keeps the operands of n chunk steps: two share
 // a compute unit, but for the variants with most weights in registers.
-static int tail_slots_fwd(int cus_per_die, int n) { return cus_per_die * (n <= 4 ? 2 : 1); }
+static int tail_slots_fwd(int cus_per_die, int n, bool narrow) { return cus_per_die * (n <= 4 && narrow ? 2 : 1); }
 static int tail_slots_bwd(int cus_per_die, int n, int cell_kind) { return cus_per_die * (n <= 5 && cell_kind == 1 ? 2 : 1); }
 template <typename T, int MODE, int RES> static void launch_tail_fwd(const GemmArgs& g, const TailArgs& t, int wgs, hipStream_t s) {
-  hipLaunchKernelGGL((k_tail_fwd<DtOf<T>::value, MODE, RES>), dim3((wgs + 1) * (int)XCDS), dim3(Tile<MODE>::NW * 64), 0, s, g, t);
+  const dim3 grid((wgs + 1) * (int)XCDS), block(Tile<MODE>::NW * 64);
+  if (g.fresh_narrow) hipLaunchKernelGGL((k_tail_fwd<DtOf<T>::value, MODE, RES, true>), grid, block, 0, s, g, t);
+  else hipLaunchKernelGGL((k_tail_fwd<DtOf<T>::value, MODE, RES, false>), grid, block, 0, s, g, t);
 }
 template <typename T, int MODE> static void tail_fwd_mode(GemmArgs g, const TailArgs& t, int cus_per_die, uint32_t row_tiles, hipStream_t s) {
   g.n_tiles_n = g.Hp / Tile<MODE>::UNITS;
   const int n = Tile<MODE>::steps_most(g.K / Chunk<T>::KC);
-  const int wgs = tail_wgs(tail_slots_fwd(cus_per_die, n), g.n_tiles_n, row_tiles);
+  const int wgs = tail_wgs(tail_slots_fwd(cus_per_die, n, MODE == LSTM_FWD || g.fresh_narrow), g.n_tiles_n, row_tiles);
   if (wgs && n <= 2) launch_tail_fwd<T, MODE, 2>(g, t, wgs, s);
   else if (wgs && n <= 4) launch_tail_fwd<T, MODE, 4>(g, t, wgs, s);
   else if (wgs && n <= 8) launch_tail_fwd<T, MODE, 8>(g, t, wgs, s);
@@ -2195,7 +2221,7 @@ TailLimit vec_tail_limit(const VecArgs& v, int cus_per_die, bool backward) {
   } else {
     const int n = lstm ? Tile<LSTM_FWD>::steps_most(v.Kp / kc) : Tile<RNN_FWD>::steps_most(v.Kp / kc);
     n_ct = v.Hp / (lstm ? Tile<LSTM_FWD>::UNITS : Tile<RNN_FWD>::UNITS);
-    wgs = n > 8 ? 0 : tail_wgs(tail_slots_fwd(cus_per_die, n), n_ct, 1u << 20);
+    wgs = n > 8 ? 0 : tail_wgs(tail_slots_fwd(cus_per_die, n, true), n_ct, 1u << 20);
   }
   return TailLimit{0xFFFFFFFFu, std::min(1024u, std::max(128u, (uint32_t)(wgs / n_ct) * (backward ? (lstm ? 128u : 160u) : (lstm ? 80u : 128u))))};
 }
@@ -2212,7 +2238,8 @@ void vec_tail_fwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, 
 
 template <typename T, int CELL, int RES>
 static void launch_tail_bwd(const GemmArgs& g, const VecArgs& v, const Engine& e, const TailArgs& t, int wgs, hipStream_t s) {
-  hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, CELL, RES>), dim3((wgs + 1) * (int)XCDS), dim3(Tile<DX_BWD>::NW * 64), 0, s, g, v, e, t);
+  const dim3 grid((wgs + 1) * (int)XCDS), block(Tile<DX_BWD>::NW * 64);
+  hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, CELL, RES>), grid, block, 0, s, g, v, e, t);
 }
 template <typename T, int CELL>
 static void tail_bwd_cell(const GemmArgs& g, const VecArgs& v, const Engine& e, const TailArgs& t, int cus_per_die, uint32_t row_tiles,
