@@ -59,7 +59,10 @@ constexpr uint32_t LANE_YOUNG = 12000;  // ticks (100 MHz) for which a run is yo
 constexpr uint32_t LANE_EARLY = 48;     // sweeps during which a wave gives work away although it has lanes without any
 // idle lanes up to which a wave gives calls to other waves
 constexpr uint32_t LANE_GIVE = 56;
-constexpr uint32_t LANE_LOOP = 64;      // iterations of a loop without calls in one sweep
+// Iterations of a loop without calls in one sweep (a multiple of four).  A sweep has some 2,000 ticks of its own and an
+// iteration of subtractive gcd takes 80: 65,536 pairs up to 1,024 took 96 us with 64, 86 with 256; the longest loop of the
+// batch, which is what the run waits for, has at most 1,023 iterations.
+constexpr uint32_t LANE_LOOP = 256;
 constexpr uint32_t LANE_RECS = 96;      // records of a wave
 constexpr uint32_t LANE_SCARCE = 8, LANE_FEW = 16;   // free records below which all frames below a given one take one; else the first so many take one each
 constexpr uint32_t LANE_QUEUE = 128;    // tasks of a wave (at least LANE_RECS: a record is queued at most once)

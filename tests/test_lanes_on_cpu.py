@@ -35,6 +35,52 @@ def test_integer_programs_against_the_oracle(name, tmp_path):
         assert got["tags"] == len(it.tags) + len(it.iter_tags) and got["depth"] == it.max_tag_len
 
 
+def _loop_of_choices(n_choices, nested):
+    """result(n, a) = { i = n; while 0 < i: i = i - 1; a = one choice after the other of a } a.  Choice k: a + k + 3 where
+    a < 5 k, else a - 2 k - 1; nested: the first case has two of its own, by a < 2 k, that one Merge takes with the third."""
+    T = tdf
+    nodes = []
+
+    def add(op, ins=(), imm=0):
+        nodes.append((op, [r if isinstance(r, tuple) else (r, 0) for r in ins], imm))
+        return len(nodes) - 1
+    i0, a0 = add(T.OP_IN, imm=0), add(T.OP_IN, imm=1)
+    p = add(T.OP_LT, [add(T.OP_CONST), i0])
+    si, sa = add(T.OP_SWITCH, [p, i0]), add(T.OP_SWITCH, [p, a0])
+    a = (sa, 0)
+    for k in range(1, n_choices + 1):
+        s = add(T.OP_SWITCH, [add(T.OP_LT, [a, add(T.OP_CONST, imm=5 * k)]), a])
+        less, more = (s, 0), add(T.OP_SUB, [(s, 1), add(T.OP_CONST, imm=2 * k + 1)])
+        if nested:
+            s2 = add(T.OP_SWITCH, [add(T.OP_LT, [less, add(T.OP_CONST, imm=2 * k)]), less])
+            a = add(T.OP_MERGE, [more, add(T.OP_MUL, [(s2, 1), add(T.OP_CONST, imm=3)]), add(T.OP_ADD, [(s2, 0), add(T.OP_CONST, imm=k + 3)])])
+        else:
+            a = add(T.OP_MERGE, [add(T.OP_ADD, [less, add(T.OP_CONST, imm=k + 3)]), more])
+    add(T.OP_NEXT, [add(T.OP_SUB, [(si, 0), add(T.OP_CONST, imm=1)]), a])
+    add(T.OP_OUT, [(sa, 1)])
+    res = [(T.OP_IN, [], 0), (T.OP_IN, [], 1), (T.OP_LOOP, [(0, 0), (1, 0)], 1), (T.OP_OUT, [(2, 0)], 0)]
+
+    def ref(n, a):
+        for _ in range(n):
+            for k in range(1, n_choices + 1):
+                a = a - 2 * k - 1 if a >= 5 * k else a * 3 if nested and a >= 2 * k else a + k + 3
+        return a
+    return ([("result", 2, res), ("W", 2, nodes)], 0), ref
+
+
+# (predicates: one for the loop, and one a choice, nested two; the truth tables hold six of them)
+@pytest.mark.parametrize("n_choices,nested", [(1, False), (5, False), (6, False), (2, True), (3, True)])
+def test_iterations_of_loops_with_choices(n_choices, nested, tmp_path):
+    prog, ref = _loop_of_choices(n_choices, nested)
+    lanes = Lanes(prog, tmp_path)
+    # around the four iterations between two looks at who goes on, and around a sweep's share
+    args = [(n, 7 * n % 31 - 9) for n in (0, 1, 2, 3, 4, 5, 7, 8, 9, 255, 256, 257, 258, 511, 512, 513, 700)]
+    for waves in (1, 3):
+        got = lanes.run(args, waves=waves)
+        assert got["status"] == 0 and got["out"] == [ref(*a) for a in args]
+        assert got["tags"] == sum(n + 1 for n, _ in args) and got["depth"] == 1
+
+
 @pytest.mark.parametrize("name", list(VECTOR))
 def test_vector_results(name, tmp_path):
     prog, forest, args, ref = VECTOR[name]()
