@@ -200,16 +200,18 @@ struct Gen {
   }
 
   // ---- the same tables for the depth-first lanes (lane_device.h) -------------------------------------
-  // A lane's frame is in a state (function, calls opened, of these still outstanding), and a sweep ends
+  // A lane's frame is in a state (function, calls opened), and a sweep ends
   // with the one thing the lane does next: a call all of whose arguments are live, the next iteration, the
   // return of a complete frame, or waiting.  What is present, and much of what is live, is known from the
   // state: the arguments of an opened call were live, so the Switches on their way went that side.  Every
   // reachable state gets code of its own with these facts folded in (fib's first sweep is a comparison,
   // its last one an addition); a lane whose sweep is a few instructions is what the machine's speed is.
-  // States beyond MAX_STATES (functions with many calls, several of them outstanding) run the generic code
+  // Which opened calls are still outstanding is looked up in the frame: with a state for each such set tak has 32
+  // and not 11 (and fib 12, not 6), of which a wave's lanes are in more at a time, each a turn of its own.
+  // States beyond MAX_STATES (functions with many calls) run the generic code
   // of their function, which keeps the present and opened sets in registers.
   static constexpr int MAX_STATES = 24;
-  struct State { int f; uint32_t mask, out; };
+  struct State { int f; uint32_t mask; };
   std::vector<State> states;
   struct B {                      // a truth value: constant 0 / 1, or an expression
     int k;
@@ -329,9 +331,9 @@ struct Gen {
     }
     return r;
   }
-  bool has_state(int f, uint32_t mask, uint32_t out) const {
+  bool has_state(int f, uint32_t mask) const {
     for (const State& t : states)
-      if (t.f == f && t.mask == mask && t.out == out) return true;
+      if (t.f == f && t.mask == mask) return true;
     return false;
   }
   // A state's number says what it is (LANE_ST in lane_device.h)
@@ -355,7 +357,7 @@ struct Gen {
     std::vector<Val> V;
     B complete = bc(false);
     std::ostringstream sink;
-    body(sink, State{f, 0, 0}, "", "on", nullptr, V, complete, nullptr);
+    body(sink, State{f, 0}, "", "on", nullptr, V, complete, nullptr);
     return V[v].p.k == 1;
   }
   // The slot that holds value `v` in a state, or -1.
@@ -394,7 +396,7 @@ struct Gen {
       c << "        const long long " << q << "v" << D << " = " << (expr.empty() ? "0" : expr) << ";\n";
       V[dst] = Val{q + "v" + D, name_b("p" + D, p), name_b("d" + D, band(p, d))};
     };
-    complete = bc(S.out == 0);
+    complete = S.mask ? named(c, q + "back", bx("x.st < 2048u")) : bc(true);   // (nothing outstanding)
     for (int ip = 0; ip < fn.count; ++ip) {
       const Instr& I = at(f, ip);
       const std::string D = std::to_string(I.dst);
@@ -406,9 +408,9 @@ struct Gen {
         case D_RET: {
           const uint32_t bit = 1u << P.label_site[I.aux2];
           if (S.mask & bit) {
-            const bool back = !(S.out & bit);
-            c << "        const long long " << q << "v" << D << " = " << (back ? "x.sv[" + std::to_string(I.aux) + "]" : "0") << ";\n";
-            V[I.dst] = Val{q + "v" + D, bc(back), bc(false)};
+            c << "        const long long " << q << "v" << D << " = x.sv[" << (int)I.aux << "];\n";
+            const B back = F.live[I.dst] == 1 ? bc(true) : name_b("p" + D, bx("!(x.st & " + std::to_string(bit << 11) + "u)"));
+            V[I.dst] = Val{q + "v" + D, back, bc(false)};
           } else {
             B all_p = bc(true), any_d = bc(false), any_arg = bc(false);
             for (int k = 0; k < 4; ++k) {
@@ -588,7 +590,7 @@ struct Gen {
       B complete = bc(false);
       bool can = true;
       std::ostringstream sink;
-      body(sink, State{f, 0, 0}, "", "on", &ins, F, W, complete, &can);
+      body(sink, State{f, 0}, "", "on", &ins, F, W, complete, &can);
       if (whole_callee(f, W, complete).k != 1) return false;
     }
     return true;
@@ -613,7 +615,11 @@ struct Gen {
     const bool loop = tight_loop(f);
     body(c, S, "", "on", nullptr, V, complete, nullptr);
     auto src = [&](const Instr& I, int k) { return source(V, I, k); };
-    auto state_name = [](int sf, uint32_t m, uint32_t ou) { return std::to_string(state_code_of(sf, m, ou)) + "u"; };
+    // a frame's own next state, with what is outstanding as it is; a callee's first one
+    auto state_name = [&](uint32_t m) {
+      return S.mask ? "(x.st | " + std::to_string((m & ~S.mask) << 3) + "u)" : std::to_string(state_code_of(f, m, 0)) + "u";
+    };
+    auto first_state = [](int sf) { return std::to_string(state_code_of(sf, 0, 0)) + "u"; };
     // ---- what the lane does next
     const std::vector<Site> ss = sites(f);
     std::string chain, nx;
@@ -628,7 +634,7 @@ struct Gen {
     B c0 = bc(false);
     if (S.mask) {
       std::ostringstream sink;
-      body(sink, State{f, 0, 0}, "", "on", nullptr, V0, c0, nullptr);
+      body(sink, State{f, 0}, "", "on", nullptr, V0, c0, nullptr);
     }
     for (const Site& t : ss) {
       const uint32_t bit = t.label >= 0 ? 1u << P.label_site[t.label] : 0u;
@@ -652,7 +658,7 @@ struct Gen {
         if (loop && all.k) {
           nx = "if (" + all.e + ") {}   // on in the next sweep\n          else ";
         } else if (all.k) {
-          nx = "if (" + all.e + ") { x.act = ACT_NEXT;" + args + " x.c_st = " + state_name(f, 0, 0) + "; }\n          else ";
+          nx = "if (" + all.e + ") { x.act = ACT_NEXT;" + args + " x.c_st = " + first_state(f) + "; }\n          else ";
         }
         continue;
       }
@@ -669,7 +675,7 @@ struct Gen {
         std::ostringstream ic;
         bool can = true;
         node_at = NodeAt{"", "", bc(false)};
-        body(ic, State{callee, 0, 0}, q, con, &ins, W, complete0, &can);
+        body(ic, State{callee, 0}, q, con, &ins, W, complete0, &can);
         const Val ov = source(W, out_entry(callee), 0);
         const B done = whole_callee(callee, W, complete0);
         if (can && done.k != 0) {
@@ -689,9 +695,9 @@ struct Gen {
       if (!r.done.empty())
         for (size_t k = 0, n = sets.size(); k < n; ++k) sets.push_back(sets[k] | r.bit);
     auto state_after = [&](uint32_t bit) {   // the state once call `bit` (0: none) is back, by what was done in place
-      std::string e2 = state_name(f, S.mask | bit | sets[0], S.out);
+      std::string e2 = state_name(S.mask | bit | sets[0]);
       for (size_t k = 1; k < sets.size(); ++k)
-        if (!(sets[k] & bit)) e2 = "(om == " + std::to_string(S.mask | sets[k]) + "u ? " + state_name(f, S.mask | bit | sets[k], S.out) + " : " + e2 + ")";
+        if (!(sets[k] & bit)) e2 = "(om == " + std::to_string(S.mask | sets[k]) + "u ? " + state_name(S.mask | bit | sets[k]) + " : " + e2 + ")";
       return e2;
     };
     auto note = [&](uint32_t m) {
@@ -727,7 +733,7 @@ struct Gen {
       for (const Ready& u : rs)
         if (&u != &r && u.t->args.size() == 1 && kept(f, u.t->args[0]->src[0]))
           keep += (u.done.empty() ? "" : " if (!" + u.done + ")") + std::string(" x.sv[") + std::to_string(u.slot) + "] = " + src(*u.t->args[0], 0).v + ";";
-      chain += std::string(n_chain++ ? "          else " : "          ") + "if (" + go + ") { x.act = ACT_CALL; x.c_st = " + state_name(r.callee, 0, 0) + "; x.c_back = " +
+      chain += std::string(n_chain++ ? "          else " : "          ") + "if (" + go + ") { x.act = ACT_CALL; x.c_st = " + first_state(r.callee) + "; x.c_back = " +
                state_after(r.bit) + " | " + std::to_string((unsigned)r.slot << 20) + "u; x.c_label = " + std::to_string(r.t->label) + "u;" + r.args + r.node + keep + " }\n";
       taken = bor(taken, r.done.empty() ? r.all : bx(go));
     }
@@ -755,9 +761,13 @@ struct Gen {
       c << "x.act = ACT_STUCK;\n";
     }
     c << "        }\n";
-    o << "      case " << state_code_of(f, S.mask, S.out) << "u: {  // function " << f << ", opened " << S.mask << ", outstanding " << S.out << "\n";
+    const std::string code = std::to_string(state_code_of(f, S.mask, 0));
+    o << "    {  // function " << f << ", opened " << S.mask << "\n";
+    o << "      const bool on = x.run && (x.st & 2047u) == " << code << "u;\n      if (__ballot(on)) {\n";
     if (loop) iterations(f);
-    o << c.str() << "      break; }\n";
+    o << c.str();
+    if (unlisted) o << "        known = known || (on && (x.act != ACT_NONE || (x.st & 2047u) == " << code << "u));\n";
+    o << "      }\n    }\n";
   }
   // The iterations of a sweep, before it looks at what the lane does next.  What bounds them is the instructions of one
   // iteration (a wave has its SIMD nearly to itself), so they are a straight run of arithmetic: every lane computes, one
@@ -775,7 +785,7 @@ struct Gen {
     std::ostringstream c;
     predicates.clear();
     loop_body = true;
-    body(c, State{f, 0, 0}, "i", "on", &ins, V, complete, &can);
+    body(c, State{f, 0}, "i", "on", &ins, V, complete, &can);
     std::string next;
     int n_args = 0;
     for (const Site& t : sites(f))
@@ -798,24 +808,23 @@ struct Gen {
     o << "          ln_loop(x, n_it, " << nv << "u);\n        }\n";
   }
 
+  bool unlisted = false;   // whether there may be states without code of their own
   void find_states() {
     states.clear();
-    for (int f = 0; f < P.n_fn; ++f) states.push_back({f, 0, 0});
-    for (int pass = 0; pass < 2; ++pass)   // first without outstanding calls, then with them
-      for (size_t k = 0; k < states.size() && states.size() < MAX_STATES; ++k) {
-        const State S = states[k];
-        std::vector<int> nx;
-        state_code(S, nx, false);
-        auto add = [&](uint32_t mask, uint32_t out) {
-          if ((int)states.size() < MAX_STATES && !has_state(S.f, mask, out)) states.push_back({S.f, mask, out});
-        };
-        for (int mask : nx) {
-          if (pass == 0 || S.out) add((uint32_t)mask, S.out);
-          if (pass == 1)   // ... with any one of the calls just opened still under way
-            for (int b2 = 0; b2 < 8; ++b2)
-              if (((uint32_t)mask & ~S.mask) >> b2 & 1) add((uint32_t)mask, S.out | (1u << b2));
-        }
+    for (int f = 0; f < P.n_fn; ++f) states.push_back({f, 0});
+    unlisted = false;
+    for (size_t k = 0; k < states.size(); ++k) {
+      const State S = states[k];
+      std::vector<int> nx;
+      state_code(S, nx, false);
+      for (int mask : nx) {
+        if (has_state(S.f, (uint32_t)mask)) continue;
+        if ((int)states.size() < MAX_STATES) states.push_back({S.f, (uint32_t)mask});
+        else unlisted = true;
       }
+    }
+    // (a frame whose call was evaluated in place goes on in a later state, with more calls opened)
+    std::sort(states.begin(), states.end(), [](const State& a, const State& b) { return a.f != b.f ? a.f < b.f : a.mask < b.mask; });
   }
   // The generic code of a function: present and opened sets from registers.
   void lane_function(int f) {
@@ -933,21 +942,26 @@ struct Gen {
     }
     o << "    return r;\n  }\n";
     o << "  static __device__ __forceinline__ void sweep(LaneX& x) {\n";
-    // One state after the other, as the wave's lanes have them.  A lane whose call was evaluated in place is
-    // in another state then and comes up again; a lane is left out once its state is done.
-    o << "    unsigned long long todo = __ballot(x.run);\n";
-    o << "    while (todo) {\n";
-    o << "      const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)x.st, __ffsll((long long)todo) - 1);\n";
-    o << "      const bool on = ((todo >> lane_id()) & 1ull) && x.st == s;\n";
-    o << "      switch (s) {\n";
+    // One state after the other, those that some lane is in.  A lane whose call was evaluated in place is in a later state
+    // then and comes up again.  A sweep is bound by the instructions of the states its lanes are in.  A loop that takes the
+    // next lane's state and switches to its code, with a state for each set of outstanding calls, cost 20 copies of the
+    // lane's registers a turn and a tree of branches: 1,950 ticks a sweep for fib, 2,800 for tak.  fib(30..32) takes 3,230 us
+    // now, not 4,090; 256 of tak 1,695, not 2,360; fib(0..20) 165, not 189; eight small ones 70, not 77.
+    if (unlisted) o << "    bool known = false;\n";
     for (const State& t : states) {
       std::vector<int> nx;
       state_code(t, nx, true);
     }
-    o << "      default: switch (s & 7u) {\n";
-    for (int f = 0; f < P.n_fn; ++f) lane_function(f);
-    o << "        default: if (on) x.act = ACT_STUCK; break;\n        } break;\n      }\n";
-    o << "      todo &= __ballot(!(on && (x.act != ACT_NONE || x.st == s)));\n    }\n";
+    if (unlisted) {
+      o << "    unsigned long long todo = __ballot(x.run && !known);\n";
+      o << "    while (todo) {\n";
+      o << "      const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)x.st, __ffsll((long long)todo) - 1);\n";
+      o << "      const bool on = ((todo >> lane_id()) & 1ull) && x.st == s;\n";
+      o << "      switch (s & 7u) {\n";
+      for (int f = 0; f < P.n_fn; ++f) lane_function(f);
+      o << "        default: if (on) x.act = ACT_STUCK; break;\n      }\n";
+      o << "      todo &= __ballot(!on);\n    }\n";
+    }
     o << "  }\n};\n}  // namespace tdf\n";
     o << "extern \"C\" __global__ void __launch_bounds__(64, 2) tdf_generated_lanes(tdf::LaneArgs a) {\n";
     o << "  extern __shared__ __attribute__((aligned(16))) char lds[];\n";
