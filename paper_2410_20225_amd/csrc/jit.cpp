@@ -694,11 +694,11 @@ struct Gen {
     for (const Ready& r : rs)
       if (!r.done.empty())
         for (size_t k = 0, n = sets.size(); k < n; ++k) sets.push_back(sets[k] | r.bit);
-    auto state_after = [&](uint32_t bit) {   // the state once call `bit` (0: none) is back, by what was done in place
-      std::string e2 = state_name(S.mask | bit | sets[0]);
-      for (size_t k = 1; k < sets.size(); ++k)
-        if (!(sets[k] & bit)) e2 = "(om == " + std::to_string(S.mask | sets[k]) + "u ? " + state_name(S.mask | bit | sets[k]) + " : " + e2 + ")";
-      return e2;
+    // the state once call `bit` (0: none) is back, by what was done in place (om: all calls opened)
+    const bool in_place = sets.size() > 1;
+    auto state_after = [&](uint32_t bit) {
+      if (!in_place) return state_name(S.mask | bit);
+      return "(x.st | " + (bit ? "(om | " + std::to_string(bit) + "u)" : std::string("om")) + " << 3)";
     };
     auto note = [&](uint32_t m) {
       if (m != S.mask) next.push_back((int)m);
@@ -708,8 +708,9 @@ struct Gen {
       if (r.done.empty()) continue;
       om += " | (" + r.done + " ? " + std::to_string(r.bit) + "u : 0u)";
       put += "          if (" + r.done + ") { x.sv[" + std::to_string(r.slot) + "] = " + r.value + "; x.present |= " + std::to_string(1u << r.slot) +
-             "u; ++x.n_tags; x.n_tokens += " + std::to_string(P.fn[r.callee].n_params + 1) + "u; x.mx_depth = max(x.mx_depth, x.depth + 1u); }\n";
+             "u; ++x.n_tags; x.n_tokens += " + std::to_string(P.fn[r.callee].n_params + 1) + "u; }\n";
     }
+    if (in_place) put += "          x.mx_depth = max(x.mx_depth, x.depth + (om != " + std::to_string(S.mask) + "u ? 1u : 0u));\n";
     for (uint32_t d : sets) note(S.mask | d);
     for (size_t k = 0; k < rs.size(); ++k) {
       const Ready& r = rs[k];
@@ -737,7 +738,7 @@ struct Gen {
                state_after(r.bit) + " | " + std::to_string((unsigned)r.slot << 20) + "u; x.c_label = " + std::to_string(r.t->label) + "u;" + r.args + r.node + keep + " }\n";
       taken = bor(taken, r.done.empty() ? r.all : bx(go));
     }
-    if (sets.size() > 1)
+    if (in_place)
       chain += std::string(n_chain++ ? "          else " : "          ") + "if (om != " + std::to_string(S.mask) + "u) { x.st = " + state_after(0) + "; }\n";
     if (!emit) return;
     const Instr& oe = out_entry(f);
