@@ -81,6 +81,59 @@ def test_iterations_of_loops_with_choices(n_choices, nested, tmp_path):
         assert got["tags"] == sum(n + 1 for n, _ in args) and got["depth"] == 1
 
 
+def _many_calls(n_calls, mutual, chained):
+    """f(n) = n + 3 where n < 1, else the sum of k f(n - k) over k = 1 .. n_calls; mutual: f calls g, and g, the same, f;
+    chained: the last call's argument is n - 2 plus what the first one returns times 0, so it is ready later than the others."""
+    T = tdf
+    bodies = [_body_of_calls(n_calls, callee, chained) for callee in ([2, 1] if mutual else [1])]
+    res = [(T.OP_IN, [], 0), (T.OP_CALLFN, [(0, 0)], 1), (T.OP_OUT, [(1, 0)], 0)]
+
+    def ref(n):   # value, tags, depth
+        if n < 1:
+            return n + 3, 1, 1
+        below = [ref(n - (2 if chained and k == n_calls else k)) for k in range(1, n_calls + 1)]
+        return sum((k + 1) * v[0] for k, v in enumerate(below)), 1 + sum(v[1] for v in below), 1 + max(v[2] for v in below)
+    return ([("result", 1, res)] + [("fg"[i], 1, b) for i, b in enumerate(bodies)], 0), ref
+
+
+def _body_of_calls(n_calls, callee, chained):
+    T = tdf
+    nodes = []
+
+    def add(op, ins=(), imm=0):
+        nodes.append((op, [r if isinstance(r, tuple) else (r, 0) for r in ins], imm))
+        return len(nodes) - 1
+    n, one = add(T.OP_IN, imm=0), add(T.OP_CONST, imm=1)
+    s = add(T.OP_SWITCH, [add(T.OP_LT, [n, one]), n])
+    total = first = None
+    for k in range(1, n_calls + 1):
+        if chained and k == n_calls:
+            a = add(T.OP_ADD, [add(T.OP_SUB, [(s, 1), add(T.OP_CONST, imm=2)]), add(T.OP_MUL, [first, add(T.OP_CONST, imm=0)])])
+        else:
+            a = add(T.OP_SUB, [(s, 1), add(T.OP_CONST, imm=k)])
+        call = add(T.OP_CALLFN, [a], imm=callee)
+        first = call if first is None else first
+        term = add(T.OP_MUL, [call, add(T.OP_CONST, imm=k)])
+        total = term if total is None else add(T.OP_ADD, [total, term])
+    add(T.OP_OUT, [add(T.OP_MERGE, [add(T.OP_ADD, [(s, 0), add(T.OP_CONST, imm=3)]), total])])
+    return nodes
+
+
+# (a state for each set of opened calls: two functions of four calls have more than get code of their own)
+@pytest.mark.parametrize("n_calls,mutual", [(4, False), (7, False), (3, True), (4, True), (5, True)])
+@pytest.mark.parametrize("chained", [False, True])
+def test_functions_with_many_calls(n_calls, mutual, chained, tmp_path):
+    prog, ref = _many_calls(n_calls, mutual, chained)
+    assert ("bool known" in lane_source(prog)) == (mutual and n_calls > 3)
+    lanes = Lanes(prog, tmp_path)
+    args = [(n,) for n in (5, 0, 3, -1, 6, 1, 2, 4)]
+    want = [ref(*a) for a in args]
+    for waves, seed in [(1, 1), (3, 2), (16, 3)]:
+        got = lanes.run(args, waves=waves, seed=seed)
+        assert got["status"] == 0 and got["out"] == [w[0] for w in want]
+        assert got["tags"] == sum(w[1] for w in want) and got["depth"] == max(w[2] for w in want)
+
+
 @pytest.mark.parametrize("name", list(VECTOR))
 def test_vector_results(name, tmp_path):
     prog, forest, args, ref = VECTOR[name]()
