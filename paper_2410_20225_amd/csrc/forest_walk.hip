@@ -4,9 +4,9 @@
 // Call_i of its two calls are the edges to the children, Return_i the edges back.  Where every node is visited at most
 // once, tags and nodes are the same thing, and what the tag machine would log (lane_device.h) follows from the forest
 // alone: a leaf fires its EMBED, an inner node its cell when both children have, one level above the higher of them.
-// A tree that lies in one piece is numbered where it lies (tree_in_piece).  Any other one wave walks, an instance each: a lane goes down to the left child and leaves the right one on a stack in LDS,
-// which lanes without a node take from; a leaf turns the lane round, and the second of two children that arrive at their
-// parent goes on up.  The schedule log is indexed by node, so a value's name is its node.
+// A tree that lies in one piece is numbered where it lies (tree_in_piece).  Any other one wave walks, an instance each: a
+// lane goes down to the left child and leaves the right one on a stack in LDS, which lanes without a node take from; a
+// leaf turns the lane round, and the second of two children that arrive at their parent goes on up.  The schedule log is indexed by node, so a value's name is its node.
 //
 // The rule: programs of that form (walk_form, below) and forests of at most as many nodes as the log has entries.  One wave
 // works on an instance, at 32 nodes a step where the tree is wide, 0.02 to 0.03 us a node; the lanes share a tree
@@ -19,9 +19,10 @@
 // 16,384 1,035 (849), 64 random ones 1,463 (2,372); chains of any length, 16,384 leaves 40.1 ms (66.8).  More than WALK_NODES
 // nodes an instance on average, more than those, were not measured and go to the lanes.
 // A forest whose nodes are shared (between parents or instances), or have bad entries, leaves a status, and the lanes run the
-// evaluation; what they make of it counts.
+// evaluation; what they make of it counts.  (The figures here and below are of trees that are walked; for those in one
+// piece see tree_in_piece.)
 //
-// What bounds it: the latency of one request per level down (the node's entries) and one up (the parent's word, in the die's
+// What bounds the walk: the latency of one request per level down (the node's entries) and one up (the parent's word, in the die's
 // L2), and some 150 instructions a step: 1.4 us a level there and back, where the lanes' sweeps take 3.3.
 // The tag phase, lanes -> walk: one tree of 35 leaves 94 -> 22 us, 50 trees of up to 50 leaves 128 -> 28, 1,024 trees 205 ->
 // 37, 4,096 trees of up to 128 leaves, a fifth of them chains, 620 -> 240, 64 chains of 4,096 leaves 13.5 -> 5.8 ms.

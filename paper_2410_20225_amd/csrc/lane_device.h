@@ -28,8 +28,8 @@
 // What bounds it: the instructions of a wave's sweeps, about 4 clocks each, vector, scalar and branch alike (a
 // recursion without parallelism runs one lane, about 1.3 us a call there and back), and with many waves how evenly
 // the calls spread over them.  A frame costs no memory traffic beyond the lane's stack, whose top is in LDS.
-// Measured, whole evaluations in us, step machine -> lanes: fib(0..20) 606 -> 214; fib(30) + fib(31) + fib(32)
-// 27600 -> 5000; tak over 256 instances 20500 -> 2600; 65536 gcd loops 7300 -> 135.
+// Measured, whole evaluations in us, step machine -> lanes: fib(0..20) 606 -> 167; fib(30) + fib(31) + fib(32)
+// 27600 -> 3270; tak over 256 instances 20500 -> 1700; 65536 gcd loops 7300 -> 84.
 // The tag phase of tree networks: 4096 random trees of up to 64 leaves 1980 -> 600, 1500 small trees 366 -> 112, a chain
 // of 512 leaves 4200 -> 1500.
 //
