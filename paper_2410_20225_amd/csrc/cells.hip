@@ -735,8 +735,8 @@ __device__ __forceinline__ TileWaits<typename TypeOf<DT>::type, MODE> tile_waits
   }
   return r;
 }
-// One look at a tile's rows, by the lanes with `fresh` (f0, f1): n chunk steps from st0 on.
-template <typename T, int MODE, int N>
+// One look at a tile's rows, by the lanes with `fresh` (f0, f1): n chunk steps from st0 on, at least LEAST.
+template <typename T, int MODE, int LEAST, int N>
 __device__ __forceinline__ void look_rows(const TileWaits<T, MODE>& w, bool narrow, int st0, int n, bool fresh, bool f0, bool f1, u32x4 (&a)[N], uint32_t& u0,
                                           uint32_t& u1) {
   constexpr uint32_t step = Chunk<T>::KC * sizeof(T);
@@ -744,21 +744,21 @@ __device__ __forceinline__ void look_rows(const TileWaits<T, MODE>& w, bool narr
     if (narrow) {
 #pragma unroll
       for (int st = 0; st < N; ++st)
-        if (st < least_steps(N) || st < n) a[st] = load_fresh16(w.rows, (uint32_t)w.off + (uint32_t)(st0 + st) * step);
+        if (st < LEAST || st < n) a[st] = load_fresh16(w.rows, (uint32_t)w.off + (uint32_t)(st0 + st) * step);
     } else {
 #pragma unroll
       for (int st = 0; st < N; ++st)
-        if (st < least_steps(N) || st < n) a[st] = load_fresh16_wide(w.rows, w.off + (uint32_t)(st0 + st) * step);
+        if (st < LEAST || st < n) a[st] = load_fresh16_wide(w.rows, w.off + (uint32_t)(st0 + st) * step);
     }
   }
   if (f0) u0 = load_fresh(w.w0);   // (written right behind the rows)
   if (MODE == LSTM_FWD && f1) u1 = load_fresh(w.w1);
 }
-template <typename T, int N> __device__ __forceinline__ bool rows_waiting(const u32x4 (&a)[N], int n) {
+template <typename T, int LEAST, int N> __device__ __forceinline__ bool rows_waiting(const u32x4 (&a)[N], int n) {
   uint32_t m = 0;
 #pragma unroll
   for (int st = 0; st < N; ++st)
-    if (st < least_steps(N) || st < n) m = Chunk<T>::greatest(m, a[st]);
+    if (st < LEAST || st < n) m = Chunk<T>::greatest(m, a[st]);
   return Chunk<T>::waiting(m);
 }
 // Waiting for rows of other workgroups: `attempt` looks again (true: this lane has what it needs) until all lanes of the
@@ -807,7 +807,9 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   typedef Tile<MODE> TL;
-  constexpr int BATCH = RES > 0 ? RES : 3;   // chunk steps in flight (not 4: least_steps)
+  // Chunk steps in flight, of which LEAST are there for sure.  Four where they are fetched as they are needed: all that a wave of a
+  // TreeLSTM of 256 units or a TreeRNN of 512 has (the gradient tail of a TreeLSTM of 256 units, 32 levels: 246 us with three, 189).
+  constexpr int BATCH = RES > 0 ? RES : 4, LEAST = least_steps(RES);
   const int lane = threadIdx.x & 63, n = c.n, s0 = c.s0, wave = c.wave;
   const bool valid = (lane >> 2) < t.M;
   const T* Ap;
@@ -830,13 +832,13 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
     if constexpr (WAIT) {
       bool open = fresh, o0 = f0 && st0 == 0, o1 = f1 && st0 == 0;
       auto still_open = [&] {
-        open = open && rows_waiting<T>(fa, cnt);
+        open = open && rows_waiting<T, LEAST>(fa, cnt);
         o0 = o0 && u0 == F_NONE;
         o1 = o1 && u1 == F_NONE;
         return open || o0 || o1;
       };
       auto attempt = [&] {
-        look_rows(tw, narrow, st0, cnt, open, o0, o1, fa, u0, u1);
+        look_rows<T, MODE, LEAST>(tw, narrow, st0, cnt, open, o0, o1, fa, u0, u1);
         return !still_open();
       };
       if (__builtin_expect(!__all(attempt()), 0))
@@ -1541,9 +1543,10 @@ __device__ __forceinline__ void tail_begin(DieSync* sy, uint32_t* failed) {
 // registers would fill it, and a wave of a small kernel on another stream (the token sort: 16 registers) that happens to be there
 // when they are placed leaves a hole that the fourth never fits into: the compute unit holds one workgroup for good, and the
 // others wait for it until the launch gives up.  So these should take at most 112 (TreeRNN forward 102 and 105, gradient 107); the
-// forward variant for rows beyond 4 GiB, which takes more, has a compute unit to itself.
+// forward variant for rows beyond 4 GiB, which takes more, has a compute unit to itself, and so has the one that fetches its
+// weights for every tile.
 template <int DT, int MODE, int RES, bool NARROW>
-__global__ void __launch_bounds__(Tile<MODE>::NW * 64, RES == 8 || (MODE == RNN_FWD && RES > 0 && !NARROW) ? (MODE == RNN_FWD ? 2 : 1) : Tile<MODE>::NW / 2)
+__global__ void __launch_bounds__(Tile<MODE>::NW * 64, RES == 8 || (MODE == RNN_FWD && (RES == 0 || !NARROW)) ? (MODE == RNN_FWD ? 2 : 1) : Tile<MODE>::NW / 2)
 k_tail_fwd(GemmArgs g, TailArgs t) {
   typedef typename TypeOf<DT>::type T;
   typedef Tile<MODE> TL;

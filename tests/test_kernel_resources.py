@@ -11,19 +11,27 @@ TOOLS = "/opt/rocm/llvm/bin"
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{(dtype, template arguments): (registers, bytes of scratch)} of k_tail_fwd and k_tail_bwd."""
+def objects(tmp_path_factory):
+    """The library's code objects, as files."""
     if not os.path.exists(os.path.join(TOOLS, "llvm-readelf")):
         pytest.skip("no LLVM tools")
     where = tmp_path_factory.mktemp("code")
     lib = os.path.join(where, "libtdf.so")
     os.symlink(build.LIB, lib)
     subprocess.run([os.path.join(TOOLS, "llvm-objdump"), "--offloading", lib], cwd=where, check=True, capture_output=True)
+    return [os.path.join(where, f) for f in sorted(os.listdir(where)) if "gfx950" in f]
+
+
+def _notes(f):
+    return subprocess.run([os.path.join(TOOLS, "llvm-readelf"), "--notes", f], capture_output=True, text=True).stdout
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
+    """{(dtype, template arguments): (registers, bytes of scratch)} of k_tail_fwd and k_tail_bwd."""
     got = {}
-    for f in sorted(os.listdir(where)):
-        if "gfx950" not in f:
-            continue
-        notes = subprocess.run([os.path.join(TOOLS, "llvm-readelf"), "--notes", os.path.join(where, f)], capture_output=True, text=True).stdout
+    for f in objects:
+        notes = _notes(f)
         for k in notes.split("  - .agpr_count:")[1:]:
             name = re.search(r"\.name:\s+\S*?(k_tail_(?:fwd|bwd))((?:IL|EL)\S+?)EEEv", k)
             if name:
@@ -41,3 +49,23 @@ def test_two_tails_on_a_compute_unit_leave_room_for_other_kernels(kernels):
     """Four waves of them share a SIMD's 512 registers with what small kernels on other streams take while they are placed."""
     two = [k for k in kernels if (k[0] == "k_tail_fwd" and k[2] == 0 and k[3] in (2, 4) and k[4] == 1) or (k[0] == "k_tail_bwd" and k[2:] == (1, 5))]
     assert len(two) == 6 and all(kernels[k][0] <= 112 for k in two)
+
+
+@pytest.fixture(scope="module")
+def code(objects):
+    """{(kernel, dtype, template arguments): instructions} of the kernels that multiply small tiles."""
+    got = {}
+    for f in objects:
+        text = subprocess.run([os.path.join(TOOLS, "llvm-objdump"), "-d", "--no-show-raw-insn", f], capture_output=True, text=True).stdout
+        for body in re.split(r"^[0-9a-f]+ <", text, flags=re.M)[1:]:
+            name = re.match(r"\S*?(k_tail_fwd|k_tail_bwd|k_cell_small)((?:IL|EL)\S+?)EEEv", body)
+            if name:
+                got[(name.group(1),) + tuple(int(x) for x in re.findall(r"L[ib](\d+)", name.group(2)))] = [i.split()[0] for i in body.splitlines()[1:] if i.strip()]
+    return got
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("mode,blocks", [(0, 2), (1, 5), (2, 2)], ids=["rnn", "lstm", "gradient"])
+def test_small_tiles_have_four_steps_of_the_reduction_in_flight(code, mode, blocks, dtype):
+    """A step is a chunk of the rows and one of every column block's weights, 16 bytes a lane."""
+    assert code[("k_cell_small", dtype, mode)].count("global_load_dwordx4") >= 4 * (1 + blocks)
