@@ -608,6 +608,7 @@ struct DzFuse {
 struct TileAt {
   uint32_t q0;
   int M, ct;
+  uint32_t lvl;   // of the walk
 };
 // What a tile reads that no tile writes, in the steps that follow one another: rows of the children (TileRows, to which
 // the fused dz adds the rows of the children's children), and what these lead to (TileAhead): operands of children that
@@ -618,7 +619,15 @@ template <int MODE> struct TileRows {
   uint32_t o_l, o_r;                // children of the lane's element
   uint32_t z_q, z_gl, z_gr;         // fused dz: the child cell (none: all ones) and its children's rows
 };
+// LOOK: a tile that is not its workgroup's first of a level reads rows that are likely there already: the tile before looks
+// for them while it sums and finishes.  Gradient tails of a TreeLSTM, whose workgroups are alone on a compute unit and have several
+// tiles a level (127 levels of up to 80 cells a die beside the level launches: 1,430 us without, 1,200); the other tails, two
+// workgroups a compute unit or a tile a level, gain nothing.
 template <typename T, int MODE, int RES, int CELL> struct TileAhead {
+  static constexpr bool LOOK = CELL == 2 && RES == 5;
+  u32x4 look[LOOK ? RES : 1];
+  uint32_t look_u0;
+  bool looked;   // (uniform)
   u32x4 a[RES > 0 && MODE != DX_BWD ? RES : 1];   // the lane's operands, if its child is complete
   float bias[Tile<MODE>::G];   // (RES == 0)
   float c_l, c_r;                             // cell states of complete children (TreeLSTM)
@@ -794,16 +803,17 @@ template <class F> __device__ __forceinline__ bool wait_rows(const TailWait& w, 
 // RES > 0: the weight operands are in `b` (all chunk steps of this wave); 0: they are fetched here.
 // WAIT: rows from g.fresh_row on (forward: children, gradient: the tile's own dz and the children's dc) are written by
 // this launch and waited for.  `request` finds a later tile and asks for what later tiles need, behind the tile's stores, which are on
-// their way to the other workgroups meanwhile.
+// their way to the other workgroups meanwhile; `look` (LOOK) looks for the next tile's rows in the products' shadow, when all that
+// was asked for before has come.
 // failed: a flag in LDS, two of them in turn like `part`; false is returned if it is set (the launch's results are void then).
 // From the tile's stores to the next tile's first look there is no wait for anything: row numbers are two looks old, and
 // each look is waited for with all that was asked for before it.  (The compiler has to see that: branches are uniform or around
 // loads alone.)
-template <int DT, int MODE, int RES, int CELL, bool WAIT, bool NARROW, class Request>
+template <int DT, int MODE, int RES, int CELL, bool WAIT, bool NARROW, class Look, class Request>
 __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLane& c, const TileAt& t, float* part, u32x4* turns, const TileRows<MODE>& p,
                                                 TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& q, const float (&bias)[Tile<MODE>::G],
                                                 const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, const TailWait& w, uint32_t* failed,
-                                                Request request) {
+                                                Look look, Request request) {
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   typedef Tile<MODE> TL;
@@ -841,7 +851,16 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
         look_rows<T, MODE, LEAST>(tw, narrow, st0, cnt, open, o0, o1, fa, u0, u1);
         return !still_open();
       };
-      if (__builtin_expect(!__all(attempt()), 0))
+      bool there = false;
+      if constexpr (TileAhead<T, MODE, RES, CELL>::LOOK) {
+        if (q.looked) {
+#pragma unroll
+          for (int st = 0; st < RES; ++st) fa[st] = q.look[st];
+          u0 = q.look_u0;
+          there = !__any(still_open());
+        }
+      }
+      if (!there && __builtin_expect(!__all(attempt()), 0))
         if (!wait_rows(w, attempt)) *failed = 1u;
       // (Whatever was requested is here by now.  Said in so many words, or the compiler, which does not know that on the way
       // past the loads above, waits for the tile's stores before the next tile's first look.)
@@ -891,6 +910,7 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
         }
     }
   }
+  look();
   // partial tiles -> LDS; every lane sums and finishes its element
 #pragma unroll
   for (int j = 0; j < TL::NB; ++j)
@@ -982,13 +1002,13 @@ __global__ void __launch_bounds__(Tile<MODE>::NW * 64) k_cell_small(GemmArgs g) 
   __shared__ u32x4 turns[Tile<MODE>::NW * TURN];
   stamp_now(g.stamp);
   const int rt = blockIdx.x / g.n_tiles_n, ct = blockIdx.x % g.n_tiles_n;   // (column tiles of one row tile side by side)
-  const TileAt t{(uint32_t)rt * Tile<MODE>::ROWS, min(Tile<MODE>::ROWS, g.M - rt * Tile<MODE>::ROWS), ct};
+  const TileAt t{(uint32_t)rt * Tile<MODE>::ROWS, min(Tile<MODE>::ROWS, g.M - rt * Tile<MODE>::ROWS), ct, 0};
   TileRows<MODE> p;
   TileAhead<typename TypeOf<DT>::type, MODE, 0, 0> q;
   const TileLane c = tile_lane<DT, MODE>(g);
   tile_rows<MODE>(g, c, t, p);
   tile_ahead<DT, MODE, 0, 0>(g, c, t, nullptr, p, q);
-  cell_small_tile<DT, MODE, 0, 0, false, false>(g, c, t, part, turns, p, q, q.bias, (const TileB<MODE, 1>*)nullptr, nullptr, TailWait{}, nullptr, [] {});
+  cell_small_tile<DT, MODE, 0, 0, false, false>(g, c, t, part, turns, p, q, q.bias, (const TileB<MODE, 1>*)nullptr, nullptr, TailWait{}, nullptr, [] {}, [] {});
 }
 
 // Levels of at most this many cells take the small-level kernel where they are launched one by one (TDF_SMALL_LEVEL overrides).
@@ -1357,6 +1377,8 @@ template <int DT, int MODE, int RES, int CELL, bool NARROW>
 __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& ta, uint32_t die, uint32_t rank, uint32_t G, float* part, u32x4* turns,
                                             const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, uint32_t* failed) {
   typedef Tile<MODE> TL;
+  typedef typename TypeOf<DT>::type T;
+  typedef TileAhead<T, MODE, RES, CELL> Ahead;
   DieSync* const sy = ta.sync + die;
   const TailWait w{sy, ta.spin_ticks};
   const uint32_t n_ct = (uint32_t)g.n_tiles_n;
@@ -1379,12 +1401,12 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
     const uint32_t rows = (end - q0 + TL::ROWS - 1) / TL::ROWS, row = RES > 0 ? t : t / n_ct;
     if (row >= rows) return false;
     const uint32_t at = q0 + row * TL::ROWS;
-    r = TileAt{at, (int)min((uint32_t)TL::ROWS, end - at), (int)(RES > 0 ? rank % n_ct : t % n_ct)};
+    r = TileAt{at, (int)min((uint32_t)TL::ROWS, end - at), (int)(RES > 0 ? rank % n_ct : t % n_ct), k};
     t += step;
     return true;
   };
   auto next = [&]() -> TileAt {
-    TileAt r{0, 0, 0};
+    TileAt r{0, 0, 0, 0};
     if (tile_of(r) || k + 1 >= n_lvl) return r;
     take(next_q0, next_end);
     for (++k, t = first; !tile_of(r) && k + 1 < n_lvl; t = first) {   // (levels without a tile for this workgroup)
@@ -1413,7 +1435,7 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
   TileAt t2 = next(), t3;
   offsets(k + 1, next_q0, next_end);
   TileRows<MODE> p0{}, p1{}, p2{}, p3{};
-  TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL> a0{}, a1{};
+  Ahead a0{}, a1{};
   tile_rows<MODE>(g, c, t0, p0);
   tile_rows<MODE>(g, c, t1, p1);
   tile_rows<MODE>(g, c, t2, p2);
@@ -1423,12 +1445,21 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
   // A tile, and behind its own loads the requests for the next one, the rows of the children's children for the one after
   // that and the rows of a third.  The registers that these go to take turns by name: a copy from tile to tile would wait
   // for them in the middle of the tile that has just asked.
-  auto tile = [&](uint32_t side, const TileAt& t, const TileRows<MODE>& p, TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& a, const TileAt& ta1,
-                  const TileRows<MODE>& pa1, TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& a1, const TileAt& ta2, TileRows<MODE>& pa2, TileAt& ta3,
+  auto tile = [&](uint32_t side, const TileAt& t, const TileRows<MODE>& p, Ahead& a, const TileAt& ta1,
+                  const TileRows<MODE>& pa1, Ahead& a1, const TileAt& ta2, TileRows<MODE>& pa2, TileAt& ta3,
                   TileRows<MODE>& pa3) __attribute__((always_inline)) {
     // (The end of the program, not a way out of the loop: the compiler joins such ways, with copies and waits where they meet.)
     if (!t.M) __builtin_amdgcn_endpgm();
     const bool ok = cell_small_tile<DT, MODE, RES, CELL, true, NARROW>(g, c, t, part + side * TL::PART, turns, p, a, RES > 0 ? bias : a.bias, b, fz, w, failed + side, [&] {
+      if constexpr (Ahead::LOOK) {
+        a1.looked = ta1.M && ta1.lvl == t.lvl;
+        if (a1.looked) {
+          const auto tw = tile_waits<DT, MODE, CELL>(g, c, ta1, pa1, fz);
+          uint32_t none;
+          look_rows<T, MODE, least_steps(RES)>(tw, true, 0, c.n, tw.fresh, tw.f0, false, a1.look, a1.look_u0, none);
+        }
+      }
+    }, [&] {
       ta3 = next();
       tile_rows<MODE>(g, c, ta3, pa3);
       tile_rows2<DT, MODE, CELL>(g, c, ta2, fz, pa2);

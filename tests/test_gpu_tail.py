@@ -35,6 +35,27 @@ def test_forward_and_gradients_at_the_widths_where_the_tiles_change(cfg, hidden,
             assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < tol, name
 
 
+# A die's level of more than 16 cells is several tiles for one workgroup, the last of which is not full: those behind the first find
+# their rows looked for already.
+@pytest.mark.parametrize("bf16", [True, False], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("hidden,trees,leaves", [(40, 8, 70), (64, 130, 12), (150, 190, 30)])
+def test_gradients_of_levels_of_several_tiles(hidden, trees, leaves, bf16):
+    c = make_config(4, n_trees=trees, max_leaves=leaves, hidden=hidden, vocab=200)
+    c["bf16"] = bf16
+    B = c["forest"].n_trees
+    dy = np.full(B, 1.0 / B)
+    ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
+    run = TreeRun(c, head=True, grad=True, stats_level=0)
+    tol = 2e-2 if bf16 else 2e-5   # (the bars of the other gradient tests)
+    for _ in range(2):
+        st, stats = run.run(dy)
+        assert stats.tail_used == 1 and stats.repeats == 0
+        assert stats.n_grad_not_once == 0 and stats.n_grad_firings == c["forest"].n_nodes
+        assert rel_fro(run.out_f32.cpu().numpy(), np.array(ref["out"])) < tol
+        for name, t in (("dW", run.dW), ("db", run.db), ("dE", run.dE)):
+            assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < tol, name
+
+
 @pytest.mark.parametrize("cfg", [3, 4])
 def test_offsets_beyond_32_bits(cfg, monkeypatch):
     import os

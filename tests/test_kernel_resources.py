@@ -69,3 +69,10 @@ def code(objects):
 def test_small_tiles_have_four_steps_of_the_reduction_in_flight(code, mode, blocks, dtype):
     """A step is a chunk of the rows and one of every column block's weights, 16 bytes a lane."""
     assert code[("k_cell_small", dtype, mode)].count("global_load_dwordx4") >= 4 * (1 + blocks)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_gradient_tiles_of_a_tree_lstm_look_for_the_next_ones_rows(code, dtype):
+    """Four copies of a tile's code take turns; each looks for the five chunk steps of the next one, beside its own looks."""
+    looks = [code[("k_tail_bwd", dtype, cell, 5)].count("buffer_load_dwordx4") for cell in (1, 2)]
+    assert looks[1] >= looks[0] + 4 * 5
