@@ -827,7 +827,8 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
   else Ap = reinterpret_cast<const T*>(g.Hs) + (p.child * (uint32_t)g.Hp + c.a);
   TileWaits<T, MODE> tw{};
   if constexpr (WAIT) tw = tile_waits<DT, MODE, CELL>(g, c, t, p, fz);
-  const bool narrow = MODE == DX_BWD || NARROW || g.fresh_narrow, fresh = tw.fresh;
+  constexpr bool narrow = MODE == DX_BWD || NARROW;
+  const bool fresh = tw.fresh;
   const int unit = t.ct * TL::UNITS + c.col;
   const bool el = c.row < t.M;   // the lane's element exists
   const bool z_left = unit < g.Hp;
@@ -868,17 +869,15 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
     }
   };
   if constexpr (RES > 0) {
-    // (Forward, NARROW: the look's lanes join those whose rows were there before, in the same registers.)
+    // (Forward: the look's lanes join those whose rows were there before, in the same registers.  With others and a choice behind it the
+    // variants for rows beyond 4 GiB took 120 to 125 and had half the workgroups: 1,024 sentences of a TreeRNN of 512 units 310 us, now
+    // 250, with 32 bits 242.)
     u32x4 fw[RES];
-    constexpr bool JOIN = MODE != DX_BWD && NARROW;
-    u32x4 (&fa)[RES] = [&]() -> u32x4 (&)[RES] { if constexpr (JOIN) return q.a; else return fw; }();
+    u32x4 (&fa)[RES] = [&]() -> u32x4 (&)[RES] { if constexpr (MODE != DX_BWD) return q.a; else return fw; }();
     await(fa, 0, n);
 #pragma unroll
     for (int st = 0; st < RES; ++st)
-      if (st < least_steps(RES) || st < n) {
-        if constexpr (MODE != DX_BWD && !JOIN) fa[st] = fresh ? fa[st] : q.a[st];
-        fa[st] = turn(turns + wave * TURN, fa[st]);
-      }
+      if (st < least_steps(RES) || st < n) fa[st] = turn(turns + wave * TURN, fa[st]);
 #pragma unroll
     for (int st = 0; st < RES; ++st)
       if (st < least_steps(RES) || st < n) {
@@ -1573,11 +1572,10 @@ __device__ __forceinline__ void tail_begin(DieSync* sy, uint32_t* failed) {
 // Workgroups of eight waves that share a compute unit with another of their kind have two waves each on a SIMD.  Four times 128
 // registers would fill it, and a wave of a small kernel on another stream (the token sort: 16 registers) that happens to be there
 // when they are placed leaves a hole that the fourth never fits into: the compute unit holds one workgroup for good, and the
-// others wait for it until the launch gives up.  So these should take at most 112 (TreeRNN forward 102 and 105, gradient 107); the
-// forward variant for rows beyond 4 GiB, which takes more, has a compute unit to itself, and so has the one that fetches its
-// weights for every tile.
+// others wait for it until the launch gives up.  So these should take at most 112 (TreeRNN forward 102 to 109, gradient 107); the
+// variants that take more, of which one fetches its weights for every tile, have a compute unit to themselves.
 template <int DT, int MODE, int RES, bool NARROW>
-__global__ void __launch_bounds__(Tile<MODE>::NW * 64, RES == 8 || (MODE == RNN_FWD && (RES == 0 || !NARROW)) ? (MODE == RNN_FWD ? 2 : 1) : Tile<MODE>::NW / 2)
+__global__ void __launch_bounds__(Tile<MODE>::NW * 64, MODE == LSTM_FWD ? (RES == 8 ? 1 : 2) : (RES == 2 || RES == 4 ? 4 : 2))
 k_tail_fwd(GemmArgs g, TailArgs t) {
   typedef typename TypeOf<DT>::type T;
   typedef Tile<MODE> TL;
@@ -2196,7 +2194,7 @@ static int tail_wgs(int slots, int n_ct, uint32_t row_tiles) {
 }
 // Workgroups of a pass that are on a die's compute units together, where a wave keeps the operands of n chunk steps: two share
 // a compute unit, but for the variants with most weights in registers.
-static int tail_slots_fwd(int cus_per_die, int n, bool narrow) { return cus_per_die * (n <= 4 && narrow ? 2 : 1); }
+static int tail_slots_fwd(int cus_per_die, int n) { return cus_per_die * (n <= 4 ? 2 : 1); }
 static int tail_slots_bwd(int cus_per_die, int n, int cell_kind) { return cus_per_die * (n <= 5 && cell_kind == 1 ? 2 : 1); }
 template <typename T, int MODE, int RES> static void launch_tail_fwd(const GemmArgs& g, const TailArgs& t, int wgs, hipStream_t s) {
   const dim3 grid((wgs + 1) * (int)XCDS), block(Tile<MODE>::NW * 64);
@@ -2206,7 +2204,7 @@ template <typename T, int MODE, int RES> static void launch_tail_fwd(const GemmA
 template <typename T, int MODE> static void tail_fwd_mode(GemmArgs g, const TailArgs& t, int cus_per_die, uint32_t row_tiles, hipStream_t s) {
   g.n_tiles_n = g.Hp / Tile<MODE>::UNITS;
   const int n = Tile<MODE>::steps_most(g.K / Chunk<T>::KC);
-  const int wgs = tail_wgs(tail_slots_fwd(cus_per_die, n, MODE == LSTM_FWD || g.fresh_narrow), g.n_tiles_n, row_tiles);
+  const int wgs = tail_wgs(tail_slots_fwd(cus_per_die, n), g.n_tiles_n, row_tiles);
   if (wgs && n <= 2) launch_tail_fwd<T, MODE, 2>(g, t, wgs, s);
   else if (wgs && n <= 4) launch_tail_fwd<T, MODE, 4>(g, t, wgs, s);
   else if (wgs && n <= 8) launch_tail_fwd<T, MODE, 8>(g, t, wgs, s);
@@ -2255,7 +2253,7 @@ TailLimit vec_tail_limit(const VecArgs& v, int cus_per_die, bool backward) {
   } else {
     const int n = lstm ? Tile<LSTM_FWD>::steps_most(v.Kp / kc) : Tile<RNN_FWD>::steps_most(v.Kp / kc);
     n_ct = v.Hp / (lstm ? Tile<LSTM_FWD>::UNITS : Tile<RNN_FWD>::UNITS);
-    wgs = n > 8 ? 0 : tail_wgs(tail_slots_fwd(cus_per_die, n, true), n_ct, 1u << 20);
+    wgs = n > 8 ? 0 : tail_wgs(tail_slots_fwd(cus_per_die, n), n_ct, 1u << 20);
   }
   return TailLimit{0xFFFFFFFFu, std::min(1024u, std::max(128u, (uint32_t)(wgs / n_ct) * (backward ? (lstm ? 128u : 160u) : (lstm ? 80u : 128u))))};
 }

@@ -74,6 +74,25 @@ def test_offsets_beyond_32_bits(cfg, monkeypatch):
         assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < 2e-2, name
 
 
+@pytest.mark.parametrize("cfg,hidden", [(2, 256), (3, 512), (4, 512)])
+def test_offsets_beyond_32_bits_at_the_widest_rows_that_share_a_compute_unit(cfg, hidden, monkeypatch):
+    # (rows that are there before the launch and rows that are waited for, in one tile; as many levels in the tail as with 32 bits)
+    import os
+    hooks = tdf.load_library(os.path.join(os.path.dirname(tdf.__file__), "libtdf_hooks.so"))
+    c = make_config(cfg, n_trees=200, max_leaves=12, hidden=hidden, vocab=200)
+    got = []
+    for wide in (False, True):
+        if wide:
+            monkeypatch.setenv("TDF_TEST_WIDE_OFFSETS", "1")
+        with tdf.use_library(hooks):
+            run = TreeRun(c, head=True, grad=False, stats_level=0)
+            for _ in range(2):
+                st, stats = run.run()
+                assert stats.tail_used == 1 and stats.repeats == 0
+        got.append((run.out_f32.clone(), stats.n_wide_waves))
+    assert torch.equal(got[0][0], got[1][0]) and got[0][1] == got[1][1]
+
+
 @pytest.mark.parametrize("pattern", [-1, 0x7FC0])
 @pytest.mark.parametrize("cfg", [3, 4])
 def test_nans_pass_through(cfg, pattern):

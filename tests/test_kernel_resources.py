@@ -51,6 +51,11 @@ def test_two_tails_on_a_compute_unit_leave_room_for_other_kernels(kernels):
     assert len(two) == 6 and all(kernels[k][0] <= 112 for k in two)
 
 
+def test_so_do_those_for_rows_beyond_4_gib(kernels):
+    wide = [k for k in kernels if k[0] == "k_tail_fwd" and k[2] == 0 and k[3] in (2, 4) and k[4] == 0]
+    assert len(wide) == 4 and all(kernels[k][0] <= 112 for k in wide)
+
+
 @pytest.fixture(scope="module")
 def code(objects):
     """{(kernel, dtype, template arguments): instructions} of the kernels that multiply small tiles."""
