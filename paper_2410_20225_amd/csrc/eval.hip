@@ -23,7 +23,7 @@ tdf_status launch_round(const DevProgram& P, const Engine& e, int cus, bool loca
                         long long spin_ticks, const JitKernels& jit, hipStream_t s);
 void launch_lane_init(const LaneArgs& a, const Stamp& st, hipStream_t s);
 tdf_status launch_lanes(const LaneArgs& a, int n_stored, const JitKernels& jit, hipStream_t s);
-void launch_forest_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s);
+int launch_forest_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s);
 void launch_lane_sort(const Engine& e, const LaneArgs& a, const LaneLimits& lim, uint32_t* row_node, LaneTotals* totals,
                       LaneReport* report, uint32_t* pin_off, uint32_t pin_keys, uint32_t seq, const Stamp& st, hipStream_t s);
 void launch_finish(const LaneArgs& a, const EndArgs& g, const Stamp& st, hipStream_t s);
@@ -606,9 +606,10 @@ tdf_status run(tdf_graph* gr, const tdf_inputs* in, const tdf_seed* dy, tdf_outp
     a.tags_at_once = std::max(64u, e.max_tags / (2u * a.n_waves));
     if (P.vec) vec_pack_w(on(s), &a, base + P.L.zero_begin, P.L.zero_end - P.L.zero_begin, s);
     else launch_lane_init(a, take(s), s);
-    if (use_walk) launch_forest_walk(a, gr->walk, take(s), s);
+    int tag_launches = 1;
+    if (use_walk) tag_launches = launch_forest_walk(a, gr->walk, take(s), s);
     else if (tdf_status ls = launch_lanes(a, P.n_stored, gr->jit, s); ls != TDF_OK) return ls;
-    end(TDF_PHASE_TAGS, 2);
+    end(TDF_PHASE_TAGS, 1 + tag_launches);
     LaneTotals lt;
     if (P.vec) {
       // Everything that does not need the host to know the run's sizes is queued behind the lanes: rows, order

@@ -6,7 +6,8 @@
 // alone: a leaf fires its EMBED, an inner node its cell when both children have, one level above the higher of them.
 // A tree that lies in one piece is numbered where it lies (tree_in_piece).  Any other one wave walks, an instance each: a
 // lane goes down to the left child and leaves the right one on a stack in LDS, which lanes without a node take from; a
-// leaf turns the lane round, and the second of two children that arrive at their parent goes on up.  The schedule log is indexed by node, so a value's name is its node.
+// leaf turns the lane round, and the second of two children that arrive at their parent goes on up.  The schedule log is
+// indexed by node, so a value's name is its node.
 //
 // The rule: programs of that form (walk_form, below) and forests of at most as many nodes as the log has entries.  One wave
 // works on an instance, at 32 nodes a step where the tree is wide, 0.02 to 0.03 us a node; the lanes share a tree
@@ -323,18 +324,9 @@ __device__ __forceinline__ bool tree_in_piece(const LaneArgs& a, const WalkForm&
   return true;
 }
 
-template <int THREADS, int WINDOW>
-__global__ void __launch_bounds__(THREADS) k_forest_walk(LaneArgs a, WalkForm w, Stamp st) {
-  extern __shared__ uint32_t lds[];   // a piece's words and heights, or the walk's stack
-  __shared__ uint32_t s_tot[THREADS / 64], s_end;
-  stamp_now(st);
-  const uint32_t lane = threadIdx.x, b = blockIdx.x, n_nodes = (uint32_t)a.n_tree_nodes;
-  const long long root = a.args[(size_t)b * a.n_args + w.root_arg];
-  if (root >= 0 && root < (long long)n_nodes &&
-      tree_in_piece<THREADS, WINDOW>(a, w, b, (uint32_t)root, lds, lds + WINDOW, s_tot, &s_end))
-    return;
-  __syncthreads();   // (the others are through with the piece's words)
-  if (THREADS > 64 && lane >= 64u) return;
+// One wave walks the tree of instance b.  `lds`: 3 * WALK_STACK words.
+__device__ __forceinline__ void walk_tree(const LaneArgs& a, const WalkForm& w, uint32_t b, long long root, uint32_t* lds) {
+  const uint32_t lane = threadIdx.x, n_nodes = (uint32_t)a.n_tree_nodes;
   uint32_t* const s_node = lds;
   uint32_t* const s_parent = lds + WALK_STACK;
   uint32_t* const s_depth = lds + 2 * WALK_STACK;
@@ -479,19 +471,60 @@ __global__ void __launch_bounds__(THREADS) k_forest_walk(LaneArgs a, WalkForm w,
     walk_count(a, b, leaves, cells, most + 64u, md, ml, iter);
   }
 }
-template <int THREADS, int WINDOW> static void launch_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s) {
-  constexpr size_t lds = sizeof(uint32_t) * (2 * WINDOW > 3 * (int)WALK_STACK ? 2 * WINDOW : 3 * (int)WALK_STACK);
+
+// A workgroup an instance: the tree in one piece, or (walks) what fails as one is walked by the first wave, or left to k_forest_walk.
+template <int WINDOW> constexpr size_t piece_lds() {
+  return sizeof(uint32_t) * (2 * WINDOW > 3 * (int)WALK_STACK ? 2 * WINDOW : 3 * (int)WALK_STACK);
+}
+template <int THREADS, int WINDOW>
+__global__ void __launch_bounds__(THREADS) k_forest_pieces(LaneArgs a, WalkForm w, bool walks, Stamp st) {
+  extern __shared__ uint32_t lds[];   // a piece's words and heights, or the walk's stack
+  __shared__ uint32_t s_tot[THREADS / 64], s_end;
+  stamp_now(st);
+  const uint32_t b = blockIdx.x;
+  const long long root = a.args[(size_t)b * a.n_args + w.root_arg];
+  if (root >= 0 && root < (long long)a.n_tree_nodes &&
+      tree_in_piece<THREADS, WINDOW>(a, w, b, (uint32_t)root, lds, lds + WINDOW, s_tot, &s_end))
+    return;
+  if (!walks) {
+    if (threadIdx.x == 0) a.root_lvl[b] = WALK_NONE;
+    return;
+  }
+  __syncthreads();   // (the others are through with the piece's words)
+  if (THREADS > 64 && threadIdx.x >= 64u) return;
+  walk_tree(a, w, b, root, lds);
+}
+// The instances that k_forest_pieces has left, in workgroups of the walk's own size.
+__global__ void __launch_bounds__(64) k_forest_walk(LaneArgs a, WalkForm w) {
+  __shared__ uint32_t lds[3 * WALK_STACK];
+  const uint32_t b = blockIdx.x;
+  if (a.root_lvl[b] != WALK_NONE) return;
+  walk_tree(a, w, b, a.args[(size_t)b * a.n_args + w.root_arg], lds);
+}
+
+template <int THREADS, int WINDOW> static void launch_pieces(const LaneArgs& a, const WalkForm& w, bool walks, const Stamp& st, hipStream_t s) {
+  constexpr size_t lds = piece_lds<WINDOW>();
   if (lds > 48 * 1024)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_forest_walk<THREADS, WINDOW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_forest_walk<THREADS, WINDOW>), dim3(a.n_inst), dim3(THREADS), lds, s, a, w, st);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_forest_pieces<THREADS, WINDOW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_forest_pieces<THREADS, WINDOW>), dim3(a.n_inst), dim3(THREADS), lds, s, a, w, walks, st);
 }
 // The workgroup and its window by the nodes of an instance on average: room for a few times as many, where that leaves a compute unit enough
-// instances to work on.
-void launch_forest_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s) {
+// instances to work on.  Number of launches.
+// What is no piece is walked in workgroups of 64 threads and 6 KB, 26 of which fit a compute unit, in a launch of its own: one
+// wave would hold the 32 or 128 KB of a piece (five or one on a compute unit) for as long as it walks.  In random order, all in
+// one launch -> two, tag phase in us: 512 chains of 3,500 leaves 10,190 -> 5,070, 512 random trees of 3,500 567 -> 463, 2,048 of
+// 600 550 -> 348, 4,096 of 800 1,316 -> 852 (1,024 of 300 leaves, five a compute unit at once: 87 -> 102).  Up to two instances of 32 KB a compute unit all are resident anyway and leave room for
+// two workgroups of another evaluation's level tails (90 KB), and the second launch is only in the way: 256 trees of up to 50
+// leaves 14 -> 20 us in order, 30 -> 39 in random order, 200 of 400 21 -> 24 and 68 -> 79.
+int launch_forest_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s) {
   const uint32_t average = (uint32_t)a.n_tree_nodes / a.n_inst;
-  if (average > 1024u) launch_walk<1024, 16384>(a, w, st, s);
-  else if (average > 192u || a.n_inst <= 256u) launch_walk<256, 4096>(a, w, st, s);
-  else launch_walk<64, 512>(a, w, st, s);
+  const bool large = average > 1024u, small = average <= 192u && a.n_inst > 256u;
+  const bool walks = small || (!large && a.n_inst <= 512u);
+  if (large) launch_pieces<1024, 16384>(a, w, walks, st, s);
+  else if (small) launch_pieces<64, 512>(a, w, walks, st, s);
+  else launch_pieces<256, 4096>(a, w, walks, st, s);
+  if (!walks) hipLaunchKernelGGL(k_forest_walk, dim3(a.n_inst), dim3(64), 0, s, a, w);
+  return walks ? 1 : 2;
 }
 
 }  // namespace tdf

@@ -362,3 +362,67 @@ def test_pieces_that_are_none(what, order):
         roots = roots[1::2]
     got = _same(programs.tree("lstm", True), (l, r, t, roots), left=left, max_tags=4 * l.size)[0]
     assert got == st if st is not None else got != tdf.OK
+
+
+# ---- the same for every size of window, beside as many and as large trees as it takes; what is no piece is walked in the same launch (one
+# wave a workgroup, or up to 512 instances of 4,096 nodes) or in one of its own
+BESIDE = {
+    "waves1": lambda rng: [_random(int(n), rng) for n in rng.integers(2, 40, 300)],
+    "waves4": lambda rng: [_random(int(n), rng) for n in rng.integers(2, 40, 200)],
+    "waves4_apart": lambda rng: [_random(int(n), rng) for n in rng.integers(100, 160, 520)],
+    "waves16": lambda rng: [_random(3000, rng), _chain(1500), _complete(11)],
+}
+
+
+def _broken(what, forest, first):
+    """-> forest, whether it is left to the lanes, status; the trees from `first` on stay as they are."""
+    l, r, t, roots = [x.copy() for x in forest]
+    inner = [next(v for v in (l[x], r[x]) if l[v] >= 0) for x in roots[:first]]
+    left, st = False, tdf.OK
+    if what == "a_child_before_its_parent":   # an inner node and the last of its subtree change places
+        name = np.arange(l.size)
+        v = inner[1]
+        low = r[v] if l[r[v]] < 0 else l[v]
+        name[[v, low]] = name[[low, v]]
+        new = lambda x: np.where(x >= 0, name[np.maximum(x, 0)], -1)  # noqa: E731
+        l2, r2, t2 = np.empty_like(l), np.empty_like(r), np.empty_like(t)
+        l2[name], r2[name], t2[name] = new(l), new(r), t
+        l, r, t, roots = l2, r2, t2, name[roots]
+    elif what == "right_is_left":
+        r[inner[1]], left = l[inner[1]], True
+    elif what == "a_child_of_two_trees":
+        r[inner[1]], left = l[inner[3]], True
+    elif what == "a_root_inside_another_tree":
+        roots[1], left = inner[0], True
+    elif what == "a_cycle":
+        leaf = inner[0]
+        while l[leaf] >= 0:
+            leaf = r[leaf]
+        l[leaf], r[leaf], st = inner[0], inner[0], None
+    elif what == "right_missing":
+        r[inner[2]], st = -1, tdf.ERR_BAD_ARG
+    elif what == "right_out_of_range":
+        r[inner[2]], st = l.size, tdf.ERR_BAD_ARG
+    elif what == "token_out_of_range":
+        t[np.nonzero(l < 0)[0][7]], st = V, tdf.ERR_BAD_ARG
+    elif what == "root_out_of_range":
+        roots[2], st = l.size, tdf.ERR_BAD_ARG
+    return (l, r, t, roots), left, st
+
+
+@pytest.mark.parametrize("size", BESIDE)
+@pytest.mark.parametrize("what", ["a_child_before_its_parent", "right_is_left", "a_child_of_two_trees", "a_root_inside_another_tree", "a_cycle",
+                                  "right_missing", "right_out_of_range", "token_out_of_range", "root_out_of_range"])
+def test_pieces_that_are_none_beside_others(what, size):
+    rng = np.random.default_rng(11)
+    some = [_chain(40), _random(30, rng), _complete(4), _random(25, rng)]
+    forest, left, st = _broken(what, _in_pieces(some + BESIDE[size](rng), "depth", rng), 4)
+    got = _same(programs.tree("lstm", True), forest, left=left, max_tags=4 * forest[0].size)[0]
+    assert got == st if st is not None else got != tdf.OK
+
+
+@pytest.mark.parametrize("size", BESIDE)
+def test_forests_in_random_order(size):
+    rng = np.random.default_rng(12)
+    stats = _same(programs.tree("lstm", True), _trees([_chain(300), _complete(5)] + BESIDE[size](rng), rng))[3]
+    assert stats.n_steps > 300

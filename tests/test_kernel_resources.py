@@ -81,3 +81,17 @@ def test_gradient_tiles_of_a_tree_lstm_look_for_the_next_ones_rows(code, dtype):
     """Four copies of a tile's code take turns; each looks for the five chunk steps of the next one, beside its own looks."""
     looks = [code[("k_tail_bwd", dtype, cell, 5)].count("buffer_load_dwordx4") for cell in (1, 2)]
     assert looks[1] >= looks[0] + 4 * 5
+
+
+def test_a_walk_holds_no_more_than_its_stack(objects):
+    """26 workgroups of the walk fit a compute unit (and its waves beside those of other kernels), however large the windows are in which
+    trees are looked for in one piece."""
+    sizes = {}
+    for f in objects:
+        for k in _notes(f).split("  - .agpr_count:")[1:]:
+            name = re.search(r"\.name:\s+\S*?(k_forest_\w+?)(?=E|I)", k)
+            if name:
+                one = [int(re.search(r"\.%s:\s+(\d+)" % x, k).group(1)) for x in ("max_flat_workgroup_size", "group_segment_fixed_size")]
+                sizes.setdefault(name.group(1), []).append(one)
+    assert len(sizes["k_forest_pieces"]) == 3
+    assert all(threads == 64 and lds <= 160 * 1024 // 26 for threads, lds in sizes["k_forest_walk"])
