@@ -775,7 +775,7 @@ struct Gen {
   // that has left its loop keeps its variables, and the wave looks up every fourth time whether anybody goes on.  Which
   // entries are live is a function of the loop's predicates; with truth tables of up to six of them most of it comes out
   // constant, a Merge is one choice, and going on one predicate.  An iteration of subtractive gcd is 17 instructions; with
-  // a way out of the loop in every iteration and the presence of every entry looked at it was 50 and 168 ticks, and
+  // a way out of the loop in every iteration and the presence of every entry looked at it was 50 and 168 clocks, and
   // 65,536 pairs up to 1,024 took 136 us, not 96 (both with 64 iterations a sweep).
   void iterations(int f) {
     const int nv = P.fn[f].n_params;
@@ -801,7 +801,8 @@ struct Gen {
     if (n_args != nv || all.k == 0) return;   // no iteration has a next one
     o << "        uint32_t n_it = 0;\n";
     for (int k = 0; k < nv; ++k) o << "        long long u" << k << " = x.sv[" << k << "];\n";
-    o << "        for (uint32_t k = 0; k < LANE_LOOP / 4; ++k) {\n        bool any = false;\n#pragma unroll\n        for (int h = 0; h < 4; ++h) {\n"
+    o << "        const uint32_t share = __ballot(x.run && !on) ? LANE_LOOP_BESIDE : LANE_LOOP;\n";
+    o << "        for (uint32_t k = 0; k < share / 4; ++k) {\n        bool any = false;\n#pragma unroll\n        for (int h = 0; h < 4; ++h) {\n"
       << c.str() << next << "        any = on && " << all.e << ";\n";
     for (int k = 0; k < nv; ++k) o << "        u" << k << " = any ? w" << k << " : u" << k << ";\n";
     o << "        n_it += any ? 1u : 0u;\n        }\n        if (__ballot(any) == 0) break;\n        }\n        if (on) {\n";
@@ -946,7 +947,7 @@ struct Gen {
     // One state after the other, those that some lane is in.  A lane whose call was evaluated in place is in a later state
     // then and comes up again.  A sweep is bound by the instructions of the states its lanes are in.  A loop that takes the
     // next lane's state and switches to its code, with a state for each set of outstanding calls, cost 20 copies of the
-    // lane's registers a turn and a tree of branches: 1,950 ticks a sweep for fib, 2,800 for tak.  fib(30..32) takes 3,230 us
+    // lane's registers a turn and a tree of branches: 1,950 clocks a sweep for fib, 2,800 for tak.  fib(30..32) takes 3,230 us
     // now, not 4,090; 256 of tak 1,695, not 2,360; fib(0..20) 165, not 189; eight small ones 70, not 77.
     if (unlisted) o << "    bool known = false;\n";
     for (const State& t : states) {

@@ -59,10 +59,12 @@ constexpr uint32_t LANE_YOUNG = 12000;  // ticks (100 MHz) for which a run is yo
 constexpr uint32_t LANE_EARLY = 48;     // sweeps during which a wave gives work away although it has lanes without any
 // idle lanes up to which a wave gives calls to other waves
 constexpr uint32_t LANE_GIVE = 56;
-// Iterations of a loop without calls in one sweep (a multiple of four).  A sweep has some 2,000 ticks of its own and an
-// iteration of subtractive gcd takes 80: 65,536 pairs up to 1,024 took 96 us with 64, 86 with 256; the longest loop of the
-// batch, which is what the run waits for, has at most 1,023 iterations.
-constexpr uint32_t LANE_LOOP = 256;
+// Iterations of a loop without calls in one sweep (multiples of four): where no lane of the wave has anything else to do, and
+// beside others, which wait for the sweep's end.  A sweep costs as much as tens of iterations (of subtractive gcd, 80 clocks each):
+// 65,536 gcds of pairs up to 1,024 take 102 us with 64 a sweep, 97 with 128 and 96 with 256.  A recursion whose 4,096 leaves are loops of 1
+// to 651 iterations takes 230 us with 64, 232 with 128, 250 with 256 and 230 with this; 64 of 256 such leaves 157, 162, 170 and 157; with
+// loops of 1 to 4,096, of which few are long, 370, 337, 321 and 323.
+constexpr uint32_t LANE_LOOP = 256, LANE_LOOP_BESIDE = 64;
 constexpr uint32_t LANE_RECS = 96;      // records of a wave
 constexpr uint32_t LANE_SCARCE = 8, LANE_FEW = 16;   // free records below which all frames below a given one take one; else the first so many take one each
 constexpr uint32_t LANE_QUEUE = 128;    // tasks of a wave (at least LANE_RECS: a record is queued at most once)

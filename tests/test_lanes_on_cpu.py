@@ -81,6 +81,35 @@ def test_iterations_of_loops_with_choices(n_choices, nested, tmp_path):
         assert got["tags"] == sum(n + 1 for n, _ in args) and got["depth"] == 1
 
 
+def _call_and_loop():
+    """result(n, s) = down(n) + { i = s; a = 0; while 0 < i: a = a + i; i = i - 1 } a, down(n) = if n < 1 then n else down(n - 1) + 1"""
+    T = programs.T
+    r = programs._Fn("result", 2)
+    n, s = r.add(T.OP_IN, imm=0), r.add(T.OP_IN, imm=1)
+    r.add(T.OP_OUT, [r.add(T.OP_ADD, [r.add(T.OP_CALLFN, [n], imm=1), r.add(T.OP_LOOP, [s, r.add(T.OP_SUB, [s, s])], imm=2)])])
+    d = programs._Fn("down", 1)
+    v, one = d.add(T.OP_IN, imm=0), d.add(T.OP_CONST, imm=1)
+    sw = d.add(T.OP_SWITCH, [d.add(T.OP_LT, [v, one]), v])
+    low, high = (sw[0], 0), (sw[0], 1)
+    rec = d.add(T.OP_CALLFN, [d.add(T.OP_SUB, [high, one])], imm=1)
+    d.add(T.OP_OUT, [d.add(T.OP_MERGE, [d.add(T.OP_ID, [low]), d.add(T.OP_ADD, [rec, one])])])
+    return [r.desc(), d.desc(), programs._counting_loop("S", 2, programs._sum_step).desc()], 0
+
+
+def test_a_long_loop_leaves_the_wave_s_other_lanes_their_turns(tmp_path):
+    # One lane's loop, alone in its wave, takes 256 iterations a sweep; beside a recursion of another lane 64: each of
+    # the recursion's sweeps waits for that many, not for 256.
+    lanes = Lanes(_call_and_loop(), tmp_path)
+    iterations, depth = 6400, 20
+    alone = lanes.run([(0, iterations)], waves=1)
+    beside = lanes.run([(0, iterations), (depth, 0)], waves=1)
+    for got, n in ((alone, 0), (beside, depth)):
+        assert got["status"] == 0 and got["out"] == [iterations * (iterations + 1) // 2] + [n] * (n > 0)
+    assert alone["sweeps"] <= iterations // 256 + 8
+    # the recursion's sweeps (one down and one up a level, the last ones in place) are of 64 iterations each
+    assert beside["sweeps"] >= 2 * (depth - 2) + (iterations - 64 * 2 * (depth + 2)) // 256
+
+
 def _many_calls(n_calls, mutual, chained):
     """f(n) = n + 3 where n < 1, else the sum of k f(n - k) over k = 1 .. n_calls; mutual: f calls g, and g, the same, f;
     chained: the last call's argument is n - 2 plus what the first one returns times 0, so it is ready later than the others."""
