@@ -13,12 +13,12 @@
 #include "die_sync.h"
 #include "engine.h"
 #include "lane_device.h"
+#include "unwritten.h"
 
 namespace tdf {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;   // one 16-byte chunk
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 namespace {
@@ -425,28 +425,14 @@ template <typename T, int MODE> void launch_gemm(GemmArgs g, int n_tiles_n, int 
 // k-values feeds four 16x16x4 products, component j of both operands in product j (a fixed permutation of the
 // reduction index).
 template <typename T> struct Chunk;
-template <> struct Chunk<__bf16> {
+template <> struct Chunk<__bf16> : Unwritten<__bf16> {
   static constexpr int KC = 32;   // reduction indices covered by one chunk step of a wave
   static constexpr int EPC = 8;   // elements per chunk
   static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   }
-  // Elements that have not been written yet hold the pattern 0xFFFF (below: announce): whether chunks hold one follows from the
-  // greatest elements of their words' halves.  (One instruction a word; the compiler, if it sees the comparison behind the
-  // maxima, compares every half.)
-  static __device__ __forceinline__ uint32_t greatest(uint32_t m, u32x4 c) {
-    typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
-    const uint32_t x = c.x, y = c.y, z = c.z, w = c.w;   // (a bit cast of a vector's component itself is the first one's, whichever it names)
-    const u16x2 a = __builtin_elementwise_max(__builtin_bit_cast(u16x2, x), __builtin_bit_cast(u16x2, y));
-    const u16x2 b = __builtin_elementwise_max(__builtin_bit_cast(u16x2, z), __builtin_bit_cast(u16x2, w));
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m), __builtin_elementwise_max(a, b)));
-  }
-  static __device__ __forceinline__ bool waiting(uint32_t m) {
-    asm("" : "+v"(m));
-    return ((0xFFFEFFFEu - m) & m & 0x80008000u) != 0;   // (a half of ~m is zero)
-  }
 };
-template <> struct Chunk<float> {
+template <> struct Chunk<float> : Unwritten<float> {
   static constexpr int KC = 16;
   static constexpr int EPC = 4;
   static __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
@@ -456,11 +442,6 @@ template <> struct Chunk<float> {
     c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, y.z, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, y.w, c, 0, 0, 0);
     return c;
-  }
-  static __device__ __forceinline__ uint32_t greatest(uint32_t m, u32x4 c) { return max(max(max(m, c.x), c.y), max(c.z, c.w)); }
-  static __device__ __forceinline__ bool waiting(uint32_t m) {
-    asm("" : "+v"(m));
-    return m == 0xFFFFFFFFu;
   }
 };
 

@@ -15,6 +15,9 @@
 #include "engine.h"
 #include "lane_device.h"
 #include "tdf_internal.h"
+#ifdef TDF_TEST_HOOKS
+#include "unwritten.h"
+#endif
 
 namespace tdf {
 
@@ -1238,3 +1241,24 @@ extern "C" tdf_status tdf_eval_static(tdf_graph* g, const tdf_inputs* in, tdf_ou
   }
   return run(g, in, nullptr, out, nullptr, ptr, TDF_STATIC_WORKSPACE_BYTES, hip_stream, stats, false, locks, 0, true);
 }
+
+#ifdef TDF_TEST_HOOKS
+// Whether any of the n_chunks chunks of row i, of n rows, holds an element that has not been written.
+namespace tdf {
+template <typename T> __global__ void k_test_unwritten(const u32x4* chunks, uint32_t n_chunks, uint32_t n, int32_t* out) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  uint32_t m = 0;
+  for (uint32_t k = 0; k < n_chunks; ++k) m = Unwritten<T>::greatest(m, chunks[(size_t)i * n_chunks + k]);
+  out[i] = Unwritten<T>::waiting(m) ? 1 : 0;
+}
+}  // namespace tdf
+extern "C" tdf_status tdf_test_unwritten(int dtype, const void* chunks, uint32_t n_chunks, uint32_t n, int32_t* out, void* hip_stream) {
+  if (!chunks || !out || !n || !n_chunks || (dtype != TDF_BF16 && dtype != TDF_F32)) return TDF_ERR_BAD_ARG;
+  const dim3 grid((n + 255) / 256), block(256);
+  const tdf::u32x4* c = (const tdf::u32x4*)chunks;
+  if (dtype == TDF_BF16) hipLaunchKernelGGL(tdf::k_test_unwritten<__bf16>, grid, block, 0, (hipStream_t)hip_stream, c, n_chunks, n, out);
+  else hipLaunchKernelGGL(tdf::k_test_unwritten<float>, grid, block, 0, (hipStream_t)hip_stream, c, n_chunks, n, out);
+  return hipGetLastError() == hipSuccess ? TDF_OK : TDF_ERR_DEVICE;
+}
+#endif

@@ -266,3 +266,9 @@ def test_the_lanes_need_no_memory_beside_the_step_machines(case):
     g = tdf.graph_build(*prog, want_grad=grad)
     with_lanes, without = (tdf.workspace_size(g, tdf.make_inputs(stats_level=level, **k), grad) for level in (0, 1))
     assert with_lanes <= 1.07 * without, (with_lanes, without)
+
+
+def test_the_product_library_has_no_kernel_for_tests():
+    here = os.path.dirname(tdf.__file__)
+    product, hooks = (open(os.path.join(here, n), "rb").read() for n in ("libtdf.so", "libtdf_hooks.so"))
+    assert b"tdf_test_" not in product and b"k_test_" not in product and b"tdf_test_unwritten" in hooks
