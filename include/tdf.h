@@ -249,7 +249,7 @@ typedef struct {
 enum {
   TDF_PHASE_TAGS = 0,    /* the step machine (clear, seed, all match/fire steps) or the walk
                             over the forest or the lanes (clear and weight packing, then
-                            one launch)                                                    */
+                            one launch; two where what is no piece is walked apart)        */
   TDF_PHASE_LEAVES,      /* EMBED rows (after the step machine: and weight packing)        */
   TDF_PHASE_LEVELS,      /* bucketing of the cell firings by dependency level              */
   TDF_PHASE_CELLS_FWD,   /* cell GEMMs of the wide levels, one launch per level; where deep
@@ -269,13 +269,15 @@ enum {
 enum {
   TDF_TAGS_STEP_MACHINE = 0, /* match/fire steps over a frame table                        */
   TDF_TAGS_LANES,            /* the depth-first lanes                                      */
-  TDF_TAGS_WALK              /* a walk over the forest                                     */
+  TDF_TAGS_WALK              /* a walk over the forest, or trees that lie in one piece      */
 };
 
 typedef struct {
   int64_t n_tags;         /* tags created = function invocations + loop iterations      */
   int64_t n_steps;        /* match/fire steps of the tag machine; on the lanes the most sweeps
-                             of one of their waves, on the walk those of its longest wave */
+                             of one of their waves, on the walk those of its longest wave; a
+                             tree that lies in one piece of memory is not walked and has the
+                             rounds in which its heights are found, 14 at most            */
   int64_t n_tokens;       /* Call and Return tokens delivered                           */
   int64_t n_leaf_rows;    /* EMBED firings                                              */
   int64_t n_cell_rows;    /* RNN_CELL / LSTM_CELL firings                               */
@@ -294,7 +296,8 @@ typedef struct {
                              the records in use at once and the frames on a lane's stack, the
                              largest number of every wave and lane summed, n_tags at most; on
                              the walk, which has no frames, the nodes that wait on a wave's stack
-                             (512 at most) and its 64 lanes, summed likewise            */
+                             (512 at most) and its 64 lanes, summed likewise, and for a tree
+                             that lies in one piece all its nodes, which are held at once */
   int64_t frames_reclaimed; /* 1: frames were given back as their tags finished (always so on
                              the lanes and the walk)                                   */
   double phase_ms[TDF_PHASE_COUNT];        /* device time of each phase                */

@@ -426,3 +426,13 @@ def test_forests_in_random_order(size):
     rng = np.random.default_rng(12)
     stats = _same(programs.tree("lstm", True), _trees([_chain(300), _complete(5)] + BESIDE[size](rng), rng))[3]
     assert stats.n_steps > 300
+
+
+def test_what_the_statistics_say_of_pieces_and_walks():
+    # include/tdf.h: the rounds of doubling and all nodes for trees in one piece, a wave's steps and its stack for trees that are walked
+    rng = np.random.default_rng(13)
+    shapes = [_chain(200), _complete(6), _random(90, rng)]
+    piece = _same(programs.tree("lstm", True), _in_pieces(shapes, "depth", rng))[3]
+    assert 2 ** piece.n_steps < 200 <= 2 ** (piece.n_steps + 1) and piece.peak_frames == piece.n_tags   # (200: the chain's height)
+    walk = _same(programs.tree("lstm", True), _trees(shapes, rng))[3]
+    assert walk.n_steps >= 200 and 64 * len(shapes) <= walk.peak_frames <= (512 + 64) * len(shapes)
