@@ -798,9 +798,12 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   typedef Tile<MODE> TL;
-  // Chunk steps in flight, of which LEAST are there for sure.  Four where they are fetched as they are needed: all that a wave of a
-  // TreeLSTM of 256 units or a TreeRNN of 512 has (the gradient tail of a TreeLSTM of 256 units, 32 levels: 246 us with three, 189).
-  constexpr int BATCH = RES > 0 ? RES : 4, LEAST = least_steps(RES);
+  // Chunk steps in flight, of which LEAST are there for sure.  Where the weights are fetched as they are needed four, all that a wave of a
+  // TreeLSTM of 256 units or a TreeRNN of 512 has (14 levels launched one by one, forward: 120 and 120 us with three, 118 and 118;
+  // TreeLSTM of 512 135 and 132), but three where rows are waited for: with more the compiler waits between the loads of a look, and
+  // without that (a step that is not there being the last one once more) it costs as much.  500 levels of a TreeRNN of 1,280 units,
+  // forward and gradient, two / three / four / five: 10.3, 9.8, 11.1, 11.3 ms; of a TreeLSTM of 640 12.9, 12.9, 13.8, 14.2.
+  constexpr int BATCH = RES > 0 ? RES : WAIT ? 3 : 4, LEAST = least_steps(RES);
   const int lane = threadIdx.x & 63, n = c.n, s0 = c.s0, wave = c.wave;
   const bool valid = (lane >> 2) < t.M;
   const T* Ap;

@@ -65,7 +65,8 @@ def code(objects):
         for body in re.split(r"^[0-9a-f]+ <", text, flags=re.M)[1:]:
             name = re.match(r"\S*?(k_tail_fwd|k_tail_bwd|k_cell_small)((?:IL|EL)\S+?)EEEv", body)
             if name:
-                got[(name.group(1),) + tuple(int(x) for x in re.findall(r"L[ib](\d+)", name.group(2)))] = [i.split()[0] for i in body.splitlines()[1:] if i.strip()]
+                args = tuple(int(x) for x in re.findall(r"L[ib](\d+)", name.group(2)))
+                got[(name.group(1),) + args] = [" ".join(i.split()[:2]) if "s_waitcnt" in i else i.split()[0] for i in body.splitlines()[1:] if i.strip()]
     return got
 
 
@@ -95,3 +96,13 @@ def test_a_walk_holds_no_more_than_its_stack(objects):
                 sizes.setdefault(name.group(1), []).append(one)
     assert len(sizes["k_forest_pieces"]) == 3
     assert all(threads == 64 and lds <= 160 * 1024 // 26 for threads, lds in sizes["k_forest_walk"])
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("kernel", [("k_tail_fwd", 0, 0, 1), ("k_tail_fwd", 1, 0, 1), ("k_tail_bwd", 1, 0), ("k_tail_bwd", 2, 0)], ids=str)
+def test_a_look_asks_for_all_its_rows_before_it_waits(code, kernel, dtype):
+    """Where the weights are fetched for every tile; three steps of the reduction a look."""
+    order = "".join("L" if i == "buffer_load_dwordx4" else "w" for i in code[kernel[:1] + (dtype,) + kernel[1:]]
+                    if i == "buffer_load_dwordx4" or i == "s_waitcnt vmcnt(0)")
+    looks = [len(x) for x in order.split("w") if x]
+    assert looks and all(n % 3 == 0 for n in looks)
