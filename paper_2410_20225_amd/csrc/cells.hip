@@ -601,11 +601,12 @@ template <int MODE> struct TileRows {
   uint32_t z_q, z_gl, z_gr;         // fused dz: the child cell (none: all ones) and its children's rows
 };
 // LOOK: a tile that is not its workgroup's first of a level reads rows that are likely there already: the tile before looks
-// for them while it sums and finishes.  Gradient tails of a TreeLSTM, whose workgroups are alone on a compute unit and have several
-// tiles a level (127 levels of up to 80 cells a die beside the level launches: 1,430 us without, 1,200); the other tails, two
-// workgroups a compute unit or a tile a level, gain nothing.
-template <typename T, int MODE, int RES, int CELL> struct TileAhead {
-  static constexpr bool LOOK = CELL == 2 && RES == 5;
+// for them while it sums and finishes.  For gradient tails of a TreeLSTM whose workgroups have more than one tile of a level on average; a tile
+// that is the only one of its level is slower for it.  us of 199 levels of 8, 128, 160, 256 and 512 cells, 256 units, without and
+// with: 344 and 377, 405 and 421, 850 and 818, 915 and 864, 1,855 and 1,657; 14 levels of sentences, 50, 200 and 300 of them, 150 units (two
+// tiles side by side): 44 and 46, 71 and 72, 66 and 64.  127 levels of up to 80 cells a die beside the level launches: 1,430 and 1,195.
+template <typename T, int MODE, int RES, int CELL, bool LOOKS> struct TileAhead {
+  static constexpr bool LOOK = LOOKS;
   u32x4 look[LOOK ? RES : 1];
   uint32_t look_u0;
   bool looked;   // (uniform)
@@ -642,9 +643,9 @@ __device__ __forceinline__ void tile_rows2(const GemmArgs& g, const TileLane& c,
     }
   }
 }
-template <int DT, int MODE, int RES, int CELL>
+template <int DT, int MODE, int RES, int CELL, class Ahead>
 __device__ __forceinline__ void tile_ahead(const GemmArgs& g, const TileLane& c, const TileAt& t, const DzFuse* fz, const TileRows<MODE>& p,
-                                           TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& q) {
+                                           Ahead& q) {
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   const int lane = threadIdx.x & 63;
@@ -790,9 +791,9 @@ template <class F> __device__ __forceinline__ bool wait_rows(const TailWait& w, 
 // From the tile's stores to the next tile's first look there is no wait for anything: row numbers are two looks old, and
 // each look is waited for with all that was asked for before it.  (The compiler has to see that: branches are uniform or around
 // loads alone.)
-template <int DT, int MODE, int RES, int CELL, bool WAIT, bool NARROW, class Look, class Request>
+template <int DT, int MODE, int RES, int CELL, bool WAIT, bool NARROW, class Ahead, class Look, class Request>
 __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLane& c, const TileAt& t, float* part, u32x4* turns, const TileRows<MODE>& p,
-                                                TileAhead<typename TypeOf<DT>::type, MODE, RES, CELL>& q, const float (&bias)[Tile<MODE>::G],
+                                                Ahead& q, const float (&bias)[Tile<MODE>::G],
                                                 const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, const TailWait& w, uint32_t* failed,
                                                 Look look, Request request) {
   typedef typename TypeOf<DT>::type T;
@@ -837,7 +838,7 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
         return !still_open();
       };
       bool there = false;
-      if constexpr (TileAhead<T, MODE, RES, CELL>::LOOK) {
+      if constexpr (Ahead::LOOK) {
         if (q.looked) {
 #pragma unroll
           for (int st = 0; st < RES; ++st) fa[st] = q.look[st];
@@ -987,7 +988,7 @@ __global__ void __launch_bounds__(Tile<MODE>::NW * 64) k_cell_small(GemmArgs g) 
   const int rt = blockIdx.x / g.n_tiles_n, ct = blockIdx.x % g.n_tiles_n;   // (column tiles of one row tile side by side)
   const TileAt t{(uint32_t)rt * Tile<MODE>::ROWS, min(Tile<MODE>::ROWS, g.M - rt * Tile<MODE>::ROWS), ct, 0};
   TileRows<MODE> p;
-  TileAhead<typename TypeOf<DT>::type, MODE, 0, 0> q;
+  TileAhead<typename TypeOf<DT>::type, MODE, 0, 0, false> q;
   const TileLane c = tile_lane<DT, MODE>(g);
   tile_rows<MODE>(g, c, t, p);
   tile_ahead<DT, MODE, 0, 0>(g, c, t, nullptr, p, q);
@@ -1356,12 +1357,12 @@ struct TailArgs {
 // that goes ahead 6.5 and 6.4; no wait between a tile's stores and the next look 6.2 and 6.4; rows loaded 64 bytes at a time 5.4
 // and 6.0; no conversions of what was just requested 5.4 and 5.3; the marks of dz in 16-byte stores 5.2 and 5.0.  127 levels of a TreeLSTM of
 // 256 units beside the level launches: 0.94 and 1.40, now 0.75 and 1.25.
-template <int DT, int MODE, int RES, int CELL, bool NARROW>
+template <int DT, int MODE, int RES, int CELL, bool NARROW, bool LOOK>
 __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& ta, uint32_t die, uint32_t rank, uint32_t G, float* part, u32x4* turns,
                                             const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, uint32_t* failed) {
   typedef Tile<MODE> TL;
   typedef typename TypeOf<DT>::type T;
-  typedef TileAhead<T, MODE, RES, CELL> Ahead;
+  typedef TileAhead<T, MODE, RES, CELL, LOOK> Ahead;
   DieSync* const sy = ta.sync + die;
   const TailWait w{sy, ta.spin_ticks};
   const uint32_t n_ct = (uint32_t)g.n_tiles_n;
@@ -1434,7 +1435,7 @@ __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& t
     // (The end of the program, not a way out of the loop: the compiler joins such ways, with copies and waits where they meet.)
     if (!t.M) __builtin_amdgcn_endpgm();
     const bool ok = cell_small_tile<DT, MODE, RES, CELL, true, NARROW>(g, c, t, part + side * TL::PART, turns, p, a, RES > 0 ? bias : a.bias, b, fz, w, failed + side, [&] {
-      if constexpr (Ahead::LOOK) {
+      if constexpr (LOOK) {
         a1.looked = ta1.M && ta1.lvl == t.lvl;
         if (a1.looked) {
           const auto tw = tile_waits<DT, MODE, CELL>(g, c, ta1, pa1, fz);
@@ -1595,13 +1596,13 @@ k_tail_fwd(GemmArgs g, TailArgs t) {
     }
   }
   if (!die_meet(sy, G, t.spin_ticks, &sh_ok)) return;
-  walk_levels<DT, MODE, RES, 0, NARROW>(g, t, die, rank, G, part, turns, &b, nullptr, failed);
+  walk_levels<DT, MODE, RES, 0, NARROW, false>(g, t, die, rank, G, part, turns, &b, nullptr, failed);
 }
 
 // Gradient pass over the same levels, deepest first.  (dz of a level's cells: from their parents' tiles, or, for the
 // roots, from k_dz_tail_roots.  Those that come from tiles were marked as not written by k_tail_fwd.)
-template <int DT, int CELL, int RES>
-__global__ void __launch_bounds__(Tile<DX_BWD>::NW * 64, CELL == 1 && RES == 5 ? 4 : 2) k_tail_bwd(GemmArgs g, VecArgs v, Engine e, TailArgs t) {
+template <int DT, int CELL, int RES, bool LOOK>
+__device__ __forceinline__ void tail_bwd(const GemmArgs& g, const VecArgs& v, const Engine& e, const TailArgs& t) {
   typedef typename TypeOf<DT>::type T;
   typedef Tile<DX_BWD> TL;
   __shared__ __attribute__((aligned(16))) float part[2 * TL::PART];
@@ -1621,7 +1622,14 @@ __global__ void __launch_bounds__(Tile<DX_BWD>::NW * 64, CELL == 1 && RES == 5 ?
     load_b<DT, DX_BWD, RES>(g, (int)(rank % (uint32_t)g.n_tiles_n), s0, TL::first_step(steps, wave + 1) - s0, b);
   }
   if (!die_meet(sy, G, t.spin_ticks, &sh_ok)) return;
-  walk_levels<DT, DX_BWD, RES, CELL, true>(g, t, die, rank, G, part, turns, &b, &fz, failed);
+  walk_levels<DT, DX_BWD, RES, CELL, true, LOOK>(g, t, die, rank, G, part, turns, &b, &fz, failed);
+}
+template <int DT, int CELL, int RES>
+__global__ void __launch_bounds__(Tile<DX_BWD>::NW * 64, CELL == 1 && RES == 5 ? 4 : 2) k_tail_bwd(GemmArgs g, VecArgs v, Engine e, TailArgs t) {
+  tail_bwd<DT, CELL, RES, false>(g, v, e, t);
+}
+template <int DT> __global__ void __launch_bounds__(Tile<DX_BWD>::NW * 64, 2) k_tail_bwd_look(GemmArgs g, VecArgs v, Engine e, TailArgs t) {
+  tail_bwd<DT, 2, 5, true>(g, v, e, t);
 }
 
 // ---- numbering of the state rows by the sorted schedule ------------------------------------------
@@ -2258,16 +2266,20 @@ static void launch_tail_bwd(const GemmArgs& g, const VecArgs& v, const Engine& e
   hipLaunchKernelGGL((k_tail_bwd<DtOf<T>::value, CELL, RES>), grid, block, 0, s, g, v, e, t);
 }
 template <typename T, int CELL>
-static void tail_bwd_cell(const GemmArgs& g, const VecArgs& v, const Engine& e, const TailArgs& t, int cus_per_die, uint32_t row_tiles,
-                          hipStream_t s) {
+static void tail_bwd_cell(const GemmArgs& g, const VecArgs& v, const Engine& e, const TailArgs& t, uint32_t n_cells, int cus_per_die,
+                          uint32_t row_tiles, hipStream_t s) {
   const int n = Tile<DX_BWD>::steps_most(g.K / Chunk<T>::KC);
   const int wgs = tail_wgs(tail_slots_bwd(cus_per_die, n, CELL), g.n_tiles_n, row_tiles);
-  if (wgs && n <= 5) launch_tail_bwd<T, CELL, 5>(g, v, e, t, wgs, s);
+  // (more than one row of tiles a level and group of workgroups on average: see TileAhead)
+  const uint64_t one_each = (uint64_t)(t.lvl_last + 1 - t.lvl_first) * t.n_dies * Tile<DX_BWD>::ROWS * (uint64_t)(wgs / g.n_tiles_n);
+  if (CELL == 2 && wgs && n <= 5 && n_cells > one_each)
+    hipLaunchKernelGGL(k_tail_bwd_look<DtOf<T>::value>, dim3((wgs + 1) * (int)XCDS), dim3(Tile<DX_BWD>::NW * 64), 0, s, g, v, e, t);
+  else if (wgs && n <= 5) launch_tail_bwd<T, CELL, 5>(g, v, e, t, wgs, s);
   else if (wgs && n <= 10) launch_tail_bwd<T, CELL, 10>(g, v, e, t, wgs, s);
   else launch_tail_bwd<T, CELL, 0>(g, v, e, t, cus_per_die, s);
 }
-template <typename T> static void tail_bwd_t(const VecArgs& v, const Engine& e, const TailArgs& t, int per_die, uint32_t row_tiles,
-                                             hipStream_t s) {
+template <typename T> static void tail_bwd_t(const VecArgs& v, const Engine& e, const TailArgs& t, uint32_t n_cells, int per_die,
+                                             uint32_t row_tiles, hipStream_t s) {
   GemmArgs g{};
   g.N = v.Kp; g.K = v.Np;
   g.A = v.Dz; g.lda = v.Np;
@@ -2275,8 +2287,8 @@ template <typename T> static void tail_bwd_t(const VecArgs& v, const Engine& e, 
   g.Hp = v.Hp; g.l = e.q_l; g.r = e.q_r;
   g.C = v.dH;
   g.n_tiles_n = v.Kp / Tile<DX_BWD>::UNITS;
-  if (v.cell_kind == 2) tail_bwd_cell<T, 2>(g, v, e, t, per_die, row_tiles, s);
-  else tail_bwd_cell<T, 1>(g, v, e, t, per_die, row_tiles, s);
+  if (v.cell_kind == 2) tail_bwd_cell<T, 2>(g, v, e, t, n_cells, per_die, row_tiles, s);
+  else tail_bwd_cell<T, 1>(g, v, e, t, n_cells, per_die, row_tiles, s);
 }
 // After the level sort: rows numbered by the sorted schedule, references translated.
 void vec_number_rows(const Engine& e, uint32_t n_leaf, uint32_t n_cell, int has_head, int has_root, hipStream_t s) {
@@ -2299,8 +2311,8 @@ void vec_tail_bwd(const VecArgs& v, const Engine& e, const uint32_t* level_off, 
   TailArgs t{level_off, lvl_first, lvl_last, n_dies, (DieSync*)sync, spin_ticks, q_first};
   if (v.dtype == TDF_BF16) hipLaunchKernelGGL(k_dz_tail_roots<TDF_BF16>, dim3(e.n_inst), dim3(256), 0, s, v, e, root_rows, q_first, q_first + n_cells);
   else hipLaunchKernelGGL(k_dz_tail_roots<TDF_F32>, dim3(e.n_inst), dim3(256), 0, s, v, e, root_rows, q_first, q_first + n_cells);
-  if (v.dtype == TDF_BF16) tail_bwd_t<__bf16>(v, e, t, per_die, (most_rows + 15u) / 16u, s);
-  else tail_bwd_t<float>(v, e, t, per_die, (most_rows + 15u) / 16u, s);
+  if (v.dtype == TDF_BF16) tail_bwd_t<__bf16>(v, e, t, n_cells, per_die, (most_rows + 15u) / 16u, s);
+  else tail_bwd_t<float>(v, e, t, n_cells, per_die, (most_rows + 15u) / 16u, s);
 }
 
 // cls < 0: every instance; else only the instances of that class (Engine::inst_class)

@@ -63,7 +63,7 @@ def code(objects):
     for f in objects:
         text = subprocess.run([os.path.join(TOOLS, "llvm-objdump"), "-d", "--no-show-raw-insn", f], capture_output=True, text=True).stdout
         for body in re.split(r"^[0-9a-f]+ <", text, flags=re.M)[1:]:
-            name = re.match(r"\S*?(k_tail_fwd|k_tail_bwd|k_cell_small)((?:IL|EL)\S+?)EEEv", body)
+            name = re.match(r"\S*?(k_tail_fwd|k_tail_bwd|k_tail_bwd_look|k_cell_small)((?:IL|EL)\S+?)EEEv", body)
             if name:
                 args = tuple(int(x) for x in re.findall(r"L[ib](\d+)", name.group(2)))
                 got[(name.group(1),) + args] = [" ".join(i.split()[:2]) if "s_waitcnt" in i else i.split()[0] for i in body.splitlines()[1:] if i.strip()]
@@ -79,9 +79,10 @@ def test_small_tiles_have_four_steps_of_the_reduction_in_flight(code, mode, bloc
 
 @pytest.mark.parametrize("dtype", [0, 1])
 def test_gradient_tiles_of_a_tree_lstm_look_for_the_next_ones_rows(code, dtype):
-    """Four copies of a tile's code take turns; each looks for the five chunk steps of the next one, beside its own looks."""
-    looks = [code[("k_tail_bwd", dtype, cell, 5)].count("buffer_load_dwordx4") for cell in (1, 2)]
-    assert looks[1] >= looks[0] + 4 * 5
+    """Four copies of a tile's code take turns; where a workgroup has several tiles of a level each looks for the five chunk steps of the
+    next one, beside its own looks, and where not none does."""
+    looks = [code[k].count("buffer_load_dwordx4") for k in (("k_tail_bwd", dtype, 1, 5), ("k_tail_bwd", dtype, 2, 5), ("k_tail_bwd_look", dtype))]
+    assert looks[0] == looks[1] and looks[2] >= looks[1] + 4 * 5
 
 
 def test_a_walk_holds_no_more_than_its_stack(objects):
