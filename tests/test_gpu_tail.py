@@ -56,6 +56,27 @@ def test_gradients_of_levels_of_several_tiles(hidden, trees, leaves, bf16):
             assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < tol, name
 
 
+# ... and where that is so on average of the levels, which takes the kernel that looks: cells of a level on a die in rows of
+# 16, a row for a group of workgroups, one for each column tile, of which a die's 32 compute units hold 31 workgroups.
+@pytest.mark.parametrize("hidden,trees,leaves,bf16", [(250, 300, 12, True), (180, 560, 10, True), (120, 800, 10, False)])
+def test_gradients_where_a_workgroup_has_several_tiles_of_a_level(hidden, trees, leaves, bf16):
+    c = make_config(4, n_trees=trees, max_leaves=leaves, hidden=hidden, vocab=200)
+    c["bf16"] = bf16
+    B = c["forest"].n_trees
+    dy = np.full(B, 1.0 / B)
+    ref = run_oracle_tree(c, head=True, grad=True, dy=dy)
+    run = TreeRun(c, head=True, grad=True, stats_level=0)
+    tol = 2e-2 if bf16 else 2e-5
+    for _ in range(2):
+        st, stats = run.run(dy)
+        groups = 31 // (2 * ((hidden + 63) // 64 * 64) // 32)
+        assert stats.tail_used == 1 and stats.n_wide_waves == 0 and stats.n_cell_rows > 8 * 16 * groups * stats.n_waves
+        assert stats.n_grad_not_once == 0 and stats.n_grad_firings == c["forest"].n_nodes
+        assert rel_fro(run.out_f32.cpu().numpy(), np.array(ref["out"])) < tol
+        for name, t in (("dW", run.dW), ("db", run.db), ("dE", run.dE)):
+            assert rel_fro(t.cpu().numpy(), ref["grads"][name]) < tol, name
+
+
 @pytest.mark.parametrize("cfg", [3, 4])
 def test_offsets_beyond_32_bits(cfg, monkeypatch):
     import os
