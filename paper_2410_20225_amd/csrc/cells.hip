@@ -416,8 +416,9 @@ template <typename T, int MODE> void launch_gemm(GemmArgs g, int n_tiles_n, int 
 // ---- small levels ----------------------------------------------------------------------
 // Deep in the recursion a dependency level holds few cells, and a level costs its latency.  A tile is kept small
 // for that: 16 cells x 16 hidden units x 5 gates (TreeLSTM, four waves), or 16 cells x 32 columns (TreeRNN and
-// input gradients, eight waves).  The waves split the reduction and load their MFMA operands straight from global
-// memory (no staging through LDS), the partial tiles meet in LDS, and every lane then finishes one element.
+// input gradients, eight waves).  The waves split the reduction and load their own operands (weights in operand order, straight
+// to registers; rows turned into it through the wave's kilobyte of LDS: turn), the partial tiles meet in LDS, and every lane then
+// finishes one element.
 // Against the 32 x 32 tile that this one replaced, a wave multiplies a quarter as long (20 products of 16 clocks
 // instead of 40 of 32 for a TreeLSTM of 256 units), a quarter as much goes through LDS, and a lane has one
 // element's gates to compute instead of four in a row.
@@ -600,11 +601,12 @@ template <int MODE> struct TileRows {
   uint32_t o_l, o_r;                // children of the lane's element
   uint32_t z_q, z_gl, z_gr;         // fused dz: the child cell (none: all ones) and its children's rows
 };
-// LOOK: a tile that is not its workgroup's first of a level reads rows that are likely there already: the tile before looks
-// for them while it sums and finishes.  For gradient tails of a TreeLSTM whose workgroups have more than one tile of a level on average; a tile
-// that is the only one of its level is slower for it.  us of 199 levels of 8, 128, 160, 256 and 512 cells, 256 units, without and
-// with: 344 and 377, 405 and 421, 850 and 818, 915 and 864, 1,855 and 1,657; 14 levels of sentences, 50, 200 and 300 of them, 150 units (two
-// tiles side by side): 44 and 46, 71 and 72, 66 and 64.  127 levels of up to 80 cells a die beside the level launches: 1,430 and 1,195.
+// LOOK: a tile that is not its workgroup's first of a level reads rows that are likely there already: the tile before looks for
+// them while it sums and finishes.  For gradient tails of a TreeLSTM whose workgroups have more than one tile of a level on average;
+// a tile that is the only one of its level is slower for it.  us of 199 levels of 8, 128, 160, 256 and 512 cells, 256 units,
+// without and with: 344 and 377, 405 and 421, 850 and 818, 915 and 864, 1,855 and 1,657; 14 levels of 50, 200 and 300 sentences, 150
+// units (two tiles side by side): 44 and 46, 71 and 72, 66 and 64.  127 levels of up to 80 cells a die beside the level launches:
+// 1,430 and 1,195.
 template <typename T, int MODE, int RES, int CELL, bool LOOKS> struct TileAhead {
   static constexpr bool LOOK = LOOKS;
   u32x4 look[LOOK ? RES : 1];
@@ -799,11 +801,11 @@ __device__ __forceinline__ bool cell_small_tile(const GemmArgs& g, const TileLan
   typedef typename TypeOf<DT>::type T;
   typedef Chunk<T> C;
   typedef Tile<MODE> TL;
-  // Chunk steps in flight, of which LEAST are there for sure.  Where the weights are fetched as they are needed four, all that a wave of a
-  // TreeLSTM of 256 units or a TreeRNN of 512 has (14 levels launched one by one, forward: 120 and 120 us with three, 118 and 118;
-  // TreeLSTM of 512 135 and 132), but three where rows are waited for: with more the compiler waits between the loads of a look, and
-  // without that (a step that is not there being the last one once more) it costs as much.  500 levels of a TreeRNN of 1,280 units,
-  // forward and gradient, two / three / four / five: 10.3, 9.8, 11.1, 11.3 ms; of a TreeLSTM of 640 12.9, 12.9, 13.8, 14.2.
+  // Chunk steps in flight, of which LEAST are there for sure.  Where the weights are fetched as they are needed four, all that a
+  // wave of a TreeLSTM of 256 units or a TreeRNN of 512 has (14 levels launched one by one, forward: both 120 us with three, 118;
+  // TreeLSTM of 512 135 and 132), but three where rows are waited for: with more the compiler waits between the loads of a look,
+  // and without that (a step that is not there being the last one once more) it costs as much.  500 levels of a TreeRNN of 1,280
+  // units, forward and gradient, two / three / four / five: 10.3, 9.8, 11.1, 11.3 ms; of a TreeLSTM of 640 12.9, 12.9, 13.8, 14.2.
   constexpr int BATCH = RES > 0 ? RES : WAIT ? 3 : 4, LEAST = least_steps(RES);
   const int lane = threadIdx.x & 63, n = c.n, s0 = c.s0, wave = c.wave;
   const bool valid = (lane >> 2) < t.M;
@@ -1356,7 +1358,7 @@ struct TailArgs {
 // of 32 x 32 11.4 and 15.0; rows that announce themselves 7.4 and 6.5; the rows to be written brought to the L2 by the workgroup
 // that goes ahead 6.5 and 6.4; no wait between a tile's stores and the next look 6.2 and 6.4; rows loaded 64 bytes at a time 5.4
 // and 6.0; no conversions of what was just requested 5.4 and 5.3; the marks of dz in 16-byte stores 5.2 and 5.0.  127 levels of a TreeLSTM of
-// 256 units beside the level launches: 0.94 and 1.40, now 0.75 and 1.25.
+// 256 units beside the level launches: 0.93 and 1.35 with rows in operand order, now 0.85 and 1.20.
 template <int DT, int MODE, int RES, int CELL, bool NARROW, bool LOOK>
 __device__ __forceinline__ void walk_levels(const GemmArgs& g, const TailArgs& ta, uint32_t die, uint32_t rank, uint32_t G, float* part, u32x4* turns,
                                             const TileB<MODE, (RES > 0 ? RES : 1)>* b, const DzFuse* fz, uint32_t* failed) {
@@ -1557,7 +1559,7 @@ __device__ __forceinline__ void tail_begin(DieSync* sy, uint32_t* failed) {
 // Workgroups of eight waves that share a compute unit with another of their kind have two waves each on a SIMD.  Four times 128
 // registers would fill it, and a wave of a small kernel on another stream (the token sort: 16 registers) that happens to be there
 // when they are placed leaves a hole that the fourth never fits into: the compute unit holds one workgroup for good, and the
-// others wait for it until the launch gives up.  So these should take at most 112 (TreeRNN forward 102 to 109, gradient 107); the
+// others wait for it until the launch gives up.  So these should take at most 112 (TreeRNN forward 102 and 105, gradient 107); the
 // variants that take more, of which one fetches its weights for every tile, have a compute unit to themselves.
 template <int DT, int MODE, int RES, bool NARROW>
 __global__ void __launch_bounds__(Tile<MODE>::NW * 64, MODE == LSTM_FWD ? (RES == 8 ? 1 : 2) : (RES == 2 || RES == 4 ? 4 : 2))

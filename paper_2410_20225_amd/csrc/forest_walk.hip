@@ -508,14 +508,15 @@ template <int THREADS, int WINDOW> static void launch_pieces(const LaneArgs& a, 
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_forest_pieces<THREADS, WINDOW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL((k_forest_pieces<THREADS, WINDOW>), dim3(a.n_inst), dim3(THREADS), lds, s, a, w, walks, st);
 }
-// The workgroup and its window by the nodes of an instance on average: room for a few times as many, where that leaves a compute unit enough
-// instances to work on.  Number of launches.
+// The workgroup and its window by the nodes of an instance on average: room for a few times as many, where that leaves a compute
+// unit enough instances to work on.  Number of launches.
 // What is no piece is walked in workgroups of 64 threads and 6 KB, 26 of which fit a compute unit, in a launch of its own: one
 // wave would hold the 32 or 128 KB of a piece (five or one on a compute unit) for as long as it walks.  In random order, all in
 // one launch -> two, tag phase in us: 512 chains of 3,500 leaves 10,190 -> 5,070, 512 random trees of 3,500 567 -> 463, 2,048 of
-// 600 550 -> 348, 4,096 of 800 1,316 -> 852 (1,024 of 300 leaves, five a compute unit at once: 87 -> 102).  Up to two instances of 32 KB a compute unit all are resident anyway and leave room for
-// two workgroups of another evaluation's level tails (90 KB), and the second launch is only in the way: 256 trees of up to 50
-// leaves 14 -> 20 us in order, 30 -> 39 in random order, 200 of 400 21 -> 24 and 68 -> 79.
+// 600 550 -> 348, 4,096 of 800 1,316 -> 852 (1,024 of 300 leaves, five a compute unit at once: 87 -> 102).  Up to two instances of
+// 32 KB a compute unit all are resident anyway and leave room for two workgroups of another evaluation's level tails (90 KB),
+// and the second launch is only in the way: 256 trees of up to 50 leaves 14 -> 20 us in order, 30 -> 39 in random order, 200 of
+// 400 21 -> 24 and 68 -> 79.
 int launch_forest_walk(const LaneArgs& a, const WalkForm& w, const Stamp& st, hipStream_t s) {
   const uint32_t average = (uint32_t)a.n_tree_nodes / a.n_inst;
   const bool large = average > 1024u, small = average <= 192u && a.n_inst > 256u;

@@ -60,10 +60,10 @@ constexpr uint32_t LANE_EARLY = 48;     // sweeps during which a wave gives work
 // idle lanes up to which a wave gives calls to other waves
 constexpr uint32_t LANE_GIVE = 56;
 // Iterations of a loop without calls in one sweep (multiples of four): where no lane of the wave has anything else to do, and
-// beside others, which wait for the sweep's end.  A sweep costs as much as tens of iterations (of subtractive gcd, 80 clocks each):
-// 65,536 gcds of pairs up to 1,024 take 102 us with 64 a sweep, 97 with 128 and 96 with 256.  A recursion whose 4,096 leaves are loops of 1
-// to 651 iterations takes 230 us with 64, 232 with 128, 250 with 256 and 230 with this; 64 of 256 such leaves 157, 162, 170 and 157; with
-// loops of 1 to 4,096, of which few are long, 370, 337, 321 and 323.
+// beside others, which wait for the sweep's end.  A sweep costs as much as tens of iterations (of subtractive gcd, 80 clocks
+// each): 65,536 gcds of pairs up to 1,024 take 102 us with 64 a sweep, 97 with 128 and 96 with 256.  A recursion whose 4,096 leaves
+// are loops of 1 to 651 iterations takes 230 us with 64, 232 with 128, 250 with 256 and 230 with this; 64 of 256 such leaves 157,
+// 162, 170 and 157; with loops of 1 to 4,096, of which few are long, 370, 337, 321 and 323.
 constexpr uint32_t LANE_LOOP = 256, LANE_LOOP_BESIDE = 64;
 constexpr uint32_t LANE_RECS = 96;      // records of a wave
 constexpr uint32_t LANE_SCARCE = 8, LANE_FEW = 16;   // free records below which all frames below a given one take one; else the first so many take one each
