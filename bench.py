@@ -268,7 +268,7 @@ def main():
                      "how": "one host thread, graph, workspace and stream per evaluation in flight; the library runs an "
                             "evaluation's tag machine (which depends on the trees only) beside the previous evaluation's "
                             "data plane; every evaluation is complete"}
-    # which tag phase it was (the walk and the depth-first lanes are one launch behind the one that clears)
+    # which tag phase it was (the depth-first lanes are one launch behind the one that clears, the walk one or two)
     tag_phase = {tdf.TAGS_STEP_MACHINE: "step machine", tdf.TAGS_LANES: "depth-first lanes", tdf.TAGS_WALK: "walk over the forest"}[int(st.tag_phase)]
     on_lanes = int(st.tag_phase) != tdf.TAGS_STEP_MACHINE
     # one more evaluation, outside the timed region, with the tag machines' step records switched on
@@ -298,7 +298,7 @@ def main():
         # (16 B a leaf or cell).  What bounds it is the chain of dependent calls or nodes, not these bytes.
         tag_bytes = (8.0 * (len(ns) * 2 if cfg == 1 else n_inst * 3) if cfg in (1, 6) else
                      12.0 * c["forest"].n_nodes + 16.0 * int(st.n_leaf_rows + st.n_cell_rows) + 8.0 * 2 * B)
-        roof_tags = {"bound": "latency", "kernel": tag_phase + " (one launch)", "tags_per_us": n_tags / (tag_ms * 1e3)}
+        roof_tags = {"bound": "latency", "kernel": tag_phase + (" (one launch)" if int(st.phase_launches[0]) == 2 else " (two launches)"), "tags_per_us": n_tags / (tag_ms * 1e3)}
     else:
         # step machine: algorithmic bytes per tag of matching + compaction (table entry and frame record
         # written, frame read on return, operand slot, arrival word, ready id, schedule-log entry): 72 B
